@@ -73,10 +73,10 @@ enum { DGC_DTYPE_F32 = 0, DGC_DTYPE_BF16 = 1 };
  *           through the packed local column ids. */
 enum { DGC_GATHER_IN_PLACE = 0, DGC_GATHER_STAGED = 1 };
 /* Which kernel runs the dense transform + time encoder:
- *  AUTO  the wave-private kernel where it applies, else the workgroup-tile kernel;
- *  TILE  64 vertices per workgroup, operands shared through LDS (any S, H up to 256);
- *  WAVE  32 vertices per wavefront, hidden state kept in registers, no barriers
- *        (S = H in {32, 64, 128}); DGC_ERR_UNSUPPORTED at forward otherwise. */
+ *  AUTO  the split kernels where they are built (S = H, or a transform alone), else the workgroup-tile kernel;
+ *  TILE  64 vertices per workgroup, operands shared through LDS, fp32 matrix instructions (any S, H up to 256);
+ *  WAVE  the split kernels: 32 vertices per workgroup, fp32 products as sums of bf16 products, for
+ *        S = H in {32, 64, 128} (a transform alone: 256, too); DGC_ERR_UNSUPPORTED at forward otherwise. */
 enum { DGC_DENSE_AUTO = 0, DGC_DENSE_TILE = 1, DGC_DENSE_WAVE = 2 };
 /* Which kernels aggregate in IN_PLACE mode (STAGED always takes WALK):
  *  TABLE  kernels that read a per-non-zero table built at create (8 bytes per stored non-zero: the column,

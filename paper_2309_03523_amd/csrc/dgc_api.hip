@@ -16,7 +16,8 @@ thread_local std::string g_create_error = "";
 
 struct Param {
   float* raw = nullptr;       // device, [n_out][n_in] or [n]
-  float4* packed = nullptr;   // device, fragment order (weights only)
+  float4* packed = nullptr;   // device, fragment order (weights only): fp32, or three bf16 parts if split
+  bool split = false;
   int32_t n_out = 0, n_in = 0;  // n_in = 0: a bias vector of n_out elements
   int64_t numel() const { return n_in ? (int64_t)n_out * n_in : n_out; }
 };
@@ -48,8 +49,10 @@ struct dgc_layer {
   Segment* d_segs = nullptr;
   ChunkInfo* d_chunks = nullptr;
   DenseTile* d_tiles = nullptr;
-  DenseTile* d_tiles32 = nullptr;
+  DenseTile* d_tiles32 = nullptr;                // the split kernel's tiles: of a whole window ...
   int64_t n_tiles32 = 0;
+  DenseTile* d_row_tiles = nullptr;              // ... and of single snapshots, ordered by snapshot
+  std::vector<int64_t> row_tile_ptr;             // [T+1] first row tile of every snapshot
   float* d_dinv = nullptr;
   int64_t* d_halo_ptr = nullptr;
   int32_t* d_halo_idx = nullptr;
@@ -184,7 +187,7 @@ dgc_status_t check_desc(const dgc_layer_desc_t& d, std::string* msg) {
       *msg = "lstm_input_concat needs two GCN layers and the LSTM"; return DGC_ERR_INVALID_ARG;
     }
     if (tile_kernel_runs(d.S, d.H, d.time_kind)) {
-      *msg = "lstm_input_concat is built in the wave-private dense kernel: S = H in {32, 64, 128}, dense_kernel not DGC_DENSE_TILE";
+      *msg = "lstm_input_concat is built in the split dense kernel: S = H in {32, 64, 128}, dense_kernel not DGC_DENSE_TILE";
       return DGC_ERR_UNSUPPORTED;
     }
   }
@@ -194,7 +197,7 @@ dgc_status_t check_desc(const dgc_layer_desc_t& d, std::string* msg) {
       *msg = "a stacked time encoder needs a GCN layer with a GRU or LSTM"; return DGC_ERR_INVALID_ARG;
     }
     if (tile_kernel_runs(d.S, d.H, d.time_kind)) {
-      *msg = "the stacked time encoder is built in the wave-private dense kernel: S = H in {32, 64, 128}, dense_kernel not DGC_DENSE_TILE";
+      *msg = "the stacked time encoder is built in the split dense kernel: S = H in {32, 64, 128}, dense_kernel not DGC_DENSE_TILE";
       return DGC_ERR_UNSUPPORTED;
     }
   }
@@ -234,20 +237,44 @@ dgc_status_t check_chunks(const dgc_chunk_t* c, int32_t n, int32_t T, int64_t N,
   return DGC_OK;
 }
 
-dgc_status_t add_param(dgc_layer* L, const std::string& name, int32_t n_out, int32_t n_in, hipStream_t st) {
+// Which dense kernel a stage of the layer runs: the split kernel wherever it is built, unless the workgroup-tile
+// kernel is asked for; a stage's weights are packed for its kernel.
+bool runs_split(const dgc_layer_desc_t& d, int32_t S, int32_t H, int32_t time_kind) {
+  return d.dense_kernel != DGC_DENSE_TILE && dense_split_supported(S, H, time_kind);
+}
+
+dgc_status_t add_param(dgc_layer* L, const std::string& name, int32_t n_out, int32_t n_in, hipStream_t st, bool split = false) {
   Failer fail{L};
   Param p;
-  p.n_out = n_out; p.n_in = n_in;
+  p.n_out = n_out; p.n_in = n_in; p.split = split;
   DGC_HIP_TRY(dev_alloc(L, &p.raw, p.numel()));
   DGC_HIP_TRY(hipMemsetAsync(p.raw, 0, sizeof(float) * p.numel(), st));
   if (n_in) {
-    const int64_t pe = packed_weight_elems(n_out, n_in);
+    const int64_t pe = split ? split_weight_bytes(n_out, n_in) / (int64_t)sizeof(float) : packed_weight_elems(n_out, n_in);
     float* pk = nullptr;
     DGC_HIP_TRY(dev_alloc(L, &pk, pe));
     DGC_HIP_TRY(hipMemsetAsync(pk, 0, sizeof(float) * pe, st));
     p.packed = reinterpret_cast<float4*>(pk);
   }
   L->params[name] = p;
+  return DGC_OK;
+}
+
+// 32-row tiles: consecutive vertices of one chunk
+std::vector<DenseTile> window_tiles(const std::vector<ChunkInfo>& chunks, int32_t rows) {
+  std::vector<DenseTile> tiles;
+  for (size_t k = 0; k < chunks.size(); ++k)
+    for (int64_t v0 = 0; v0 < chunks[k].nv; v0 += rows)
+      tiles.push_back(DenseTile{(int32_t)k, (int32_t)v0, (int32_t)std::min<int64_t>(rows, chunks[k].nv - v0), 0});
+  return tiles;
+}
+
+dgc_status_t upload_tiles(dgc_layer* L, const std::vector<DenseTile>& tiles, DenseTile** out, hipStream_t st) {
+  Failer fail{L};
+  DGC_HIP_TRY(dev_alloc(L, out, (int64_t)tiles.size()));
+  if (!tiles.empty())
+    DGC_HIP_TRY(hipMemcpyAsync(*out, tiles.data(), sizeof(DenseTile) * tiles.size(), hipMemcpyHostToDevice, st));
+  DGC_HIP_TRY(hipStreamSynchronize(st));
   return DGC_OK;
 }
 
@@ -261,6 +288,7 @@ dgc_status_t build_evolve(dgc_layer* L, const std::vector<ChunkInfo>& cinfo, hip
   const int64_t n = (int64_t)F * S;
   EvolveWs& ev = L->evo;
   ev.T = T; ev.F = F; ev.S = S;
+  ev.split = runs_split(L->desc, S, 0, DGC_TIME_NONE);
   for (int k = 0; k < EV_NPAR; ++k) {
     const bool fs = (k == EV_W || k == EV_BZ || k == EV_BR || k == EV_BH);
     Param p;                      // stored as [rows][cols] with n_out = rows, n_in = cols; never packed
@@ -283,7 +311,7 @@ dgc_status_t build_evolve(dgc_layer* L, const std::vector<ChunkInfo>& cinfo, hip
   DGC_HIP_TRY(dev_alloc(L, &ev.Rg, T * n));
   DGC_HIP_TRY(dev_alloc(L, &ev.Wc, T * n));
   float* pk = nullptr;
-  DGC_HIP_TRY(dev_alloc(L, &pk, (int64_t)T * packed_weight_elems(S, F)));
+  DGC_HIP_TRY(dev_alloc(L, &pk, (int64_t)T * evolve_packed_bytes(ev, ev.split) / (int64_t)sizeof(float)));
   ev.Wt_packed = reinterpret_cast<float4*>(pk);
   for (double*& t : ev.tmp) DGC_HIP_TRY(dev_alloc(L, &t, n));
   DGC_HIP_TRY(dev_alloc(L, &ev.dWd, T * n));
@@ -291,25 +319,11 @@ dgc_status_t build_evolve(dgc_layer* L, const std::vector<ChunkInfo>& cinfo, hip
   DGC_HIP_TRY(dev_alloc(L, &ev.loss_partial, evolve_loss_partial_elems(T)));
   DGC_HIP_TRY(dev_alloc(L, &L->d_zero_bias, S));
   DGC_HIP_TRY(hipMemsetAsync(L->d_zero_bias, 0, sizeof(float) * S, st));
-  // 32-row tiles of every snapshot, snapshot by snapshot, chunks in order
-  std::vector<DenseTile> items;
-  std::vector<int64_t> ptr(T + 1, 0);
-  for (int32_t t = 0; t < T; ++t) {
-    for (int32_t k = 0; k < L->n_chunks; ++k) {
-      if (t < cinfo[k].t_lo || t >= cinfo[k].t_lo + cinfo[k].w) continue;
-      for (int64_t v0 = 0; v0 < cinfo[k].nv; v0 += kWaveTileRows)
-        items.push_back(DenseTile{k, (int32_t)v0, (int32_t)std::min<int64_t>(kWaveTileRows, cinfo[k].nv - v0), 0});
-    }
-    ptr[t + 1] = (int64_t)items.size();
-  }
-  DenseTile* d_items = nullptr;
   int64_t* d_ptr = nullptr;
-  DGC_HIP_TRY(dev_alloc(L, &d_items, (int64_t)items.size()));
   DGC_HIP_TRY(dev_alloc(L, &d_ptr, T + 1));
-  DGC_HIP_TRY(hipMemcpyAsync(d_items, items.data(), sizeof(DenseTile) * items.size(), hipMemcpyHostToDevice, st));
-  DGC_HIP_TRY(hipMemcpyAsync(d_ptr, ptr.data(), sizeof(int64_t) * (T + 1), hipMemcpyHostToDevice, st));
+  DGC_HIP_TRY(hipMemcpyAsync(d_ptr, L->row_tile_ptr.data(), sizeof(int64_t) * (T + 1), hipMemcpyHostToDevice, st));
   DGC_HIP_TRY(hipStreamSynchronize(st));
-  ev.items = d_items; ev.item_ptr = d_ptr;
+  ev.items = L->d_row_tiles; ev.item_ptr = d_ptr;
   return DGC_OK;
 }
 
@@ -572,19 +586,34 @@ dgc_status_t build_layer(dgc_layer* L, const dgc_graph_t* graph, hipStream_t st)
     L->n_tiles = (int64_t)tiles.size();
     DGC_HIP_TRY(dev_alloc(L, &L->d_tiles, L->n_tiles));
     DGC_HIP_TRY(hipMemcpyAsync(L->d_tiles, tiles.data(), sizeof(DenseTile) * tiles.size(), hipMemcpyHostToDevice, st));
-    std::vector<DenseTile> tiles32;
-    for (int32_t k = 0; k < L->n_chunks; ++k)
-      for (int64_t v0 = 0; v0 < cinfo[k].nv; v0 += kWaveTileRows)
-        tiles32.push_back(DenseTile{k, (int32_t)v0, (int32_t)std::min<int64_t>(kWaveTileRows, cinfo[k].nv - v0), 0});
-    L->n_tiles32 = (int64_t)tiles32.size();
-    DGC_HIP_TRY(dev_alloc(L, &L->d_tiles32, L->n_tiles32));
-    DGC_HIP_TRY(hipMemcpyAsync(L->d_tiles32, tiles32.data(), sizeof(DenseTile) * tiles32.size(), hipMemcpyHostToDevice, st));
+    if (!gat_layer) {
+      dgc_status_t e;
+      const std::vector<DenseTile> t32 = window_tiles(cinfo, kWaveTileRows);
+      L->n_tiles32 = (int64_t)t32.size();
+      if ((e = upload_tiles(L, t32, &L->d_tiles32, st)) != DGC_OK) return e;
+      if (d.time_kind == DGC_TIME_NONE || d.n_struct_layers == 2) {     // a transform alone: row tiles, snapshot by snapshot
+        std::vector<std::vector<DenseTile>> by_t(T);
+        for (const DenseTile& w : t32)
+          for (int32_t s = 0; s < cinfo[w.chunk].w; ++s) {
+            DenseTile r = w;
+            r.step = s;
+            by_t[cinfo[w.chunk].t_lo + s].push_back(r);
+          }
+        std::vector<DenseTile> rows;
+        L->row_tile_ptr.assign(T + 1, 0);
+        for (int32_t t = 0; t < T; ++t) {
+          rows.insert(rows.end(), by_t[t].begin(), by_t[t].end());
+          L->row_tile_ptr[t + 1] = (int64_t)rows.size();
+        }
+        if ((e = upload_tiles(L, rows, &L->d_row_tiles, st)) != DGC_OK) return e;
+      }
+    }
     DGC_HIP_TRY(hipStreamSynchronize(st));
   }
 
   // workspace
   const int32_t Fmax = std::max(d.F, d.n_struct_layers == 2 ? d.S : 0);
-  L->ldm = (Fmax + 7) / 8 * 8;  // whole k-blocks of 8; the aggregation zero-fills the pad columns
+  L->ldm = (Fmax + 15) / 16 * 16;  // whole k-blocks; the aggregation zero-fills the pad columns
   const bool gat = d.struct_kind == DGC_STRUCT_GAT;
   if (!gat) {
     DGC_HIP_TRY(dev_alloc(L, &L->d_M, L->total_rows * L->ldm));
@@ -603,21 +632,22 @@ dgc_status_t build_layer(dgc_layer* L, const dgc_graph_t* graph, hipStream_t st)
   } else if (d.struct_kind == DGC_STRUCT_EVOLVE_GCN_O) {
     if ((rc = build_evolve(L, cinfo, st)) != DGC_OK) return rc;
   } else {
-  if ((rc = add_param(L, "gcn0.weight", d.S, d.F, st)) != DGC_OK) return rc;
+  const bool sp = runs_split(d, d.S, d.H, d.time_kind), sp0 = runs_split(d, d.S, 0, DGC_TIME_NONE);
+  if ((rc = add_param(L, "gcn0.weight", d.S, d.F, st, d.n_struct_layers == 2 ? sp0 : sp)) != DGC_OK) return rc;
   if ((rc = add_param(L, "gcn0.bias", d.S, 0, st)) != DGC_OK) return rc;
   if (d.n_struct_layers == 2) {
-    if ((rc = add_param(L, "gcn1.weight", d.S, d.S, st)) != DGC_OK) return rc;
+    if ((rc = add_param(L, "gcn1.weight", d.S, d.S, st, sp)) != DGC_OK) return rc;
     if ((rc = add_param(L, "gcn1.bias", d.S, 0, st)) != DGC_OK) return rc;
   }
   if (d.time_kind != DGC_TIME_NONE) {
     const int32_t gH = (d.time_kind == DGC_TIME_LSTM ? 4 : 3) * d.H;
-    if ((rc = add_param(L, "rnn.weight_ih", gH, d.lstm_input_concat ? 2 * d.S : d.S, st)) != DGC_OK) return rc;
-    if ((rc = add_param(L, "rnn.weight_hh", gH, d.H, st)) != DGC_OK) return rc;
+    if ((rc = add_param(L, "rnn.weight_ih", gH, d.lstm_input_concat ? 2 * d.S : d.S, st, sp)) != DGC_OK) return rc;
+    if ((rc = add_param(L, "rnn.weight_hh", gH, d.H, st, sp)) != DGC_OK) return rc;
     if ((rc = add_param(L, "rnn.bias_ih", gH, 0, st)) != DGC_OK) return rc;
     if ((rc = add_param(L, "rnn.bias_hh", gH, 0, st)) != DGC_OK) return rc;
     if (d.n_time_layers == 2) {
-      if ((rc = add_param(L, "rnn1.weight_ih", gH, d.H, st)) != DGC_OK) return rc;
-      if ((rc = add_param(L, "rnn1.weight_hh", gH, d.H, st)) != DGC_OK) return rc;
+      if ((rc = add_param(L, "rnn1.weight_ih", gH, d.H, st, sp)) != DGC_OK) return rc;
+      if ((rc = add_param(L, "rnn1.weight_hh", gH, d.H, st, sp)) != DGC_OK) return rc;
       if ((rc = add_param(L, "rnn1.bias_ih", gH, 0, st)) != DGC_OK) return rc;
       if ((rc = add_param(L, "rnn1.bias_hh", gH, 0, st)) != DGC_OK) return rc;
     }
@@ -751,11 +781,7 @@ dgc_status_t set_presence_labelled(dgc_layer* L, const uint8_t* present, hipStre
   DGC_HIP_TRY(hipMemcpyAsync(tf.chunks_v, &cv, sizeof(ChunkInfo), hipMemcpyHostToDevice, st));
   lp_fill(present, d_first, d_pos, d_last, d_lane, d_off, T, N, n_l, tf.slot_row, tf.row_map, tf.slot_reset, tf.seq_in,
           tf.seq_out, st);
-  std::vector<DenseTile> t64, t32;
-  for (int64_t v0 = 0; v0 < n_l; v0 += kTileRows)
-    t64.push_back(DenseTile{0, (int32_t)v0, (int32_t)std::min<int64_t>(kTileRows, n_l - v0), 0});
-  for (int64_t v0 = 0; v0 < n_l; v0 += kWaveTileRows)
-    t32.push_back(DenseTile{0, (int32_t)v0, (int32_t)std::min<int64_t>(kWaveTileRows, n_l - v0), 0});
+  const std::vector<DenseTile> t64 = window_tiles({cv}, kTileRows), t32 = window_tiles({cv}, kWaveTileRows);
   tf.n_tiles_v = (int64_t)t64.size(); tf.n_tiles32_v = (int64_t)t32.size();
   DGC_HIP_TRY(dev_alloc(L, &tf.tiles_v, tf.n_tiles_v));
   DGC_HIP_TRY(dev_alloc(L, &tf.tiles32_v, tf.n_tiles32_v));
@@ -861,7 +887,8 @@ dgc_status_t dgc_layer_set_param(dgc_layer_t* L, const char* name, const float* 
     dysat_pack_params(L->dy, nullptr);
     DGC_HIP_TRY(hipDeviceSynchronize());
   } else if (p.packed) {
-    launch_pack_weight(p.raw, p.n_out, p.n_in, p.packed, nullptr);
+    if (p.split) launch_pack_split(p.raw, 0, p.n_in, 1, p.n_out, p.n_in, 1, p.packed, nullptr);
+    else launch_pack_weight(p.raw, p.n_out, p.n_in, p.packed, nullptr);
     DGC_HIP_TRY(hipDeviceSynchronize());
   }
   return DGC_OK;
@@ -887,8 +914,8 @@ dgc_status_t dgc_layer_aggregate(dgc_layer_t* L, const float* X, int64_t ldx, co
   if ((rc = check_tensor(fail, "X", X, ldx, L->desc.F, true)) != DGC_OK) return rc;
   if ((rc = check_tensor(fail, "C", C, ldc, L->desc.F, true)) != DGC_OK) return rc;
   if ((rc = check_tensor(fail, "M", M, ldm, L->desc.F, true)) != DGC_OK) return rc;
-  // the split-row scratch and the staged halo buffer are sized for pitch round_up(F,8)
-  if (ldm > L->ldm) return fail(DGC_ERR_INVALID_ARG, "M: pitch must not exceed round_up(F,8)");
+  // the split-row scratch and the staged halo buffer are sized for this pitch at least
+  if (ldm > (std::max(L->desc.F, L->desc.n_struct_layers == 2 ? L->desc.S : 0) + 7) / 8 * 8) return fail(DGC_ERR_INVALID_ARG, "M: pitch must not exceed round_up(F,8)");
   run_aggregate(L, X, ldx, C, ldc, L->desc.F, M, ldm, static_cast<hipStream_t>(stream));
   DGC_HIP_TRY(hipGetLastError());
   return DGC_OK;
@@ -946,6 +973,7 @@ dgc_status_t dgc_layer_forward(dgc_layer_t* L, const void* Xv, int64_t ldx, cons
   DenseArgs da{};
   da.tiles = L->d_tiles; da.n_tiles = L->n_tiles; da.chunks = L->d_chunks;
   da.tiles32 = L->d_tiles32; da.n_tiles32 = L->n_tiles32; da.variant = d.dense_kernel;
+  da.row_tiles = L->d_row_tiles; da.n_row_tiles = L->row_tile_ptr.empty() ? 0 : L->row_tile_ptr.back();
   da.N = L->N; da.total_state_rows = L->total_state_rows;
   da.M = L->d_M; da.ldm = L->ldm;
   da.S = d.S; da.H = d.H;
@@ -971,7 +999,7 @@ dgc_status_t dgc_layer_forward(dgc_layer_t* L, const void* Xv, int64_t ldx, cons
     // first layer for every row of the batch -> Z1 [T,N,S]; then aggregate Z1 | C1
     da.K0 = d.F; da.act = d.act_hidden; da.time_kind = DGC_TIME_NONE;
     da.Wg = L->params["gcn0.weight"].packed; da.bg = L->params["gcn0.bias"].raw;
-    da.wg_bytes = sizeof(float) * packed_weight_elems(d.S, d.F); da.wg_step_bytes = 0;
+    da.wg_step_bytes = 0;
     da.Y = L->d_Z1; da.ldy = d.S;
     if (!launch_dense(da, st, &why)) return fail(DGC_ERR_UNSUPPORTED, why);
     if (prof) DGC_HIP_TRY(hipEventRecord(L->ev[2], st));
@@ -988,12 +1016,11 @@ dgc_status_t dgc_layer_forward(dgc_layer_t* L, const void* Xv, int64_t ldx, cons
   if (evolve) {
     da.Wg = L->evo.Wt_packed;
     da.bg = L->d_zero_bias;
-    da.wg_step_bytes = (int32_t)(sizeof(float) * packed_weight_elems(d.S, d.F));
-    da.wg_bytes = (int64_t)L->T * da.wg_step_bytes;
+    da.wg_step_bytes = evolve_packed_bytes(L->evo, L->evo.split);
   } else {
     da.Wg = L->params[std::string(last) + ".weight"].packed;
     da.bg = L->params[std::string(last) + ".bias"].raw;
-    da.wg_bytes = sizeof(float) * packed_weight_elems(d.S, da.K0); da.wg_step_bytes = 0;
+    da.wg_step_bytes = 0;
   }
   if (d.time_kind != DGC_TIME_NONE) {
     da.Wih = L->params["rnn.weight_ih"].packed; da.Whh = L->params["rnn.weight_hh"].packed;
@@ -1038,7 +1065,7 @@ dgc_status_t dgc_layer_forward(dgc_layer_t* L, const void* Xv, int64_t ldx, cons
     da.M = Y; da.ldm = ldy; da.m_by_vertex = true; da.input_is_z = true; da.K0 = 0;
     da.Wih = L->params["rnn1.weight_ih"].packed; da.Whh = L->params["rnn1.weight_hh"].packed;
     da.bih = L->params["rnn1.bias_ih"].raw; da.bhh = L->params["rnn1.bias_hh"].raw;
-    da.Wg = da.Wih; da.wg_bytes = sizeof(float) * packed_weight_elems((d.time_kind == DGC_TIME_LSTM ? 4 : 3) * d.H, d.H);
+    da.Wg = nullptr; da.bg = nullptr;
     da.wg_step_bytes = 0; da.act = DGC_ACT_NONE;
     da.X2 = nullptr; da.x2_map = nullptr;
     da.H0 = H0 ? H0 + block : nullptr; da.HN = HN ? HN + block : nullptr;
@@ -1157,7 +1184,7 @@ dgc_status_t dgc_layer_backward(dgc_layer_t* L, const void* Yv, int64_t ldy, con
     if (!L->d_dM) {
       DGC_HIP_TRY(dev_alloc(L, &L->d_dM, (int64_t)L->T * L->N * d.F));
       DGC_HIP_TRY(dev_alloc(L, &L->d_rowidx, L->total_rows));
-      DGC_HIP_TRY(dev_alloc(L, &L->d_Wt_plain, (int64_t)L->T * packed_weight_elems(d.F, d.S) / 4));
+      DGC_HIP_TRY(dev_alloc(L, &L->d_Wt_plain, (int64_t)L->T * evolve_packed_bytes(L->evo, L->evo.split) / (int64_t)sizeof(float4)));
       evolve_row_index(L->d_chunks, L->n_chunks, max_nv, max_w, L->N, L->d_rowidx, st);
     }
     L->m_saved = false;
@@ -1165,13 +1192,12 @@ dgc_status_t dgc_layer_backward(dgc_layer_t* L, const void* Yv, int64_t ldy, con
     evolve_pack_weights_plain(L->evo, L->d_Wt_plain, st);
     DenseArgs da{};
     da.tiles = L->d_tiles; da.n_tiles = L->n_tiles; da.chunks = L->d_chunks;
-    da.tiles32 = L->d_tiles32; da.n_tiles32 = L->n_tiles32; da.variant = d.dense_kernel;
+    da.row_tiles = L->d_row_tiles; da.n_row_tiles = L->row_tile_ptr.back(); da.variant = d.dense_kernel;
     da.N = L->N; da.total_state_rows = L->total_state_rows;
     da.M = L->d_M; da.ldm = L->ldm;
     da.K0 = d.S; da.S = d.F; da.H = 0; da.act = DGC_ACT_NONE; da.time_kind = DGC_TIME_NONE;
     da.Wg = L->d_Wt_plain; da.bg = L->d_zero_bias;
-    da.wg_step_bytes = (int32_t)(sizeof(float) * packed_weight_elems(d.F, d.S));
-    da.wg_bytes = (int64_t)L->T * da.wg_step_bytes;
+    da.wg_step_bytes = evolve_packed_bytes(L->evo, L->evo.split);
     da.Y = L->d_dM; da.ldy = d.F;
     if (!launch_dense(da, st, &why)) return fail(DGC_ERR_UNSUPPORTED, why);
     SpmmArgs sa = spmm_args(L, L->d_dM, d.F, L->d_dM, d.F, d.F, static_cast<float*>(dX), d.F);
@@ -1290,13 +1316,7 @@ dgc_status_t dgc_layer_set_presence(dgc_layer_t* L, const uint8_t* present, void
   tf_fill(present, L->d_chunks, nc, max_nv, L->N, d_lane, d_off, tf.n_lanes, tf.Lmax, tf.chunks_v, L->total_rows,
           tf.slot_row, tf.row_map, tf.slot_reset, tf.seq_in, tf.seq_out, st);
   // tiles of the virtual chunks
-  std::vector<DenseTile> t64, t32;
-  for (int32_t k = 0; k < nc; ++k) {
-    for (int64_t v0 = 0; v0 < cv[k].nv; v0 += kTileRows)
-      t64.push_back(DenseTile{k, (int32_t)v0, (int32_t)std::min<int64_t>(kTileRows, cv[k].nv - v0), 0});
-    for (int64_t v0 = 0; v0 < cv[k].nv; v0 += kWaveTileRows)
-      t32.push_back(DenseTile{k, (int32_t)v0, (int32_t)std::min<int64_t>(kWaveTileRows, cv[k].nv - v0), 0});
-  }
+  const std::vector<DenseTile> t64 = window_tiles(cv, kTileRows), t32 = window_tiles(cv, kWaveTileRows);
   tf.n_tiles_v = (int64_t)t64.size(); tf.n_tiles32_v = (int64_t)t32.size();
   DGC_HIP_TRY(dev_alloc(L, &tf.tiles_v, tf.n_tiles_v));
   DGC_HIP_TRY(dev_alloc(L, &tf.tiles32_v, tf.n_tiles32_v));

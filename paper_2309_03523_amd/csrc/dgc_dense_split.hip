@@ -1,0 +1,648 @@
+// Dense part of the layer on the bf16 matrix cores at fp32 accuracy.
+//
+// An fp32 number is the exact sum of three bf16 numbers (8 significant bits each, cut off one after the
+// other), so a product of fp32 operands is six bf16 MFMAs: hi*hi, hi*mid, mid*hi, mid*mid, hi*lo, lo*hi,
+// all accumulated in fp32; what is left out is below 2^-24 of a term, less than one rounding of the
+// accumulator.  v_mfma_f32_32x32x16_bf16 does 16 times the work of v_mfma_f32_32x32x2f32 per cycle, so the
+// six cost 2.7 times less than the fp32 instruction and add up in fewer roundings.  Exponents are those of
+// fp32: no scaling, no overflow that fp32 would not have.
+//
+// With the weights as A operand (lane l: A[l%32][8*(l/32) .. +7]) and 32 activation rows as B operand
+// (B[8*(l/32) .. +7][l%32]), lane (n = l%32, half = l/32) receives of row n the columns 8*g4 + 4*half + e in
+// register 4*g4 + e.  Registers 0..7 (8..15) are then one k-half of a 16-wide k-block whose slots
+// 8*half + 4*p + e stand for columns 8*p + 4*half + e: with the weights' columns packed in that order a
+// result is the next product's operand without moving between lanes.
+//
+// What bounds them: the matrix cores' power.  Random operands through a loop of nothing but this MFMA reach
+// 1.83 PFLOP/s of bf16 on this GPU (2.46 with zeros), a library product 1.33; the time encoders run at 1.1
+// (GRU 128 wide, 3.2 M rows: 6.27 ms on the fp32 instruction, 3.96 ms here; the two LSTM layers of MPNN-LSTM over
+// 1.28 M rows 6.90 + 4.35 -> 2.85 + 1.80 ms; GRU 256 wide, 160 k rows 2.29 -> 0.88 ms).  Without the weights' loads,
+// the LDS reads and the gate arithmetic the first would still take 3.5 ms.  Tiles of 64 vertices halve the weights'
+// L2 traffic and are no faster (4.15 ms: two workgroups of 256 registers a wave, more work behind each barrier);
+// three workgroups per CU of 168 registers spill (4.36 ms).
+//
+// k_dense_split (time encoders): a workgroup owns 32 vertices of one chunk and walks the chunk's window; wave jb
+// owns columns 32*jb .. +31 of Z, of every gate and of the state.  So a weight fragment is read from L2 by one
+// wave of the workgroup, and only the split activations (h, M, Z in turn) go through LDS.
+// k_rows_split (transforms alone): wave jb keeps its columns of the weights in registers and a workgroup streams
+// row tiles past them, so that nothing but rows is read (4 M rows, 256 -> 256: 5.16 ms on the fp32 instruction, 3.67
+// with the weights from L2 for every 64 rows, 3.3 like this, of which the rows alone take 2.0 and the products alone
+// 2.3; 1.28 M rows, 172 -> 128: 0.85 -> 0.38 ms).
+#include <algorithm>
+#include <atomic>
+
+#include "dgc_internal.h"
+
+namespace dgc {
+namespace {
+
+typedef float floatx16 __attribute__((ext_vector_type(16)));
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef int intx4 __attribute__((ext_vector_type(4)));
+
+constexpr int kFrag = 64;                  // uint4 of one fragment part (32 rows x 16 k, one bf16 part)
+constexpr int kUnitBytes = 3 * kFrag * 16; // a weight fragment's three parts
+
+__device__ __forceinline__ float sigmoid_fast(float x) { return __builtin_amdgcn_rcpf(1.0f + __expf(-x)); }
+__device__ __forceinline__ float tanh_fast(float x) { return 1.0f - 2.0f * __builtin_amdgcn_rcpf(1.0f + __expf(2.0f * x)); }
+__device__ __forceinline__ bf16x8 as_frag(uint4 u) { return __builtin_bit_cast(bf16x8, u); }
+__device__ __forceinline__ float cut(float x) { return __uint_as_float(__float_as_uint(x) & 0xffff0000u); }
+__device__ __forceinline__ uint32_t tops(float lo, float hi) {   // the upper halves of two words
+  return __builtin_amdgcn_perm(__float_as_uint(hi), __float_as_uint(lo), 0x07060302u);
+}
+__device__ __forceinline__ uint4 tops8(const float (&x)[8]) {
+  return make_uint4(tops(x[0], x[1]), tops(x[2], x[3]), tops(x[4], x[5]), tops(x[6], x[7]));
+}
+
+// x = p[0] + p[1] + p[2], exactly, for finite x; an infinity is p[0] alone (its remainder would be NaN)
+__device__ __forceinline__ void split8(const float (&x)[8], uint4 (&p)[3]) {
+  float m[8], l[8];
+  float top = 0.f;
+#pragma unroll
+  for (int i = 0; i < 8; ++i) {
+    m[i] = x[i] - cut(x[i]);
+    top = fmaxf(top, fabsf(x[i]));
+  }
+  if (__builtin_expect(__any(top == __builtin_inff()), 0)) {
+#pragma unroll
+    for (int i = 0; i < 8; ++i) m[i] = fabsf(x[i]) == __builtin_inff() ? 0.f : m[i];
+  }
+#pragma unroll
+  for (int i = 0; i < 8; ++i) l[i] = m[i] - cut(m[i]);
+  p[0] = tops8(x);
+  p[1] = tops8(m);
+  p[2] = tops8(l);
+}
+
+// Weights come by buffer loads: resource descriptor in scalar registers, the fragment's place as scalar
+// offset, the lane's 16 bytes as vector offset.  A vector offset beyond the resource reads as zero without
+// touching memory: that is what a fragment past the end of a product gets, so that the loops have no branches.
+struct WeightStream {
+  __amdgpu_buffer_rsrc_t rsrc;
+  __device__ __forceinline__ void unit(uint4 (&w)[3], int lane16, int off, bool there) const {
+    const int v = lane16 + (there ? 0 : 0x40000000);
+#pragma unroll
+    for (int p = 0; p < 3; ++p) {
+      const intx4 x = __builtin_amdgcn_raw_buffer_load_b128(rsrc, v, off + p * kFrag * 16, 0);
+      w[p] = make_uint4(x.x, x.y, x.z, x.w);
+    }
+  }
+};
+__device__ __forceinline__ WeightStream make_stream(const void* p, int64_t bytes) {
+  WeightStream w;
+  w.rsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), 0, (int)bytes, 0x00020000);
+  return w;
+}
+
+// The weight fragments of a product are read in the order (k-block, gate), D - 1 of them ahead of their use.
+// fetch_ahead: the first D - 1, before the barrier that the product waits at.  nkb: k-blocks that have weights.
+template <int NG, int D>
+__device__ __forceinline__ void fetch_ahead(uint4 (&w)[D][3], const WeightStream& ws, int off, int gstride, int nkb, int lane16) {
+#pragma unroll
+  for (int u = 0; u < D - 1; ++u) ws.unit(w[u], lane16, off + (u % NG) * gstride + (u / NG) * kUnitBytes, u / NG < nkb);
+}
+
+// c += weights x rows of one fragment each, the smallest products first
+__device__ __forceinline__ void six(floatx16& c, const uint4 (&w)[3], const uint4 (&x)[3]) {
+  const bf16x8 w0 = as_frag(w[0]), w1 = as_frag(w[1]), w2 = as_frag(w[2]);
+  const bf16x8 x0 = as_frag(x[0]), x1 = as_frag(x[1]), x2 = as_frag(x[2]);
+  c = __builtin_amdgcn_mfma_f32_32x32x16_bf16(w0, x2, c, 0, 0, 0);
+  c = __builtin_amdgcn_mfma_f32_32x32x16_bf16(w2, x0, c, 0, 0, 0);
+  c = __builtin_amdgcn_mfma_f32_32x32x16_bf16(w1, x1, c, 0, 0, 0);
+  c = __builtin_amdgcn_mfma_f32_32x32x16_bf16(w0, x1, c, 0, 0, 0);
+  c = __builtin_amdgcn_mfma_f32_32x32x16_bf16(w1, x0, c, 0, 0, 0);
+  c = __builtin_amdgcn_mfma_f32_32x32x16_bf16(w0, x0, c, 0, 0, 0);
+}
+
+// acc(g) += W_g x rows, over nkb k-blocks; fr: this lane's first operand of the staged rows
+template <int NG, int D, class Acc>
+__device__ __forceinline__ void product(Acc&& acc, const uint4* fr, const WeightStream& ws, int off, int gstride, int nkb,
+                                        int lane16, uint4 (&w)[D][3]) {
+  constexpr int UK = D > NG ? D / NG : 1;
+  static_assert((UK * NG) % D == 0, "the buffers come round within the unrolled k-blocks");
+  uint4 b[3];
+#pragma unroll
+  for (int p = 0; p < 3; ++p) b[p] = fr[p * kFrag];
+  __builtin_amdgcn_s_setprio(1);   // the other workgroups of the CU do their vector work beside this
+#pragma unroll 1
+  for (int kb = 0; kb < nkb; kb += UK) {
+#pragma unroll
+    for (int i = 0; i < UK; ++i) {
+      const int k = kb + i;
+      if (UK > 1 && k >= nkb) break;
+#pragma unroll
+      for (int g = 0; g < NG; ++g) {
+        const int u = i * NG + g;
+        const int kn = k + (g + D - 1) / NG, gn = (g + D - 1) % NG;
+        ws.unit(w[(u + D - 1) % D], lane16, off + gn * gstride + kn * kUnitBytes, kn < nkb);
+        __builtin_amdgcn_sched_barrier(0);
+        six(acc(g), w[u % D], b);
+        if (g == NG - 1) {
+          const uint4* next = fr + min(k + 1, nkb - 1) * (3 * kFrag);
+#pragma unroll
+          for (int p = 0; p < 3; ++p) b[p] = next[p * kFrag];
+        }
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    }
+  }
+  __builtin_amdgcn_s_setprio(0);
+}
+
+__device__ __forceinline__ void put(uint4* frag, const float (&x)[8]) {
+  uint4 p[3];
+  split8(x, p);
+#pragma unroll
+  for (int q = 0; q < 3; ++q) frag[q * kFrag] = p[q];
+}
+// columns 16*kb .. +15 of an input row (a pitch is a multiple of 16 floats); row: the lane's first column
+__device__ __forceinline__ void load_x(const float* row, int kb, float4 (&x)[2]) {
+  x[0] = *reinterpret_cast<const float4*>(row + 16 * kb);
+  x[1] = *reinterpret_cast<const float4*>(row + 16 * kb + 8);
+}
+__device__ __forceinline__ void put_x(uint4* frag, const float4 (&x)[2]) {
+  const float v[8] = {x[0].x, x[0].y, x[0].z, x[0].w, x[1].x, x[1].y, x[1].z, x[1].w};
+  put(frag, v);
+}
+// a lane's 16 values of a 32-column block in global memory or LDS; p: its first column
+__device__ __forceinline__ floatx16 load_block(const float* p) {
+  floatx16 r;
+#pragma unroll
+  for (int g4 = 0; g4 < 4; ++g4) {
+    const float4 b = *reinterpret_cast<const float4*>(p + 8 * g4);
+    r[4 * g4] = b.x; r[4 * g4 + 1] = b.y; r[4 * g4 + 2] = b.z; r[4 * g4 + 3] = b.w;
+  }
+  return r;
+}
+__device__ __forceinline__ void store_block(float* p, const floatx16& v) {
+#pragma unroll
+  for (int g4 = 0; g4 < 4; ++g4)
+    *reinterpret_cast<float4*>(p + 8 * g4) = make_float4(v[4 * g4], v[4 * g4 + 1], v[4 * g4 + 2], v[4 * g4 + 3]);
+}
+__device__ __forceinline__ void relu(floatx16& z) {
+#pragma unroll
+  for (int v = 0; v < 16; ++v) z[v] = fmaxf(z[v], 0.f);
+}
+
+// A table that no kernel writes while it is read: the address space lets wave-uniform entries come through the
+// scalar cache, apart from the vector memory operations (which retire in order).
+template <class T>
+__device__ __forceinline__ T table_entry(const T* table, int64_t i) {
+  union {
+    T entry;
+    uint32_t word[sizeof(T) / 4];
+  } r;
+  const auto* p = (const __attribute__((address_space(4))) uint32_t*)(table + i);
+#pragma unroll
+  for (size_t k = 0; k < sizeof(T) / 4; ++k) r.word[k] = p[k];
+  return r.entry;
+}
+
+// KIND: DGC_TIME_GRU or DGC_TIME_LSTM.  SEQ, CAT, STACK: as the fields of DenseArgs say (sequences inside the window;
+// the time encoder's input is [X2 row, Z]; a second recurrent layer without a transform).
+template <int KIND, bool SEQ, bool CAT, bool STACK, int MAXW>
+__global__ __launch_bounds__(64 * MAXW, 2) void k_dense_split(DenseArgs a) {
+  constexpr bool kLstm = KIND == DGC_TIME_LSTM;
+  constexpr int NG = kLstm ? 4 : 3;
+  constexpr int DG = NG, DZ = 4;              // weight fragments held: gates, transform
+  extern __shared__ __align__(16) uint4 lds[];
+  const int njb = blockDim.x >> 6, kbh = 2 * njb, H = 32 * njb;
+  const int lane = threadIdx.x & 63, l32 = lane & 31, half = lane >> 5;
+  const int jb = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int lane16 = lane * 16;
+  const int kbc = a.kb_chunk;                 // k-blocks that a staging buffer holds
+  // Two staging buffers in turn: a buffer is written again after a barrier that every wave reached past its
+  // reads of it.
+  uint4* buf = lds + lane;
+  uint4* other = buf + kbc * 3 * kFrag;
+  float* gbias = reinterpret_cast<float*>(lds + 2 * kbc * 3 * kFrag);
+  float* zbias = gbias + 4 * H;
+  for (int i = threadIdx.x; i < H; i += blockDim.x) {
+    zbias[i] = a.bg ? a.bg[i] : 0.f;
+    if constexpr (kLstm) {
+#pragma unroll
+      for (int g = 0; g < 4; ++g) gbias[g * H + i] = a.bih[g * H + i] + a.bhh[g * H + i];
+    } else {
+      gbias[i] = a.bih[i] + a.bhh[i];
+      gbias[H + i] = a.bih[H + i] + a.bhh[H + i];
+      gbias[2 * H + i] = a.bih[2 * H + i];
+      gbias[3 * H + i] = a.bhh[2 * H + i];
+    }
+  }
+  const DenseTile tile = table_entry(a.tiles32, blockIdx.x);
+  const ChunkInfo ch = table_entry(a.chunks, tile.chunk);
+  const int nkb0 = STACK ? kbh : (a.K0 + 15) / 16, nchunk = (nkb0 + kbc - 1) / kbc;
+  const int kbx = CAT ? 2 * kbh : kbh;        // k-blocks of the time encoder's input
+  const int64_t V = a.total_state_rows;
+  const WeightStream wsg = make_stream(a.Wg, STACK ? 0 : (int64_t)njb * nkb0 * kUnitBytes);
+  const WeightStream wsi = make_stream(a.Wih, (int64_t)NG * njb * kbx * kUnitBytes);
+  const WeightStream wsh = make_stream(a.Whh, (int64_t)NG * njb * kbh * kUnitBytes);
+  const int offz = jb * nkb0 * kUnitBytes;
+  const int offx = jb * kbx * kUnitBytes, gsx = njb * kbx * kUnitBytes;
+  const int offh = jb * kbh * kUnitBytes, gsh = njb * kbh * kUnitBytes;
+  const int col0 = 32 * jb + 4 * half;        // this lane's columns: col0 + 8*g4 + e
+  const bool valid = l32 < tile.nrows;        // rows past the tile's end repeat its last row and are never stored
+  const int row = min(l32, tile.nrows - 1);
+  const int64_t v0 = ch.v_lo + tile.v0 + row, s0 = ch.state_off + tile.v0 + row;
+  auto slot = [&](int64_t ts) { return ts * a.N + v0; };
+
+  // SEQ with a row map: row of Y of this step and of the next one
+  const bool mapped = SEQ && a.y_map != nullptr;
+  int yrow = 0, yrow_next = 0;
+  if (mapped) yrow_next = (int)a.y_map[slot(ch.t_lo)];
+  auto in_row = [&](int s) -> const float* {
+    int64_t r;
+    if constexpr (STACK) r = mapped ? (int64_t)max(yrow_next, 0) : slot(ch.t_lo + s);
+    else r = ch.row_off0 + (int64_t)s * ch.nv + tile.v0 + row;
+    return a.M + r * a.ldm + 4 * half;
+  };
+  // Staging: wave w takes k-blocks 2w, 2w + 1 (then 2w + 2*njb ...).  The first two are requested ahead (past the
+  // row's end: its last one).
+  float4 xq[2][2];
+  auto request_x = [&](int s, int c) {
+    const float* p = in_row(s);
+#pragma unroll
+    for (int q = 0; q < 2; ++q) load_x(p, min(c * kbc + 2 * jb + q, nkb0 - 1), xq[q]);
+  };
+  auto stage_x = [&](int s, int c) {
+    const int k0 = c * kbc, n = min(kbc, nkb0 - k0);
+#pragma unroll
+    for (int q = 0; q < 2; ++q)
+      if (2 * jb + q < n) put_x(buf + (2 * jb + q) * 3 * kFrag, xq[q]);
+    for (int kb = 2 * (jb + njb); kb < n; kb += 2 * njb)
+#pragma unroll
+      for (int q = 0; q < 2; ++q)
+        if (kb + q < n) {
+          float4 x[2];
+          load_x(in_row(s), k0 + kb + q, x);
+          put_x(buf + (kb + q) * 3 * kFrag, x);
+        }
+  };
+  // a 32-column block in registers -> k-blocks 2*jb, 2*jb + 1 of the other buffer
+  auto turn = [&]() { uint4* x = buf; buf = other; other = x; };
+  auto put_block = [&](const floatx16& v) {
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {
+      const float x[8] = {v[8 * q], v[8 * q + 1], v[8 * q + 2], v[8 * q + 3], v[8 * q + 4], v[8 * q + 5], v[8 * q + 6], v[8 * q + 7]};
+      put(buf + (2 * jb + q) * 3 * kFrag, x);
+    }
+  };
+
+  floatx16 h = (floatx16)(0.f), c = (floatx16)(0.f);
+  // The state that enters a snapshot: a masked row starts from zero; with SEQ a row where a sequence starts takes
+  // the sequence's state, which is requested well before (rows where none starts request the first state row).
+  int64_t sr = -1;
+  floatx16 hin = (floatx16)(0.f), cin = (floatx16)(0.f);
+  auto request_state = [&]() {
+    if (a.H0) {
+      const int64_t r = max(sr, (int64_t)0);
+      hin = load_block(a.H0 + r * H + col0);
+      if constexpr (kLstm) cin = load_block(a.H0 + (V + r) * H + col0);
+    }
+  };
+  auto enter = [&](int64_t ts) {
+    if constexpr (SEQ) {
+#pragma unroll
+      for (int v = 0; v < 16; ++v) {
+        h[v] = sr >= 0 ? hin[v] : h[v];
+        if constexpr (kLstm) c[v] = sr >= 0 ? cin[v] : c[v];
+      }
+    } else if (a.reset_mask && a.reset_mask[slot(ts)]) {
+      h = (floatx16)(0.f);
+      c = (floatx16)(0.f);
+    }
+  };
+  if constexpr (SEQ) {
+    sr = a.seq_in[slot(ch.t_lo)];
+    request_state();
+  } else if (a.H0) {
+    h = load_block(a.H0 + s0 * H + col0);
+    if constexpr (kLstm) c = load_block(a.H0 + (V + s0) * H + col0);
+  }
+  enter(ch.t_lo);
+  uint4 wg[DG][3], wz[DZ][3];
+  fetch_ahead<NG, DG>(wg, wsh, offh, gsh, kbh, lane16);
+  request_x(0, 0);
+
+  for (int s = 0; s < ch.w; ++s) {
+    const int64_t ts = ch.t_lo + s;
+    if constexpr (SEQ) sr = a.seq_in[slot(min(ts + 1, (int64_t)ch.t_lo + ch.w - 1))];    // of the next step
+    int64_t so = -1;                          // state row that leaves after this step
+    if constexpr (SEQ) so = a.seq_out[slot(ts)];
+    else if (s + 1 == ch.w) so = s0;
+    // hidden side first: the state is there while the input rows are on their way
+    floatx16 acc[4];
+    turn();
+    put_block(h);
+    __syncthreads();                          // (first step: the biases are there, too)
+#pragma unroll
+    for (int g = 0; g < 4; ++g)
+      if (kLstm || g != 2) acc[g] = load_block(gbias + g * H + col0);
+    product<NG, DG>([&](int g) -> floatx16& { return acc[!kLstm && g == 2 ? 3 : g]; }, buf, wsh, offh, gsh, kbh, lane16, wg);
+    auto in = [&](int g) -> floatx16& { return acc[g]; };
+    if constexpr (!STACK) {
+      floatx16 z;
+      for (int k = 0; k < nchunk; ++k) {
+        const int n = min(kbc, nkb0 - k * kbc);
+        turn();
+        stage_x(s, k);
+        fetch_ahead<1, DZ>(wz, wsg, offz + k * kbc * kUnitBytes, 0, n, lane16);
+        if (k + 1 < nchunk) request_x(s, k + 1);
+        __syncthreads();
+        if (k == 0) z = load_block(zbias + col0);
+        product<1, DZ>([&](int) -> floatx16& { return z; }, buf, wsg, offz + k * kbc * kUnitBytes, 0, n, lane16, wz);
+      }
+      if (a.act == DGC_ACT_RELU) relu(z);
+      if constexpr (CAT) {                    // the other half of the time encoder's input first
+        fetch_ahead<NG, DG>(wg, wsi, offx, gsx, kbh, lane16);
+        int64_t r2 = slot(ts);
+        if (a.x2_map) r2 = max(a.x2_map[r2], (int64_t)0);   // an empty slot reads row 0; its output is not used
+        turn();
+        put_block(load_block(a.X2 + r2 * a.ldx2 + col0));
+        __syncthreads();
+        product<NG, DG>(in, buf, wsi, offx, gsx, kbh, lane16, wg);
+      }
+      fetch_ahead<NG, DG>(wg, wsi, offx + (kbx - kbh) * kUnitBytes, gsx, kbh, lane16);
+      turn();
+      put_block(z);
+    } else {
+      fetch_ahead<NG, DG>(wg, wsi, offx, gsx, kbh, lane16);
+      turn();
+      stage_x(s, 0);
+    }
+    __syncthreads();
+    if constexpr (!kLstm) acc[2] = load_block(gbias + 2 * H + col0);
+    product<NG, DG>(in, buf, wsi, offx + (kbx - kbh) * kUnitBytes, gsx, kbh, lane16, wg);
+    // requests of the next step go out before this step's stores: memory operations retire in order
+    if (mapped) {
+      yrow = yrow_next;
+      if (s + 1 < ch.w) yrow_next = (int)a.y_map[slot(ts + 1)];
+    }
+    if (s + 1 < ch.w) {
+      fetch_ahead<NG, DG>(wg, wsh, offh, gsh, kbh, lane16);
+      if constexpr (SEQ) request_state();
+      request_x(s + 1, 0);
+    }
+#pragma unroll
+    for (int v = 0; v < 16; ++v) {
+      if constexpr (kLstm) {                  // i, f, g, o
+        const float ig = sigmoid_fast(acc[0][v]), fg = sigmoid_fast(acc[1][v]);
+        const float gg = tanh_fast(acc[2][v]), og = sigmoid_fast(acc[3][v]);
+        c[v] = fg * c[v] + ig * gg;
+        h[v] = og * tanh_fast(c[v]);
+      } else {                                // r, z, input part of n, hidden part of n
+        const float r = sigmoid_fast(acc[0][v]), zg = sigmoid_fast(acc[1][v]);
+        const float n = tanh_fast(acc[2][v] + r * acc[3][v]);
+        h[v] = (1.0f - zg) * n + zg * h[v];
+      }
+    }
+    if (valid) {
+      const int64_t yr = mapped ? (int64_t)yrow : slot(ts);
+      if (yr >= 0) store_block(a.Y + yr * a.ldy + col0, h);
+      if (a.HN && so >= 0) {
+        store_block(a.HN + so * H + col0, h);
+        if constexpr (kLstm) store_block(a.HN + (V + so) * H + col0, c);
+      }
+    }
+    if (s + 1 < ch.w) enter(ts + 1);
+  }
+}
+
+// Transforms alone, Y = act(M W^T + b): a workgroup takes a run of the row tiles (ordered by snapshot).  Its waves
+// hold the weights, NKB k-blocks of them, and read them again only when the snapshot (and with it the weights)
+// changes; the rows of the next tile are on their way while a tile is multiplied.
+// kb0: first k-block of this launch (rows wider than the registers hold take a second launch, which goes on from Y).
+template <int NKB, int MAXW, bool FIRST>
+__global__ __launch_bounds__(64 * MAXW, 2) void k_rows_split(DenseArgs a, int kb0) {
+  constexpr int XP = NKB > 2 * MAXW ? 4 : 2;  // k-blocks that a wave requests ahead
+  extern __shared__ __align__(16) uint4 lds[];
+  const int njb = blockDim.x >> 6;
+  const int lane = threadIdx.x & 63, l32 = lane & 31, half = lane >> 5;
+  const int jb = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int nkb_all = (a.K0 + 15) / 16, nkb0 = min(nkb_all - kb0, NKB), col0 = 32 * jb + 4 * half;
+  const bool last = kb0 + nkb0 == nkb_all;
+  const bool two = a.kb_chunk == 2 * NKB;     // two staging buffers, or one
+  uint4* buf = lds + lane;
+  uint4* other = buf + (two ? NKB * 3 * kFrag : 0);
+  const float* zbias = reinterpret_cast<float*>(lds + a.kb_chunk * 3 * kFrag);
+  for (int i = threadIdx.x; i < 32 * njb; i += blockDim.x) const_cast<float*>(zbias)[i] = a.bg[i];
+  for (int i = threadIdx.x; i < a.kb_chunk * 3 * kFrag; i += blockDim.x) lds[i] = make_uint4(0, 0, 0, 0);   // k-blocks past the row stay zero
+  __syncthreads();
+  const int64_t i0 = a.n_row_tiles * blockIdx.x / gridDim.x, i1 = a.n_row_tiles * (blockIdx.x + 1) / gridDim.x;
+  float4 xq[XP][2];
+  auto kb_of = [&](int q) { return 2 * jb + (q / 2) * 2 * njb + q % 2; };
+  auto m_row = [&](const DenseTile& t, const ChunkInfo& ch) {
+    return a.M + (ch.row_off0 + (int64_t)t.step * ch.nv + t.v0 + min(l32, t.nrows - 1)) * a.ldm + 16 * kb0 + 4 * half;
+  };
+  auto request_x = [&](const float* p) {
+#pragma unroll
+    for (int q = 0; q < XP; ++q) load_x(p, min(kb_of(q), nkb0 - 1), xq[q]);
+  };
+  if (i0 >= i1) return;
+  DenseTile tile = table_entry(a.row_tiles, i0);
+  ChunkInfo ch = table_entry(a.chunks, tile.chunk);
+  request_x(m_row(tile, ch));
+  uint4 w[NKB][3];
+  int64_t have = -1;
+  for (int64_t i = i0; i < i1; ++i) {
+    const int64_t t = ch.t_lo + tile.step;
+    const int64_t want = a.wg_step_bytes ? t : 0;
+    if (want != have) {
+      const WeightStream ws = make_stream(reinterpret_cast<const char*>(a.Wg) + t * a.wg_step_bytes, (int64_t)njb * nkb_all * kUnitBytes);
+#pragma unroll
+      for (int k = 0; k < NKB; ++k) ws.unit(w[k], lane * 16, (jb * nkb_all + kb0 + k) * kUnitBytes, k < nkb0);
+      __builtin_amdgcn_s_waitcnt(0x0f70);     // vmcnt 0, here: else every tile would wait for the weights, and so for the stores before it
+      have = want;
+    }
+    if (two) { uint4* x = buf; buf = other; other = x; }
+    else __syncthreads();
+#pragma unroll
+    for (int q = 0; q < XP; ++q)
+      if (kb_of(q) < nkb0) put_x(buf + kb_of(q) * 3 * kFrag, xq[q]);
+    for (int kb = kb_of(XP); kb < nkb0; kb += 2 * njb)
+#pragma unroll
+      for (int q = 0; q < 2; ++q)
+        if (kb + q < nkb0) {
+          float4 x[2];
+          load_x(m_row(tile, ch), kb + q, x);
+          put_x(buf + (kb + q) * 3 * kFrag, x);
+        }
+    const int nrows = tile.nrows;
+    float* y = a.Y + (t * a.N + ch.v_lo + tile.v0 + l32) * a.ldy + col0;
+    if (i + 1 < i1) {
+      tile = table_entry(a.row_tiles, i + 1);
+      ch = table_entry(a.chunks, tile.chunk);
+      request_x(m_row(tile, ch));
+    }
+    __syncthreads();
+    floatx16 z = load_block(zbias + col0);
+    if constexpr (!FIRST) {
+      if (l32 < nrows) z = load_block(y);
+    }
+    uint4 b[2][3];                            // the operands one k-block ahead
+#pragma unroll
+    for (int p = 0; p < 3; ++p) b[0][p] = buf[p * kFrag];
+#pragma unroll
+    for (int k = 0; k < NKB; ++k) {
+      if (k + 1 < NKB) {
+#pragma unroll
+        for (int p = 0; p < 3; ++p) b[(k + 1) % 2][p] = buf[((k + 1) * 3 + p) * kFrag];
+      }
+      six(z, w[k], b[k % 2]);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    if (last && a.act == DGC_ACT_RELU) relu(z);
+    if (l32 < nrows) store_block(y, z);
+  }
+}
+
+// W [n_out][n_in] (strides so, si) -> three bf16 parts per fragment: packed[((jb*nkb + kb)*3 + part)*64 + lane] holds of
+// row jb*32 + lane%32 the columns 16*kb + 8*p + 4*(lane/32) + e (p = 0, 1; e = 0..3), zero beyond n_in.
+// The middle and low parts of a weight that is not zero keep its sign and are never zero (2^-126 stands in),
+// so that an infinite activation times the three parts is the infinity that it is in fp32, not infinity times zero.
+__global__ void k_pack_split(const float* W, int64_t per_w, int64_t so, int64_t si, int32_t n_out, int32_t n_in, int64_t count,
+                             uint4* packed) {
+  const int nkb = (n_in + 15) / 16;
+  const int64_t per = (int64_t)(n_out / 32) * nkb * 64;
+  const int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (idx >= per * count) return;
+  const int64_t m = idx / per, i = idx - m * per;
+  const int lane = (int)(i & 63);
+  const int64_t f = i >> 6;
+  const int kb = (int)(f % nkb);
+  const int64_t out = (f / nkb) * 32 + (lane & 31);
+  const float* w = W + m * per_w + out * so;
+  uint16_t part[3][8];
+  for (int k = 0; k < 8; ++k) {
+    const int col = 16 * kb + 8 * (k / 4) + 4 * (lane >> 5) + k % 4;
+    const float x = col < n_in ? w[col * si] : 0.f;
+    const float sign = copysignf(1.1754943508222875e-38f, x);
+    const bool real = fabsf(x) > 7.9e-31f && fabsf(x) < __builtin_inff();     // 2^-100: below it the stand-in would count
+    float md = fabsf(x) == __builtin_inff() ? 0.f : x - cut(x);
+    float lo = md - cut(md);
+    if (real && cut(md) == 0.f) md = sign;
+    if (real && cut(lo) == 0.f) lo = sign;
+    part[0][k] = (uint16_t)(__float_as_uint(x) >> 16);
+    part[1][k] = (uint16_t)(__float_as_uint(md) >> 16);
+    part[2][k] = (uint16_t)(__float_as_uint(lo) >> 16);
+  }
+  for (int p = 0; p < 3; ++p) {
+    uint32_t u[4];
+    for (int k = 0; k < 4; ++k) u[k] = part[p][2 * k] | (uint32_t)part[p][2 * k + 1] << 16;
+    packed[((m * per + (f << 6)) * 3 + p * 64) + lane] = make_uint4(u[0], u[1], u[2], u[3]);
+  }
+}
+
+constexpr size_t kMaxLds = 160 * 1024;
+constexpr int kCus = 256;
+
+template <class Kernel>
+bool allow_lds(Kernel* kernel, std::atomic<uint64_t>& ready, std::string* why) {   // ready: devices where it is done
+  int dev = 0;
+  (void)hipGetDevice(&dev);
+  const uint64_t bit = 1ull << (dev & 63);
+  if (ready.load(std::memory_order_relaxed) & bit) return true;
+  const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize,
+                                           (int)kMaxLds);
+  if (e != hipSuccess) {
+    if (why) *why = std::string("hipFuncSetAttribute: ") + hipGetErrorString(e);
+    return false;
+  }
+  ready.fetch_or(bit, std::memory_order_relaxed);
+  return true;
+}
+
+template <int KIND, bool SEQ, bool CAT, bool STACK, int MAXW>
+bool launch_time(DenseArgs a, int njb, hipStream_t st, std::string* why) {
+  const int nkb0 = STACK ? 2 * njb : (a.K0 + 15) / 16;
+  // a staging buffer holds the state's k-blocks, and of a wider input row what 48 KB take
+  a.kb_chunk = std::max(2 * njb, std::min(nkb0, 48 * 1024 / kUnitBytes));
+  const size_t lds = (size_t)2 * a.kb_chunk * kUnitBytes + sizeof(float) * 5 * 32 * njb;
+  static std::atomic<uint64_t> ready{0};
+  auto* kernel = &k_dense_split<KIND, SEQ, CAT, STACK, MAXW>;
+  if (!allow_lds(kernel, ready, why)) return false;
+  if (a.n_tiles32 > 0) hipLaunchKernelGGL(kernel, (unsigned)a.n_tiles32, 64 * njb, lds, st, a);
+  return true;
+}
+
+template <int KIND, int MAXW>
+bool launch_variant(const DenseArgs& a, int njb, hipStream_t st, std::string* why) {
+  const bool seq = a.seq_in != nullptr;
+  if (a.input_is_z) return seq ? launch_time<KIND, true, false, true, MAXW>(a, njb, st, why)
+                               : launch_time<KIND, false, false, true, MAXW>(a, njb, st, why);
+  if constexpr (KIND == DGC_TIME_LSTM) {
+    if (a.X2) return seq ? launch_time<KIND, true, true, false, MAXW>(a, njb, st, why)
+                         : launch_time<KIND, false, true, false, MAXW>(a, njb, st, why);
+  }
+  return seq ? launch_time<KIND, true, false, false, MAXW>(a, njb, st, why)
+             : launch_time<KIND, false, false, false, MAXW>(a, njb, st, why);
+}
+
+template <int KIND>
+bool launch_kind(const DenseArgs& a, int njb, hipStream_t st, std::string* why) {
+  return njb <= 4 ? launch_variant<KIND, 4>(a, njb, st, why) : launch_variant<KIND, 8>(a, njb, st, why);
+}
+
+template <int NKB, int MAXW, bool FIRST>
+bool launch_rows(DenseArgs a, int kb0, hipStream_t st, std::string* why) {
+  const int njb = a.S / 32;
+  // eight waves per CU hold 256 registers each; two staging buffers if they then still fit
+  const int per_cu = 8 / njb > 0 ? 8 / njb : 1;
+  const size_t one = (size_t)NKB * kUnitBytes, bias = sizeof(float) * 32 * njb;
+  const bool two = (2 * one + bias) * per_cu <= kMaxLds;
+  a.kb_chunk = two ? 2 * NKB : NKB;
+  const size_t lds = a.kb_chunk * kUnitBytes + bias;
+  static std::atomic<uint64_t> ready{0};
+  auto* kernel = &k_rows_split<NKB, MAXW, FIRST>;
+  if (!allow_lds(kernel, ready, why)) return false;
+  const int64_t grid = std::min<int64_t>(a.n_row_tiles, (int64_t)kCus * per_cu);
+  if (grid > 0) hipLaunchKernelGGL(kernel, (unsigned)grid, 64 * njb, lds, st, a, kb0);
+  return true;
+}
+
+template <int MAXW, bool FIRST>
+bool launch_rows_k(const DenseArgs& a, int kb0, hipStream_t st, std::string* why) {
+  switch ((std::min((a.K0 + 15) / 16 - kb0, 16) + 1) / 2) {
+    case 1: return launch_rows<2, MAXW, FIRST>(a, kb0, st, why);
+    case 2: return launch_rows<4, MAXW, FIRST>(a, kb0, st, why);
+    case 3: return launch_rows<6, MAXW, FIRST>(a, kb0, st, why);
+    case 4: return launch_rows<8, MAXW, FIRST>(a, kb0, st, why);
+    case 5: return launch_rows<10, MAXW, FIRST>(a, kb0, st, why);
+    case 6: return launch_rows<12, MAXW, FIRST>(a, kb0, st, why);
+    case 7: return launch_rows<14, MAXW, FIRST>(a, kb0, st, why);
+    case 8: return launch_rows<16, MAXW, FIRST>(a, kb0, st, why);
+  }
+  return false;
+}
+
+template <int MAXW>
+bool launch_transform(const DenseArgs& a, hipStream_t st, std::string* why) {
+  if (!launch_rows_k<MAXW, true>(a, 0, st, why)) return false;
+  return a.K0 <= 256 || launch_rows_k<MAXW, false>(a, 16, st, why);
+}
+
+}  // namespace
+
+bool dense_split_supported(int32_t S, int32_t H, int32_t time_kind) {
+  return S % 32 == 0 && S >= 32 && S <= 256 && (time_kind == DGC_TIME_NONE || H == S);
+}
+
+bool launch_dense_split(const DenseArgs& a, hipStream_t st, std::string* why) {
+  const int njb = a.S / 32;
+  switch (a.time_kind) {
+    case DGC_TIME_NONE: return njb <= 4 ? launch_transform<4>(a, st, why) : launch_transform<8>(a, st, why);
+    case DGC_TIME_GRU: return launch_kind<DGC_TIME_GRU>(a, njb, st, why);
+    case DGC_TIME_LSTM: return launch_kind<DGC_TIME_LSTM>(a, njb, st, why);
+  }
+  return false;
+}
+
+void launch_pack_split(const float* W, int64_t per_w, int64_t out_stride, int64_t in_stride, int32_t n_out, int32_t n_in,
+                       int64_t count, void* packed, hipStream_t st) {
+  const int64_t total = count * (n_out / 32) * ((n_in + 15) / 16) * 64;
+  if (total > 0)
+    hipLaunchKernelGGL(k_pack_split, (unsigned)((total + 255) / 256), 256, 0, st, W, per_w, out_stride, in_stride, n_out, n_in,
+                       count, static_cast<uint4*>(packed));
+}
+
+}  // namespace dgc

@@ -13,7 +13,7 @@ namespace dgc {
 
 constexpr int kWave = 64;
 constexpr int kTileRows = 64;      // rows of one tile of the workgroup-tile dense kernel
-constexpr int kWaveTileRows = 32;  // rows of one tile of the wave-private dense kernel
+constexpr int kWaveTileRows = 32;  // rows of one tile of the split dense kernels and the weight-gradient kernel
 
 // One (chunk, snapshot) pair of the fused batch.
 struct Segment {
@@ -42,7 +42,7 @@ struct DenseTile {
   int32_t chunk;
   int32_t v0;     // first vertex, relative to the chunk's v_lo
   int32_t nrows;
-  int32_t pad;
+  int32_t step;   // in a list of row tiles: the snapshot within the chunk's window
 };
 
 struct GraphDev {
@@ -148,8 +148,11 @@ inline int64_t packed_weight_elems(int32_t n_out, int32_t n_in) {
 struct DenseArgs {
   const DenseTile* tiles;       // 64-row tiles
   int64_t n_tiles;
-  const DenseTile* tiles32;     // 32-row tiles
+  const DenseTile* tiles32;     // 32-row tiles of the split kernel
   int64_t n_tiles32;
+  const DenseTile* row_tiles;   // 32-row tiles of single snapshots, ordered by snapshot (transforms alone)
+  int64_t n_row_tiles;
+  int32_t kb_chunk;             // set by the launch: k-blocks of 16 that a staging buffer holds
   int32_t variant;              // DGC_DENSE_*
   const ChunkInfo* chunks;
   int64_t N;
@@ -160,8 +163,7 @@ struct DenseArgs {
   int32_t act;                  // activation after the GCN transform
   int32_t time_kind;
   const float4* Wg;             // packed GCN weight [S][K0] (one per snapshot if wg_step_bytes != 0)
-  int64_t wg_bytes;             // size of the packed GCN weights
-  int32_t wg_step_bytes;        // distance between consecutive snapshots' packed weights, or 0
+  int64_t wg_step_bytes;        // distance between consecutive snapshots' packed weights, or 0
   const float* bg;              // [S]
   const float4* Wih;            // packed [gH][S] ([gH][2S] with X2)
   const float4* Whh;            // packed [gH][H]
@@ -185,17 +187,24 @@ struct DenseArgs {
   // x2_map[t*N + v] (negative: any row, the output is not used), or t*N + v without a map.
   const float* X2; int64_t ldx2;
   const int64_t* x2_map;
-  // A stacked recurrent layer (wave-private kernel only): the rows of M are rows t*N + v of a
+  // A stacked recurrent layer (split kernel only): the rows of M are rows t*N + v of a
   // [T,N,ldm] tensor (m_by_vertex) and are the time encoder's input as they are (input_is_z: no
-  // transform, K0 = 0; Wg must still name readable packed weights, its fragments are prefetched).
+  // transform, K0 = 0).
   // M may be Y itself: a wave reads row (t, v) in step t and writes it one step later.
   bool m_by_vertex;
   bool input_is_z;
 };
 // returns false if the (S,H,K0) combination has no kernel
 bool launch_dense(const DenseArgs& a, hipStream_t st, std::string* why);
-bool dense_wave_supported(const DenseArgs& a);
-bool launch_dense_wave(const DenseArgs& a, hipStream_t st, std::string* why);
+// The split kernel (dgc_dense_split.hip) takes weights as three bf16 parts per fragment of 32 x 16, see k_pack_split.
+bool dense_split_supported(int32_t S, int32_t H, int32_t time_kind);
+bool launch_dense_split(const DenseArgs& a, hipStream_t st, std::string* why);
+inline int64_t split_weight_bytes(int32_t n_out, int32_t n_in) {
+  return (int64_t)(n_out / 32) * ((n_in + 15) / 16) * 3 * 64 * 16;
+}
+// `count` matrices, per_w floats apart, element (out, in) at out * out_stride + in * in_stride
+void launch_pack_split(const float* W, int64_t per_w, int64_t out_stride, int64_t in_stride, int32_t n_out, int32_t n_in,
+                       int64_t count, void* packed, hipStream_t st);
 size_t dense_lds_bytes(int32_t K0, int32_t S, int32_t H);
 int dense_ld(int32_t K0, int32_t S, int32_t H);
 
@@ -204,6 +213,7 @@ enum { EV_W = 0, EV_UZ, EV_VZ, EV_BZ, EV_UR, EV_VR, EV_BR, EV_UH, EV_VH, EV_BH, 
 
 struct EvolveWs {
   int32_t T, F, S;
+  bool split;                // the transforms run the split dense kernel
   const float* P[EV_NPAR];   // parameters (device, fp32): W_init, Uz, Vz, Bz, Ur, Vr, Br, Uh, Vh, Bh
   float* G[EV_NPAR];         // their gradients (fp32, what the caller reads)
   double* Pd[EV_NPAR];       // the parameters widened to double for the weight recurrence
@@ -215,7 +225,7 @@ struct EvolveWs {
   float* dWd;                // [T][F][S] direct gradient of each W_t
   float* partial;            // [T][split][F][S]
   float* loss_partial;       // [T][split]
-  const DenseTile* items;    // 32-row tiles ordered by snapshot
+  const DenseTile* items;    // 32-row tiles ordered by snapshot (the layer's row tiles)
   const int64_t* item_ptr;   // [T+1]
 };
 
@@ -230,6 +240,10 @@ struct EvolveBwdIn {
   float* loss_out;           // device, or nullptr
 };
 
+// one snapshot's weights, packed for the dense kernel that runs them
+inline int64_t evolve_packed_bytes(const EvolveWs& ws, bool split) {
+  return split ? split_weight_bytes(ws.S, ws.F) : (int64_t)sizeof(float) * packed_weight_elems(ws.S, ws.F);
+}
 int64_t evolve_partial_elems(int32_t T, int32_t F, int32_t S);
 int64_t evolve_loss_partial_elems(int32_t T);
 void evolve_forward_weights(const EvolveWs& ws, hipStream_t st);

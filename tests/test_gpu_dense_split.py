@@ -1,0 +1,59 @@
+"""The split dense kernels (fp32 products as sums of bf16 products) against the oracle, at the sizes where they can go
+wrong: widths of one and of eight column blocks and those between, input widths that leave a part of the last
+k-block (or of the second launch of a wide transform) empty, chunks that end inside a tile.  The oracle's products are
+double; the bar is the repository's fp32 one."""
+import numpy as np
+import pytest
+
+import oracle
+from refs import rel_err
+from workloads import synth
+
+pytestmark = pytest.mark.gpu
+
+CASES = [  # F, S, time encoder, GCN layers, chunk bounds over 70 vertices
+    (1, 32, "gru", 1, (0, 1, 33, 70)),
+    (17, 64, "lstm", 1, (0, 31, 63, 70)),
+    (50, 96, "gru", 1, (0, 32, 70)),
+    (96, 160, "lstm", 1, (0, 64, 70)),
+    (128, 128, "gru", 2, (0, 33, 70)),
+    (172, 128, "lstm", 2, (0, 70)),
+    (250, 192, "gru", 1, (0, 7, 70)),
+    (300, 256, "lstm", 1, (0, 70)),
+    (500, 64, "gru", 1, (0, 70)),
+    (3, 32, "none", 1, (0, 1, 33, 70)),
+    (16, 96, "none", 2, (0, 31, 70)),
+    (240, 256, "none", 1, (0, 65, 70)),
+    (257, 128, "none", 1, (0, 70)),
+    (500, 256, "none", 1, (0, 33, 70)),
+]
+
+
+@pytest.mark.parametrize("F,S,kind,layers,bounds", CASES)
+def test_split_dense_shapes(F, S, kind, layers, bounds):
+    from paper_2309_03523_amd.runner import run_forward
+    chunks = synth.grid_chunks(5, 3, [np.asarray(bounds)] * 2)
+    wl = synth.random_small(F + S, 5, 70, F, S, S, 4.0, chunks, kind, layers)
+    Y = run_forward(wl)
+    want = oracle.forward(wl.graph, wl.chunks, wl.params, wl.X, wl.C, time_kind=kind, C1=wl.C1, H0=wl.H0,
+                          n_struct_layers=layers)
+    assert rel_err(Y, want) < 1e-4
+
+
+def test_split_dense_infinite_input():
+    """An infinite input gives the infinities (and the NaN where opposite ones meet) that fp32 products give."""
+    from paper_2309_03523_amd.runner import run_forward
+    wl = synth.random_small(3, 2, 50, 40, 64, 64, 0.0, [[0, 50, 0, 2]], "none")     # no edges: a row sees itself
+    wl.X[0, 5, 7] = np.inf
+    wl.X[1, 33, 0] = -np.inf
+    wl.X[1, 40, 39] = np.nan
+    wl.X[0, 6, :2] = 3e38
+    Y = run_forward(wl)
+    with np.errstate(all="ignore"):
+        want = (wl.X.astype(np.float64) @ wl.params["gcn0.weight"].astype(np.float64).T + wl.params["gcn0.bias"])
+        want = want.astype(np.float32)
+    assert np.array_equal(np.isnan(Y), np.isnan(want))
+    assert np.array_equal(np.isposinf(Y), np.isposinf(want)) and np.array_equal(np.isneginf(Y), np.isneginf(want))
+    keep = np.ones((2, 50), bool)
+    keep[0, 5:7] = keep[1, 33] = keep[1, 40] = False
+    assert rel_err(Y[keep], want[keep]) < 1e-4
