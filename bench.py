@@ -113,7 +113,7 @@ def parity_numbers(got, want) -> dict:
             "p999_unfloored": float(np.quantile(d[nz] / a[nz], 0.999)) if nz.any() else 0.0}
 
 
-AGG_KERNELS = {"table": "k_agg_short + k_agg_long + k_spmm_long_reduce (edge-table kernels)",
+AGG_KERNELS = {"table": "k_agg + k_spmm_long_reduce (edge-table kernels)",
                "walk": "k_spmm_short + k_spmm_long + k_spmm_long_reduce (column-walking kernels)"}
 
 

@@ -80,8 +80,8 @@ enum { DGC_GATHER_IN_PLACE = 0, DGC_GATHER_STAGED = 1 };
 enum { DGC_DENSE_AUTO = 0, DGC_DENSE_TILE = 1, DGC_DENSE_WAVE = 2 };
 /* Which kernels aggregate in IN_PLACE mode (STAGED always takes WALK):
  *  TABLE  kernels that read a per-non-zero table built at create (8 bytes per stored non-zero: the column,
- *         marked fresh / cache, and the neighbour's degree scaling); needs equal pitches of X and C and
- *         F <= 256, else WALK runs;
+ *         marked fresh / cache, and the neighbour's degree scaling); needs equal pitches of X and C,
+ *         else WALK runs;
  *  WALK   kernels that walk colidx, test the chunk range and look the scaling up (no table).
  * Results differ only in summation order. */
 enum { DGC_AGG_TABLE = 0, DGC_AGG_WALK = 1 };

@@ -12,6 +12,8 @@
 // address is wave-uniform.  Eight neighbour rows are in flight per wave.  Rows of 65 to 128
 // floats take the two-rows-per-load variant instead (each half of the wave one neighbour, 16
 // bytes per lane, sixteen rows in flight).
+#include <algorithm>
+
 #include "dgc_internal.h"
 
 namespace dgc {
@@ -335,7 +337,7 @@ __global__ __launch_bounds__(256) void k_spmm_long_reduce(SpmmArgs a) {
 
 // ---------------------------------------------------------------------------------------------
 // Second generation of the aggregation kernels (IN_PLACE and generated chunks, equal pitches of the
-// fresh and the cache tensor, rows of at most 256 floats).  The first generation above spends some
+// fresh and the cache tensor).  The first generation above spends some
 // thirty vector instructions per gathered row on broadcasting column ids, range tests and 64-bit
 // address arithmetic, and is bound by instruction issue, not by memory.  Here the per-non-zero
 // work is prepared once, at packing time, in an edge table (SpmmArgs::etab): a lane reads the
@@ -412,20 +414,26 @@ __device__ __forceinline__ void agg_range(const int2* tab, int pos, int end, int
   }
 }
 
-// Write one output row: columns < F scaled, columns F .. ldm-1 zero.  Lane l of the writing group
-// owns columns 4l .. 4l+3 and, if the pitch is wider than the group, the same columns of every
-// further stretch of 4 * LPR.
+// A launch's columns [c0, c1) of the output rows: all of them, or for rows of more than 256 floats one of two
+// stretches (c1 of the last stretch is the pitch).
+struct AggCols {
+  int32_t c0, c1;
+};
+
+// Write this launch's columns of one output row: columns < F scaled, the others (up to the pitch) zero.  Lane l of
+// the writing group owns columns c0 + 4l .. +3 and, if there are more than the group spans, the same columns of
+// every further stretch of 4 * LPR.
 template <int LPR>
-__device__ __forceinline__ void agg_store(float* out, int l, int F, int64_t ldm, const float (&acc)[4], float scale) {
-  const int fi = 4 * l;
-  if (fi < ldm) {
+__device__ __forceinline__ void agg_store(float* out, int l, AggCols cols, int F, const float (&acc)[4], float scale) {
+  const int fi = cols.c0 + 4 * l;
+  if (fi < cols.c1) {
     float o[4];
 #pragma unroll
     for (int q = 0; q < 4; ++q) o[q] = (fi + q < F) ? acc[q] * scale : 0.f;
     vstore<4>(out + fi, o);
   }
   const float z[4] = {0.f, 0.f, 0.f, 0.f};
-  for (int c = fi + 4 * LPR; c < ldm; c += 4 * LPR) vstore<4>(out + c, z);
+  for (int c = fi + 4 * LPR; c < cols.c1; c += 4 * LPR) vstore<4>(out + c, z);
 }
 
 template <int LPR>
@@ -446,10 +454,10 @@ struct AggCtx {
 };
 
 template <int LPR>
-__device__ __forceinline__ AggCtx agg_ctx(const SpmmArgs& a, const Segment& sg, int64_t first_e, int l) {
+__device__ __forceinline__ AggCtx agg_ctx(const SpmmArgs& a, const Segment& sg, int64_t first_e, int l, int c0) {
   AggCtx c;
   c.tab = a.etab + sg.nnz_off + (first_e - sg.e0);
-  const int fi = (4 * l < a.F) ? 4 * l : 0;     // lanes past the row's end re-read its first columns (never stored)
+  const int fi = (c0 + 4 * l < a.F) ? c0 + 4 * l : c0;     // lanes past the row's end re-read its first columns (never stored)
   const int64_t snap = (int64_t)sg.t * a.g.N * a.ld_fresh;
   c.fresh_l = reinterpret_cast<const char*>(a.fresh + snap + fi);
   c.stale_l = reinterpret_cast<const char*>(a.stale + snap + fi);
@@ -458,11 +466,9 @@ __device__ __forceinline__ AggCtx agg_ctx(const SpmmArgs& a, const Segment& sg, 
 }
 
 template <int LPR, bool SKIP>
-__global__ __launch_bounds__(256) void k_agg_short(SpmmArgs a) {
+__device__ __forceinline__ void agg_short(const SpmmArgs& a, AggCols cols, int64_t item) {
   constexpr int G = 64 / LPR;
   const int lane = threadIdx.x & (kWave - 1);
-  const int64_t wave = (int64_t)blockIdx.x * (256 / kWave) + (threadIdx.x / kWave);
-  const int64_t item = wave;
   if (item >= a.n_short) return;
   const int seg = uniform(a.work_short[3 * item + 0]);
   const int r0 = uniform(a.work_short[3 * item + 1]);
@@ -472,7 +478,7 @@ __global__ __launch_bounds__(256) void k_agg_short(SpmmArgs a) {
   const int64_t* rp = a.g.rowptr[sg.t] + sg.v_lo + r0;
   const int64_t rp0 = rp[0];
   const int my_rel = lane <= n ? (int)(rp[lane] - rp0) : 0;     // lanes 0..n: row offsets relative to the group's start
-  const AggCtx c = agg_ctx<LPR>(a, sg, rp0, l);
+  const AggCtx c = agg_ctx<LPR>(a, sg, rp0, l, cols.c0);
   const float* dinv_rows = a.dinv + (int64_t)sg.t * a.g.N + sg.v_lo + r0;
   const int64_t prow0 = sg.row_off + r0;
   const int64_t ldo = a.ld_out ? a.ld_out : a.ldm;
@@ -489,7 +495,7 @@ __global__ __launch_bounds__(256) void k_agg_short(SpmmArgs a) {
       agg_range<LPR, SKIP>(c.tab, e_r + g * kU, e_r1, kU * G, (int)(sg.v_lo + r0 + r), c.fresh_l, c.stale_l, c.ld_bytes, acc);
       agg_reduce_groups<LPR>(acc);
       const int64_t orow = a.row_map ? a.row_map[prow0 + r] : prow0 + r;
-      if (g == 0) agg_store<LPR>(a.M + orow * ldo, l, a.F, a.ldm, acc, dinv_rows[r]);
+      if (g == 0) agg_store<LPR>(a.M + orow * ldo, l, cols, a.F, acc, dinv_rows[r]);
       todo &= todo - 1;
     } else {
       // up to G of the next wanted small rows, one per lane group
@@ -507,18 +513,16 @@ __global__ __launch_bounds__(256) void k_agg_short(SpmmArgs a) {
       const int b = __shfl(my_rel, mine), e = __shfl(my_rel, mine + 1);
       agg_range<LPR, SKIP>(c.tab, b, g < take ? e : b, kU, (int)(sg.v_lo + r0 + mine), c.fresh_l, c.stale_l, c.ld_bytes, acc);
       const int64_t orow = a.row_map ? a.row_map[prow0 + mine] : prow0 + mine;
-      if (g < take) agg_store<LPR>(a.M + orow * ldo, l, a.F, a.ldm, acc, dinv_rows[mine]);
+      if (g < take) agg_store<LPR>(a.M + orow * ldo, l, cols, a.F, acc, dinv_rows[mine]);
     }
   }
 }
 
 // One wave per part of a split row: unscaled partial sums.
 template <int LPR, bool SKIP>
-__global__ __launch_bounds__(256) void k_agg_long(SpmmArgs a) {
+__device__ __forceinline__ void agg_long(const SpmmArgs& a, AggCols cols, int64_t item) {
   constexpr int G = 64 / LPR;
   const int lane = threadIdx.x & (kWave - 1);
-  const int64_t wave = (int64_t)blockIdx.x * (256 / kWave) + (threadIdx.x / kWave);
-  const int64_t item = wave;
   if (item >= a.n_long) return;
   const int seg = uniform(a.work_long[4 * item + 0]);
   const int row = uniform(a.work_long[4 * item + 1]);
@@ -530,27 +534,46 @@ __global__ __launch_bounds__(256) void k_agg_long(SpmmArgs a) {
   const int64_t ra = rp[0], rb = rp[1];
   const int64_t ea = ra + (int64_t)part * a.part_nnz;
   const int len = (int)((ea + a.part_nnz < rb ? ea + a.part_nnz : rb) - ea);
-  const AggCtx c = agg_ctx<LPR>(a, sg, ea, l);
+  const AggCtx c = agg_ctx<LPR>(a, sg, ea, l, cols.c0);
   float acc[4] = {0.f, 0.f, 0.f, 0.f};
   agg_range<LPR, SKIP>(c.tab, g * kU, len, kU * G, (int)(sg.v_lo + row), c.fresh_l, c.stale_l, c.ld_bytes, acc);
   agg_reduce_groups<LPR>(acc);
-  if (g == 0) agg_store<LPR>(a.partial + item * a.ldm, l, a.F, a.ldm, acc, 1.0f);
+  if (g == 0) agg_store<LPR>(a.partial + item * a.ldm, l, cols, a.F, acc, 1.0f);
+}
+
+// One launch for both lists, the split rows first: a part of one is the longest work there is, and on a small graph
+// a launch of its own waits for one.  As two launches and as one: 12 345 vertices x 10 snapshots, F = 50, 94 and
+// 72 us; 40 000 x 32, F = 172, 1.27 and 1.22 ms; 100 000 x 32, F = 128, 3.01 and 2.96 ms.
+template <int LPR, bool SKIP>
+__global__ __launch_bounds__(256) void k_agg(SpmmArgs a, AggCols cols, int64_t long_blocks) {
+  const int64_t block = blockIdx.x, wave = threadIdx.x / kWave;
+  if (block < long_blocks) agg_long<LPR, SKIP>(a, cols, block * (256 / kWave) + wave);
+  else agg_short<LPR, SKIP>(a, cols, (block - long_blocks) * (256 / kWave) + wave);
 }
 
 template <int LPR>
-void launch_agg(const SpmmArgs& a, hipStream_t st) {
-  const unsigned gs = (unsigned)((a.n_short + 3) / 4), gl = (unsigned)((a.n_long + 3) / 4);
-  if (gs) {
-    if (a.skip_stale) hipLaunchKernelGGL((k_agg_short<LPR, true>), gs, 256, 0, st, a);
-    else hipLaunchKernelGGL((k_agg_short<LPR, false>), gs, 256, 0, st, a);
+void launch_agg(const SpmmArgs& a, AggCols cols, hipStream_t st) {
+  const int64_t gs = (a.n_short + 3) / 4, gl = (a.n_long + 3) / 4;
+  if (gs + gl == 0) return;
+  if (a.skip_stale) hipLaunchKernelGGL((k_agg<LPR, true>), (unsigned)(gs + gl), 256, 0, st, a, cols, gl);
+  else hipLaunchKernelGGL((k_agg<LPR, false>), (unsigned)(gs + gl), 256, 0, st, a, cols, gl);
+}
+
+// Rows wider than the 256 floats that a wave's lanes span go in stretches: 2.4 M gathers of 300 floats (uniform over
+// 20 000 vertices, 8 snapshots) as 256 + 44 take 514 us where the column-walking kernels took 853.
+void launch_agg_all(const SpmmArgs& a, hipStream_t st) {
+  for (int32_t c0 = 0; c0 < a.F; c0 += 256) {
+    const int32_t n = std::min(a.F - c0, 256);
+    const AggCols cols{c0, c0 + n < a.F ? c0 + n : (int32_t)a.ldm};
+    if (n <= 64) launch_agg<16>(a, cols, st);
+    else if (n <= 128) launch_agg<32>(a, cols, st);
+    else launch_agg<64>(a, cols, st);
   }
-  if (gl) {
-    if (a.skip_stale) hipLaunchKernelGGL((k_agg_long<LPR, true>), gl, 256, 0, st, a);
-    else hipLaunchKernelGGL((k_agg_long<LPR, false>), gl, 256, 0, st, a);
-    if (a.ldm <= 64) hipLaunchKernelGGL((k_spmm_long_reduce<1>), gl, 256, 0, st, a);
-    else if (a.ldm <= 128) hipLaunchKernelGGL((k_spmm_long_reduce<2>), gl, 256, 0, st, a);
-    else hipLaunchKernelGGL((k_spmm_long_reduce<4>), gl, 256, 0, st, a);
-  }
+  const unsigned gl = (unsigned)((a.n_long + 3) / 4);
+  if (!gl) return;
+  if (a.ldm <= 64) hipLaunchKernelGGL((k_spmm_long_reduce<1>), gl, 256, 0, st, a);
+  else if (a.ldm <= 128) hipLaunchKernelGGL((k_spmm_long_reduce<2>), gl, 256, 0, st, a);
+  else hipLaunchKernelGGL((k_spmm_long_reduce<4>), gl, 256, 0, st, a);
 }
 
 // etab[p] = (marked column, scaling of the neighbour) for packed non-zero p
@@ -619,11 +642,9 @@ void launch_edge_table(const GraphDev& g, const Segment* segs, int64_t nseg, int
 
 
 void launch_spmm(const SpmmArgs& a, hipStream_t st) {
-  // the edge-table kernels: rows read in place, one pitch for both sources, at most 256 columns
-  if (a.etab && !a.halo && a.ld_fresh == a.ld_stale && a.F <= 256 && a.ld_fresh * 4 < (int64_t(1) << 31)) {
-    if (a.F <= 64) launch_agg<16>(a, st);
-    else if (a.F <= 128) launch_agg<32>(a, st);
-    else launch_agg<64>(a, st);
+  // the edge-table kernels: rows read in place, one pitch for both sources
+  if (a.etab && !a.halo && a.ld_fresh == a.ld_stale && a.ld_fresh * 4 < (int64_t(1) << 31)) {
+    launch_agg_all(a, st);
     return;
   }
   if (a.F <= 64) launch_spmm_v<1>(a, st);
