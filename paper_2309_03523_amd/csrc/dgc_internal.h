@@ -221,7 +221,9 @@ struct EvolveWs {
   double *Wt, *Zg, *Rg, *Wc; // [T][F][S]: evolved weights and the gates that produced them
   float* Wt_f32;             // [T][F][S]: W_t rounded to fp32
   float4* Wt_packed;         // every W_t^T (fp32) in MFMA fragment order
-  double* tmp[6];            // [F][S] scratch
+  double* tmp[3];            // [F][S] scratch
+  double *zsum, *rsum;       // U_z + V_z, U_r + V_r
+  double *back0[3], *back1[3];   // dA_h, dA_z, Rg * W of even and odd steps of the back-propagation
   float* dWd;                // [T][F][S] direct gradient of each W_t
   float* partial;            // [T][split][F][S]
   float* loss_partial;       // [T][split]
