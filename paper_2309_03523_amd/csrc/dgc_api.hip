@@ -326,8 +326,11 @@ dgc_status_t build_evolve(dgc_layer* L, const std::vector<ChunkInfo>& cinfo, hip
   for (double*& t : ev.back0) DGC_HIP_TRY(dev_alloc(L, &t, n));
   for (double*& t : ev.back1) DGC_HIP_TRY(dev_alloc(L, &t, n));
   DGC_HIP_TRY(dev_alloc(L, &ev.dWd, T * n));
-  DGC_HIP_TRY(dev_alloc(L, &ev.partial, evolve_partial_elems(T, F, S)));
-  DGC_HIP_TRY(dev_alloc(L, &ev.loss_partial, evolve_loss_partial_elems(T)));
+  int64_t most = 1;
+  for (int32_t t = 0; t < T; ++t) most = std::max(most, L->row_tile_ptr[t + 1] - L->row_tile_ptr[t]);
+  ev.split_dw = evolve_dw_split(T, F, most);
+  DGC_HIP_TRY(dev_alloc(L, &ev.partial, evolve_partial_elems(ev)));
+  DGC_HIP_TRY(dev_alloc(L, &ev.loss_partial, evolve_loss_partial_elems(ev)));
   DGC_HIP_TRY(dev_alloc(L, &L->d_zero_bias, S));
   DGC_HIP_TRY(hipMemsetAsync(L->d_zero_bias, 0, sizeof(float) * S, st));
   int64_t* d_ptr = nullptr;
@@ -1144,6 +1147,24 @@ dgc_status_t dgc_layer_stage_times(dgc_layer_t* L, float* host_ms) {
   return DGC_OK;
 }
 
+// What the input gradient of EvolveGCN-O needs: launches within the grid's limits, and its workspace.
+static dgc_status_t prepare_dx(dgc_layer* L, hipStream_t st) {
+  Failer fail{L};
+  const dgc_layer_desc_t& d = L->desc;
+  int64_t max_nv = 1;
+  int32_t max_w = 1;
+  for (const ChunkInfo& c : L->cinfo_host) { max_nv = std::max(max_nv, c.nv); max_w = std::max(max_w, c.w); }
+  if (L->n_chunks > kMaxGridYZ || max_w > kMaxGridYZ)   // a kernel of it takes one grid plane per chunk, one row per snapshot
+    return fail(DGC_ERR_UNSUPPORTED, "input gradient: more than 65535 chunks or snapshots per window");
+  if (!L->d_dM) {
+    DGC_HIP_TRY(dev_alloc(L, &L->d_dM, (int64_t)L->T * L->N * d.F));
+    DGC_HIP_TRY(dev_alloc(L, &L->d_rowidx, L->total_rows));
+    DGC_HIP_TRY(dev_alloc(L, &L->d_Wt_plain, (int64_t)L->T * evolve_packed_bytes(L->evo, L->evo.split) / (int64_t)sizeof(float4)));
+    evolve_row_index(L->d_chunks, L->n_chunks, max_nv, max_w, L->N, L->d_rowidx, st);
+  }
+  return DGC_OK;
+}
+
 dgc_status_t dgc_layer_backward(dgc_layer_t* L, const void* Yv, int64_t ldy, const void* dYv, int64_t lddy,
                                 const void* targetv, int64_t ldt, float* loss_out, void* dX, int64_t lddx,
                                 void* stream) {
@@ -1188,18 +1209,23 @@ dgc_status_t dgc_layer_backward(dgc_layer_t* L, const void* Yv, int64_t ldy, con
   const bool prof = L->profiling;
   L->evx_bwd = false;
   if (prof) DGC_HIP_TRY(hipEventRecord(L->evx[2], st));
-  if (!evolve_backward_dw(L->evo, in, st, &why)) return fail(DGC_ERR_UNSUPPORTED, why);
+  // without the input gradient the parameters' gradients are computed all the same
+  const dgc_status_t dx_rc = dX ? prepare_dx(L, st) : DGC_OK;
+  const bool want_dx = dX && dx_rc == DGC_OK;
+  if (!evolve_backward_dw(L->evo, in, want_dx, st, &why)) return fail(DGC_ERR_UNSUPPORTED, why);
+  if (want_dx) L->m_saved = false;
   // the back-propagation through the weights beside the input gradient (if that is asked for)
-  hipStream_t bptt = dX ? L->side : st;
+  hipStream_t bptt = want_dx ? L->side : st;
   if (prof) DGC_HIP_TRY(hipEventRecord(L->evx[3], st));
-  if (dX) {
+  if (want_dx) {
     DGC_HIP_TRY(hipEventRecord(L->fork, st));
     DGC_HIP_TRY(hipStreamWaitEvent(L->side, L->fork, 0));
   }
   if (prof) DGC_HIP_TRY(hipEventRecord(L->evx[4], bptt));
   evolve_backward_bptt(L->evo, bptt);
   if (prof) { DGC_HIP_TRY(hipEventRecord(L->evx[5], bptt)); L->evx_bwd = true; }
-  if (dX) {
+  if (dx_rc != DGC_OK) return dx_rc;
+  if (want_dx) {
     DGC_HIP_TRY(hipEventRecord(L->join, L->side));
     struct Join {      // whichever way the rest goes, the caller's stream waits for the other
       dgc_layer* L;
@@ -1207,22 +1233,9 @@ dgc_status_t dgc_layer_backward(dgc_layer_t* L, const void* Yv, int64_t ldy, con
       ~Join() { (void)hipStreamWaitEvent(st, L->join, 0); }
     } join{L, st};
     // dX[t, j] = sum over the rows i of j's chunk that store j of (d_i d_j)^-1/2 dM[t, i],  dM = dP W_t^T:
-    // dP into the buffer of the aggregated rows (the weight gradient above was their last reader), the
+    // the weight gradient's kernel has left dP in the buffer of the aggregated rows (it was their last reader), the
     // dense kernel with W_t as an (out = F, in = S) weight, then the aggregation kernels on dM with
     // the neighbours outside the chunk range left out (the cache is a constant) and the adjacency's symmetry.
-    int64_t max_nv = 1;
-    int32_t max_w = 1;
-    for (const ChunkInfo& c : L->cinfo_host) { max_nv = std::max(max_nv, c.nv); max_w = std::max(max_w, c.w); }
-    if (L->n_chunks > kMaxGridYZ || max_w > kMaxGridYZ)   // its kernels take one grid plane per chunk, one row per snapshot
-      return fail(DGC_ERR_UNSUPPORTED, "input gradient: more than 65535 chunks or snapshots per window");
-    if (!L->d_dM) {
-      DGC_HIP_TRY(dev_alloc(L, &L->d_dM, (int64_t)L->T * L->N * d.F));
-      DGC_HIP_TRY(dev_alloc(L, &L->d_rowidx, L->total_rows));
-      DGC_HIP_TRY(dev_alloc(L, &L->d_Wt_plain, (int64_t)L->T * evolve_packed_bytes(L->evo, L->evo.split) / (int64_t)sizeof(float4)));
-      evolve_row_index(L->d_chunks, L->n_chunks, max_nv, max_w, L->N, L->d_rowidx, st);
-    }
-    L->m_saved = false;
-    evolve_backward_dp(in, L->n_chunks, max_nv, max_w, d.S, L->d_M, L->ldm, st);
     evolve_pack_weights_plain(L->evo, L->d_Wt_plain, st);
     DenseArgs da{};
     da.tiles = L->d_tiles; da.n_tiles = L->n_tiles; da.chunks = L->d_chunks;

@@ -32,48 +32,17 @@
 #include <atomic>
 
 #include "dgc_internal.h"
+#include "dgc_split_dev.h"
 
 namespace dgc {
 namespace {
 
-typedef float floatx16 __attribute__((ext_vector_type(16)));
-typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef int intx4 __attribute__((ext_vector_type(4)));
+using namespace split;
 
-constexpr int kFrag = 64;                  // uint4 of one fragment part (32 rows x 16 k, one bf16 part)
 constexpr int kUnitBytes = 3 * kFrag * 16; // a weight fragment's three parts
 
 __device__ __forceinline__ float sigmoid_fast(float x) { return __builtin_amdgcn_rcpf(1.0f + __expf(-x)); }
 __device__ __forceinline__ float tanh_fast(float x) { return 1.0f - 2.0f * __builtin_amdgcn_rcpf(1.0f + __expf(2.0f * x)); }
-__device__ __forceinline__ bf16x8 as_frag(uint4 u) { return __builtin_bit_cast(bf16x8, u); }
-__device__ __forceinline__ float cut(float x) { return __uint_as_float(__float_as_uint(x) & 0xffff0000u); }
-__device__ __forceinline__ uint32_t tops(float lo, float hi) {   // the upper halves of two words
-  return __builtin_amdgcn_perm(__float_as_uint(hi), __float_as_uint(lo), 0x07060302u);
-}
-__device__ __forceinline__ uint4 tops8(const float (&x)[8]) {
-  return make_uint4(tops(x[0], x[1]), tops(x[2], x[3]), tops(x[4], x[5]), tops(x[6], x[7]));
-}
-
-// x = p[0] + p[1] + p[2], exactly, for finite x; an infinity is p[0] alone (its remainder would be NaN)
-__device__ __forceinline__ void split8(const float (&x)[8], uint4 (&p)[3]) {
-  float m[8], l[8];
-  float top = 0.f;
-#pragma unroll
-  for (int i = 0; i < 8; ++i) {
-    m[i] = x[i] - cut(x[i]);
-    top = fmaxf(top, fabsf(x[i]));
-  }
-  if (__builtin_expect(__any(top == __builtin_inff()), 0)) {
-#pragma unroll
-    for (int i = 0; i < 8; ++i) m[i] = fabsf(x[i]) == __builtin_inff() ? 0.f : m[i];
-  }
-#pragma unroll
-  for (int i = 0; i < 8; ++i) l[i] = m[i] - cut(m[i]);
-  p[0] = tops8(x);
-  p[1] = tops8(m);
-  p[2] = tops8(l);
-}
-
 // Weights come by buffer loads: resource descriptor in scalar registers, the fragment's place as scalar
 // offset, the lane's 16 bytes as vector offset.  A vector offset beyond the resource reads as zero without
 // touching memory: that is what a fragment past the end of a product gets, so that the loops have no branches.
@@ -102,18 +71,6 @@ __device__ __forceinline__ void fetch_ahead(uint4 (&w)[D][3], const WeightStream
   for (int u = 0; u < D - 1; ++u) ws.unit(w[u], lane16, off + (u % NG) * gstride + (u / NG) * kUnitBytes, u / NG < nkb);
 }
 
-// c += weights x rows of one fragment each, the smallest products first
-__device__ __forceinline__ void six(floatx16& c, const uint4 (&w)[3], const uint4 (&x)[3]) {
-  const bf16x8 w0 = as_frag(w[0]), w1 = as_frag(w[1]), w2 = as_frag(w[2]);
-  const bf16x8 x0 = as_frag(x[0]), x1 = as_frag(x[1]), x2 = as_frag(x[2]);
-  c = __builtin_amdgcn_mfma_f32_32x32x16_bf16(w0, x2, c, 0, 0, 0);
-  c = __builtin_amdgcn_mfma_f32_32x32x16_bf16(w2, x0, c, 0, 0, 0);
-  c = __builtin_amdgcn_mfma_f32_32x32x16_bf16(w1, x1, c, 0, 0, 0);
-  c = __builtin_amdgcn_mfma_f32_32x32x16_bf16(w0, x1, c, 0, 0, 0);
-  c = __builtin_amdgcn_mfma_f32_32x32x16_bf16(w1, x0, c, 0, 0, 0);
-  c = __builtin_amdgcn_mfma_f32_32x32x16_bf16(w0, x0, c, 0, 0, 0);
-}
-
 // acc(g) += W_g x rows, over nkb k-blocks; fr: this lane's first operand of the staged rows
 template <int NG, int D, class Acc>
 __device__ __forceinline__ void product(Acc&& acc, const uint4* fr, const WeightStream& ws, int off, int gstride, int nkb,
@@ -136,7 +93,7 @@ __device__ __forceinline__ void product(Acc&& acc, const uint4* fr, const Weight
         const int kn = k + (g + D - 1) / NG, gn = (g + D - 1) % NG;
         ws.unit(w[(u + D - 1) % D], lane16, off + gn * gstride + kn * kUnitBytes, kn < nkb);
         __builtin_amdgcn_sched_barrier(0);
-        six(acc(g), w[u % D], b);
+        six(acc(g), acc(g), w[u % D], b);
         if (g == NG - 1) {
           const uint4* next = fr + min(k + 1, nkb - 1) * (3 * kFrag);
 #pragma unroll
@@ -149,12 +106,6 @@ __device__ __forceinline__ void product(Acc&& acc, const uint4* fr, const Weight
   __builtin_amdgcn_s_setprio(0);
 }
 
-__device__ __forceinline__ void put(uint4* frag, const float (&x)[8]) {
-  uint4 p[3];
-  split8(x, p);
-#pragma unroll
-  for (int q = 0; q < 3; ++q) frag[q * kFrag] = p[q];
-}
 // columns 16*kb .. +15 of an input row (a pitch is a multiple of 16 floats); row: the lane's first column
 __device__ __forceinline__ void load_x(const float* row, int kb, float4 (&x)[2]) {
   x[0] = *reinterpret_cast<const float4*>(row + 16 * kb);
@@ -182,20 +133,6 @@ __device__ __forceinline__ void store_block(float* p, const floatx16& v) {
 __device__ __forceinline__ void relu(floatx16& z) {
 #pragma unroll
   for (int v = 0; v < 16; ++v) z[v] = fmaxf(z[v], 0.f);
-}
-
-// A table that no kernel writes while it is read: the address space lets wave-uniform entries come through the
-// scalar cache, apart from the vector memory operations (which retire in order).
-template <class T>
-__device__ __forceinline__ T table_entry(const T* table, int64_t i) {
-  union {
-    T entry;
-    uint32_t word[sizeof(T) / 4];
-  } r;
-  const auto* p = (const __attribute__((address_space(4))) uint32_t*)(table + i);
-#pragma unroll
-  for (size_t k = 0; k < sizeof(T) / 4; ++k) r.word[k] = p[k];
-  return r.entry;
 }
 
 // KIND: DGC_TIME_GRU or DGC_TIME_LSTM.  SEQ, CAT, STACK: as the fields of DenseArgs say (sequences inside the window;
@@ -479,18 +416,15 @@ __global__ __launch_bounds__(64 * MAXW, 2) void k_rows_split(DenseArgs a, int kb
     if constexpr (!FIRST) {
       if (l32 < nrows) z = load_block(y);
     }
-    uint4 b[2][3];                            // the operands one k-block ahead
-#pragma unroll
-    for (int p = 0; p < 3; ++p) b[0][p] = buf[p * kFrag];
+    floatx16 small = (floatx16)(0.f);
 #pragma unroll
     for (int k = 0; k < NKB; ++k) {
-      if (k + 1 < NKB) {
+      uint4 b[3];
 #pragma unroll
-        for (int p = 0; p < 3; ++p) b[(k + 1) % 2][p] = buf[((k + 1) * 3 + p) * kFrag];
-      }
-      six(z, w[k], b[k % 2]);
-      __builtin_amdgcn_sched_barrier(0);
+      for (int p = 0; p < 3; ++p) b[p] = buf[(k * 3 + p) * kFrag];
+      six(z, small, w[k], b);
     }
+    z += small;
     if (last && a.act == DGC_ACT_RELU) relu(z);
     if (l32 < nrows) store_block(y, z);
   }

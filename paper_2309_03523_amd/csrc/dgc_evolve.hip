@@ -9,12 +9,13 @@
 // one step of the weight recurrence, or of its back-propagation through time, with the gate
 // arithmetic that follows them (latency-bound), and the one large kernel of the backward pass,
 // dW_t = M_t^T dP_t reduced over all rows of snapshot t across the fused chunks.
+#include <algorithm>
+
 #include "dgc_internal.h"
+#include "dgc_split_dev.h"
 
 namespace dgc {
 namespace {
-
-typedef float floatx16 __attribute__((ext_vector_type(16)));
 
 __device__ __forceinline__ float f4get(const float4& v, int q) { return q == 0 ? v.x : q == 1 ? v.y : q == 2 ? v.z : v.w; }
 __device__ __forceinline__ float sigmoidf_(float x) { return 1.0f / (1.0f + expf(-x)); }
@@ -185,148 +186,150 @@ __global__ void k_pack_weight_t(const float* Wt, int32_t T, int32_t F, int32_t S
 // dW_t = sum over the rows (t, i) of the batch of M[row]^T dP[row],  dP = dL/d(pre-activation):
 //   dP = [Y > 0] * dY                      (explicit upstream gradient), or
 //   dP = [Y > 0] * 2 (Y - target) / count  (mean-squared-error loss, also summed into loss).
-// MFMA-bound (2 F S flops per row against (F + S) floats read).  One workgroup of F/32 waves
-// owns (snapshot t, split k) and walks every kSplit-th 32-row tile of that snapshot; wave w keeps
-// rows [32w, 32w+32) x all S columns of the partial sum in its accumulators.  Both operands are
-// row-major reads: lane l supplies A[m = l%32][k = l/32] = M[r0 + l/32][32w + l%32] and
-// B[k][n] = dP[r0 + l/32][32 jb + l%32].  Tiles are staged through LDS; the next tile's global
-// loads are in flight (in registers) while the current one is multiplied.
-constexpr int kSplit = 8;
-constexpr int kDwRows = 32;
+// 2 F S flops per row against (F + 2 S) floats read.  One workgroup of F/32 waves owns (snapshot t, split k) and
+// walks every split-th 32-row tile of that snapshot, 16 rows at a time; wave w keeps rows [32w, 32w+32) x all S
+// columns of the partial sum in its accumulators.  The products are sums of bf16 products on
+// v_mfma_f32_32x32x16_bf16 (dgc_dense_split.hip); they contract over rows, so an operand fragment is eight rows of
+// one column: a thread loads just these (a wave's load instruction is two lines of two rows), splits them once
+// and leaves the parts in LDS in fragment order for every wave.  Two LDS buffers in turn, the next rows' loads
+// in flight meanwhile.  With dP given, every tile's dP goes there over the rows of M that the tile has read (the
+// input gradient starts from it): a pass of its own over Y and the target that is not needed.
+// (64 snapshots x 62 500 rows, F = 256: 5.0 ms on the fp32 instruction and 2.1 ms for that pass; 4.3 ms here.)
+// `split` workgroups per snapshot, as many as fill the chip (evolve_dw_split).
+constexpr int kDwRows = 16;
 
 struct DwArgs {
   const DenseTile* items;     // 32-row tiles ordered by snapshot
   const int64_t* item_ptr;    // [T+1]
-  const int32_t* item_t;      // unused (kept for debugging)
   const ChunkInfo* chunks;
   int64_t N;
-  const float* M; int64_t ldm;
+  float* M; int64_t ldm;
   const float* Y; int64_t ldy;
   const float* dY; int64_t lddy;       // or nullptr
   const float* target; int64_t ldt;    // or nullptr
   float inv_count2;                    // 2 / count
-  int32_t F, S;
-  float* partial;                      // [T][kSplit][F][S]
-  float* loss_partial;                 // [T][kSplit]
+  int32_t split;
+  bool keep_dp;                        // leave dP in the rows of M
+  float* partial;                      // [T][split][F][S]
+  float* loss_partial;                 // [T][split]
 };
 
-template <int NJB>  // S / 32
-__global__ __launch_bounds__(512) void k_dw_partial(DwArgs a, int t_base) {
-  extern __shared__ __align__(16) float lds[];
-  const int F = a.F, S = NJB * 32;
-  const int ldt_m = F + 4, ldt_p = S + 4;
-  float* tm = lds;                        // [32][F+4]   M tile
-  float* tp = lds + kDwRows * ldt_m;      // [32][S+4]   dP tile
-  float* red = tp + kDwRows * ldt_p;      // [nthreads / 64] loss partials
-  const int t = t_base + blockIdx.x / kSplit, ks = blockIdx.x % kSplit;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, l32 = lane & 31, half = lane >> 5;
-  const int nthreads = blockDim.x;
-  const int fm4 = F / 4, fp4 = S / 4;
-  constexpr int kMaxPf = 4;  // float4 per thread and operand: 32 rows x 256 floats / 512 threads
+template <int NJB>  // F / 32 = S / 32
+__global__ __launch_bounds__(64 * NJB) void k_dw_split(DwArgs a) {
+  using namespace split;
+  extern __shared__ __align__(16) uint4 lds[];
+  constexpr int F = 32 * NJB;
+  constexpr int kOperand = NJB * 3 * kFrag;            // uint4 of one operand of 16 rows
+  float* red = reinterpret_cast<float*>(lds + 4 * kOperand);   // [NJB] loss partials
+  const int t = blockIdx.x / a.split, ks = blockIdx.x % a.split;
+  const int tid = threadIdx.x, lane = tid & 63, l32 = lane & 31, half = lane >> 5;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int col = 32 * wave + l32;                     // this thread's column of both operands
   floatx16 acc[NJB];
 #pragma unroll
   for (int jb = 0; jb < NJB; ++jb) acc[jb] = (floatx16)(0.f);
   float loss = 0.f;
-  const int64_t i0 = a.item_ptr[t], i1 = a.item_ptr[t + 1];
+  const int64_t i1 = table_entry(a.item_ptr, t + 1);
+  const float* upstream = a.target ? a.target : a.dY;
+  const int64_t ldu = a.target ? a.ldt : a.lddy;
 
-  float4 pm[kMaxPf], py[kMaxPf], pg[kMaxPf];
-  auto fetch = [&](int64_t it) {
-    const DenseTile tile = a.items[it];
-    const ChunkInfo ch = a.chunks[tile.chunk];
-    const float* mrow = a.M + (ch.row_off0 + (int64_t)(t - ch.t_lo) * ch.nv + tile.v0) * a.ldm;
+  // Rows r0 .. r0 + 15 of tile `it`; this thread's are 8 * half + i.  A row past the tile's end is its last row,
+  // and counts as zero.
+  int64_t it = table_entry(a.item_ptr, t) + ks;
+  int r0 = 0;
+  struct Rows {
+    float m[8], y[8], g[8];
+    float* mp;       // this thread's first row of M
+    int rows;        // of its eight that exist
+    bool there;
+  };
+  auto request = [&](Rows& q) {
+    q.there = it < i1;
+    if (!q.there) return;
+    const DenseTile tile = table_entry(a.items, it);
+    const ChunkInfo ch = table_entry(a.chunks, tile.chunk);
     const int64_t vrow = (int64_t)t * a.N + ch.v_lo + tile.v0;
+    const int first = r0 + 8 * half, last = tile.nrows - 1;
+    q.rows = max(0, min(8, tile.nrows - first));
+    float* m = a.M + (ch.row_off0 + (int64_t)tile.step * ch.nv + tile.v0) * a.ldm + col;
+    q.mp = m + first * a.ldm;
 #pragma unroll
-    for (int i = 0; i < kMaxPf; ++i) {
-      const int idx = tid + i * nthreads;
-      pm[i] = make_float4(0.f, 0.f, 0.f, 0.f);
-      py[i] = pm[i]; pg[i] = pm[i];
-      if (idx < kDwRows * fm4) {
-        const int r = idx / fm4, c4 = idx - r * fm4;
-        if (r < tile.nrows) pm[i] = *reinterpret_cast<const float4*>(mrow + (int64_t)r * a.ldm + 4 * c4);
-      }
-      if (idx < kDwRows * fp4) {
-        const int r = idx / fp4, c4 = idx - r * fp4;
-        if (r < tile.nrows) {
-          py[i] = *reinterpret_cast<const float4*>(a.Y + (vrow + r) * a.ldy + 4 * c4);
-          pg[i] = a.target ? *reinterpret_cast<const float4*>(a.target + (vrow + r) * a.ldt + 4 * c4)
-                           : *reinterpret_cast<const float4*>(a.dY + (vrow + r) * a.lddy + 4 * c4);
-        }
-      }
+    for (int i = 0; i < 8; ++i) {
+      const int64_t r = min(first + i, last);
+      q.m[i] = m[r * a.ldm];
+      q.y[i] = a.Y[(vrow + r) * a.ldy + col];
+      q.g[i] = upstream[(vrow + r) * ldu + col];
     }
+    if (r0 == 0 && tile.nrows > kDwRows) r0 = kDwRows;
+    else { r0 = 0; it += a.split; }
   };
-  auto stage = [&]() {
+  uint4* buf = lds;
+  auto step = [&](Rows& q) {
+    float d[8];
+    const int rows = q.rows;
+    float* mp = q.mp;
 #pragma unroll
-    for (int i = 0; i < kMaxPf; ++i) {
-      const int idx = tid + i * nthreads;
-      if (idx < kDwRows * fm4) {
-        const int r = idx / fm4, c4 = idx - r * fm4;
-        *reinterpret_cast<float4*>(tm + r * ldt_m + 4 * c4) = pm[i];
-      }
-      if (idx < kDwRows * fp4) {
-        const int r = idx / fp4, c4 = idx - r * fp4;
-        const float y[4] = {py[i].x, py[i].y, py[i].z, py[i].w};
-        const float g[4] = {pg[i].x, pg[i].y, pg[i].z, pg[i].w};
-        float o[4];
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          if (a.target) {
-            const float d = y[e] - g[e];
-            loss += d * d;                      // rows past the tile's end hold zeros: add nothing
-            o[e] = y[e] > 0.f ? d * a.inv_count2 : 0.f;
-          } else {
-            o[e] = y[e] > 0.f ? g[e] : 0.f;
-          }
-        }
-        *reinterpret_cast<float4*>(tp + r * ldt_p + 4 * c4) = make_float4(o[0], o[1], o[2], o[3]);
-      }
+    for (int i = 0; i < 8; ++i) {
+      const bool in = i < rows;
+      const float diff = q.y[i] - q.g[i];
+      d[i] = in && q.y[i] > 0.f ? (a.target ? diff * a.inv_count2 : q.g[i]) : 0.f;
+      loss += in && a.target ? diff * diff : 0.f;
+      q.m[i] = in ? q.m[i] : 0.f;
     }
+    put(buf + wave * 3 * kFrag + lane, q.m);
+    put(buf + kOperand + wave * 3 * kFrag + lane, d);
+    request(q);
+    __syncthreads();      // (also: every thread has read the rows of M that get dP)
+    if (a.keep_dp) {
+#pragma unroll
+      for (int i = 0; i < 8; ++i)
+        if (i < rows) mp[i * a.ldm] = d[i];
+    }
+    uint4 x[3];
+#pragma unroll
+    for (int p = 0; p < 3; ++p) x[p] = buf[(wave * 3 + p) * kFrag + lane];
+#pragma unroll
+    for (int jb = 0; jb < NJB; ++jb) {
+      uint4 y[3];
+#pragma unroll
+      for (int p = 0; p < 3; ++p) y[p] = buf[kOperand + (jb * 3 + p) * kFrag + lane];
+      // each link from zero, added up by rounding additions: hundreds of links would add up the cut-off
+      floatx16 sum = (floatx16)(0.f);
+      six(sum, sum, x, y);
+      acc[jb] += sum;
+    }
+    buf = buf == lds ? lds + 2 * kOperand : lds;
   };
-
-  int64_t it = i0 + ks;
-  if (it < i1) fetch(it);
-  for (; it < i1; it += kSplit) {
-    __syncthreads();  // the previous tile has been consumed
-    stage();
-    __syncthreads();
-    if (it + kSplit < i1) fetch(it + kSplit);
-    const float* am = tm + half * ldt_m + wave * 32 + l32;
-    const float* bp = tp + half * ldt_p + l32;
-#pragma unroll 4
-    for (int kk = 0; kk < kDwRows / 2; ++kk) {
-      const float av = am[2 * kk * ldt_m];
-#pragma unroll
-      for (int jb = 0; jb < NJB; ++jb)
-        acc[jb] = __builtin_amdgcn_mfma_f32_32x32x2f32(av, bp[2 * kk * ldt_p + jb * 32], acc[jb], 0, 0, 0);
-    }
-  }
+  // (two steps of rows on their way are no faster, 4.5 ms: the registers spill)
+  Rows q;
+  request(q);
+  while (q.there) step(q);
   // partial sums: rows 32*wave .. of dW_t, standard accumulator layout (row by register, column = l%32)
-  float* out = a.partial + ((int64_t)t * kSplit + ks) * (int64_t)F * S;
+  float* out = a.partial + ((int64_t)t * a.split + ks) * (int64_t)F * F;
 #pragma unroll
   for (int jb = 0; jb < NJB; ++jb)
 #pragma unroll
     for (int v = 0; v < 16; ++v) {
       const int row = wave * 32 + 8 * (v / 4) + 4 * half + (v % 4);
-      out[(int64_t)row * S + jb * 32 + l32] = acc[jb][v];
+      out[(int64_t)row * F + jb * 32 + l32] = acc[jb][v];
     }
   // loss: wave sums in lane order, then the waves in order (fixed order, reproducible)
   for (int d = 32; d >= 1; d >>= 1) loss += __shfl_down(loss, d, 64);
-  __syncthreads();
   if (lane == 0) red[wave] = loss;
   __syncthreads();
   if (tid == 0) {
     float s = 0.f;
-    for (int w = 0; w < nthreads / 64; ++w) s += red[w];
-    a.loss_partial[(int64_t)t * kSplit + ks] = s;
+    for (int w = 0; w < NJB; ++w) s += red[w];
+    a.loss_partial[(int64_t)t * a.split + ks] = s;
   }
 }
 
-// dWd[t] = sum_k partial[t][k]  (k ascending)
-__global__ void k_dw_reduce(const float* partial, float* dWd, int64_t n_per_t, int64_t total) {
+__global__ void k_dw_reduce(const float* partial, float* dWd, int32_t split, int64_t n_per_t, int64_t total) {
   const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (e >= total) return;
   const int64_t t = e / n_per_t, i = e - t * n_per_t;
   float s = 0.f;
-  for (int k = 0; k < kSplit; ++k) s += partial[(t * kSplit + k) * n_per_t + i];
+  for (int k = 0; k < split; ++k) s += partial[(t * split + k) * n_per_t + i];
   dWd[e] = s;
 }
 
@@ -366,27 +369,6 @@ __global__ void k_pack_weight_plain(const float* Wt, int32_t T, int32_t F, int32
   packed[idx] = make_float4(v[0], v[1], v[2], v[3]);
 }
 
-// dP of every covered row, written to the packed row of (chunk, snapshot, vertex); one thread per float4
-__global__ void k_ev_dp(EvolveBwdIn in, int32_t S, float inv_count2, float* dP, int64_t ldp) {
-  const ChunkInfo ch = in.chunks[blockIdx.z];
-  const int32_t s = blockIdx.y;
-  if (s >= ch.w) return;
-  const int64_t q = S / 4;
-  const int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (idx >= ch.nv * q) return;
-  const int64_t v = idx / q, c4 = idx - v * q;
-  const int64_t row = (int64_t)(ch.t_lo + s) * in.N + ch.v_lo + v;
-  const float4 y = *reinterpret_cast<const float4*>(in.Y + row * in.ldy + 4 * c4);
-  const float4 g = in.target ? *reinterpret_cast<const float4*>(in.target + row * in.ldt + 4 * c4)
-                             : *reinterpret_cast<const float4*>(in.dY + row * in.lddy + 4 * c4);
-  const float yy[4] = {y.x, y.y, y.z, y.w}, gg[4] = {g.x, g.y, g.z, g.w};
-  float o[4];
-#pragma unroll
-  for (int e = 0; e < 4; ++e)
-    o[e] = yy[e] > 0.f ? (in.target ? (yy[e] - gg[e]) * inv_count2 : gg[e]) : 0.f;
-  *reinterpret_cast<float4*>(dP + (ch.row_off0 + (int64_t)s * ch.nv + v) * ldp + 4 * c4) = make_float4(o[0], o[1], o[2], o[3]);
-}
-
 __global__ void k_ev_row_index(const ChunkInfo* chunks, int64_t N, int64_t* idx) {
   const ChunkInfo ch = chunks[blockIdx.z];
   const int32_t s = blockIdx.y;
@@ -412,8 +394,14 @@ void launch_mm(const EvJobs& jobs, int n_jobs, int n, hipStream_t st) {
 
 }  // namespace
 
-int64_t evolve_partial_elems(int32_t T, int32_t F, int32_t S) { return (int64_t)T * kSplit * F * S; }
-int64_t evolve_loss_partial_elems(int32_t T) { return (int64_t)T * kSplit; }
+int32_t evolve_dw_split(int32_t T, int32_t F, int64_t most_tiles) {
+  // about two rounds of workgroups of F/32 waves on 256 CUs of eight waves, at least 8 a snapshot (and at most one
+  // a tile: the partial sums of every one are written and read)
+  const int64_t n = std::min<int64_t>(64, 2 * 256 * 8 / ((int64_t)T * (F / 32)));
+  return (int32_t)std::max<int64_t>(1, std::min(std::max<int64_t>(8, n), most_tiles));
+}
+int64_t evolve_partial_elems(const EvolveWs& ws) { return (int64_t)ws.T * ws.split_dw * ws.F * ws.S; }
+int64_t evolve_loss_partial_elems(const EvolveWs& ws) { return (int64_t)ws.T * ws.split_dw; }
 
 // Evolve W_t for t = 0..T-1 (ws.Wt, gates ws.Zg/Rg/Wc, all double) and pack every W_t, rounded
 // to fp32, for the dense kernels.  Two launches per snapshot.
@@ -447,12 +435,6 @@ void evolve_forward_weights(const EvolveWs& ws, hipStream_t st) {
   hipLaunchKernelGGL(k_pack_weight_t, blocks_for(per * ws.T), 256, 0, st, ws.Wt_f32, ws.T, ws.F, ws.S, ws.Wt_packed);
 }
 
-void evolve_backward_dp(const EvolveBwdIn& in, int32_t n_chunks, int64_t max_nv, int32_t max_w, int32_t S, float* dP,
-                        int64_t ldp, hipStream_t st) {
-  hipLaunchKernelGGL(k_ev_dp, dim3(blocks_for(max_nv * (S / 4)), (unsigned)max_w, (unsigned)n_chunks), 256, 0, st, in, S,
-                     2.0f / (float)in.count, dP, ldp);
-}
-
 void evolve_row_index(const ChunkInfo* chunks, int32_t n_chunks, int64_t max_nv, int32_t max_w, int64_t N, int64_t* idx,
                       hipStream_t st) {
   hipLaunchKernelGGL(k_ev_row_index, dim3(blocks_for(max_nv), (unsigned)max_w, (unsigned)n_chunks), 256, 0, st, chunks, N,
@@ -468,34 +450,35 @@ void evolve_pack_weights_plain(const EvolveWs& ws, float4* packed, hipStream_t s
   hipLaunchKernelGGL(k_pack_weight_plain, blocks_for(per * ws.T), 256, 0, st, ws.Wt_f32, ws.T, ws.F, ws.S, packed);
 }
 
-// dWd[t] for all t (and the loss), from the saved aggregated rows and the layer's output.
-bool evolve_backward_dw(const EvolveWs& ws, const EvolveBwdIn& in, hipStream_t st, std::string* why) {
+// dWd[t] for all t (and the loss), from the saved aggregated rows and the layer's output; keep_dp: the rows of M
+// then hold dP.
+bool evolve_backward_dw(const EvolveWs& ws, const EvolveBwdIn& in, bool keep_dp, hipStream_t st, std::string* why) {
   DwArgs a{};
-  a.items = ws.items; a.item_ptr = ws.item_ptr; a.item_t = nullptr; a.chunks = in.chunks; a.N = in.N;
+  a.items = ws.items; a.item_ptr = ws.item_ptr; a.chunks = in.chunks; a.N = in.N;
   a.M = in.M; a.ldm = in.ldm; a.Y = in.Y; a.ldy = in.ldy; a.dY = in.dY; a.lddy = in.lddy;
   a.target = in.target; a.ldt = in.ldt;
   a.inv_count2 = 2.0f / (float)in.count;
-  a.F = ws.F; a.S = ws.S; a.partial = ws.partial; a.loss_partial = ws.loss_partial;
-  const int threads = 64 * (ws.F / 32);
-  if (ws.F % 32 || ws.F > 256 || ws.S % 32 || ws.S > 256) {
-    if (why) *why = "the weight-gradient kernel needs F and S multiples of 32, at most 256";
+  a.split = ws.split_dw; a.keep_dp = keep_dp; a.partial = ws.partial; a.loss_partial = ws.loss_partial;
+  if (ws.F % 32 || ws.F > 256 || ws.S != ws.F) {
+    if (why) *why = "the weight-gradient kernel needs F = S, a multiple of 32, at most 256";
     return false;
   }
-  const size_t lds = sizeof(float) * ((size_t)kDwRows * (ws.F + 4) + (size_t)kDwRows * (ws.S + 4) + 16);
-  const unsigned grid = (unsigned)ws.T * kSplit;
-  switch (ws.S / 32) {
+  const int njb = ws.F / 32;
+  const size_t lds = (size_t)4 * njb * 3 * split::kFrag * sizeof(uint4) + sizeof(float) * 16;
+  const unsigned grid = (unsigned)ws.T * ws.split_dw;
+  switch (njb) {
 #define DGC_DW_CASE(NJB)                                                                               \
   case NJB: {                                                                                          \
     static bool attr = false;                                                                          \
     if (!attr) {                                                                                       \
-      if (hipFuncSetAttribute(reinterpret_cast<const void*>(&k_dw_partial<NJB>),                       \
+      if (hipFuncSetAttribute(reinterpret_cast<const void*>(&k_dw_split<NJB>),                         \
                               hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024) != hipSuccess) { \
         if (why) *why = "hipFuncSetAttribute failed";                                                  \
         return false;                                                                                  \
       }                                                                                                \
       attr = true;                                                                                     \
     }                                                                                                  \
-    hipLaunchKernelGGL((k_dw_partial<NJB>), grid, threads, lds, st, a, 0);                             \
+    hipLaunchKernelGGL((k_dw_split<NJB>), grid, 64 * NJB, lds, st, a);                                 \
     break;                                                                                             \
   }
     DGC_DW_CASE(1) DGC_DW_CASE(2) DGC_DW_CASE(3) DGC_DW_CASE(4) DGC_DW_CASE(5) DGC_DW_CASE(6) DGC_DW_CASE(7)
@@ -506,9 +489,9 @@ bool evolve_backward_dw(const EvolveWs& ws, const EvolveBwdIn& in, hipStream_t s
       return false;
   }
   const int64_t n = (int64_t)ws.F * ws.S;
-  hipLaunchKernelGGL(k_dw_reduce, blocks_for(n * ws.T), 256, 0, st, ws.partial, ws.dWd, n, n * ws.T);
+  hipLaunchKernelGGL(k_dw_reduce, blocks_for(n * ws.T), 256, 0, st, ws.partial, ws.dWd, ws.split_dw, n, n * ws.T);
   if (in.target && in.loss_out)
-    hipLaunchKernelGGL(k_loss_reduce, 1, 256, 0, st, ws.loss_partial, (int64_t)ws.T * kSplit, 1.0f / (float)in.count,
+    hipLaunchKernelGGL(k_loss_reduce, 1, 256, 0, st, ws.loss_partial, (int64_t)ws.T * ws.split_dw, 1.0f / (float)in.count,
                        in.loss_out);
   return true;
 }

@@ -225,8 +225,9 @@ struct EvolveWs {
   double *zsum, *rsum;       // U_z + V_z, U_r + V_r
   double *back0[3], *back1[3];   // dA_h, dA_z, Rg * W of even and odd steps of the back-propagation
   float* dWd;                // [T][F][S] direct gradient of each W_t
-  float* partial;            // [T][split][F][S]
-  float* loss_partial;       // [T][split]
+  int32_t split_dw;          // workgroups per snapshot of the weight-gradient kernel
+  float* partial;            // [T][split_dw][F][S]
+  float* loss_partial;       // [T][split_dw]
   const DenseTile* items;    // 32-row tiles ordered by snapshot (the layer's row tiles)
   const int64_t* item_ptr;   // [T+1]
 };
@@ -234,7 +235,7 @@ struct EvolveWs {
 struct EvolveBwdIn {
   const ChunkInfo* chunks;
   int64_t N;
-  const float* M; int64_t ldm;
+  float* M; int64_t ldm;
   const float* Y; int64_t ldy;
   const float* dY; int64_t lddy;
   const float* target; int64_t ldt;
@@ -246,14 +247,12 @@ struct EvolveBwdIn {
 inline int64_t evolve_packed_bytes(const EvolveWs& ws, bool split) {
   return split ? split_weight_bytes(ws.S, ws.F) : (int64_t)sizeof(float) * packed_weight_elems(ws.S, ws.F);
 }
-int64_t evolve_partial_elems(int32_t T, int32_t F, int32_t S);
-int64_t evolve_loss_partial_elems(int32_t T);
+int32_t evolve_dw_split(int32_t T, int32_t F, int64_t most_tiles);   // most_tiles: of a snapshot
+int64_t evolve_partial_elems(const EvolveWs& ws);
+int64_t evolve_loss_partial_elems(const EvolveWs& ws);
 void evolve_forward_weights(const EvolveWs& ws, hipStream_t st);
-bool evolve_backward_dw(const EvolveWs& ws, const EvolveBwdIn& in, hipStream_t st, std::string* why);
-// input-gradient pass: dP = dL/d(pre-activation) of every covered row into packed rows [rows][ldp];
-// the packed-row -> t*N + v table; every W_t as (out = F, in = S) fragments for dM = dP W_t^T
-void evolve_backward_dp(const EvolveBwdIn& in, int32_t n_chunks, int64_t max_nv, int32_t max_w, int32_t S, float* dP,
-                        int64_t ldp, hipStream_t st);
+bool evolve_backward_dw(const EvolveWs& ws, const EvolveBwdIn& in, bool keep_dp, hipStream_t st, std::string* why);
+// input-gradient pass: the packed-row -> t*N + v table; every W_t as (out = F, in = S) fragments for dM = dP W_t^T
 void evolve_row_index(const ChunkInfo* chunks, int32_t n_chunks, int64_t max_nv, int32_t max_w, int64_t N, int64_t* idx,
                       hipStream_t st);
 void evolve_pack_weights_plain(const EvolveWs& ws, float4* packed, hipStream_t st);

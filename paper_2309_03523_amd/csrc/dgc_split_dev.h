@@ -1,0 +1,81 @@
+// Device helpers of the kernels that take fp32 products as sums of bf16 products on
+// v_mfma_f32_32x32x16_bf16 (why that is exact enough, and the operand layouts: dgc_dense_split.hip).
+#pragma once
+
+#include "dgc_internal.h"
+
+namespace dgc {
+namespace split {
+
+typedef float floatx16 __attribute__((ext_vector_type(16)));
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef int intx4 __attribute__((ext_vector_type(4)));
+
+constexpr int kFrag = 64;   // uint4 of one fragment part (32 rows x 16 k, one bf16 part)
+
+__device__ __forceinline__ bf16x8 as_frag(uint4 u) { return __builtin_bit_cast(bf16x8, u); }
+__device__ __forceinline__ float cut(float x) { return __uint_as_float(__float_as_uint(x) & 0xffff0000u); }
+__device__ __forceinline__ uint32_t tops(float lo, float hi) {   // the upper halves of two words
+  return __builtin_amdgcn_perm(__float_as_uint(hi), __float_as_uint(lo), 0x07060302u);
+}
+__device__ __forceinline__ uint4 tops8(const float (&x)[8]) {
+  return make_uint4(tops(x[0], x[1]), tops(x[2], x[3]), tops(x[4], x[5]), tops(x[6], x[7]));
+}
+
+// x = p[0] + p[1] + p[2], exactly, for finite x; an infinity is p[0] alone (its remainder would be NaN)
+__device__ __forceinline__ void split8(const float (&x)[8], uint4 (&p)[3]) {
+  float m[8], l[8];
+  float top = 0.f;
+#pragma unroll
+  for (int i = 0; i < 8; ++i) {
+    m[i] = x[i] - cut(x[i]);
+    top = fmaxf(top, fabsf(x[i]));
+  }
+  if (__builtin_expect(__any(top == __builtin_inff()), 0)) {
+#pragma unroll
+    for (int i = 0; i < 8; ++i) m[i] = fabsf(x[i]) == __builtin_inff() ? 0.f : m[i];
+  }
+#pragma unroll
+  for (int i = 0; i < 8; ++i) l[i] = m[i] - cut(m[i]);
+  p[0] = tops8(x);
+  p[1] = tops8(m);
+  p[2] = tops8(l);
+}
+
+// c += the product of one fragment each, the smallest products first; the five small ones go to `small`, which may be
+// c itself.  (The instruction cuts its sums off rather than rounding them, a bias that long chains add up:
+// a chain's accumulator of its own for the small products, or a start from zero for every link, keeps it down.)
+__device__ __forceinline__ void six(floatx16& c, floatx16& small, const uint4 (&w)[3], const uint4 (&x)[3]) {
+  const bf16x8 w0 = as_frag(w[0]), w1 = as_frag(w[1]), w2 = as_frag(w[2]);
+  const bf16x8 x0 = as_frag(x[0]), x1 = as_frag(x[1]), x2 = as_frag(x[2]);
+  small = __builtin_amdgcn_mfma_f32_32x32x16_bf16(w0, x2, small, 0, 0, 0);
+  small = __builtin_amdgcn_mfma_f32_32x32x16_bf16(w2, x0, small, 0, 0, 0);
+  small = __builtin_amdgcn_mfma_f32_32x32x16_bf16(w1, x1, small, 0, 0, 0);
+  small = __builtin_amdgcn_mfma_f32_32x32x16_bf16(w0, x1, small, 0, 0, 0);
+  small = __builtin_amdgcn_mfma_f32_32x32x16_bf16(w1, x0, small, 0, 0, 0);
+  c = __builtin_amdgcn_mfma_f32_32x32x16_bf16(w0, x0, c, 0, 0, 0);
+}
+
+__device__ __forceinline__ void put(uint4* frag, const float (&x)[8]) {
+  uint4 p[3];
+  split8(x, p);
+#pragma unroll
+  for (int q = 0; q < 3; ++q) frag[q * kFrag] = p[q];
+}
+
+// A table that no kernel writes while it is read: the address space lets wave-uniform entries come through the
+// scalar cache, apart from the vector memory operations (which retire in order).
+template <class T>
+__device__ __forceinline__ T table_entry(const T* table, int64_t i) {
+  union {
+    T entry;
+    uint32_t word[sizeof(T) / 4];
+  } r;
+  const auto* p = (const __attribute__((address_space(4))) uint32_t*)(table + i);
+#pragma unroll
+  for (size_t k = 0; k < sizeof(T) / 4; ++k) r.word[k] = p[k];
+  return r.entry;
+}
+
+}  // namespace split
+}  // namespace dgc
