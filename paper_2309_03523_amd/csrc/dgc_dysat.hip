@@ -49,11 +49,21 @@ __global__ void k_owner(const Segment* segs, int64_t N, int32_t* owner) {
   for (int64_t v = s.v_lo + threadIdx.x; v < s.v_hi; v += blockDim.x) owner[(int64_t)s.t * N + v] = s.chunk;
 }
 
+// x of this lane where the lane's row of 16 (half of 32) has the even number, else y, each plus its partner's
+__device__ __forceinline__ float add_rows16(float x, float y) {
+  auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(y), false, false);
+  return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+}
+__device__ __forceinline__ float add_rows32(float x, float y) {
+  auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(y), false, false);
+  return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+}
 // ---------------------------------------------------------------------------------------------
 // Projection z = W x for every vertex of every snapshot in use: zC from the cache rows (any
 // vertex can be somebody's out-of-chunk neighbour), zX from the input rows of covered vertices,
 // plus the attention scalars s_src[h] = a_src^h . z^h, s_dst[h] = a_dst^h . z^h (from the fp32
-// accumulators).  One wavefront per 32 vertices.
+// accumulators).  A wave takes 32 vertices at a time; the workgroup keeps W (32 KB) in LDS.  Bound by memory: 4.4 GB in 1.27 ms
+// for 4 000 000 vertices (1.70 ms with W from the caches and 8-byte stores).
 struct ProjArgs {
   const uint16_t* X; int64_t ldx;
   const uint16_t* C; int64_t ldc;
@@ -65,79 +75,79 @@ struct ProjArgs {
   float* sC;   // [T*N][8]:  s_src
 };
 
-__global__ __launch_bounds__(256) void k_gat_project(ProjArgs a) {
+__global__ __launch_bounds__(512, 4) void k_gat_project(ProjArgs a) {
+  __shared__ uint4 w[4 * 8 * 64];
+  __shared__ float4 att[2][kS / 4];     // a_src, a_dst
+  for (int i = threadIdx.x; i < 4 * 8 * 64; i += 512) w[i] = a.Wp[i];
+  if (threadIdx.x < kS / 4) att[0][threadIdx.x] = reinterpret_cast<const float4*>(a.a_src)[threadIdx.x];
+  else if (threadIdx.x < kS / 2) att[1][threadIdx.x - kS / 4] = reinterpret_cast<const float4*>(a.a_dst)[threadIdx.x - kS / 4];
+  __syncthreads();
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int n = lane & 31, hh = lane >> 5;
-  const int64_t tiles_per_t = (a.N + 31) / 32;
-  const int64_t tile = (int64_t)blockIdx.x * 4 + wave;
-  if (tile >= tiles_per_t * a.n_used) return;
-  const int32_t t = a.used_t[tile / tiles_per_t];
-  const int64_t v = (tile % tiles_per_t) * 32 + n;
-  const bool valid = v < a.N;
-  const int64_t row = (int64_t)t * a.N + (valid ? v : a.N - 1);
-  const bool covered = valid && a.owner[row] >= 0;
-  const bool any_cov = __ballot(covered) != 0ull;
-  for (int side = 0; side < 2; ++side) {          // 0: cache rows, 1: input rows
-    if (side == 1 && !any_cov) break;
-    const uint16_t* src = side ? a.X + row * a.ldx : a.C + row * a.ldc;
-    const bool wr = side ? covered : valid;
-    bf16x8 xf[8];
+  const int64_t tiles_per_t = (a.N + 31) / 32, n_tiles = tiles_per_t * a.n_used;
+  for (int64_t tile = (int64_t)blockIdx.x * 8 + wave; tile < n_tiles; tile += (int64_t)gridDim.x * 8) {
+    const int32_t t = a.used_t[tile / tiles_per_t];
+    const int64_t v = (tile % tiles_per_t) * 32 + n;
+    const bool valid = v < a.N;
+    const int64_t row = (int64_t)t * a.N + (valid ? v : a.N - 1);
+    const bool covered = valid && a.owner[row] >= 0;
+    const bool any_cov = __ballot(covered) != 0ull;
+#pragma unroll 1
+    for (int side = 0; side < 2; ++side) {          // 0: cache rows, 1: input rows
+      if (side == 1 && !any_cov) break;
+      const uint16_t* src = side ? a.X + row * a.ldx : a.C + row * a.ldc;
+      const bool wr = side ? covered : valid;
+      bf16x8 xf[8];
 #pragma unroll
-    for (int kb = 0; kb < 8; ++kb) xf[kb] = as_frag(*reinterpret_cast<const uint4*>(src + kb * 16 + 8 * hh));
-    uint16_t* z = (side ? a.zX : a.zC) + row * kS;
-    float ssrc[kHeads], sdst[kHeads];
+      for (int kb = 0; kb < 8; ++kb) xf[kb] = as_frag(*reinterpret_cast<const uint4*>(src + kb * 16 + 8 * hh));
+      uint16_t* z = (side ? a.zX : a.zC) + row * kS;
+#pragma unroll 1
+      for (int jb = 0; jb < 4; ++jb) {
+        floatx16 acc = {};
+        float ssrc[2], sdst[2];
 #pragma unroll
-    for (int jb = 0; jb < 4; ++jb) {
-      floatx16 acc = {};
+        for (int kb = 0; kb < 8; ++kb) acc = mfma(as_frag(w[(jb * 8 + kb) * 64 + lane]), xf[kb], acc);
 #pragma unroll
-      for (int kb = 0; kb < 8; ++kb) acc = mfma(as_frag(a.Wp[(jb * 8 + kb) * 64 + lane]), xf[kb], acc);
-      if (wr) {
+        for (int hd = 0; hd < 2; ++hd) {
+          const int h = 2 * jb + hd;
+          const uint2 z0 = packh4(acc[8 * hd], acc[8 * hd + 1], acc[8 * hd + 2], acc[8 * hd + 3]);
+          const uint2 z1 = packh4(acc[8 * hd + 4], acc[8 * hd + 5], acc[8 * hd + 6], acc[8 * hd + 7]);
+          const uint4 o = head_order(make_uint4(z0.x, z0.y, z1.x, z1.y));
+          if (wr) *reinterpret_cast<uint4*>(z + h * kD + 8 * hh) = o;
+          float ps = 0.f, pd = 0.f;
 #pragma unroll
-        for (int g = 0; g < 4; ++g)
-          *reinterpret_cast<uint2*>(z + jb * 32 + 8 * g + 4 * hh) = packh4(acc[4 * g], acc[4 * g + 1], acc[4 * g + 2], acc[4 * g + 3]);
-      }
-#pragma unroll
-      for (int hd = 0; hd < 2; ++hd) {
-        const int h = 2 * jb + hd;
-        float ps = 0.f, pd = 0.f;
-#pragma unroll
-        for (int c = 0; c < 2; ++c) {
-          const float4 as = *reinterpret_cast<const float4*>(a.a_src + h * kD + 8 * c + 4 * hh);
-          const float4 ad = *reinterpret_cast<const float4*>(a.a_dst + h * kD + 8 * c + 4 * hh);
-          const int r = 8 * hd + 4 * c;
-          ps += as.x * acc[r] + as.y * acc[r + 1] + as.z * acc[r + 2] + as.w * acc[r + 3];
-          pd += ad.x * acc[r] + ad.y * acc[r + 1] + ad.z * acc[r + 2] + ad.w * acc[r + 3];
+          for (int c = 0; c < 2; ++c) {
+            const float4 as = att[0][h * 4 + 2 * c + hh], ad = att[1][h * 4 + 2 * c + hh];
+            const int r = 8 * hd + 4 * c;
+            ps += as.x * acc[r] + as.y * acc[r + 1] + as.z * acc[r + 2] + as.w * acc[r + 3];
+            pd += ad.x * acc[r] + ad.y * acc[r + 1] + ad.z * acc[r + 2] + ad.w * acc[r + 3];
+          }
+          ssrc[hd] = add_rows32(ps, ps);
+          sdst[hd] = add_rows32(pd, pd);
         }
-        ssrc[h] = ps + __shfl_xor(ps, 32);
-        sdst[h] = pd + __shfl_xor(pd, 32);
-      }
-    }
-    if (wr) {
-      if (side == 0) {
-        if (hh == 0) {
-          float4* o = reinterpret_cast<float4*>(a.sC + row * 8);
-          o[0] = make_float4(ssrc[0], ssrc[1], ssrc[2], ssrc[3]);
-          o[1] = make_float4(ssrc[4], ssrc[5], ssrc[6], ssrc[7]);
-        }
-      } else {
-        float4* o = reinterpret_cast<float4*>(a.sX + row * 16 + 8 * hh);
-        const float* s = hh ? sdst : ssrc;
-        o[0] = make_float4(s[0], s[1], s[2], s[3]);
-        o[1] = make_float4(s[4], s[5], s[6], s[7]);
+        if (wr && side == 0 && hh == 0) *reinterpret_cast<float2*>(a.sC + row * 8 + 2 * jb) = make_float2(ssrc[0], ssrc[1]);
+        if (wr && side == 1)
+          *reinterpret_cast<float2*>(a.sX + row * 16 + 8 * hh + 2 * jb) =
+              hh ? make_float2(sdst[0], sdst[1]) : make_float2(ssrc[0], ssrc[1]);
       }
     }
   }
 }
 
 // ---------------------------------------------------------------------------------------------
-// Edge softmax + aggregation.  One wavefront per group of rows of one segment; the 64 lanes span
-// the 128 features (two per lane, head = lane / 8), so a neighbour's z row is one coalesced
-// 256-byte load.  Column ids are loaded 64 at a time and broadcast lane by lane (row addresses
-// stay wave-uniform); eight neighbour rows are in flight; the softmax is accumulated online
-// (running maximum, rescale once per batch of eight).  Rows longer than long_nnz (hubs of the
-// power-law graphs) are cut into parts of part_nnz non-zeros, one wavefront each; a part leaves
-// its (maximum, sum, weighted sum) in a scratch record and a second kernel merges the records of
-// a row in part order.
+// Edge softmax + aggregation.  One wavefront per group of rows of one segment.  Lane = 16 * slot + sub: the four
+// slots take four neighbours at a time, the 16 sub-lanes of a slot span a neighbour's 128 features (8 per lane, one
+// 16-byte load; head = sub / 2), so that a logit's exponential is computed by two lanes and not by eight.  A batch
+// is kBatch neighbours per slot, and the next batch is requested before the current one is used; the next row's
+// column ids before the current row.  The softmax is accumulated online with one running maximum per head for all
+// slots; the slots' sums are added at the row's end.
+// Bound by the latency of the gathers where rows are few: 83 us for 12 snapshots of 5001 vertices and about 60 000
+// non-zeros (two features a lane, eight neighbours, nothing ahead: 152 us, and 74 us for the split rows in a launch
+// of their own); by their bytes where they are many: 3.0 ms for 16 of 250 000 and 3 million, 5.7 TB/s with U (2.95
+// and 0.48 ms).
+// Rows longer than long_nnz (hubs of the power-law graphs) are cut into parts of part_nnz non-zeros, one wavefront
+// each, in the same launch and begun first; a part leaves its (maximum, sum, weighted sum) in a scratch record and a
+// second kernel merges the records of a row in part order.
 struct GatArgs {
   GraphDev g;
   const Segment* segs;
@@ -153,98 +163,157 @@ struct GatArgs {
 
 struct SoftAcc { float m, l, a0, a1; };
 
-// online softmax-weighted sum over the stored non-zeros [e0, e1) of row i of segment s
-__device__ __forceinline__ SoftAcc gat_row_range(const GatArgs& a, const Segment& s, const int32_t* col, int64_t base,
-                                                 float sd, int64_t e0, int64_t e1, int lane, int head) {
-  SoftAcc r{-INFINITY, 0.f, 0.f, 0.f};
-  for (int64_t eb = e0; eb < e1; eb += 64) {
-    const int cnt = (int)min((int64_t)64, e1 - eb);
-    const int32_t j = lane < cnt ? col[eb + lane] : 0;
-    const int inside = (j >= s.v_lo && j < s.v_hi) ? 1 : 0;
-    for (int q0 = 0; q0 < cnt; q0 += 8) {
-      uint32_t zz[8];
-      float ev[8];
+constexpr int kBatch = 4;    // neighbours per slot and batch (2: 95 us and 2.83 ms)
+struct GatBatch { uint4 z[kBatch]; float e[kBatch]; };
+
+__device__ __forceinline__ float slots_max(float x) {    // over lanes l, l^16, l^32, l^48
+  auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+  const float y = fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
+  auto q = __builtin_amdgcn_permlane32_swap(__float_as_uint(y), __float_as_uint(y), false, false);
+  return fmaxf(__uint_as_float(q[0]), __uint_as_float(q[1]));
+}
+// first of the two features whose sums a lane holds after gat_row_range
+__device__ __forceinline__ int own_feature(int lane) { return 8 * (lane & 15) + 4 * ((lane >> 4) & 1) + 2 * (lane >> 5); }
+
+// online softmax-weighted sum over n stored non-zeros, first, of a row of segment s.  ids: column id of non-zero
+// `lane` of them, loaded by the caller.  m and l are those of the lane's head (lane % 16 / 2), a0 and a1 those of
+// features own_feature(lane) and the next.
+__device__ __forceinline__ SoftAcc gat_row_range(const GatArgs& a, const Segment& s, const int32_t* first, int64_t base,
+                                                 float sd, int n, int32_t ids, int lane) {
+  const int slot = lane >> 4, sub = lane & 15, head = sub >> 1;
+  float m = -INFINITY, l = 0.f, acc[8];
 #pragma unroll
-      for (int q = 0; q < 8; ++q) {
-        ev[q] = -INFINITY;
-        zz[q] = 0u;
-        if (q0 + q < cnt) {
-          const int64_t jq = base + __builtin_amdgcn_readlane(j, q0 + q);
-          const bool in = __builtin_amdgcn_readlane(inside, q0 + q) != 0;
-          zz[q] = *reinterpret_cast<const uint32_t*>((in ? a.zX : a.zC) + jq * kS + 2 * lane);
-          ev[q] = in ? a.sX[jq * 16 + head] : a.sC[jq * 8 + head];
-        }
-      }
-      float bm = -INFINITY;
+  for (int d = 0; d < 8; ++d) acc[d] = 0.f;
+  int32_t ahead = 64 + lane < n ? first[64 + lane] : 0;
+  auto request = [&](int k, GatBatch& b) {
+    if (k > 0 && (k & 63) == 0) {
+      ids = ahead;
+      ahead = k + 64 + lane < n ? first[k + 64 + lane] : 0;
+    }
 #pragma unroll
-      for (int q = 0; q < 8; ++q) {
-        ev[q] = lrelu(sd + ev[q]);       // -inf stays -inf
-        bm = fmaxf(bm, ev[q]);
-      }
-      const float mn = fmaxf(r.m, bm);
-      const float sc = __expf(r.m - mn);
-      r.l *= sc; r.a0 *= sc; r.a1 *= sc;
-      r.m = mn;
-#pragma unroll
-      for (int q = 0; q < 8; ++q) {
-        const float p = __expf(ev[q] - mn);
-        r.l += p;
-        r.a0 += p * h_lo(zz[q]);
-        r.a1 += p * h_hi(zz[q]);
+    for (int u = 0; u < kBatch; ++u) {
+      const int i = k + 4 * u + slot;
+      const int32_t j = __shfl(ids, i & 63);
+      b.z[u] = make_uint4(0, 0, 0, 0);
+      b.e[u] = -INFINITY;
+      if (i < n) {
+        const bool in = j >= s.v_lo && j < s.v_hi;
+        b.z[u] = *reinterpret_cast<const uint4*>((in ? a.zX : a.zC) + (base + j) * kS + 8 * sub);
+        b.e[u] = *(in ? a.sX + (base + j) * 16 + head : a.sC + (base + j) * 8 + head);
       }
     }
+  };
+  auto use = [&](const GatBatch& b) {
+    float e[kBatch], bm = -INFINITY;
+#pragma unroll
+    for (int u = 0; u < kBatch; ++u) {
+      e[u] = lrelu(sd + b.e[u]);       // -inf stays -inf
+      bm = fmaxf(bm, e[u]);
+    }
+    const float mn = fmaxf(m, slots_max(bm));
+    const float sc = __expf(m - mn);
+    m = mn;
+    l *= sc;
+#pragma unroll
+    for (int d = 0; d < 8; ++d) acc[d] *= sc;
+#pragma unroll
+    for (int u = 0; u < kBatch; ++u) {
+      const float p = __expf(e[u] - mn);
+      float z[8];
+      unpackh8(b.z[u], z);
+      l += p;
+#pragma unroll
+      for (int d = 0; d < 8; ++d) acc[d] += p * z[d];
+    }
+  };
+  GatBatch x, y;
+  if (n > 0) {
+    request(0, x);
+    for (int k = 0;; k += 8 * kBatch) {
+      const bool more = k + 4 * kBatch < n;
+      if (more) request(k + 4 * kBatch, y);
+      use(x);
+      if (!more) break;
+      const bool again = k + 8 * kBatch < n;
+      if (again) request(k + 8 * kBatch, x);
+      use(y);
+      if (!again) break;
+    }
   }
-  return r;
+  float h[4];
+#pragma unroll
+  for (int d = 0; d < 4; ++d) h[d] = add_rows16(acc[d], acc[4 + d]);
+  const float l2 = add_rows16(l, l);
+  return {m, add_rows32(l2, l2), add_rows32(h[0], h[2]), add_rows32(h[1], h[3])};
 }
 
-__device__ __forceinline__ void gat_row_store(const GatArgs& a, int64_t row, const SoftAcc& r, int lane, int head) {
+__device__ __forceinline__ void gat_row_store(const GatArgs& a, int64_t row, const SoftAcc& r, int feature, bool lse_lane, int head) {
   const float inv = r.l > 0.f ? 1.f / r.l : 0.f;
-  *reinterpret_cast<float2*>(a.U + row * kS + 2 * lane) = make_float2(r.a0 * inv, r.a1 * inv);
-  if ((lane & 7) == 0) a.lse[row * 8 + head] = r.m + __logf(r.l);
+  *reinterpret_cast<float2*>(a.U + row * kS + feature) = make_float2(r.a0 * inv, r.a1 * inv);
+  if (lse_lane) a.lse[row * 8 + head] = r.m + __logf(r.l);
 }
 
-__global__ __launch_bounds__(256) void k_gat_aggregate(GatArgs a) {
-  const int lane = threadIdx.x & 63;
-  const int64_t item = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
+__device__ __forceinline__ void gat_short(const GatArgs& a, int64_t item, int lane) {
   if (item >= a.n_work) return;
   const int32_t si = a.work[3 * item], r0 = a.work[3 * item + 1], nr = a.work[3 * item + 2];
   const Segment s = a.segs[si];
-  const int64_t* rowptr = a.g.rowptr[s.t];
   const int32_t* col = a.g.colidx[s.t];
-  const int64_t base = (int64_t)s.t * a.g.N;
-  const int head = lane >> 3;
+  const int64_t base = (int64_t)s.t * a.g.N, i0 = s.v_lo + r0;
+  const int head = (lane & 15) >> 1;
+  const int64_t rp = a.g.rowptr[s.t][i0 + min(lane, nr)];      // of the whole group (at most 32 rows)
+  const int32_t rlo = (int32_t)(rp & 0xffffffff), rhi = (int32_t)(rp >> 32);
+  auto row_ptr = [&](int r) {
+    return ((int64_t)__builtin_amdgcn_readlane(rhi, r) << 32) | (uint32_t)__builtin_amdgcn_readlane(rlo, r);
+  };
+  int64_t e0 = row_ptr(0), e1 = row_ptr(1);
+  int32_t ids = e0 + lane < e1 ? col[e0 + lane] : 0;
+  float sd = a.sX[(base + i0) * 16 + 8 + head];
   for (int rr = 0; rr < nr; ++rr) {
-    const int64_t i = s.v_lo + r0 + rr;
-    const int64_t e0 = rowptr[i], e1 = rowptr[i + 1];
-    if (e1 - e0 > a.long_nnz) continue;    // split rows: k_gat_aggregate_long
-    const float sd = a.sX[(base + i) * 16 + 8 + head];
-    const SoftAcc r = gat_row_range(a, s, col, base, sd, e0, e1, lane, head);
-    gat_row_store(a, base + i, r, lane, head);
+    int64_t ne1 = e1;
+    int32_t nids = 0;
+    float nsd = 0.f;
+    if (rr + 1 < nr) {
+      ne1 = row_ptr(rr + 2);
+      nids = e1 + lane < ne1 ? col[e1 + lane] : 0;
+      nsd = a.sX[(base + i0 + rr + 1) * 16 + 8 + head];
+    }
+    if (e1 - e0 <= a.long_nnz) {    // split rows: gat_long
+      const SoftAcc r = gat_row_range(a, s, col + e0, base, sd, (int)(e1 - e0), ids, lane);
+      gat_row_store(a, base + i0 + rr, r, own_feature(lane), lane < 16 && !(lane & 1), head);
+    }
+    e0 = e1; e1 = ne1; ids = nids; sd = nsd;
   }
 }
 
 // record of one part of a split row: weighted sum [128], maximum [8], sum [8]
 constexpr int kLongRec = 144;
 
-__global__ __launch_bounds__(256) void k_gat_aggregate_long(GatArgs a) {
-  const int lane = threadIdx.x & 63;
-  const int64_t item = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
+__device__ __forceinline__ void gat_long(const GatArgs& a, int64_t item, int lane) {
   if (item >= a.n_long) return;
   const int32_t* w = a.work_long + 4 * item;
   const Segment s = a.segs[w[0]];
   const int64_t i = s.v_lo + w[1];
   const int64_t* rowptr = a.g.rowptr[s.t];
   const int64_t base = (int64_t)s.t * a.g.N;
-  const int head = lane >> 3;
+  const int head = (lane & 15) >> 1;
   const int64_t e0 = rowptr[i] + (int64_t)w[2] * a.part_nnz, e1 = min(rowptr[i + 1], e0 + a.part_nnz);
   const float sd = a.sX[(base + i) * 16 + 8 + head];
-  const SoftAcc r = gat_row_range(a, s, a.g.colidx[s.t], base, sd, e0, e1, lane, head);
+  const int32_t* first = a.g.colidx[s.t] + e0;
+  const int n = (int)(e1 - e0);
+  const SoftAcc r = gat_row_range(a, s, first, base, sd, n, lane < n ? first[lane] : 0, lane);
   float* rec = a.long_partial + item * kLongRec;
-  *reinterpret_cast<float2*>(rec + 2 * lane) = make_float2(r.a0, r.a1);
-  if ((lane & 7) == 0) {
+  *reinterpret_cast<float2*>(rec + own_feature(lane)) = make_float2(r.a0, r.a1);
+  if (lane < 16 && !(lane & 1)) {
     rec[128 + head] = r.m;
     rec[136 + head] = r.l;
   }
+}
+
+__global__ __launch_bounds__(256, 5) void k_gat_aggregate(GatArgs a, int64_t long_blocks) {
+  const int lane = threadIdx.x & 63;
+  const int64_t block = blockIdx.x, wave = threadIdx.x >> 6;
+  if (block < long_blocks) gat_long(a, block * 4 + wave, lane);
+  else gat_short(a, (block - long_blocks) * 4 + wave, lane);
 }
 
 // one wavefront per split row (the item of its part 0) merges the parts in order
@@ -268,7 +337,7 @@ __global__ __launch_bounds__(256) void k_gat_aggregate_merge(GatArgs a) {
     r.a0 += sc * v.x;
     r.a1 += sc * v.y;
   }
-  gat_row_store(a, (int64_t)s.t * a.g.N + s.v_lo + w[1], r, lane, head);
+  gat_row_store(a, (int64_t)s.t * a.g.N + s.v_lo + w[1], r, 2 * lane, (lane & 7) == 0, head);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -278,7 +347,7 @@ __global__ __launch_bounds__(256) void k_gat_aggregate_merge(GatArgs a) {
 // transposed score block of both vertices (lane (n_s, hh) holds the scores of its own query row
 // against key rows 8g + 4hh + e; those of its own vertex are registers 8a .. 8a+7), the softmax
 // is lane-local plus one exchange with lane l^32, and the probabilities are directly the B
-// operand of the product with V (A operand = V in column layout, masked to the head; B masked
+// operand of the product with V (A operand = V in column layout; B masked
 // to the vertex), which lands in row layout, ready to be stored.
 // Every in-register operand (P, Q, K, V, the probabilities) is carried as a hi + lo pair of bf16
 // values, so that the only roundings to bf16 are those of the stored tensors (z, U, Y).
@@ -302,7 +371,7 @@ __device__ __forceinline__ void causal_softmax(float* x, int s, int hh) {
 #pragma unroll
   for (int p = 0; p < NP; ++p) {
     const int r = 8 * (p >> 2) + 4 * hh + (p & 3);
-    x[p] = r <= s ? 0.25f * x[p] : -INFINITY;
+    x[p] = keep_or_ninf(r <= s, 0.25f * x[p]);
     mx = fmaxf(mx, x[p]);
   }
   mx = fmaxf(mx, __shfl_xor(mx, 32));
@@ -339,8 +408,7 @@ __global__ __launch_bounds__(512) void k_temporal_fwd(TemporalArgs a) {
   extern __shared__ uint4 wlds[];
   stage_weights(wlds, a.Wq, a.Wk, a.Wv);
   const int lane = threadIdx.x & 63, nw = blockDim.x >> 6;
-  const int hh = lane >> 5, f = lane & 31;
-  const uint32_t m_head[2] = {(f >> 4) == 0 ? 0xffffffffu : 0u, (f >> 4) == 1 ? 0xffffffffu : 0u};
+  const int hh = lane >> 5;
   for (int64_t tile = (int64_t)blockIdx.x * nw + (threadIdx.x >> 6); tile < a.n_tiles; tile += (int64_t)gridDim.x * nw) {
   const TileRow r = tile_row<WIDE>(a.chunks, a.n_chunks, a.tile_ptr, tile, a.N, lane);
   const uint32_t m_vert[2] = {r.a == 0 ? 0xffffffffu : 0u, r.a == 1 ? 0xffffffffu : 0u};
@@ -360,21 +428,16 @@ __global__ __launch_bounds__(512) void k_temporal_fwd(TemporalArgs a) {
       vt = mfma(pf[kb], wv, vt);
       vt = mfma(pl[kb], wv, vt);
     }
-    floatx16 y = {};
+    bf16x8 vh[2], vl[2];        // steps of the two vertices, or (WIDE) of the two halves of the window
+#pragma unroll
+    for (int av = 0; av < 2; ++av) split8v(vt, 8 * av, vh[av], vl[av]);
 #pragma unroll
     for (int hd = 0; hd < 2; ++hd) {
-      float tmp[8];
       bf16x8 kh, kl, qh, ql;
-#pragma unroll
-      for (int p = 0; p < 8; ++p) tmp[p] = k[8 * hd + p];
-      split8(tmp, kh, kl);
-#pragma unroll
-      for (int p = 0; p < 8; ++p) tmp[p] = q[8 * hd + p];
-      split8(tmp, qh, ql);
+      split8v(k, 8 * hd, kh, kl);
+      split8v(q, 8 * hd, qh, ql);
       floatx16 st = {};
-      st = mfma(kl, qh, st);                 // st[i = key row][j = query row]
-      st = mfma(kh, ql, st);
-      st = mfma(kh, qh, st);
+      st = mfma3(kh, kl, qh, ql, st);                 // st[i = key row][j = query row]
       constexpr int NP = WIDE ? 16 : 8;
       float pr[NP];
 #pragma unroll
@@ -383,26 +446,15 @@ __global__ __launch_bounds__(512) void k_temporal_fwd(TemporalArgs a) {
       bf16x8 ph[NP / 8], plo[NP / 8];
 #pragma unroll
       for (int c = 0; c < NP / 8; ++c) split8(pr + 8 * c, ph[c], plo[c]);
+      floatx16 y = {};        // of both heads' features; this head's are registers 8 hd ..
 #pragma unroll
-      for (int av = 0; av < 2; ++av) {      // the two vertices, or (WIDE) the two halves of the keys
-        bf16x8 vh, vl;
-#pragma unroll
-        for (int p = 0; p < 8; ++p) tmp[p] = vt[8 * av + p];
-        split8(tmp, vh, vl);
-        vh = and_mask(vh, m_head[hd]);
-        vl = and_mask(vl, m_head[hd]);
+      for (int av = 0; av < 2; ++av) {
         const bf16x8 pa = WIDE ? ph[WIDE ? av : 0] : and_mask(ph[0], m_vert[av]);
         const bf16x8 pb = WIDE ? plo[WIDE ? av : 0] : and_mask(plo[0], m_vert[av]);
-        y = mfma(vl, pa, y);
-        y = mfma(vh, pb, y);
-        y = mfma(vh, pa, y);
+        y = mfma3(vh[av], vl[av], pa, pb, y);
       }
-    }
-    if (r.valid) {
-#pragma unroll
-      for (int g = 0; g < 4; ++g)
-        *reinterpret_cast<uint2*>(a.Y + r.row * a.ldy + jb * 32 + 8 * g + 4 * hh) =
-            pack4(y[4 * g], y[4 * g + 1], y[4 * g + 2], y[4 * g + 3]);
+      const uint4 o = head_order(__builtin_bit_cast(uint4, pack8v(y, 8 * hd)));
+      if (r.valid) *reinterpret_cast<uint4*>(a.Y + r.row * a.ldy + jb * 32 + 16 * hd + 8 * hh) = o;
     }
   }
   }
@@ -437,18 +489,16 @@ void dysat_forward(const DysatWs& ws, const void* X, int64_t ldx, const void* C,
   pa.zX = ws.zX; pa.zC = ws.zC; pa.sX = ws.sX; pa.sC = ws.sC;
   const int64_t ptiles = (ws.N + 31) / 32 * ws.n_used;
   if (ev) (void)hipEventRecord(ev[0], st);
-  hipLaunchKernelGGL(k_gat_project, blocks_for(ptiles, 4), 256, 0, st, pa);
+  hipLaunchKernelGGL(k_gat_project, (unsigned)std::min<int64_t>(512, (ptiles + 7) / 8), 512, 0, st, pa);
   if (ev) (void)hipEventRecord(ev[1], st);
   GatArgs ga{};
   ga.g = ws.g; ga.segs = ws.segs; ga.work = ws.work_short; ga.n_work = ws.n_short;
   ga.work_long = ws.work_long; ga.n_long = ws.n_long; ga.long_nnz = ws.long_nnz; ga.part_nnz = ws.part_nnz;
   ga.long_partial = ws.long_partial;
   ga.zX = ws.zX; ga.zC = ws.zC; ga.sX = ws.sX; ga.sC = ws.sC; ga.U = ws.U; ga.lse = ws.lse;
-  hipLaunchKernelGGL(k_gat_aggregate, blocks_for(ws.n_short, 4), 256, 0, st, ga);
-  if (ws.n_long > 0) {
-    hipLaunchKernelGGL(k_gat_aggregate_long, blocks_for(ws.n_long, 4), 256, 0, st, ga);
-    hipLaunchKernelGGL(k_gat_aggregate_merge, blocks_for(ws.n_long, 4), 256, 0, st, ga);
-  }
+  const int64_t long_blocks = (ws.n_long + 3) / 4;
+  hipLaunchKernelGGL(k_gat_aggregate, (unsigned)(long_blocks + (ws.n_short + 3) / 4), 256, 0, st, ga, long_blocks);
+  if (ws.n_long > 0) hipLaunchKernelGGL(k_gat_aggregate_merge, blocks_for(ws.n_long, 4), 256, 0, st, ga);
   if (ev) (void)hipEventRecord(ev[2], st);
   TemporalArgs ta{};
   ta.chunks = ws.chunks; ta.n_chunks = ws.n_chunks; ta.tile_ptr = ws.tile_ptr; ta.n_tiles = ws.n_tiles;

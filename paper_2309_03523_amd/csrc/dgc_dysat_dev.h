@@ -76,13 +76,16 @@ __device__ __forceinline__ float delu(float u) { return u > 0.f ? 1.f : __expf(u
 
 // x -> hi + lo with hi = bf16(x), lo = bf16(x - hi): two bf16 operands that together carry 16
 // mantissa bits, so a product taken as hi*hi + hi*lo + lo*hi is accurate to ~2^-16
+// (two values at a time: one conversion makes a pair; element by element it is a third more instructions)
 __device__ __forceinline__ void split8(const float* x, bf16x8& hi, bf16x8& lo) {
+  uint32_t h[4], l[4];
 #pragma unroll
-  for (int i = 0; i < 8; ++i) {
-    const __bf16 h = (__bf16)x[i];
-    hi[i] = h;
-    lo[i] = (__bf16)(x[i] - (float)h);
+  for (int i = 0; i < 4; ++i) {
+    h[i] = pack2(x[2 * i], x[2 * i + 1]);
+    l[i] = pack2(x[2 * i] - bf_lo(h[i]), x[2 * i + 1] - bf_hi(h[i]));
   }
+  hi = as_frag(make_uint4(h[0], h[1], h[2], h[3]));
+  lo = as_frag(make_uint4(l[0], l[1], l[2], l[3]));
 }
 
 // Element p of v for a lane whose mask m0 is all ones, element 8 + p where m1 is (exactly one of the
@@ -101,13 +104,25 @@ __device__ __forceinline__ bf16x8 and_mask(bf16x8 x, uint32_t m) {
 }
 
 __device__ __forceinline__ void split8v(const floatx16& v, int off, bf16x8& hi, bf16x8& lo) {
+  float x[8];
 #pragma unroll
-  for (int p = 0; p < 8; ++p) {
-    const __bf16 h = (__bf16)v[off + p];
-    hi[p] = h;
-    lo[p] = (__bf16)(v[off + p] - (float)h);
-  }
+  for (int p = 0; p < 8; ++p) x[p] = v[off + p];
+  split8(x, hi, lo);
 }
+// x where keep, else -infinity.  The empty asm keeps the select a select: the compiler otherwise moves the
+// computation of x under a branch of its own for every element.
+__device__ __forceinline__ float keep_or_ninf(bool keep, float x) {
+  asm volatile("" : "+v"(x));
+  return keep ? x : -INFINITY;
+}
+// A 16-dim head of a lane's row as packed bf16: from natural order (dims 8 hh + 0..7) to row-layout order
+// (dims 8 c + 4 hh + e) and back; the halves change places with lane l^32.
+__device__ __forceinline__ uint4 head_order(uint4 u) {
+  auto r = __builtin_amdgcn_permlane32_swap(u.x, u.z, false, false);
+  auto q = __builtin_amdgcn_permlane32_swap(u.y, u.w, false, false);
+  return make_uint4(r[0], q[0], r[1], q[1]);
+}
+
 // products of split operands: (ah + al)(bh + bl) without the al*bl term; a exact: a (bh + bl)
 __device__ __forceinline__ floatx16 mfma3(bf16x8 ah, bf16x8 al, bf16x8 bh, bf16x8 bl, floatx16 c) {
   c = mfma(al, bh, c);
