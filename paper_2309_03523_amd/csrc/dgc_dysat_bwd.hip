@@ -81,177 +81,164 @@ __device__ __forceinline__ void stage_weights(uint4* lds, const uint4* w0, const
   __syncthreads();
 }
 
+// One head of a row-layout tensor in column layout: out[c] = rows 16 c .. of the lane's feature, zero for the
+// features that sel does not take.  Exact: a product with 0 and 1.
+__device__ __forceinline__ void to_columns(bf16x8 x, bf16x8 sel, bf16x8* out) {
+  floatx16 t = {};
+  t = mfma(x, sel, t);
+  out[0] = pack8v(t, 0);
+  out[1] = pack8v(t, 8);
+}
+
 // Temporal self-attention, backward, first half: dQ, dK, dV (and the loss).  The workgroup stages
 // W_q, W_k, W_v in LDS; each of its waves then walks 2-vertex tiles with a grid stride.  Per tile
-// it recomputes P, Q, K, V (Q, K also in column layout).  Per head, the "query-major" score block
+// it recomputes P, Q, K, V.  Per head, the "query-major" score block
 // (lane = query row, registers = key steps) gives the probabilities p, delta = sum_r p dp and dS;
 // dQ needs dS in that orientation, dK and dV need dS and p "key-major" (lane = key row,
 // registers = query steps): those are obtained by one product each with a selection operand
-// (a 16 x 16 transpose per vertex on the matrix core, exact for the hi and the lo part).
-// All operands are hi + lo pairs.  dQ, dK, dV land in row layout and are stored (bf16).
+// (a 16 x 16 transpose per vertex on the matrix core, exact for the hi and the lo part); so are Q, K and dY in
+// column layout, which the three products take as their other operand.  A head's 16 dims go to memory (bf16) before the
+// next head is begun.
+// All operands are hi + lo pairs.
+// Bound by the vector units (softmax, splits) and the matrix cores side by side (the memory's share is 1.5 of
+// 2.9 ms at 4 000 000 rows): at most 256 registers, so that a SIMD has two waves to overlap them
+// (4.2 ms with one wave of 392 registers, which held Q, K by a second set of products and the three results).
 // WIDE (one vertex per tile, windows of up to 32 snapshots): a lane's 16 score registers are all
 // keys of its own vertex, the transposes are 32 x 32 (two selection products, one per half of the
 // keys), and the three final products contract over the two halves of the keys / queries instead
 // of over two vertices.
 template <bool WIDE>
-__global__ __launch_bounds__(256) void k_temporal_bwd(TemporalBwdArgs a) {
+__global__ __launch_bounds__(512) void k_temporal_bwd(TemporalBwdArgs a) {
   extern __shared__ uint4 wlds[];
   stage_weights(wlds, a.Wq, a.Wk, a.Wv);
   const int lane = threadIdx.x & 63, nw = blockDim.x >> 6, wave = threadIdx.x >> 6;
-  const int hh = lane >> 5, f = lane & 31;
+  const int hh = lane >> 5;
   float sq = 0.f;
-  const uint32_t m_head[2] = {(f >> 4) == 0 ? 0xffffffffu : 0u, (f >> 4) == 1 ? 0xffffffffu : 0u};
-  const bf16x8 sel0 = sel_frag(0, lane), sel1 = sel_frag(1, lane);
   constexpr int NP = WIDE ? 16 : 8, NH = NP / 8;
-  // B operand: element p of lane (j, hh) is 1 where step 8 (p/4) + 4 hh + p%4 == j % 16 (WIDE: where
-  // step 16 c + ... == j, one operand per half c of the steps)
-  bf16x8 selT[NH];
+  // B operands: element p of lane (j, hh) is 1 where 16 c + 8 (p/4) + 4 hh + p%4 == j
+  bf16x8 sel[2];
 #pragma unroll
-  for (int c = 0; c < NH; ++c)
+  for (int c = 0; c < 2; ++c)
 #pragma unroll
     for (int p = 0; p < 8; ++p)
-      selT[c][p] = (16 * c + 8 * (p >> 2) + 4 * hh + (p & 3) == (WIDE ? (lane & 31) : (lane & 15))) ? (__bf16)1.0f : (__bf16)0.0f;
+      sel[c][p] = 16 * c + 8 * (p >> 2) + 4 * hh + (p & 3) == (lane & 31) ? (__bf16)1.0f : (__bf16)0.0f;
   for (int64_t tile = (int64_t)blockIdx.x * nw + wave; tile < a.n_tiles; tile += (int64_t)gridDim.x * nw) {
     const TileRow r = tile_row<WIDE>(a.chunks, a.n_chunks, a.tile_ptr, tile, a.N, lane);
     const uint32_t m_vert[2] = {r.a == 0 ? 0xffffffffu : 0u, r.a == 1 ? 0xffffffffu : 0u};
-    DyRaw raw[2];
-    raw[0] = load_dy_raw(a, r.row, 8 * hh, r.valid);
-    raw[1] = load_dy_raw(a, r.row, 16 + 8 * hh, r.valid);
     bf16x8 pf[8], pl[8];
     load_p_frags<true>(a.U, a.pos, r, hh, pf, pl);
 #pragma unroll 1
     for (int jb = 0; jb < 4; ++jb) {
-      // dL/dY of features [32 jb, 32 jb + 32): d8[c] = natural fragment kb = 2 jb + c; the next
-      // block's pieces are requested now
-      float d8[2][8];
-      dy_from_raw(a, raw[0], d8[0], sq);
-      dy_from_raw(a, raw[1], d8[1], sq);
-      if (jb < 3) {
-        raw[0] = load_dy_raw(a, r.row, (2 * jb + 2) * 16 + 8 * hh, r.valid);
-        raw[1] = load_dy_raw(a, r.row, (2 * jb + 3) * 16 + 8 * hh, r.valid);
-      }
-      floatx16 q = {}, k = {}, v = {}, qt = {}, kt = {}, dyt = {};
-#pragma unroll
-      for (int kb = 0; kb < 8; ++kb) {
-        const int fi = (jb * 8 + kb) * 64 + lane;
-        const bf16x8 wq = as_frag(wlds[fi]), wk = as_frag(wlds[kFragsPerW + fi]), wv = as_frag(wlds[2 * kFragsPerW + fi]);
-        q = mfma2b(wq, pf[kb], pl[kb], q);
-        k = mfma2b(wk, pf[kb], pl[kb], k);
-        v = mfma2b(wv, pf[kb], pl[kb], v);
-        qt = mfma2a(pf[kb], pl[kb], wq, qt);
-        kt = mfma2a(pf[kb], pl[kb], wk, kt);
-      }
+      DyRaw raw[2];
+      raw[0] = load_dy_raw(a, r.row, 2 * jb * 16 + 8 * hh, r.valid);
+      raw[1] = load_dy_raw(a, r.row, (2 * jb + 1) * 16 + 8 * hh, r.valid);
+      bf16x8 kh[2], kl[2], qh[2], ql[2], vh[2], vl[2];
       {
-        bf16x8 dh, dl;
-        split8(d8[0], dh, dl);
-        dyt = mfma2a(dh, dl, sel0, dyt);
-        split8(d8[1], dh, dl);
-        dyt = mfma2a(dh, dl, sel1, dyt);
+        floatx16 q = {}, k = {}, v = {};
+#pragma unroll
+        for (int kb = 0; kb < 8; ++kb) {
+          const int fi = (jb * 8 + kb) * 64 + lane;
+          q = mfma2b(as_frag(wlds[fi]), pf[kb], pl[kb], q);
+          k = mfma2b(as_frag(wlds[kFragsPerW + fi]), pf[kb], pl[kb], k);
+          v = mfma2b(as_frag(wlds[2 * kFragsPerW + fi]), pf[kb], pl[kb], v);
+        }
+#pragma unroll
+        for (int c = 0; c < 2; ++c) {
+          split8v(q, 8 * c, qh[c], ql[c]);
+          split8v(k, 8 * c, kh[c], kl[c]);
+          split8v(v, 8 * c, vh[c], vl[c]);
+        }
       }
-      floatx16 dq = {}, dk = {}, dv = {};
+      // dL/dY of features [32 jb, 32 jb + 32), head c in row-layout order; the next block's pieces
+      // are requested now
+      bf16x8 dyh[2], dyl[2];
+#pragma unroll
+      for (int c = 0; c < 2; ++c) {
+        float d8[8];
+        dy_from_raw(a, raw[c], d8, sq);
+        bf16x8 h, l;
+        split8(d8, h, l);
+        dyh[c] = as_frag(head_order(__builtin_bit_cast(uint4, h)));
+        dyl[c] = as_frag(head_order(__builtin_bit_cast(uint4, l)));
+      }
 #pragma unroll
       for (int hd = 0; hd < 2; ++hd) {
-        bf16x8 kh, kl, qh, ql, vh, vl, dyh, dyl;
-        split8v(k, 8 * hd, kh, kl);
-        split8v(q, 8 * hd, qh, ql);
-        split8v(v, 8 * hd, vh, vl);
-        {
-          // dL/dY of the head's 16 dims in row-layout order: dims 8 c + 4 hh + e; the half c == hh is
-          // in the lane's own natural fragment, the other half in lane l^32's
-          float x[8];
-#pragma unroll
-          for (int e = 0; e < 4; ++e) {
-            const float lo4 = d8[hd][e], hi4 = d8[hd][4 + e];   // static indices: a lane-dependent index
-            const float other = xor32(hh ? lo4 : hi4, hh);       // would be lowered to a chain of selects
-            const float own = hh ? hi4 : lo4;
-            x[e] = hh ? other : own;
-            x[4 + e] = hh ? own : other;
-          }
-          split8(x, dyh, dyl);
-        }
-        floatx16 st = {}, dpt = {};
-        st = mfma3(kh, kl, qh, ql, st);         // [key row][query row]
-        dpt = mfma3(vh, vl, dyh, dyl, dpt);
-        float pr[NP], dst[NP];
-        float mx = -INFINITY;
-#pragma unroll
-        for (int p = 0; p < NP; ++p) {
-          const int rk = 8 * (p >> 2) + 4 * hh + (p & 3);
-          pr[p] = rk <= r.s ? 0.25f * (WIDE ? st[p] : pick_half(st, p, m_vert[0], m_vert[1])) : -INFINITY;
-          mx = fmaxf(mx, pr[p]);
-        }
-        mx = fmaxf(mx, xor32(mx, hh));
-        float sum = 0.f;
-#pragma unroll
-        for (int p = 0; p < NP; ++p) {
-          pr[p] = __expf(pr[p] - mx);
-          sum += pr[p];
-        }
-        sum += xor32(sum, hh);
-        const float inv = 1.f / sum;
-        float delta = 0.f;
-#pragma unroll
-        for (int p = 0; p < NP; ++p) {
-          pr[p] *= inv;
-          dst[p] = WIDE ? dpt[p] : pick_half(dpt, p, m_vert[0], m_vert[1]);
-          delta += pr[p] * dst[p];
-        }
-        delta += xor32(delta, hh);
-#pragma unroll
-        for (int p = 0; p < NP; ++p) dst[p] = 0.25f * pr[p] * (dst[p] - delta);
         bf16x8 dsth[NH], dstl[NH], prh[NH], prl[NH];
+        {
+          floatx16 st = {}, dpt = {};
+          st = mfma3(kh[hd], kl[hd], qh[hd], ql[hd], st);         // [key row][query row]
+          dpt = mfma3(vh[hd], vl[hd], dyh[hd], dyl[hd], dpt);
+          float pr[NP], dst[NP];
+          float mx = -INFINITY;
 #pragma unroll
-        for (int c = 0; c < NH; ++c) {
-          split8(dst + 8 * c, dsth[c], dstl[c]);
-          split8(pr + 8 * c, prh[c], prl[c]);
-        }
-        // key-major copies: T[i = query row][j = key row]
-        floatx16 t0 = {}, t1 = {}, t2 = {}, t3 = {};
+          for (int p = 0; p < NP; ++p) {
+            const int rk = 8 * (p >> 2) + 4 * hh + (p & 3);
+            pr[p] = keep_or_ninf(rk <= r.s, 0.25f * (WIDE ? st[p] : pick_half(st, p, m_vert[0], m_vert[1])));
+            mx = fmaxf(mx, pr[p]);
+          }
+          mx = fmaxf(mx, xor32(mx, hh));
+          float sum = 0.f;
 #pragma unroll
-        for (int c = 0; c < NH; ++c) {
-          t0 = mfma(dsth[c], selT[c], t0);
-          t1 = mfma(dstl[c], selT[c], t1);
-          t2 = mfma(prh[c], selT[c], t2);
-          t3 = mfma(prl[c], selT[c], t3);
-        }
-        // own-vertex half of the registers, blended arithmetically (a select here gets merged with the
-        // packing below into per-element selects on 16-bit halves); WIDE: all 16 are the vertex's own
-        const float fa0 = r.a ? 0.f : 1.f, fa1 = 1.f - fa0;
-        float tx[4][NP];
+          for (int p = 0; p < NP; ++p) {
+            pr[p] = __expf(pr[p] - mx);
+            sum += pr[p];
+          }
+          sum += xor32(sum, hh);
+          const float inv = 1.f / sum;
+          float delta = 0.f;
 #pragma unroll
-        for (int p = 0; p < NP; ++p) {
-          tx[0][p] = WIDE ? t0[p] : fa0 * t0[p] + fa1 * t0[8 + (p & 7)];
-          tx[1][p] = WIDE ? t1[p] : fa0 * t1[p] + fa1 * t1[8 + (p & 7)];
-          tx[2][p] = WIDE ? t2[p] : fa0 * t2[p] + fa1 * t2[8 + (p & 7)];
-          tx[3][p] = WIDE ? t3[p] : fa0 * t3[p] + fa1 * t3[8 + (p & 7)];
-        }
-        bf16x8 ds2h[NH], ds2l[NH], p2h[NH], p2l[NH];
+          for (int p = 0; p < NP; ++p) {
+            pr[p] *= inv;
+            dst[p] = WIDE ? dpt[p] : pick_half(dpt, p, m_vert[0], m_vert[1]);
+            delta += pr[p] * dst[p];
+          }
+          delta += xor32(delta, hh);
 #pragma unroll
-        for (int c = 0; c < NH; ++c) {
-          ds2h[c] = pack8(tx[0] + 8 * c); ds2l[c] = pack8(tx[1] + 8 * c);
-          p2h[c] = pack8(tx[2] + 8 * c); p2l[c] = pack8(tx[3] + 8 * c);
-        }
+          for (int p = 0; p < NP; ++p) dst[p] = 0.25f * pr[p] * (dst[p] - delta);
 #pragma unroll
-        for (int av = 0; av < 2; ++av) {      // the two vertices, or (WIDE) the two halves of the window's steps
-          const uint32_t mv = WIDE ? 0xffffffffu : m_vert[av], mh = m_head[hd];
-          const int c = WIDE ? av : 0;
-          bf16x8 ah, al;
-          split8v(kt, 8 * av, ah, al);
-          dq = mfma3(and_mask(ah, mh), and_mask(al, mh), and_mask(dsth[c], mv), and_mask(dstl[c], mv), dq);
-          split8v(qt, 8 * av, ah, al);
-          dk = mfma3(and_mask(ah, mh), and_mask(al, mh), and_mask(ds2h[c], mv), and_mask(ds2l[c], mv), dk);
-          split8v(dyt, 8 * av, ah, al);
-          dv = mfma3(and_mask(ah, mh), and_mask(al, mh), and_mask(p2h[c], mv), and_mask(p2l[c], mv), dv);
+          for (int c = 0; c < NH; ++c) {
+            split8(dst + 8 * c, dsth[c], dstl[c]);
+            split8(pr + 8 * c, prh[c], prl[c]);
+          }
         }
-      }
-      if (r.valid) {
+        // d[f][row] = sum over av (the two vertices, or, WIDE, the two halves of the window's steps) of
+        // x[f][steps of av] b[steps of av][row]; dims of this head: registers 8 hd ..
+        auto product = [&](bf16x8 xh, bf16x8 xl, const bf16x8* bh, const bf16x8* bl, uint16_t* out) {
+          bf16x8 xth[2], xtl[2];
+          to_columns(xh, sel[hd], xth);
+          to_columns(xl, sel[hd], xtl);
+          floatx16 d = {};
 #pragma unroll
-        for (int g = 0; g < 4; ++g) {
-          const int64_t o = r.row * kS + jb * 32 + 8 * g + 4 * hh;
-          *reinterpret_cast<uint2*>(a.dQ + o) = pack4(dq[4 * g], dq[4 * g + 1], dq[4 * g + 2], dq[4 * g + 3]);
-          *reinterpret_cast<uint2*>(a.dK + o) = pack4(dk[4 * g], dk[4 * g + 1], dk[4 * g + 2], dk[4 * g + 3]);
-          *reinterpret_cast<uint2*>(a.dV + o) = pack4(dv[4 * g], dv[4 * g + 1], dv[4 * g + 2], dv[4 * g + 3]);
-        }
+          for (int av = 0; av < 2; ++av) {
+            const uint32_t mv = WIDE ? 0xffffffffu : m_vert[av];
+            d = mfma3(xth[av], xtl[av], and_mask(bh[av], mv), and_mask(bl[av], mv), d);
+          }
+          const uint4 o = head_order(__builtin_bit_cast(uint4, pack8v(d, 8 * hd)));
+          if (r.valid) *reinterpret_cast<uint4*>(out + r.row * kS + jb * 32 + 16 * hd + 8 * hh) = o;
+        };
+        // key-major copy of one part: T[i = query row][j = key row], the query rows of vertex (half) c in bt[c]
+        auto key_major = [&](const bf16x8* b, bf16x8* bt) {
+          floatx16 t = {};
+          if (WIDE) {
+#pragma unroll
+            for (int c = 0; c < NH; ++c) t = mfma(b[c], sel[c], t);
+          } else {
+            const uint4 s0 = __builtin_bit_cast(uint4, sel[0]), s1 = __builtin_bit_cast(uint4, sel[1]);
+            t = mfma(b[0], as_frag(make_uint4(s0.x | s1.x, s0.y | s1.y, s0.z | s1.z, s0.w | s1.w)), t);   // j % 16
+          }
+          bt[0] = pack8v(t, 0);
+          bt[1] = pack8v(t, 8);
+        };
+        bf16x8 bh[2], bl[2];
+        bh[0] = dsth[0]; bh[1] = dsth[NH - 1];
+        bl[0] = dstl[0]; bl[1] = dstl[NH - 1];
+        product(kh[hd], kl[hd], bh, bl, a.dQ);
+        key_major(dsth, bh);
+        key_major(dstl, bl);
+        product(qh[hd], ql[hd], bh, bl, a.dK);
+        key_major(prh, bh);
+        key_major(prl, bl);
+        product(dyh[hd], dyl[hd], bh, bl, a.dV);
       }
     }
   }
@@ -261,11 +248,15 @@ __global__ __launch_bounds__(256) void k_temporal_bwd(TemporalBwdArgs a) {
 }
 
 // Temporal self-attention, backward, second half: dP = dQ W_q + dK W_k + dV W_v from the stored
-// gradients, dU = dP * ELU'(U), and the gradient of the position table (column sums of dP per
+// gradients, dU = dP * ELU'(U), c = du . u per head for the passes over the non-zeros, and the gradient of the
+// position table (column sums of dP per
 // snapshot).  Rows are the covered vertices of the snapshots in use, 32 per tile; the transposed
-// weights are staged in LDS; dQ/dK/dV row fragments are B operands as they come from memory.
+// weights are staged in LDS; dQ/dK/dV row fragments are B operands as they come from memory, a quarter of the row at a
+// time with the next two quarters on their way (also those of the next tile).  They are loaded whether or not the row
+// counts and masked when used: loads under a condition are waited for one by one.
 // Every wave sums dP over its tiles in registers (lane = row slot) and, when the snapshot
 // changes, adds the 32 row slots and writes the sums to its own slot of the scratch buffer.
+// Bound by memory: 6.3 GB in 1.72 ms for 4 000 000 rows (2.13 ms with three conditional loads in flight).
 struct TemporalBwd2Args {
   const int32_t* used_t; int32_t n_used; int64_t N; int32_t T;
   const int32_t* owner;
@@ -273,6 +264,7 @@ struct TemporalBwd2Args {
   const uint4 *WqT, *WkT, *WvT;
   const uint16_t *dQ, *dK, *dV;
   uint16_t* dU;
+  float* c;              // [T*N][16]: c^h = du^h . u^h of the graph attention in the first 8
   float* dpos_partial;   // [gridDim.x * waves per block][T][128], zero on entry
 };
 
@@ -312,46 +304,82 @@ __global__ __launch_bounds__(512) void k_temporal_bwd2(TemporalBwd2Args a) {
   float* slot = a.dpos_partial + gw * a.T * kS;
   floatx16 dpos[4] = {};
   int cur_t = -1;
+  struct Quarter { uint4 q[2], k[2], v[2]; };      // a quarter of the lane's rows
+  auto request = [&](int64_t row, int part, Quarter& x) {
+    const int64_t o = row * kS + 32 * part + 8 * hh;
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      x.q[i] = *reinterpret_cast<const uint4*>(a.dQ + o + 16 * i);
+      x.k[i] = *reinterpret_cast<const uint4*>(a.dK + o + 16 * i);
+      x.v[i] = *reinterpret_cast<const uint4*>(a.dV + o + 16 * i);
+    }
+  };
+  int64_t row = 0, next_row = 0;
+  auto row_of = [&](int64_t tile) {      // always a row of the tensors
+    return (int64_t)a.used_t[tile / tiles_per_t] * a.N + min(a.N - 1, (tile % tiles_per_t) * 32 + n);
+  };
+  Quarter x, y;
+  if (tile0 < tile1) {
+    next_row = row_of(tile0);
+    request(next_row, 0, x);
+    request(next_row, 1, y);
+  }
   for (int64_t tile = tile0; tile < tile1; ++tile) {
     const int32_t t = a.used_t[tile / tiles_per_t];
     if (t != cur_t) {
       if (cur_t >= 0) flush_dpos(slot, cur_t, lane, dpos);
       cur_t = t;
     }
-    const int64_t v = (tile % tiles_per_t) * 32 + n;
-    const bool valid = v < a.N;
-    const int64_t row = (int64_t)t * a.N + (valid ? v : a.N - 1);
-    const bool ok = valid && a.owner[row] >= 0;
+    row = next_row;
+    const bool ok = (tile % tiles_per_t) * 32 + n < a.N && a.owner[row] >= 0;
+    const uint32_t keep = ok ? 0xffffffffu : 0u;     // a row no chunk covers was never written
     floatx16 dP[4] = {};
-#pragma unroll 2
-    for (int ks = 0; ks < 8; ++ks) {
-      uint4 uq = make_uint4(0, 0, 0, 0), uk = uq, uv = uq;
-      if (ok) {
-        uq = *reinterpret_cast<const uint4*>(a.dQ + row * kS + ks * 16 + 8 * hh);
-        uk = *reinterpret_cast<const uint4*>(a.dK + row * kS + ks * 16 + 8 * hh);
-        uv = *reinterpret_cast<const uint4*>(a.dV + row * kS + ks * 16 + 8 * hh);
-      }
+    auto add = [&](const Quarter& g, int part) {
 #pragma unroll
-      for (int ib = 0; ib < 4; ++ib) {
-        const int fi = (ib * 8 + ks) * 64 + lane;
-        dP[ib] = mfma(as_frag(wlds[fi]), as_frag(uq), dP[ib]);
-        dP[ib] = mfma(as_frag(wlds[kFragsPerW + fi]), as_frag(uk), dP[ib]);
-        dP[ib] = mfma(as_frag(wlds[2 * kFragsPerW + fi]), as_frag(uv), dP[ib]);
-      }
-    }
+      for (int i = 0; i < 2; ++i) {
+        const bf16x8 uq = and_mask(as_frag(g.q[i]), keep), uk = and_mask(as_frag(g.k[i]), keep), uv = and_mask(as_frag(g.v[i]), keep);
 #pragma unroll
-    for (int ib = 0; ib < 4; ++ib) {
-      if (ok) {
-#pragma unroll
-        for (int g = 0; g < 4; ++g) {
-          const int64_t o = row * kS + ib * 32 + 8 * g + 4 * hh;
-          const float4 u = *reinterpret_cast<const float4*>(a.U + o);
-          *reinterpret_cast<uint2*>(a.dU + o) = pack4(dP[ib][4 * g] * delu(u.x), dP[ib][4 * g + 1] * delu(u.y),
-                                                     dP[ib][4 * g + 2] * delu(u.z), dP[ib][4 * g + 3] * delu(u.w));
+        for (int ib = 0; ib < 4; ++ib) {
+          const int fi = (ib * 8 + 2 * part + i) * 64 + lane;
+          dP[ib] = mfma(as_frag(wlds[fi]), uq, dP[ib]);
+          dP[ib] = mfma(as_frag(wlds[kFragsPerW + fi]), uk, dP[ib]);
+          dP[ib] = mfma(as_frag(wlds[2 * kFragsPerW + fi]), uv, dP[ib]);
         }
       }
+    };
+    add(x, 0);
+    request(row, 2, x);
+    add(y, 1);
+    request(row, 3, y);
+    const bool more = tile + 1 < tile1;
+    if (more) next_row = row_of(tile + 1);
+    add(x, 2);
+    if (more) request(next_row, 0, x);
+    add(y, 3);
+    if (more) request(next_row, 1, y);
+    float c[kHeads];
+#pragma unroll
+    for (int ib = 0; ib < 4; ++ib) {
       dpos[ib] += dP[ib];
+#pragma unroll
+      for (int hd = 0; hd < 2; ++hd) {
+        const int64_t o = row * kS + ib * 32 + 16 * hd;
+        const float4 u0 = *reinterpret_cast<const float4*>(a.U + o + 4 * hh);
+        const float4 u1 = *reinterpret_cast<const float4*>(a.U + o + 8 + 4 * hh);
+        const floatx16& p = dP[ib];
+        const uint2 d0 = pack4(p[8 * hd] * delu(u0.x), p[8 * hd + 1] * delu(u0.y), p[8 * hd + 2] * delu(u0.z), p[8 * hd + 3] * delu(u0.w));
+        const uint2 d1 = pack4(p[8 * hd + 4] * delu(u1.x), p[8 * hd + 5] * delu(u1.y), p[8 * hd + 6] * delu(u1.z), p[8 * hd + 7] * delu(u1.w));
+        const uint4 out = head_order(make_uint4(d0.x, d0.y, d1.x, d1.y));
+        if (ok) *reinterpret_cast<uint4*>(a.dU + o + 8 * hh) = out;
+        // of the values as stored: what the passes over the non-zeros read
+        const float part = bf_lo(d0.x) * u0.x + bf_hi(d0.x) * u0.y + bf_lo(d0.y) * u0.z + bf_hi(d0.y) * u0.w +
+                           bf_lo(d1.x) * u1.x + bf_hi(d1.x) * u1.y + bf_lo(d1.y) * u1.z + bf_hi(d1.y) * u1.w;
+        c[2 * ib + hd] = part + xor32(part, hh);
+      }
     }
+    if (ok)
+      *reinterpret_cast<float4*>(a.c + row * 16 + 4 * hh) =
+          hh ? make_float4(c[4], c[5], c[6], c[7]) : make_float4(c[0], c[1], c[2], c[3]);
   }
   if (cur_t >= 0) flush_dpos(slot, cur_t, lane, dpos);
 }
@@ -559,12 +587,16 @@ __global__ __launch_bounds__(1024) void k_reduce_slots(const float* partial, int
 }
 
 // ---------------------------------------------------------------------------------------------
-// Graph attention backward, row pass: for every covered row i, c_i^h = du_i^h . u_i^h and
+// Graph attention backward, row pass: for every covered row i, with c_i^h = du_i^h . u_i^h,
 // d s_dst_i^h = sum_j dpre_ij^h,  dpre = alpha (du_i^h . z_j^h - c_i^h) LeakyReLU'(e_ij^h).
 // Lane = (neighbour slot lane/8, head lane%8): eight neighbours at a time, each lane reads its
-// head's 32-byte slice of the neighbour's z row and does the 16-dim dot product on its own.
-// Rows longer than long_nnz are cut into parts (one wavefront each) whose sums a merge kernel
-// adds in part order.
+// head's 32-byte slice of the neighbour's z row and does the 16-dim dot product on its own.  Two neighbours per slot
+// are a batch, and the next batch is requested before the current one is used; the next row's column ids and own
+// values before the current row.
+// Bound by the gathers' bytes: 2.7 ms for 16 snapshots of 250 000 vertices and 3 million non-zeros (one batch at a
+// time, c computed here from rows of U, split rows in a launch of their own: 2.74 and 0.44 ms).
+// Rows longer than long_nnz are cut into parts (one wavefront each, in the same launch and begun first) whose sums a
+// merge kernel adds in part order.
 constexpr int kLongRec = 144;    // floats per scratch record of a part of a split row (forward, row pass)
 
 struct GatBwdRowsArgs {
@@ -576,53 +608,85 @@ struct GatBwdRowsArgs {
   float* long_partial;
   const uint16_t* zX; const uint16_t* zC;
   const float* sX; const float* sC;
-  const float* U; const uint16_t* dU;
+  const uint16_t* dU;
+  const float* c;    // [T*N][16], the first 8
   const float* lse;
   float4* st2;    // [T*N][8]: per head (s_dst, lse, c, d s_dst): what the reverse-edge pass needs of a row
 };
 
-__device__ __forceinline__ void load16(const uint16_t* p, float* x) {
-  unpack8(reinterpret_cast<const uint4*>(p)[0], x);
-  unpack8(reinterpret_cast<const uint4*>(p)[1], x + 8);
+struct RowOwn { uint4 du[2]; float c, sd, lse; };    // what a lane keeps about its own row and head
+
+__device__ __forceinline__ RowOwn row_own(const GatBwdRowsArgs& a, int64_t row, int h) {
+  RowOwn o;
+  const uint4* p = reinterpret_cast<const uint4*>(a.dU + row * kS + 16 * h);
+  o.du[0] = p[0];
+  o.du[1] = p[1];
+  o.c = a.c[row * 16 + h];
+  o.sd = a.sX[row * 16 + 8 + h];
+  o.lse = a.lse[row * 8 + h];
+  return o;
 }
 
-// du_i^h (16 values) and c_i^h for the lane's head
-__device__ __forceinline__ float load_du_c(const GatBwdRowsArgs& a, int64_t row, int h, float* du) {
-  load16(a.dU + row * kS + 16 * h, du);
-  float c = 0.f;
-#pragma unroll
-  for (int d4 = 0; d4 < 4; ++d4) {
-    const float4 x = *reinterpret_cast<const float4*>(a.U + row * kS + 16 * h + 4 * d4);
-    c += du[4 * d4] * x.x + du[4 * d4 + 1] * x.y + du[4 * d4 + 2] * x.z + du[4 * d4 + 3] * x.w;
-  }
-  return c;
-}
+constexpr int kRowBatch = 2;    // neighbours per slot and batch
+struct RowBatch { uint4 z[kRowBatch][2]; float s[kRowBatch]; };
 
-// this lane's share (its neighbour slot) of sum_j dpre_ij^h over the non-zeros [e0, e1) of row i
-__device__ __forceinline__ float gat_bwd_row_range(const GatBwdRowsArgs& a, const Segment& s, const int32_t* col,
-                                                   int64_t base, const float* du, float c, float sd, float lse,
-                                                   int64_t e0, int64_t e1, int lane) {
+// sum_j dpre_ij^h over n stored non-zeros of row i, from `first` (the same in every slot); ids: column id of non-zero
+// `lane` of them
+__device__ __forceinline__ float gat_bwd_row_range(const GatBwdRowsArgs& a, const Segment& s, const int32_t* first,
+                                                   int64_t base, const RowOwn& o, int n, int32_t ids, int lane) {
   const int slot = lane >> 3, h = lane & 7;
-  float dsd = 0.f;
-  for (int64_t eb = e0; eb < e1; eb += 64) {
-    const int cnt = (int)min((int64_t)64, e1 - eb);
-    const int32_t jl = lane < cnt ? col[eb + lane] : 0;
-    for (int q0 = 0; q0 < cnt; q0 += 8) {
-      const int32_t j = __shfl(jl, q0 + slot);
-      if (q0 + slot < cnt) {
-        const bool in = j >= s.v_lo && j < s.v_hi;
-        float z[16];
-        const uint16_t* zp = (in ? a.zX : a.zC) + (base + j) * kS + 16 * h;   // half precision
-        unpackh8(reinterpret_cast<const uint4*>(zp)[0], z);
-        unpackh8(reinterpret_cast<const uint4*>(zp)[1], z + 8);
-        const float ss = in ? a.sX[(base + j) * 16 + h] : a.sC[(base + j) * 8 + h];
-        const float e = sd + ss;
-        const float al = __expf(lrelu(e) - lse);
-        float da = 0.f;
+  float dsd = 0.f, du[16];
+  unpack8(o.du[0], du);
+  unpack8(o.du[1], du + 8);
+  int32_t ahead = 64 + lane < n ? first[64 + lane] : 0;
+  auto request = [&](int k, RowBatch& b) {
+    if (k > 0 && (k & 63) == 0) {
+      ids = ahead;
+      ahead = k + 64 + lane < n ? first[k + 64 + lane] : 0;
+    }
 #pragma unroll
-        for (int d = 0; d < 16; ++d) da += du[d] * z[d];
-        dsd += al * (da - c) * (e > 0.f ? 1.f : kSlope);
+    for (int u = 0; u < kRowBatch; ++u) {
+      const int i = k + 8 * u + slot;
+      const int32_t j = __shfl(ids, i & 63);
+      b.z[u][0] = make_uint4(0, 0, 0, 0);
+      b.z[u][1] = b.z[u][0];
+      b.s[u] = -INFINITY;     // no weight
+      if (i < n) {
+        const bool in = j >= s.v_lo && j < s.v_hi;
+        const uint4* zp = reinterpret_cast<const uint4*>((in ? a.zX : a.zC) + (base + j) * kS + 16 * h);
+        b.z[u][0] = zp[0];
+        b.z[u][1] = zp[1];
+        b.s[u] = *(in ? a.sX + (base + j) * 16 + h : a.sC + (base + j) * 8 + h);
       }
+    }
+  };
+  auto use = [&](const RowBatch& b) {
+#pragma unroll
+    for (int u = 0; u < kRowBatch; ++u) {
+      float z[16];
+      unpackh8(b.z[u][0], z);      // half precision
+      unpackh8(b.z[u][1], z + 8);
+      const float e = o.sd + b.s[u];
+      const float al = __expf(lrelu(e) - o.lse);
+      float da = 0.f;
+#pragma unroll
+      for (int d = 0; d < 16; ++d) da += du[d] * z[d];
+      dsd += al * (da - o.c) * (e > 0.f ? 1.f : kSlope);
+    }
+  };
+  RowBatch x, y;
+  constexpr int kStep = 8 * kRowBatch;
+  if (n > 0) {
+    request(0, x);
+    for (int k = 0;; k += 2 * kStep) {
+      const bool more = k + kStep < n;
+      if (more) request(k + kStep, y);
+      use(x);
+      if (!more) break;
+      const bool again = k + 2 * kStep < n;
+      if (again) request(k + 2 * kStep, x);
+      use(y);
+      if (!again) break;
     }
   }
   dsd += __shfl_xor(dsd, 8);
@@ -631,47 +695,58 @@ __device__ __forceinline__ float gat_bwd_row_range(const GatBwdRowsArgs& a, cons
   return dsd;
 }
 
-__global__ __launch_bounds__(256) void k_gat_bwd_rows(GatBwdRowsArgs a) {
-  const int lane = threadIdx.x & 63;
-  const int64_t item = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
+__device__ __forceinline__ void rows_short(const GatBwdRowsArgs& a, int64_t item, int lane) {
   if (item >= a.n_work) return;
   const int32_t si = a.work[3 * item], r0 = a.work[3 * item + 1], nr = a.work[3 * item + 2];
   const Segment s = a.segs[si];
-  const int64_t* rowptr = a.g.rowptr[s.t];
   const int32_t* col = a.g.colidx[s.t];
-  const int64_t base = (int64_t)s.t * a.g.N;
+  const int64_t base = (int64_t)s.t * a.g.N, i0 = s.v_lo + r0;
   const int slot = lane >> 3, h = lane & 7;
+  const int64_t rp = a.g.rowptr[s.t][i0 + min(lane, nr)];      // of the whole group (at most 32 rows)
+  const int32_t rlo = (int32_t)(rp & 0xffffffff), rhi = (int32_t)(rp >> 32);
+  auto row_ptr = [&](int r) {
+    return ((int64_t)__builtin_amdgcn_readlane(rhi, r) << 32) | (uint32_t)__builtin_amdgcn_readlane(rlo, r);
+  };
+  int64_t e0 = row_ptr(0), e1 = row_ptr(1);
+  int32_t ids = e0 + lane < e1 ? col[e0 + lane] : 0;
+  RowOwn o = row_own(a, base + i0, h);
   for (int rr = 0; rr < nr; ++rr) {
-    const int64_t i = s.v_lo + r0 + rr;
-    const int64_t e0 = rowptr[i], e1 = rowptr[i + 1];
-    if (e1 - e0 > a.long_nnz) continue;
-    float du[16];
-    const float c = load_du_c(a, base + i, h, du);
-    const float sd = a.sX[(base + i) * 16 + 8 + h], lse = a.lse[(base + i) * 8 + h];
-    const float dsd = gat_bwd_row_range(a, s, col, base, du, c, sd, lse, e0, e1, lane);
-    if (slot == 0) a.st2[(base + i) * 8 + h] = make_float4(sd, lse, c, dsd);
+    int64_t ne1 = e1;
+    int32_t nids = 0;
+    RowOwn no = o;
+    if (rr + 1 < nr) {
+      ne1 = row_ptr(rr + 2);
+      nids = e1 + lane < ne1 ? col[e1 + lane] : 0;
+      no = row_own(a, base + i0 + rr + 1, h);
+    }
+    if (e1 - e0 <= a.long_nnz) {    // split rows: rows_long
+      const float dsd = gat_bwd_row_range(a, s, col + e0, base, o, (int)(e1 - e0), ids, lane);
+      if (slot == 0) a.st2[(base + i0 + rr) * 8 + h] = make_float4(o.sd, o.lse, o.c, dsd);
+    }
+    e0 = e1; e1 = ne1; ids = nids; o = no;
   }
 }
 
-__global__ __launch_bounds__(256) void k_gat_bwd_rows_long(GatBwdRowsArgs a) {
-  const int lane = threadIdx.x & 63;
-  const int64_t item = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
+__device__ __forceinline__ void rows_long(const GatBwdRowsArgs& a, int64_t item, int lane) {
   if (item >= a.n_long) return;
   const int32_t* w = a.work_long + 4 * item;
   const Segment s = a.segs[w[0]];
   const int64_t i = s.v_lo + w[1];
   const int64_t* rowptr = a.g.rowptr[s.t];
   const int64_t base = (int64_t)s.t * a.g.N;
-  const int slot = lane >> 3, h = lane & 7;
   const int64_t e0 = rowptr[i] + (int64_t)w[2] * a.part_nnz, e1 = min(rowptr[i + 1], e0 + a.part_nnz);
-  float du[16];
-  const float c = load_du_c(a, base + i, h, du);
-  const float dsd = gat_bwd_row_range(a, s, a.g.colidx[s.t], base, du, c, a.sX[(base + i) * 16 + 8 + h],
-                                      a.lse[(base + i) * 8 + h], e0, e1, lane);
-  if (slot == 0) {
-    a.long_partial[item * kLongRec + h] = dsd;
-    a.long_partial[item * kLongRec + 8 + h] = c;
-  }
+  const int32_t* first = a.g.colidx[s.t] + e0;
+  const int n = (int)(e1 - e0), h = lane & 7;
+  const RowOwn o = row_own(a, base + i, h);
+  const float dsd = gat_bwd_row_range(a, s, first, base, o, n, lane < n ? first[lane] : 0, lane);
+  if (lane < 8) a.long_partial[item * kLongRec + h] = dsd;
+}
+
+__global__ __launch_bounds__(256) void k_gat_bwd_rows(GatBwdRowsArgs a, int64_t long_blocks) {
+  const int lane = threadIdx.x & 63;
+  const int64_t block = blockIdx.x, wave = threadIdx.x >> 6;
+  if (block < long_blocks) rows_long(a, block * 4 + wave, lane);
+  else rows_short(a, (block - long_blocks) * 4 + wave, lane);
 }
 
 __global__ void k_gat_bwd_rows_merge(GatBwdRowsArgs a) {
@@ -685,7 +760,7 @@ __global__ void k_gat_bwd_rows_merge(GatBwdRowsArgs a) {
   float dsd = 0.f;
   for (int p = 0; p < w[3]; ++p) dsd += a.long_partial[(item + p) * kLongRec + h];
   const int64_t row = (int64_t)s.t * a.g.N + s.v_lo + w[1];
-  a.st2[row * 8 + h] = make_float4(a.sX[row * 16 + 8 + h], a.lse[row * 8 + h], a.long_partial[item * kLongRec + 8 + h], dsd);
+  a.st2[row * 8 + h] = make_float4(a.sX[row * 16 + 8 + h], a.lse[row * 8 + h], a.c[row * 16 + h], dsd);
 }
 
 // Graph attention backward, reverse-edge pass: for every vertex j of every snapshot in use, the
@@ -1133,8 +1208,10 @@ constexpr int kColsBlocks = 1024;  // workgroups of the reverse-edge pass (4 slo
 
 // Gradient of the input rows: the projection is z = W x, so dx = W^T dz, i.e. dX[row] = dzX[row] W for
 // every covered row (a row no chunk covers is never an input row; it is not written).  Same
-// tiling as the projection: one wave per 32 vertices of a snapshot, dzX rows as the second operand
-// straight from memory, fragments of W^T as the first.
+// tiling as the projection: a wave per 32 vertices of a snapshot in turn, dzX rows as the second operand
+// straight from memory, fragments of W^T (both parts, 64 KB, staged in LDS once per workgroup) as the first.
+// Bound by memory: 3.2 GB in 0.72 ms for 4 000 000 rows (1.02 ms with W^T from the caches,
+// loads under a condition and 8-byte stores).
 struct GatDxArgs {
   const uint16_t* dzX; const uint16_t* dzXlo;
   const uint4* WT; const uint4* WTlo;
@@ -1142,47 +1219,49 @@ struct GatDxArgs {
   uint16_t* dX; int64_t lddx;
 };
 
-__global__ __launch_bounds__(256) void k_gat_dx(GatDxArgs a) {
+__global__ __launch_bounds__(512, 4) void k_gat_dx(GatDxArgs a) {
+  extern __shared__ uint4 wlds[];
+  for (int i = threadIdx.x; i < kFragsPerW; i += 512) {
+    wlds[i] = a.WT[i];
+    wlds[kFragsPerW + i] = a.WTlo[i];
+  }
+  __syncthreads();
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int n = lane & 31, hh = lane >> 5;
-  const int64_t tiles_per_t = (a.N + 31) / 32;
-  const int64_t tile = (int64_t)blockIdx.x * 4 + wave;
-  if (tile >= tiles_per_t * a.n_used) return;
-  const int32_t t = a.used_t[tile / tiles_per_t];
-  const int64_t v = (tile % tiles_per_t) * 32 + n;
-  const bool valid = v < a.N;
-  const int64_t row = (int64_t)t * a.N + (valid ? v : a.N - 1);
-  const bool covered = valid && a.owner[row] >= 0;
-  if (__ballot(covered) == 0ull) return;
-  // both operands as a bf16 value plus what it lost to rounding: a row's gradient is one sum of
-  // 128 terms, nothing averages the roundings out as the sums over rows of the weight gradients do
-  bf16x8 gf[8], gl[8];
-#pragma unroll
-  for (int ks = 0; ks < 8; ++ks) {
-    // rows no chunk covers hold no gradient (their dzX was never written): zeros
-    uint4 raw = make_uint4(0, 0, 0, 0), rawl = raw;
-    if (covered) {
-      raw = *reinterpret_cast<const uint4*>(a.dzX + row * kS + ks * 16 + 8 * hh);
-      rawl = *reinterpret_cast<const uint4*>(a.dzXlo + row * kS + ks * 16 + 8 * hh);
-    }
-    gf[ks] = as_frag(raw);
-    gl[ks] = as_frag(rawl);
-  }
-#pragma unroll
-  for (int ib = 0; ib < 4; ++ib) {
-    floatx16 acc = {};
+  const int64_t tiles_per_t = (a.N + 31) / 32, n_tiles = tiles_per_t * a.n_used;
+  for (int64_t tile = (int64_t)blockIdx.x * 8 + wave; tile < n_tiles; tile += (int64_t)gridDim.x * 8) {
+    const int32_t t = a.used_t[tile / tiles_per_t];
+    const int64_t v = (tile % tiles_per_t) * 32 + n;
+    const bool valid = v < a.N;
+    const int64_t row = (int64_t)t * a.N + (valid ? v : a.N - 1);
+    const bool covered = valid && a.owner[row] >= 0;
+    if (__ballot(covered) == 0ull) continue;
+    const uint32_t keep = covered ? 0xffffffffu : 0u;
+    // both operands as a bf16 value plus what it lost to rounding: a row's gradient is one sum of
+    // 128 terms, nothing averages the roundings out as the sums over rows of the weight gradients do
+    bf16x8 gf[8], gl[8];
 #pragma unroll
     for (int ks = 0; ks < 8; ++ks) {
-      const bf16x8 wh = as_frag(a.WT[(ib * 8 + ks) * 64 + lane]), wl = as_frag(a.WTlo[(ib * 8 + ks) * 64 + lane]);
-      acc = mfma(wl, gf[ks], acc);
-      acc = mfma(wh, gl[ks], acc);
-      acc = mfma(wh, gf[ks], acc);
+      // rows no chunk covers hold no gradient (their dzX was never written): zeros.  Loaded all the same: loads under
+      // a condition are each waited for
+      gf[ks] = and_mask(as_frag(*reinterpret_cast<const uint4*>(a.dzX + row * kS + ks * 16 + 8 * hh)), keep);
+      gl[ks] = and_mask(as_frag(*reinterpret_cast<const uint4*>(a.dzXlo + row * kS + ks * 16 + 8 * hh)), keep);
     }
-    if (covered) {
+#pragma unroll 1
+    for (int ib = 0; ib < 4; ++ib) {
+      floatx16 acc = {};
 #pragma unroll
-      for (int g = 0; g < 4; ++g)
-        *reinterpret_cast<uint2*>(a.dX + row * a.lddx + ib * 32 + 8 * g + 4 * hh) =
-            pack4(acc[4 * g], acc[4 * g + 1], acc[4 * g + 2], acc[4 * g + 3]);
+      for (int ks = 0; ks < 8; ++ks) {
+        const bf16x8 wh = as_frag(wlds[(ib * 8 + ks) * 64 + lane]), wl = as_frag(wlds[kFragsPerW + (ib * 8 + ks) * 64 + lane]);
+        acc = mfma(wl, gf[ks], acc);
+        acc = mfma(wh, gl[ks], acc);
+        acc = mfma(wh, gf[ks], acc);
+      }
+#pragma unroll
+      for (int hd = 0; hd < 2; ++hd) {
+        const uint4 o = head_order(__builtin_bit_cast(uint4, pack8v(acc, 8 * hd)));
+        if (covered) *reinterpret_cast<uint4*>(a.dX + row * a.lddx + ib * 32 + 16 * hd + 8 * hh) = o;
+      }
     }
   }
 }
@@ -1231,7 +1310,7 @@ void dysat_backward(const DysatWs& ws, const void* Y, int64_t ldy, const void* d
       attr_set = true;
     }
   }
-  const int grid_a = (int)std::min<int64_t>(256, (ws.n_tiles + 3) / 4);
+  const int grid_a = (int)std::min<int64_t>(kTbwdWaves / 8, (ws.n_tiles + 7) / 8);
   const int grid_b = (int)std::min<int64_t>(kTbwdWaves / 8, (tiles32 + 7) / 8);
   const int n_tw = grid_b * 8;
   hipLaunchKernelGGL(k_fill_f32, blocks_for((int64_t)n_tw * ws.T * kS, 256), 256, 0, st, dpos_slots, 0.f,
@@ -1247,15 +1326,15 @@ void dysat_backward(const DysatWs& ws, const void* Y, int64_t ldy, const void* d
   ta.scale = 2.0f / (float)count;
   ta.dQ = ws.dQ; ta.dK = ws.dK; ta.dV = ws.dV;
   ta.loss_partial = ws.loss_partial;
-  if (ws.wide) hipLaunchKernelGGL(k_temporal_bwd<true>, grid_a, 256, lds, st, ta);
-  else hipLaunchKernelGGL(k_temporal_bwd<false>, grid_a, 256, lds, st, ta);
+  if (ws.wide) hipLaunchKernelGGL(k_temporal_bwd<true>, grid_a, 512, lds, st, ta);
+  else hipLaunchKernelGGL(k_temporal_bwd<false>, grid_a, 512, lds, st, ta);
   if (target && loss_out)
-    hipLaunchKernelGGL(k_reduce_slots, 1, 1024, 0, st, ws.loss_partial, (int64_t)grid_a * 4, (int64_t)1, (int64_t)1,
+    hipLaunchKernelGGL(k_reduce_slots, 1, 1024, 0, st, ws.loss_partial, (int64_t)grid_a * 8, (int64_t)1, (int64_t)1,
                        1.0f / (float)count, loss_out);
   TemporalBwd2Args tb{};
   tb.used_t = ws.used_t; tb.n_used = ws.n_used; tb.N = ws.N; tb.T = ws.T; tb.owner = ws.owner; tb.U = ws.U;
   tb.WqT = ws.WqT; tb.WkT = ws.WkT; tb.WvT = ws.WvT; tb.dQ = ws.dQ; tb.dK = ws.dK; tb.dV = ws.dV;
-  tb.dU = ws.dU; tb.dpos_partial = dpos_slots;
+  tb.dU = ws.dU; tb.c = ws.dss; tb.dpos_partial = dpos_slots;
   hipLaunchKernelGGL(k_temporal_bwd2, grid_b, 512, lds, st, tb);
   hipLaunchKernelGGL(k_reduce_slots, blocks_for((int64_t)ws.T * kS, 64), 1024, 0, st, dpos_slots, (int64_t)n_tw,
                      (int64_t)ws.T * kS, (int64_t)ws.T * kS, 1.f, ws.G[DY_POS]);
@@ -1278,15 +1357,13 @@ void dysat_backward(const DysatWs& ws, const void* Y, int64_t ldy, const void* d
   // (3) graph attention, row pass
   GatBwdRowsArgs ra{};
   ra.g = ws.g; ra.segs = ws.segs; ra.work = ws.work_short; ra.n_work = ws.n_short;
-  ra.zX = ws.zX; ra.zC = ws.zC; ra.sX = ws.sX; ra.sC = ws.sC; ra.U = ws.U; ra.dU = ws.dU; ra.lse = ws.lse;
+  ra.zX = ws.zX; ra.zC = ws.zC; ra.sX = ws.sX; ra.sC = ws.sC; ra.dU = ws.dU; ra.c = ws.dss; ra.lse = ws.lse;
   ra.st2 = reinterpret_cast<float4*>(ws.st2);
   ra.work_long = ws.work_long; ra.n_long = ws.n_long; ra.long_nnz = ws.long_nnz; ra.part_nnz = ws.part_nnz;
   ra.long_partial = ws.long_partial;
-  hipLaunchKernelGGL(k_gat_bwd_rows, blocks_for(ws.n_short, 4), 256, 0, st, ra);
-  if (ws.n_long > 0) {
-    hipLaunchKernelGGL(k_gat_bwd_rows_long, blocks_for(ws.n_long, 4), 256, 0, st, ra);
-    hipLaunchKernelGGL(k_gat_bwd_rows_merge, blocks_for(ws.n_long * 8, 256), 256, 0, st, ra);
-  }
+  const int64_t long_blocks = (ws.n_long + 3) / 4;
+  hipLaunchKernelGGL(k_gat_bwd_rows, (unsigned)(long_blocks + (ws.n_short + 3) / 4), 256, 0, st, ra, long_blocks);
+  if (ws.n_long > 0) hipLaunchKernelGGL(k_gat_bwd_rows_merge, blocks_for(ws.n_long * 8, 256), 256, 0, st, ra);
   if (ev) (void)hipEventRecord(ev[2], st);
   // (4) reverse-edge pass, then the gradients of the attention vectors
   const int64_t items = (ws.N + 15) / 16 * ws.n_used;
@@ -1335,7 +1412,7 @@ void dysat_backward(const DysatWs& ws, const void* Y, int64_t ldy, const void* d
     GatDxArgs xa{};
     xa.dzX = ws.dzX; xa.dzXlo = ws.dzXlo; xa.WT = ws.WT; xa.WTlo = ws.WTlo; xa.owner = ws.owner; xa.used_t = ws.used_t; xa.n_used = ws.n_used; xa.N = ws.N;
     xa.dX = static_cast<uint16_t*>(dX); xa.lddx = lddx;
-    hipLaunchKernelGGL(k_gat_dx, blocks_for((ws.N + 31) / 32 * ws.n_used, 4), 256, 0, st, xa);
+    hipLaunchKernelGGL(k_gat_dx, (unsigned)std::min<int64_t>(512, (tiles32 + 7) / 8), 512, sizeof(uint4) * 2 * kFragsPerW, st, xa);
   }
   if (ev) (void)hipEventRecord(ev[3], st);
 }
