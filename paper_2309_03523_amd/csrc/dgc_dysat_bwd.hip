@@ -387,11 +387,15 @@ __global__ __launch_bounds__(512) void k_temporal_bwd2(TemporalBwd2Args a) {
 // ---------------------------------------------------------------------------------------------
 // Weight gradients  dW_G[out][in] = sum over rows of G[row][out] * A[row][in]  for NG tensors G
 // sharing one A (A = the rows of a bf16 tensor, or P = ELU(U) + pos recomputed from U).  Rows are
-// the vertices of the snapshots in use, 32 per tile.  A workgroup of 4 waves walks a contiguous
-// range of tiles; wave w owns output rows [32w, 32w+32) of every dW_G.  Both operands need the
+// the vertices of the snapshots in use, 32 per tile.  A workgroup walks a contiguous
+// range of tiles.  Both operands need the
 // row index as contraction index, i.e. column layout: obtained from natural row fragments with
-// the selection products described above.  Eight waves per workgroup: wave w owns output rows
-// [32 (w%4), +32) and input columns [64 (w/4), +64) of every dW_G.
+// the selection products described above.  Each of the eight waves does that for a part of the tile, 32 columns of A
+// (waves 0..3) or of every G (4..7), and leaves the fragments in one of two LDS buffers for all; then wave w adds
+// output rows [32 (w%4), +32) x input columns [64 (w/4), +64) of every dW_G.  The next tile is on its way from memory.
+// Bound by memory: for 4 000 000 rows dW_q, dW_k, dW_v 5.1 GB in 1.31 ms, and dW from the input and the cache rows (one
+// launch, blockIdx.y) 4.1 GB in 0.88 ms; with every wave converting what it multiplies, 2.06 and 2 x 0.80 ms.  (Two tiles
+// ahead: the registers spill.)
 struct DwBf16Args {
   const int32_t* used_t; int32_t n_used; int64_t N;
   const int32_t* owner; int32_t covered_only;
@@ -402,61 +406,20 @@ struct DwBf16Args {
   int32_t n_groups;
 };
 
-// Raw operand rows of one 32-row tile as they come from memory, requested ahead of their use
-// (loads return in order, so waiting for older registers does not wait for younger requests):
-//  - bf16 x bf16 products: both sides of the next tile are requested before the current tile is
-//    multiplied;
-//  - the ELU(U) + pos variant with three accumulator sets has no room for a second tile: the
-//    gradient rows of the current tile are requested before U is converted, and U of the next tile
-//    as soon as the conversion has used up the current one; the position rows of the snapshots a
-//    workgroup meets are staged in LDS once.
-template <bool AU>
-struct DwRawA {
-  float4 u[AU ? 8 : 1];   // AU: fp32 rows of U, [jb][c][half]
-  uint4 a[AU ? 1 : 4];    // otherwise: bf16 rows of A, [jb][c]
-  int32_t k;              // index of the tile's snapshot among the snapshots in use
-  bool ok;
-};
-
 struct DwRow {
   int64_t row;
   int32_t k;
   bool ok;
 };
 
-__device__ __forceinline__ DwRow dw_row(const DwBf16Args& a, int64_t tile, int64_t tiles_per_t, int n) {
+__device__ __forceinline__ DwRow dw_row(const DwBf16Args& a, bool covered_only, int64_t tile, int64_t tiles_per_t, int n) {
   DwRow r;
   r.k = (int32_t)(tile / tiles_per_t);
   const int64_t v = (tile % tiles_per_t) * 32 + n;
   const bool valid = v < a.N;
   r.row = (int64_t)a.used_t[r.k] * a.N + (valid ? v : a.N - 1);    // always a row of the tensors
-  r.ok = valid && (!a.covered_only || a.owner[r.row] >= 0);       // rows that do not count are zeroed when used
+  r.ok = valid && (!covered_only || a.owner[r.row] >= 0);       // rows that do not count are zeroed when used
   return r;
-}
-
-template <bool AU>
-__device__ __forceinline__ void dw_load_a(const DwBf16Args& a, const DwRow& rw, int hh, int ih, DwRawA<AU>& r) {
-  r.ok = rw.ok;
-  r.k = rw.k;
-#pragma unroll
-  for (int q = 0; q < 4; ++q) {
-    const int off = (2 * (2 * ih + (q >> 1)) + (q & 1)) * 16 + 8 * hh;
-    if (AU) {
-      r.u[2 * q] = *reinterpret_cast<const float4*>(a.Uf + rw.row * kS + off);
-      r.u[2 * q + 1] = *reinterpret_cast<const float4*>(a.Uf + rw.row * kS + off + 4);
-    } else {
-      r.a[q] = *reinterpret_cast<const uint4*>(a.A + rw.row * a.lda + off);
-    }
-  }
-}
-
-template <int NG>
-__device__ __forceinline__ void dw_load_g(const DwBf16Args& a, const DwRow& rw, int hh, int ob, uint4 (&g)[NG][2]) {
-#pragma unroll
-  for (int gi = 0; gi < NG; ++gi)
-#pragma unroll
-    for (int c = 0; c < 2; ++c)
-      g[gi][c] = *reinterpret_cast<const uint4*>(a.G[gi] + rw.row * kS + (2 * ob + c) * 16 + 8 * hh);
 }
 
 __device__ __forceinline__ uint4 keep_if(bool ok, uint4 u) {
@@ -464,15 +427,27 @@ __device__ __forceinline__ uint4 keep_if(bool ok, uint4 u) {
 }
 
 template <int NG, bool AU>
-__global__ __launch_bounds__(512) void k_dw_bf16(DwBf16Args a) {
-  const int lane = threadIdx.x & 63, ob = (threadIdx.x >> 6) & 3, ih = threadIdx.x >> 8;
+constexpr int dw_frags() { return 8 * (AU ? 2 : 1) + 8 * NG; }     // of a tile: A (hi, and lo if AU), then the G
+
+// second: the arguments of the workgroups of blockIdx.y = 1
+template <int NG, bool AU>
+__global__ __launch_bounds__(512) void k_dw_bf16(DwBf16Args a, DwBf16Args second) {
+  constexpr int NA = AU ? 2 : 1, kFrags = dw_frags<NG, AU>();
+  const bool other = !AU && blockIdx.y;
+  const uint16_t* const A = other ? second.A : a.A;
+  const uint16_t* const G0 = other ? second.G[0] : a.G[0];
+  const int64_t lda = other ? second.lda : a.lda;
+  const bool covered_only = other ? second.covered_only : a.covered_only;
+  float* const partial = other ? second.partial : a.partial;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), ob = wave & 3, ih = wave >> 2;
   const int n = lane & 31, hh = lane >> 5;
   const int64_t tiles_per_t = (a.N + 31) / 32, n_tiles = tiles_per_t * a.n_used;
   const int64_t per = (n_tiles + a.n_groups - 1) / a.n_groups;
   const int64_t tile0 = (int64_t)blockIdx.x * per, tile1 = min(n_tiles, tile0 + per);
   const bf16x8 sel0 = sel_frag(0, lane), sel1 = sel_frag(1, lane);
   floatx16 acc[NG][2] = {};
-  extern __shared__ float pos_lds[];   // AU: position rows of the snapshots of tiles [tile0, tile1)
+  extern __shared__ uint4 dw_lds[];    // [2][kFrags][64], then (AU) the position rows of the snapshots of the range
+  float* pos_lds = reinterpret_cast<float*>(dw_lds + 2 * kFrags * 64);
   const int32_t k0 = (int32_t)(tile0 / tiles_per_t);
   if (AU) {
     if (tile0 < tile1) {
@@ -481,82 +456,104 @@ __global__ __launch_bounds__(512) void k_dw_bf16(DwBf16Args a) {
     }
     __syncthreads();
   }
-  DwRawA<AU> ra;
-  uint4 rg[NG][2];
-  if (tile0 < tile1) {
-    const DwRow rw = dw_row(a, tile0, tiles_per_t, n);
-    dw_load_a<AU>(a, rw, hh, ih, ra);
-    if (!AU) dw_load_g<NG>(a, rw, hh, ob, rg);
-  }
-  for (int64_t tile = tile0; tile < tile1; ++tile) {
-    const bool ok = ra.ok;
-    const bool more = tile + 1 < tile1;
-    DwRow rn{};
-    if (more) rn = dw_row(a, tile + 1, tiles_per_t, n);
-    DwRawA<AU> na;
-    uint4 ng[NG][2];
-    if (AU) {
-      dw_load_g<NG>(a, dw_row(a, tile, tiles_per_t, n), hh, ob, rg);
-    } else if (more) {
-      dw_load_a<AU>(a, rn, hh, ih, na);
-      dw_load_g<NG>(a, rn, hh, ob, ng);
-    }
-    bf16x8 at[2][2], al[2][2];
-#pragma unroll
-    for (int jb = 0; jb < 2; ++jb) {
-      floatx16 tr = {}, trl = {};
-#pragma unroll
-      for (int c = 0; c < 2; ++c) {
-        if (AU) {
-          const float4 u0 = ra.u[(jb * 2 + c) * 2], u1 = ra.u[(jb * 2 + c) * 2 + 1];
-          const float* pp = pos_lds + (ra.k - k0) * kS + (2 * (2 * ih + jb) + c) * 16 + 8 * hh;
-          const float4 p0 = *reinterpret_cast<const float4*>(pp), p1 = *reinterpret_cast<const float4*>(pp + 4);
-          float x[8];
-          x[0] = elu(u0.x) + p0.x; x[1] = elu(u0.y) + p0.y; x[2] = elu(u0.z) + p0.z; x[3] = elu(u0.w) + p0.w;
-          x[4] = elu(u1.x) + p1.x; x[5] = elu(u1.y) + p1.y; x[6] = elu(u1.z) + p1.z; x[7] = elu(u1.w) + p1.w;
-#pragma unroll
-          for (int i = 0; i < 8; ++i) x[i] = ok ? x[i] : 0.f;
-          bf16x8 xh, xl;
-          split8(x, xh, xl);
-          tr = mfma(xh, c ? sel1 : sel0, tr);
-          trl = mfma(xl, c ? sel1 : sel0, trl);
-        } else {
-          tr = mfma(as_frag(keep_if(ok, ra.a[jb * 2 + c])), c ? sel1 : sel0, tr);
-        }
+  struct Raw { uint4 r0, r1, r2, r3, r4, r5; int32_t k; bool ok; };     // the lane's pieces of a tile as they come from memory
+  auto request = [&](int64_t tile, Raw& q) {
+    const DwRow rw = dw_row(a, covered_only, tile, tiles_per_t, n);
+    q.k = rw.k;
+    q.ok = rw.ok;
+    const int off = 32 * ob + 8 * hh;
+    auto at = [&](const uint16_t* p, int64_t ld, int c) { return *reinterpret_cast<const uint4*>(p + rw.row * ld + off + 16 * c); };
+    if (wave >= 4) {
+      q.r0 = at(G0, kS, 0);
+      q.r1 = at(G0, kS, 1);
+      if constexpr (NG == 3) {
+        q.r2 = at(a.G[1], kS, 0);
+        q.r3 = at(a.G[1], kS, 1);
+        q.r4 = at(a.G[2], kS, 0);
+        q.r5 = at(a.G[2], kS, 1);
       }
-      at[jb][0] = pack8v(tr, 0);
-      at[jb][1] = pack8v(tr, 8);
-      if (AU) {
-        al[jb][0] = pack8v(trl, 0);
-        al[jb][1] = pack8v(trl, 8);
-      }
+    } else if constexpr (AU) {
+      const uint4* u = reinterpret_cast<const uint4*>(a.Uf + rw.row * kS + off);
+      q.r0 = u[0];
+      q.r1 = u[1];
+      q.r2 = u[4];
+      q.r3 = u[5];
+    } else {
+      q.r0 = at(A, lda, 0);
+      q.r1 = at(A, lda, 1);
     }
-    if (AU && more) dw_load_a<AU>(a, rn, hh, ih, ra);   // U of this tile is used up: request the next tile's
+  };
+  auto columns = [&](bf16x8 x0, bf16x8 x1, uint4* out) {     // the fragments of both halves of the rows
+    floatx16 tr = {};
+    tr = mfma(x0, sel0, tr);
+    tr = mfma(x1, sel1, tr);
+    out[0] = __builtin_bit_cast(uint4, pack8v(tr, 0));
+    out[64] = __builtin_bit_cast(uint4, pack8v(tr, 8));
+  };
+  auto convert = [&](const Raw& q, uint4* buf) {
+    buf += lane;
+    auto kept = [&](uint4 u) { return as_frag(keep_if(q.ok, u)); };
+    if (wave >= 4) {
+      uint4* g = buf + (8 * NA + 2 * ob) * 64;
+      columns(kept(q.r0), kept(q.r1), g);
+      if constexpr (NG == 3) {
+        columns(kept(q.r2), kept(q.r3), g + 8 * 64);
+        columns(kept(q.r4), kept(q.r5), g + 16 * 64);
+      }
+    } else if constexpr (AU) {
+      const float* pp = pos_lds + (q.k - k0) * kS + 32 * ob + 8 * hh;
+      auto part = [&](uint4 ua, uint4 ub, const float* pp, bf16x8& xh, bf16x8& xl) {
+        const float4 u0 = __builtin_bit_cast(float4, ua), u1 = __builtin_bit_cast(float4, ub);
+        const float4 p0 = *reinterpret_cast<const float4*>(pp), p1 = *reinterpret_cast<const float4*>(pp + 4);
+        float x[8];
+        x[0] = elu(u0.x) + p0.x; x[1] = elu(u0.y) + p0.y; x[2] = elu(u0.z) + p0.z; x[3] = elu(u0.w) + p0.w;
+        x[4] = elu(u1.x) + p1.x; x[5] = elu(u1.y) + p1.y; x[6] = elu(u1.z) + p1.z; x[7] = elu(u1.w) + p1.w;
+        split8(x, xh, xl);
+        xh = kept(__builtin_bit_cast(uint4, xh));
+        xl = kept(__builtin_bit_cast(uint4, xl));
+      };
+      bf16x8 xh0, xl0, xh1, xl1;
+      part(q.r0, q.r1, pp, xh0, xl0);
+      part(q.r2, q.r3, pp + 16, xh1, xl1);
+      columns(xh0, xh1, buf + 2 * ob * 64);
+      columns(xl0, xl1, buf + (8 + 2 * ob) * 64);
+    } else {
+      columns(kept(q.r0), kept(q.r1), buf + 2 * ob * 64);
+    }
+  };
+  auto multiply = [&](const uint4* buf) {
+    buf += lane;
+    bf16x8 at[NA][2][2];
+#pragma unroll
+    for (int p = 0; p < NA; ++p)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) at[p][i >> 1][i & 1] = as_frag(buf[(8 * p + 4 * ih + i) * 64]);
 #pragma unroll
     for (int gi = 0; gi < NG; ++gi) {
-      floatx16 tr = {};
+      const bf16x8 g0 = as_frag(buf[(8 * NA + 8 * gi + 2 * ob) * 64]), g1 = as_frag(buf[(8 * NA + 8 * gi + 2 * ob + 1) * 64]);
 #pragma unroll
-      for (int c = 0; c < 2; ++c) tr = mfma(as_frag(keep_if(ok, rg[gi][c])), c ? sel1 : sel0, tr);
-      const bf16x8 g0 = pack8v(tr, 0), g1 = pack8v(tr, 8);
+      for (int ib = 0; ib < 2; ++ib)
 #pragma unroll
-      for (int ib = 0; ib < 2; ++ib) {
-        acc[gi][ib] = mfma(g0, at[ib][0], acc[gi][ib]);
-        acc[gi][ib] = mfma(g1, at[ib][1], acc[gi][ib]);
-        if (AU) {
-          acc[gi][ib] = mfma(g0, al[ib][0], acc[gi][ib]);
-          acc[gi][ib] = mfma(g1, al[ib][1], acc[gi][ib]);
+        for (int p = 0; p < NA; ++p) {
+          acc[gi][ib] = mfma(g0, at[p][ib][0], acc[gi][ib]);
+          acc[gi][ib] = mfma(g1, at[p][ib][1], acc[gi][ib]);
         }
-      }
     }
-    if (!AU && more) {
-      ra = na;
-#pragma unroll
-      for (int gi = 0; gi < NG; ++gi) { rg[gi][0] = ng[gi][0]; rg[gi][1] = ng[gi][1]; }
-    }
+  };
+  Raw q;
+  if (tile0 < tile1) request(tile0, q);
+  uint4* buf = dw_lds;
+  // a buffer is written again only after the barrier of the tile between, which every wave reaches after its products
+  for (int64_t tile = tile0; tile < tile1; ++tile) {
+    convert(q, buf);
+    if (tile + 1 < tile1) request(tile + 1, q);
+    __syncthreads();
+    multiply(buf);
+    buf = buf == dw_lds ? dw_lds + kFrags * 64 : dw_lds;
   }
 #pragma unroll
   for (int gi = 0; gi < NG; ++gi) {
-    float* out = a.partial + ((int64_t)blockIdx.x * NG + gi) * kS * kS;
+    float* out = partial + ((int64_t)blockIdx.x * NG + gi) * kS * kS;
 #pragma unroll
     for (int ib = 0; ib < 2; ++ib)
 #pragma unroll
@@ -1013,12 +1010,45 @@ __global__ __launch_bounds__(256, kSlotWaves) void k_gat_bwd_cols_slot(GatBwdCol
   if (n > 0) gat_bwd_col_finish<LO, true>(a, row, o, r, v, lane);
 }
 
+__device__ __forceinline__ void cols_long_part(const GatBwdColsArgs& a, int64_t item, int lane) {
+  if (item >= a.n_cols_long) return;
+  const int32_t* w = a.cols_long + 4 * item;   // snapshot, vertex, part, parts
+  const int64_t base = (int64_t)w[0] * a.g.N, j = w[1];
+  const int sub = lane & 15;
+  const int64_t* rowptr = a.g.rowptr[w[0]];
+  const int64_t e0 = rowptr[j] + (int64_t)w[2] * a.part_nnz, e1 = min(rowptr[j + 1], e0 + a.part_nnz);
+  const ColOwn o = col_own(a, base + j, sub);
+  const int32_t* col = a.g.colidx[w[0]];
+  const uint8_t* code = a.ecode + a.ecode_off[w[0]];
+  const int32_t il = e0 + lane < e1 ? col[e0 + lane] : 0;
+  const int32_t cl = e0 + lane < e1 ? code[e0 + lane] : 0;
+  const ColAcc r = gat_bwd_col_range(a, col, code, base, o, e0, e1, il, cl, lane);
+  if ((lane >> 4) == 0) {
+    float* rec = a.long_partial + item * kColsRec;
+    float4* x = reinterpret_cast<float4*>(rec + 8 * sub);
+    x[0] = make_float4(r.ax[0], r.ax[1], r.ax[2], r.ax[3]);
+    x[1] = make_float4(r.ax[4], r.ax[5], r.ax[6], r.ax[7]);
+    float4* c = reinterpret_cast<float4*>(rec + kS + 8 * sub);
+    c[0] = make_float4(r.ac[0], r.ac[1], r.ac[2], r.ac[3]);
+    c[1] = make_float4(r.ac[4], r.ac[5], r.ac[6], r.ac[7]);
+    if ((sub & 1) == 0) {
+      rec[256 + (sub >> 1)] = r.dsx;
+      rec[264 + (sub >> 1)] = r.dsc;
+    }
+  }
+}
+
 template <bool LO>
-__global__ __launch_bounds__(256, 4) void k_gat_bwd_cols(GatBwdColsArgs a) {   // 4 waves per SIMD: 128 registers
+__global__ __launch_bounds__(256, 4) void k_gat_bwd_cols(GatBwdColsArgs a, int64_t long_blocks) {   // 4 waves per SIMD: 128 registers
   const int lane = threadIdx.x & 63;
+  const int64_t block = (int64_t)blockIdx.x - long_blocks;
+  if (block < 0) {       // parts of split rows go first
+    cols_long_part(a, (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6), lane);
+    return;
+  }
   const int64_t N = a.g.N;
   const int64_t groups_per_t = (N + 15) / 16, n_items = groups_per_t * a.n_used;
-  const int64_t item = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
+  const int64_t item = block * 4 + (threadIdx.x >> 6);
   if (item >= n_items) return;
   const int sub = lane & 15;
   const AttVec v = att_init(a, sub);
@@ -1052,36 +1082,6 @@ __global__ __launch_bounds__(256, 4) void k_gat_bwd_cols(GatBwdColsArgs a) {   /
       gat_bwd_col_finish<LO>(a, base + j0 + rr, o, r, v, lane);
     }
     e0 = ne0; e1 = ne1; il = nil; cl = ncl;
-  }
-}
-
-__global__ __launch_bounds__(256) void k_gat_bwd_cols_long(GatBwdColsArgs a) {
-  const int lane = threadIdx.x & 63;
-  const int64_t item = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
-  if (item >= a.n_cols_long) return;
-  const int32_t* w = a.cols_long + 4 * item;   // snapshot, vertex, part, parts
-  const int64_t base = (int64_t)w[0] * a.g.N, j = w[1];
-  const int sub = lane & 15;
-  const int64_t* rowptr = a.g.rowptr[w[0]];
-  const int64_t e0 = rowptr[j] + (int64_t)w[2] * a.part_nnz, e1 = min(rowptr[j + 1], e0 + a.part_nnz);
-  const ColOwn o = col_own(a, base + j, sub);
-  const int32_t* col = a.g.colidx[w[0]];
-  const uint8_t* code = a.ecode + a.ecode_off[w[0]];
-  const int32_t il = e0 + lane < e1 ? col[e0 + lane] : 0;
-  const int32_t cl = e0 + lane < e1 ? code[e0 + lane] : 0;
-  const ColAcc r = gat_bwd_col_range(a, col, code, base, o, e0, e1, il, cl, lane);
-  if ((lane >> 4) == 0) {
-    float* rec = a.long_partial + item * kColsRec;
-    float4* x = reinterpret_cast<float4*>(rec + 8 * sub);
-    x[0] = make_float4(r.ax[0], r.ax[1], r.ax[2], r.ax[3]);
-    x[1] = make_float4(r.ax[4], r.ax[5], r.ax[6], r.ax[7]);
-    float4* c = reinterpret_cast<float4*>(rec + kS + 8 * sub);
-    c[0] = make_float4(r.ac[0], r.ac[1], r.ac[2], r.ac[3]);
-    c[1] = make_float4(r.ac[4], r.ac[5], r.ac[6], r.ac[7]);
-    if ((sub & 1) == 0) {
-      rec[256 + (sub >> 1)] = r.dsx;
-      rec[264 + (sub >> 1)] = r.dsc;
-    }
   }
 }
 
@@ -1305,6 +1305,8 @@ void dysat_backward(const DysatWs& ws, const void* Y, int64_t ldy, const void* d
                                 (int)lds);
       (void)hipFuncSetAttribute(reinterpret_cast<const void*>(k_temporal_bwd<true>), hipFuncAttributeMaxDynamicSharedMemorySize,
                                 (int)lds);
+      (void)hipFuncSetAttribute(reinterpret_cast<const void*>(k_dw_bf16<3, true>), hipFuncAttributeMaxDynamicSharedMemorySize,
+                                (int)(sizeof(uint4) * 2 * 64 * dw_frags<3, true>() + 65536));   // and the position rows
       (void)hipFuncSetAttribute(reinterpret_cast<const void*>(k_temporal_bwd2),
                                 hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
       attr_set = true;
@@ -1348,7 +1350,7 @@ void dysat_backward(const DysatWs& ws, const void* Y, int64_t ldy, const void* d
     const int64_t tiles_per_t = (ws.N + 31) / 32, n_tiles = tiles_per_t * ws.n_used;
     const int64_t per = (n_tiles + groups - 1) / groups;
     const size_t pos_lds = sizeof(float) * kS * (size_t)((per + tiles_per_t - 1) / tiles_per_t + 1);
-    hipLaunchKernelGGL((k_dw_bf16<3, true>), groups, 512, pos_lds, st, da);
+    hipLaunchKernelGGL((k_dw_bf16<3, true>), groups, 512, (sizeof(uint4) * 2 * 64 * dw_frags<3, true>()) + pos_lds, st, da, da);
   }
   for (int gi = 0; gi < 3; ++gi)
     hipLaunchKernelGGL(k_reduce_slots, blocks_for(kS * kS, 64), 1024, 0, st, dw_slots + (int64_t)gi * kS * kS,
@@ -1380,10 +1382,11 @@ void dysat_backward(const DysatWs& ws, const void* Y, int64_t ldy, const void* d
   const int64_t quads = (ws.N + 3) / 4 * ws.n_used;
   if (dX) hipLaunchKernelGGL(k_gat_bwd_cols_slot<true>, blocks_for(quads, 4), 256, 0, st, ca);
   else hipLaunchKernelGGL(k_gat_bwd_cols_slot<false>, blocks_for(quads, 4), 256, 0, st, ca);
-  if (dX) hipLaunchKernelGGL(k_gat_bwd_cols<true>, blocks_for(items, 4), 256, 0, st, ca);
-  else hipLaunchKernelGGL(k_gat_bwd_cols<false>, blocks_for(items, 4), 256, 0, st, ca);
+  const int64_t cols_long_blocks = (ws.n_cols_long + 3) / 4;
+  const unsigned cols_blocks = (unsigned)(cols_long_blocks + (items + 3) / 4);
+  if (dX) hipLaunchKernelGGL(k_gat_bwd_cols<true>, cols_blocks, 256, 0, st, ca, cols_long_blocks);
+  else hipLaunchKernelGGL(k_gat_bwd_cols<false>, cols_blocks, 256, 0, st, ca, cols_long_blocks);
   if (ws.n_cols_long > 0) {
-    hipLaunchKernelGGL(k_gat_bwd_cols_long, blocks_for(ws.n_cols_long, 4), 256, 0, st, ca);
     if (dX) hipLaunchKernelGGL(k_gat_bwd_cols_merge<true>, blocks_for(ws.n_cols_long, 4), 256, 0, st, ca);
     else hipLaunchKernelGGL(k_gat_bwd_cols_merge<false>, blocks_for(ws.n_cols_long, 4), 256, 0, st, ca);
   }
@@ -1400,11 +1403,10 @@ void dysat_backward(const DysatWs& ws, const void* Y, int64_t ldy, const void* d
   DwBf16Args dx = da;
   dx.A = static_cast<const uint16_t*>(ws.X); dx.lda = ws.ldx; dx.Uf = nullptr; dx.covered_only = 1;
   dx.G[0] = ws.dzX; dx.partial = dw_slots;
-  hipLaunchKernelGGL((k_dw_bf16<1, false>), groups, 512, 0, st, dx);
   DwBf16Args dc = dx;
   dc.A = static_cast<const uint16_t*>(ws.C); dc.lda = ws.ldc; dc.covered_only = 0;
   dc.G[0] = ws.dzC; dc.partial = dw_slots + (int64_t)groups * kS * kS;
-  hipLaunchKernelGGL((k_dw_bf16<1, false>), groups, 512, 0, st, dc);
+  hipLaunchKernelGGL((k_dw_bf16<1, false>), dim3(groups, 2), 512, (sizeof(uint4) * 2 * 64 * dw_frags<1, false>()), st, dx, dc);
   hipLaunchKernelGGL(k_reduce_slots, blocks_for(kS * kS, 64), 1024, 0, st, dw_slots, (int64_t)2 * groups,
                      (int64_t)kS * kS, (int64_t)kS * kS, 1.f, ws.G[DY_W]);
   // (6) optional: the gradient of the input rows, dX = dzX W (covered rows only)
