@@ -141,13 +141,11 @@ __device__ __forceinline__ void relu(floatx16& z) {
 template <int KIND, bool SEQ, bool CAT, bool STACK, int MAXW>
 __global__ __launch_bounds__(64 * MAXW, 2) void k_dense_split(DenseArgs a) {
   constexpr bool kLstm = KIND == DGC_TIME_LSTM;
-  // The five small products of a sum go apart from the large one where registers are left for it (Z without SEQ, the
-  // gates of a second recurrent layer): the matrix unit truncates when it adds, and a small sum is truncated by less.
-  // Error against 64 bits: 32 x 100 000 vertices, width 128, GRU 3.1e-7 -> 2.5e-7; two LSTM layers 6.4e-7 -> 6.2e-7;
-  // no difference in time.
-  constexpr bool kApart = STACK && !SEQ;
+  // The five small products of Z go apart from the large one (the matrix unit truncates when it adds, and a small sum is
+  // truncated by less), the gates' do not (no registers).  Every variant adds in one order: a sequence table that says
+  // what the window says gives the same numbers.
   constexpr int NG = kLstm ? 4 : 3;
-  constexpr int DG = NG, DZ = 4;              // weight fragments held: gates, transform
+  constexpr int DG = NG, DZ = SEQ ? 3 : 4;    // weight fragments held: gates, transform
   extern __shared__ __align__(16) uint4 lds[];
   const int njb = blockDim.x >> 6, kbh = 2 * njb, H = 32 * njb;
   const int lane = threadIdx.x & 63, l32 = lane & 31, half = lane >> 5;
@@ -281,14 +279,9 @@ __global__ __launch_bounds__(64 * MAXW, 2) void k_dense_split(DenseArgs a) {
 #pragma unroll
     for (int g = 0; g < 4; ++g)
       if (kLstm || g != 2) acc[g] = load_block(gbias + g * H + col0);
-    floatx16 accs[kApart ? 4 : 1];
-    if constexpr (kApart)
-#pragma unroll
-      for (int g = 0; g < 4; ++g) accs[g] = (floatx16)(0.f);
-    auto small = [&](int g) -> floatx16& { return kApart ? accs[kApart ? g : 0] : acc[g]; };
-    product<NG, DG>([&](int g) -> floatx16& { return acc[!kLstm && g == 2 ? 3 : g]; },
-                    [&](int g) -> floatx16& { return small(!kLstm && g == 2 ? 3 : g); }, buf, wsh, offh, gsh, kbh, lane16, wg);
+    auto hidden = [&](int g) -> floatx16& { return acc[!kLstm && g == 2 ? 3 : g]; };
     auto in = [&](int g) -> floatx16& { return acc[g]; };
+    product<NG, DG>(hidden, hidden, buf, wsh, offh, gsh, kbh, lane16, wg);
     if constexpr (!STACK) {
       floatx16 z, zs = (floatx16)(0.f);
       for (int k = 0; k < nchunk; ++k) {
@@ -299,9 +292,9 @@ __global__ __launch_bounds__(64 * MAXW, 2) void k_dense_split(DenseArgs a) {
         if (k + 1 < nchunk) request_x(s, k + 1);
         __syncthreads();
         if (k == 0) z = load_block(zbias + col0);
-        product<1, DZ>([&](int) -> floatx16& { return z; }, [&](int) -> floatx16& { return SEQ ? z : zs; }, buf, wsg, offz + k * kbc * kUnitBytes, 0, n, lane16, wz);
+        product<1, DZ>([&](int) -> floatx16& { return z; }, [&](int) -> floatx16& { return zs; }, buf, wsg, offz + k * kbc * kUnitBytes, 0, n, lane16, wz);
       }
-      if constexpr (!SEQ) z += zs;
+      z += zs;
       if (a.act == DGC_ACT_RELU) relu(z);
       if constexpr (CAT) {                    // the other half of the time encoder's input first
         fetch_ahead<NG, DG>(wg, wsi, offx, gsx, kbh, lane16);
@@ -310,7 +303,7 @@ __global__ __launch_bounds__(64 * MAXW, 2) void k_dense_split(DenseArgs a) {
         turn();
         put_block(load_block(a.X2 + r2 * a.ldx2 + col0));
         __syncthreads();
-        product<NG, DG>(in, small, buf, wsi, offx, gsx, kbh, lane16, wg);
+        product<NG, DG>(in, in, buf, wsi, offx, gsx, kbh, lane16, wg);
       }
       fetch_ahead<NG, DG>(wg, wsi, offx + (kbx - kbh) * kUnitBytes, gsx, kbh, lane16);
       turn();
@@ -322,10 +315,7 @@ __global__ __launch_bounds__(64 * MAXW, 2) void k_dense_split(DenseArgs a) {
     }
     __syncthreads();
     if constexpr (!kLstm) acc[2] = load_block(gbias + 2 * H + col0);
-    product<NG, DG>(in, small, buf, wsi, offx + (kbx - kbh) * kUnitBytes, gsx, kbh, lane16, wg);
-    if constexpr (kApart)
-#pragma unroll
-      for (int g = 0; g < 4; ++g) acc[g] += accs[g];
+    product<NG, DG>(in, in, buf, wsi, offx + (kbx - kbh) * kUnitBytes, gsx, kbh, lane16, wg);
     // requests of the next step go out before this step's stores: memory operations retire in order
     if (mapped) {
       yrow = yrow_next;
