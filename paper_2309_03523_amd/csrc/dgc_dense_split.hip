@@ -438,8 +438,6 @@ __global__ __launch_bounds__(64 * MAXW, 2) void k_rows_split(DenseArgs a, int kb
 
 // W [n_out][n_in] (strides so, si) -> three bf16 parts per fragment: packed[((jb*nkb + kb)*3 + part)*64 + lane] holds of
 // row jb*32 + lane%32 the columns 16*kb + 8*p + 4*(lane/32) + e (p = 0, 1; e = 0..3), zero beyond n_in.
-// The middle and low parts of a weight that is not zero keep its sign and are never zero (2^-126 stands in),
-// so that an infinite activation times the three parts is the infinity that it is in fp32, not infinity times zero.
 __global__ void k_pack_split(const float* W, int64_t per_w, int64_t so, int64_t si, int32_t n_out, int32_t n_in, int64_t count,
                              uint4* packed) {
   const int nkb = (n_in + 15) / 16;
@@ -452,25 +450,14 @@ __global__ void k_pack_split(const float* W, int64_t per_w, int64_t so, int64_t 
   const int kb = (int)(f % nkb);
   const int64_t out = (f / nkb) * 32 + (lane & 31);
   const float* w = W + m * per_w + out * so;
-  uint16_t part[3][8];
+  float x[8];
   for (int k = 0; k < 8; ++k) {
     const int col = 16 * kb + 8 * (k / 4) + 4 * (lane >> 5) + k % 4;
-    const float x = col < n_in ? w[col * si] : 0.f;
-    const float sign = copysignf(1.1754943508222875e-38f, x);
-    const bool real = fabsf(x) > 7.9e-31f && fabsf(x) < __builtin_inff();     // 2^-100: below it the stand-in would count
-    float md = fabsf(x) == __builtin_inff() ? 0.f : x - cut(x);
-    float lo = md - cut(md);
-    if (real && cut(md) == 0.f) md = sign;
-    if (real && cut(lo) == 0.f) lo = sign;
-    part[0][k] = (uint16_t)(__float_as_uint(x) >> 16);
-    part[1][k] = (uint16_t)(__float_as_uint(md) >> 16);
-    part[2][k] = (uint16_t)(__float_as_uint(lo) >> 16);
+    x[k] = col < n_in ? w[col * si] : 0.f;
   }
-  for (int p = 0; p < 3; ++p) {
-    uint32_t u[4];
-    for (int k = 0; k < 4; ++k) u[k] = part[p][2 * k] | (uint32_t)part[p][2 * k + 1] << 16;
-    packed[((m * per + (f << 6)) * 3 + p * 64) + lane] = make_uint4(u[0], u[1], u[2], u[3]);
-  }
+  uint4 part[3];
+  split8(x, part);
+  for (int p = 0; p < 3; ++p) packed[((m * per + (f << 6)) * 3 + p * 64) + lane] = part[p];
 }
 
 constexpr size_t kMaxLds = 160 * 1024;

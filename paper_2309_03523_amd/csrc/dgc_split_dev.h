@@ -22,22 +22,28 @@ __device__ __forceinline__ uint4 tops8(const float (&x)[8]) {
   return make_uint4(tops(x[0], x[1]), tops(x[2], x[3]), tops(x[4], x[5]), tops(x[6], x[7]));
 }
 
-// x = p[0] + p[1] + p[2], exactly, for finite x; an infinity is p[0] alone (its remainder would be NaN)
+// x = p[0] + p[1] + p[2], exactly, for finite x.  An infinity goes into the low part: that meets only the other operand's
+// high part, which has the sign of the whole number and is zero where that is.  Its other parts are the smallest normal
+// number of its sign, so that two infinities make one, too.
 __device__ __forceinline__ void split8(const float (&x)[8], uint4 (&p)[3]) {
-  float m[8], l[8];
+  float h[8], m[8], l[8];
   float top = 0.f;
 #pragma unroll
   for (int i = 0; i < 8; ++i) {
+    h[i] = x[i];
     m[i] = x[i] - cut(x[i]);
+    l[i] = m[i] - cut(m[i]);
     top = fmaxf(top, fabsf(x[i]));
   }
   if (__builtin_expect(__any(top == __builtin_inff()), 0)) {
 #pragma unroll
-    for (int i = 0; i < 8; ++i) m[i] = fabsf(x[i]) == __builtin_inff() ? 0.f : m[i];
+    for (int i = 0; i < 8; ++i)
+      if (fabsf(x[i]) == __builtin_inff()) {
+        h[i] = m[i] = copysignf(1.1754943508222875e-38f, x[i]);
+        l[i] = x[i];
+      }
   }
-#pragma unroll
-  for (int i = 0; i < 8; ++i) l[i] = m[i] - cut(m[i]);
-  p[0] = tops8(x);
+  p[0] = tops8(h);
   p[1] = tops8(m);
   p[2] = tops8(l);
 }

@@ -57,3 +57,43 @@ def test_split_dense_infinite_input():
     keep = np.ones((2, 50), bool)
     keep[0, 5:7] = keep[1, 33] = keep[1, 40] = False
     assert rel_err(Y[keep], want[keep]) < 1e-4
+
+
+def _same_specials(got, want):
+    return (np.array_equal(np.isnan(got), np.isnan(want)) and np.array_equal(np.isposinf(got), np.isposinf(want))
+            and np.array_equal(np.isneginf(got), np.isneginf(want)))
+
+
+def test_split_dense_infinite_weight():
+    """Infinite weights against inputs whose lower parts are zero (1, 0, powers of two), against infinite inputs and
+    against ordinary ones: the infinities of fp32 products, NaN only where they give it (infinity times zero,
+    opposite infinities)."""
+    from paper_2309_03523_amd.runner import run_forward
+    wl = synth.random_small(4, 2, 50, 40, 64, 64, 0.0, [[0, 50, 0, 2]], "none")     # no edges: a row sees itself
+    W = wl.params["gcn0.weight"]
+    W[3, 7], W[40, 0], W[41, 0], W[41, 39] = np.inf, -np.inf, np.inf, np.inf
+    wl.X[0, :, 7] = np.tile(np.float32([1.0, -1.0, 0.0, 2.0 ** -60, 0.3]), 10)
+    wl.X[1, :, 0] = np.tile(np.float32([1.0, -2.0, np.inf, -np.inf, 3.0]), 10)
+    wl.X[1, :5, 39] = np.float32([1.0, 1.0, 1.0, np.inf, -0.25])
+    Y = run_forward(wl)
+    with np.errstate(all="ignore"):
+        want = (wl.X.astype(np.float64) @ W.astype(np.float64).T + wl.params["gcn0.bias"]).astype(np.float32)
+    assert _same_specials(Y, want) and np.isnan(want).any() and np.isinf(want).any()
+    finite = np.isfinite(want)
+    assert rel_err(Y[finite], want[finite]) < 1e-4
+
+
+@pytest.mark.parametrize("kind", ["gru", "lstm"])
+def test_split_time_encoder_infinite_weight(kind):
+    """An infinite gate weight saturates its gate whatever the bits of the state: no NaN that the oracle does not have."""
+    from paper_2309_03523_amd.runner import run_forward
+    wl = synth.random_small(5, 3, 40, 24, 32, 32, 0.0, [[0, 40, 0, 3]], kind)
+    wl.H0[:, 4] = 1.0
+    wl.H0[:, 9] = -0.5
+    wl.params["rnn.weight_hh"][5, 4] = np.inf
+    wl.params["rnn.weight_hh"][38, 9] = np.inf
+    Y = run_forward(wl)
+    with np.errstate(all="ignore"):
+        want = oracle.forward(wl.graph, wl.chunks, wl.params, wl.X, wl.C, time_kind=kind, H0=wl.H0)
+    assert np.isfinite(want).all()
+    assert rel_err(Y, want) < 1e-4

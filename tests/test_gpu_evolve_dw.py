@@ -54,3 +54,28 @@ def test_weight_gradient_shapes(F, T, N, chunks, upstream):
         assert rel_err(alone[k], want["grads"][k]) < 1e-4, k
         assert np.array_equal(alone[k], beside[k]), k
     dw.layer.destroy()
+
+
+def test_weight_gradient_infinite_rows():
+    """An infinite row element against upstream gradients of 1 (whose lower parts are zero): the weight gradient has the
+    infinities that fp32 products give, and NaN only where they do (infinity times a gradient that is zero).  One
+    snapshot: the bias gradients are dL/dW times positive factors, element by element."""
+    import torch
+    from paper_2309_03523_amd.runner import DeviceWorkload
+    F, N = 64, 40
+    wl = synth.random_small(9, 1, N, F, F, F, 0.0, [[0, N, 0, 1]], "none")     # no edges: a row sees itself
+    wl.params = synth.evolve_params(9, F, F, random_bias=True)
+    wl.X[0, 3, 5], wl.X[0, 20, 7], wl.X[0, 21, 7] = np.inf, -np.inf, 2.0
+    dw = DeviceWorkload(wl, struct_kind="evolve_gcn_o", act_out="relu")
+    Y = dw.forward()
+    dY = torch.ones((1, N, F), device="cuda")
+    dw.layer.backward(Y, dY=dY)
+    torch.cuda.synchronize()
+    got = dw.layer.get_param("evolve.B_h.grad", (F, F))
+    with np.errstate(all="ignore"):
+        d = (Y.cpu().numpy()[0] > 0).astype(np.float64)
+        want = wl.X[0].astype(np.float64).T @ d
+    for special in (np.isnan, np.isposinf, np.isneginf):
+        assert np.array_equal(special(got), special(want))
+    assert np.isinf(want).any() and np.isnan(want).any()
+    dw.layer.destroy()
