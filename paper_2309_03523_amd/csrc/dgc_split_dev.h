@@ -9,6 +9,7 @@ namespace split {
 
 typedef float floatx16 __attribute__((ext_vector_type(16)));
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 typedef int intx4 __attribute__((ext_vector_type(4)));
 
 constexpr int kFrag = 64;   // uint4 of one fragment part (32 rows x 16 k, one bf16 part)
@@ -18,34 +19,54 @@ __device__ __forceinline__ float cut(float x) { return __uint_as_float(__float_a
 __device__ __forceinline__ uint32_t tops(float lo, float hi) {   // the upper halves of two words
   return __builtin_amdgcn_perm(__float_as_uint(hi), __float_as_uint(lo), 0x07060302u);
 }
+__device__ __forceinline__ uint32_t nearest(float lo, float hi) {   // two floats, each rounded to the nearest bf16 number
+  const bf16x2 v = {(__bf16)lo, (__bf16)hi};
+  return __builtin_bit_cast(uint32_t, v);
+}
+__device__ __forceinline__ float bf_lo(uint32_t u) { return __uint_as_float(u << 16); }
+__device__ __forceinline__ float bf_hi(uint32_t u) { return __uint_as_float(u & 0xffff0000u); }
 __device__ __forceinline__ uint4 tops8(const float (&x)[8]) {
   return make_uint4(tops(x[0], x[1]), tops(x[2], x[3]), tops(x[4], x[5]), tops(x[6], x[7]));
 }
 
-// x = p[0] + p[1] + p[2], exactly, for finite x.  An infinity goes into the low part: that meets only the other operand's
-// high part, which has the sign of the whole number and is zero where that is.  Its other parts are the smallest normal
-// number of its sign, so that two infinities make one, too.
+// x = p[0] + p[1] + p[2], exactly, for finite x: p[0] the bf16 number nearest to x, p[1] the one nearest to what is left,
+// p[2] the rest (at most seven bits).  To the nearest, not cut off: the rests then have either sign and half the size, and
+// what a product of parts leaves out has either sign, too.
+// An infinity goes into the low part: that meets only the other operand's high part, which has the sign of the whole
+// number and is zero where that is.  Its other parts are the smallest normal number of its sign, so that two infinities
+// make one, too.
 __device__ __forceinline__ void split8(const float (&x)[8], uint4 (&p)[3]) {
-  float h[8], m[8], l[8];
+  uint32_t h[4], m[4], l[4];
   float top = 0.f;
 #pragma unroll
-  for (int i = 0; i < 8; ++i) {
-    h[i] = x[i];
-    m[i] = x[i] - cut(x[i]);
-    l[i] = m[i] - cut(m[i]);
-    top = fmaxf(top, fabsf(x[i]));
+  for (int i = 0; i < 4; ++i) {
+    const float x0 = x[2 * i], x1 = x[2 * i + 1];
+    h[i] = nearest(x0, x1);
+    const float m0 = x0 - bf_lo(h[i]), m1 = x1 - bf_hi(h[i]);
+    m[i] = nearest(m0, m1);
+    l[i] = tops(m0 - bf_lo(m[i]), m1 - bf_hi(m[i]));
+    top = fmaxf(top, fmaxf(fabsf(x0), fabsf(x1)));
   }
-  if (__builtin_expect(__any(top == __builtin_inff()), 0)) {
+  if (__builtin_expect(__any(top > 3.3895313892515355e38f), 0)) {   // the largest bf16 number: beyond it, x may round to infinity
+    float a[8], b[8], c[8];
 #pragma unroll
-    for (int i = 0; i < 8; ++i)
+    for (int i = 0; i < 8; ++i) {
+      a[i] = cut(x[i]);
+      b[i] = x[i] - a[i];
+      c[i] = b[i] - cut(b[i]);
       if (fabsf(x[i]) == __builtin_inff()) {
-        h[i] = m[i] = copysignf(1.1754943508222875e-38f, x[i]);
-        l[i] = x[i];
+        a[i] = b[i] = copysignf(1.1754943508222875e-38f, x[i]);
+        c[i] = x[i];
       }
+    }
+    p[0] = tops8(a);
+    p[1] = tops8(b);
+    p[2] = tops8(c);
+    return;
   }
-  p[0] = tops8(h);
-  p[1] = tops8(m);
-  p[2] = tops8(l);
+  p[0] = make_uint4(h[0], h[1], h[2], h[3]);
+  p[1] = make_uint4(m[0], m[1], m[2], m[3]);
+  p[2] = make_uint4(l[0], l[1], l[2], l[3]);
 }
 
 // c += the product of one fragment each, the smallest products first; the five small ones go to `small`, which may be

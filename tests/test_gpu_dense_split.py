@@ -97,3 +97,21 @@ def test_split_time_encoder_infinite_weight(kind):
         want = oracle.forward(wl.graph, wl.chunks, wl.params, wl.X, wl.C, time_kind=kind, H0=wl.H0)
     assert np.isfinite(want).all()
     assert rel_err(Y, want) < 1e-4
+
+
+@pytest.mark.parametrize("F,S", [(64, 64), (256, 256), (300, 96)])
+def test_split_products_have_no_bias(F, S):
+    """What the six bf16 products of an fp32 product leave out has either sign.  Parts that are cut off instead of rounded
+    leave out 2^-24.5 of a term in the mean, always towards zero: 4e-8 of every sum.  Rounded ones leave the truncation of
+    the matrix unit's additions (measured 6e-9) and noise of 1e-7 an element, over 1e5 elements less than 1e-9.  The bars:
+    2e-8 for the mean, and for the root mean square 1.5e-7 (about one rounding of an fp32 sum; 1.2e-7 measured)."""
+    from paper_2309_03523_amd.runner import run_forward
+    N = 2000
+    wl = synth.random_small(F, 1, N, F, S, S, 0.0, [[0, N, 0, 1]], "none")     # no edges: a row sees itself
+    Y = run_forward(wl).astype(np.float64)
+    want = wl.X.astype(np.float64) @ wl.params["gcn0.weight"].astype(np.float64).T + wl.params["gcn0.bias"].astype(np.float64)
+    d = Y - want
+    bias = float((d * np.sign(want)).sum() / np.abs(want).sum())
+    rms = float(np.linalg.norm(d) / np.linalg.norm(want))
+    print(f"F={F} S={S}: bias {bias:.2e}, rms {rms:.2e}", flush=True)
+    assert abs(bias) < 2e-8 and rms < 1.5e-7
