@@ -194,7 +194,7 @@ __global__ void k_pack_weight_t(const float* Wt, int32_t T, int32_t F, int32_t S
 // and leaves the parts in LDS in fragment order for every wave.  Two LDS buffers in turn, the next rows' loads
 // in flight meanwhile.  With dP given, every tile's dP goes there over the rows of M that the tile has read (the
 // input gradient starts from it): a pass of its own over Y and the target that is not needed.
-// (64 snapshots x 62 500 rows, F = 256: 5.0 ms on the fp32 instruction and 2.1 ms for that pass; 4.3 ms here.)
+// (64 snapshots x 62 500 rows, F = 256: 5.0 ms on the fp32 instruction and 2.1 ms for that pass; 4.8 ms here.)
 // `split` workgroups per snapshot, as many as fill the chip (evolve_dw_split).
 constexpr int kDwRows = 16;
 
@@ -293,10 +293,12 @@ __global__ __launch_bounds__(64 * NJB) void k_dw_split(DwArgs a) {
       uint4 y[3];
 #pragma unroll
       for (int p = 0; p < 3; ++p) y[p] = buf[kOperand + (jb * 3 + p) * kFrag + lane];
-      // each link from zero, added up by rounding additions: hundreds of links would add up the cut-off
+      // each link from zero, its small products apart, added up by rounding additions: hundreds of links would add up
+      // the cut-off.  (16 x 3000 rows, width 64: U_r's gradient is 4.3e-8 off 64 bits, 8.4e-8 with the six in one sum.)
       floatx16 sum = (floatx16)(0.f);
-      six(sum, sum, x, y);
+      five(sum, x, y);
       acc[jb] += sum;
+      acc[jb] += __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_frag(x[0]), as_frag(y[0]), (floatx16)(0.f), 0, 0, 0);
     }
     buf = buf == lds ? lds + 2 * kOperand : lds;
   };
@@ -328,9 +330,9 @@ __global__ void k_dw_reduce(const float* partial, float* dWd, int32_t split, int
   const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (e >= total) return;
   const int64_t t = e / n_per_t, i = e - t * n_per_t;
-  float s = 0.f;
-  for (int k = 0; k < split; ++k) s += partial[(t * split + k) * n_per_t + i];
-  dWd[e] = s;
+  double s = 0.0;
+  for (int k = 0; k < split; ++k) s += (double)partial[(t * split + k) * n_per_t + i];
+  dWd[e] = (float)s;
 }
 
 // loss = (sum of the partial sums, in index order) / count; one block

@@ -79,3 +79,28 @@ def test_weight_gradient_infinite_rows():
         assert np.array_equal(special(got), special(want))
     assert np.isinf(want).any() and np.isnan(want).any()
     dw.layer.destroy()
+
+
+def test_weight_gradient_rounding():
+    """Distance of the ten gradients from double precision, root mean square.  The recurrence runs in double and the number
+    of elements is a power of two, so what is left is the rounding of the gradient itself (3.4e-8 at most in the mean) and
+    of the sums over 4096 rows a snapshot, which are kept below that.  The bar is 6e-8; sums that drop a part of the
+    products, or add their small parts to the large ones, are at 8e-8 to 1.2e-7."""
+    import torch
+    from paper_2309_03523_amd.runner import DeviceWorkload
+    T, N, F = 4, 4096, 64
+    wl = synth.random_small(11, T, N, F, F, F, 4.0, [[0, N, 0, T]], "none")
+    wl.params = synth.evolve_params(11, F, F, random_bias=True)
+    target = synth.stream(F, "target").standard_normal((T, N, F)).astype(np.float32)
+    dw = DeviceWorkload(wl, struct_kind="evolve_gcn_o", act_out="relu")
+    Y = dw.forward()
+    dw.layer.backward(Y, target=torch.from_numpy(target).cuda())
+    torch.cuda.synchronize()
+    want = oracle.evolve(wl.graph, wl.chunks, wl.params, wl.X, wl.C, target, want_grads=True)
+    off = {}
+    for k in oracle.EVOLVE_PARAMS:
+        w = np.asarray(want["grads"][k], np.float64)
+        off[k] = float(np.linalg.norm(dw.layer.get_param(k + ".grad", wl.params[k].shape) - w) / np.linalg.norm(w))
+    print({k: f"{v:.2e}" for k, v in off.items()}, flush=True)
+    assert max(off.values()) < 6e-8
+    dw.layer.destroy()
