@@ -75,8 +75,9 @@ __device__ __forceinline__ void fetch_ahead(uint4 (&w)[D][3], const WeightStream
 }
 
 // acc(g) + small(g) += W_g x rows, over nkb k-blocks (small: the five small products; may be acc); fr: this lane's
-// first operand of the staged rows
-template <int NG, int D, class Acc, class Small>
+// first operand of the staged rows.  LINKS: the small products of every k-block go to a sum of their own, which is added
+// to acc by rounding additions.
+template <int NG, int D, bool LINKS = false, class Acc, class Small>
 __device__ __forceinline__ void product(Acc&& acc, Small&& small, const uint4* fr, const WeightStream& ws, int off, int gstride, int nkb,
                                         int lane16, uint4 (&w)[D][3]) {
   constexpr int UK = D > NG ? D / NG : 1;
@@ -97,7 +98,13 @@ __device__ __forceinline__ void product(Acc&& acc, Small&& small, const uint4* f
         const int kn = k + (g + D - 1) / NG, gn = (g + D - 1) % NG;
         ws.unit(w[(u + D - 1) % D], lane16, off + gn * gstride + kn * kUnitBytes, kn < nkb);
         __builtin_amdgcn_sched_barrier(0);
-        six(acc(g), small(g), w[u % D], b);
+        if constexpr (LINKS) {
+          floatx16 link = (floatx16)(0.f);
+          six(acc(g), link, w[u % D], b);
+          acc(g) += link;
+        } else {
+          six(acc(g), small(g), w[u % D], b);
+        }
         if (g == NG - 1) {
           const uint4* next = fr + min(k + 1, nkb - 1) * (3 * kFrag);
 #pragma unroll
@@ -145,8 +152,10 @@ template <int KIND, bool SEQ, bool CAT, bool STACK, int MAXW>
 __global__ __launch_bounds__(64 * MAXW, 2) void k_dense_split(DenseArgs a) {
   constexpr bool kLstm = KIND == DGC_TIME_LSTM;
   // The five small products of Z go apart from the large one (the matrix unit truncates when it adds, and a small sum is
-  // truncated by less), the gates' do not (no registers).  Every variant adds in one order: a sequence table that says
-  // what the window says gives the same numbers.
+  // truncated by less), the gates' do not (no registers), but for a second recurrent layer: without a transform whose
+  // better sums make up for it, its gates' products alone would be off 64 bits by up to 1.4 times as much as on the fp32
+  // instruction.  There every k-block's go apart (0.8 times as much; two LSTM layers over 1.28 M rows 7.17 -> 7.32 ms).
+  // Every variant adds in one order with and without SEQ: a sequence table that says what the window says gives the same numbers.
   constexpr int NG = kLstm ? 4 : 3;
   constexpr int DG = SEQ && CAT ? 2 : NG, DZ = SEQ ? 3 : 4;    // weight fragments held: gates, transform
   extern __shared__ __align__(16) uint4 lds[];
@@ -284,7 +293,7 @@ __global__ __launch_bounds__(64 * MAXW, 2) void k_dense_split(DenseArgs a) {
       if (kLstm || g != 2) acc[g] = load_block(gbias + g * H + col0);
     auto hidden = [&](int g) -> floatx16& { return acc[!kLstm && g == 2 ? 3 : g]; };
     auto in = [&](int g) -> floatx16& { return acc[g]; };
-    product<NG, DG>(hidden, hidden, buf, wsh, offh, gsh, kbh, lane16, wg);
+    product<NG, DG, STACK>(hidden, hidden, buf, wsh, offh, gsh, kbh, lane16, wg);
     if constexpr (!STACK) {
       floatx16 z, zs = (floatx16)(0.f);
       for (int k = 0; k < nchunk; ++k) {
@@ -318,7 +327,7 @@ __global__ __launch_bounds__(64 * MAXW, 2) void k_dense_split(DenseArgs a) {
     }
     __syncthreads();
     if constexpr (!kLstm) acc[2] = load_block(gbias + 2 * H + col0);
-    product<NG, DG>(in, in, buf, wsi, offx + (kbx - kbh) * kUnitBytes, gsx, kbh, lane16, wg);
+    product<NG, DG, STACK>(in, in, buf, wsi, offx + (kbx - kbh) * kUnitBytes, gsx, kbh, lane16, wg);
     // requests of the next step go out before this step's stores: memory operations retire in order
     if (mapped) {
       yrow = yrow_next;
