@@ -118,6 +118,8 @@ hipError_t dev_alloc(dgc_layer* L, T** p, int64_t count) {
   if (e == hipSuccess) {
     L->allocs.push_back(v);
     *p = static_cast<T*>(v);
+  } else {
+    (void)hipGetLastError();      // reported here; a later call must not find it
   }
   return e;
 }
@@ -128,6 +130,20 @@ void dev_free(dgc_layer* L, T* p) {
   auto it = std::find(L->allocs.begin(), L->allocs.end(), static_cast<void*>(p));
   if (it != L->allocs.end()) L->allocs.erase(it);
   (void)hipFree(p);
+}
+
+// Buffers that are used together: all of them, or none and the error.
+template <class T>
+struct Wanted {
+  T** p;
+  int64_t count;
+};
+template <class... T>
+hipError_t dev_alloc_all(dgc_layer* L, Wanted<T>... w) {
+  hipError_t e = hipSuccess;
+  ((e = e == hipSuccess ? dev_alloc(L, w.p, w.count) : e), ...);
+  if (e != hipSuccess) ((dev_free(L, *w.p), *w.p = nullptr), ...);
+  return e;
 }
 
 void free_all(dgc_layer* L) {
@@ -1157,9 +1173,9 @@ static dgc_status_t prepare_dx(dgc_layer* L, hipStream_t st) {
   if (L->n_chunks > kMaxGridYZ || max_w > kMaxGridYZ)   // a kernel of it takes one grid plane per chunk, one row per snapshot
     return fail(DGC_ERR_UNSUPPORTED, "input gradient: more than 65535 chunks or snapshots per window");
   if (!L->d_dM) {
-    DGC_HIP_TRY(dev_alloc(L, &L->d_dM, (int64_t)L->T * L->N * d.F));
-    DGC_HIP_TRY(dev_alloc(L, &L->d_rowidx, L->total_rows));
-    DGC_HIP_TRY(dev_alloc(L, &L->d_Wt_plain, (int64_t)L->T * evolve_packed_bytes(L->evo, L->evo.split) / (int64_t)sizeof(float4)));
+    const int64_t wt = (int64_t)L->T * evolve_packed_bytes(L->evo, L->evo.split) / (int64_t)sizeof(float4);
+    DGC_HIP_TRY(dev_alloc_all(L, Wanted<float>{&L->d_dM, (int64_t)L->T * L->N * d.F}, Wanted<int64_t>{&L->d_rowidx, L->total_rows},
+                              Wanted<float4>{&L->d_Wt_plain, wt}));
     evolve_row_index(L->d_chunks, L->n_chunks, max_nv, max_w, L->N, L->d_rowidx, st);
   }
   return DGC_OK;
@@ -1397,10 +1413,9 @@ dgc_status_t dgc_layer_set_labels(dgc_layer_t* L, const int32_t* labels, void* s
   if (L->T > kMaxGridYZ) return fail(DGC_ERR_UNSUPPORTED, "generated chunks: more than 65535 snapshots");
   Labelled& lab = L->lab;
   if (!lab.col_signed) {
-    DGC_HIP_TRY(dev_alloc(L, &lab.col_signed, L->total_nnz));
-    DGC_HIP_TRY(dev_alloc(L, &lab.seq_in, (int64_t)L->T * L->N));
-    DGC_HIP_TRY(dev_alloc(L, &lab.seq_out, (int64_t)L->T * L->N));
-    DGC_HIP_TRY(dev_alloc(L, &lab.labels, (int64_t)L->T * L->N));
+    const int64_t tn = (int64_t)L->T * L->N;
+    DGC_HIP_TRY(dev_alloc_all(L, Wanted<int32_t>{&lab.col_signed, L->total_nnz}, Wanted<int64_t>{&lab.seq_in, tn},
+                              Wanted<int64_t>{&lab.seq_out, tn}, Wanted<int32_t>{&lab.labels, tn}));
   }
   DGC_HIP_TRY(hipMemcpyAsync(lab.labels, labels, sizeof(int32_t) * (size_t)L->T * L->N, hipMemcpyDeviceToDevice, st));
   labels_build(L->graph_dev(), L->d_segs, labels, lab.col_signed, lab.seq_in, lab.seq_out, st);

@@ -1,0 +1,135 @@
+// The layer's host code (csrc/dgc_api.hip holds no kernel) on stand-ins of the HIP runtime and of the kernels' launchers:
+// device memory is host memory, the n-th allocation can be made to fail, launches leave their names and their pointers in
+// a log.  Called by test_host_layer.py with the name of a check; a check that fails says so and ends the program with 1.
+#include "dgc_api.hip"
+
+#include <cstdio>
+#include <cstdlib>
+
+static std::vector<std::string> calls;      // launches and stream operations, in order
+static int allocations = 0, fails_at = 0;   // the fails_at-th allocation fails (0: none)
+static hipError_t last_error = hipSuccess;
+static bool null_pointer = false;           // a launcher was handed one
+
+static void launched(const char* name, std::initializer_list<const void*> pointers) {
+  calls.push_back(name);
+  for (const void* p : pointers) null_pointer |= p == nullptr;
+}
+static int count(const char* name) { return (int)std::count(calls.begin(), calls.end(), name); }
+static void expect(bool ok, const char* what) {
+  if (ok) return;
+  std::printf("not so: %s\n", what);
+  std::exit(1);
+}
+
+extern "C" {
+hipError_t hipMalloc(void** p, size_t n) {
+  if (++allocations == fails_at) return last_error = hipErrorOutOfMemory;
+  *p = std::calloc(n ? n : 1, 1);
+  return hipSuccess;
+}
+hipError_t hipFree(void* p) { std::free(p); return hipSuccess; }
+hipError_t hipGetLastError() { const hipError_t e = last_error; last_error = hipSuccess; return e; }
+const char* hipGetErrorString(hipError_t) { return "out of memory"; }
+hipError_t hipMemcpyAsync(void* to, const void* from, size_t n, hipMemcpyKind, hipStream_t) { std::memcpy(to, from, n); return hipSuccess; }
+hipError_t hipStreamSynchronize(hipStream_t) { return hipSuccess; }
+hipError_t hipStreamWaitEvent(hipStream_t, hipEvent_t, unsigned) { calls.push_back("wait"); return hipSuccess; }
+hipError_t hipEventRecord(hipEvent_t e, hipStream_t) {
+  calls.push_back("event " + std::to_string(reinterpret_cast<uintptr_t>(e)));
+  return hipSuccess;
+}
+hipError_t hipEventSynchronize(hipEvent_t) { return hipSuccess; }
+hipError_t hipEventElapsedTime(float* ms, hipEvent_t a, hipEvent_t b) {
+  *ms = (float)(reinterpret_cast<uintptr_t>(b) - reinterpret_cast<uintptr_t>(a));
+  return hipSuccess;
+}
+hipError_t hipStreamDestroy(hipStream_t) { return hipSuccess; }
+hipError_t hipEventDestroy(hipEvent_t) { return hipSuccess; }
+}
+
+namespace dgc {
+void launch_spmm(const SpmmArgs& a, hipStream_t) { launched("spmm", {a.fresh, a.M}); if (a.skip_stale) null_pointer |= !a.row_map; }
+bool launch_dense(const DenseArgs& a, hipStream_t, std::string*) { launched("dense", {a.M, a.Wg, a.Y}); return true; }
+void evolve_forward_weights(const EvolveWs&, hipStream_t) { launched("recurrence", {}); }
+bool evolve_backward_dw(const EvolveWs&, const EvolveBwdIn&, bool, hipStream_t, std::string*) { launched("weight gradient", {}); return true; }
+void evolve_backward_bptt(const EvolveWs&, hipStream_t) { launched("back-propagation", {}); }
+void evolve_row_index(const ChunkInfo*, int32_t, int64_t, int32_t, int64_t, int64_t* idx, hipStream_t) { launched("row index", {idx}); }
+void evolve_pack_weights_plain(const EvolveWs&, float4* packed, hipStream_t) { launched("pack", {packed}); }
+void labels_build(const GraphDev&, const Segment*, const int32_t*, int32_t* col, int64_t* in, int64_t* out, hipStream_t) {
+  launched("labels", {col, in, out});
+}
+}  // namespace dgc
+
+// An EvolveGCN-O layer of one chunk, 2 snapshots x 40 vertices, width 32, after its forward.
+static dgc_layer* evolve_layer() {
+  static float memory[64];
+  static int64_t index[3] = {0, 2, 4};
+  dgc_layer* L = new dgc_layer();
+  L->desc.struct_kind = DGC_STRUCT_EVOLVE_GCN_O;
+  L->desc.n_struct_layers = 1;
+  L->desc.F = L->desc.S = L->desc.H = 32;
+  L->desc.act_out = DGC_ACT_RELU;
+  L->T = 2; L->N = 40; L->n_chunks = 1;
+  L->chunks = {dgc_chunk_t{0, 40, 0, 2}};
+  L->total_rows = 80; L->total_nnz = 80;
+  L->cinfo_host = {ChunkInfo{0, 40, 0, 0, 0, 2}};
+  L->row_tile_ptr.assign(index, index + 3);
+  L->evo.T = 2; L->evo.F = L->evo.S = 32; L->evo.split = true;
+  L->d_M = memory; L->ldm = 32;
+  L->evo.Wt_packed = reinterpret_cast<float4*>(memory);
+  L->side = reinterpret_cast<hipStream_t>(uintptr_t(1));
+  L->fork = reinterpret_cast<hipEvent_t>(uintptr_t(101));
+  L->join = reinterpret_cast<hipEvent_t>(uintptr_t(102));
+  L->forward_done = L->m_saved = true;
+  return L;
+}
+alignas(16) static float tensor[64];
+
+// Whichever buffer of the input gradient there is no memory for: the call reports it and starts nothing of the input
+// gradient, and so does the next call; the parameters' gradients are computed; with memory the next call does it all.
+static void input_gradient_memory() {
+  for (int n = 1; n <= 3; ++n) {
+    dgc_layer* L = evolve_layer();
+    auto backward = [&] { return dgc_layer_backward(L, tensor, 32, nullptr, 0, tensor, 32, nullptr, tensor, 32, nullptr); };
+    calls.clear();
+    for (int attempt = 0; attempt < 2; ++attempt) {
+      allocations = 0; fails_at = n;
+      expect(backward() != DGC_OK, "a backward without memory for the input gradient is an error");
+      expect(allocations == n, "the buffers are asked for one after the other");
+      expect(count("weight gradient") == attempt + 1 && count("back-propagation") == attempt + 1, "the parameters' gradients are computed");
+      expect(count("row index") + count("pack") + count("dense") + count("spmm") == 0, "nothing of the input gradient is started");
+      expect(L->allocs.empty(), "what was allocated is given back");
+      expect(hipGetLastError() == hipSuccess, "no error is left for a later call");
+    }
+    fails_at = 0;
+    expect(backward() == DGC_OK, "with memory it works");
+    expect(count("row index") == 1 && count("pack") == 1 && count("dense") == 1 && count("spmm") == 1 && !null_pointer,
+           "the input gradient is computed from buffers that are there");
+    L->m_saved = true;
+    expect(backward() == DGC_OK && count("row index") == 1 && L->allocs.size() == 3, "the buffers are kept");
+  }
+}
+
+static void label_memory() {
+  for (int n = 1; n <= 4; ++n) {
+    dgc_layer* L = evolve_layer();
+    std::vector<int32_t> labels(80, 0);
+    calls.clear();
+    for (int attempt = 0; attempt < 2; ++attempt) {
+      allocations = 0; fails_at = n;
+      expect(dgc_layer_set_labels(L, labels.data(), nullptr) != DGC_OK, "labels without memory are an error");
+      expect(calls.empty() && L->allocs.empty() && !L->lab.built, "nothing is started or kept");
+    }
+    fails_at = 0;
+    expect(dgc_layer_set_labels(L, labels.data(), nullptr) == DGC_OK && count("labels") == 1 && !null_pointer, "with memory it works");
+  }
+}
+
+int main(int argc, char** argv) {
+  const std::string check = argc > 1 ? argv[1] : "";
+  if (check == "input gradient memory") input_gradient_memory();
+  else if (check == "label memory") label_memory();
+  else expect(false, "the check is known");
+  std::puts("so");
+  return 0;
+}

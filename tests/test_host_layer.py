@@ -1,0 +1,24 @@
+"""The layer's host code on the CPU, built with stand-ins for the HIP runtime and the kernels' launchers (host_layer.cpp):
+what it does when device memory runs out, and in which order it enqueues what runs on two streams."""
+import os
+import subprocess
+
+import pytest
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+ROOT = os.path.dirname(HERE)
+
+
+@pytest.fixture(scope="module")
+def program(tmp_path_factory):
+    out = str(tmp_path_factory.mktemp("host_layer") / "host_layer")
+    subprocess.run(["g++", "-std=c++17", "-O1", "-D__HIP_PLATFORM_AMD__", "-I", "/opt/rocm/include", "-I", os.path.join(ROOT, "include"),
+                    "-I", os.path.join(ROOT, "paper_2309_03523_amd", "csrc"), os.path.join(HERE, "host_layer.cpp"), "-o", out,
+                    "-Wl,--unresolved-symbols=ignore-all"], check=True, timeout=120)     # launchers that no check reaches
+    return out
+
+
+@pytest.mark.parametrize("check", ["input gradient memory", "label memory"])
+def test_host_layer(program, check):
+    r = subprocess.run([program, check], capture_output=True, text=True, timeout=60)
+    assert r.returncode == 0, r.stdout + r.stderr
