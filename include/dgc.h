@@ -280,8 +280,11 @@ dgc_status_t dgc_layer_aggregate(dgc_layer_t* layer, const float* X, int64_t ldx
 dgc_status_t dgc_layer_gather(dgc_layer_t* layer, const float* C, int64_t ldc, float* halo,
                               int64_t ldh, void* stream);
 
-/* Per-stage device time, from HIP events recorded on the caller's stream (for measurement;
- * adds no synchronisation to forward / backward themselves).  Stages:
+/* Per-stage device time, from HIP events recorded on the stream that the stage runs on (for
+ * measurement; adds no synchronisation to forward / backward themselves).  That is the caller's
+ * stream, but for stage 4 and, in a backward that computes dX, stage 6: they run on a stream of
+ * the layer's own and may overlap stage 0 and the input gradient, so the stages of an EvolveGCN-O
+ * pass do not add up to it (and a wait of one stream for the other is in no stage).  Stages:
  *  0 aggregation of the first GCN layer (gather + split-row reduction included)
  *  1 first GCN layer's dense transform            (0 ms unless n_struct_layers = 2)
  *  2 aggregation of the second GCN layer          (0 ms unless n_struct_layers = 2)

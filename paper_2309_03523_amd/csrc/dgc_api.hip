@@ -1017,9 +1017,11 @@ dgc_status_t dgc_layer_forward(dgc_layer_t* L, const void* Xv, int64_t ldx, cons
   const bool evolve = d.struct_kind == DGC_STRUCT_EVOLVE_GCN_O;
   L->evx_fwd = false;
   if (evolve) {
-    // The weights evolve beside the aggregation: two dependent launches per snapshot, each a few microseconds on a
-    // few compute units.  With the other half of it, the back-propagation beside the input gradient: a training step
-    // of 64 snapshots x 62 500 vertices, F = 256, 31.1 -> 28.3 ms.
+    // The weights evolve on a stream of their own (two dependent launches per snapshot, each a few microseconds on a few
+    // compute units), and so does the back-propagation when an input gradient is asked for.  Little of either runs beside
+    // the large launches: these are enqueued after some 130 small ones, and a small one finds no free compute unit
+    // while a grid that fills the chip is being dispatched.  A training step of 64 snapshots x 62 500 vertices, F = 256:
+    // 27.4 ms on one stream, 27.1 on two; of 16 x 3000, F = 64: 599 and 590 us.
     DGC_HIP_TRY(hipEventRecord(L->fork, st));
     DGC_HIP_TRY(hipStreamWaitEvent(L->side, L->fork, 0));
     if (prof) DGC_HIP_TRY(hipEventRecord(L->evx[0], L->side));
@@ -1032,8 +1034,8 @@ dgc_status_t dgc_layer_forward(dgc_layer_t* L, const void* Xv, int64_t ldx, cons
   // order and skips the rows of absent vertices
   const bool tfl1 = L->tf.built && d.n_struct_layers == 1, tfl2 = L->tf.built && d.n_struct_layers == 2;
   run_aggregate(L, X, ldx, C, ldc, d.F, tfl1 ? L->tf.Mv : L->d_M, L->ldm, st, tfl1 ? L->tf.row_map : nullptr);
-  if (evolve) DGC_HIP_TRY(hipStreamWaitEvent(st, L->join, 0));
   if (prof) DGC_HIP_TRY(hipEventRecord(L->ev[1], st));
+  if (evolve) DGC_HIP_TRY(hipStreamWaitEvent(st, L->join, 0));      // in no stage: between two events
   const char* last = "gcn0";
   if (d.n_struct_layers == 2) {
     // first layer for every row of the batch -> Z1 [T,N,S]; then aggregate Z1 | C1
@@ -1153,7 +1155,8 @@ dgc_status_t dgc_layer_stage_times(dgc_layer_t* L, float* host_ms) {
   }
   if (!L->ev_valid) return fail(DGC_ERR_STATE, "no profiled forward has been enqueued");
   DGC_HIP_TRY(hipEventSynchronize(L->ev[4]));
-  for (int i = 0; i < 4; ++i) DGC_HIP_TRY(hipEventElapsedTime(&host_ms[i], L->ev[i], L->ev[i + 1]));
+  for (int i = 0; i < 4; ++i)
+    if (L->desc.n_struct_layers == 2 || i == 0 || i == 3) DGC_HIP_TRY(hipEventElapsedTime(&host_ms[i], L->ev[i], L->ev[i + 1]));
   if (L->evx_fwd) DGC_HIP_TRY(hipEventElapsedTime(&host_ms[4], L->evx[0], L->evx[1]));
   if (L->evx_bwd) {
     DGC_HIP_TRY(hipEventSynchronize(L->evx[5]));
@@ -1224,10 +1227,10 @@ dgc_status_t dgc_layer_backward(dgc_layer_t* L, const void* Yv, int64_t ldy, con
   std::string why;
   const bool prof = L->profiling;
   L->evx_bwd = false;
-  if (prof) DGC_HIP_TRY(hipEventRecord(L->evx[2], st));
   // without the input gradient the parameters' gradients are computed all the same
   const dgc_status_t dx_rc = dX ? prepare_dx(L, st) : DGC_OK;
   const bool want_dx = dX && dx_rc == DGC_OK;
+  if (prof) DGC_HIP_TRY(hipEventRecord(L->evx[2], st));
   if (!evolve_backward_dw(L->evo, in, want_dx, st, &why)) return fail(DGC_ERR_UNSUPPORTED, why);
   if (want_dx) L->m_saved = false;
   // the back-propagation through the weights beside the input gradient (if that is asked for)

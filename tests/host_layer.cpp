@@ -125,10 +125,41 @@ static void label_memory() {
   }
 }
 
+// The events around a stage enclose its launches and nothing else: the caller's stream waits for the weight recurrence
+// after the aggregation's last event and before the dense stage's first; no stage 1 or 2 without a second GCN layer.
+static void stage_events() {
+  dgc_layer* L = evolve_layer();
+  for (int i = 0; i <= DGC_N_STAGES; ++i) L->ev[i] = reinterpret_cast<hipEvent_t>(uintptr_t(1 + 10 * i));
+  for (int i = 0; i < 6; ++i) L->evx[i] = reinterpret_cast<hipEvent_t>(uintptr_t(1001 + 10 * i));
+  L->profiling = true;
+  calls.clear();
+  expect(dgc_layer_forward(L, tensor, 32, tensor, 32, nullptr, 0, nullptr, nullptr, tensor, 32, nullptr, nullptr) == DGC_OK, "forward");
+  auto at = [&](const char* name, int nth = 0) {
+    for (size_t i = 0; i < calls.size(); ++i)
+      if (calls[i] == name && nth-- == 0) return (int)i;
+    return -1;
+  };
+  expect(count("wait") == 2 && at("wait", 0) < at("recurrence"), "the recurrence's stream waits for the caller's, then the caller's for it");
+  const int join = at("wait", 1);
+  expect(at("event 1") >= 0 && at("event 1") < at("spmm") && at("event 11") == at("spmm") + 1, "stage 0 is the aggregation");
+  expect(at("event 11") < join && join < at("event 31"), "no stage holds the wait");
+  expect(at("event 31") == at("dense") - 1 && at("event 41") == at("dense") + 1, "stage 3 is the dense kernel");
+  expect(at("event 1001") == at("recurrence") - 1 && at("event 1011") == at("recurrence") + 1, "stage 4 is the recurrence");
+  float ms[DGC_N_STAGES];
+  expect(dgc_layer_stage_times(L, ms) == DGC_OK, "stage times");
+  expect(ms[0] == 10 && ms[1] == 0 && ms[2] == 0 && ms[3] == 10 && ms[4] == 10 && ms[5] == 0, "the stages that ran");
+  calls.clear();
+  expect(dgc_layer_backward(L, tensor, 32, nullptr, 0, tensor, 32, nullptr, tensor, 32, nullptr) == DGC_OK, "backward");
+  expect(at("event 1021") == at("weight gradient") - 1 && at("event 1031") == at("weight gradient") + 1, "stage 5 is the weight gradient");
+  expect(at("event 1041") == at("back-propagation") - 1 && at("event 1051") == at("back-propagation") + 1, "stage 6 is the back-propagation");
+  expect(calls.back() == "wait", "the caller's stream waits for the other one");
+}
+
 int main(int argc, char** argv) {
   const std::string check = argc > 1 ? argv[1] : "";
   if (check == "input gradient memory") input_gradient_memory();
   else if (check == "label memory") label_memory();
+  else if (check == "stage events") stage_events();
   else expect(false, "the check is known");
   std::puts("so");
   return 0;
