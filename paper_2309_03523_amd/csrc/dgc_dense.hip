@@ -488,19 +488,9 @@ bool launch_k(const DenseArgs& a, hipStream_t st, std::string* why) {
   const int ld = dense_ld(a.K0, a.S, KIND == DGC_TIME_NONE ? 0 : a.H);
   const size_t lds = dense_lds_bytes(a.K0, a.S, KIND == DGC_TIME_NONE ? 0 : a.H);
   constexpr bool kSeq = KIND != DGC_TIME_NONE;
-  static bool attr_done = false;  // per instantiation
-  if (!attr_done) {
-    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_dense<KIND, NRB, UPW, false>),
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
-    if (e == hipSuccess && kSeq)
-      e = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_dense<KIND, NRB, UPW, kSeq>),
-                              hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
-    if (e != hipSuccess) {
-      if (why) *why = std::string("hipFuncSetAttribute: ") + hipGetErrorString(e);
-      return false;
-    }
-    attr_done = true;
-  }
+  static std::atomic<uint64_t> ready{0}, ready_seq{0};  // per instantiation
+  if (!allow_lds(reinterpret_cast<const void*>(&k_dense<KIND, NRB, UPW, false>), 160 * 1024, ready, why)) return false;
+  if (kSeq && !allow_lds(reinterpret_cast<const void*>(&k_dense<KIND, NRB, UPW, kSeq>), 160 * 1024, ready_seq, why)) return false;
   if (a.n_tiles > 0) {
     if (kSeq && a.seq_in)
       hipLaunchKernelGGL((k_dense<KIND, NRB, UPW, kSeq>), (unsigned)a.n_tiles, kThreads, lds, st, a, ld);

@@ -32,7 +32,6 @@
 // with the weights from L2 for every 64 rows, 3.3 like this, of which the rows alone take 2.0 and the products alone
 // 2.3; 1.28 M rows, 172 -> 128: 0.85 -> 0.38 ms).
 #include <algorithm>
-#include <atomic>
 
 #include "dgc_internal.h"
 #include "dgc_split_dev.h"
@@ -475,22 +474,6 @@ __global__ void k_pack_split(const float* W, int64_t per_w, int64_t so, int64_t 
 constexpr size_t kMaxLds = 160 * 1024;
 constexpr int kCus = 256;
 
-template <class Kernel>
-bool allow_lds(Kernel* kernel, std::atomic<uint64_t>& ready, std::string* why) {   // ready: devices where it is done
-  int dev = 0;
-  (void)hipGetDevice(&dev);
-  const uint64_t bit = 1ull << (dev & 63);
-  if (ready.load(std::memory_order_relaxed) & bit) return true;
-  const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize,
-                                           (int)kMaxLds);
-  if (e != hipSuccess) {
-    if (why) *why = std::string("hipFuncSetAttribute: ") + hipGetErrorString(e);
-    return false;
-  }
-  ready.fetch_or(bit, std::memory_order_relaxed);
-  return true;
-}
-
 template <int KIND, bool SEQ, bool CAT, bool STACK, int MAXW>
 bool launch_time(DenseArgs a, int njb, hipStream_t st, std::string* why) {
   const int nkb0 = STACK ? 2 * njb : (a.K0 + 15) / 16;
@@ -499,7 +482,7 @@ bool launch_time(DenseArgs a, int njb, hipStream_t st, std::string* why) {
   const size_t lds = (size_t)2 * a.kb_chunk * kUnitBytes + sizeof(float) * 5 * 32 * njb;
   static std::atomic<uint64_t> ready{0};
   auto* kernel = &k_dense_split<KIND, SEQ, CAT, STACK, MAXW>;
-  if (!allow_lds(kernel, ready, why)) return false;
+  if (!allow_lds(reinterpret_cast<const void*>(kernel), kMaxLds, ready, why)) return false;
   if (a.n_tiles32 > 0) hipLaunchKernelGGL(kernel, (unsigned)a.n_tiles32, 64 * njb, lds, st, a);
   return true;
 }
@@ -533,7 +516,7 @@ bool launch_rows(DenseArgs a, int kb0, hipStream_t st, std::string* why) {
   const size_t lds = a.kb_chunk * kUnitBytes + bias;
   static std::atomic<uint64_t> ready{0};
   auto* kernel = &k_rows_split<NKB, MAXW, FIRST>;
-  if (!allow_lds(kernel, ready, why)) return false;
+  if (!allow_lds(reinterpret_cast<const void*>(kernel), kMaxLds, ready, why)) return false;
   const int64_t grid = std::min<int64_t>(a.n_row_tiles, (int64_t)kCus * per_cu);
   if (grid > 0) hipLaunchKernelGGL(kernel, (unsigned)grid, 64 * njb, lds, st, a, kb0);
   return true;

@@ -506,15 +506,10 @@ void dysat_forward(const DysatWs& ws, const void* X, int64_t ldx, const void* C,
   ta.Wq = ws.Wqp; ta.Wk = ws.Wkp; ta.Wv = ws.Wvp;
   ta.Y = static_cast<uint16_t*>(Y); ta.ldy = ldy;
   {
-    static bool attr_set = false;   // dynamic LDS above 64 KB has to be allowed once per kernel
+    static std::atomic<uint64_t> ready{0}, ready_wide{0};
     const size_t lds = sizeof(uint4) * 3 * kFragsPerW;
-    if (!attr_set) {
-      (void)hipFuncSetAttribute(reinterpret_cast<const void*>(k_temporal_fwd<false>), hipFuncAttributeMaxDynamicSharedMemorySize,
-                                (int)lds);
-      (void)hipFuncSetAttribute(reinterpret_cast<const void*>(k_temporal_fwd<true>), hipFuncAttributeMaxDynamicSharedMemorySize,
-                                (int)lds);
-      attr_set = true;
-    }
+    (void)(ws.wide ? allow_lds(reinterpret_cast<const void*>(k_temporal_fwd<true>), lds, ready_wide)
+                   : allow_lds(reinterpret_cast<const void*>(k_temporal_fwd<false>), lds, ready));   // if not, the launch is an error
     const unsigned grid = (unsigned)std::min<int64_t>(256, (ws.n_tiles + 7) / 8);
     if (ws.wide) hipLaunchKernelGGL(k_temporal_fwd<true>, grid, 512, lds, st, ta);
     else hipLaunchKernelGGL(k_temporal_fwd<false>, grid, 512, lds, st, ta);

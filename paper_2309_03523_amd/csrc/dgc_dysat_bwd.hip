@@ -1299,18 +1299,13 @@ void dysat_backward(const DysatWs& ws, const void* Y, int64_t ldy, const void* d
   // (1) temporal attention: dQ, dK, dV (+ loss), then dP -> dU and the position-table gradient
   const size_t lds = sizeof(uint4) * 3 * kFragsPerW;
   {
-    static bool attr_set = false;   // dynamic LDS above 64 KB has to be allowed once per kernel
-    if (!attr_set) {
-      (void)hipFuncSetAttribute(reinterpret_cast<const void*>(k_temporal_bwd<false>), hipFuncAttributeMaxDynamicSharedMemorySize,
-                                (int)lds);
-      (void)hipFuncSetAttribute(reinterpret_cast<const void*>(k_temporal_bwd<true>), hipFuncAttributeMaxDynamicSharedMemorySize,
-                                (int)lds);
-      (void)hipFuncSetAttribute(reinterpret_cast<const void*>(k_dw_bf16<3, true>), hipFuncAttributeMaxDynamicSharedMemorySize,
-                                (int)(sizeof(uint4) * 2 * 64 * dw_frags<3, true>() + 65536));   // and the position rows
-      (void)hipFuncSetAttribute(reinterpret_cast<const void*>(k_temporal_bwd2),
-                                hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-      attr_set = true;
-    }
+    // (if not allowed, the launch is an error)
+    static std::atomic<uint64_t> ready[4] = {};
+    (void)allow_lds(reinterpret_cast<const void*>(k_temporal_bwd<false>), lds, ready[0]);
+    (void)allow_lds(reinterpret_cast<const void*>(k_temporal_bwd<true>), lds, ready[1]);
+    (void)allow_lds(reinterpret_cast<const void*>(k_dw_bf16<3, true>), sizeof(uint4) * 2 * 64 * dw_frags<3, true>() + 65536,
+                    ready[2]);   // and the position rows
+    (void)allow_lds(reinterpret_cast<const void*>(k_temporal_bwd2), lds, ready[3]);
   }
   const int grid_a = (int)std::min<int64_t>(kTbwdWaves / 8, (ws.n_tiles + 7) / 8);
   const int grid_b = (int)std::min<int64_t>(kTbwdWaves / 8, (tiles32 + 7) / 8);

@@ -471,15 +471,8 @@ bool evolve_backward_dw(const EvolveWs& ws, const EvolveBwdIn& in, bool keep_dp,
   switch (njb) {
 #define DGC_DW_CASE(NJB)                                                                               \
   case NJB: {                                                                                          \
-    static bool attr = false;                                                                          \
-    if (!attr) {                                                                                       \
-      if (hipFuncSetAttribute(reinterpret_cast<const void*>(&k_dw_split<NJB>),                         \
-                              hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024) != hipSuccess) { \
-        if (why) *why = "hipFuncSetAttribute failed";                                                  \
-        return false;                                                                                  \
-      }                                                                                                \
-      attr = true;                                                                                     \
-    }                                                                                                  \
+    static std::atomic<uint64_t> ready{0};                                                             \
+    if (!allow_lds(reinterpret_cast<const void*>(&k_dw_split<NJB>), 160 * 1024, ready, why)) return false;\
     hipLaunchKernelGGL((k_dw_split<NJB>), grid, 64 * NJB, lds, st, a);                                 \
     break;                                                                                             \
   }

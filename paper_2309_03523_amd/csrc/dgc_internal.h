@@ -4,6 +4,7 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <atomic>
 #include <string>
 #include <vector>
 
@@ -59,6 +60,21 @@ struct GraphDev {
       return fail(DGC_ERR_DEVICE, std::string(#expr) + ": " + hipGetErrorString(e_)); \
     }                                                                 \
   } while (0)
+
+// Dynamic LDS above 64 KB has to be allowed once per kernel and device; done: the devices where it is.
+inline bool allow_lds(const void* kernel, size_t bytes, std::atomic<uint64_t>& done, std::string* why = nullptr) {
+  int dev = 0;
+  (void)hipGetDevice(&dev);
+  const uint64_t bit = 1ull << (dev & 63);
+  if (done.load(std::memory_order_relaxed) & bit) return true;
+  const hipError_t e = hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
+  if (e != hipSuccess) {
+    if (why) *why = std::string("hipFuncSetAttribute: ") + hipGetErrorString(e);
+    return false;
+  }
+  done.fetch_or(bit, std::memory_order_relaxed);
+  return true;
+}
 
 // text that dgc_last_error(NULL) returns on the calling thread (dgc_api.hip)
 void set_thread_error(const std::string& msg);

@@ -9,6 +9,7 @@
 static std::vector<std::string> calls;      // launches and stream operations, in order
 static int allocations = 0, fails_at = 0;   // the fails_at-th allocation fails (0: none)
 static hipError_t last_error = hipSuccess;
+static int device = 0;
 static bool null_pointer = false;           // a launcher was handed one
 
 static void launched(const char* name, std::initializer_list<const void*> pointers) {
@@ -42,6 +43,11 @@ hipError_t hipEventSynchronize(hipEvent_t) { return hipSuccess; }
 hipError_t hipEventElapsedTime(float* ms, hipEvent_t a, hipEvent_t b) {
   *ms = (float)(reinterpret_cast<uintptr_t>(b) - reinterpret_cast<uintptr_t>(a));
   return hipSuccess;
+}
+hipError_t hipGetDevice(int* d) { *d = device; return hipSuccess; }
+hipError_t hipFuncSetAttribute(const void*, hipFuncAttribute, int bytes) {
+  calls.push_back("allow " + std::to_string(bytes));
+  return fails_at < 0 ? hipErrorInvalidValue : hipSuccess;
 }
 hipError_t hipStreamDestroy(hipStream_t) { return hipSuccess; }
 hipError_t hipEventDestroy(hipEvent_t) { return hipSuccess; }
@@ -155,11 +161,27 @@ static void stage_events() {
   expect(calls.back() == "wait", "the caller's stream waits for the other one");
 }
 
+// Large dynamic LDS is allowed once on every device that a kernel runs on; a refusal is reported and not taken for done.
+static void lds_per_device() {
+  std::atomic<uint64_t> done{0};
+  std::string why;
+  calls.clear();
+  for (int pass = 0; pass < 2; ++pass)
+    for (device = 0; device < 3; ++device) expect(allow_lds(&done, 98304, done, &why), "it is allowed");
+  expect(count("allow 98304") == 3, "once on each device");
+  fails_at = -1;
+  device = 5;
+  expect(!allow_lds(&done, 98304, done, &why) && !why.empty(), "a refusal is reported");
+  fails_at = 0;
+  expect(allow_lds(&done, 98304, done, &why) && count("allow 98304") == 5, "and asked for again");
+}
+
 int main(int argc, char** argv) {
   const std::string check = argc > 1 ? argv[1] : "";
   if (check == "input gradient memory") input_gradient_memory();
   else if (check == "label memory") label_memory();
   else if (check == "stage events") stage_events();
+  else if (check == "lds per device") lds_per_device();
   else expect(false, "the check is known");
   std::puts("so");
   return 0;

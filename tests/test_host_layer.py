@@ -1,5 +1,6 @@
 """The layer's host code on the CPU, built with stand-ins for the HIP runtime and the kernels' launchers (host_layer.cpp):
-what it does when device memory runs out, and in which order it enqueues what runs on two streams."""
+what it does when device memory runs out, in which order it enqueues what runs on two streams, and that what has to be
+allowed once per device is."""
 import os
 import subprocess
 
@@ -18,7 +19,7 @@ def program(tmp_path_factory):
     return out
 
 
-@pytest.mark.parametrize("check", ["input gradient memory", "label memory", "stage events"])
+@pytest.mark.parametrize("check", ["input gradient memory", "label memory", "stage events", "lds per device"])
 def test_host_layer(program, check):
     r = subprocess.run([program, check], capture_output=True, text=True, timeout=60)
     assert r.returncode == 0, r.stdout + r.stderr
