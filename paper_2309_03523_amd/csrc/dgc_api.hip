@@ -195,13 +195,13 @@ dgc_status_t check_desc(const dgc_layer_desc_t& d, std::string* msg) {
   if (d.rows_per_group < 0 || d.rows_per_group > 32) { *msg = "rows_per_group must be in [0,32]"; return DGC_ERR_INVALID_ARG; }
   if (d.dense_kernel < DGC_DENSE_AUTO || d.dense_kernel > DGC_DENSE_WAVE) { *msg = "unknown dense_kernel"; return DGC_ERR_INVALID_ARG; }
   if (d.long_nnz < 0 || d.part_nnz < 0) { *msg = "long_nnz / part_nnz must be >= 0"; return DGC_ERR_INVALID_ARG; }
-  // Where the workgroup-tile kernel runs a dense stage, its operand tile must fit the 160 KB of LDS.
-  auto tile_kernel_runs = [&](int32_t S, int32_t H, int32_t kind) {
-    const bool s_ok = S == 32 || S == 64 || S == 128 || (S == 256 && kind == DGC_TIME_NONE);
-    return d.dense_kernel == DGC_DENSE_TILE || !(s_ok && (kind == DGC_TIME_NONE || H == S));
+  // A dense stage of another shape, or that the workgroup-tile kernel is asked for, must fit that kernel's operand tile in
+  // the 160 KB of LDS, whichever kernel then runs it.
+  auto other_shape = [&](int32_t S, int32_t H, int32_t kind) {
+    return d.dense_kernel == DGC_DENSE_TILE || !dense_wave_shape(S, H, kind);
   };
   auto fits = [&](int32_t K0, int32_t S, int32_t H, int32_t kind) {
-    return !tile_kernel_runs(S, H, kind) || dense_lds_bytes(K0, S, kind == DGC_TIME_NONE ? 0 : H) <= 160 * 1024;
+    return !other_shape(S, H, kind) || dense_lds_bytes(K0, S, kind == DGC_TIME_NONE ? 0 : H) <= 160 * 1024;
   };
   if (d.agg_kernel < DGC_AGG_TABLE || d.agg_kernel > DGC_AGG_WALK) { *msg = "unknown agg_kernel"; return DGC_ERR_INVALID_ARG; }
   if (d.lstm_input_concat < 0 || d.lstm_input_concat > 1) { *msg = "lstm_input_concat must be 0 or 1"; return DGC_ERR_INVALID_ARG; }
@@ -209,7 +209,7 @@ dgc_status_t check_desc(const dgc_layer_desc_t& d, std::string* msg) {
     if (d.struct_kind != DGC_STRUCT_GCN || d.n_struct_layers != 2 || d.time_kind != DGC_TIME_LSTM) {
       *msg = "lstm_input_concat needs two GCN layers and the LSTM"; return DGC_ERR_INVALID_ARG;
     }
-    if (tile_kernel_runs(d.S, d.H, d.time_kind)) {
+    if (other_shape(d.S, d.H, d.time_kind)) {
       *msg = "lstm_input_concat is built in the split dense kernel: S = H in {32, 64, 128}, dense_kernel not DGC_DENSE_TILE";
       return DGC_ERR_UNSUPPORTED;
     }
@@ -219,14 +219,15 @@ dgc_status_t check_desc(const dgc_layer_desc_t& d, std::string* msg) {
     if (d.struct_kind != DGC_STRUCT_GCN || (d.time_kind != DGC_TIME_GRU && d.time_kind != DGC_TIME_LSTM)) {
       *msg = "a stacked time encoder needs a GCN layer with a GRU or LSTM"; return DGC_ERR_INVALID_ARG;
     }
-    if (tile_kernel_runs(d.S, d.H, d.time_kind)) {
+    if (other_shape(d.S, d.H, d.time_kind)) {
       *msg = "the stacked time encoder is built in the split dense kernel: S = H in {32, 64, 128}, dense_kernel not DGC_DENSE_TILE";
       return DGC_ERR_UNSUPPORTED;
     }
   }
   const bool two = d.n_struct_layers == 2;
   if (!fits(two ? d.S : d.F, d.S, d.H, d.time_kind) || (two && !fits(d.F, d.S, 0, DGC_TIME_NONE))) {
-    *msg = "these dimensions need the workgroup-tile kernel, whose tile holds max(F rounded up to 8, S, H) <= 304 columns";
+    *msg = "other shapes than S = H in {32, 64, 128} (a transform alone: 256, too) must fit the workgroup-tile kernel, whose tile "
+           "holds max(F rounded up to 8, S, H) <= 304 columns";
     return DGC_ERR_UNSUPPORTED;
   }
   return DGC_OK;
@@ -1104,7 +1105,7 @@ dgc_status_t dgc_layer_forward(dgc_layer_t* L, const void* Xv, int64_t ldx, cons
     //  sequences are the first one's)
     const int32_t n_st = d.time_kind == DGC_TIME_LSTM ? 2 : 1;
     const int64_t block = (int64_t)n_st * da.total_state_rows * d.H;
-    da.M = Y; da.ldm = ldy; da.m_by_vertex = true; da.input_is_z = true; da.K0 = 0;
+    da.M = Y; da.ldm = ldy; da.input_is_z = true; da.K0 = 0;
     da.Wih = L->params["rnn1.weight_ih"].packed; da.Whh = L->params["rnn1.weight_hh"].packed;
     da.bih = L->params["rnn1.bias_ih"].raw; da.bhh = L->params["rnn1.bias_hh"].raw;
     da.Wg = nullptr; da.bg = nullptr;

@@ -532,11 +532,10 @@ void launch_pack_weight(const float* W, int32_t n_out, int32_t n_in, float4* pac
 }
 
 bool launch_dense(const DenseArgs& a, hipStream_t st, std::string* why) {
-  const bool wave_shape = a.S == 32 || a.S == 64 || a.S == 128 || (a.S == 256 && a.time_kind == DGC_TIME_NONE);
-  if (a.variant != DGC_DENSE_TILE && !(a.variant == DGC_DENSE_WAVE && !wave_shape) &&
+  if (a.variant != DGC_DENSE_TILE && !(a.variant == DGC_DENSE_WAVE && !dense_wave_shape(a.S, a.H, a.time_kind)) &&
       dense_split_supported(a.S, a.H, a.time_kind))
     return launch_dense_split(a, st, why);
-  if (a.variant == DGC_DENSE_WAVE || a.X2 || a.input_is_z || a.m_by_vertex) {
+  if (a.variant == DGC_DENSE_WAVE || a.X2 || a.input_is_z) {
     if (why) *why = "the split dense kernel needs S = H in {32, 64, 128}";
     return false;
   }

@@ -204,16 +204,18 @@ struct DenseArgs {
   const float* X2; int64_t ldx2;
   const int64_t* x2_map;
   // A stacked recurrent layer (split kernel only): the rows of M are rows t*N + v of a
-  // [T,N,ldm] tensor (m_by_vertex) and are the time encoder's input as they are (input_is_z: no
-  // transform, K0 = 0).
-  // M may be Y itself: a wave reads row (t, v) in step t and writes it one step later.
-  bool m_by_vertex;
+  // [T,N,ldm] tensor and are the time encoder's input as they are (no transform, K0 = 0).
+  // M may be Y itself: a wave requests row (t, v) before step t and writes it at that step's end.
   bool input_is_z;
 };
 // returns false if the (S,H,K0) combination has no kernel
 bool launch_dense(const DenseArgs& a, hipStream_t st, std::string* why);
 // The split kernel (dgc_dense_split.hip) takes weights as three bf16 parts per fragment of 32 x 16, see k_pack_split.
 bool dense_split_supported(int32_t S, int32_t H, int32_t time_kind);
+// Of its shapes, those that DGC_DENSE_WAVE, the concatenated input, the stacked time encoder and F above 304 are offered for.
+inline bool dense_wave_shape(int32_t S, int32_t H, int32_t time_kind) {
+  return (S == 32 || S == 64 || S == 128 || (S == 256 && time_kind == DGC_TIME_NONE)) && (time_kind == DGC_TIME_NONE || H == S);
+}
 bool launch_dense_split(const DenseArgs& a, hipStream_t st, std::string* why);
 inline int64_t split_weight_bytes(int32_t n_out, int32_t n_in) {
   return (int64_t)(n_out / 32) * ((n_in + 15) / 16) * 3 * 64 * 16;

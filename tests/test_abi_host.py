@@ -66,7 +66,7 @@ def test_create_rejects_bad_descriptors(lib):
     assert _create(lib, dict(gat), chunks=((0, 5, 0, 2),))[0] == 3
     assert _create(lib, dict(rows_per_group=64))[0] == 1
     assert _create(lib, null_snapshot=True)[0] == 1
-    # the LSTM reading both GCN layers' outputs: two layers, LSTM, the wave-private kernel's sizes
+    # the LSTM reading both GCN layers' outputs: two layers, LSTM, the sizes of DGC_DENSE_WAVE
     cat = dict(lstm_input_concat=1, n_struct_layers=2, time_kind=2)
     assert _create(lib, dict(cat, time_kind=1))[0] == 1
     assert _create(lib, dict(cat, n_struct_layers=1))[0] == 1
@@ -74,6 +74,17 @@ def test_create_rejects_bad_descriptors(lib):
     assert _create(lib, dict(cat, S=96, H=96))[0] == 4
     assert _create(lib, dict(cat, dense_kernel=1))[0] == 4
     assert _create(lib, dict(gat, lstm_input_concat=1))[0] == 1
+
+
+def test_wide_inputs_outside_the_wave_shapes(lib):
+    """F above 304 is offered for the shapes of DGC_DENSE_WAVE; elsewhere it is refused, also where another kernel than the
+    workgroup-tile one would run, and the message says which shapes take it."""
+    for kw in (dict(F=400, S=96, H=96), dict(F=312, S=256, H=256), dict(F=400, S=160, H=160, time_kind=0),
+               dict(F=312, S=128, H=128, dense_kernel=1)):
+        rc, msg = _create(lib, kw)
+        assert rc == 4 and "S = H in {32, 64, 128}" in msg and "304" in msg, msg
+    for kw in (dict(F=512, S=128, H=128), dict(F=512, S=256, time_kind=0), dict(F=304, S=96, H=96)):
+        assert _create(lib, kw, chunks=((0, 5, 0, 2),))[0] == 3        # past the dimensions: the chunk is refused
 
 
 def test_create_rejects_bad_chunks(lib):

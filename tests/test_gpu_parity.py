@@ -127,8 +127,8 @@ def _compare_layer(torch, wl, dw, mask=None, **okw):
 @pytest.mark.parametrize("F,S,H", [(32, 32, 32), (20, 64, 32), (77, 64, 64), (128, 128, 128), (172, 128, 128),
                                    (40, 96, 160), (64, 256, 256)])
 def test_layer_matches_oracle(torch_mod, kind, F, S, H, dense):
-    """dense = auto runs the wave-private kernel where it applies (S = H in {32, 64, 128}) and the
-    workgroup-tile kernel elsewhere; dense = tile forces the latter everywhere."""
+    """dense = auto runs the split kernels where they are built (S = H) and the workgroup-tile kernel
+    elsewhere; dense = tile forces the latter everywhere."""
     N, T = 203, 5
     # ragged tiles (vertex counts 1, 63, 65, 74), windows of different length, a gap in coverage
     chunks = [[0, 1, 0, 5], [1, 64, 0, 2], [1, 64, 2, 5], [64, 129, 0, 5], [129, 203, 1, 4]]
@@ -144,8 +144,8 @@ def test_layer_matches_oracle(torch_mod, kind, F, S, H, dense):
 @pytest.mark.parametrize("kind,F,S,H", [("gru", 512, 128, 128), ("lstm", 512, 128, 128), ("none", 512, 256, 256),
                                         ("gru", 304, 256, 256), ("lstm", 300, 256, 256)])
 def test_maximum_dimensions(torch_mod, kind, F, S, H):
-    """The largest dimensions that run: F = 512 with the wave-private kernel, max(F, S, H) = 304
-    columns where the workgroup-tile kernel (its tile lives in LDS) has to run."""
+    """The largest dimensions that run: F = 512 in the shapes of DGC_DENSE_WAVE, max(F, S, H) = 304
+    columns where the workgroup-tile kernel's tile has to fit in LDS."""
     N, T = 140, 3
     chunks = [[0, 70, 0, 3], [70, 140, 0, 2], [70, 140, 2, 3]]
     wl = synth.random_small(9, T, N, F, S, H, 5.0, chunks, kind, hub=True)
