@@ -1,11 +1,11 @@
 // Graph-attention + causal temporal self-attention layer, bf16: backward pass (gradients of the
-// seven parameter tensors; the cache is a constant and input gradients are not produced).
+// seven parameter tensors and, if asked for, of the input rows; the cache is a constant).
 //
 // Stages: (1) temporal attention backward per 2-vertex tile (recomputes P, Q, K, V and the
 // probabilities; writes dU, dQ, dK, dV and the position-table gradient), (2) dW_q, dW_k, dW_v as
 // products over all rows, (3) graph attention row pass (gradients of the destination logits),
 // (4) reverse-edge pass (gradients of both projections of every vertex, of a_src and a_dst),
-// (5) dW of the projection from the input and the cache rows.  Every reduction over rows goes
+// (5) dW of the projection from the input and the cache rows, (6) dX.  Every reduction over rows goes
 // through per-wave (per-workgroup) slots that are added in slot order: no floating-point atomics.
 #include "dgc_dysat_dev.h"
 
@@ -149,8 +149,7 @@ __global__ __launch_bounds__(512) void k_temporal_bwd(TemporalBwdArgs a) {
           split8v(v, 8 * c, vh[c], vl[c]);
         }
       }
-      // dL/dY of features [32 jb, 32 jb + 32), head c in row-layout order; the next block's pieces
-      // are requested now
+      // dL/dY of features [32 jb, 32 jb + 32), head c in row-layout order (requested before the products above)
       bf16x8 dyh[2], dyl[2];
 #pragma unroll
       for (int c = 0; c < 2; ++c) {

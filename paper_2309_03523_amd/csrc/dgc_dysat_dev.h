@@ -133,10 +133,6 @@ __device__ __forceinline__ floatx16 mfma2b(bf16x8 a, bf16x8 bh, bf16x8 bl, float
   c = mfma(a, bl, c);
   return mfma(a, bh, c);
 }
-__device__ __forceinline__ floatx16 mfma2a(bf16x8 ah, bf16x8 al, bf16x8 b, floatx16 c) {
-  c = mfma(al, b, c);
-  return mfma(ah, b, c);
-}
 
 // Selection operand that transposes a 32 x 16 piece of a row-major tile on the matrix core:
 // as B operand, element p of lane (j = l%32, hh) is 1 where j == 16 c + 8 hh + p.  With a natural

@@ -17,9 +17,6 @@
 namespace dgc {
 namespace {
 
-__device__ __forceinline__ float f4get(const float4& v, int q) { return q == 0 ? v.x : q == 1 ? v.y : q == 2 ? v.z : v.w; }
-__device__ __forceinline__ float sigmoidf_(float x) { return 1.0f / (1.0f + expf(-x)); }
-
 // ---------------------------------------------------------------------------------------------
 // The weight recurrence and its back-propagation through time run in DOUBLE precision: W is the
 // state of a 64-step recurrence whose rounding errors feed every output row of every snapshot,
