@@ -768,7 +768,7 @@ def labelled_main(args):
                         "bound": "mfma", "achieved": achieved, "peak": PEAK_SPLIT_MFMA_TFLOPS, "unit": "TFLOP/s",
                         "frac": achieved / PEAK_SPLIT_MFMA_TFLOPS, "traffic": traffic.get("dense"),
                         "flops_per_launch": dense_flops, "ms_per_launch": dense_ms},
-           "roofline_aggregation": {"kernel": "k_spmm_short + k_spmm_long + k_spmm_long_reduce (pre-marked columns)",
+           "roofline_aggregation": {"kernel": "k_agg + k_spmm_long_reduce (edge-table kernels over pre-marked columns)",
                                     "bound": "hbm", "achieved": agg_bytes / (agg_ms * 1e-3) / 1e9, "peak": PEAK_HBM_GBS,
                                     "unit": "GB/s", "frac": agg_bytes / (agg_ms * 1e-3) / 1e9 / PEAK_HBM_GBS,
                                     "traffic": traffic.get("aggregation"), "bytes_per_launch": agg_bytes,
