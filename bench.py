@@ -175,6 +175,8 @@ def evolve_report(args, wl, desc, dw, rows, value, ms_per_step, stage, t_gen, t_
            "stage_ms": {"aggregate0": float(stage[0]), "dense_forward": float(stage[3]),
                         "weight_evolution": float(stage[4]), "weight_gradient": float(stage[5]),
                         "bptt": float(stage[6])},
+           "stage_note": "weight_evolution and, with the input gradient, bptt run on a stream of the layer's own beside the large "
+                         "launches: from the first launch to the last, waits for compute units included",
            "loss": float(loss.item()), "setup_s": {"generate": t_gen, "upload_create_pack": t_create}}
     if graph_ms is not None:
         out["hip_graph_replay_ms_per_step"] = graph_ms

@@ -285,7 +285,8 @@ dgc_status_t dgc_layer_gather(dgc_layer_t* layer, const float* C, int64_t ldc, f
  * measurement; adds no synchronisation to forward / backward themselves).  That is the caller's
  * stream, but for stage 4 and, in a backward that computes dX, stage 6: they run on a stream of
  * the layer's own and may overlap stage 0 and the input gradient, so the stages of an EvolveGCN-O
- * pass do not add up to it (and a wait of one stream for the other is in no stage).  Stages:
+ * pass do not add up to it (and a wait of one stream for the other is in no stage; but a stage's
+ * time includes what its launches wait for compute units that the other stream holds).  Stages:
  *  0 aggregation of the first GCN layer (gather + split-row reduction included)
  *  1 first GCN layer's dense transform            (0 ms unless n_struct_layers = 2)
  *  2 aggregation of the second GCN layer          (0 ms unless n_struct_layers = 2)

@@ -17,9 +17,10 @@
 // result is the next product's operand without moving between lanes.
 //
 // What bounds them: the matrix cores' power.  Random operands through a loop of nothing but this MFMA reach
-// 1.83 PFLOP/s of bf16 on this GPU (2.46 with zeros), a library product 1.33; the time encoders run at 1.1
-// (GRU 128 wide, 3.2 M rows: 6.27 ms on the fp32 instruction, 3.96 ms here; the two LSTM layers of MPNN-LSTM over
-// 1.28 M rows 6.90 + 4.35 -> 2.85 + 1.80 ms; GRU 256 wide, 160 k rows 2.29 -> 0.88 ms).  Without the weights' loads,
+// 1.8 PFLOP/s of bf16 on this GPU (2.46 with zeros), a library product 1.33; the time encoders run at 1.1, at 1.6 GHz in
+// the mean with the matrix units busy for two cycles of three
+// (GRU 128 wide, 3.2 M rows: 6.27 ms on the fp32 instruction, 3.93 ms here; the two LSTM layers of MPNN-LSTM over
+// 1.28 M rows 6.90 + 4.35 -> 2.9 + 1.95 ms; GRU 256 wide, 160 k rows 2.29 -> 0.9 ms).  Without the weights' loads,
 // the LDS reads and the gate arithmetic the first would still take 3.5 ms.  Tiles of 64 vertices halve the weights'
 // L2 traffic and are no faster (4.15 ms: two workgroups of 256 registers a wave, more work behind each barrier);
 // three workgroups per CU of 168 registers spill (4.36 ms).
@@ -29,8 +30,9 @@
 // wave of the workgroup, and only the split activations (h, M, Z in turn) go through LDS.
 // k_rows_split (transforms alone): wave jb keeps its columns of the weights in registers and a workgroup streams
 // row tiles past them, so that nothing but rows is read (4 M rows, 256 -> 256: 5.16 ms on the fp32 instruction, 3.67
-// with the weights from L2 for every 64 rows, 3.3 like this, of which the rows alone take 2.0 and the products alone
-// 2.3; 1.28 M rows, 172 -> 128: 0.85 -> 0.38 ms).
+// with the weights from L2 for every 64 rows, 3.5 like this, of which the rows alone take 2.0 and the products alone
+// 2.3; 1.28 M rows, 172 -> 128: 0.85 -> 0.39 ms).  From 13 k-blocks on (four waves; 15 with eight) 256 registers do not
+// hold the weights, both sums and the requested rows: 8 to 36 of them go to scratch.
 #include <algorithm>
 
 #include "dgc_internal.h"

@@ -115,3 +115,19 @@ def test_split_products_have_no_bias(F, S):
     rms = float(np.linalg.norm(d) / np.linalg.norm(want))
     print(f"F={F} S={S}: bias {bias:.2e}, rms {rms:.2e}", flush=True)
     assert abs(bias) < 2e-8 and rms < 1.5e-7
+
+
+@pytest.mark.parametrize("F,S,kind,layers,bounds", CASES)
+def test_split_dense_rounding(F, S, kind, layers, bounds):
+    """Root mean square distance from the oracle's double products.  With all six part products a transform is up to 1.5e-7 off,
+    a time encoder up to 3.3e-7 (its fast exponentials); a transform that leaves one of them out is 5e-6 off or more.  The
+    bar between: 1e-6."""
+    from paper_2309_03523_amd.runner import run_forward
+    chunks = synth.grid_chunks(5, 3, [np.asarray(bounds)] * 2)
+    wl = synth.random_small(F + S, 5, 70, F, S, S, 4.0, chunks, kind, layers)
+    Y = run_forward(wl).astype(np.float64)
+    want = oracle.forward(wl.graph, wl.chunks, wl.params, wl.X, wl.C, time_kind=kind, C1=wl.C1, H0=wl.H0,
+                          n_struct_layers=layers).astype(np.float64)
+    off = float(np.linalg.norm(Y - want) / np.linalg.norm(want))
+    print(f"F={F} S={S} {kind} layers={layers}: {off:.2e}", flush=True)
+    assert off < 1e-6
