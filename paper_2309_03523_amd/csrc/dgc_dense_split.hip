@@ -6,9 +6,10 @@
 // without a bias.  (Parts cut off instead of rounded leave out up to 2^-21 and 2^-24.5 in the mean, always of the
 // product's own sign: a GRU over 32 x 100 000 rows is then 2.5e-7 off 64 bits instead of 2.3e-7, EvolveGCN-O's gradients
 // twice to three times as far.)  v_mfma_f32_32x32x16_bf16 does 16 times the work of v_mfma_f32_32x32x2f32 per cycle, so the
-// six cost 2.7 times less than the fp32 instruction and add up in fewer roundings.  No scaling is needed, and what
-// overflows fp32 overflows here; but of a number below 2^-110 the parts below the smallest bf16 number are lost: a product
-// of nothing but such rows is 3e-7 off at 2^-112 and 3e-3 at 2^-126.
+// six cost 2.7 times less than the fp32 instruction and add up in fewer roundings.  No scaling is needed, but
+// at the ends of the range fp32 has a little more: a product within 1 % of the largest float may overflow (its rounded high
+// parts do), and of a number below 2^-110 the parts below the smallest bf16 number are lost (a transform of nothing but
+// such rows is 3e-7 off at 2^-112 and 3e-3 at 2^-126).
 //
 // With the weights as A operand (lane l: A[l%32][8*(l/32) .. +7]) and 32 activation rows as B operand
 // (B[8*(l/32) .. +7][l%32]), lane (n = l%32, half = l/32) receives of row n the columns 8*g4 + 4*half + e in
