@@ -779,9 +779,9 @@ def labelled_main(args):
            "device_ms_per_step": {"median": float(np.median(per)), "min": float(per.min()), "max": float(per.max())},
            "chunks": {"count": int(sizes.size), "largest": int(sizes.max()), "median": float(np.median(sizes)),
                       "iterations": iters, "converged": bool(conv),
-                      "stale_neighbour_reads": se, "stale_neighbour_fraction": se / nnz,
-                      "stale_state_reads": st_, "stale_state_fraction": st_ / rows,
-                      "rectangular_64_chunks": {"stale_neighbour_fraction": re_ / nnz, "stale_state_fraction": rt / rows}},
+                      "stale_neighbour_reads": se, "stale_neighbour_fraction": se / g.nnz,
+                      "stale_state_reads": st_, "stale_state_fraction": st_ / (T * N),
+                      "rectangular_64_chunks": {"stale_neighbour_fraction": re_ / g.nnz, "stale_state_fraction": rt / (T * N)}},
            "setup_s": {"generate": t_gen, "upload_create_pack": t_create, "label_propagation": t_labels,
                        "label_tables": t_tables, "lanes": t_lanes}}
     if not args.no_cpu_baseline:
