@@ -326,22 +326,19 @@ dgc_status_t build_evolve(dgc_layer* L, const std::vector<ChunkInfo>& cinfo, hip
     DGC_HIP_TRY(hipMemsetAsync(g.raw, 0, sizeof(float) * g.numel(), st));
     L->params[std::string(kEvolveNames[k]) + ".grad"] = g;
     ev.G[k] = g.raw;
-    DGC_HIP_TRY(dev_alloc(L, &ev.Pd[k], n));
-    DGC_HIP_TRY(dev_alloc(L, &ev.Gd[k], n));
   }
   DGC_HIP_TRY(dev_alloc(L, &ev.Wt_f32, T * n));
-  DGC_HIP_TRY(dev_alloc(L, &ev.Wt, T * n));
+  DGC_HIP_TRY(dev_alloc(L, &ev.walk_packed, evolve_walk_elems(ev)));
+  DGC_HIP_TRY(dev_alloc(L, &ev.Wt, (T + 1) * n));
   DGC_HIP_TRY(dev_alloc(L, &ev.Zg, T * n));
   DGC_HIP_TRY(dev_alloc(L, &ev.Rg, T * n));
   DGC_HIP_TRY(dev_alloc(L, &ev.Wc, T * n));
+  DGC_HIP_TRY(dev_alloc(L, &ev.Ah, T * n));
+  DGC_HIP_TRY(dev_alloc(L, &ev.Az, T * n));
+  DGC_HIP_TRY(dev_alloc(L, &ev.Ar, T * n));
   float* pk = nullptr;
   DGC_HIP_TRY(dev_alloc(L, &pk, (int64_t)T * evolve_packed_bytes(ev, ev.split) / (int64_t)sizeof(float)));
   ev.Wt_packed = reinterpret_cast<float4*>(pk);
-  for (double*& t : ev.tmp) DGC_HIP_TRY(dev_alloc(L, &t, n));
-  DGC_HIP_TRY(dev_alloc(L, &ev.zsum, n));
-  DGC_HIP_TRY(dev_alloc(L, &ev.rsum, n));
-  for (double*& t : ev.back0) DGC_HIP_TRY(dev_alloc(L, &t, n));
-  for (double*& t : ev.back1) DGC_HIP_TRY(dev_alloc(L, &t, n));
   DGC_HIP_TRY(dev_alloc(L, &ev.dWd, T * n));
   int64_t most = 1;
   for (int32_t t = 0; t < T; ++t) most = std::max(most, L->row_tile_ptr[t + 1] - L->row_tile_ptr[t]);
@@ -1018,12 +1015,10 @@ dgc_status_t dgc_layer_forward(dgc_layer_t* L, const void* Xv, int64_t ldx, cons
   const bool evolve = d.struct_kind == DGC_STRUCT_EVOLVE_GCN_O;
   L->evx_fwd = false;
   if (evolve) {
-    // The weights evolve on a stream of their own (two dependent launches per snapshot, each a few microseconds on a few
-    // compute units), and so does the back-propagation when an input gradient is asked for.  It saves little: these are
-    // some 130 small launches, enqueued before the large one that should run beside them, and a small launch finds
-    // no free compute unit while a grid that fills the chip is being dispatched.  64 snapshots x 62 500 vertices, F = 256:
-    // 8.3 ms from the recurrence's first launch to its last (1.3 by itself) beside 7.4 of aggregation, 10.1 (2.0) back beside
-    // 8.3; a training step takes 27.4 ms on one stream, 27.1 on two; of 16 x 3000, F = 64: 599 and 590 us.
+    // The weights evolve on a stream of their own: one launch of S / 4 workgroups that walks all snapshots beside the
+    // aggregation, and so does the back-propagation beside the input gradient when that is asked for.  A training step of
+    // 64 snapshots x 62 500 vertices, F = 256, takes 26.8 ms on one stream and 25.6 on two, of 16 x 5000 1.57 and 1.38 ms; of 16 x 3000,
+    // F = 64, 0.40 ms either way (0.33 and 0.34 without the input gradient).
     DGC_HIP_TRY(hipEventRecord(L->fork, st));
     DGC_HIP_TRY(hipStreamWaitEvent(L->side, L->fork, 0));
     if (prof) DGC_HIP_TRY(hipEventRecord(L->evx[0], L->side));

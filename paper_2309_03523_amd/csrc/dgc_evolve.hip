@@ -20,144 +20,336 @@ namespace {
 // ---------------------------------------------------------------------------------------------
 // The weight recurrence and its back-propagation through time run in DOUBLE precision: W is the
 // state of a 64-step recurrence whose rounding errors feed every output row of every snapshot,
-// and the work is tiny (a handful of n x n x n products per step, n = F = S <= 256), so it is
-// latency-bound whatever the precision: a chain of two dependent launches per snapshot each way.
-// One kernel does every matrix step:
-//   tile(C) = [C +] sum_p op(A_p) op(B_p)   followed by an elementwise epilogue,
-// on v_mfma_f64_16x16x4f64 (lane l supplies A[l%16][l/16], B[l/16][l%16]; receives
-// D[4*v + l/16][l%16], v = 0..3).  A workgroup of 4 waves owns one 16 x 16 tile; the waves
-// split K, their partial tiles are added in wave order (reproducible), a quarter of the tile by each wave,
-// which then applies the epilogue to it.  grid.z selects one of several independent jobs of a launch.
-// A wave's whole share of a product is requested at once, the next product's behind it.
-// (n = 64, 16 snapshots: the weights and their back-propagation took 490 us of device time as six launches per snapshot
-// that read eight k at a time; 263 us like this.)
+// and the work is tiny (four n x n x n products per step, n = F = S <= 256), so it is bound by the
+// serial chain whatever the precision.
+// The columns of W never meet: every product multiplies W (or its gradient) from the left.  So a workgroup
+// owns four columns and walks all snapshots by itself, one launch each way, and the only waits are its own two
+// barriers a step.  Four columns, because v_mfma_f64_4x4x4_4b does as many products per cycle as the
+// 16x16x4 form: a step's chain is as short as it gets and n / 4 workgroups share the work.
+//   Wave w of the n / 16 that share a product owns rows 16 w .. +15.  The four 4x4 blocks of an instruction take four
+//   quarters of a 16-wide stretch of the contraction, and four accumulators the four row groups: lane
+//   (i = l / 16, blk = l / 4 % 4, j = l % 4) supplies A[4 g + i'][16 kc + 4 blk + k'] (i' = l % 4, k' = l / 16) and
+//   B[16 kc + 4 blk + i][j].  After the four blocks' sums are added up the lane holds row 4 blk + i,
+//   column j of the wave's sixteen rows: the layout of B, so a state goes to LDS and comes back one double a lane in order.
+//   The small matrices stay in registers (n <= 64); larger ones are read from L2 at every step, a batch of 32 columns of
+//   16 rows at a time, D batches ahead, which is what bounds them (2 MB a step for n = 256).
+// Up to n = 128 two sets of waves share a step: the first gate (whose product with the state the last product waits
+// for) is the second set's.
+// Measured alone, per snapshot: n = 64 1.4 us forward and 1.2 back (8 and 10 us as two launches per snapshot of 16 x 16
+// tiles, K split over four waves, with the gaps between them), n = 128 4.1 and 5.2, n = 256 17.7 and 21.4 (20 and 31).
 typedef double doublex4 __attribute__((ext_vector_type(4)));
-
-struct EvProd { const double* A; const double* B; int ta, tb; };  // ta: A stored [K][M]; tb: B stored [N][K]
-enum { EPI_ZR = 1, EPI_OUT = 2, EPI_BWD2 = 3, EPI_STEP = 4 };
-struct EvJob {
-  EvProd p[3];
-  int np;
-  double* C;           // STEP, jobs after the first: C += sum
-  // operands of the epilogues (see k_ev_mm)
-  const double* bias;  // ZR, OUT: gate bias
-  const double* W;     // ZR, OUT, BWD2: previous weights
-  const double* z;     // OUT: update gate      BWD2: reset gate r
-  double* o0;          // ZR: gate out          OUT: Wc      BWD2: dAr     STEP: running gradient G
-  double* o1;          // ZR(r job): Rg*W       OUT: W_t     BWD2: dWp (+=)   STEP: dWp (read)
-  float* o2;           // OUT: W_t in fp32 (for the dense kernels)
-  double* o3;          // BWD2: gradient of B_r (+=)
-  int write_rw;        // ZR: this is the r job
-};
-
-// First elementwise half of a backward step, from G = dL/dW_t without the direct part.
-struct EvBack {
-  const float* dWd;              // direct gradient of W_t
-  const double *z, *r, *c, *Wp;  // gates of step t, weights before it
-  double *dWp, *dAh, *dAz, *rw;
-  double *gBh, *gBz;
-};
-struct EvJobs { EvJob j[5]; EvBack back; };   // back: of the step that follows, dWd = NULL after the last one
+typedef double doublex2 __attribute__((ext_vector_type(2)));
 
 __device__ __forceinline__ double sigmoidd(double x) { return 1.0 / (1.0 + exp(-x)); }
 
-__device__ __forceinline__ void ev_back(const EvBack& b, double g, int64_t e) {
-  g += (double)b.dWd[e];
-  const double zz = b.z[e], cc = b.c[e], wp = b.Wp[e];
-  const double dz = g * (cc - wp), dc = g * zz;
-  b.dWp[e] = g * (1.0 - zz);
-  const double ah = dc * (1.0 - cc * cc), azv = dz * zz * (1.0 - zz);
-  b.dAh[e] = ah; b.dAz[e] = azv;
-  b.rw[e] = b.r[e] * wp;
-  b.gBh[e] += ah; b.gBz[e] += azv;
+struct EvWalkArgs {
+  int32_t T;
+  const float* P[EV_NPAR];
+  const doublex2* packed;          // streamed matrices (ev_packed_index); unused where they are resident
+  double *Wt, *Zg, *Rg, *Wc;       // Wt[0] = W_init, Wt[t + 1] = W_t
+  float* Wt_f32;
+  const float* dWd;                // back: direct gradient of every W_t
+  double *Ah, *Az, *Ar;            // back: gradients of the gates' arguments
+  float *gW, *gBz, *gBr, *gBh;     // back: gradients of W_init and of the biases
+};
+
+// Matrix m of a step at [row][k].  Forward: U_r + V_r, U_z + V_z, U_h, V_h; back: V_h, U_z + V_z, U_h, U_r + V_r, transposed.
+// (The input of the recurrence is its state, so U and V of a gate multiply the same matrix.)
+template <bool BACK>
+__device__ __forceinline__ double ev_weight(const float* const (&P)[EV_NPAR], int m, int n, int row, int k) {
+  const int e = BACK ? k * n + row : row * n + k;
+  switch (BACK && m != 1 && m != 2 ? 3 - m : m) {
+    case 0: return (double)P[EV_UR][e] + (double)P[EV_VR][e];
+    case 1: return (double)P[EV_UZ][e] + (double)P[EV_VZ][e];
+    case 2: return (double)P[EV_UH][e];
+    default: return (double)P[EV_VH][e];
+  }
 }
 
-// KS: k-steps of 4 that a wave takes of a product (n = 16 KS)
-template <int EPI, int KS>
-__global__ __launch_bounds__(256) void k_ev_mm(EvJobs jobs) {
-  constexpr int n = 16 * KS;
-  __shared__ double part[4][64][4];
-  const EvJob& J = jobs.j[blockIdx.z];
+// A batch is 32 columns of a wave's 16 rows: pair q of lane l holds row groups 2 (q % 2), + 1 of stretch 2 batch + q / 2.
+struct EvElement { int row, k; };
+__device__ __forceinline__ EvElement ev_element(int wave, int batch, int q, int half, int lane) {
+  return {16 * wave + 4 * (2 * (q & 1) + half) + (lane & 3), 16 * (2 * batch + (q >> 1)) + (lane & 12) + (lane >> 4)};
+}
+
+struct EvPackArgs { const float* P[EV_NPAR]; doublex2* packed; int32_t n; };
+template <bool BACK>
+__global__ __launch_bounds__(256) void k_ev_pack(EvPackArgs a) {
+  const int nw = a.n / 16, nb = nw / 2;
+  const int idx = blockIdx.x * blockDim.x + threadIdx.x;      // ((m * nw + wave) * nb + batch) * 256 + q * 64 + lane
+  if (idx >= 4 * nw * nb * 256) return;
+  const int lane = idx & 63, q = (idx >> 6) & 3;
+  int r = idx >> 8;
+  const int batch = r % nb; r /= nb;
+  const int wave = r % nw, m = r / nw;
+  const EvElement x = ev_element(wave, batch, q, 0, lane), y = ev_element(wave, batch, q, 1, lane);
+  doublex2 v;
+  v.x = ev_weight<BACK>(a.P, m, a.n, x.row, x.k);
+  v.y = ev_weight<BACK>(a.P, m, a.n, y.row, y.k);
+  a.packed[idx] = v;
+}
+
+template <int CTRL>
+__device__ __forceinline__ double move_lanes(double x) {
+  const uint64_t u = __builtin_bit_cast(uint64_t, x);
+  const int lo = __builtin_amdgcn_update_dpp(0, (int)(uint32_t)u, CTRL, 0xf, 0xf, true);
+  const int hi = __builtin_amdgcn_update_dpp(0, (int)(uint32_t)(u >> 32), CTRL, 0xf, 0xf, true);
+  return __builtin_bit_cast(double, (uint64_t)(uint32_t)hi << 32 | (uint32_t)lo);
+}
+// sum over the four blocks of the accumulator that a lane's own block stands for
+__device__ __forceinline__ double add_blocks(const double (&acc)[4], int lane) {
+  const bool b1 = lane & 8, b0 = lane & 4;
+  const double k0 = (b1 ? acc[2] : acc[0]) + move_lanes<0x128>(b1 ? acc[0] : acc[2]);    // lane ^ 8: rotation by 8 of 16
+  const double k1 = (b1 ? acc[3] : acc[1]) + move_lanes<0x128>(b1 ? acc[1] : acc[3]);
+  return (b0 ? k1 : k0) + move_lanes<0x1b>(move_lanes<0x141>(b0 ? k0 : k1));             // lane ^ 4: ^ 7, then ^ 3
+}
+
+// One role's matrices, in the order of their use: resident in registers, or streamed through a ring of D batches.
+template <int NW, int FIRST, int NM, bool RESIDENT, bool BACK>
+struct EvMatrices {
+  static constexpr int NB = NW / 2;
+  static constexpr int D = RESIDENT ? NM * NB : (NM * NB) % 4 == 0 ? 4 : 3;
+  static_assert((NM * NB) % D == 0, "the ring comes round with the step");
+  doublex2 w[D][4];
+  __amdgpu_buffer_rsrc_t rsrc;     // streamed: the place of a batch is a scalar, the lane's part of it a vector offset
+  int first, lane16;
+  __device__ __forceinline__ void fetch(int id) {
+    const int at = first + ((id / NB) * NW * NB + id % NB) * 4096;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) w[id % D][q] = __builtin_bit_cast(doublex2, __builtin_amdgcn_raw_buffer_load_b128(rsrc, lane16, at + q * 1024, 0));
+  }
+  __device__ __forceinline__ void start(const EvWalkArgs& a, int wave, int lane) {
+    if constexpr (RESIDENT) {
+#pragma unroll
+      for (int id = 0; id < D; ++id)
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          const EvElement x = ev_element(wave, id % NB, q, 0, lane), y = ev_element(wave, id % NB, q, 1, lane);
+          w[id][q].x = ev_weight<BACK>(a.P, FIRST + id / NB, 16 * NW, x.row, x.k);
+          w[id][q].y = ev_weight<BACK>(a.P, FIRST + id / NB, 16 * NW, y.row, y.k);
+        }
+    } else {
+      rsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<doublex2*>(a.packed), 0, 4 * NW * NB * 4096, 0x00020000);
+      first = (FIRST * NW + wave) * NB * 4096;
+      lane16 = lane * 16;
+#pragma unroll
+      for (int id = 0; id < D; ++id) fetch(id);
+    }
+  }
+  // acc += matrix m of this role's x the state in LDS
+  __device__ __forceinline__ void product(int m, const double* state, double (&acc)[4]) {
+#pragma unroll
+    for (int b = 0; b < NB; ++b) {
+      const int id = m * NB + b;
+#pragma unroll
+      for (int c = 0; c < 2; ++c) {
+        const double s = state[(2 * b + c) * 64];
+        acc[0] = __builtin_amdgcn_mfma_f64_4x4x4f64(w[id % D][2 * c].x, s, acc[0], 0, 0, 0);
+        acc[1] = __builtin_amdgcn_mfma_f64_4x4x4f64(w[id % D][2 * c].y, s, acc[1], 0, 0, 0);
+        acc[2] = __builtin_amdgcn_mfma_f64_4x4x4f64(w[id % D][2 * c + 1].x, s, acc[2], 0, 0, 0);
+        acc[3] = __builtin_amdgcn_mfma_f64_4x4x4f64(w[id % D][2 * c + 1].y, s, acc[3], 0, 0, 0);
+      }
+      if constexpr (!RESIDENT) {
+        fetch((id + D) % (NM * NB));
+        __builtin_amdgcn_sched_barrier(0);    // else all of the state is read ahead, and the registers spill
+      }
+    }
+  }
+};
+
+// What the two sets of waves do, and in which order, is written once: ONE set does both, the first one FIRST..
+template <int NW, int ROLE, bool BACK>   // ROLE 0: one set of waves does it all; 1: the first gate; 2: the rest
+__device__ __forceinline__ void ev_walk(const EvWalkArgs& a, int wave, double* lds) {
+  constexpr int n = 16 * NW;
+  constexpr bool kGate = ROLE != 2, kRest = ROLE != 1;
+  constexpr bool kResident = ROLE == 1 || NW <= 4;
+  const int lane = threadIdx.x & 63;
+  const int e = (16 * wave + (lane & 12) + (lane >> 4)) * n + 4 * blockIdx.x + (lane & 3);
+  constexpr int64_t nn = (int64_t)n * n;
+  // states that all waves read: S (and S2 back), Q between the step's two barriers, P back to the other set
+  double *S = lds, *S2 = lds + n * 4, *Q = lds + 2 * n * 4, *P = lds + 3 * n * 4;
+  const int own = wave * 64 + lane;
+  EvMatrices<NW, ROLE == 2 ? 1 : 0, ROLE == 0 ? 4 : ROLE == 1 ? 1 : 3, kResident, BACK> mat;
+  constexpr int m1 = ROLE == 0 ? 1 : 0;       // the rest's first matrix
+  mat.start(a, wave, lane);
+  if constexpr (!BACK) {
+    double W = (double)a.P[EV_W][e];
+    double bz = 0.0, br = 0.0, bh = 0.0;
+    if constexpr (kGate) br = (double)a.P[EV_BR][e];
+    if constexpr (kRest) {
+      bz = (double)a.P[EV_BZ][e]; bh = (double)a.P[EV_BH][e];
+      S[own] = W;
+      a.Wt[e] = W;
+    }
+    for (int t = 0; t < a.T; ++t) {
+      __syncthreads();
+      if constexpr (kGate) {
+        if (ROLE == 1) W = S[own];
+        double acc[4] = {0.0, 0.0, 0.0, 0.0};
+        mat.product(0, S + lane, acc);
+        const double r = sigmoidd(add_blocks(acc, lane) + br);
+        Q[own] = r * W;
+        a.Rg[t * nn + e] = r;
+      }
+      double z = 0.0, acc[4] = {0.0, 0.0, 0.0, 0.0};
+      if constexpr (kRest) {
+        double az[4] = {0.0, 0.0, 0.0, 0.0};
+        mat.product(m1, S + lane, az);
+        z = sigmoidd(add_blocks(az, lane) + bz);
+        mat.product(m1 + 1, S + lane, acc);
+      }
+      __syncthreads();
+      if constexpr (kRest) {
+        mat.product(m1 + 2, Q + lane, acc);
+        const double c = tanh(add_blocks(acc, lane) + bh);
+        W = (1.0 - z) * W + z * c;
+        S[own] = W;
+        a.Zg[t * nn + e] = z;
+        a.Wc[t * nn + e] = c;
+        a.Wt[(t + 1) * nn + e] = W;
+        a.Wt_f32[t * nn + e] = (float)W;
+      }
+    }
+  } else {
+    // operands of a step's elementwise part, requested a step ahead
+    double z = 0.0, c = 0.0, wp = 0.0, r = 0.0;
+    float d = 0.f;
+    auto request = [&](int t) {
+      wp = a.Wt[t * nn + e];
+      if constexpr (kGate) r = a.Rg[t * nn + e];
+      if constexpr (kRest) { z = a.Zg[t * nn + e]; c = a.Wc[t * nn + e]; d = a.dWd[t * nn + e]; }
+    };
+    double G = 0.0, bz = 0.0, br = 0.0, bh = 0.0;
+    request(a.T - 1);
+    for (int t = a.T - 1; t >= 0; --t) {
+      double direct = 0.0;                    // of dL/dW_{t-1}: the part that no matrix multiplies
+      if constexpr (kRest) {
+        const double g = G + (double)d;
+        const double dz = g * (c - wp), dc = g * z;
+        const double ah = dc * (1.0 - c * c), az = dz * z * (1.0 - z);
+        direct = g * (1.0 - z);
+        S[own] = ah; S2[own] = az;
+        bh += ah; bz += az;
+        a.Ah[t * nn + e] = ah;
+        a.Az[t * nn + e] = az;
+      }
+      const double wp_t = wp, r_t = r;
+      if (t > 0) request(t - 1);
+      __syncthreads();
+      if constexpr (kGate) {
+        double acc[4] = {0.0, 0.0, 0.0, 0.0};
+        mat.product(0, S + lane, acc);
+        const double s = add_blocks(acc, lane);      // gradient of R * W
+        const double ar = s * wp_t * r_t * (1.0 - r_t);
+        Q[own] = ar;
+        if constexpr (kRest) direct += s * r_t;
+        else P[own] = s * r_t;
+        br += ar;
+        a.Ar[t * nn + e] = ar;
+      }
+      double acc[4] = {0.0, 0.0, 0.0, 0.0};
+      if constexpr (kRest) {
+        mat.product(m1, S2 + lane, acc);
+        mat.product(m1 + 1, S + lane, acc);
+      }
+      __syncthreads();
+      if constexpr (kRest) {
+        mat.product(m1 + 2, Q + lane, acc);
+        if constexpr (!kGate) direct += P[own];
+        G = direct + add_blocks(acc, lane);
+      }
+    }
+    if constexpr (kGate) a.gBr[e] = (float)br;
+    if constexpr (kRest) {
+      a.gW[e] = (float)G;
+      a.gBz[e] = (float)bz;
+      a.gBh[e] = (float)bh;
+    }
+  }
+}
+
+template <int NW, bool BACK>
+__global__ __launch_bounds__(64 * (NW <= 8 ? 2 * NW : NW)) void k_ev_walk(EvWalkArgs a) {
+  __shared__ double lds[4 * 16 * NW * 4];
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  if constexpr (NW <= 8) {
+    if (wave >= NW) ev_walk<NW, 1, BACK>(a, wave - NW, lds);
+    else ev_walk<NW, 2, BACK>(a, wave, lds);
+  } else {
+    ev_walk<NW, 0, BACK>(a, wave, lds);
+  }
+}
+
+// Parameter gradients, sums over snapshots and columns of W (the contraction):
+//   dU_h = sum Ah Wp^T   dV_h = sum Ah (R * Wp)^T   dU_z = dV_z = sum Az Wp^T   dU_r = dV_r = sum Ar Wp^T
+// A workgroup of 8 waves owns a TM x TM tile of one of them; its waves split the contraction sixteen columns at a time and
+// their partial tiles are added in wave order (reproducible).  TM = 32 halves what is read per product, TM = 16 gives a
+// small matrix more workgroups.  v_mfma_f64_16x16x4f64: lane l supplies A[l%16][l/16], B[l/16][l%16] and receives
+// D[4*v + l/16][l%16]; four consecutive columns of a lane are four instructions.
+struct EvGradArgs { int32_t T, n; const double *Wt, *Rg, *Ah, *Az, *Ar; float* G[EV_NPAR]; };
+
+template <int TM>
+__global__ __launch_bounds__(512) void k_ev_grads(EvGradArgs a) {
+  constexpr int NT = TM / 16;
+  __shared__ double part[8][TM * TM];
+  const int n = a.n, job = blockIdx.z;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, l16 = lane & 15, kq = lane >> 4;
-  const int n0 = blockIdx.x * 16, m0 = blockIdx.y * 16;
-  doublex4 acc = {0.0, 0.0, 0.0, 0.0};
-  double a[2][KS], b[2][KS];
-  auto request = [&](int p) {
-    const int ak = J.p[p].ta ? n : 1, am = J.p[p].ta ? 1 : n;   // strides of A along k and m
-    const int bk = J.p[p].tb ? 1 : n, bn = J.p[p].tb ? n : 1;
-    const int k0 = wave * 4 * KS + kq;
-    const double* A = J.p[p].A + (m0 + l16) * am + k0 * ak;
-    const double* B = J.p[p].B + (n0 + l16) * bn + k0 * bk;
+  const int m0 = blockIdx.y * TM, n0 = blockIdx.x * TM;
+  const double* A = job < 2 ? a.Ah : job == 2 ? a.Az : a.Ar;
+  const int per_t = n / 16, units = a.T * per_t;
+  const int64_t nn = (int64_t)n * n;
+  doublex4 acc[NT][NT];
 #pragma unroll
-    for (int k = 0; k < KS; ++k) { a[p & 1][k] = A[4 * k * ak]; b[p & 1][k] = B[4 * k * bk]; }
+  for (int i = 0; i < NT; ++i)
+#pragma unroll
+    for (int j = 0; j < NT; ++j) acc[i][j] = (doublex4)(0.0);
+  doublex2 x[NT][2], y[NT][2], r[NT][2];
+  auto request = [&](int u) {
+    const int t = u / per_t, s0 = (u - t * per_t) * 16 + 4 * kq;
+#pragma unroll
+    for (int i = 0; i < NT; ++i)
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        const int64_t ea = t * nn + (m0 + 16 * i + l16) * n + s0 + 2 * h, eb = t * nn + (n0 + 16 * i + l16) * n + s0 + 2 * h;
+        x[i][h] = *reinterpret_cast<const doublex2*>(A + ea);
+        y[i][h] = *reinterpret_cast<const doublex2*>(a.Wt + eb);
+        if (job == 1) r[i][h] = *reinterpret_cast<const doublex2*>(a.Rg + eb);
+      }
   };
-  request(0);
+  if (wave < units) request(wave);
+  for (int u = wave; u < units; u += 8) {
+    doublex2 p[NT][2], q[NT][2];
 #pragma unroll
-  for (int p = 0; p < 3; ++p) {
-    if (p >= J.np) break;
-    if (p + 1 < 3 && p + 1 < J.np) request(p + 1);
+    for (int i = 0; i < NT; ++i)
 #pragma unroll
-    for (int k = 0; k < KS; ++k) acc = __builtin_amdgcn_mfma_f64_16x16x4f64(a[p & 1][k], b[p & 1][k], acc, 0, 0, 0);
+      for (int h = 0; h < 2; ++h) { p[i][h] = x[i][h]; q[i][h] = job == 1 ? y[i][h] * r[i][h] : y[i][h]; }
+    if (u + 8 < units) request(u + 8);
+#pragma unroll
+    for (int h = 0; h < 2; ++h)
+#pragma unroll
+      for (int k = 0; k < 2; ++k)
+#pragma unroll
+        for (int i = 0; i < NT; ++i)
+#pragma unroll
+          for (int j = 0; j < NT; ++j) acc[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(p[i][h][k], q[j][h][k], acc[i][j], 0, 0, 0);
   }
 #pragma unroll
-  for (int v = 0; v < 4; ++v) part[wave][lane][v] = acc[v];
+  for (int i = 0; i < NT; ++i)
+#pragma unroll
+    for (int j = 0; j < NT; ++j)
+#pragma unroll
+      for (int v = 0; v < 4; ++v) part[wave][(16 * i + 4 * v + kq) * TM + 16 * j + l16] = acc[i][j][v];
   __syncthreads();
-  const int v = wave;
-  const double sum = ((part[0][lane][v] + part[1][lane][v]) + part[2][lane][v]) + part[3][lane][v];
-  const int64_t e = (int64_t)(m0 + 4 * v + kq) * n + n0 + l16;
-  if (EPI == EPI_ZR) {
-    const double g = sigmoidd(sum + J.bias[e]);
-    J.o0[e] = g;
-    if (J.write_rw) J.o1[e] = g * J.W[e];
-  } else if (EPI == EPI_OUT) {
-    const double c = tanh(sum + J.bias[e]);
-    const double zz = J.z[e];
-    const double wn = (1.0 - zz) * J.W[e] + zz * c;
-    J.o0[e] = c;
-    J.o1[e] = wn;
-    J.o2[e] = (float)wn;
-  } else if (EPI == EPI_BWD2) {   // sum = Vh^T dAh = gradient of (Rg * W)
-    const double rr = J.z[e];
-    const double dar = sum * J.W[e] * rr * (1.0 - rr);
-    J.o0[e] = dar;
-    J.o1[e] += sum * rr;
-    J.o3[e] += dar;
-  } else if (blockIdx.z > 0) {    // a parameter gradient
-    J.C[e] += sum;
-  } else {                        // G_{t-1} = dWp + sum, and the first half of the step before
-    const double g = J.o1[e] + sum;
-    J.o0[e] = g;
-    if (jobs.back.dWd) ev_back(jobs.back, g, e);
+  float* G = a.G[job == 0 ? EV_UH : job == 1 ? EV_VH : job == 2 ? EV_UZ : EV_UR];
+  float* G2 = job < 2 ? nullptr : a.G[job == 2 ? EV_VZ : EV_VR];    // the input is the state: U and V get one gradient
+  for (int i = tid; i < TM * TM; i += 512) {
+    double sum = part[0][i];
+#pragma unroll
+    for (int w = 1; w < 8; ++w) sum += part[w][i];
+    const int64_t e = (int64_t)(m0 + i / TM) * n + n0 + i % TM;
+    G[e] = (float)sum;
+    if (G2) G2[e] = (float)sum;
   }
-}
-
-// the first half of the last snapshot's step (G = 0)
-__global__ void k_ev_back(EvBack b, int64_t n) {
-  const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (e < n) ev_back(b, 0.0, e);
-}
-
-// The parameters widened to double, and the sums of those that multiply the same matrix (the input of the
-// recurrence is its state): U_z + V_z, U_r + V_r.
-struct EvParams { const float* P[EV_NPAR]; double* D[EV_NPAR]; double *zsum, *rsum; };
-__global__ void k_ev_widen(EvParams p, int64_t n) {
-  const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (e >= n) return;
-  for (int k = 0; k < EV_NPAR; ++k) p.D[k][e] = (double)p.P[k][e];
-  p.zsum[e] = (double)p.P[EV_UZ][e] + (double)p.P[EV_VZ][e];
-  p.rsum[e] = (double)p.P[EV_UR][e] + (double)p.P[EV_VR][e];
-}
-struct EvGrads { float* G[EV_NPAR]; double* D[EV_NPAR]; };
-__global__ void k_ev_clear(EvGrads p, int64_t n) {
-  const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (e >= n) return;
-  for (int k = 0; k < EV_NPAR; ++k) p.D[k][e] = 0.0;
-}
-// the input of the GRU is the state itself, so Uz, Vz (and Ur, Vr) receive identical gradients
-__global__ void k_ev_round(EvGrads p, int64_t n) {
-  const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (e >= n) return;
-  for (int k = 0; k < EV_NPAR; ++k) p.G[k][e] = (float)p.D[k == EV_VZ ? EV_UZ : k == EV_VR ? EV_UR : k][e];
 }
 
 // W_t [F][S] for all t -> fragment order of W_t^T [S][F] (the dense kernels take (out, in) weights)
@@ -376,18 +568,32 @@ __global__ void k_ev_row_index(const ChunkInfo* chunks, int64_t N, int64_t* idx)
   idx[ch.row_off0 + (int64_t)s * ch.nv + v] = (int64_t)(ch.t_lo + s) * N + ch.v_lo + v;
 }
 
-template <int EPI>
-void launch_mm(const EvJobs& jobs, int n_jobs, int n, hipStream_t st) {
-  const dim3 grid(n / 16, n / 16, n_jobs);
+template <bool BACK>
+void launch_walk(const EvolveWs& ws, hipStream_t st) {
+  const int n = ws.F;
+  EvWalkArgs a{};
+  a.T = ws.T;
+  for (int k = 0; k < EV_NPAR; ++k) a.P[k] = ws.P[k];
+  a.packed = reinterpret_cast<const doublex2*>(ws.walk_packed);
+  a.Wt = ws.Wt; a.Zg = ws.Zg; a.Rg = ws.Rg; a.Wc = ws.Wc; a.Wt_f32 = ws.Wt_f32; a.dWd = ws.dWd;
+  a.Ah = ws.Ah; a.Az = ws.Az; a.Ar = ws.Ar;
+  a.gW = ws.G[EV_W]; a.gBz = ws.G[EV_BZ]; a.gBr = ws.G[EV_BR]; a.gBh = ws.G[EV_BH];
+  if (n > 64) {
+    EvPackArgs p{};
+    for (int k = 0; k < EV_NPAR; ++k) p.P[k] = ws.P[k];
+    p.packed = reinterpret_cast<doublex2*>(ws.walk_packed);
+    p.n = n;
+    hipLaunchKernelGGL((k_ev_pack<BACK>), blocks_for(evolve_walk_elems(ws) / 2), 256, 0, st, p);
+  }
   switch (n / 32) {
-    case 1: hipLaunchKernelGGL((k_ev_mm<EPI, 2>), grid, 256, 0, st, jobs); break;
-    case 2: hipLaunchKernelGGL((k_ev_mm<EPI, 4>), grid, 256, 0, st, jobs); break;
-    case 3: hipLaunchKernelGGL((k_ev_mm<EPI, 6>), grid, 256, 0, st, jobs); break;
-    case 4: hipLaunchKernelGGL((k_ev_mm<EPI, 8>), grid, 256, 0, st, jobs); break;
-    case 5: hipLaunchKernelGGL((k_ev_mm<EPI, 10>), grid, 256, 0, st, jobs); break;
-    case 6: hipLaunchKernelGGL((k_ev_mm<EPI, 12>), grid, 256, 0, st, jobs); break;
-    case 7: hipLaunchKernelGGL((k_ev_mm<EPI, 14>), grid, 256, 0, st, jobs); break;
-    case 8: hipLaunchKernelGGL((k_ev_mm<EPI, 16>), grid, 256, 0, st, jobs); break;
+    case 1: hipLaunchKernelGGL((k_ev_walk<2, BACK>), n / 4, 256, 0, st, a); break;
+    case 2: hipLaunchKernelGGL((k_ev_walk<4, BACK>), n / 4, 512, 0, st, a); break;
+    case 3: hipLaunchKernelGGL((k_ev_walk<6, BACK>), n / 4, 768, 0, st, a); break;
+    case 4: hipLaunchKernelGGL((k_ev_walk<8, BACK>), n / 4, 1024, 0, st, a); break;
+    case 5: hipLaunchKernelGGL((k_ev_walk<10, BACK>), n / 4, 640, 0, st, a); break;
+    case 6: hipLaunchKernelGGL((k_ev_walk<12, BACK>), n / 4, 768, 0, st, a); break;
+    case 7: hipLaunchKernelGGL((k_ev_walk<14, BACK>), n / 4, 896, 0, st, a); break;
+    case 8: hipLaunchKernelGGL((k_ev_walk<16, BACK>), n / 4, 1024, 0, st, a); break;
   }
 }
 
@@ -403,29 +609,10 @@ int64_t evolve_partial_elems(const EvolveWs& ws) { return (int64_t)ws.T * ws.spl
 int64_t evolve_loss_partial_elems(const EvolveWs& ws) { return (int64_t)ws.T * ws.split_dw; }
 
 // Evolve W_t for t = 0..T-1 (ws.Wt, gates ws.Zg/Rg/Wc, all double) and pack every W_t, rounded
-// to fp32, for the dense kernels.  Two launches per snapshot.
+// to fp32, for the dense kernels.
 void evolve_forward_weights(const EvolveWs& ws, hipStream_t st) {
-  const int n = ws.F;
-  const int64_t nn = (int64_t)n * n;
-  EvParams par{};
-  for (int k = 0; k < EV_NPAR; ++k) { par.P[k] = ws.P[k]; par.D[k] = ws.Pd[k]; }
-  par.zsum = ws.zsum; par.rsum = ws.rsum;
-  hipLaunchKernelGGL(k_ev_widen, blocks_for(nn), 256, 0, st, par, nn);
-  for (int t = 0; t < ws.T; ++t) {
-    const double* W = t ? ws.Wt + (t - 1) * nn : ws.Pd[EV_W];
-    double *z = ws.Zg + t * nn, *r = ws.Rg + t * nn, *c = ws.Wc + t * nn, *Wn = ws.Wt + t * nn;
-    EvJobs zr{};
-    zr.j[0].p[0] = {ws.zsum, W, 0, 0}; zr.j[0].np = 1;
-    zr.j[0].bias = ws.Pd[EV_BZ]; zr.j[0].W = W; zr.j[0].o0 = z; zr.j[0].write_rw = 0;
-    zr.j[1].p[0] = {ws.rsum, W, 0, 0}; zr.j[1].np = 1;
-    zr.j[1].bias = ws.Pd[EV_BR]; zr.j[1].W = W; zr.j[1].o0 = r; zr.j[1].o1 = ws.tmp[1]; zr.j[1].write_rw = 1;
-    launch_mm<EPI_ZR>(zr, 2, n, st);
-    EvJobs out{};
-    out.j[0].p[0] = {ws.Pd[EV_UH], W, 0, 0}; out.j[0].p[1] = {ws.Pd[EV_VH], ws.tmp[1], 0, 0}; out.j[0].np = 2;
-    out.j[0].bias = ws.Pd[EV_BH]; out.j[0].W = W; out.j[0].z = z; out.j[0].o0 = c; out.j[0].o1 = Wn;
-    out.j[0].o2 = ws.Wt_f32 + t * nn;
-    launch_mm<EPI_OUT>(out, 1, n, st);
-  }
+  const int64_t nn = (int64_t)ws.F * ws.S;
+  launch_walk<false>(ws, st);
   if (ws.split) {
     launch_pack_split(ws.Wt_f32, nn, 1, ws.S, ws.S, ws.F, ws.T, ws.Wt_packed, st);
     return;
@@ -488,50 +675,15 @@ bool evolve_backward_dw(const EvolveWs& ws, const EvolveBwdIn& in, bool keep_dp,
   return true;
 }
 
-// Back-propagation through time over the weight recurrence (double precision, two launches per
-// snapshot); the gradients of the ten parameters end up in ws.G[k] as fp32.
+// Back-propagation through time over the weight recurrence (double precision); the gradients of the ten
+// parameters end up in ws.G[k] as fp32.
 void evolve_backward_bptt(const EvolveWs& ws, hipStream_t st) {
-  const int n = ws.F;
-  const int64_t nn = (int64_t)n * n;
-  const unsigned nb = blocks_for(nn);
-  EvGrads gr{};
-  for (int k = 0; k < EV_NPAR; ++k) { gr.G[k] = ws.G[k]; gr.D[k] = ws.Gd[k]; }
-  hipLaunchKernelGGL(k_ev_clear, nb, 256, 0, st, gr, nn);
-  double* Gt = ws.Gd[EV_W];  // running dL/dW_t; ends as the gradient of W_init
-  double *dWp = ws.tmp[0], *dAr = ws.tmp[2];
-  // A step's launch leaves the first half of the step before it in the other one of two sets: its tiles still read
-  // this step's.
-  auto back = [&](int t) {
-    EvBack b{};
-    if (t < 0) return b;
-    double* const* set = t % 2 ? ws.back1 : ws.back0;
-    b.dWd = ws.dWd + t * nn;
-    b.z = ws.Zg + t * nn; b.r = ws.Rg + t * nn; b.c = ws.Wc + t * nn;
-    b.Wp = t ? ws.Wt + (t - 1) * nn : ws.Pd[EV_W];
-    b.dWp = dWp; b.dAh = set[0]; b.dAz = set[1]; b.rw = set[2];
-    b.gBh = ws.Gd[EV_BH]; b.gBz = ws.Gd[EV_BZ];
-    return b;
-  };
-  hipLaunchKernelGGL(k_ev_back, nb, 256, 0, st, back(ws.T - 1), nn);
-  for (int t = ws.T - 1; t >= 0; --t) {
-    const EvBack cur = back(t);
-    EvJobs b2{};   // Vh^T dAh -> dAr, dWp += ., dB_r += .
-    b2.j[0].p[0] = {ws.Pd[EV_VH], cur.dAh, 1, 0}; b2.j[0].np = 1;
-    b2.j[0].W = cur.Wp; b2.j[0].z = cur.r; b2.j[0].o0 = dAr; b2.j[0].o1 = dWp; b2.j[0].o3 = ws.Gd[EV_BR];
-    launch_mm<EPI_BWD2>(b2, 1, n, st);
-    EvJobs g{};    // G_{t-1} = dWp + Uh^T dAh + (Uz + Vz)^T dAz + (Ur + Vr)^T dAr
-    g.j[0].p[0] = {ws.Pd[EV_UH], cur.dAh, 1, 0}; g.j[0].p[1] = {ws.zsum, cur.dAz, 1, 0}; g.j[0].p[2] = {ws.rsum, dAr, 1, 0};
-    g.j[0].np = 3;
-    g.j[0].o0 = Gt; g.j[0].o1 = dWp;
-    // dUh += dAh Wp^T, dVh += dAh (Rg*Wp)^T, dUz += dAz Wp^T, dUr += dAr Wp^T
-    g.j[1].p[0] = {cur.dAh, cur.Wp, 0, 1}; g.j[1].np = 1; g.j[1].C = ws.Gd[EV_UH];
-    g.j[2].p[0] = {cur.dAh, cur.rw, 0, 1}; g.j[2].np = 1; g.j[2].C = ws.Gd[EV_VH];
-    g.j[3].p[0] = {cur.dAz, cur.Wp, 0, 1}; g.j[3].np = 1; g.j[3].C = ws.Gd[EV_UZ];
-    g.j[4].p[0] = {dAr, cur.Wp, 0, 1}; g.j[4].np = 1; g.j[4].C = ws.Gd[EV_UR];
-    g.back = back(t - 1);
-    launch_mm<EPI_STEP>(g, 5, n, st);
-  }
-  hipLaunchKernelGGL(k_ev_round, nb, 256, 0, st, gr, nn);
+  launch_walk<true>(ws, st);
+  EvGradArgs g{};
+  g.T = ws.T; g.n = ws.F; g.Wt = ws.Wt; g.Rg = ws.Rg; g.Ah = ws.Ah; g.Az = ws.Az; g.Ar = ws.Ar;
+  for (int k = 0; k < EV_NPAR; ++k) g.G[k] = ws.G[k];
+  if (ws.F <= 128) hipLaunchKernelGGL((k_ev_grads<16>), dim3(ws.F / 16, ws.F / 16, 4), 512, 0, st, g);
+  else hipLaunchKernelGGL((k_ev_grads<32>), dim3(ws.F / 32, ws.F / 32, 4), 512, 0, st, g);
 }
 
 }  // namespace dgc

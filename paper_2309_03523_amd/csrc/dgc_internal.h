@@ -234,14 +234,12 @@ struct EvolveWs {
   bool split;                // the transforms run the split dense kernel
   const float* P[EV_NPAR];   // parameters (device, fp32): W_init, Uz, Vz, Bz, Ur, Vr, Br, Uh, Vh, Bh
   float* G[EV_NPAR];         // their gradients (fp32, what the caller reads)
-  double* Pd[EV_NPAR];       // the parameters widened to double for the weight recurrence
-  double* Gd[EV_NPAR];       // gradient accumulators of the back-propagation through time
-  double *Wt, *Zg, *Rg, *Wc; // [T][F][S]: evolved weights and the gates that produced them
+  double* walk_packed;       // matrices of the weight recurrence that are read at every step (evolve_walk_elems)
+  double* Wt;                // [T+1][F][S]: W_init, then the evolved weights
+  double *Zg, *Rg, *Wc;      // [T][F][S]: the gates that produced them
+  double *Ah, *Az, *Ar;      // [T][F][S]: gradients of the gates' arguments
   float* Wt_f32;             // [T][F][S]: W_t rounded to fp32
   float4* Wt_packed;         // every W_t^T (fp32) in MFMA fragment order
-  double* tmp[3];            // [F][S] scratch
-  double *zsum, *rsum;       // U_z + V_z, U_r + V_r
-  double *back0[3], *back1[3];   // dA_h, dA_z, Rg * W of even and odd steps of the back-propagation
   float* dWd;                // [T][F][S] direct gradient of each W_t
   int32_t split_dw;          // workgroups per snapshot of the weight-gradient kernel
   float* partial;            // [T][split_dw][F][S]
@@ -265,6 +263,7 @@ struct EvolveBwdIn {
 inline int64_t evolve_packed_bytes(const EvolveWs& ws, bool split) {
   return split ? split_weight_bytes(ws.S, ws.F) : (int64_t)sizeof(float) * packed_weight_elems(ws.S, ws.F);
 }
+inline int64_t evolve_walk_elems(const EvolveWs& ws) { return 4 * (int64_t)ws.F * ws.S; }
 int32_t evolve_dw_split(int32_t T, int32_t F, int64_t most_tiles);   // most_tiles: of a snapshot
 int64_t evolve_partial_elems(const EvolveWs& ws);
 int64_t evolve_loss_partial_elems(const EvolveWs& ws);
