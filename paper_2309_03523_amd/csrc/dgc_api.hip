@@ -39,7 +39,7 @@ struct dgc_layer {
   int32_t n_chunks = 0;
   int64_t nseg = 0, total_rows = 0, total_nnz = 0, total_halo = 0, total_state_rows = 0;
   int64_t n_short = 0, n_long = 0, n_tiles = 0;
-  int32_t rows_per_group = 16, long_nnz = 1024, part_nnz = 512;
+  int32_t rows_per_group = 16, long_nnz = 1024, part_nnz = 512, longest_row = 0;
   std::vector<dgc_chunk_t> chunks;
   std::vector<Segment> segs_host;
   std::vector<void*> allocs;          // everything hipMalloc'ed, freed in destroy
@@ -485,13 +485,14 @@ dgc_status_t build_layer(dgc_layer* L, const dgc_graph_t* graph, hipStream_t st)
   const GraphDev g = L->graph_dev();
 
   int32_t* d_flags = nullptr;
-  DGC_HIP_TRY(dev_alloc(L, &d_flags, 4));
-  DGC_HIP_TRY(hipMemsetAsync(d_flags, 0, sizeof(int32_t) * 4, st));
-  launch_validate_rowptr(g, d_flags, st);
-  int32_t flags[4] = {0, 0, 0, 0};
+  DGC_HIP_TRY(dev_alloc(L, &d_flags, 5));
+  DGC_HIP_TRY(hipMemsetAsync(d_flags, 0, sizeof(int32_t) * 5, st));
+  launch_validate_rowptr(g, d_flags, d_flags + 4, st);
+  int32_t flags[5] = {0, 0, 0, 0, 0};
   DGC_HIP_TRY(hipMemcpyAsync(flags, d_flags, sizeof(flags), hipMemcpyDeviceToHost, st));
   DGC_HIP_TRY(hipStreamSynchronize(st));
   if (flags[0]) return fail(DGC_ERR_BAD_GRAPH, "rowptr does not start at 0 or decreases");
+  L->longest_row = flags[4];
   if (d.validate_level >= 1) {
     launch_validate_graph(g, d_flags, st);
     DGC_HIP_TRY(hipMemcpyAsync(flags, d_flags, sizeof(flags), hipMemcpyDeviceToHost, st));
@@ -714,7 +715,7 @@ SpmmArgs spmm_args(dgc_layer* L, const float* fresh, int64_t ld_fresh, const flo
   a.halo = nullptr; a.ld_halo = 0; a.col_local = nullptr;
   a.col_signed = L->lab.built ? L->lab.col_signed : nullptr;
   a.F = F;
-  a.long_nnz = L->long_nnz; a.part_nnz = L->part_nnz;
+  a.long_nnz = L->long_nnz; a.part_nnz = L->part_nnz; a.longest_row = L->longest_row;
   a.partial = L->d_partial;
   a.M = M; a.ldm = ldm;
   a.row_map = nullptr;

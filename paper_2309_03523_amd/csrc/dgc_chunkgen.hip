@@ -387,7 +387,7 @@ extern "C" dgc_status_t dgc_chunk_generate(const dgc_graph_t* graph, int32_t w_s
   a.g = GraphDev{graph->T, graph->N, d_rp, d_ci};
   {  // the kernels index by the stored columns: check the graph contract first
     int32_t flags[4] = {0, 0, 0, 0};
-    launch_validate_rowptr(a.g, counters, st);
+    launch_validate_rowptr(a.g, counters, nullptr, st);
     CG_TRY(hipMemcpyAsync(flags, counters, sizeof(flags), hipMemcpyDeviceToHost, st));
     CG_TRY(hipStreamSynchronize(st));
     if (flags[0]) { release(); return bad(DGC_ERR_BAD_GRAPH, "chunk generate: rowptr does not start at 0 or decreases"); }

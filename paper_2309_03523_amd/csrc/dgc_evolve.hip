@@ -520,7 +520,14 @@ __global__ void k_dw_reduce(const float* partial, float* dWd, int32_t split, int
   if (e >= total) return;
   const int64_t t = e / n_per_t, i = e - t * n_per_t;
   double s = 0.0;
-  for (int k = 0; k < split; ++k) s += (double)partial[(t * split + k) * n_per_t + i];
+  constexpr int kAhead = 8;        // partial sums requested together (past the last: the last one, not added)
+  for (int k0 = 0; k0 < split; k0 += kAhead) {
+    float v[kAhead];
+#pragma unroll
+    for (int k = 0; k < kAhead; ++k) v[k] = partial[(t * split + min(k0 + k, split - 1)) * n_per_t + i];
+#pragma unroll
+    for (int k = 0; k < kAhead; ++k) s += k0 + k < split ? (double)v[k] : 0.0;
+  }
   dWd[e] = (float)s;
 }
 

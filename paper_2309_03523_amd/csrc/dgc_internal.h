@@ -84,7 +84,7 @@ void launch_segment_bounds(const GraphDev& g, Segment* segs, int64_t nseg, hipSt
 void launch_deg_inv_sqrt(const GraphDev& g, float* dinv, hipStream_t st);
 void launch_mark_halo(const GraphDev& g, const Segment* segs, int64_t nseg, int64_t total_nnz,
                       int64_t words_per_seg, uint32_t* bitmap, int32_t* flags /*[4]*/, hipStream_t st);
-void launch_validate_rowptr(const GraphDev& g, int32_t* flags /*[4]*/, hipStream_t st);
+void launch_validate_rowptr(const GraphDev& g, int32_t* flags /*[4]*/, int32_t* longest_row /*or nullptr; starts at 0*/, hipStream_t st);
 // exclusive scan of `n` int64 counts (in place); total written to *total_dev (device int64).
 // tmp must hold ceil(n/2048)+2 int64.
 void launch_exclusive_scan(int64_t* data, int64_t n, int64_t* tmp, int64_t* total_dev, hipStream_t st);
@@ -131,6 +131,7 @@ struct SpmmArgs {
   const int32_t* col_signed;              // generated chunks: stored columns marked j (fresh) / ~j (cache), or nullptr
   int32_t F;
   int32_t long_nnz, part_nnz;
+  int32_t longest_row;        // non-zeros of the longest stored row
   float* partial;             // [n_long][ldm] scratch for split rows
   float* M; int64_t ldm;      // [rows, ldm]; columns F..ldm-1 are written as zero
   const int64_t* row_map;     // nullptr, or [rows]: row of M that packed row r goes to (< 0: skip the row)

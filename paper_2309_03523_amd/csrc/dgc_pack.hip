@@ -62,12 +62,21 @@ __global__ void k_mark_halo(GraphDev g, const Segment* segs, int64_t nseg, int64
 }
 
 // rowptr starts at 0 and never decreases: with that, every row's range lies inside colidx.
-__global__ void k_validate_rowptr(GraphDev g, int32_t* flags) {
+__global__ void k_validate_rowptr(GraphDev g, int32_t* flags, int32_t* longest_row) {
   const int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (idx >= (int64_t)g.T * g.N) return;
-  const int64_t t = idx / g.N, i = idx - t * g.N;
-  const int64_t* rp = g.rowptr[t];
-  if ((i == 0 && rp[0] != 0) || rp[i + 1] < rp[i]) atomicOr(&flags[0], 1);
+  int64_t len = 0;
+  if (idx < (int64_t)g.T * g.N) {
+    const int64_t t = idx / g.N, i = idx - t * g.N;
+    const int64_t* rp = g.rowptr[t];
+    len = rp[i + 1] - rp[i];
+    if ((i == 0 && rp[0] != 0) || len < 0) atomicOr(&flags[0], 1);
+  }
+  if (!longest_row) return;
+  int longest = (int)(len < 0 ? 0 : len > INT32_MAX ? INT32_MAX : len);
+  for (int d = kWave / 2; d >= 1; d >>= 1) longest = max(longest, __shfl_xor(longest, d, kWave));
+  // one atomic a wave at most, and few of them once a long row has been seen
+  if ((threadIdx.x & (kWave - 1)) == 0 && longest > __hip_atomic_load(longest_row, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
+    atomicMax(longest_row, longest);
 }
 
 __global__ void k_popcount_words(const uint32_t* bitmap, int64_t n_words, int64_t* counts) {
@@ -268,9 +277,9 @@ void launch_mark_halo(const GraphDev& g, const Segment* segs, int64_t nseg, int6
                        words_per_seg, bitmap, flags);
 }
 
-void launch_validate_rowptr(const GraphDev& g, int32_t* flags, hipStream_t st) {
+void launch_validate_rowptr(const GraphDev& g, int32_t* flags, int32_t* longest_row, hipStream_t st) {
   const int64_t n = (int64_t)g.T * g.N;
-  if (n > 0) hipLaunchKernelGGL(k_validate_rowptr, grid_for(n), kBlock, 0, st, g, flags);
+  if (n > 0) hipLaunchKernelGGL(k_validate_rowptr, grid_for(n), kBlock, 0, st, g, flags, longest_row);
 }
 
 void launch_popcount_words(const uint32_t* bitmap, int64_t n_words, int64_t* counts, hipStream_t st) {

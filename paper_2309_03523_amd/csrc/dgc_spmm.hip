@@ -321,11 +321,15 @@ __global__ __launch_bounds__(256) void k_spmm_long_reduce(SpmmArgs a) {
     double sum[VEC];
 #pragma unroll
     for (int q = 0; q < VEC; ++q) sum[q] = 0.0;
-    for (int p = 0; p < parts; ++p) {
-      float v[VEC];
-      vload<VEC>(v, a.partial + (item + p) * a.ldm + fi);
+    constexpr int kAhead = 8;      // parts requested together (past the last: the last one, not added)
+    for (int p0 = 0; p0 < parts; p0 += kAhead) {
+      float v[kAhead][VEC];
 #pragma unroll
-      for (int q = 0; q < VEC; ++q) sum[q] += (double)v[q];
+      for (int k = 0; k < kAhead; ++k) vload<VEC>(v[k], a.partial + (item + min(p0 + k, parts - 1)) * a.ldm + fi);
+#pragma unroll
+      for (int k = 0; k < kAhead; ++k)
+#pragma unroll
+        for (int q = 0; q < VEC; ++q) sum[q] += p0 + k < parts ? (double)v[k][q] : 0.0;
     }
     float acc[VEC];
 #pragma unroll
@@ -465,11 +469,25 @@ __device__ __forceinline__ AggCtx agg_ctx(const SpmmArgs& a, const Segment& sg, 
   return c;
 }
 
-template <int LPR, bool SKIP>
-__device__ __forceinline__ void agg_short(const SpmmArgs& a, AggCols cols, int64_t item) {
+// TEAM: the four waves of a workgroup share the rows of more than kShared<LPR> non-zeros, a quarter each: they are left in
+// `queue` here and taken by agg_team.
+struct TeamRow {
+  int64_t e;        // table entry of the row's first non-zero
+  int64_t orow;     // row of M (a part: of the partial sums)
+  int nnz, self_j, t;
+  float scale;
+};
+constexpr int kTeam = 4;
+template <int LPR> constexpr int kShared = 4 * kU * (64 / LPR);    // four batches of a wave
+
+template <int LPR, bool SKIP, bool TEAM>
+__device__ __forceinline__ void agg_short(const SpmmArgs& a, AggCols cols, int64_t item, TeamRow* queue, int* n_queued) {
   constexpr int G = 64 / LPR;
   const int lane = threadIdx.x & (kWave - 1);
-  if (item >= a.n_short) return;
+  if (item >= a.n_short) {
+    if (TEAM && lane == 0) *n_queued = 0;
+    return;
+  }
   const int seg = uniform(a.work_short[3 * item + 0]);
   const int r0 = uniform(a.work_short[3 * item + 1]);
   const int n = uniform(a.work_short[3 * item + 2]);
@@ -484,6 +502,18 @@ __device__ __forceinline__ void agg_short(const SpmmArgs& a, AggCols cols, int64
   const int64_t ldo = a.ld_out ? a.ld_out : a.ldm;
   // rows whose output nobody wants (row_map < 0: absent under temporal fusion) are not computed
   uint64_t todo = __ballot(lane < n && (!a.row_map || a.row_map[prow0 + lane] >= 0));
+  if constexpr (TEAM) {
+    const int nnz = __shfl(my_rel, lane + 1) - my_rel;           // of row `lane`, where todo has its bit
+    const bool wanted = todo >> lane & 1;
+    const uint64_t shared = __ballot(wanted && nnz > kShared<LPR> && nnz <= a.long_nnz);
+    if (shared >> lane & 1) {
+      const int64_t orow = a.row_map ? a.row_map[prow0 + lane] : prow0 + lane;
+      queue[__popcll(shared & ((1ull << lane) - 1))] =
+          TeamRow{sg.nnz_off + (rp0 - sg.e0) + my_rel, orow, nnz, (int)(sg.v_lo + r0 + lane), sg.t, dinv_rows[lane]};
+    }
+    if (lane == 0) *n_queued = __popcll(shared);
+    todo &= ~shared;
+  }
   while (todo) {
     const int r = __builtin_ctzll(todo);
     const int e_r = __builtin_amdgcn_readlane(my_rel, r), e_r1 = __builtin_amdgcn_readlane(my_rel, r + 1);
@@ -547,16 +577,77 @@ __device__ __forceinline__ void agg_long(const SpmmArgs& a, AggCols cols, int64_
 template <int LPR, bool SKIP>
 __global__ __launch_bounds__(256) void k_agg(SpmmArgs a, AggCols cols, int64_t long_blocks) {
   const int64_t block = blockIdx.x, wave = threadIdx.x / kWave;
-  if (block < long_blocks) agg_long<LPR, SKIP>(a, cols, block * (256 / kWave) + wave);
-  else agg_short<LPR, SKIP>(a, cols, (block - long_blocks) * (256 / kWave) + wave);
+  if (block < long_blocks) agg_long<LPR, SKIP>(a, cols, block * kTeam + wave);
+  else agg_short<LPR, SKIP, false>(a, cols, (block - long_blocks) * kTeam + wave, nullptr, nullptr);
 }
 
+// The same on a graph that does not fill the chip for long: there the longest row is what the launch waits for (1024
+// non-zeros are 32 batches of gathers, each waited for), so the four waves of a workgroup share a part, and the
+// longer rows of their four groups once they have done the short ones.  A row's quarters are added in wave order.
+template <int LPR, bool SKIP>
+__global__ __launch_bounds__(256) void k_agg_team(SpmmArgs a, AggCols cols, int64_t long_blocks) {
+  constexpr int G = 64 / LPR;
+  __shared__ TeamRow queue[kTeam][32];       // a group has at most 32 rows
+  __shared__ int queued[kTeam];
+  __shared__ float4 sums[2][kTeam][LPR];
+  const int lane = threadIdx.x & (kWave - 1), wave = uniform(threadIdx.x / kWave);
+  const int g = lane / LPR, l = lane % LPR;
+  const bool part = blockIdx.x < long_blocks;
+  if (part) {
+    if (lane == 0) queued[wave] = 0;
+    if (wave == 0) {
+      const int64_t item = blockIdx.x;
+      const int32_t* w = a.work_long + 4 * item;
+      const Segment sg = a.segs[uniform(w[0])];
+      const int row = uniform(w[1]);
+      const int64_t* rp = a.g.rowptr[sg.t] + sg.v_lo + row;
+      const int64_t ea = rp[0] + (int64_t)uniform(w[2]) * a.part_nnz, eb = rp[1];
+      const bool wanted = !a.row_map || a.row_map[sg.row_off + row] >= 0;
+      if (lane == 0 && wanted) {
+        queue[0][0] = TeamRow{sg.nnz_off + (ea - sg.e0), item, (int)(min(ea + a.part_nnz, eb) - ea), (int)(sg.v_lo + row), sg.t, 1.0f};
+        queued[0] = 1;
+      }
+    }
+  } else {
+    agg_short<LPR, SKIP, true>(a, cols, ((int64_t)blockIdx.x - long_blocks) * kTeam + wave, queue[wave], queued + wave);
+  }
+  __syncthreads();
+  float* const out = part ? a.partial : a.M;
+  const int64_t ldo = part || !a.ld_out ? a.ldm : a.ld_out;
+  const int fi = (cols.c0 + 4 * l < a.F) ? cols.c0 + 4 * l : cols.c0;
+  const uint32_t ld_bytes = (uint32_t)(a.ld_fresh * sizeof(float));
+  int turn = 0;
+  for (int from = 0; from < kTeam; ++from)
+    for (int i = 0; i < queued[from]; ++i, ++turn) {
+      const TeamRow row = queue[from][i];
+      const int t = uniform(row.t), nnz = uniform(row.nnz);
+      const int64_t snap = (int64_t)t * a.g.N * a.ld_fresh;
+      const int quarter = (nnz + kTeam - 1) / kTeam, e0 = wave * quarter;
+      float acc[4] = {0.f, 0.f, 0.f, 0.f};
+      agg_range<LPR, SKIP>(a.etab + row.e, e0 + g * kU, min(e0 + quarter, nnz), kU * G, row.self_j, reinterpret_cast<const char*>(a.fresh + snap + fi),
+                           reinterpret_cast<const char*>(a.stale + snap + fi), ld_bytes, acc);
+      agg_reduce_groups<LPR>(acc);
+      if (g == 0) sums[turn & 1][wave][l] = make_float4(acc[0], acc[1], acc[2], acc[3]);
+      __syncthreads();       // (the next row's sums go to the other buffer)
+      if (wave == (turn & (kTeam - 1)) && g == 0) {
+        const float4 s0 = sums[turn & 1][0][l], s1 = sums[turn & 1][1][l], s2 = sums[turn & 1][2][l], s3 = sums[turn & 1][3][l];
+        const float sum[4] = {((s0.x + s1.x) + s2.x) + s3.x, ((s0.y + s1.y) + s2.y) + s3.y, ((s0.z + s1.z) + s2.z) + s3.z,
+                              ((s0.w + s1.w) + s2.w) + s3.w};
+        agg_store<LPR>(out + row.orow * ldo, l, cols, a.F, sum, row.scale);
+      }
+    }
+}
+
+// Without a row to share the team's queue and barriers would only cost (8 x 1000 rows of at most 30 non-zeros, width 32:
+// 9.0 us without, 10.0 with); with one the team is the faster at every size tried, 5000 x 8 rows up to 100 000 x 32.
 template <int LPR>
 void launch_agg(const SpmmArgs& a, AggCols cols, hipStream_t st) {
-  const int64_t gs = (a.n_short + 3) / 4, gl = (a.n_long + 3) / 4;
+  const bool team = a.longest_row > kShared<LPR>;
+  const int64_t gs = (a.n_short + kTeam - 1) / kTeam, gl = team ? a.n_long : (a.n_long + kTeam - 1) / kTeam;
   if (gs + gl == 0) return;
-  if (a.skip_stale) hipLaunchKernelGGL((k_agg<LPR, true>), (unsigned)(gs + gl), 256, 0, st, a, cols, gl);
-  else hipLaunchKernelGGL((k_agg<LPR, false>), (unsigned)(gs + gl), 256, 0, st, a, cols, gl);
+  auto* kernel = team ? (a.skip_stale ? &k_agg_team<LPR, true> : &k_agg_team<LPR, false>)
+                      : (a.skip_stale ? &k_agg<LPR, true> : &k_agg<LPR, false>);
+  hipLaunchKernelGGL(kernel, (unsigned)(gs + gl), 256, 0, st, a, cols, gl);
 }
 
 // Rows wider than the 256 floats that a wave's lanes span go in stretches: 2.4 M gathers of 300 floats (uniform over
