@@ -425,7 +425,7 @@ dgc_status_t build_dysat(dgc_layer* L, const std::vector<ChunkInfo>& cinfo, hipS
   DGC_HIP_TRY(dev_alloc(L, &w.dss, TN * 16));
   // split rows: those of the covered rows come from the packing; the reverse-edge pass walks every
   // vertex of the snapshots in use and gets its own list
-  w.long_nnz = L->long_nnz; w.part_nnz = L->part_nnz;
+  w.long_nnz = L->long_nnz; w.part_nnz = L->part_nnz; w.longest_row = L->longest_row;
   w.work_long = L->d_work_long; w.n_long = L->n_long;
   {
     int32_t* d_cnt = nullptr;

@@ -141,10 +141,9 @@ __global__ __launch_bounds__(512, 4) void k_gat_project(ProjArgs a) {
 // is kBatch neighbours per slot, and the next batch is requested before the current one is used; the next row's
 // column ids before the current row.  The softmax is accumulated online with one running maximum per head for all
 // slots; the slots' sums are added at the row's end.
-// Bound by the latency of the gathers where rows are few: 83 us for 12 snapshots of 5001 vertices and about 60 000
-// non-zeros (two features a lane, eight neighbours, nothing ahead: 152 us, and 74 us for the split rows in a launch
-// of their own); by their bytes where they are many: 3.0 ms for 16 of 250 000 and 3 million, 5.7 TB/s with U (2.95
-// and 0.48 ms).
+// Bound by the latency of the gathers where rows are few: 51 us for 12 snapshots of 5001 vertices and about 60 000
+// non-zeros (83 us without the team); by their bytes where they are many: 2.9 ms for 16 of 250 000 and 3 million, 5.8 TB/s
+// with U.
 // Rows longer than long_nnz (hubs of the power-law graphs) are cut into parts of part_nnz non-zeros, one wavefront
 // each, in the same launch and begun first; a part leaves its (maximum, sum, weighted sum) in a scratch record and a
 // second kernel merges the records of a row in part order.
@@ -253,7 +252,16 @@ __device__ __forceinline__ void gat_row_store(const GatArgs& a, int64_t row, con
   if (lse_lane) a.lse[row * 8 + head] = r.m + __logf(r.l);
 }
 
-__device__ __forceinline__ void gat_short(const GatArgs& a, int64_t item, int lane) {
+// TEAM: rows of more than kShared non-zeros are left in `queue` for the four waves of the workgroup.
+constexpr int kTeam = 4, kShared = 8 * 4 * kBatch;     // eight batches of a wave (four: the same on small graphs, 0.5 % more on large ones)
+struct TeamRow { int64_t e0; int32_t seg, i, n; };     // first non-zero, segment, vertex, non-zeros
+
+template <bool TEAM>
+__device__ __forceinline__ void gat_short(const GatArgs& a, int64_t item, int lane, TeamRow* queue, int* n_queued) {
+  int queued = 0;
+  if constexpr (TEAM) {
+    if (lane == 0) *n_queued = 0;
+  }
   if (item >= a.n_work) return;
   const int32_t si = a.work[3 * item], r0 = a.work[3 * item + 1], nr = a.work[3 * item + 2];
   const Segment s = a.segs[si];
@@ -277,16 +285,45 @@ __device__ __forceinline__ void gat_short(const GatArgs& a, int64_t item, int la
       nids = e1 + lane < ne1 ? col[e1 + lane] : 0;
       nsd = a.sX[(base + i0 + rr + 1) * 16 + 8 + head];
     }
-    if (e1 - e0 <= a.long_nnz) {    // split rows: gat_long
+    if (TEAM && e1 - e0 > kShared && e1 - e0 <= a.long_nnz) {
+      if (lane == 0) queue[queued] = TeamRow{e0, si, (int32_t)(i0 + rr), (int32_t)(e1 - e0)};
+      ++queued;
+    } else if (e1 - e0 <= a.long_nnz) {    // split rows: gat_long
       const SoftAcc r = gat_row_range(a, s, col + e0, base, sd, (int)(e1 - e0), ids, lane);
       gat_row_store(a, base + i0 + rr, r, own_feature(lane), lane < 16 && !(lane & 1), head);
     }
     e0 = e1; e1 = ne1; ids = nids; sd = nsd;
   }
+  if constexpr (TEAM) {
+    if (lane == 0) *n_queued = queued;
+  }
 }
 
 // record of one part of a split row: weighted sum [128], maximum [8], sum [8]
 constexpr int kLongRec = 144;
+__device__ __forceinline__ void put_record(float* rec, const SoftAcc& r, int lane) {
+  *reinterpret_cast<float2*>(rec + own_feature(lane)) = make_float2(r.a0, r.a1);
+  if (lane < 16 && !(lane & 1)) {
+    rec[128 + (lane >> 1)] = r.m;
+    rec[136 + (lane >> 1)] = r.l;
+  }
+}
+// n records in their order; the lane's features are 2 lane and the next, its head lane / 8
+__device__ __forceinline__ SoftAcc merge_records(const float* recs, int n, int lane) {
+  const int head = lane >> 3;
+  float mx = -INFINITY;
+  for (int p = 0; p < n; ++p) mx = fmaxf(mx, recs[p * kLongRec + 128 + head]);
+  SoftAcc r{mx, 0.f, 0.f, 0.f};
+  for (int p = 0; p < n; ++p) {
+    const float* rec = recs + p * kLongRec;
+    const float sc = __expf(rec[128 + head] - mx);
+    const float2 v = *reinterpret_cast<const float2*>(rec + 2 * lane);
+    r.l += sc * rec[136 + head];
+    r.a0 += sc * v.x;
+    r.a1 += sc * v.y;
+  }
+  return r;
+}
 
 __device__ __forceinline__ void gat_long(const GatArgs& a, int64_t item, int lane) {
   if (item >= a.n_long) return;
@@ -301,19 +338,69 @@ __device__ __forceinline__ void gat_long(const GatArgs& a, int64_t item, int lan
   const int32_t* first = a.g.colidx[s.t] + e0;
   const int n = (int)(e1 - e0);
   const SoftAcc r = gat_row_range(a, s, first, base, sd, n, lane < n ? first[lane] : 0, lane);
-  float* rec = a.long_partial + item * kLongRec;
-  *reinterpret_cast<float2*>(rec + own_feature(lane)) = make_float2(r.a0, r.a1);
-  if (lane < 16 && !(lane & 1)) {
-    rec[128 + head] = r.m;
-    rec[136 + head] = r.l;
-  }
+  put_record(a.long_partial + item * kLongRec, r, lane);
 }
 
 __global__ __launch_bounds__(256, 5) void k_gat_aggregate(GatArgs a, int64_t long_blocks) {
   const int lane = threadIdx.x & 63;
   const int64_t block = blockIdx.x, wave = threadIdx.x >> 6;
-  if (block < long_blocks) gat_long(a, block * 4 + wave, lane);
-  else gat_short(a, (block - long_blocks) * 4 + wave, lane);
+  if (block < long_blocks) gat_long(a, block * kTeam + wave, lane);
+  else gat_short<false>(a, (block - long_blocks) * kTeam + wave, lane, nullptr, nullptr);
+}
+
+// The same where a row is longer than kShared: the launch on a small graph waits for its longest row (1024 non-zeros are 64
+// batches in turn), so the four waves of a workgroup share a part, and the longer rows of their groups
+// once the others are done.  The quarters' records meet in LDS and are merged in wave order.
+__global__ __launch_bounds__(256, 5) void k_gat_aggregate_team(GatArgs a, int64_t long_blocks) {
+  __shared__ TeamRow queue[kTeam][32];          // a group has at most 32 rows
+  __shared__ int queued[kTeam];
+  __shared__ __align__(16) float recs[2][kTeam][kLongRec];
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int64_t block = blockIdx.x;
+  const bool part = block < long_blocks;
+  if (part) {
+    if (lane == 0) {
+      queued[wave] = wave == 0;
+      if (wave == 0) {
+        const int32_t* w = a.work_long + 4 * block;
+        const Segment s = a.segs[w[0]];
+        const int64_t i = s.v_lo + w[1];
+        const int64_t* rowptr = a.g.rowptr[s.t];
+        const int64_t e0 = rowptr[i] + (int64_t)w[2] * a.part_nnz;
+        queue[0][0] = TeamRow{e0, w[0], (int32_t)i, (int32_t)(min(rowptr[i + 1], e0 + a.part_nnz) - e0)};
+      }
+    }
+  } else {
+    gat_short<true>(a, (block - long_blocks) * kTeam + wave, lane, queue[wave], queued + wave);
+  }
+  __syncthreads();
+  int turn = 0;
+  for (int from = 0; from < kTeam; ++from)
+    for (int k = 0; k < queued[from]; ++k, ++turn) {
+      const TeamRow row = queue[from][k];
+      const Segment s = a.segs[__builtin_amdgcn_readfirstlane(row.seg)];
+      const int64_t base = (int64_t)s.t * a.g.N;
+      const int n = __builtin_amdgcn_readfirstlane(row.n), quarter = (n + kTeam - 1) / kTeam;
+      const int b = min(n, wave * quarter), m = min(n, b + quarter) - b;
+      const float sd = a.sX[(base + row.i) * 16 + 8 + ((lane & 15) >> 1)];
+      const int32_t* first = a.g.colidx[s.t] + row.e0 + b;
+      put_record(recs[turn & 1][wave], gat_row_range(a, s, first, base, sd, m, lane < m ? first[lane] : 0, lane), lane);
+      __syncthreads();        // (the next row's records go to the other buffer)
+      if (wave == (turn & (kTeam - 1))) {
+        const SoftAcc r = merge_records(recs[turn & 1][0], kTeam, lane);
+        const int head = lane >> 3;
+        if (part) {
+          float* rec = a.long_partial + block * kLongRec;
+          *reinterpret_cast<float2*>(rec + 2 * lane) = make_float2(r.a0, r.a1);
+          if ((lane & 7) == 0) {
+            rec[128 + head] = r.m;
+            rec[136 + head] = r.l;
+          }
+        } else {
+          gat_row_store(a, base + row.i, r, 2 * lane, (lane & 7) == 0, head);
+        }
+      }
+    }
 }
 
 // one wavefront per split row (the item of its part 0) merges the parts in order
@@ -324,20 +411,8 @@ __global__ __launch_bounds__(256) void k_gat_aggregate_merge(GatArgs a) {
   const int32_t* w = a.work_long + 4 * item;
   if (w[2] != 0) return;
   const Segment s = a.segs[w[0]];
-  const int head = lane >> 3;
-  const int parts = w[3];
-  float mx = -INFINITY;
-  for (int p = 0; p < parts; ++p) mx = fmaxf(mx, a.long_partial[(item + p) * kLongRec + 128 + head]);
-  SoftAcc r{mx, 0.f, 0.f, 0.f};
-  for (int p = 0; p < parts; ++p) {
-    const float* rec = a.long_partial + (item + p) * kLongRec;
-    const float sc = __expf(rec[128 + head] - mx);
-    const float2 v = *reinterpret_cast<const float2*>(rec + 2 * lane);
-    r.l += sc * rec[136 + head];
-    r.a0 += sc * v.x;
-    r.a1 += sc * v.y;
-  }
-  gat_row_store(a, (int64_t)s.t * a.g.N + s.v_lo + w[1], r, 2 * lane, (lane & 7) == 0, head);
+  const SoftAcc r = merge_records(a.long_partial + item * kLongRec, w[3], lane);
+  gat_row_store(a, (int64_t)s.t * a.g.N + s.v_lo + w[1], r, 2 * lane, (lane & 7) == 0, lane >> 3);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -496,8 +571,10 @@ void dysat_forward(const DysatWs& ws, const void* X, int64_t ldx, const void* C,
   ga.work_long = ws.work_long; ga.n_long = ws.n_long; ga.long_nnz = ws.long_nnz; ga.part_nnz = ws.part_nnz;
   ga.long_partial = ws.long_partial;
   ga.zX = ws.zX; ga.zC = ws.zC; ga.sX = ws.sX; ga.sC = ws.sC; ga.U = ws.U; ga.lse = ws.lse;
-  const int64_t long_blocks = (ws.n_long + 3) / 4;
-  hipLaunchKernelGGL(k_gat_aggregate, (unsigned)(long_blocks + (ws.n_short + 3) / 4), 256, 0, st, ga, long_blocks);
+  const bool team = ws.longest_row > kShared;      // else there is nothing to share
+  const int64_t long_blocks = team ? ws.n_long : (ws.n_long + kTeam - 1) / kTeam;
+  hipLaunchKernelGGL(team ? k_gat_aggregate_team : k_gat_aggregate, (unsigned)(long_blocks + (ws.n_short + kTeam - 1) / kTeam), 256, 0, st,
+                     ga, long_blocks);
   if (ws.n_long > 0) hipLaunchKernelGGL(k_gat_aggregate_merge, blocks_for(ws.n_long, 4), 256, 0, st, ga);
   if (ev) (void)hipEventRecord(ev[2], st);
   TemporalArgs ta{};

@@ -311,6 +311,7 @@ struct DysatWs {
   float* loss_partial;
   // rows longer than long_nnz are cut into parts of part_nnz non-zeros
   int32_t long_nnz, part_nnz;
+  int32_t longest_row;                             // non-zeros of the longest stored row
   const int32_t* work_long; int64_t n_long;        // covered rows: (segment, local row, part, parts)
   const int32_t* cols_long; int64_t n_cols_long;   // all vertices: (snapshot, vertex, part, parts)
   float* long_partial;                             // one record per part

@@ -1,0 +1,38 @@
+"""Rows of the graph attention that the four waves of a workgroup share: lengths around the threshold (128) and where a quarter
+ends inside a batch or is shorter than the others, whole and as parts of split rows, several in one group and in one workgroup.
+Rows of more than 128 neighbours average as many projections, so the bar is the layer's bf16 one relative to the root mean
+square of the row looked at."""
+import numpy as np
+import pytest
+
+from oracle import dysat
+from refs import rel_err
+from workloads import synth
+
+pytestmark = pytest.mark.gpu
+
+TOL = 2e-2
+LENGTHS = [128, 129, 130, 131, 132, 133, 160, 191, 192, 193, 255, 256, 257, 258, 319, 320, 321, 400, 511, 512, 513, 600]
+
+
+@pytest.mark.parametrize("T,N,cut,kw", [
+    (2, 700, 11, {}), (1, 701, 350, dict(rows_per_group=32)), (1, 689, 5, dict(rows_per_group=1)),
+    (1, 700, 20, dict(long_nnz=300, part_nnz=131, rows_per_group=8)), (2, 693, 400, dict(long_nnz=130, part_nnz=3)),
+])
+def test_shared_rows(T, N, cut, kw):
+    from paper_2309_03523_amd.runner import DysatDevice
+    wl = synth.dysat_small(N, T, N, 128, 8, 3.0, [[0, cut, 0, T], [cut, N, 0, T]])
+    k = len(LENGTHS)
+    for t in range(T):
+        rng = synth.stream(N + t, "rows")
+        leaves = [rng.choice(N - k, size=n - 1, replace=False) + k for n in LENGTHS]
+        u = np.concatenate([np.full(len(x), i) for i, x in enumerate(leaves)])
+        wl.graph.snaps[t] = synth.csr_from_undirected(N, u, np.concatenate(leaves))
+        assert np.diff(wl.graph.snaps[t].rowptr)[:k].tolist() == LENGTHS
+    dd = DysatDevice(wl, validate_level=1, **kw)
+    got = dd.forward().float().cpu().numpy()
+    want = dysat.gradients(wl.graph, wl.chunks, wl.params, wl.X, wl.C, 8, dY=np.zeros_like(wl.X))["Y"]
+    for i in range(k):
+        assert rel_err(got[:, i], want[:, i], floor=1.0) < TOL, LENGTHS[i]
+    assert rel_err(got, want, floor=1.0) < TOL
+    dd.layer.destroy()
