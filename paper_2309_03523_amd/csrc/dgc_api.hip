@@ -17,6 +17,7 @@ thread_local std::string g_create_error = "";
 struct Param {
   float* raw = nullptr;       // device, [n_out][n_in] or [n]
   float4* packed = nullptr;   // device, fragment order (weights only): fp32, or three bf16 parts if split
+  float4* narrow = nullptr;   // the same in the order of the narrow time encoder, where that may run
   bool split = false;
   int32_t n_out = 0, n_in = 0;  // n_in = 0: a bias vector of n_out elements
   int64_t numel() const { return n_in ? (int64_t)n_out * n_in : n_out; }
@@ -64,6 +65,7 @@ struct dgc_layer {
   float* d_partial = nullptr;                    // split-row partial sums
   float* d_halo = nullptr; int64_t ld_halo = 0;  // STAGED: gathered cache rows
   float* d_Z1 = nullptr;                         // 2 layers: first layer's output [T,N,S]
+  bool narrow = false;                           // the narrow kernel may run the (first) time encoder
   float* d_zero_bias = nullptr;                  // [S] zeros (EvolveGCN-O has no bias)
   EvolveWs evo{};                                // EvolveGCN-O workspace
   // the weight recurrence's own stream: a chain of small launches beside the work that does not wait for it
@@ -267,18 +269,31 @@ bool runs_split(const dgc_layer_desc_t& d, int32_t S, int32_t H, int32_t time_ki
   return d.dense_kernel != DGC_DENSE_TILE && dense_split_supported(S, H, time_kind);
 }
 
-dgc_status_t add_param(dgc_layer* L, const std::string& name, int32_t n_out, int32_t n_in, hipStream_t st, bool split = false) {
+// Whether the time encoder that a transform feeds may run the narrow kernel; the number of its tiles decides (dense_narrow_wanted).
+bool may_run_narrow(const dgc_layer_desc_t& d) {
+  return runs_split(d, d.S, d.H, d.time_kind) && !d.lstm_input_concat &&
+         dense_narrow_supported(d.S, d.H, d.n_struct_layers == 2 ? d.S : d.F, d.time_kind);
+}
+
+dgc_status_t add_param(dgc_layer* L, const std::string& name, int32_t n_out, int32_t n_in, hipStream_t st, bool split = false,
+                       bool narrow = false) {
   Failer fail{L};
   Param p;
   p.n_out = n_out; p.n_in = n_in; p.split = split;
   DGC_HIP_TRY(dev_alloc(L, &p.raw, p.numel()));
   DGC_HIP_TRY(hipMemsetAsync(p.raw, 0, sizeof(float) * p.numel(), st));
+  auto packed = [&](int64_t floats, float4** out) -> dgc_status_t {
+    float* pk = nullptr;
+    DGC_HIP_TRY(dev_alloc(L, &pk, floats));
+    DGC_HIP_TRY(hipMemsetAsync(pk, 0, sizeof(float) * floats, st));
+    *out = reinterpret_cast<float4*>(pk);
+    return DGC_OK;
+  };
+  dgc_status_t rc;
   if (n_in) {
     const int64_t pe = split ? split_weight_bytes(n_out, n_in) / (int64_t)sizeof(float) : packed_weight_elems(n_out, n_in);
-    float* pk = nullptr;
-    DGC_HIP_TRY(dev_alloc(L, &pk, pe));
-    DGC_HIP_TRY(hipMemsetAsync(pk, 0, sizeof(float) * pe, st));
-    p.packed = reinterpret_cast<float4*>(pk);
+    if ((rc = packed(pe, &p.packed)) != DGC_OK) return rc;
+    if (narrow && (rc = packed(narrow_weight_bytes(n_out, n_in) / (int64_t)sizeof(float), &p.narrow)) != DGC_OK) return rc;
   }
   L->params[name] = p;
   return DGC_OK;
@@ -665,16 +680,17 @@ dgc_status_t build_layer(dgc_layer* L, const dgc_graph_t* graph, hipStream_t st)
     if ((rc = build_evolve(L, cinfo, st)) != DGC_OK) return rc;
   } else {
   const bool sp = runs_split(d, d.S, d.H, d.time_kind), sp0 = runs_split(d, d.S, 0, DGC_TIME_NONE);
-  if ((rc = add_param(L, "gcn0.weight", d.S, d.F, st, d.n_struct_layers == 2 ? sp0 : sp)) != DGC_OK) return rc;
+  const bool nw = L->narrow = may_run_narrow(d), two = d.n_struct_layers == 2;
+  if ((rc = add_param(L, "gcn0.weight", d.S, d.F, st, two ? sp0 : sp, nw && !two)) != DGC_OK) return rc;
   if ((rc = add_param(L, "gcn0.bias", d.S, 0, st)) != DGC_OK) return rc;
   if (d.n_struct_layers == 2) {
-    if ((rc = add_param(L, "gcn1.weight", d.S, d.S, st, sp)) != DGC_OK) return rc;
+    if ((rc = add_param(L, "gcn1.weight", d.S, d.S, st, sp, nw)) != DGC_OK) return rc;
     if ((rc = add_param(L, "gcn1.bias", d.S, 0, st)) != DGC_OK) return rc;
   }
   if (d.time_kind != DGC_TIME_NONE) {
     const int32_t gH = (d.time_kind == DGC_TIME_LSTM ? 4 : 3) * d.H;
-    if ((rc = add_param(L, "rnn.weight_ih", gH, d.lstm_input_concat ? 2 * d.S : d.S, st, sp)) != DGC_OK) return rc;
-    if ((rc = add_param(L, "rnn.weight_hh", gH, d.H, st, sp)) != DGC_OK) return rc;
+    if ((rc = add_param(L, "rnn.weight_ih", gH, d.lstm_input_concat ? 2 * d.S : d.S, st, sp, nw)) != DGC_OK) return rc;
+    if ((rc = add_param(L, "rnn.weight_hh", gH, d.H, st, sp, nw)) != DGC_OK) return rc;
     if ((rc = add_param(L, "rnn.bias_ih", gH, 0, st)) != DGC_OK) return rc;
     if ((rc = add_param(L, "rnn.bias_hh", gH, 0, st)) != DGC_OK) return rc;
     if (d.n_time_layers == 2) {
@@ -919,6 +935,7 @@ dgc_status_t dgc_layer_set_param(dgc_layer_t* L, const char* name, const float* 
     dysat_pack_params(L->dy, nullptr);
     DGC_HIP_TRY(hipDeviceSynchronize());
   } else if (p.packed) {
+    if (p.narrow) launch_pack_narrow(p.raw, p.n_out, p.n_in, p.narrow, nullptr);
     if (p.split) launch_pack_split(p.raw, 0, p.n_in, 1, p.n_out, p.n_in, 1, p.packed, nullptr);
     else launch_pack_weight(p.raw, p.n_out, p.n_in, p.packed, nullptr);
     DGC_HIP_TRY(hipDeviceSynchronize());
@@ -1092,8 +1109,14 @@ dgc_status_t dgc_layer_forward(dgc_layer_t* L, const void* Xv, int64_t ldx, cons
     da.total_state_rows = L->lab.built ? (int64_t)L->T * L->N : L->total_state_rows;
     da.x2_map = tf.slot_row;      // a slot's row of the first layer's output
     if (HN && !L->lab.built) tf_carry(tf.seq_len, L->total_state_rows, d.time_kind == DGC_TIME_LSTM ? 2 : 1, d.H, H0, HN, st);
-    if (tf.n_lanes > 0 && !launch_dense(da, st, &why)) return fail(DGC_ERR_UNSUPPORTED, why);
-  } else if (!launch_dense(da, st, &why)) return fail(DGC_ERR_UNSUPPORTED, why);
+  }
+  da.narrow = L->narrow && dense_narrow_wanted(d.H, da.n_tiles32);
+  if (da.narrow) {
+    da.Wg = L->params[std::string(last) + ".weight"].narrow;
+    da.Wih = L->params["rnn.weight_ih"].narrow; da.Whh = L->params["rnn.weight_hh"].narrow;
+  }
+  if ((!L->tf.built || L->tf.n_lanes > 0) && !launch_dense(da, st, &why)) return fail(DGC_ERR_UNSUPPORTED, why);
+  da.narrow = false;
   if (d.n_time_layers == 2) {
     // The second recurrent layer: the same kernel without a transform, its input rows the first
     // layer's output, read from Y row by row one step before the row is overwritten with the second

@@ -532,6 +532,7 @@ void launch_pack_weight(const float* W, int32_t n_out, int32_t n_in, float4* pac
 }
 
 bool launch_dense(const DenseArgs& a, hipStream_t st, std::string* why) {
+  if (a.narrow) return launch_dense_narrow(a, st, why);
   if (a.variant != DGC_DENSE_TILE && !(a.variant == DGC_DENSE_WAVE && !dense_wave_shape(a.S, a.H, a.time_kind)) &&
       dense_split_supported(a.S, a.H, a.time_kind))
     return launch_dense_split(a, st, why);

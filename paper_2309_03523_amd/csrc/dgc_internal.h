@@ -208,11 +208,18 @@ struct DenseArgs {
   // [T,N,ldm] tensor and are the time encoder's input as they are (no transform, K0 = 0).
   // M may be Y itself: a wave requests row (t, v) before step t and writes it at that step's end.
   bool input_is_z;
+  bool narrow;                  // the weights are packed for the narrow kernel, which runs
 };
 // returns false if the (S,H,K0) combination has no kernel
 bool launch_dense(const DenseArgs& a, hipStream_t st, std::string* why);
 // The split kernel (dgc_dense_split.hip) takes weights as three bf16 parts per fragment of 32 x 16, see k_pack_split.
 bool dense_split_supported(int32_t S, int32_t H, int32_t time_kind);
+// The first recurrent layer of narrow layers, without a concatenated input (dgc_dense_narrow.hip); K0: input columns
+bool dense_narrow_supported(int32_t S, int32_t H, int32_t K0, int32_t time_kind);
+bool dense_narrow_wanted(int32_t H, int64_t n_tiles32);      // whether it is the faster one
+bool launch_dense_narrow(const DenseArgs& a, hipStream_t st, std::string* why);
+int64_t narrow_weight_bytes(int32_t n_out, int32_t n_in);
+void launch_pack_narrow(const float* W, int32_t n_out, int32_t n_in, void* packed, hipStream_t st);
 // Of its shapes, those that DGC_DENSE_WAVE, the concatenated input, the stacked time encoder and F above 304 are offered for.
 inline bool dense_wave_shape(int32_t S, int32_t H, int32_t time_kind) {
   return (S == 32 || S == 64 || S == 128 || (S == 256 && time_kind == DGC_TIME_NONE)) && (time_kind == DGC_TIME_NONE || H == S);

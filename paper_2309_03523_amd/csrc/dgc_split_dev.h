@@ -25,9 +25,6 @@ __device__ __forceinline__ uint32_t nearest(float lo, float hi) {   // two float
 }
 __device__ __forceinline__ float bf_lo(uint32_t u) { return __uint_as_float(u << 16); }
 __device__ __forceinline__ float bf_hi(uint32_t u) { return __uint_as_float(u & 0xffff0000u); }
-__device__ __forceinline__ uint4 tops8(const float (&x)[8]) {
-  return make_uint4(tops(x[0], x[1]), tops(x[2], x[3]), tops(x[4], x[5]), tops(x[6], x[7]));
-}
 
 // x = p[0] + p[1] + p[2], exactly, for finite x: p[0] the bf16 number nearest to x, p[1] the one nearest to what is left,
 // p[2] the rest (at most seven bits).  To the nearest, not cut off: the rests then have either sign and half the size, and
@@ -35,11 +32,11 @@ __device__ __forceinline__ uint4 tops8(const float (&x)[8]) {
 // An infinity goes into the low part: that meets only the other operand's high part, which has the sign of the whole
 // number and is zero where that is.  Its other parts are the smallest normal number of its sign, so that two infinities
 // make one, too.
-__device__ __forceinline__ void split8(const float (&x)[8], uint4 (&p)[3]) {
-  uint32_t h[4], m[4], l[4];
+template <int N>    // N numbers, two a word of h, m and l
+__device__ __forceinline__ void split_parts(const float (&x)[N], uint32_t (&h)[N / 2], uint32_t (&m)[N / 2], uint32_t (&l)[N / 2]) {
   float top = 0.f;
 #pragma unroll
-  for (int i = 0; i < 4; ++i) {
+  for (int i = 0; i < N / 2; ++i) {
     const float x0 = x[2 * i], x1 = x[2 * i + 1];
     h[i] = nearest(x0, x1);
     const float m0 = x0 - bf_lo(h[i]), m1 = x1 - bf_hi(h[i]);
@@ -48,9 +45,9 @@ __device__ __forceinline__ void split8(const float (&x)[8], uint4 (&p)[3]) {
     top = fmaxf(top, fmaxf(fabsf(x0), fabsf(x1)));
   }
   if (__builtin_expect(__any(top > 3.3895313892515355e38f), 0)) {   // the largest bf16 number: beyond it, x may round to infinity
-    float a[8], b[8], c[8];
+    float a[N], b[N], c[N];
 #pragma unroll
-    for (int i = 0; i < 8; ++i) {
+    for (int i = 0; i < N; ++i) {
       a[i] = cut(x[i]);
       b[i] = x[i] - a[i];
       c[i] = b[i] - cut(b[i]);
@@ -59,14 +56,27 @@ __device__ __forceinline__ void split8(const float (&x)[8], uint4 (&p)[3]) {
         c[i] = x[i];
       }
     }
-    p[0] = tops8(a);
-    p[1] = tops8(b);
-    p[2] = tops8(c);
-    return;
+#pragma unroll
+    for (int i = 0; i < N / 2; ++i) {
+      h[i] = tops(a[2 * i], a[2 * i + 1]);
+      m[i] = tops(b[2 * i], b[2 * i + 1]);
+      l[i] = tops(c[2 * i], c[2 * i + 1]);
+    }
   }
+}
+__device__ __forceinline__ void split8(const float (&x)[8], uint4 (&p)[3]) {
+  uint32_t h[4], m[4], l[4];
+  split_parts(x, h, m, l);
   p[0] = make_uint4(h[0], h[1], h[2], h[3]);
   p[1] = make_uint4(m[0], m[1], m[2], m[3]);
   p[2] = make_uint4(l[0], l[1], l[2], l[3]);
+}
+__device__ __forceinline__ void split4(const float (&x)[4], uint2 (&p)[3]) {
+  uint32_t h[2], m[2], l[2];
+  split_parts(x, h, m, l);
+  p[0] = make_uint2(h[0], h[1]);
+  p[1] = make_uint2(m[0], m[1]);
+  p[2] = make_uint2(l[0], l[1]);
 }
 
 // The product of one fragment each, the smallest part products first: the five small ones to `small`, the large one to
