@@ -475,16 +475,21 @@ __device__ __forceinline__ void stage_weights(uint4* lds, const uint4* w0, const
   __syncthreads();
 }
 
+// Twelve waves, three a SIMD, are what 155 registers allow: 12 x 5001 vertices, 2508 tiles, are one round of them on 256
+// CUs, 35 us, and were two of eight, 44; an inference of 16 x 250 000 vertices takes 5.32 ms, with eight 5.43.  A wave's tiles lie gridDim apart, so
+// that few tiles spread over all CUs.
+constexpr int kTemporalWaves = 12;
+
 // WIDE: one vertex per tile, windows of up to 32 snapshots: the score block of a head is the whole
 // 32 x 32 product (all 16 registers of a lane are keys of its own vertex), and the product with V
 // contracts over the two halves of the keys (registers 0..7 and 8..15) instead of over two vertices.
 template <bool WIDE>
-__global__ __launch_bounds__(512) void k_temporal_fwd(TemporalArgs a) {
+__global__ __launch_bounds__(64 * kTemporalWaves) void k_temporal_fwd(TemporalArgs a) {
   extern __shared__ uint4 wlds[];
   stage_weights(wlds, a.Wq, a.Wk, a.Wv);
-  const int lane = threadIdx.x & 63, nw = blockDim.x >> 6;
+  const int lane = threadIdx.x & 63;
   const int hh = lane >> 5;
-  for (int64_t tile = (int64_t)blockIdx.x * nw + (threadIdx.x >> 6); tile < a.n_tiles; tile += (int64_t)gridDim.x * nw) {
+  for (int64_t tile = (int64_t)(threadIdx.x >> 6) * gridDim.x + blockIdx.x; tile < a.n_tiles; tile += (int64_t)gridDim.x * kTemporalWaves) {
   const TileRow r = tile_row<WIDE>(a.chunks, a.n_chunks, a.tile_ptr, tile, a.N, lane);
   const uint32_t m_vert[2] = {r.a == 0 ? 0xffffffffu : 0u, r.a == 1 ? 0xffffffffu : 0u};
   bf16x8 pf[8], pl[8];
@@ -587,9 +592,9 @@ void dysat_forward(const DysatWs& ws, const void* X, int64_t ldx, const void* C,
     const size_t lds = sizeof(uint4) * 3 * kFragsPerW;
     (void)(ws.wide ? allow_lds(reinterpret_cast<const void*>(k_temporal_fwd<true>), lds, ready_wide)
                    : allow_lds(reinterpret_cast<const void*>(k_temporal_fwd<false>), lds, ready));   // if not, the launch is an error
-    const unsigned grid = (unsigned)std::min<int64_t>(256, (ws.n_tiles + 7) / 8);
-    if (ws.wide) hipLaunchKernelGGL(k_temporal_fwd<true>, grid, 512, lds, st, ta);
-    else hipLaunchKernelGGL(k_temporal_fwd<false>, grid, 512, lds, st, ta);
+    const unsigned grid = (unsigned)std::min<int64_t>(256, ws.n_tiles);
+    if (ws.wide) hipLaunchKernelGGL(k_temporal_fwd<true>, grid, 64 * kTemporalWaves, lds, st, ta);
+    else hipLaunchKernelGGL(k_temporal_fwd<false>, grid, 64 * kTemporalWaves, lds, st, ta);
   }
   if (ev) (void)hipEventRecord(ev[3], st);
 }
