@@ -66,6 +66,15 @@ struct dgc_layer {
   float* d_halo = nullptr; int64_t ld_halo = 0;  // STAGED: gathered cache rows
   float* d_Z1 = nullptr;                         // 2 layers: first layer's output [T,N,S]
   bool narrow = false;                           // the narrow kernel may run the (first) time encoder
+  // The transform before the time encoder folded into its input-side weights, when no activation stands between them.
+  // ok: the four parameters have been set and the folded ones are finite.
+  struct Fold {
+    bool may = false, ok = false;
+    int set = 0;                                 // which of the four have been
+    float *W = nullptr, *bias = nullptr;         // [gH][K0], [gH]
+    float4* packed = nullptr;
+    int32_t* bad = nullptr;
+  } fold;
   float* d_zero_bias = nullptr;                  // [S] zeros (EvolveGCN-O has no bias)
   EvolveWs evo{};                                // EvolveGCN-O workspace
   // the weight recurrence's own stream: a chain of small launches beside the work that does not wait for it
@@ -693,6 +702,16 @@ dgc_status_t build_layer(dgc_layer* L, const dgc_graph_t* graph, hipStream_t st)
     if ((rc = add_param(L, "rnn.weight_hh", gH, d.H, st, sp, nw)) != DGC_OK) return rc;
     if ((rc = add_param(L, "rnn.bias_ih", gH, 0, st)) != DGC_OK) return rc;
     if ((rc = add_param(L, "rnn.bias_hh", gH, 0, st)) != DGC_OK) return rc;
+    const int32_t K0 = two ? d.S : d.F;
+    if (sp && d.act_out == DGC_ACT_NONE && dense_fold_wanted(d.S, K0, d.time_kind) && !(nw && dense_narrow_wanted(d.H, INT64_MAX))) {
+      float* pk = nullptr;
+      DGC_HIP_TRY(dev_alloc(L, &L->fold.W, (int64_t)gH * K0));
+      DGC_HIP_TRY(dev_alloc(L, &L->fold.bias, gH));
+      DGC_HIP_TRY(dev_alloc(L, &pk, split_weight_bytes(gH, K0) / (int64_t)sizeof(float)));
+      DGC_HIP_TRY(dev_alloc(L, &L->fold.bad, 1));
+      L->fold.packed = reinterpret_cast<float4*>(pk);
+      L->fold.may = true;
+    }
     if (d.n_time_layers == 2) {
       if ((rc = add_param(L, "rnn1.weight_ih", gH, d.H, st, sp)) != DGC_OK) return rc;
       if ((rc = add_param(L, "rnn1.weight_hh", gH, d.H, st, sp)) != DGC_OK) return rc;
@@ -919,6 +938,34 @@ dgc_status_t dgc_layer_destroy(dgc_layer_t* L) {
   return DGC_OK;
 }
 
+// After a parameter of the transform or of the time encoder's input side has changed: the product of the two.
+static dgc_status_t refold(dgc_layer* L, const std::string& name) {
+  Failer fail{L};
+  const dgc_layer_desc_t& d = L->desc;
+  const bool two = d.n_struct_layers == 2;
+  const std::string gcn = two ? "gcn1" : "gcn0";
+  const std::string names[4] = {gcn + ".weight", gcn + ".bias", "rnn.weight_ih", "rnn.bias_ih"};
+  dgc_layer::Fold& f = L->fold;
+  int which = -1;
+  for (int k = 0; k < 4; ++k)
+    if (name == names[k]) which = k;
+  if (which < 0) return DGC_OK;
+  f.set |= 1 << which;
+  f.ok = false;
+  if (f.set != 15) return DGC_OK;
+  const Param &wg = L->params[names[0]], &wih = L->params[names[2]];
+  const int32_t other = wih.n_in - d.S;          // columns of the concatenated input's other half, which come first
+  DGC_HIP_TRY(hipMemset(f.bad, 0, sizeof(int32_t)));
+  launch_fold(wih.raw + other, wih.n_in, wg.raw, L->params[names[1]].raw, L->params[names[3]].raw, wih.n_out, d.S, wg.n_in, f.W, f.bias,
+              f.bad, nullptr);
+  launch_pack_split(f.W, 0, wg.n_in, 1, wih.n_out, wg.n_in, 1, f.packed, nullptr);
+  int32_t bad = 0;
+  DGC_HIP_TRY(hipMemcpy(&bad, f.bad, sizeof(bad), hipMemcpyDeviceToHost));
+  DGC_HIP_TRY(hipDeviceSynchronize());
+  f.ok = bad == 0;
+  return DGC_OK;
+}
+
 dgc_status_t dgc_layer_set_param(dgc_layer_t* L, const char* name, const float* host_src, int64_t numel) {
   if (!L) return DGC_ERR_INVALID_ARG;
   Failer fail{L};
@@ -940,6 +987,7 @@ dgc_status_t dgc_layer_set_param(dgc_layer_t* L, const char* name, const float* 
     else launch_pack_weight(p.raw, p.n_out, p.n_in, p.packed, nullptr);
     DGC_HIP_TRY(hipDeviceSynchronize());
   }
+  if (L->fold.may) return refold(L, nm);
   return DGC_OK;
 }
 
@@ -1115,8 +1163,10 @@ dgc_status_t dgc_layer_forward(dgc_layer_t* L, const void* Xv, int64_t ldx, cons
     da.Wg = L->params[std::string(last) + ".weight"].narrow;
     da.Wih = L->params["rnn.weight_ih"].narrow; da.Whh = L->params["rnn.weight_hh"].narrow;
   }
+  if (L->fold.ok && !da.narrow) { da.Wf = L->fold.packed; da.bf = L->fold.bias; }
   if ((!L->tf.built || L->tf.n_lanes > 0) && !launch_dense(da, st, &why)) return fail(DGC_ERR_UNSUPPORTED, why);
   da.narrow = false;
+  da.Wf = nullptr; da.bf = nullptr;
   if (d.n_time_layers == 2) {
     // The second recurrent layer: the same kernel without a transform, its input rows the first
     // layer's output, read from Y row by row one step before the row is overwritten with the second

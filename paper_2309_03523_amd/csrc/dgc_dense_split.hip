@@ -148,11 +148,20 @@ __device__ __forceinline__ void relu(floatx16& z) {
   for (int v = 0; v < 16; ++v) z[v] = fmaxf(z[v], 0.f);
 }
 
-// KIND: DGC_TIME_GRU or DGC_TIME_LSTM.  SEQ, CAT, STACK: as the fields of DenseArgs say (sequences inside the window;
-// the time encoder's input is [X2 row, Z]; a second recurrent layer without a transform).
-template <int KIND, bool SEQ, bool CAT, bool STACK, int MAXW>
+// What a row of M is to the time encoder: Z's operand; its input by way of the folded weights (no transform: where no
+// activation stands between them, W_ih (W_g m + b_g) = (W_ih W_g) m + W_ih b_g); its input as it is (a second recurrent layer).
+// Folding takes 48 of 336 MFMAs a tile and step from a GRU 128 wide over 128 columns, and the matrix cores' power is what bounds
+// the kernel: 32 x 100 000 vertices 4.05 -> 3.45 ms, the two GCN layers and LSTM of MPNN-LSTM (624 -> 576) 2.92 -> 2.70.  The product of
+// the weights is summed in double and rounded once, where Z was rounded, so nothing gets further from 64 bits (0.87 of the
+// distance in the mean of 46 outputs of GRUs, 0.94 of 24 of LSTMs, 0.999 at most).
+enum Input { kTransform, kFolded, kStack };
+
+// KIND: DGC_TIME_GRU or DGC_TIME_LSTM.  SEQ, CAT: as the fields of DenseArgs say (sequences inside the window;
+// the time encoder's input is [X2 row, Z]).
+template <int KIND, bool SEQ, bool CAT, Input INPUT, int MAXW>
 __global__ __launch_bounds__(64 * MAXW, 2) void k_dense_split(DenseArgs a) {
-  constexpr bool kLstm = KIND == DGC_TIME_LSTM;
+  constexpr bool kLstm = KIND == DGC_TIME_LSTM, STACK = INPUT == kStack, FOLD = INPUT == kFolded;
+  const float* const bih = FOLD ? a.bf : a.bih;
   // The five small products of Z go apart from the large one (the matrix unit truncates when it adds, and a small sum is
   // truncated by less), the gates' do not (no registers), but for a second recurrent layer: without a transform whose
   // better sums make up for it, its gates' products alone would be off 64 bits by up to 1.4 times as much as on the fp32
@@ -176,11 +185,11 @@ __global__ __launch_bounds__(64 * MAXW, 2) void k_dense_split(DenseArgs a) {
     zbias[i] = a.bg ? a.bg[i] : 0.f;
     if constexpr (kLstm) {
 #pragma unroll
-      for (int g = 0; g < 4; ++g) gbias[g * H + i] = a.bih[g * H + i] + a.bhh[g * H + i];
+      for (int g = 0; g < 4; ++g) gbias[g * H + i] = bih[g * H + i] + a.bhh[g * H + i];
     } else {
-      gbias[i] = a.bih[i] + a.bhh[i];
-      gbias[H + i] = a.bih[H + i] + a.bhh[H + i];
-      gbias[2 * H + i] = a.bih[2 * H + i];
+      gbias[i] = bih[i] + a.bhh[i];
+      gbias[H + i] = bih[H + i] + a.bhh[H + i];
+      gbias[2 * H + i] = bih[2 * H + i];
       gbias[3 * H + i] = a.bhh[2 * H + i];
     }
   }
@@ -189,7 +198,7 @@ __global__ __launch_bounds__(64 * MAXW, 2) void k_dense_split(DenseArgs a) {
   const int nkb0 = STACK ? kbh : (a.K0 + 15) / 16, nchunk = (nkb0 + kbc - 1) / kbc;
   const int kbx = CAT ? 2 * kbh : kbh;        // k-blocks of the time encoder's input
   const int64_t V = a.total_state_rows;
-  const WeightStream wsg = make_stream(a.Wg, STACK ? 0 : (int64_t)njb * nkb0 * kUnitBytes);
+  const WeightStream wsg = make_stream(FOLD ? a.Wf : a.Wg, STACK ? 0 : (int64_t)(FOLD ? NG : 1) * njb * nkb0 * kUnitBytes);
   const WeightStream wsi = make_stream(a.Wih, (int64_t)NG * njb * kbx * kUnitBytes);
   const WeightStream wsh = make_stream(a.Whh, (int64_t)NG * njb * kbh * kUnitBytes);
   const int offz = jb * nkb0 * kUnitBytes;
@@ -219,18 +228,29 @@ __global__ __launch_bounds__(64 * MAXW, 2) void k_dense_split(DenseArgs a) {
 #pragma unroll
     for (int q = 0; q < 2; ++q) load_x(p, min(c * kbc + 2 * jb + q, nkb0 - 1), xq[q]);
   };
+  // An infinite input makes NaN of the gates: Z's infinities have either sign, and so the gates' sums.  The folded
+  // weights would hide that.
+  auto put_row = [&](uint4* frag, const float4 (&x)[2]) {
+    if constexpr (FOLD) {
+      auto nan_of_inf = [](float4 v) { return make_float4(fmaf(v.x, 0.f, v.x), fmaf(v.y, 0.f, v.y), fmaf(v.z, 0.f, v.z), fmaf(v.w, 0.f, v.w)); };
+      const float4 y[2] = {nan_of_inf(x[0]), nan_of_inf(x[1])};
+      put_x(frag, y);
+    } else {
+      put_x(frag, x);
+    }
+  };
   auto stage_x = [&](int s, int c) {
     const int k0 = c * kbc, n = min(kbc, nkb0 - k0);
 #pragma unroll
     for (int q = 0; q < 2; ++q)
-      if (2 * jb + q < n) put_x(buf + (2 * jb + q) * 3 * kFrag, xq[q]);
+      if (2 * jb + q < n) put_row(buf + (2 * jb + q) * 3 * kFrag, xq[q]);
     for (int kb = 2 * (jb + njb); kb < n; kb += 2 * njb)
 #pragma unroll
       for (int q = 0; q < 2; ++q)
         if (kb + q < n) {
           float4 x[2];
           load_x(in_row(s), k0 + kb + q, x);
-          put_x(buf + (kb + q) * 3 * kFrag, x);
+          put_row(buf + (kb + q) * 3 * kFrag, x);
         }
   };
   // a 32-column block in registers -> k-blocks 2*jb, 2*jb + 1 of the other buffer
@@ -296,7 +316,38 @@ __global__ __launch_bounds__(64 * MAXW, 2) void k_dense_split(DenseArgs a) {
     auto hidden = [&](int g) -> floatx16& { return acc[!kLstm && g == 2 ? 3 : g]; };
     auto in = [&](int g) -> floatx16& { return acc[g]; };
     product<NG, DG, STACK>(hidden, hidden, buf, wsh, offh, gsh, kbh, lane16, wg);
-    if constexpr (!STACK) {
+    if constexpr (FOLD) {
+      if constexpr (!kLstm) acc[2] = load_block(gbias + 2 * H + col0);
+      if constexpr (CAT) {                    // the other half of the time encoder's input first
+        fetch_ahead<NG, DG>(wg, wsi, offx, gsx, kbh, lane16);
+        int64_t r2 = slot(ts);
+        if (a.x2_map) r2 = max(a.x2_map[r2], (int64_t)0);   // an empty slot reads row 0; its output is not used
+        turn();
+        put_block(load_block(a.X2 + r2 * a.ldx2 + col0));
+        __syncthreads();
+        product<NG, DG>(in, in, buf, wsi, offx, gsx, kbh, lane16, wg);
+      }
+      // The small part products apart, as in the transform that this stands for: a GRU's in sums of their own, an LSTM's (whose
+      // registers do not hold four more) for every k-block.
+      floatx16 sums[kLstm ? 1 : NG];
+      auto small = [&](int g) -> floatx16& { return sums[kLstm ? 0 : g]; };
+      if constexpr (!kLstm)
+#pragma unroll
+        for (int g = 0; g < NG; ++g) sums[g] = (floatx16)(0.f);
+      const int offf = jb * nkb0 * kUnitBytes, gsf = njb * nkb0 * kUnitBytes;
+      for (int k = 0; k < nchunk; ++k) {
+        const int n = min(kbc, nkb0 - k * kbc);
+        turn();
+        stage_x(s, k);
+        fetch_ahead<NG, DG>(wg, wsg, offf + k * kbc * kUnitBytes, gsf, n, lane16);
+        if (k + 1 < nchunk) request_x(s, k + 1);
+        __syncthreads();
+        product<NG, DG, kLstm>(in, small, buf, wsg, offf + k * kbc * kUnitBytes, gsf, n, lane16, wg);
+      }
+      if constexpr (!kLstm)
+#pragma unroll
+        for (int g = 0; g < NG; ++g) acc[g] += sums[g];
+    } else if constexpr (!STACK) {
       floatx16 z, zs = (floatx16)(0.f);
       for (int k = 0; k < nchunk; ++k) {
         const int n = min(kbc, nkb0 - k * kbc);
@@ -327,9 +378,11 @@ __global__ __launch_bounds__(64 * MAXW, 2) void k_dense_split(DenseArgs a) {
       turn();
       stage_x(s, 0);
     }
-    __syncthreads();
-    if constexpr (!kLstm) acc[2] = load_block(gbias + 2 * H + col0);
-    product<NG, DG, STACK>(in, in, buf, wsi, offx + (kbx - kbh) * kUnitBytes, gsx, kbh, lane16, wg);
+    if constexpr (!FOLD) {
+      __syncthreads();
+      if constexpr (!kLstm) acc[2] = load_block(gbias + 2 * H + col0);
+      product<NG, DG, STACK>(in, in, buf, wsi, offx + (kbx - kbh) * kUnitBytes, gsx, kbh, lane16, wg);
+    }
     // requests of the next step go out before this step's stores: memory operations retire in order
     if (mapped) {
       yrow = yrow_next;
@@ -474,33 +527,52 @@ __global__ void k_pack_split(const float* W, int64_t per_w, int64_t so, int64_t 
   for (int p = 0; p < 3; ++p) packed[((m * per + (f << 6)) * 3 + p * 64) + lane] = part[p];
 }
 
+// out[r][k] = sum over s of wih[r][s] wg[s][k], bias[r] = bih[r] + sum over s of wih[r][s] bg[s], both summed in double;
+// *bad if one of them is not finite.  One workgroup of 64 per (row, 64 columns); column K0 is the bias.
+struct FoldArgs { const float *wih, *wg, *bg, *bih; int64_t ld_wih; int32_t S, K0; float *out, *bias; int32_t* bad; };
+__global__ __launch_bounds__(64) void k_fold(FoldArgs a) {
+  const int r = blockIdx.y, k = blockIdx.x * 64 + threadIdx.x;
+  if (k > a.K0) return;
+  const float* w = a.wih + r * a.ld_wih;
+  double sum = k < a.K0 ? 0.0 : (double)a.bih[r];
+  const float* x = k < a.K0 ? a.wg + k : a.bg;
+  const int ldx = k < a.K0 ? a.K0 : 1;
+#pragma unroll 8
+  for (int s = 0; s < a.S; ++s) sum += (double)w[s] * (double)x[s * ldx];
+  const float f = (float)sum;
+  if (k < a.K0) a.out[(int64_t)r * a.K0 + k] = f;
+  else a.bias[r] = f;
+  if (!(fabsf(f) <= 3.4028234663852886e38f)) atomicOr(a.bad, 1);
+}
+
 constexpr size_t kMaxLds = 160 * 1024;
 constexpr int kCus = 256;
 
-template <int KIND, bool SEQ, bool CAT, bool STACK, int MAXW>
+template <int KIND, bool SEQ, bool CAT, Input INPUT, int MAXW>
 bool launch_time(DenseArgs a, int njb, hipStream_t st, std::string* why) {
-  const int nkb0 = STACK ? 2 * njb : (a.K0 + 15) / 16;
+  const int nkb0 = INPUT == kStack ? 2 * njb : (a.K0 + 15) / 16;
   // a staging buffer holds the state's k-blocks, and of a wider input row what 48 KB take
   a.kb_chunk = std::max(2 * njb, std::min(nkb0, 48 * 1024 / kUnitBytes));
   const size_t lds = (size_t)2 * a.kb_chunk * kUnitBytes + sizeof(float) * 5 * 32 * njb;
   static std::atomic<uint64_t> ready{0};
-  auto* kernel = &k_dense_split<KIND, SEQ, CAT, STACK, MAXW>;
+  auto* kernel = &k_dense_split<KIND, SEQ, CAT, INPUT, MAXW>;
   if (!allow_lds(reinterpret_cast<const void*>(kernel), kMaxLds, ready, why)) return false;
   if (a.n_tiles32 > 0) hipLaunchKernelGGL(kernel, (unsigned)a.n_tiles32, 64 * njb, lds, st, a);
   return true;
 }
 
+template <int KIND, bool CAT, Input INPUT, int MAXW>
+bool launch_seq(const DenseArgs& a, int njb, hipStream_t st, std::string* why) {
+  return a.seq_in ? launch_time<KIND, true, CAT, INPUT, MAXW>(a, njb, st, why) : launch_time<KIND, false, CAT, INPUT, MAXW>(a, njb, st, why);
+}
+
 template <int KIND, int MAXW>
 bool launch_variant(const DenseArgs& a, int njb, hipStream_t st, std::string* why) {
-  const bool seq = a.seq_in != nullptr;
-  if (a.input_is_z) return seq ? launch_time<KIND, true, false, true, MAXW>(a, njb, st, why)
-                               : launch_time<KIND, false, false, true, MAXW>(a, njb, st, why);
+  if (a.input_is_z) return launch_seq<KIND, false, kStack, MAXW>(a, njb, st, why);
   if constexpr (KIND == DGC_TIME_LSTM) {
-    if (a.X2) return seq ? launch_time<KIND, true, true, false, MAXW>(a, njb, st, why)
-                         : launch_time<KIND, false, true, false, MAXW>(a, njb, st, why);
+    if (a.X2) return a.Wf ? launch_seq<KIND, true, kFolded, MAXW>(a, njb, st, why) : launch_seq<KIND, true, kTransform, MAXW>(a, njb, st, why);
   }
-  return seq ? launch_time<KIND, true, false, false, MAXW>(a, njb, st, why)
-             : launch_time<KIND, false, false, false, MAXW>(a, njb, st, why);
+  return a.Wf ? launch_seq<KIND, false, kFolded, MAXW>(a, njb, st, why) : launch_seq<KIND, false, kTransform, MAXW>(a, njb, st, why);
 }
 
 template <int KIND>
@@ -560,6 +632,17 @@ bool launch_dense_split(const DenseArgs& a, hipStream_t st, std::string* why) {
     case DGC_TIME_LSTM: return launch_kind<DGC_TIME_LSTM>(a, njb, st, why);
   }
   return false;
+}
+
+// MFMAs of a tile and 32 columns, in k-blocks: the gates over the input's width against the transform and the gates over its output's.
+bool dense_fold_wanted(int32_t S, int32_t K0, int32_t time_kind) {
+  const int ng = time_kind == DGC_TIME_LSTM ? 4 : 3, kbh = S / 16, nkb0 = (K0 + 15) / 16;
+  return ng * nkb0 < nkb0 + ng * kbh;
+}
+
+void launch_fold(const float* wih, int64_t ld_wih, const float* wg, const float* bg, const float* bih, int32_t gH, int32_t S, int32_t K0,
+                 float* out, float* bias, int32_t* bad, hipStream_t st) {
+  hipLaunchKernelGGL(k_fold, dim3((unsigned)(K0 / 64 + 1), (unsigned)gH), 64, 0, st, FoldArgs{wih, wg, bg, bih, ld_wih, S, K0, out, bias, bad});
 }
 
 void launch_pack_split(const float* W, int64_t per_w, int64_t out_stride, int64_t in_stride, int32_t n_out, int32_t n_in,

@@ -208,6 +208,9 @@ struct DenseArgs {
   // [T,N,ldm] tensor and are the time encoder's input as they are (no transform, K0 = 0).
   // M may be Y itself: a wave requests row (t, v) before step t and writes it at that step's end.
   bool input_is_z;
+  // The transform folded into the input side of the time encoder (no activation between them), or nullptr: packed
+  // [gH][K0] = W_ih W_g (with X2: the second half of W_ih), bias [gH] = b_ih + W_ih b_g.  Wg and bg are then not read.
+  const float4* Wf; const float* bf;
   bool narrow;                  // the weights are packed for the narrow kernel, which runs
 };
 // returns false if the (S,H,K0) combination has no kernel
@@ -229,6 +232,10 @@ inline int64_t split_weight_bytes(int32_t n_out, int32_t n_in) {
   return (int64_t)(n_out / 32) * ((n_in + 15) / 16) * 3 * 64 * 16;
 }
 // `count` matrices, per_w floats apart, element (out, in) at out * out_stride + in * in_stride
+bool dense_fold_wanted(int32_t S, int32_t K0, int32_t time_kind);   // whether folding saves products
+// out [gH][K0], bias [gH]; *bad is set where a value is not finite
+void launch_fold(const float* wih, int64_t ld_wih, const float* wg, const float* bg, const float* bih, int32_t gH, int32_t S, int32_t K0,
+                 float* out, float* bias, int32_t* bad, hipStream_t st);
 void launch_pack_split(const float* W, int64_t per_w, int64_t out_stride, int64_t in_stride, int32_t n_out, int32_t n_in,
                        int64_t count, void* packed, hipStream_t st);
 size_t dense_lds_bytes(int32_t K0, int32_t S, int32_t H);
