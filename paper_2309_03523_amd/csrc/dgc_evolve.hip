@@ -286,7 +286,9 @@ __global__ __launch_bounds__(64 * (NW <= 8 ? 2 * NW : NW)) void k_ev_walk(EvWalk
 // their partial tiles are added in wave order (reproducible).  TM = 32 halves what is read per product, TM = 16 gives a
 // small matrix more workgroups.  v_mfma_f64_16x16x4f64: lane l supplies A[l%16][l/16], B[l/16][l%16] and receives
 // D[4*v + l/16][l%16]; four consecutive columns of a lane are four instructions.
-struct EvGradArgs { int32_t T, n; const double *Wt, *Rg, *Ah, *Az, *Ar; float* G[EV_NPAR]; };
+// Jobs 4 to 7 take the walk's own four gradients to where the caller reads them (the walk writes 16 bytes of a row at a
+// time, which is no way to write to host memory).
+struct EvGradArgs { int32_t T, n; const double *Wt, *Rg, *Ah, *Az, *Ar; const float* walk; float* G[EV_NPAR]; };
 
 template <int TM>
 __global__ __launch_bounds__(512) void k_ev_grads(EvGradArgs a) {
@@ -295,6 +297,14 @@ __global__ __launch_bounds__(512) void k_ev_grads(EvGradArgs a) {
   const int n = a.n, job = blockIdx.z;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, l16 = lane & 15, kq = lane >> 4;
   const int m0 = blockIdx.y * TM, n0 = blockIdx.x * TM;
+  if (job >= 4) {
+    float* G = a.G[job == 4 ? EV_W : job == 5 ? EV_BZ : job == 6 ? EV_BR : EV_BH];
+    for (int i = tid; i < TM * TM; i += 512) {
+      const int64_t e = (int64_t)(m0 + i / TM) * n + n0 + i % TM;
+      G[e] = a.walk[(int64_t)(job - 4) * n * n + e];
+    }
+    return;
+  }
   const double* A = job < 2 ? a.Ah : job == 2 ? a.Az : a.Ar;
   const int per_t = n / 16, units = a.T * per_t;
   const int64_t nn = (int64_t)n * n;
@@ -584,7 +594,8 @@ void launch_walk(const EvolveWs& ws, hipStream_t st) {
   a.packed = reinterpret_cast<const doublex2*>(ws.walk_packed);
   a.Wt = ws.Wt; a.Zg = ws.Zg; a.Rg = ws.Rg; a.Wc = ws.Wc; a.Wt_f32 = ws.Wt_f32; a.dWd = ws.dWd;
   a.Ah = ws.Ah; a.Az = ws.Az; a.Ar = ws.Ar;
-  a.gW = ws.G[EV_W]; a.gBz = ws.G[EV_BZ]; a.gBr = ws.G[EV_BR]; a.gBh = ws.G[EV_BH];
+  const int64_t nn = (int64_t)n * n;
+  a.gW = ws.walk_grads; a.gBz = a.gW + nn; a.gBr = a.gBz + nn; a.gBh = a.gBr + nn;
   if (n > 64) {
     EvPackArgs p{};
     for (int k = 0; k < EV_NPAR; ++k) p.P[k] = ws.P[k];
@@ -687,10 +698,10 @@ bool evolve_backward_dw(const EvolveWs& ws, const EvolveBwdIn& in, bool keep_dp,
 void evolve_backward_bptt(const EvolveWs& ws, hipStream_t st) {
   launch_walk<true>(ws, st);
   EvGradArgs g{};
-  g.T = ws.T; g.n = ws.F; g.Wt = ws.Wt; g.Rg = ws.Rg; g.Ah = ws.Ah; g.Az = ws.Az; g.Ar = ws.Ar;
+  g.T = ws.T; g.n = ws.F; g.Wt = ws.Wt; g.Rg = ws.Rg; g.Ah = ws.Ah; g.Az = ws.Az; g.Ar = ws.Ar; g.walk = ws.walk_grads;
   for (int k = 0; k < EV_NPAR; ++k) g.G[k] = ws.G[k];
-  if (ws.F <= 128) hipLaunchKernelGGL((k_ev_grads<16>), dim3(ws.F / 16, ws.F / 16, 4), 512, 0, st, g);
-  else hipLaunchKernelGGL((k_ev_grads<32>), dim3(ws.F / 32, ws.F / 32, 4), 512, 0, st, g);
+  if (ws.F <= 128) hipLaunchKernelGGL((k_ev_grads<16>), dim3(ws.F / 16, ws.F / 16, 8), 512, 0, st, g);
+  else hipLaunchKernelGGL((k_ev_grads<32>), dim3(ws.F / 32, ws.F / 32, 8), 512, 0, st, g);
 }
 
 }  // namespace dgc
