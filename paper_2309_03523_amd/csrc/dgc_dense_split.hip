@@ -20,9 +20,9 @@
 // What bounds them: the matrix cores' power.  Random operands through a loop of nothing but this MFMA reach
 // 1.8 PFLOP/s of bf16 on this GPU (2.46 with zeros), a library product 1.33; the time encoders run at 1.1, at 1.6 GHz in
 // the mean with the matrix units busy for two cycles of three
-// (GRU 128 wide, 3.2 M rows: 6.27 ms on the fp32 instruction, 3.93 ms here; the two LSTM layers of MPNN-LSTM over
-// 1.28 M rows 6.90 + 4.35 -> 2.9 + 1.95 ms; GRU 256 wide, 160 k rows 2.29 -> 0.9 ms).  Without the weights' loads,
-// the LDS reads and the gate arithmetic the first would still take 3.5 ms.  Tiles of 64 vertices halve the weights'
+// (GRU 128 wide, 3.2 M rows: 6.27 ms on the fp32 instruction, 3.93 ms here, 3.5 with the transform folded; the two LSTM layers of
+// MPNN-LSTM over 1.28 M rows 6.90 + 4.35 -> 2.9 + 1.95 ms, the first 2.78 folded; GRU 256 wide, 160 k rows 2.29 -> 0.9, 0.85).  Without the weights' loads,
+// the LDS reads and the gate arithmetic the first would still take 3.5 ms (of 3.93), with half of the products 2.7.  Tiles of 64 vertices halve the weights'
 // L2 traffic and are no faster (4.15 ms: two workgroups of 256 registers a wave, more work behind each barrier);
 // three workgroups per CU of 168 registers spill (4.36 ms).
 //
@@ -151,7 +151,7 @@ __device__ __forceinline__ void relu(floatx16& z) {
 // What a row of M is to the time encoder: Z's operand; its input by way of the folded weights (no transform: where no
 // activation stands between them, W_ih (W_g m + b_g) = (W_ih W_g) m + W_ih b_g); its input as it is (a second recurrent layer).
 // Folding takes 48 of 336 MFMAs a tile and step from a GRU 128 wide over 128 columns, and the matrix cores' power is what bounds
-// the kernel: 32 x 100 000 vertices 4.05 -> 3.45 ms, the two GCN layers and LSTM of MPNN-LSTM (624 -> 576) 2.92 -> 2.70.  The product of
+// the kernel: 32 x 100 000 vertices 4.05 -> 3.5 ms, MPNN-LSTM's first LSTM layer with the concatenated input (624 -> 576) 2.92 -> 2.78.  The product of
 // the weights is summed in double and rounded once, where Z was rounded, so nothing gets further from 64 bits (0.87 of the
 // distance in the mean of 46 outputs of GRUs, 0.94 of 24 of LSTMs, 0.999 at most).
 enum Input { kTransform, kFolded, kStack };

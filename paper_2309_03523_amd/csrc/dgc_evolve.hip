@@ -5,9 +5,8 @@
 // evolved once per snapshot over all T snapshots (global, independent of the chunk windows),
 // Y[t,i] = relu(M[t,i] W_t), mean-squared-error loss, gradients of all ten parameter matrices.
 //
-// Kernels here: a double-precision MFMA kernel that fuses the small (F x F)(F x S) products of
-// one step of the weight recurrence, or of its back-propagation through time, with the gate
-// arithmetic that follows them (latency-bound), and the one large kernel of the backward pass,
+// Kernels here: the weight recurrence and its back-propagation in double precision on f64 MFMA, one launch each that
+// walks all snapshots, the parameter gradients as one launch after it, and the one large kernel of the backward pass,
 // dW_t = M_t^T dP_t reduced over all rows of snapshot t across the fused chunks.
 #include <algorithm>
 

@@ -61,6 +61,31 @@ def test_parameters_change():
     dw.layer.destroy()
 
 
+def test_parameters_change_under_a_captured_forward():
+    """A graph captured before the parameters change replays with the ones that are set."""
+    import torch
+    from paper_2309_03523_amd.runner import DeviceWorkload
+    wl = synth.random_small(13, 4, 70, 96, 96, 96, 4.0, CHUNKS, "lstm")
+    other = synth.random_small(14, 4, 70, 96, 96, 96, 4.0, CHUNKS, "lstm").params
+    dw = DeviceWorkload(wl)
+    dw.forward()
+    side = torch.cuda.Stream()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=side):
+        dw.layer.forward(dw.X, dw.C, dw.Y, C1=dw.C1, H0=dw.H0)
+    for name in wl.params:
+        wl.params[name] = other[name]
+        dw.layer.set_param(name, other[name])
+        eager = dw.forward().clone()
+        dw.Y.fill_(float("nan"))
+        torch.cuda.synchronize()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(torch.nan_to_num(dw.Y, nan=-7.0), torch.nan_to_num(eager, nan=-7.0)), name
+    _close(dw.Y.cpu().numpy(), _oracle(wl, "lstm"))
+    dw.layer.destroy()
+
+
 def test_parameters_never_set():
     from paper_2309_03523_amd import binding
     from paper_2309_03523_amd.runner import DeviceWorkload
