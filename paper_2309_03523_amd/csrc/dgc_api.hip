@@ -1375,6 +1375,7 @@ dgc_status_t dgc_layer_backward(dgc_layer_t* L, const void* Yv, int64_t ldy, con
     da.Wg = L->d_Wt_plain; da.bg = L->d_zero_bias;
     da.wg_step_bytes = evolve_packed_bytes(L->evo, L->evo.split);
     da.Y = L->d_dM; da.ldy = d.F;
+    da.shares_chip = true;        // with the back-propagation
     if (!launch_dense(da, st, &why)) return fail(DGC_ERR_UNSUPPORTED, why);
     SpmmArgs sa = spmm_args(L, L->d_dM, d.F, L->d_dM, d.F, d.F, static_cast<float*>(dX), d.F);
     sa.ld_out = lddx;

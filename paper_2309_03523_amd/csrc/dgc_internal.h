@@ -168,6 +168,7 @@ struct DenseArgs {
   const DenseTile* tiles32;     // 32-row tiles of the split kernel
   int64_t n_tiles32;
   const DenseTile* row_tiles;   // 32-row tiles of single snapshots, ordered by snapshot (transforms alone)
+  bool shares_chip;             // transforms alone: another launch of the layer runs beside this one
   int64_t n_row_tiles;
   int32_t kb_chunk;             // set by the launch: k-blocks of 16 that a staging buffer holds
   int32_t variant;              // DGC_DENSE_*
