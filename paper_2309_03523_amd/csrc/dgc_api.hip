@@ -381,6 +381,7 @@ dgc_status_t build_evolve(dgc_layer* L, const std::vector<ChunkInfo>& cinfo, hip
   if ((rc = add_gradients(L, kEvolveNames, ev.G)) != DGC_OK) return rc;
   DGC_HIP_TRY(dev_alloc(L, &ev.walk_grads, 4 * n));
   DGC_HIP_TRY(dev_alloc(L, &ev.Wt_f32, T * n));
+  DGC_HIP_TRY(dev_alloc(L, &ev.kept, 6 * n));
   DGC_HIP_TRY(dev_alloc(L, &ev.walk_packed, evolve_walk_elems(ev)));
   DGC_HIP_TRY(dev_alloc(L, &ev.Wt, (T + 1) * n));
   DGC_HIP_TRY(dev_alloc(L, &ev.Zg, T * n));

@@ -43,7 +43,8 @@ __device__ __forceinline__ double sigmoidd(double x) { return 1.0 / (1.0 + exp(-
 
 struct EvWalkArgs {
   int32_t T;
-  const float* P[EV_NPAR];
+  const float* P[EV_NPAR];         // back: U and V are those kept
+  float* kept;                     // forward, resident: ev_keep
   const doublex2* packed;          // streamed matrices (ev_packed_index); unused where they are resident
   double *Wt, *Zg, *Rg, *Wc;       // Wt[0] = W_init, Wt[t + 1] = W_t
   float* Wt_f32;
@@ -65,18 +66,30 @@ __device__ __forceinline__ double ev_weight(const float* const (&P)[EV_NPAR], in
   }
 }
 
+// The way back is that of the parameters which the forward pass used, whatever has been set since: the first launch of a forward
+// keeps its U and V, [6][n][n], in the order of kKept (beside its loads of them; 1 us at most).
+constexpr int kKept[6] = {EV_UZ, EV_VZ, EV_UR, EV_VR, EV_UH, EV_VH};
+__device__ __forceinline__ void ev_keep(const float* const (&P)[EV_NPAR], float* kept, int n, int first, int stride) {
+  const int quads = n * n / 4;
+#pragma unroll
+  for (int m = 0; m < 6; ++m)
+    for (int i = first; i < quads; i += stride)
+      reinterpret_cast<float4*>(kept)[m * quads + i] = reinterpret_cast<const float4*>(P[kKept[m]])[i];
+}
+
 // A batch is 32 columns of a wave's 16 rows: pair q of lane l holds row groups 2 (q % 2), + 1 of stretch 2 batch + q / 2.
 struct EvElement { int row, k; };
 __device__ __forceinline__ EvElement ev_element(int wave, int batch, int q, int half, int lane) {
   return {16 * wave + 4 * (2 * (q & 1) + half) + (lane & 3), 16 * (2 * batch + (q >> 1)) + (lane & 12) + (lane >> 4)};
 }
 
-struct EvPackArgs { const float* P[EV_NPAR]; doublex2* packed; int32_t n; };
+struct EvPackArgs { const float* P[EV_NPAR]; float* kept; doublex2* packed; int32_t n; };
 template <bool BACK>
 __global__ __launch_bounds__(256) void k_ev_pack(EvPackArgs a) {
   const int nw = a.n / 16, nb = nw / 2;
   const int idx = blockIdx.x * blockDim.x + threadIdx.x;      // ((m * nw + wave) * nb + batch) * 256 + q * 64 + lane
   if (idx >= 4 * nw * nb * 256) return;
+  if constexpr (!BACK) ev_keep(a.P, a.kept, a.n, idx, 4 * nw * nb * 256);
   const int lane = idx & 63, q = (idx >> 6) & 3;
   int r = idx >> 8;
   const int batch = r % nb; r /= nb;
@@ -271,6 +284,7 @@ template <int NW, bool BACK>
 __global__ __launch_bounds__(64 * (NW <= 8 ? 2 * NW : NW)) void k_ev_walk(EvWalkArgs a) {
   __shared__ double lds[4 * 16 * NW * 4];
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  if constexpr (!BACK && NW <= 4) ev_keep(a.P, a.kept, 16 * NW, blockIdx.x * blockDim.x + threadIdx.x, gridDim.x * blockDim.x);
   if constexpr (NW <= 8) {
     if (wave >= NW) ev_walk<NW, 1, BACK>(a, wave - NW, lds);
     else ev_walk<NW, 2, BACK>(a, wave, lds);
@@ -590,6 +604,9 @@ void launch_walk(const EvolveWs& ws, hipStream_t st) {
   EvWalkArgs a{};
   a.T = ws.T;
   for (int k = 0; k < EV_NPAR; ++k) a.P[k] = ws.P[k];
+  if (BACK)
+    for (int k = 0; k < 6; ++k) a.P[kKept[k]] = ws.kept + (int64_t)k * n * n;
+  a.kept = ws.kept;
   a.packed = reinterpret_cast<const doublex2*>(ws.walk_packed);
   a.Wt = ws.Wt; a.Zg = ws.Zg; a.Rg = ws.Rg; a.Wc = ws.Wc; a.Wt_f32 = ws.Wt_f32; a.dWd = ws.dWd;
   a.Ah = ws.Ah; a.Az = ws.Az; a.Ar = ws.Ar;
@@ -597,7 +614,8 @@ void launch_walk(const EvolveWs& ws, hipStream_t st) {
   a.gW = ws.walk_grads; a.gBz = a.gW + nn; a.gBr = a.gBz + nn; a.gBh = a.gBr + nn;
   if (n > 64) {
     EvPackArgs p{};
-    for (int k = 0; k < EV_NPAR; ++k) p.P[k] = ws.P[k];
+    for (int k = 0; k < EV_NPAR; ++k) p.P[k] = a.P[k];
+    p.kept = ws.kept;
     p.packed = reinterpret_cast<doublex2*>(ws.walk_packed);
     p.n = n;
     hipLaunchKernelGGL((k_ev_pack<BACK>), blocks_for(evolve_walk_elems(ws) / 2), 256, 0, st, p);

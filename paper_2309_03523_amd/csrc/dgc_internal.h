@@ -251,6 +251,7 @@ struct EvolveWs {
   const float* P[EV_NPAR];   // parameters (device, fp32): W_init, Uz, Vz, Bz, Ur, Vr, Br, Uh, Vh, Bh
   float* G[EV_NPAR];         // their gradients (fp32, what the caller reads; pinned host memory)
   float* walk_grads;         // [4][F][S]: those of W_init, B_z, B_r, B_h as the recurrence leaves them, on the device
+  float* kept;               // [6][F][F] U and V as the last forward found them, for the backward
   double* walk_packed;       // matrices of the weight recurrence that are read at every step (evolve_walk_elems)
   double* Wt;                // [T+1][F][S]: W_init, then the evolved weights
   double *Zg, *Rg, *Wc;      // [T][F][S]: the gates that produced them
