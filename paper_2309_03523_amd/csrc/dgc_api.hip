@@ -387,9 +387,6 @@ dgc_status_t build_evolve(dgc_layer* L, const std::vector<ChunkInfo>& cinfo, hip
   DGC_HIP_TRY(dev_alloc(L, &ev.Zg, T * n));
   DGC_HIP_TRY(dev_alloc(L, &ev.Rg, T * n));
   DGC_HIP_TRY(dev_alloc(L, &ev.Wc, T * n));
-  DGC_HIP_TRY(dev_alloc(L, &ev.Ah, T * n));
-  DGC_HIP_TRY(dev_alloc(L, &ev.Az, T * n));
-  DGC_HIP_TRY(dev_alloc(L, &ev.Ar, T * n));
   float* pk = nullptr;
   DGC_HIP_TRY(dev_alloc(L, &pk, (int64_t)T * evolve_packed_bytes(ev, ev.split) / (int64_t)sizeof(float)));
   ev.Wt_packed = reinterpret_cast<float4*>(pk);
@@ -397,7 +394,12 @@ dgc_status_t build_evolve(dgc_layer* L, const std::vector<ChunkInfo>& cinfo, hip
   int64_t most = 1;
   for (int32_t t = 0; t < T; ++t) most = std::max(most, L->row_tile_ptr[t + 1] - L->row_tile_ptr[t]);
   ev.split_dw = evolve_dw_split(T, F, most);
-  DGC_HIP_TRY(dev_alloc(L, &ev.partial, evolve_partial_elems(ev)));
+  // the gradients of the gates' arguments lie where the partial sums of the weight gradients have been (six floats an element
+  // against at least eight partial sums, but where a snapshot has fewer than eight row tiles)
+  DGC_HIP_TRY(dev_alloc(L, &ev.partial, std::max(evolve_partial_elems(ev), 6 * T * n)));
+  ev.Ah = reinterpret_cast<double*>(ev.partial);
+  ev.Az = ev.Ah + T * n;
+  ev.Ar = ev.Az + T * n;
   DGC_HIP_TRY(dev_alloc(L, &ev.loss_partial, evolve_loss_partial_elems(ev)));
   DGC_HIP_TRY(dev_alloc(L, &L->d_zero_bias, S));
   DGC_HIP_TRY(hipMemsetAsync(L->d_zero_bias, 0, sizeof(float) * S, st));

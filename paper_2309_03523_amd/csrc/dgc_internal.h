@@ -255,7 +255,7 @@ struct EvolveWs {
   double* walk_packed;       // matrices of the weight recurrence that are read at every step (evolve_walk_elems)
   double* Wt;                // [T+1][F][S]: W_init, then the evolved weights
   double *Zg, *Rg, *Wc;      // [T][F][S]: the gates that produced them
-  double *Ah, *Az, *Ar;      // [T][F][S]: gradients of the gates' arguments
+  double *Ah, *Az, *Ar;      // [T][F][S]: gradients of the gates' arguments (in the memory of `partial`, which is read before they are written)
   float* Wt_f32;             // [T][F][S]: W_t rounded to fp32
   float4* Wt_packed;         // every W_t^T (fp32) in MFMA fragment order
   float* dWd;                // [T][F][S] direct gradient of each W_t

@@ -8,6 +8,7 @@
 
 static std::vector<std::string> calls;      // launches and stream operations, in order
 static int allocations = 0, fails_at = 0;   // the fails_at-th allocation fails (0: none)
+static size_t bytes_allocated = 0;          // of device memory
 static hipError_t last_error = hipSuccess;
 static int device = 0;
 static bool null_pointer = false;           // a launcher was handed one
@@ -25,6 +26,7 @@ static void expect(bool ok, const char* what) {
 
 extern "C" {
 hipError_t hipMalloc(void** p, size_t n) {
+  bytes_allocated += n;
   if (++allocations == fails_at) return last_error = hipErrorOutOfMemory;
   *p = std::calloc(n ? n : 1, 1);
   return hipSuccess;
@@ -49,6 +51,10 @@ hipError_t hipFuncSetAttribute(const void*, hipFuncAttribute, int bytes) {
   calls.push_back("allow " + std::to_string(bytes));
   return fails_at < 0 ? hipErrorInvalidValue : hipSuccess;
 }
+hipError_t hipHostMalloc(void** p, size_t n, unsigned) { *p = std::calloc(n, 1); return hipSuccess; }
+hipError_t hipMemsetAsync(void* p, int value, size_t n, hipStream_t) { std::memset(p, value, n); return hipSuccess; }
+hipError_t hipStreamCreateWithFlags(hipStream_t* s, unsigned) { *s = nullptr; return hipSuccess; }
+hipError_t hipEventCreateWithFlags(hipEvent_t* e, unsigned) { *e = nullptr; return hipSuccess; }
 hipError_t hipStreamDestroy(hipStream_t) { return hipSuccess; }
 hipError_t hipEventDestroy(hipEvent_t) { return hipSuccess; }
 }
@@ -59,6 +65,10 @@ bool launch_dense(const DenseArgs& a, hipStream_t, std::string*) { launched("den
 void evolve_forward_weights(const EvolveWs&, hipStream_t) { launched("recurrence", {}); }
 bool evolve_backward_dw(const EvolveWs&, const EvolveBwdIn&, bool, hipStream_t, std::string*) { launched("weight gradient", {}); return true; }
 void evolve_backward_bptt(const EvolveWs&, hipStream_t) { launched("back-propagation", {}); }
+int32_t evolve_dw_split(int32_t, int32_t, int64_t most_tiles) { return (int32_t)std::min<int64_t>(8, most_tiles); }
+int64_t evolve_partial_elems(const EvolveWs& ws) { return (int64_t)ws.T * ws.split_dw * ws.F * ws.S; }
+int64_t evolve_loss_partial_elems(const EvolveWs& ws) { return (int64_t)ws.T * ws.split_dw; }
+bool dense_split_supported(int32_t, int32_t, int32_t) { return true; }
 void evolve_row_index(const ChunkInfo*, int32_t, int64_t, int32_t, int64_t, int64_t* idx, hipStream_t) { launched("row index", {idx}); }
 void evolve_pack_weights_plain(const EvolveWs&, float4* packed, hipStream_t) { launched("pack", {packed}); }
 void labels_build(const GraphDev&, const Segment*, const int32_t*, int32_t* col, int64_t* in, int64_t* out, hipStream_t) {
@@ -131,6 +141,26 @@ static void label_memory() {
   }
 }
 
+// What an EvolveGCN-O layer keeps per snapshot beside the partial sums of the weight gradients: the weights and gates in double,
+// the weights in fp32 and packed, their direct gradient.  The gradients of the gates' arguments are not on top of that.
+static void evolve_memory() {
+  for (int64_t tiles : {8, 3}) {
+    dgc_layer L;
+    L.desc.struct_kind = DGC_STRUCT_EVOLVE_GCN_O;
+    L.desc.F = L.desc.S = 64;
+    L.T = 200;
+    for (int64_t t = 0; t <= L.T; ++t) L.row_tile_ptr.push_back(t * tiles);
+    bytes_allocated = 0;
+    expect(build_evolve(&L, {}, nullptr) == DGC_OK, "the layer is built");
+    const size_t n = 64 * 64, per_snapshot = n * (4 * sizeof(double) + sizeof(float) + 6 + sizeof(float));
+    const size_t partial = n * sizeof(float) * std::max<size_t>(tiles, 6), once = n * 48 * sizeof(float) + 65536;
+    expect(bytes_allocated <= 200 * (per_snapshot + partial) + once, "memory is that of the partial sums, the weights and the gates");
+    const char *first = reinterpret_cast<char*>(L.evo.partial), *end = first + 200 * partial;
+    for (double* a : {L.evo.Ah, L.evo.Az, L.evo.Ar})
+      expect(reinterpret_cast<char*>(a) >= first && reinterpret_cast<char*>(a + 200 * n) <= end, "the arguments' gradients lie in it");
+  }
+}
+
 // The events around a stage enclose its launches and nothing else: the caller's stream waits for the weight recurrence
 // after the aggregation's last event and before the dense stage's first; no stage 1 or 2 without a second GCN layer.
 static void stage_events() {
@@ -182,6 +212,7 @@ int main(int argc, char** argv) {
   else if (check == "label memory") label_memory();
   else if (check == "stage events") stage_events();
   else if (check == "lds per device") lds_per_device();
+  else if (check == "evolve memory") evolve_memory();
   else expect(false, "the check is known");
   std::puts("so");
   return 0;
