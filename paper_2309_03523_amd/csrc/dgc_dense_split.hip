@@ -228,8 +228,8 @@ __global__ __launch_bounds__(64 * MAXW, 2) void k_dense_split(DenseArgs a) {
 #pragma unroll
     for (int q = 0; q < 2; ++q) load_x(p, min(c * kbc + 2 * jb + q, nkb0 - 1), xq[q]);
   };
-  // An infinite input makes NaN of the gates: Z's infinities have either sign, and so the gates' sums.  The folded
-  // weights would hide that.
+  // An infinite input makes NaN of the gates: Z's infinities have either sign, and so the gates' sums (k_fold finds the weights
+  // of which this is not true, and they are not folded).  The folded weights would hide that.
   auto put_row = [&](uint4* frag, const float4 (&x)[2]) {
     if constexpr (FOLD) {
       auto nan_of_inf = [](float4 v) { return make_float4(fmaf(v.x, 0.f, v.x), fmaf(v.y, 0.f, v.y), fmaf(v.z, 0.f, v.z), fmaf(v.w, 0.f, v.w)); };
@@ -527,8 +527,11 @@ __global__ void k_pack_split(const float* W, int64_t per_w, int64_t so, int64_t 
   for (int p = 0; p < 3; ++p) packed[((m * per + (f << 6)) * 3 + p * 64) + lane] = part[p];
 }
 
-// out[r][k] = sum over s of wih[r][s] wg[s][k], bias[r] = bih[r] + sum over s of wih[r][s] bg[s], both summed in double;
-// *bad if one of them is not finite.  One workgroup of 64 per (row, 64 columns); column K0 is the bias.
+// out[r][k] = sum over s of wih[r][s] wg[s][k], bias[r] = bih[r] + sum over s of wih[r][s] bg[s], both summed in double.
+// *bad where the transform would do better: a value is not finite; or an
+// infinity in column k need not make NaN of gate r.  It does, whatever the other columns hold, where a weight is zero or the
+// products have both signs, as those of ordinary weights do; products of one sign would leave a saturated gate.
+// One workgroup of 64 per (row, 64 columns); column K0 is the bias.
 struct FoldArgs { const float *wih, *wg, *bg, *bih; int64_t ld_wih; int32_t S, K0; float *out, *bias; int32_t* bad; };
 __global__ __launch_bounds__(64) void k_fold(FoldArgs a) {
   const int r = blockIdx.y, k = blockIdx.x * 64 + threadIdx.x;
@@ -537,12 +540,18 @@ __global__ __launch_bounds__(64) void k_fold(FoldArgs a) {
   double sum = k < a.K0 ? 0.0 : (double)a.bih[r];
   const float* x = k < a.K0 ? a.wg + k : a.bg;
   const int ldx = k < a.K0 ? a.K0 : 1;
+  bool up = k == a.K0, down = up;       // some product is positive (zero), negative (zero)
 #pragma unroll 8
-  for (int s = 0; s < a.S; ++s) sum += (double)w[s] * (double)x[s * ldx];
+  for (int s = 0; s < a.S; ++s) {
+    const double p = (double)w[s] * (double)x[s * ldx];
+    up |= p >= 0.0;
+    down |= p <= 0.0;
+    sum += p;
+  }
   const float f = (float)sum;
   if (k < a.K0) a.out[(int64_t)r * a.K0 + k] = f;
   else a.bias[r] = f;
-  if (!(fabsf(f) <= 3.4028234663852886e38f)) atomicOr(a.bad, 1);
+  if (!(fabsf(f) <= 3.4028234663852886e38f) || !up || !down) atomicOr(a.bad, 1);
 }
 
 constexpr size_t kMaxLds = 160 * 1024;

@@ -126,3 +126,17 @@ def test_not_finite():
     dw.layer.destroy()
     want = _oracle(wl, "gru")
     assert np.isfinite(Y).all() and np.abs(Y - want).mean() < 1e-4
+
+
+@pytest.mark.parametrize("kind", ["gru", "lstm"])
+@pytest.mark.parametrize("sign", [1, -1])
+def test_infinite_inputs_of_weights_of_one_sign(kind, sign):
+    """Weights whose products have one sign saturate the gates for an infinite input, and the outputs are finite: the oracle's."""
+    from paper_2309_03523_amd.runner import run_forward
+    wl = synth.random_small(15, 3, 40, 128, 128, 128, 0.0, [[0, 40, 0, 3]], kind)      # no edges: a row sees itself
+    wl.params["gcn0.weight"] = np.maximum(np.abs(wl.params["gcn0.weight"]), np.float32(1e-3))
+    wl.params["rnn.weight_ih"] = sign * np.maximum(np.abs(wl.params["rnn.weight_ih"]), np.float32(1e-3))
+    wl.X[1, 5, 7], wl.X[2, 9, 0] = np.inf, -np.inf
+    got = run_forward(wl)
+    assert np.isfinite(got).all()
+    assert rel_err(got, _oracle(wl, kind)) < 1e-4
