@@ -528,7 +528,7 @@ __global__ void k_pack_split(const float* W, int64_t per_w, int64_t so, int64_t 
 }
 
 // out[r][k] = sum over s of wih[r][s] wg[s][k], bias[r] = bih[r] + sum over s of wih[r][s] bg[s], both summed in double.
-// *bad where the transform would do better: a value is not finite; or an
+// *bad where the transform would do better: a value is not finite; it is below what three bf16 parts hold (2^-110); or an
 // infinity in column k need not make NaN of gate r.  It does, whatever the other columns hold, where a weight is zero or the
 // products have both signs, as those of ordinary weights do; products of one sign would leave a saturated gate.
 // One workgroup of 64 per (row, 64 columns); column K0 is the bias.
@@ -551,7 +551,8 @@ __global__ __launch_bounds__(64) void k_fold(FoldArgs a) {
   const float f = (float)sum;
   if (k < a.K0) a.out[(int64_t)r * a.K0 + k] = f;
   else a.bias[r] = f;
-  if (!(fabsf(f) <= 3.4028234663852886e38f) || !up || !down) atomicOr(a.bad, 1);
+  const bool small = k < a.K0 && sum != 0.0 && fabs(sum) < 0x1p-110;
+  if (!(fabsf(f) <= 3.4028234663852886e38f) || small || !up || !down) atomicOr(a.bad, 1);
 }
 
 constexpr size_t kMaxLds = 160 * 1024;

@@ -140,3 +140,15 @@ def test_infinite_inputs_of_weights_of_one_sign(kind, sign):
     got = run_forward(wl)
     assert np.isfinite(got).all()
     assert rel_err(got, _oracle(wl, kind)) < 1e-4
+
+
+def test_products_below_the_split_range():
+    """Weights whose products are below 2^-110 are not folded: their parts would be lost, where the transformed rows keep them."""
+    from paper_2309_03523_amd.runner import run_forward
+    wl = synth.random_small(16, 4, 70, 128, 128, 128, 4.0, CHUNKS, "gru")
+    for name in ("gcn0.weight", "rnn.weight_ih"):
+        wl.params[name] = wl.params[name] * np.float32(2.0 ** -60)
+    wl.params["gcn0.bias"] = wl.params["gcn0.bias"] * np.float32(2.0 ** 60)
+    wl.X *= np.float32(2.0 ** 120)
+    wl.C *= np.float32(2.0 ** 120)
+    _close(run_forward(wl), _oracle(wl, "gru"))
