@@ -70,13 +70,12 @@ struct dgc_layer {
   float* d_Z1 = nullptr;                         // 2 layers: first layer's output [T,N,S]
   bool narrow = false;                           // the narrow kernel may run the (first) time encoder
   // The transform before the time encoder folded into its input-side weights, when no activation stands between them.
-  // ok: the four parameters have been set and the folded ones are finite.
   struct Fold {
-    bool may = false, ok = false;
+    bool may = false, made = false;              // made: since the four parameters have all been set
     int set = 0;                                 // which of the four have been
     float *W = nullptr, *bias = nullptr;         // [gH][K0], [gH]
     float4* packed = nullptr;
-    int32_t* bad = nullptr;
+    int32_t* bad = nullptr;                      // the product does not stand for the two
   } fold;
   float* d_zero_bias = nullptr;                  // [S] zeros (EvolveGCN-O has no bias)
   EvolveWs evo{};                                // EvolveGCN-O workspace
@@ -981,18 +980,17 @@ static dgc_status_t refold(dgc_layer* L, const std::string& name) {
     if (name == names[k]) which = k;
   if (which < 0) return DGC_OK;
   f.set |= 1 << which;
-  f.ok = false;
   if (f.set != 15) return DGC_OK;
+  f.made = false;
   const Param &wg = L->params[names[0]], &wih = L->params[names[2]];
   const int32_t other = wih.n_in - d.S;          // columns of the concatenated input's other half, which come first
   DGC_HIP_TRY(hipMemset(f.bad, 0, sizeof(int32_t)));
   launch_fold(wih.raw + other, wih.n_in, wg.raw, L->params[names[1]].raw, L->params[names[3]].raw, wih.n_out, d.S, wg.n_in, f.W, f.bias,
               f.bad, nullptr);
   launch_pack_split(f.W, 0, wg.n_in, 1, wih.n_out, wg.n_in, 1, f.packed, nullptr);
-  int32_t bad = 0;
-  DGC_HIP_TRY(hipMemcpy(&bad, f.bad, sizeof(bad), hipMemcpyDeviceToHost));
+  DGC_HIP_TRY(hipGetLastError());
   DGC_HIP_TRY(hipDeviceSynchronize());
-  f.ok = bad == 0;
+  f.made = true;
   return DGC_OK;
 }
 
@@ -1205,7 +1203,7 @@ dgc_status_t dgc_layer_forward(dgc_layer_t* L, const void* Xv, int64_t ldx, cons
     da.Wg = L->params[std::string(last) + ".weight"].narrow;
     da.Wih = L->params["rnn.weight_ih"].narrow; da.Whh = L->params["rnn.weight_hh"].narrow;
   }
-  if (L->fold.ok && !da.narrow) { da.Wf = L->fold.packed; da.bf = L->fold.bias; }
+  if (L->fold.made && !da.narrow) { da.Wf = L->fold.packed; da.bf = L->fold.bias; da.fold_bad = L->fold.bad; }
   if ((!L->tf.built || L->tf.n_lanes > 0) && !launch_dense(da, st, &why)) return fail(DGC_ERR_UNSUPPORTED, why);
   da.narrow = false;
   da.Wf = nullptr; da.bf = nullptr;

@@ -158,8 +158,8 @@ enum Input { kTransform, kFolded, kStack };
 
 // KIND: DGC_TIME_GRU or DGC_TIME_LSTM.  SEQ, CAT: as the fields of DenseArgs say (sequences inside the window;
 // the time encoder's input is [X2 row, Z]).
-template <int KIND, bool SEQ, bool CAT, Input INPUT, int MAXW>
-__global__ __launch_bounds__(64 * MAXW, 2) void k_dense_split(DenseArgs a) {
+template <int KIND, bool SEQ, bool CAT, Input INPUT>
+__device__ __forceinline__ void dense_split(const DenseArgs& a) {
   constexpr bool kLstm = KIND == DGC_TIME_LSTM, STACK = INPUT == kStack, FOLD = INPUT == kFolded;
   const float* const bih = FOLD ? a.bf : a.bih;
   // The five small products of Z go apart from the large one (the matrix unit truncates when it adds, and a small sum is
@@ -416,6 +416,19 @@ __global__ __launch_bounds__(64 * MAXW, 2) void k_dense_split(DenseArgs a) {
     }
     if (s + 1 < ch.w) enter(ts + 1);
   }
+}
+
+// Whether the weights can be folded is known on the device (k_fold), where a graph that was captured before other weights were
+// set finds it, too.
+template <int KIND, bool SEQ, bool CAT, Input INPUT, int MAXW>
+__global__ __launch_bounds__(64 * MAXW, 2) void k_dense_split(DenseArgs a) {
+  if constexpr (INPUT == kFolded) {
+    if (table_entry(a.fold_bad, 0)) {
+      dense_split<KIND, SEQ, CAT, kTransform>(a);
+      return;
+    }
+  }
+  dense_split<KIND, SEQ, CAT, INPUT>(a);
 }
 
 // Transforms alone, Y = act(M W^T + b): a workgroup takes a run of the row tiles (ordered by snapshot).  Its waves

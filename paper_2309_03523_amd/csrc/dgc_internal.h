@@ -210,8 +210,9 @@ struct DenseArgs {
   // M may be Y itself: a wave requests row (t, v) before step t and writes it at that step's end.
   bool input_is_z;
   // The transform folded into the input side of the time encoder (no activation between them), or nullptr: packed
-  // [gH][K0] = W_ih W_g (with X2: the second half of W_ih), bias [gH] = b_ih + W_ih b_g.  Wg and bg are then not read.
-  const float4* Wf; const float* bf;
+  // [gH][K0] = W_ih W_g (with X2: the second half of W_ih), bias [gH] = b_ih + W_ih b_g.  *fold_bad (device) says that they
+  // do not stand for the transform: Wg, bg, Wih and bih are read as without them.
+  const float4* Wf; const float* bf; const int32_t* fold_bad;
   bool narrow;                  // the weights are packed for the narrow kernel, which runs
 };
 // returns false if the (S,H,K0) combination has no kernel

@@ -83,6 +83,20 @@ def test_parameters_change_under_a_captured_forward():
         torch.cuda.synchronize()
         assert torch.equal(torch.nan_to_num(dw.Y, nan=-7.0), torch.nan_to_num(eager, nan=-7.0)), name
     _close(dw.Y.cpu().numpy(), _oracle(wl, "lstm"))
+    # then weights whose product overflows (the transformed rows do not), and the ones before again
+    for scale, inputs in ((1e20, 1e-25), (1e-20, 1e25)):
+        for name in ("gcn0.weight", "rnn.weight_ih"):
+            wl.params[name] = wl.params[name] * np.float32(scale)
+            dw.layer.set_param(name, wl.params[name])
+        dw.X *= inputs
+        dw.C *= inputs
+        eager = dw.forward().clone()
+        dw.Y.fill_(float("nan"))
+        torch.cuda.synchronize()
+        graph.replay()
+        torch.cuda.synchronize()
+        covered = ~torch.isnan(eager)
+        assert covered.any() and torch.equal(dw.Y[covered], eager[covered]) and torch.equal(covered, ~torch.isnan(dw.Y))
     dw.layer.destroy()
 
 
