@@ -24,6 +24,12 @@ static void expect(bool ok, const char* what) {
   std::exit(1);
 }
 
+static std::string fails;                   // the call of this name fails
+static hipError_t next_call(const std::string& name) {
+  calls.push_back(name);
+  return name == fails ? last_error = hipErrorUnknown : hipSuccess;
+}
+
 extern "C" {
 hipError_t hipMalloc(void** p, size_t n) {
   bytes_allocated += n;
@@ -35,7 +41,16 @@ hipError_t hipFree(void* p) { std::free(p); return hipSuccess; }
 hipError_t hipGetLastError() { const hipError_t e = last_error; last_error = hipSuccess; return e; }
 const char* hipGetErrorString(hipError_t) { return "out of memory"; }
 hipError_t hipMemcpyAsync(void* to, const void* from, size_t n, hipMemcpyKind, hipStream_t) { std::memcpy(to, from, n); return hipSuccess; }
-hipError_t hipStreamSynchronize(hipStream_t) { return hipSuccess; }
+hipError_t hipMemcpy(void* to, const void* from, size_t n, hipMemcpyKind) { std::memcpy(to, from, n); return next_call("copy"); }
+hipError_t hipMemset(void* p, int value, size_t n) { std::memset(p, value, n); return next_call("clear"); }
+hipError_t hipDeviceSynchronize() { return next_call("wait for the device"); }
+static float* finished_by_waiting = nullptr;      // a number that the device still writes: there after the default stream has been waited for
+hipError_t hipStreamSynchronize(hipStream_t s) {
+  const hipError_t e = next_call("wait for stream " + std::to_string(reinterpret_cast<uintptr_t>(s)) + " of device " + std::to_string(device));
+  if (e == hipSuccess && finished_by_waiting) *finished_by_waiting += 1.f;
+  return e;
+}
+hipError_t hipSetDevice(int d) { device = d; return next_call("device " + std::to_string(d)); }
 hipError_t hipStreamWaitEvent(hipStream_t, hipEvent_t, unsigned) { calls.push_back("wait"); return hipSuccess; }
 hipError_t hipEventRecord(hipEvent_t e, hipStream_t) {
   calls.push_back("event " + std::to_string(reinterpret_cast<uintptr_t>(e)));
@@ -61,7 +76,19 @@ hipError_t hipEventDestroy(hipEvent_t) { return hipSuccess; }
 
 namespace dgc {
 void launch_spmm(const SpmmArgs& a, hipStream_t) { launched("spmm", {a.fresh, a.M}); if (a.skip_stale) null_pointer |= !a.row_map; }
-bool launch_dense(const DenseArgs& a, hipStream_t, std::string*) { launched("dense", {a.M, a.Wg, a.Y}); return true; }
+bool launch_dense(const DenseArgs& a, hipStream_t, std::string*) {
+  launched(a.Wf ? "folded dense" : "dense", {a.M, a.Wg, a.Y});
+  if (a.Wf) null_pointer |= !a.bf || !a.fold_bad;
+  return true;
+}
+void launch_fold(const float* wih, int64_t, const float* wg, const float* bg, const float* bih, int32_t, int32_t, int32_t, float* out, float* bias,
+                 int32_t* bad, hipStream_t) {
+  launched("fold", {wih, wg, bg, bih, out, bias, bad});
+}
+void launch_pack_split(const float* w, int64_t, int64_t, int64_t, int32_t, int32_t, int64_t, void* packed, hipStream_t) {
+  launched("pack weight", {w, packed});
+}
+bool dense_narrow_wanted(int32_t, int64_t) { return false; }
 void evolve_forward_weights(const EvolveWs&, hipStream_t) { launched("recurrence", {}); }
 bool evolve_backward_dw(const EvolveWs&, const EvolveBwdIn&, bool, hipStream_t, std::string*) { launched("weight gradient", {}); return true; }
 void evolve_backward_bptt(const EvolveWs&, hipStream_t) { launched("back-propagation", {}); }
@@ -191,6 +218,74 @@ static void stage_events() {
   expect(calls.back() == "wait", "the caller's stream waits for the other one");
 }
 
+// A gradient is read after the default stream of the layer's device has been waited for, whichever device is current, and not
+// at all if the wait fails; the caller's device is current again in either case.
+static void gradient_read() {
+  dgc_layer L;
+  float there[2] = {1.f, 2.f}, out[2];
+  Param p;
+  p.raw = there; p.on_host = true; p.n_out = 2;
+  L.params["x.grad"] = p;
+  L.device = 1;
+  finished_by_waiting = there + 1;
+  for (int current : {0, 1}) {
+    device = current;
+    calls.clear();
+    out[0] = out[1] = -1.f;
+    there[1] = 2.f;
+    expect(dgc_layer_get_param(&L, "x.grad", out, 2) == DGC_OK && out[0] == 1.f && out[1] == 3.f, "what is read has been finished");
+    expect(device == current && count("wait for stream 0 of device 1") == 1 && count("copy") == 0, "the layer's device is waited for");
+    expect((int)calls.size() == (current == 1 ? 1 : 3), "and made current only where it is not");
+    fails = "wait for stream 0 of device 1";
+    out[0] = -1.f;
+    expect(dgc_layer_get_param(&L, "x.grad", out, 2) == DGC_ERR_DEVICE && out[0] == -1.f && device == current, "a failed wait is reported");
+    fails.clear();
+  }
+  expect(dgc_layer_get_param(&L, "x.grad", out, 3) == DGC_ERR_INVALID_ARG && dgc_layer_set_param(&L, "x.grad", out, 2) == DGC_ERR_INVALID_ARG,
+         "sizes are checked, gradients are not set");
+  finished_by_waiting = nullptr;
+}
+
+// The folded weights are made when the last of the four parameters has been set, and again whenever one of them is; a forward
+// takes them only if the last attempt succeeded.
+static void folded_weights() {
+  dgc_layer* L = new dgc_layer();
+  L->desc.struct_kind = DGC_STRUCT_GCN;
+  L->desc.time_kind = DGC_TIME_GRU;
+  L->desc.n_struct_layers = 1;
+  L->desc.F = L->desc.S = L->desc.H = 32;
+  L->T = 2; L->N = 40; L->n_chunks = 1;
+  L->d_M = tensor; L->ldm = 32;
+  std::vector<float> v(96 * 32, 0.5f);
+  const std::vector<std::string> names = {"gcn0.weight", "gcn0.bias", "rnn.weight_ih", "rnn.weight_hh", "rnn.bias_ih", "rnn.bias_hh"};
+  for (const std::string& name : names) {
+    const bool rnn = name[0] == 'r', weight = name.find("weight") != std::string::npos;
+    expect(add_param(L, name, rnn ? 96 : 32, weight ? 32 : 0, nullptr, true) == DGC_OK, "a parameter");
+  }
+  L->fold.may = true;
+  expect(dev_alloc_all(L, Wanted<float>{&L->fold.W, 96 * 32}, Wanted<float>{&L->fold.bias, 96}, Wanted<float4>{&L->fold.packed, 96 * 32},
+                       Wanted<int32_t>{&L->fold.bad, 1}) == hipSuccess, "memory");
+  auto set = [&](const std::string& name) { return dgc_layer_set_param(L, name.c_str(), v.data(), L->params[name].numel()); };
+  auto folds = [&] {
+    calls.clear();
+    expect(dgc_layer_forward(L, tensor, 32, tensor, 32, nullptr, 0, nullptr, nullptr, tensor, 32, nullptr, nullptr) == DGC_OK, "forward");
+    expect(count("folded dense") + count("dense") == 1 && !null_pointer, "one time encoder, on weights that are there");
+    return count("folded dense") == 1;
+  };
+  for (size_t k = 0; k < names.size(); ++k) {
+    calls.clear();
+    expect(set(names[k]) == DGC_OK && count("fold") == (k == 4), "made with the last of the four");
+    expect(folds() == (k >= 4), "and used from then on");
+  }
+  for (const char* where : {"clear", "wait for the device"}) {
+    fails = where;
+    expect(set("gcn0.bias") == DGC_ERR_DEVICE && hipGetLastError() != hipSuccess && !folds(), "after an error the transform runs");
+    fails.clear();
+    calls.clear();
+    expect(set("rnn.bias_ih") == DGC_OK && count("fold") == 1 && folds(), "until the next parameter");
+  }
+}
+
 // Large dynamic LDS is allowed once on every device that a kernel runs on; a refusal is reported and not taken for done.
 static void lds_per_device() {
   std::atomic<uint64_t> done{0};
@@ -213,6 +308,8 @@ int main(int argc, char** argv) {
   else if (check == "stage events") stage_events();
   else if (check == "lds per device") lds_per_device();
   else if (check == "evolve memory") evolve_memory();
+  else if (check == "gradient read") gradient_read();
+  else if (check == "folded weights") folded_weights();
   else expect(false, "the check is known");
   std::puts("so");
   return 0;

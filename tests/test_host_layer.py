@@ -1,6 +1,6 @@
 """The layer's host code on the CPU, built with stand-ins for the HIP runtime and the kernels' launchers (host_layer.cpp):
-what it does when device memory runs out, in which order it enqueues what runs on two streams, and that what has to be
-allowed once per device is."""
+what it does when device memory runs out, how much it takes, in which order it enqueues what runs on two streams, what it waits for
+before it reads, what it does with a call that fails, and that what has to be allowed once per device is."""
 import os
 import subprocess
 
@@ -19,7 +19,7 @@ def program(tmp_path_factory):
     return out
 
 
-@pytest.mark.parametrize("check", ["input gradient memory", "label memory", "stage events", "lds per device", "evolve memory"])
+@pytest.mark.parametrize("check", ["input gradient memory", "label memory", "stage events", "lds per device", "evolve memory", "gradient read", "folded weights"])
 def test_host_layer(program, check):
     r = subprocess.run([program, check], capture_output=True, text=True, timeout=60)
     assert r.returncode == 0, r.stdout + r.stderr
