@@ -41,7 +41,7 @@ struct dgc_layer {
   int32_t n_chunks = 0;
   int64_t nseg = 0, total_rows = 0, total_nnz = 0, total_halo = 0, total_state_rows = 0;
   int64_t n_short = 0, n_long = 0, n_tiles = 0;
-  int32_t rows_per_group = 16, long_nnz = 1024, part_nnz = 512, longest_row = 0;
+  int32_t rows_per_group = 16, long_nnz = 1024, part_nnz = 512, longest_row = 0, longest_window = 0;
   std::vector<dgc_chunk_t> chunks;
   std::vector<Segment> segs_host;
   std::vector<void*> allocs;          // everything hipMalloc'ed, freed in destroy
@@ -282,7 +282,7 @@ bool runs_split(const dgc_layer_desc_t& d, int32_t S, int32_t H, int32_t time_ki
   return d.dense_kernel != DGC_DENSE_TILE && dense_split_supported(S, H, time_kind);
 }
 
-// Whether the time encoder that a transform feeds may run the narrow kernel; the number of its tiles decides (dense_narrow_wanted).
+// Whether the time encoder that a transform feeds may run the narrow kernel; its tiles decide (dense_narrow_wanted).
 bool may_run_narrow(const dgc_layer_desc_t& d) {
   return runs_split(d, d.S, d.H, d.time_kind) && !d.lstm_input_concat &&
          dense_narrow_supported(d.S, d.H, d.n_struct_layers == 2 ? d.S : d.F, d.time_kind);
@@ -572,6 +572,7 @@ dgc_status_t build_layer(dgc_layer* L, const dgc_graph_t* graph, hipStream_t st)
     state_off += c.v_hi - c.v_lo;
   }
   L->cinfo_host = cinfo;
+  for (const ChunkInfo& c : cinfo) L->longest_window = std::max(L->longest_window, c.w);
   L->nseg = (int64_t)segs.size();
   L->total_rows = row_off;
   L->total_state_rows = state_off;
@@ -732,7 +733,7 @@ dgc_status_t build_layer(dgc_layer* L, const dgc_graph_t* graph, hipStream_t st)
     if ((rc = add_param(L, "rnn.bias_ih", gH, 0, st)) != DGC_OK) return rc;
     if ((rc = add_param(L, "rnn.bias_hh", gH, 0, st)) != DGC_OK) return rc;
     const int32_t K0 = two ? d.S : d.F;
-    if (sp && d.act_out == DGC_ACT_NONE && dense_fold_wanted(d.S, K0, d.time_kind) && !(nw && dense_narrow_wanted(d.H, INT64_MAX))) {
+    if (sp && d.act_out == DGC_ACT_NONE && dense_fold_wanted(d.S, K0, d.time_kind)) {
       float* pk = nullptr;
       DGC_HIP_TRY(dev_alloc(L, &L->fold.W, (int64_t)gH * K0));
       DGC_HIP_TRY(dev_alloc(L, &L->fold.bias, gH));
@@ -1198,7 +1199,7 @@ dgc_status_t dgc_layer_forward(dgc_layer_t* L, const void* Xv, int64_t ldx, cons
     da.x2_map = tf.slot_row;      // a slot's row of the first layer's output
     if (HN && !L->lab.built) tf_carry(tf.seq_len, L->total_state_rows, d.time_kind == DGC_TIME_LSTM ? 2 : 1, d.H, H0, HN, st);
   }
-  da.narrow = L->narrow && dense_narrow_wanted(d.H, da.n_tiles32);
+  da.narrow = L->narrow && dense_narrow_wanted(d.H, da.K0, L->fold.made, da.n_tiles32, L->longest_window);
   if (da.narrow) {
     da.Wg = L->params[std::string(last) + ".weight"].narrow;
     da.Wih = L->params["rnn.weight_ih"].narrow; da.Whh = L->params["rnn.weight_hh"].narrow;

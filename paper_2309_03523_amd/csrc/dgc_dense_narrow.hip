@@ -410,13 +410,30 @@ bool dense_narrow_supported(int32_t S, int32_t H, int32_t K0, int32_t time_kind)
   return S == H && (H == 32 || H == 64) && (time_kind == DGC_TIME_GRU || time_kind == DGC_TIME_LSTM) && narrow_lds(H, K0, time_kind) <= 160 * 1024;
 }
 
-// 32 wide: always (8 x 200 000 vertices: GRU 614 -> 549 us with the aggregation, LSTM 658 -> 581; 8 x 8000: 63 -> 38 and
-// 68 -> 39).  64 wide: while the other kernel's tiles all fit the chip at once, so that it takes one tile's chain whatever their
-// number (8 x 8000: GRU 69 -> 53 us, LSTM 79 -> 58; 8 x 16 000: 106 -> 91, 123 -> 101); beyond, its rate counts, and a
-// workgroup of eight waves a CU is slower where windows are short (10 x 12 345 in windows of 4: 118 -> 125 and 133 -> 138;
-// 8 x 50 000: 260 -> 245 and 300 -> 271).
-bool dense_narrow_wanted(int32_t H, int64_t n_tiles32) {
-  return H == 32 || n_tiles32 <= 1024;
+// Against k_dense_split, which takes the folded transform where there is one.  What this kernel has the less of is the chain of a
+// step and the transform's time; what it pays is that a workgroup loads all weights first (with windows of one step for nothing)
+// and, where tiles are many, that fewer of them are on the chip at once.  So it is for few tiles, the more the longer the windows
+// are, for more where the other kernel's transform is not folded, and for any number where the input is wide.
+// A forward of 8 snapshots, GRU, other kernel -> this one, in us; w: the windows' snapshots (LSTM: 2 to 8 % better for this one).
+//   64 wide, folded, 64 columns:  128 tiles w 1 16.1 -> 16.3, w 2 19.9 -> 17.3, w 8 53.9 -> 33.4; 512 w 2 31.5 -> 33.6, w 8 98 -> 93;
+//                                 1024 w 8 151 -> 169
+//            folded, 16 columns:  128 tiles w 8 1.5 times as fast, 256 w 4 as fast, 400 w 8 0.92 times
+//            128 columns:         256 tiles w 1 19.4 -> 20.0, w 2 30.9 -> 28.2; 1024 w 2 80.3 -> 72.6, w 8 285 -> 241
+//            96 columns:          640 tiles w 2 as fast, w 8 1.14 times; 900 w 2 0.92, w 8 0.97 times
+//   32 wide, folded, 32 columns:  512 tiles w 1 15.8 -> 17.1, w 2 21.2 -> 21.2; 1024 w 2 33.4 -> 35.3, w 8 101 -> 98; 2048 w 8 161 -> 176
+//            48 columns:          1024 tiles w 8 118 -> 102; 2048 w 2 57.7 -> 60.2, w 8 185 -> 186
+//            64 columns:          1024 tiles w 1 24.7 -> 26.0, w 2 39.2 -> 38.9; 2048 w 1 41.2 -> 39.6, w 8 245 -> 205; 20 000 w 8 2082 -> 1945
+//            128 columns:         512 tiles w 1 24.3 -> 23.6; 20 000 w 8 4199 -> 3212
+bool dense_narrow_wanted(int32_t H, int32_t K0, bool folds, int64_t n_tiles32, int32_t window) {
+  const int64_t w = std::min(window, 4);
+  if (H == 32) {
+    if (K0 > 64) return true;
+    if (K0 > 48) return window > 1 || n_tiles32 >= 2048;
+    return window > 1 && n_tiles32 <= (folds ? 256 * w : 1024);
+  }
+  if (window == 1) return K0 > 128 && n_tiles32 <= 256;
+  if (folds) return n_tiles32 <= (K0 > 32 ? 128 : 64) * w;
+  return n_tiles32 <= (K0 > 96 ? 1024 : 640);
 }
 
 bool launch_dense_narrow(const DenseArgs& a, hipStream_t st, std::string* why) {

@@ -221,7 +221,8 @@ bool launch_dense(const DenseArgs& a, hipStream_t st, std::string* why);
 bool dense_split_supported(int32_t S, int32_t H, int32_t time_kind);
 // The first recurrent layer of narrow layers, without a concatenated input (dgc_dense_narrow.hip); K0: input columns
 bool dense_narrow_supported(int32_t S, int32_t H, int32_t K0, int32_t time_kind);
-bool dense_narrow_wanted(int32_t H, int64_t n_tiles32);      // whether it is the faster one
+// whether it is the faster one; folds: the other kernel would take the folded transform, window: the most steps of a tile
+bool dense_narrow_wanted(int32_t H, int32_t K0, bool folds, int64_t n_tiles32, int32_t window);
 bool launch_dense_narrow(const DenseArgs& a, hipStream_t st, std::string* why);
 int64_t narrow_weight_bytes(int32_t n_out, int32_t n_in);
 void launch_pack_narrow(const float* W, int32_t n_out, int32_t n_in, void* packed, hipStream_t st);

@@ -88,7 +88,7 @@ void launch_fold(const float* wih, int64_t, const float* wg, const float* bg, co
 void launch_pack_split(const float* w, int64_t, int64_t, int64_t, int32_t, int32_t, int64_t, void* packed, hipStream_t) {
   launched("pack weight", {w, packed});
 }
-bool dense_narrow_wanted(int32_t, int64_t) { return false; }
+bool dense_narrow_wanted(int32_t, int32_t, bool, int64_t, int32_t) { return false; }
 void evolve_forward_weights(const EvolveWs&, hipStream_t) { launched("recurrence", {}); }
 bool evolve_backward_dw(const EvolveWs&, const EvolveBwdIn&, bool, hipStream_t, std::string*) { launched("weight gradient", {}); return true; }
 void evolve_backward_bptt(const EvolveWs&, hipStream_t) { launched("back-propagation", {}); }

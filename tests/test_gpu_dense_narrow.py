@@ -1,6 +1,7 @@
 """The narrow time encoder (S = H of 32 and 64) where it can go wrong: input widths around 16, 32 and the k-blocks that a wave
 requests ahead, chunks that leave part of a 16-vertex tile or its second half empty, windows of one step, several tiles a
-workgroup with windows of different lengths, masks, sequences, and rows of infinities.  Against the oracle in double; the bar for
+workgroup with windows of different lengths, masks, sequences, and rows of infinities; and the same forms on either side of the
+sizes where the other kernel takes over.  Against the oracle in double; the bar for
 the root mean square distance is what the fp32 instruction's kernel is off by at these sizes (3e-7: rounded sums of the products
 and the gates' fast exponentials), for the largest element the repository's fp32 one."""
 import numpy as np
@@ -15,20 +16,20 @@ pytestmark = pytest.mark.gpu
 WIDTHS = [1, 4, 15, 16, 17, 31, 32, 33, 48, 50, 64, 65, 96, 128, 129, 200, 256, 257]
 
 
-def _check(wl, kind, H, windows, seed, mask=None):
+def _check(wl, kind, H, windows, seed, mask=None, act="none"):
     import torch
     from paper_2309_03523_amd.runner import DeviceWorkload
     V = int(sum(c[1] - c[0] for c in wl.chunks))
     n = 2 if kind == "lstm" else 1
     H0 = (0.5 * synth.stream(seed, "h0").standard_normal((n * V, H))).astype(np.float32)
-    dw = DeviceWorkload(wl)
+    dw = DeviceWorkload(wl, act_out=act)
     dw.H0 = torch.from_numpy(H0).cuda()
     kw = {} if mask is None else dict(reset_mask=torch.from_numpy(mask).cuda())
     dw.Y.fill_(float("nan"))
     HN = torch.full_like(dw.H0, float("nan"))
     dw.layer.forward(dw.X, dw.C, dw.Y, C1=dw.C1, H0=dw.H0, HN=HN, **kw)
     torch.cuda.synchronize()
-    want = oracle.forward(wl.graph, wl.chunks, wl.params, wl.X, wl.C, time_kind=kind, H0=H0, reset_mask=mask)
+    want = oracle.forward(wl.graph, wl.chunks, wl.params, wl.X, wl.C, time_kind=kind, H0=H0, reset_mask=mask, act_out=act)
     want = np.asarray(want, np.float64)
     got = dw.Y.cpu().numpy()
     here = ~np.isnan(want)
@@ -52,21 +53,99 @@ def test_input_widths(F, H, kind):
     _check(wl, kind, H, chunks, F + H)
 
 
-@pytest.mark.parametrize("H", [32, 64])
+# Workgroups that the chip holds at once, and the most tiles of 32 vertices with which the kernel runs for inputs of 20 columns
+# and windows of at most 3 and of 6, where the transform can be folded; where an activation forbids it.
+GROUPS = {32: 768, 64: 256}
+LIMIT = {(32, 3): 768, (64, 3): 192, (32, 6): 1024, (64, 6): 256}
+LIMIT_UNFOLDED = {32: 1024, 64: 640}
+
+
+@pytest.mark.parametrize("H,act,N,ranges", [(32, "none", 7000, 48), (32, "none", 24000, 48), (32, "relu", 9000, 48), (32, "relu", 24000, 48),
+                                            (64, "none", 2000, 16), (64, "none", 6000, 48), (64, "relu", 6000, 48), (64, "relu", 24000, 48)])
 @pytest.mark.parametrize("kind", ["gru", "lstm"])
-def test_many_tiles_and_masks(H, kind):
-    """More half tiles than workgroups; windows of 1, 2 and 3."""
-    n, T = 48, 6
+def test_many_tiles_and_masks(H, act, N, ranges, kind):
+    """More half tiles than workgroups; windows of 1, 2 and 3.  The smaller sizes are this kernel's, the larger ones the other's."""
+    T = 6
     rng = synth.stream(H, "bounds")
-    N = 24000
-    cut = np.concatenate([[0], np.sort(rng.choice(N - 1, n - 1, replace=False)) + 1, [N]])
+    cut = np.concatenate([[0], np.sort(rng.choice(N - 1, ranges - 1, replace=False)) + 1, [N]])
     chunks = []
-    for i in range(n):
+    for i in range(ranges):
         chunks += [[int(cut[i]), int(cut[i + 1]), t, t + w] for t, w in ([(0, 1), (1, 2), (3, 3)] if i % 2 else [(0, 3), (3, 2), (5, 1)])]
     chunks = [c for c in chunks if (c[2] + c[0]) % 7]         # some vertices are not covered there
+    size = np.array([c[1] - c[0] for c in chunks])
+    tiles, limit = (-(-size // 32)).sum(), LIMIT[H, 3] if act == "none" else LIMIT_UNFOLDED[H]
+    assert (-(-size // 16)).sum() > GROUPS[H] and (tiles <= limit) == (N < 24000 and (H, act, N) != (64, "none", 6000))
     wl = synth.random_small(H, T, N, 20, H, H, 2.0, chunks, kind)
     mask = (rng.random((T, N)) < 0.3).astype(np.uint8)
-    _check(wl, kind, H, chunks, H, mask)
+    _check(wl, kind, H, chunks, H, mask, act)
+
+
+@pytest.mark.parametrize("H", [32, 64])
+@pytest.mark.parametrize("kind", ["gru", "lstm"])
+@pytest.mark.parametrize("what", ["presence", "labels", "both"])
+def test_many_sequences(H, kind, what):
+    """Sequences inside the window (of present vertices, of equal labels, of both) on more half tiles than workgroups: outputs and the
+    states that leave, which enter from a table of states.  A vertex sees only itself, so a row is transformed as it is."""
+    import torch
+    from oracle import tfusion
+    from paper_2309_03523_amd.runner import DeviceWorkload
+    T, F, N = 6, 20, {32: 20000, 64: 6000}[H]
+    rng = synth.stream(H, "sequences")
+    chunks = [[0, N // 3, 0, 6], [N // 3, N, 0, 2], [N // 3, N, 2, 6]] if what == "presence" else [[0, N, 0, T]]
+    wl = synth.random_small(H, T, N, F, H, H, 0.0, chunks, kind)
+    present = rng.random((T, N)) < 0.75 if what != "labels" else np.ones((T, N), bool)
+    labels = np.zeros((T, N), np.int64)
+    row = np.empty((T, N), np.int64)         # state row of (t, i)
+    if what == "presence":                   # a chunk's windows are its labels here
+        off = 0
+        for k, (lo, hi, t0, t1) in enumerate(chunks):
+            labels[t0:t1, lo:hi], row[t0:t1, lo:hi] = k, off + np.arange(hi - lo)
+            off += hi - lo
+    else:
+        labels = np.cumsum(rng.random((T, N)) < 0.3, axis=0)
+        row, off = np.arange(T * N).reshape(T, N), T * N
+    n_state = 2 if kind == "lstm" else 1
+    H0 = (0.5 * rng.standard_normal((n_state * off, H))).astype(np.float32)
+    dw = DeviceWorkload(wl)
+    if what != "presence":
+        dw.layer.set_labels(torch.from_numpy(labels.astype(np.int32).reshape(-1)).cuda())
+    if what != "labels":
+        dw.layer.set_presence(torch.from_numpy(present.astype(np.uint8)).cuda())
+    lanes = np.diff(dw.layer.packing("lane_ptr")) if what != "labels" else np.array([N])
+    assert (-(-lanes // 16)).sum() > GROUPS[H] and (-(-lanes // 32)).sum() <= LIMIT[H, 6]
+    HN = torch.full((n_state * off, H), float("nan"), device="cuda")
+    dw.Y.fill_(float("nan"))
+    dw.layer.forward(dw.X, dw.C, dw.Y, H0=torch.from_numpy(H0).cuda(), HN=HN)
+    torch.cuda.synchronize()
+    Z = wl.X.astype(np.float64) @ wl.params["gcn0.weight"].T.astype(np.float64) + wl.params["gcn0.bias"]
+    want = np.full((T, N, H), np.nan)
+    want_HN = H0.astype(np.float64) if what == "presence" else np.full(H0.shape, np.nan)
+    h, c = np.zeros((N, H)), np.zeros((N, H))
+    last = np.full(N, -1)                    # label of a vertex's present instance before
+    for t in range(T):
+        p = present[t]
+        begins = p & (last != labels[t])
+        h[begins] = H0[row[t][begins]]
+        if kind == "gru":
+            h[p] = tfusion.gru_step(wl.params, Z[t][p], h[p])
+        else:
+            c[begins] = H0[off + row[t][begins]]
+            h[p], c[p] = tfusion.lstm_step(wl.params, Z[t][p], h[p], c[p])
+        want[t][p] = h[p]
+        last[p] = labels[t][p]
+        after = np.full(N, -1)               # label of the next present instance
+        for u in range(T - 1, t, -1):
+            after[present[u]] = labels[u][present[u]]
+        ends = p & (after != labels[t])
+        want_HN[row[t][ends]] = h[ends]
+        if kind == "lstm":
+            want_HN[off + row[t][ends]] = c[ends]
+    for got, w in ((dw.Y.cpu().numpy(), want), (HN.cpu().numpy(), want_HN)):
+        here = ~np.isnan(w)
+        assert np.array_equal(np.isnan(got), ~here)
+        off_by = np.linalg.norm((got - w)[here]) / np.linalg.norm(w[here])
+        assert off_by < 3e-7 and rel_err(got[here], w[here]) < 1e-4, off_by
+    dw.layer.destroy()
 
 
 @pytest.mark.parametrize("H", [32, 64])
