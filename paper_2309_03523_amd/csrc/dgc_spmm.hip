@@ -321,8 +321,9 @@ __global__ __launch_bounds__(256) void k_spmm_long_reduce(SpmmArgs a) {
     double sum[VEC];
 #pragma unroll
     for (int q = 0; q < VEC; ++q) sum[q] = 0.0;
-    constexpr int kAhead = 8;      // parts requested together (past the last: the last one, not added)
-    for (int p0 = 0; p0 < parts; p0 += kAhead) {
+    // parts requested together (past the last: the last one, not added): two of a row that has no more, else eight
+    auto add = [&](int p0, auto ahead) {
+      constexpr int kAhead = decltype(ahead)::value;
       float v[kAhead][VEC];
 #pragma unroll
       for (int k = 0; k < kAhead; ++k) vload<VEC>(v[k], a.partial + (item + min(p0 + k, parts - 1)) * a.ldm + fi);
@@ -330,7 +331,10 @@ __global__ __launch_bounds__(256) void k_spmm_long_reduce(SpmmArgs a) {
       for (int k = 0; k < kAhead; ++k)
 #pragma unroll
         for (int q = 0; q < VEC; ++q) sum[q] += p0 + k < parts ? (double)v[k][q] : 0.0;
-    }
+    };
+    if (parts <= 2) add(0, std::integral_constant<int, 2>());
+    else
+      for (int p0 = 0; p0 < parts; p0 += 8) add(p0, std::integral_constant<int, 8>());
     float acc[VEC];
 #pragma unroll
     for (int q = 0; q < VEC; ++q) acc[q] = (float)(sum[q] * (double)di);
@@ -581,9 +585,9 @@ __global__ __launch_bounds__(256) void k_agg(SpmmArgs a, AggCols cols, int64_t l
   else agg_short<LPR, SKIP, false>(a, cols, (block - long_blocks) * kTeam + wave, nullptr, nullptr);
 }
 
-// The same on a graph that does not fill the chip for long: there the longest row is what the launch waits for (1024
-// non-zeros are 32 batches of gathers, each waited for), so the four waves of a workgroup share a part, and the
-// longer rows of their four groups once they have done the short ones.  A row's quarters are added in wave order.
+// The same where there are rows long enough to be shared: on a graph that does not fill the chip for long the longest row is
+// what the launch waits for (1024 non-zeros are 32 batches of gathers, each waited for), so the four waves of a workgroup share a
+// part, and the longer rows of their four groups once they have done the short ones.  A row's quarters are added in wave order.
 template <int LPR, bool SKIP>
 __global__ __launch_bounds__(256) void k_agg_team(SpmmArgs a, AggCols cols, int64_t long_blocks) {
   constexpr int G = 64 / LPR;
@@ -640,9 +644,11 @@ __global__ __launch_bounds__(256) void k_agg_team(SpmmArgs a, AggCols cols, int6
 
 // Without a row to share the team's queue and barriers would only cost (8 x 1000 rows of at most 30 non-zeros, width 32:
 // 9.0 us without, 10.0 with); with one the team is the faster at every size tried, 5000 x 8 rows up to 100 000 x 32.
+// Parts shorter than a shared row are a workgroup's only while the chip holds all of them at once: many of them are work for
+// every wave (4 x 400 000 rows, 1.7 M parts of 16: 2.25 -> 5.02 ms at width 8, 5.41 -> 7.13 at 256; 4 x 20 000: 147 -> 257 us at 8).
 template <int LPR>
 void launch_agg(const SpmmArgs& a, AggCols cols, hipStream_t st) {
-  const bool team = a.longest_row > kShared<LPR>;
+  const bool team = a.longest_row > kShared<LPR> && a.n_long <= (a.part_nnz > kShared<LPR> ? kMostTeams : kTeamsAtOnce);
   const int64_t gs = (a.n_short + kTeam - 1) / kTeam, gl = team ? a.n_long : (a.n_long + kTeam - 1) / kTeam;
   if (gs + gl == 0) return;
   auto* kernel = team ? (a.skip_stale ? &k_agg_team<LPR, true> : &k_agg_team<LPR, false>)

@@ -1,5 +1,6 @@
 """Rows that the four waves of a workgroup share in the aggregation: lengths around every threshold (a row per lane group, a
-row per wave, four batches of a wave, split rows), groups of one row up to 32, and a workgroup whose last groups are missing.
+row per wave, four batches of a wave, split rows), groups of one row up to 32, a workgroup whose last groups are missing, and short
+parts, few (shared) and more than the chip holds workgroups (one a wave).
 Bound of an fp32 sum of n products in any order: n + 3 roundings of 2^-24 of the sum of the products' sizes."""
 import numpy as np
 import pytest
@@ -14,7 +15,7 @@ LENGTHS = [1, 2, 8, 9, 16, 17, 31, 32, 33, 34, 63, 64, 65, 96, 127, 128, 129, 13
 
 
 @pytest.mark.parametrize("F", [5, 64, 66, 128, 200, 300])
-@pytest.mark.parametrize("rows_per_group,long_nnz,part_nnz", [(0, 0, 0), (16, 256, 100), (32, 500, 130), (5, 40, 33)])
+@pytest.mark.parametrize("rows_per_group,long_nnz,part_nnz", [(0, 0, 0), (16, 256, 100), (32, 500, 130), (5, 40, 33), (16, 130, 16)])
 def test_shared_rows(F, rows_per_group, long_nnz, part_nnz):
     import torch
     from paper_2309_03523_amd import binding

@@ -1,5 +1,6 @@
 """Rows of the graph attention that the four waves of a workgroup share: lengths around the threshold (128) and where a quarter
-ends inside a batch or is shorter than the others, whole and as parts of split rows, several in one group and in one workgroup.
+ends inside a batch or is shorter than the others, whole and as parts of split rows, several in one group and in one workgroup; short parts, few (shared)
+and more than the chip holds workgroups (one a wave).
 Rows of more than 128 neighbours average as many projections, so the bar is the layer's bf16 one relative to the root mean
 square of the row looked at."""
 import numpy as np
@@ -18,6 +19,7 @@ LENGTHS = [128, 129, 130, 131, 132, 133, 160, 191, 192, 193, 255, 256, 257, 258,
 @pytest.mark.parametrize("T,N,cut,kw", [
     (2, 700, 11, {}), (1, 701, 350, dict(rows_per_group=32)), (1, 689, 5, dict(rows_per_group=1)),
     (1, 700, 20, dict(long_nnz=300, part_nnz=131, rows_per_group=8)), (2, 693, 400, dict(long_nnz=130, part_nnz=3)),
+    (1, 693, 400, dict(long_nnz=130, part_nnz=40)),
 ])
 def test_shared_rows(T, N, cut, kw):
     from paper_2309_03523_amd.runner import DysatDevice
