@@ -161,6 +161,7 @@ struct GatArgs {
 };
 
 struct SoftAcc { float m, l, a0, a1; };
+constexpr float kLowest = -3.4028234663852886e38f;
 
 constexpr int kBatch = 4;    // neighbours per slot and batch (2: 95 us and 2.83 ms)
 struct GatBatch { uint4 z[kBatch]; float e[kBatch]; };
@@ -180,7 +181,9 @@ __device__ __forceinline__ int own_feature(int lane) { return 8 * (lane & 15) + 
 __device__ __forceinline__ SoftAcc gat_row_range(const GatArgs& a, const Segment& s, const int32_t* first, int64_t base,
                                                  float sd, int n, int32_t ids, int lane) {
   const int slot = lane >> 4, sub = lane & 15, head = sub >> 1;
-  float m = -INFINITY, l = 0.f, acc[8];
+  // The maximum starts at the lowest float, so that neighbours of weight zero (logit -inf) leave zeros where they come first in
+  // a part or a quarter, as they do behind others.
+  float m = kLowest, l = 0.f, acc[8];
 #pragma unroll
   for (int d = 0; d < 8; ++d) acc[d] = 0.f;
   int32_t ahead = 64 + lane < n ? first[64 + lane] : 0;
@@ -206,7 +209,7 @@ __device__ __forceinline__ SoftAcc gat_row_range(const GatArgs& a, const Segment
     float e[kBatch], bm = -INFINITY;
 #pragma unroll
     for (int u = 0; u < kBatch; ++u) {
-      e[u] = lrelu(sd + b.e[u]);       // -inf stays -inf
+      e[u] = lrelu(sd + b.e[u]);       // -inf stays -inf (no neighbour)
       bm = fmaxf(bm, e[u]);
     }
     const float mn = fmaxf(m, slots_max(bm));
@@ -246,10 +249,13 @@ __device__ __forceinline__ SoftAcc gat_row_range(const GatArgs& a, const Segment
   return {m, add_rows32(l2, l2), add_rows32(h[0], h[2]), add_rows32(h[1], h[3])};
 }
 
-__device__ __forceinline__ void gat_row_store(const GatArgs& a, int64_t row, const SoftAcc& r, int feature, bool lse_lane, int head) {
-  const float inv = r.l > 0.f ? 1.f / r.l : 0.f;
+// stored: the row has neighbours; then a sum of zero means that no logit is above -inf, and the softmax is NaN
+__device__ __forceinline__ void gat_row_store(const GatArgs& a, int64_t row, const SoftAcc& r, int feature, bool lse_lane, int head,
+                                              bool stored = true) {
+  const float l = stored && r.l == 0.f ? NAN : r.l;
+  const float inv = l > 0.f ? 1.f / l : l;
   *reinterpret_cast<float2*>(a.U + row * kS + feature) = make_float2(r.a0 * inv, r.a1 * inv);
-  if (lse_lane) a.lse[row * 8 + head] = r.m + __logf(r.l);
+  if (lse_lane) a.lse[row * 8 + head] = r.m + __logf(l);
 }
 
 // TEAM: rows of more than kShared non-zeros are left in `queue` for the four waves of the workgroup.
@@ -290,7 +296,7 @@ __device__ __forceinline__ void gat_short(const GatArgs& a, int64_t item, int la
       ++queued;
     } else if (e1 - e0 <= a.long_nnz) {    // split rows: gat_long
       const SoftAcc r = gat_row_range(a, s, col + e0, base, sd, (int)(e1 - e0), ids, lane);
-      gat_row_store(a, base + i0 + rr, r, own_feature(lane), lane < 16 && !(lane & 1), head);
+      gat_row_store(a, base + i0 + rr, r, own_feature(lane), lane < 16 && !(lane & 1), head, e1 > e0);
     }
     e0 = e1; e1 = ne1; ids = nids; sd = nsd;
   }

@@ -38,3 +38,26 @@ def test_shared_rows(T, N, cut, kw):
         assert rel_err(got[:, i], want[:, i], floor=1.0) < TOL, LENGTHS[i]
     assert rel_err(got, want, floor=1.0) < TOL
     dd.layer.destroy()
+
+
+@pytest.mark.parametrize("first", [16, 64, 120, 180])
+@pytest.mark.parametrize("kw", [{}, dict(long_nnz=130, part_nnz=50)])
+def test_neighbours_of_weight_zero(first, kw):
+    """A run of neighbours whose logits are below every float (their projections are finite) has weight zero wherever it lies in a
+    shared or split row, also where it fills the first of a wave's batches; a row of nothing but such neighbours is NaN."""
+    from paper_2309_03523_amd.runner import DysatDevice
+    T, N, n = 2, 300, 240
+    wl = synth.dysat_small(4, T, N, 128, 8, 3.0, [[0, N, 0, T]])
+    for t in range(T):                                   # vertex 0: neighbours 0 .. n; the others see it and themselves
+        wl.graph.snaps[t] = synth.csr_from_undirected(N, np.zeros(n, np.int64), np.arange(1, n + 1))
+    wl.params["gat.weight"] = np.eye(128, dtype=np.float32)
+    wl.params["gat.att_src"] = np.full((8, 16), -1e35, np.float32)
+    wl.params["gat.att_dst"] = np.zeros((8, 16), np.float32)
+    wl.X[:, first:first + 50] = 1e4                      # logits beyond the largest float
+    wl.X[:, n + 2:] = 1e4                                # see only themselves (and n + 1 shares a tile with one of them)
+    dd = DysatDevice(wl, **kw)
+    got = dd.forward().float().cpu().numpy()
+    dd.layer.destroy()
+    assert np.isnan(got[:, n + 2:]).all() and np.isfinite(got[:, :n + 1]).all()
+    want = dysat.gradients(wl.graph, wl.chunks, wl.params, wl.X, wl.C, 8, dY=np.zeros_like(wl.X))["Y"]
+    assert rel_err(got[:, 0], want[:, 0], floor=1.0) < TOL
