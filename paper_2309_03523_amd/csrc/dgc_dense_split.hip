@@ -663,10 +663,15 @@ bool launch_dense_split(const DenseArgs& a, hipStream_t st, std::string* why) {
   return false;
 }
 
-// MFMAs of a tile and 32 columns, in k-blocks: the gates over the input's width against the transform and the gates over its output's.
+// Products of a tile and 32 columns, in k-blocks: the gates over the input's width against the transform and the gates over its
+// output's.  Any that are saved pay (GRU 96 to 256 wide, 2 saved of 44 to 113: 5 to 10 %; LSTM 160 to 256 wide, 1 of 93 and more: 2 %),
+// but for the LSTM 96 and 128 wide: there the rounding additions of the small part products of every k-block are as much as
+// five (8 x 500 vertices, saved 2 of 74: 104.6 -> 110.5 us, 5 of 73: 97.6 -> 100.7, 8 of 72: 94.6 -> 93.9; 8 x 20 000, 5: 382 -> 374).
 bool dense_fold_wanted(int32_t S, int32_t K0, int32_t time_kind) {
-  const int ng = time_kind == DGC_TIME_LSTM ? 4 : 3, kbh = S / 16, nkb0 = (K0 + 15) / 16;
-  return ng * nkb0 < nkb0 + ng * kbh;
+  const bool lstm = time_kind == DGC_TIME_LSTM;
+  const int ng = lstm ? 4 : 3, kbh = S / 16, nkb0 = (K0 + 15) / 16;
+  const int saved = nkb0 + ng * kbh - ng * nkb0;
+  return saved >= (lstm && (S == 96 || S == 128) ? 6 : 1);
 }
 
 void launch_fold(const float* wih, int64_t ld_wih, const float* wg, const float* bg, const float* bih, int32_t gH, int32_t S, int32_t K0,

@@ -30,7 +30,8 @@ def _oracle(wl, kind, layers=1, **kw):
 @pytest.mark.parametrize("F,S,kind,layers", [
     (1, 96, "gru", 1), (96, 96, "lstm", 1), (128, 96, "lstm", 1), (129, 96, "lstm", 1), (144, 96, "gru", 1), (145, 96, "gru", 1),
     (97, 128, "gru", 1), (192, 128, "gru", 1), (193, 128, "gru", 1), (40, 128, "lstm", 2), (300, 256, "gru", 1), (304, 256, "lstm", 1),
-    (272, 192, "gru", 1), (273, 192, "gru", 1), (257, 224, "lstm", 1), (60, 160, "gru", 2),
+    (272, 192, "gru", 1), (273, 192, "gru", 1), (257, 224, "lstm", 1), (60, 160, "gru", 2), (97, 96, "lstm", 1), (128, 128, "lstm", 1),
+    (129, 128, "lstm", 1), (288, 224, "lstm", 1), (208, 160, "lstm", 1),
 ])
 def test_widths(F, S, kind, layers):
     from paper_2309_03523_amd.runner import run_forward
