@@ -125,6 +125,51 @@ def flops_per_row(wl) -> dict:
     return {"transform": dense, "rnn": rnn}
 
 
+def folds_transform(K0: int, S: int, kind: str) -> bool:
+    """Whether the time encoder behind a transform without an activation takes the transform folded into its input-side weights
+    (the library's dense_fold_wanted): products in k-blocks of 16, an LSTM 96 or 128 wide from six saved on."""
+    g, nkb = {"gru": 3, "lstm": 4}[kind], (K0 + 15) // 16
+    return nkb + g * (S // 16) - g * nkb >= (6 if kind == "lstm" and S in (96, 128) else 1)
+
+
+def runs_narrow(K0: int, S: int, kind: str, tiles: int, window: int) -> bool:
+    """Whether a layer 32 or 64 wide runs the kernel of 16-vertex tiles (the library's dense_narrow_wanted); tiles of 32
+    vertices, window: the longest."""
+    if S not in (32, 64):
+        return False
+    w, folds = min(window, 4), folds_transform(K0, S, kind)
+    if S == 32:
+        if K0 > 64:
+            return True
+        if K0 > 48:
+            return window > 1 or tiles >= 2048
+        return window > 1 and tiles <= (256 * w if folds else 1024)
+    if window == 1:
+        return K0 > 128 and tiles <= 256
+    if folds:
+        return tiles <= (128 if K0 > 32 else 64) * w
+    return tiles <= (1024 if K0 > 96 else 640)
+
+
+def time_encoder_work(K0: int, S: int, kind: str, tiles: int, window: int, concat: bool = False) -> dict:
+    """The kernel of the last GCN layer's transform and the time encoder (S = H, no activation between them), what it does, and
+    its flops per row: those of the layer as it is defined and those of the products that the kernel executes."""
+    gH = {"gru": 3, "lstm": 4}[kind] * S
+    rest = 2 * S * gH * (2 if concat else 1)        # hidden side, and the other half of a concatenated input
+    layer = 2 * K0 * S + 2 * S * gH + rest
+    if not concat and runs_narrow(K0, S, kind, tiles, window):
+        return {"kernel": f"k_dense_narrow<{kind.upper()}>", "what": "GCN transform + time encoder", "layer": layer, "executed": layer}
+    if folds_transform(K0, S, kind):
+        return {"kernel": f"k_dense_split<{kind.upper()}>", "what": "time encoder with the GCN transform folded into its input-side weights",
+                "layer": layer, "executed": 2 * K0 * gH + rest}
+    return {"kernel": f"k_dense_split<{kind.upper()}>", "what": "GCN transform + time encoder", "layer": layer, "executed": layer}
+
+
+def tiles_of(sizes) -> int:
+    """Tiles of 32 vertices (or lanes) of chunks of these sizes."""
+    return int(sum(-(-int(n) // 32) for n in sizes))
+
+
 def measured_traffic(workload: str, gather_mode: str) -> dict:
     """HBM bytes per launch measured with rocprofv3 --pmc FETCH_SIZE / WRITE_SIZE (two separate runs of
     this script, scaled by a plain copy of known size; figures and commands in profiles/).  They
@@ -749,7 +794,9 @@ def labelled_main(args):
     fl = flops_per_row(wl)
     n_lanes = int(layer.packing("lane_ptr")[-1]) if present is not None else 0
     dense_rows = rows if present is None else n_lanes * T           # the kernel computes every lane slot
-    dense_flops = (fl["transform"] + fl["rnn"]) * dense_rows
+    work = time_encoder_work(wl.F, wl.S, wl.time_kind, tiles_of([N if present is None else n_lanes]), T)
+    assert work["layer"] == fl["transform"] + fl["rnn"]
+    dense_flops = work["executed"] * dense_rows
     dense_ms, agg_ms = float(stage[3]), float(stage[0])
     achieved = dense_flops / (dense_ms * 1e-3) / 1e12
     if present is not None:
@@ -766,10 +813,10 @@ def labelled_main(args):
                                    f" with config2tf's presence matrix: temporal fusion over the generated chunks, {n_lanes} lanes of {T} "
                                    f"slots for {rows} present rows ({rows / max(1, n_lanes * T):.1%} of the slots filled); value counts present rows"),
                       "rows": rows, "nnz": nnz, "gather_mode": "in_place", "pass": "forward"},
-           "roofline": {"kernel": "k_dense_split<GRU, SEQ> (GCN transform + time encoder over every vertex's label runs)",
+           "roofline": {"kernel": f"{work['kernel']} ({work['what']}, over every vertex's label runs)",
                         "bound": "mfma", "achieved": achieved, "peak": PEAK_SPLIT_MFMA_TFLOPS, "unit": "TFLOP/s",
                         "frac": achieved / PEAK_SPLIT_MFMA_TFLOPS, "traffic": traffic.get("dense"),
-                        "flops_per_launch": dense_flops, "ms_per_launch": dense_ms},
+                        "flops_per_launch": dense_flops, "layer_flops_per_launch": work["layer"] * dense_rows, "ms_per_launch": dense_ms},
            "roofline_aggregation": {"kernel": "k_agg_team / k_agg + k_spmm_long_reduce (edge-table kernels over pre-marked columns)",
                                     "bound": "hbm", "achieved": agg_bytes / (agg_ms * 1e-3) / 1e9, "peak": PEAK_HBM_GBS,
                                     "unit": "GB/s", "frac": agg_bytes / (agg_ms * 1e-3) / 1e9 / PEAK_HBM_GBS,
@@ -1043,15 +1090,18 @@ def gcn_run(args) -> dict:
     fl = flops_per_row(wl)
     # the last dense launch: last GCN layer's transform + time encoder
     dense_rows = tfuse["lane_slots"] if tfuse else rows     # the kernel also computes the empty slots
-    dense_flops = (fl["transform"] + fl["rnn"]) * dense_rows if wl.n_struct_layers == 1 else \
-        (2 * wl.S * wl.S + fl["rnn"]) * dense_rows
+    size = np.diff(layer.packing("lane_ptr")) if tfuse else wl.chunks[:, 1] - wl.chunks[:, 0]
+    work = time_encoder_work(wl.F if wl.n_struct_layers == 1 else wl.S, wl.S, wl.time_kind, tiles_of(size),
+                             int((wl.chunks[:, 3] - wl.chunks[:, 2]).max()), bool(wl.notes.get("input_concat")))
+    assert work["layer"] == fl["rnn"] + (fl["transform"] if wl.n_struct_layers == 1 else 2 * wl.S * wl.S)
+    dense_flops = work["executed"] * dense_rows
     dense_ms = float(stage[3])
     achieved = dense_flops / (dense_ms * 1e-3) / 1e12
     traffic = measured_traffic(args.workload, args.gather_mode)
-    roofline = {"kernel": "k_dense_split (GCN transform + time encoder, fused over the window; without an activation between them the transform is folded into the input-side weights, the flops are those of the layer as it is defined)",
+    roofline = {"kernel": f"{work['kernel']} ({work['what']}, fused over the window)",
                 "bound": "mfma", "achieved": achieved, "peak": PEAK_SPLIT_MFMA_TFLOPS, "unit": "TFLOP/s",
                 "frac": achieved / PEAK_SPLIT_MFMA_TFLOPS, "traffic": traffic.get("dense"),
-                "flops_per_launch": dense_flops, "ms_per_launch": dense_ms}
+                "flops_per_launch": dense_flops, "layer_flops_per_launch": work["layer"] * dense_rows, "ms_per_launch": dense_ms}
     # aggregation kernels: algorithmic (compulsory) bytes = X rows once + CSR + M written once
     nnz = int(layer.packing("seg_nnz_off")[-1])
     if tfuse:
@@ -1179,15 +1229,17 @@ def config3_run(args) -> dict:
     F, S, H = 172, 128, 128
     rows = tot["rows"]
     full = bool(getattr(args, "mpnn_lstm", False))
-    dense_flops = (2 * S * S + 2 * (2 * S if full else S) * 4 * H + 2 * H * 4 * H + (4 * H * 4 * H if full else 0)) * rows
+    work = time_encoder_work(S, S, "lstm", 1 << 20, 32, concat=full)
+    second = 4 * H * 4 * H if full else 0           # the second LSTM layer
+    dense_flops = (work["executed"] + second) * rows
     dense_ms = float(stage_sum[3])
     ach = dense_flops / (dense_ms * 1e-3) / 1e12
     traffic = measured_traffic("config3_mpnn_lstm" if full else "config3", args.gather_mode)     # per window
-    roofline = {"kernel": "k_dense_split<LSTM> (second GCN transform + LSTM, fused over the window" +
+    roofline = {"kernel": f"{work['kernel']} ({work['what']}, second GCN layer, fused over the window" +
                           (", and the second LSTM layer's launch)" if full else ")"), "bound": "mfma",
                 "achieved": ach, "peak": PEAK_SPLIT_MFMA_TFLOPS, "unit": "TFLOP/s", "frac": ach / PEAK_SPLIT_MFMA_TFLOPS,
                 "traffic": traffic.get("dense"), "flops_per_launch": dense_flops / len(windows),
-                "ms_per_launch": dense_ms / len(windows)}
+                "layer_flops_per_launch": (work["layer"] + second) * rows / len(windows), "ms_per_launch": dense_ms / len(windows)}
     first_flops = 2 * F * S * rows
     agg_bytes = rows * (F * 4) * 2 + rows * (S * 4) * 2 + 2 * (tot["nnz"] * 4 + rows * 8)
     agg_ms = float(stage_sum[0] + stage_sum[2])

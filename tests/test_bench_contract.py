@@ -50,3 +50,24 @@ def test_json_line_of_the_smallest_workload(monkeypatch, capsys):
         assert key in c, key
     assert c["kind"] == "oracle" and c["value"] > 0 and c["cores"] >= 1
     assert c["gpu_max_rel_err_on_sample"] < 1e-4
+
+
+def test_dense_kernel_rules_are_the_librarys():
+    """What the roofline names and counts is what the library's own rules choose, over widths, tiles and windows on either side."""
+    import ctypes as ct
+    lib = ct.CDLL(os.path.join(ROOT, "paper_2309_03523_amd", "libdgc.so"))
+    fold, narrow = lib._ZN3dgc17dense_fold_wantedEiii, lib._ZN3dgc19dense_narrow_wantedEiibli
+    fold.restype = narrow.restype = ct.c_bool
+    fold.argtypes, narrow.argtypes = [ct.c_int32] * 3, [ct.c_int32, ct.c_int32, ct.c_bool, ct.c_int64, ct.c_int32]
+    b = _bench()
+    for kind, code in (("gru", 1), ("lstm", 2)):
+        for S in range(32, 257, 32):
+            for K0 in range(1, 305):
+                folds = b.folds_transform(K0, S, kind)
+                assert folds == fold(S, K0, code), (kind, S, K0)
+                if S > 64:
+                    assert not b.runs_narrow(K0, S, kind, 1, 8)
+                    continue
+                for tiles in (1, 64, 65, 128, 129, 192, 256, 257, 384, 512, 513, 640, 641, 768, 769, 1024, 1025, 2047, 2048, 100000):
+                    for window in (1, 2, 3, 4, 5, 32):
+                        assert b.runs_narrow(K0, S, kind, tiles, window) == narrow(S, K0, folds, tiles, window), (kind, S, K0, tiles, window)
