@@ -75,8 +75,9 @@ enum { DGC_GATHER_IN_PLACE = 0, DGC_GATHER_STAGED = 1 };
 /* Which kernel runs the dense transform + time encoder:
  *  AUTO  the split kernels where they are built (S = H, or a transform alone), else the workgroup-tile kernel;
  *  TILE  64 vertices per workgroup, operands shared through LDS, fp32 matrix instructions (any S, H up to 256);
- *  WAVE  the split kernels: 32 vertices per workgroup, fp32 products as sums of bf16 products, for
- *        S = H in {32, 64, 128} (a transform alone: 256, too); DGC_ERR_UNSUPPORTED at forward otherwise. */
+ *  WAVE  the split kernels: 32 vertices per workgroup (16 for narrow layers of few tiles), fp32 products
+ *        as sums of bf16 products, for S = H in {32, 64, 128} (a transform alone: 256, too);
+ *        DGC_ERR_UNSUPPORTED at forward otherwise. */
 enum { DGC_DENSE_AUTO = 0, DGC_DENSE_TILE = 1, DGC_DENSE_WAVE = 2 };
 /* Which kernels aggregate in IN_PLACE mode (STAGED always takes WALK):
  *  TABLE  kernels that read a per-non-zero table built at create (8 bytes per stored non-zero: the column,
@@ -171,7 +172,8 @@ dgc_status_t dgc_layer_destroy(dgc_layer_t* layer);
  *  "attn.pos" [T,S]  "attn.weight_q" "attn.weight_k" "attn.weight_v" [S,S] (out, in); values are
  *  rounded to bfloat16 where the kernels use them as matrix operands.
  *  After dgc_layer_backward, "<name>.grad" reads the gradient of that parameter (get only).
- * host_src / host_dst: host, numel elements; numel must equal the parameter's size. */
+ * host_src / host_dst: host, numel elements; numel must equal the parameter's size.  A forward recorded
+ * into a HIP graph reads the parameters that are set when the graph is replayed. */
 dgc_status_t dgc_layer_set_param(dgc_layer_t* layer, const char* name, const float* host_src,
                                  int64_t numel);
 dgc_status_t dgc_layer_get_param(dgc_layer_t* layer, const char* name, float* host_dst,
@@ -246,7 +248,8 @@ dgc_status_t dgc_layer_set_labels(dgc_layer_t* layer, const int32_t* labels, voi
 
 /* Backward pass: gradients of a scalar loss with respect to the layer's parameters, for the
  * batch of the last dgc_layer_forward on this layer (the layer keeps the aggregated rows of that
- * pass; a forward in between invalidates them).  Built for DGC_STRUCT_EVOLVE_GCN_O and
+ * pass; a forward in between invalidates them) and, for DGC_STRUCT_EVOLVE_GCN_O, the parameters it used, whatever
+ * has been set since; DGC_STRUCT_GAT reads its parameters again, so none is set between the two.  Built for DGC_STRUCT_EVOLVE_GCN_O and
  * DGC_STRUCT_GAT; other layers return DGC_ERR_UNSUPPORTED.  DGC_ERR_STATE if no forward has run.
  * DGC_STRUCT_GAT needs a symmetric adjacency (its gradient with respect to a neighbour's
  * projection is gathered through the reverse edge).

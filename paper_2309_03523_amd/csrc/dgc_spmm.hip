@@ -474,7 +474,7 @@ __device__ __forceinline__ AggCtx agg_ctx(const SpmmArgs& a, const Segment& sg, 
 }
 
 // TEAM: the four waves of a workgroup share the rows of more than kShared<LPR> non-zeros, a quarter each: they are left in
-// `queue` here and taken by agg_team.
+// `queue` here and taken by k_agg_team.
 struct TeamRow {
   int64_t e;        // table entry of the row's first non-zero
   int64_t orow;     // row of M (a part: of the partial sums)
