@@ -734,7 +734,9 @@ dgc_status_t build_layer(dgc_layer* L, const dgc_graph_t* graph, hipStream_t st)
     if ((rc = add_param(L, "rnn.bias_ih", gH, 0, st)) != DGC_OK) return rc;
     if ((rc = add_param(L, "rnn.bias_hh", gH, 0, st)) != DGC_OK) return rc;
     const int32_t K0 = two ? d.S : d.F;
-    if (sp && d.act_out == DGC_ACT_NONE && dense_fold_wanted(d.S, K0, d.time_kind)) {
+    // (not for a layer whose tiles are the narrow kernel's: presence and labels hardly make them more)
+    if (sp && d.act_out == DGC_ACT_NONE && dense_fold_wanted(d.S, K0, d.time_kind) &&
+        !(nw && dense_narrow_wanted(d.H, K0, true, L->n_tiles32, L->longest_window))) {
       float* pk = nullptr;
       DGC_HIP_TRY(dev_alloc(L, &L->fold.W, (int64_t)gH * K0));
       DGC_HIP_TRY(dev_alloc(L, &L->fold.bias, gH));
