@@ -1048,7 +1048,7 @@ def gcn_run(args) -> dict:
     # so the caller can record it once and replay it
     graph_ms = None
     if args.workload in ("config1", "config4s"):
-        # (config4s: its weight recurrence is some 330 small dependent launches per step)
+        # (config4s: some twenty launches a step on two streams)
         side = torch.cuda.Stream()
         side.wait_stream(stream)
         hip_graph = torch.cuda.CUDAGraph()
