@@ -286,7 +286,7 @@ dgc_status_t dgc_layer_gather(dgc_layer_t* layer, const float* C, int64_t ldc, f
 
 /* Per-stage device time, from HIP events recorded on the stream that the stage runs on (for
  * measurement; adds no synchronisation to forward / backward themselves).  That is the caller's
- * stream, but for stage 4 and, in a backward that computes dX, stage 6: they run on a stream of
+ * stream, but for stage 4 (more than two snapshots, or F <= 64) and, in a backward that computes dX, stage 6: they run on a stream of
  * the layer's own and may overlap stage 0 and the input gradient, so the stages of an EvolveGCN-O
  * pass do not add up to it (and a wait of one stream for the other is in no stage; but a stage's
  * time includes what its launches wait for compute units that the other stream holds).  Stages:

@@ -1124,17 +1124,24 @@ dgc_status_t dgc_layer_forward(dgc_layer_t* L, const void* Xv, int64_t ldx, cons
   L->ev_valid = false;
   const bool evolve = d.struct_kind == DGC_STRUCT_EVOLVE_GCN_O;
   L->evx_fwd = false;
+  const bool beside = evolve && (L->T > 2 || d.F <= 64);
   if (evolve) {
     // The weights evolve on a stream of their own: one launch of S / 4 workgroups that walks all snapshots beside the
     // aggregation, and so does the back-propagation beside the input gradient when that is asked for.  A training step of
     // 64 snapshots x 62 500 vertices, F = 256, takes 26.8 ms on one stream and 25.6 on two, of 16 x 5000 1.57 and 1.38 ms; of 16 x 3000,
     // F = 64, 0.40 ms either way (0.33 and 0.34 without the input gradient).
-    DGC_HIP_TRY(hipEventRecord(L->fork, st));
-    DGC_HIP_TRY(hipStreamWaitEvent(L->side, L->fork, 0));
-    if (prof) DGC_HIP_TRY(hipEventRecord(L->evx[0], L->side));
-    evolve_forward_weights(L->evo, L->side);
-    if (prof) { DGC_HIP_TRY(hipEventRecord(L->evx[1], L->side)); L->evx_fwd = true; }
-    DGC_HIP_TRY(hipEventRecord(L->join, L->side));
+    // Not one or two snapshots whose matrices are streamed: such a walk is as short as the events, and its workgroups, a CU each,
+    // wait for the aggregation's to leave (500 vertices, width 256, 1 and 2 snapshots: 68.6 and 84.2 us on two streams, 51.4 and 67.3 on
+    // one; 80 000: 187 and 342, 185 and 345; two launches a snapshot took 61.3, 79.7, 180 and 336).
+    if (beside) {
+      DGC_HIP_TRY(hipEventRecord(L->fork, st));
+      DGC_HIP_TRY(hipStreamWaitEvent(L->side, L->fork, 0));
+    }
+    hipStream_t walk = beside ? L->side : st;
+    if (prof) DGC_HIP_TRY(hipEventRecord(L->evx[0], walk));
+    evolve_forward_weights(L->evo, walk);
+    if (prof) { DGC_HIP_TRY(hipEventRecord(L->evx[1], walk)); L->evx_fwd = true; }
+    if (beside) DGC_HIP_TRY(hipEventRecord(L->join, L->side));
   }
   if (prof) DGC_HIP_TRY(hipEventRecord(L->ev[0], st));
   // with temporal fusion the aggregation that feeds the time encoder writes its rows in lane
@@ -1142,7 +1149,7 @@ dgc_status_t dgc_layer_forward(dgc_layer_t* L, const void* Xv, int64_t ldx, cons
   const bool tfl1 = L->tf.built && d.n_struct_layers == 1, tfl2 = L->tf.built && d.n_struct_layers == 2;
   run_aggregate(L, X, ldx, C, ldc, d.F, tfl1 ? L->tf.Mv : L->d_M, L->ldm, st, tfl1 ? L->tf.row_map : nullptr);
   if (prof) DGC_HIP_TRY(hipEventRecord(L->ev[1], st));
-  if (evolve) DGC_HIP_TRY(hipStreamWaitEvent(st, L->join, 0));      // in no stage: between two events
+  if (beside) DGC_HIP_TRY(hipStreamWaitEvent(st, L->join, 0));      // in no stage: between two events
   const char* last = "gcn0";
   if (d.n_struct_layers == 2) {
     // first layer for every row of the batch -> Z1 [T,N,S]; then aggregate Z1 | C1

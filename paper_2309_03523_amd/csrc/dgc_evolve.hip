@@ -37,8 +37,7 @@ namespace {
 // Measured alone, per snapshot: n = 64 1.4 us forward and 1.2 back (8 and 10 us as two launches per snapshot of 16 x 16
 // tiles, K split over four waves, with the gaps between them), n = 128 4.1 and 5.2, n = 256 17.7 and 21.4 (20 and 31).
 // The matrices' batches take the registers to their limit in the widest walks: of a lane 12 (forward) and 18 (back) go to scratch
-// for n = 224, 10 back for n = 256.  A single snapshot of n >= 224 is not faster so: its matrices are packed for one step
-// (a forward of 500 vertices 67 us, 62 with the two launches).
+// for n = 224, 10 back for n = 256.
 typedef double doublex4 __attribute__((ext_vector_type(4)));
 typedef double doublex2 __attribute__((ext_vector_type(2)));
 

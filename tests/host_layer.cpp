@@ -286,6 +286,20 @@ static void folded_weights() {
   }
 }
 
+// One or two snapshots of streamed matrices evolve on the caller's stream, before the aggregation and the transform.
+static void one_stream() {
+  for (int T : {1, 2, 3}) {
+    dgc_layer* L = evolve_layer();
+    L->T = T;
+    L->desc.F = L->desc.S = L->desc.H = 96;
+    calls.clear();
+    expect(dgc_layer_forward(L, tensor, 96, tensor, 96, nullptr, 0, nullptr, nullptr, tensor, 96, nullptr, nullptr) == DGC_OK, "forward");
+    expect(count("recurrence") == 1 && count("spmm") == 1 && count("dense") == 1, "its launches");
+    if (T <= 2) expect(calls == std::vector<std::string>({"recurrence", "spmm", "dense"}), "no event, in this order");
+    else expect(count("wait") == 2, "more snapshots: beside the aggregation");
+  }
+}
+
 // Large dynamic LDS is allowed once on every device that a kernel runs on; a refusal is reported and not taken for done.
 static void lds_per_device() {
   std::atomic<uint64_t> done{0};
@@ -307,6 +321,7 @@ int main(int argc, char** argv) {
   else if (check == "label memory") label_memory();
   else if (check == "stage events") stage_events();
   else if (check == "lds per device") lds_per_device();
+  else if (check == "one stream") one_stream();
   else if (check == "evolve memory") evolve_memory();
   else if (check == "gradient read") gradient_read();
   else if (check == "folded weights") folded_weights();
