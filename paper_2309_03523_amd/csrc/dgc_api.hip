@@ -304,7 +304,7 @@ dgc_status_t add_param(dgc_layer* L, const std::string& name, int32_t n_out, int
   };
   dgc_status_t rc;
   if (n_in) {
-    const int64_t pe = split ? split_weight_bytes(n_out, n_in) / (int64_t)sizeof(float) : packed_weight_elems(n_out, n_in);
+    const int64_t pe = split ? split_halves_bytes(n_out, n_in) / (int64_t)sizeof(float) : packed_weight_elems(n_out, n_in);
     if ((rc = packed(pe, &p.packed)) != DGC_OK) return rc;
     if (narrow && (rc = packed(narrow_weight_bytes(n_out, n_in) / (int64_t)sizeof(float), &p.narrow)) != DGC_OK) return rc;
   }
@@ -740,7 +740,7 @@ dgc_status_t build_layer(dgc_layer* L, const dgc_graph_t* graph, hipStream_t st)
       float* pk = nullptr;
       DGC_HIP_TRY(dev_alloc(L, &L->fold.W, (int64_t)gH * K0));
       DGC_HIP_TRY(dev_alloc(L, &L->fold.bias, gH));
-      DGC_HIP_TRY(dev_alloc(L, &pk, split_weight_bytes(gH, K0) / (int64_t)sizeof(float)));
+      DGC_HIP_TRY(dev_alloc(L, &pk, split_halves_bytes(gH, K0) / (int64_t)sizeof(float)));
       DGC_HIP_TRY(dev_alloc(L, &L->fold.bad, 1));
       L->fold.packed = reinterpret_cast<float4*>(pk);
       L->fold.may = true;
@@ -971,6 +971,14 @@ dgc_status_t dgc_layer_destroy(dgc_layer_t* L) {
   return DGC_OK;
 }
 
+// A weight in both forms that the split kernel reads.
+static hipError_t pack_split(const float* W, int32_t n_out, int32_t n_in, float4* packed) {
+  char* const word = reinterpret_cast<char*>(packed) + split_halves_bytes(n_out, n_in) - 64;
+  const hipError_t e = hipMemset(word, 0, sizeof(int32_t));
+  if (e == hipSuccess) launch_pack_split(W, 0, n_in, 1, n_out, n_in, 1, packed, true, nullptr);
+  return e;
+}
+
 // After a parameter of the transform or of the time encoder's input side has changed: the product of the two.
 static dgc_status_t refold(dgc_layer* L, const std::string& name) {
   Failer fail{L};
@@ -991,7 +999,7 @@ static dgc_status_t refold(dgc_layer* L, const std::string& name) {
   DGC_HIP_TRY(hipMemset(f.bad, 0, sizeof(int32_t)));
   launch_fold(wih.raw + other, wih.n_in, wg.raw, L->params[names[1]].raw, L->params[names[3]].raw, wih.n_out, d.S, wg.n_in, f.W, f.bias,
               f.bad, nullptr);
-  launch_pack_split(f.W, 0, wg.n_in, 1, wih.n_out, wg.n_in, 1, f.packed, nullptr);
+  DGC_HIP_TRY(pack_split(f.W, wih.n_out, wg.n_in, f.packed));
   DGC_HIP_TRY(hipGetLastError());
   DGC_HIP_TRY(hipDeviceSynchronize());
   f.made = true;
@@ -1015,7 +1023,7 @@ dgc_status_t dgc_layer_set_param(dgc_layer_t* L, const char* name, const float* 
     DGC_HIP_TRY(hipDeviceSynchronize());
   } else if (p.packed) {
     if (p.narrow) launch_pack_narrow(p.raw, p.n_out, p.n_in, p.narrow, nullptr);
-    if (p.split) launch_pack_split(p.raw, 0, p.n_in, 1, p.n_out, p.n_in, 1, p.packed, nullptr);
+    if (p.split) DGC_HIP_TRY(pack_split(p.raw, p.n_out, p.n_in, p.packed));
     else launch_pack_weight(p.raw, p.n_out, p.n_in, p.packed, nullptr);
     DGC_HIP_TRY(hipDeviceSynchronize());
   }

@@ -1,15 +1,23 @@
-// Dense part of the layer on the bf16 matrix cores at fp32 accuracy.
+// Dense part of the layer on the matrix cores of 16-bit numbers at fp32 accuracy.
 //
-// An fp32 number is the exact sum of three bf16 numbers, each the nearest to what is left (split8), so a product of fp32
-// operands is six bf16 MFMAs: hi*hi, hi*mid, mid*hi, mid*mid, hi*lo, lo*hi, all accumulated in fp32.  What is left out
-// (mid*lo, lo*mid, lo*lo) is within 2^-24 of the product and of either sign: over random operands 2^-28 in the mean,
-// without a bias.  (Parts cut off instead of rounded leave out up to 2^-21 and 2^-24.5 in the mean, always of the
-// product's own sign: a GRU over 32 x 100 000 rows is then 2.5e-7 off 64 bits instead of 2.3e-7, EvolveGCN-O's gradients
-// twice to three times as far.)  v_mfma_f32_32x32x16_bf16 does 16 times the work of v_mfma_f32_32x32x2f32 per cycle, so the
-// six cost 2.7 times less than the fp32 instruction and add up in fewer roundings.  No scaling is needed, but
-// at the ends of the range fp32 has a little more: a product within 1 % of the largest float may overflow (its rounded high
-// parts do), and of a number below 2^-110 the parts below the smallest bf16 number are lost (a transform of nothing but
-// such rows is 3e-7 off at 2^-112 and 3e-3 at 2^-126).
+// Transforms alone: an fp32 number is the exact sum of three bf16 numbers, each the nearest to what is left (split8), so a
+// product of fp32 operands is six bf16 MFMAs: hi*hi, hi*mid, mid*hi, mid*mid, hi*lo, lo*hi, all accumulated in fp32.  What is
+// left out (mid*lo, lo*mid, lo*lo) is within 2^-24 of the product and of either sign: over random operands 2^-28 in the mean,
+// without a bias.  (Parts cut off instead of rounded leave out up to 2^-21, always of the product's own sign: EvolveGCN-O's
+// gradients are then twice to three times as far off.)  v_mfma_f32_32x32x16_bf16 does 16 times the work of
+// v_mfma_f32_32x32x2f32 per cycle, so the six cost 2.7 times less than the fp32 instruction and add up in fewer roundings.  No
+// scaling is needed, but at the ends of the range fp32 has a little more: a product within 1 % of the largest float may
+// overflow (its rounded high parts do), and of a number below 2^-110 the parts below the smallest bf16 number are lost (a
+// transform of nothing but such rows is 3e-7 off at 2^-112 and 3e-3 at 2^-126).
+//
+// Time encoders: their sums go into sigmoid and tanh, which are at most 1 and off by a rounding of 1, so an error that is small
+// beside 1 does.  There a number is two half-precision numbers (halve8), and a product three MFMAs: hi*lo, lo*hi, hi*hi.  Two
+// halves hold 22 to 24 bits of a number, and nothing below 2^-31 of an input or a state (taken 64 times) and 2^-35 of a weight
+// (1024 times); what is left out, lo*lo, is within 2^-22 of the product and of either sign.  With tanh_of, whose series keeps what
+// 1 - 2 / (1 + e^2x) loses below 1/2, outputs and states are nearer to 64 bits than on six bf16 products and the plain
+// formula: over 46 outputs of drawn cases 0.69 of the distance in the mean, 0.95 at most.  Where an operand is above 1023 (or a weight
+// above 16, all of a matrix below 2^-8, a bias above 1e30) the tile goes on from that step on three bf16 parts.
+// GRU 128 wide, 3.2 M rows: 3.5 -> 2.35 ms; the two LSTM layers of MPNN-LSTM over 1.28 M rows 2.78 + 1.99 -> 1.9 + 1.2.
 //
 // With the weights as A operand (lane l: A[l%32][8*(l/32) .. +7]) and 32 activation rows as B operand
 // (B[8*(l/32) .. +7][l%32]), lane (n = l%32, half = l/32) receives of row n the columns 8*g4 + 4*half + e in
@@ -17,14 +25,11 @@
 // 8*half + 4*p + e stand for columns 8*p + 4*half + e: with the weights' columns packed in that order a
 // result is the next product's operand without moving between lanes.
 //
-// What bounds them: the matrix cores' power.  Random operands through a loop of nothing but this MFMA reach
-// 1.8 PFLOP/s of bf16 on this GPU (2.46 with zeros), a library product 1.33; the time encoders run at 1.1, at 1.6 GHz in
-// the mean with the matrix units busy for two cycles of three
-// (GRU 128 wide, 3.2 M rows: 6.27 ms on the fp32 instruction, 3.93 ms here, 3.5 with the transform folded; the two LSTM layers of
-// MPNN-LSTM over 1.28 M rows 6.90 + 4.35 -> 2.9 + 1.95 ms, the first 2.78 folded; GRU 256 wide, 160 k rows 2.29 -> 0.9, 0.85).  Without the weights' loads,
-// the LDS reads and the gate arithmetic the first would still take 3.5 ms (of 3.93), with half of the products 2.7.  Tiles of 64 vertices halve the weights'
-// L2 traffic and are no faster (4.15 ms: two workgroups of 256 registers a wave, more work behind each barrier);
-// three workgroups per CU of 168 registers spill (4.36 ms).
+// What bounds them.  Transforms: the matrix cores' power.  Random operands through a loop of nothing but this MFMA reach
+// 1.8 PFLOP/s of bf16 on this GPU (2.46 with zeros), a library product 1.33.
+// Time encoders: the weights' way from the L2 to the registers, 64 bytes a cycle and CU.  With a third of the products they take
+// the same time, with three waves a SIMD instead of two, too (2.35 ms of GRU 128 wide, of 3.2 M rows, at 40 % of the matrix cores' cycles);
+// with every weight read from the nearest cache 2.1.
 //
 // k_dense_split (time encoders): a workgroup owns 32 vertices of one chunk and walks the chunk's window; wave jb
 // owns columns 32*jb .. +31 of Z, of every gate and of the state.  So a weight fragment is read from L2 by one
@@ -45,18 +50,36 @@ namespace {
 using namespace split;
 
 constexpr int kUnitBytes = 3 * kFrag * 16; // a weight fragment's three parts
+template <int P> constexpr int kUnit = P * kFrag * 16;    // P parts
 
-__device__ __forceinline__ float sigmoid_fast(float x) { return __builtin_amdgcn_rcpf(1.0f + __expf(-x)); }
-__device__ __forceinline__ float tanh_fast(float x) { return 1.0f - 2.0f * __builtin_amdgcn_rcpf(1.0f + __expf(2.0f * x)); }
+// What a matrix's word says of it: a weight is above 16 or not finite; one is at least 2^-8; one is not zero.
+constexpr int32_t kHalfLarge = 1, kHalfFull = 2, kHalfAny = 4;
+constexpr float kHalfLeast = 0x1p-8f, kHalfWeight = 16.f;
+constexpr float kActScale = 64.f, kWeightScale = 1024.f, kSumScale = kActScale * kWeightScale;
+constexpr float kMostBias = 1e30f;
+
+// Of x scale: the gates' arguments come in the scale of their sums.
+__device__ __forceinline__ float sigmoid_of(float x, float scale) {
+  return __builtin_amdgcn_rcpf(1.0f + __builtin_amdgcn_exp2f(x * (-1.4426950408889634f * scale)));
+}
+// Below 1/2 by x + x^3 P(x^2), P the polynomial of least relative error there (1.5e-8): 1 - 2 / (1 + e^2x) leaves an error of the
+// size of 1's rounding however small x is.
+__device__ __forceinline__ float tanh_of(float x, float scale) {
+  const float y = x * scale, z = y * y;
+  const float p = fmaf(fmaf(fmaf(0.01724136434495449f, z, -0.05304544046521187f), z, 0.13325878977775574f), z, -0.333331435918808f);
+  const float t = fmaf(-2.0f, __builtin_amdgcn_rcpf(1.0f + __builtin_amdgcn_exp2f(x * (2.8853900817779268f * scale))), 1.0f);
+  return fabsf(y) < 0.5f ? fmaf(y * z, p, y) : t;
+}
 // Weights come by buffer loads: resource descriptor in scalar registers, the fragment's place as scalar
 // offset, the lane's 16 bytes as vector offset.  A vector offset beyond the resource reads as zero without
 // touching memory: that is what a fragment past the end of a product gets, so that the loops have no branches.
 struct WeightStream {
   __amdgpu_buffer_rsrc_t rsrc;
-  __device__ __forceinline__ void unit(uint4 (&w)[3], int lane16, int off, bool there) const {
+  template <int P>
+  __device__ __forceinline__ void unit(uint4 (&w)[P], int lane16, int off, bool there) const {
     const int v = lane16 + (there ? 0 : 0x40000000);
 #pragma unroll
-    for (int p = 0; p < 3; ++p) {
+    for (int p = 0; p < P; ++p) {
       const intx4 x = __builtin_amdgcn_raw_buffer_load_b128(rsrc, v, off + p * kFrag * 16, 0);
       w[p] = make_uint4(x.x, x.y, x.z, x.w);
     }
@@ -68,25 +91,44 @@ __device__ __forceinline__ WeightStream make_stream(const void* p, int64_t bytes
   return w;
 }
 
+// A matrix of `units` fragments as k_pack_split leaves it: three bf16 parts a fragment, two halves a fragment, and a word.
+struct Weights {
+  const uint4* parts;
+  int units;
+  __device__ __forceinline__ Weights(const void* p, int n) : parts(static_cast<const uint4*>(p)), units(n) {}
+  __device__ __forceinline__ WeightStream stream(std::integral_constant<int, 3>) const { return make_stream(parts, (int64_t)units * kUnit<3>); }
+  __device__ __forceinline__ WeightStream stream(std::integral_constant<int, 2>) const {
+    return make_stream(parts + (int64_t)units * 3 * kFrag, (int64_t)units * kUnit<2>);
+  }
+  __device__ __forceinline__ bool halves_good() const {
+    const int32_t w = table_entry(reinterpret_cast<const int32_t*>(parts + (int64_t)units * 5 * kFrag), 0);
+    return !(w & kHalfLarge) && (w & (kHalfFull | kHalfAny)) != kHalfAny;
+  }
+};
+
 // The weight fragments of a product are read in the order (k-block, gate), D - 1 of them ahead of their use.
 // fetch_ahead: the first D - 1, before the barrier that the product waits at.  nkb: k-blocks that have weights.
-template <int NG, int D>
-__device__ __forceinline__ void fetch_ahead(uint4 (&w)[D][3], const WeightStream& ws, int off, int gstride, int nkb, int lane16) {
+template <int NG, int D, int P>
+__device__ __forceinline__ void fetch_ahead(uint4 (&w)[D][P], const WeightStream& ws, int off, int gstride, int nkb, int lane16) {
 #pragma unroll
-  for (int u = 0; u < D - 1; ++u) ws.unit(w[u], lane16, off + (u % NG) * gstride + (u / NG) * kUnitBytes, u / NG < nkb);
+  for (int u = 0; u < D - 1; ++u) ws.unit(w[u], lane16, off + (u % NG) * gstride + (u / NG) * kUnit<P>, u / NG < nkb);
 }
 
 // acc(g) + small(g) += W_g x rows, over nkb k-blocks (small: the five small products; may be acc); fr: this lane's
 // first operand of the staged rows.  LINKS: the small products of every k-block go to a sum of their own, which is added
 // to acc by rounding additions.
-template <int NG, int D, bool LINKS = false, class Acc, class Small>
+template <int NG, int D, int P, bool LINKS = false, class Acc, class Small>
 __device__ __forceinline__ void product(Acc&& acc, Small&& small, const uint4* fr, const WeightStream& ws, int off, int gstride, int nkb,
-                                        int lane16, uint4 (&w)[D][3]) {
+                                        int lane16, uint4 (&w)[D][P]) {
   constexpr int UK = D > NG ? D / NG : 1;
   static_assert((UK * NG) % D == 0, "the buffers come round within the unrolled k-blocks");
-  uint4 b[3];
+  auto add = [](floatx16& c, floatx16& s, const uint4 (&a)[P], const uint4 (&b)[P]) {
+    if constexpr (P == 3) six(c, s, a, b);
+    else three(c, s, a, b);
+  };
+  uint4 b[P];
 #pragma unroll
-  for (int p = 0; p < 3; ++p) b[p] = fr[p * kFrag];
+  for (int p = 0; p < P; ++p) b[p] = fr[p * kFrag];
   __builtin_amdgcn_s_setprio(1);   // the other workgroups of the CU do their vector work beside this
 #pragma unroll 1
   for (int kb = 0; kb < nkb; kb += UK) {
@@ -98,19 +140,19 @@ __device__ __forceinline__ void product(Acc&& acc, Small&& small, const uint4* f
       for (int g = 0; g < NG; ++g) {
         const int u = i * NG + g;
         const int kn = k + (g + D - 1) / NG, gn = (g + D - 1) % NG;
-        ws.unit(w[(u + D - 1) % D], lane16, off + gn * gstride + kn * kUnitBytes, kn < nkb);
+        ws.unit(w[(u + D - 1) % D], lane16, off + gn * gstride + kn * kUnit<P>, kn < nkb);
         __builtin_amdgcn_sched_barrier(0);
         if constexpr (LINKS) {
           floatx16 link = (floatx16)(0.f);
-          six(acc(g), link, w[u % D], b);
+          add(acc(g), link, w[u % D], b);
           acc(g) += link;
         } else {
-          six(acc(g), small(g), w[u % D], b);
+          add(acc(g), small(g), w[u % D], b);
         }
         if (g == NG - 1) {
-          const uint4* next = fr + min(k + 1, nkb - 1) * (3 * kFrag);
+          const uint4* next = fr + min(k + 1, nkb - 1) * (P * kFrag);
 #pragma unroll
-          for (int p = 0; p < 3; ++p) b[p] = next[p * kFrag];
+          for (int p = 0; p < P; ++p) b[p] = next[p * kFrag];
         }
         __builtin_amdgcn_sched_barrier(0);
       }
@@ -127,6 +169,14 @@ __device__ __forceinline__ void load_x(const float* row, int kb, float4 (&x)[2])
 __device__ __forceinline__ void put_x(uint4* frag, const float4 (&x)[2]) {
   const float v[8] = {x[0].x, x[0].y, x[0].z, x[0].w, x[1].x, x[1].y, x[1].z, x[1].w};
   put(frag, v);
+}
+// x scale as two halves; whether one of them is too large
+__device__ __forceinline__ bool put_halves(uint4* frag, const float (&v)[8], float scale) {
+  uint4 p[2];
+  const float top = halve8(v, scale, p);
+#pragma unroll
+  for (int q = 0; q < 2; ++q) frag[q * kFrag] = p[q];
+  return top * scale > kHalfMost;
 }
 // a lane's 16 values of a 32-column block in global memory or LDS; p: its first column
 __device__ __forceinline__ floatx16 load_block(const float* p) {
@@ -156,19 +206,17 @@ __device__ __forceinline__ void relu(floatx16& z) {
 // distance in the mean of 46 outputs of GRUs, 0.94 of 24 of LSTMs, 0.999 at most).
 enum Input { kTransform, kFolded, kStack };
 
+template <int NG, bool FEW, int P> constexpr int kHeldOf = FEW && P == 3 ? 2 : NG;     // weight fragments held of the gates
+
 // KIND: DGC_TIME_GRU or DGC_TIME_LSTM.  SEQ, CAT: as the fields of DenseArgs say (sequences inside the window;
 // the time encoder's input is [X2 row, Z]).
-template <int KIND, bool SEQ, bool CAT, Input INPUT>
+// HALVES: on two halves a number while these hold them, and on three bf16 parts from the step on where one does not.
+template <int KIND, bool SEQ, bool CAT, Input INPUT, bool HALVES>
 __device__ __forceinline__ void dense_split(const DenseArgs& a) {
   constexpr bool kLstm = KIND == DGC_TIME_LSTM, STACK = INPUT == kStack, FOLD = INPUT == kFolded;
   const float* const bih = FOLD ? a.bf : a.bih;
-  // The five small products of Z go apart from the large one (the matrix unit truncates when it adds, and a small sum is
-  // truncated by less), the gates' do not (no registers), but for a second recurrent layer: without a transform whose
-  // better sums make up for it, its gates' products alone would be off 64 bits by up to 1.4 times as much as on the fp32
-  // instruction.  There every k-block's go apart (0.8 times as much; two LSTM layers over 1.28 M rows 7.17 -> 7.32 ms).
-  // Every variant adds in one order with and without SEQ: a sequence table that says what the window says gives the same numbers.
   constexpr int NG = kLstm ? 4 : 3;
-  constexpr int DG = SEQ && CAT ? 2 : NG, DZ = SEQ ? 3 : 4;    // weight fragments held: gates, transform
+  constexpr int DZ = SEQ ? 3 : 4;             // weight fragments held of the transform
   extern __shared__ __align__(16) uint4 lds[];
   const int njb = blockDim.x >> 6, kbh = 2 * njb, H = 32 * njb;
   const int lane = threadIdx.x & 63, l32 = lane & 31, half = lane >> 5;
@@ -181,6 +229,12 @@ __device__ __forceinline__ void dense_split(const DenseArgs& a) {
   uint4* other = buf + kbc * 3 * kFrag;
   float* gbias = reinterpret_cast<float*>(lds + 2 * kbc * 3 * kFrag);
   float* zbias = gbias + 4 * H;
+  int* said = reinterpret_cast<int*>(zbias + H);    // the last two products with an operand out of range; [2]: a bias is
+  if constexpr (HALVES) {
+    if (threadIdx.x < 3) said[threadIdx.x] = 0;
+    __syncthreads();
+  }
+  float most_bias = 0.f;
   for (int i = threadIdx.x; i < H; i += blockDim.x) {
     zbias[i] = a.bg ? a.bg[i] : 0.f;
     if constexpr (kLstm) {
@@ -192,18 +246,22 @@ __device__ __forceinline__ void dense_split(const DenseArgs& a) {
       gbias[2 * H + i] = bih[2 * H + i];
       gbias[3 * H + i] = a.bhh[2 * H + i];
     }
+    most_bias = fmaxf(most_bias, fabsf(zbias[i]));
+#pragma unroll
+    for (int g = 0; g < 4; ++g) most_bias = fmaxf(most_bias, fabsf(gbias[g * H + i]));
   }
+  if (HALVES && most_bias > kMostBias) said[2] = 1;
   const DenseTile tile = table_entry(a.tiles32, blockIdx.x);
   const ChunkInfo ch = table_entry(a.chunks, tile.chunk);
   const int nkb0 = STACK ? kbh : (a.K0 + 15) / 16, nchunk = (nkb0 + kbc - 1) / kbc;
   const int kbx = CAT ? 2 * kbh : kbh;        // k-blocks of the time encoder's input
   const int64_t V = a.total_state_rows;
-  const WeightStream wsg = make_stream(FOLD ? a.Wf : a.Wg, STACK ? 0 : (int64_t)(FOLD ? NG : 1) * njb * nkb0 * kUnitBytes);
-  const WeightStream wsi = make_stream(a.Wih, (int64_t)NG * njb * kbx * kUnitBytes);
-  const WeightStream wsh = make_stream(a.Whh, (int64_t)NG * njb * kbh * kUnitBytes);
-  const int offz = jb * nkb0 * kUnitBytes;
-  const int offx = jb * kbx * kUnitBytes, gsx = njb * kbx * kUnitBytes;
-  const int offh = jb * kbh * kUnitBytes, gsh = njb * kbh * kUnitBytes;
+  const Weights wsg(FOLD ? a.Wf : a.Wg, STACK ? 0 : (FOLD ? NG : 1) * njb * nkb0);
+  const Weights wsi(a.Wih, NG * njb * kbx);
+  const Weights wsh(a.Whh, NG * njb * kbh);
+  const int uz = jb * nkb0;                   // first fragments of this wave, and from gate to gate
+  const int ux = jb * kbx, gx = njb * kbx, uh = jb * kbh, gh = njb * kbh;
+  const int uf = jb * nkb0, gf = njb * nkb0;
   const int col0 = 32 * jb + 4 * half;        // this lane's columns: col0 + 8*g4 + e
   const bool valid = l32 < tile.nrows;        // rows past the tile's end repeat its last row and are never stored
   const int row = min(l32, tile.nrows - 1);
@@ -228,39 +286,49 @@ __device__ __forceinline__ void dense_split(const DenseArgs& a) {
 #pragma unroll
     for (int q = 0; q < 2; ++q) load_x(p, min(c * kbc + 2 * jb + q, nkb0 - 1), xq[q]);
   };
+  // a 16-column block of numbers -> its place in a buffer of P parts a k-block; whether it is out of the halves' range
+  auto put_parts = [&](auto parts, int kb, const float (&x)[8], float scale) -> bool {
+    constexpr int P = decltype(parts)::value;
+    uint4* const frag = buf + kb * P * kFrag;
+    if constexpr (P == 2) return put_halves(frag, x, scale);
+    put(frag, x);
+    return false;
+  };
   // An infinite input makes NaN of the gates: Z's infinities have either sign, and so the gates' sums (k_fold finds the weights
   // of which this is not true, and they are not folded).  The folded weights would hide that.
-  auto put_row = [&](uint4* frag, const float4 (&x)[2]) {
-    if constexpr (FOLD) {
-      auto nan_of_inf = [](float4 v) { return make_float4(fmaf(v.x, 0.f, v.x), fmaf(v.y, 0.f, v.y), fmaf(v.z, 0.f, v.z), fmaf(v.w, 0.f, v.w)); };
-      const float4 y[2] = {nan_of_inf(x[0]), nan_of_inf(x[1])};
-      put_x(frag, y);
-    } else {
-      put_x(frag, x);
-    }
+  auto put_row = [&](auto parts, int kb, const float4 (&x)[2]) -> bool {
+    float v[8] = {x[0].x, x[0].y, x[0].z, x[0].w, x[1].x, x[1].y, x[1].z, x[1].w};
+    if constexpr (FOLD)
+#pragma unroll
+      for (int e = 0; e < 8; ++e) v[e] = fmaf(v[e], 0.f, v[e]);
+    return put_parts(parts, kb, v, kActScale);
   };
-  auto stage_x = [&](int s, int c) {
+  auto stage_x = [&](auto parts, int s, int c) -> bool {
     const int k0 = c * kbc, n = min(kbc, nkb0 - k0);
+    bool out = false;
 #pragma unroll
     for (int q = 0; q < 2; ++q)
-      if (2 * jb + q < n) put_row(buf + (2 * jb + q) * 3 * kFrag, xq[q]);
+      if (2 * jb + q < n) out |= put_row(parts, 2 * jb + q, xq[q]);
     for (int kb = 2 * (jb + njb); kb < n; kb += 2 * njb)
 #pragma unroll
       for (int q = 0; q < 2; ++q)
         if (kb + q < n) {
           float4 x[2];
           load_x(in_row(s), k0 + kb + q, x);
-          put_row(buf + (kb + q) * 3 * kFrag, x);
+          out |= put_row(parts, kb + q, x);
         }
+    return out;
   };
-  // a 32-column block in registers -> k-blocks 2*jb, 2*jb + 1 of the other buffer
+  // a 32-column block in registers -> k-blocks 2*jb, 2*jb + 1
   auto turn = [&]() { uint4* x = buf; buf = other; other = x; };
-  auto put_block = [&](const floatx16& v) {
+  auto put_block = [&](auto parts, const floatx16& v, float scale) -> bool {
+    bool out = false;
 #pragma unroll
     for (int q = 0; q < 2; ++q) {
       const float x[8] = {v[8 * q], v[8 * q + 1], v[8 * q + 2], v[8 * q + 3], v[8 * q + 4], v[8 * q + 5], v[8 * q + 6], v[8 * q + 7]};
-      put(buf + (2 * jb + q) * 3 * kFrag, x);
+      out |= put_parts(parts, 2 * jb + q, x, scale);
     }
+    return out;
   };
 
   floatx16 h = (floatx16)(0.f), c = (floatx16)(0.f);
@@ -295,93 +363,113 @@ __device__ __forceinline__ void dense_split(const DenseArgs& a) {
     if constexpr (kLstm) c = load_block(a.H0 + (V + s0) * H + col0);
   }
   enter(ch.t_lo);
-  uint4 wg[DG][3], wz[DZ][3];
-  fetch_ahead<NG, DG>(wg, wsh, offh, gsh, kbh, lane16);
-  request_x(0, 0);
+  if constexpr (HALVES) __syncthreads();
+  int number = 0;                             // of products so far
 
-  for (int s = 0; s < ch.w; ++s) {
+  // A step on P parts.  False: an operand is out of the halves' range, and nothing has changed yet.
+  auto step = [&](auto parts, auto& wg, int s) -> bool {
+    constexpr int P = decltype(parts)::value;
+    constexpr float up = P == 2 ? kSumScale : 1.f, down = 1.f / up;     // the sums are in the scale of the products
     const int64_t ts = ch.t_lo + s;
     if constexpr (SEQ) sr = a.seq_in[slot(min(ts + 1, (int64_t)ch.t_lo + ch.w - 1))];    // of the next step
     int64_t so = -1;                          // state row that leaves after this step
     if constexpr (SEQ) so = a.seq_out[slot(ts)];
     else if (s + 1 == ch.w) so = s0;
+    auto scaled = [&](floatx16 v) {
+#pragma unroll
+      for (int i = 0; i < 16; ++i) v[i] *= up;
+      return v;
+    };
+    // The barrier before a product; out: this wave's share of the operand is out of range.
+    auto meet = [&](bool out) -> bool {
+      ++number;
+      if constexpr (P == 2) {
+        if (__any(out)) said[number & 1] = number;
+      }
+      __syncthreads();
+      return P == 3 || __builtin_expect(__builtin_amdgcn_readfirstlane(said[number & 1]) != number, 1);
+    };
+    auto gates = [&](auto links, auto&& to, auto&& small, const Weights& ws, int u, int gstride, int n) {
+      product<NG, kHeldOf<NG, SEQ && kLstm, P>, P, decltype(links)::value>(to, small, buf, ws.stream(parts), u * kUnit<P>, gstride * kUnit<P>, n, lane16, wg);
+    };
+    auto ahead = [&](const Weights& ws, int u, int gstride, int n) {
+      fetch_ahead<NG, kHeldOf<NG, SEQ && kLstm, P>>(wg, ws.stream(parts), u * kUnit<P>, gstride * kUnit<P>, n, lane16);
+    };
+    constexpr std::bool_constant<STACK && P == 3> stack_links;
     // hidden side first: the state is there while the input rows are on their way
     floatx16 acc[4];
-    turn();
-    put_block(h);
-    __syncthreads();                          // (first step: the biases are there, too)
-#pragma unroll
-    for (int g = 0; g < 4; ++g)
-      if (kLstm || g != 2) acc[g] = load_block(gbias + g * H + col0);
     auto hidden = [&](int g) -> floatx16& { return acc[!kLstm && g == 2 ? 3 : g]; };
     auto in = [&](int g) -> floatx16& { return acc[g]; };
-    product<NG, DG, STACK>(hidden, hidden, buf, wsh, offh, gsh, kbh, lane16, wg);
+    turn();
+    if (!meet(put_block(parts, h, kActScale))) return false;
+#pragma unroll
+    for (int g = 0; g < 4; ++g)
+      if (kLstm || g != 2) acc[g] = scaled(load_block(gbias + g * H + col0));
+    gates(stack_links, hidden, hidden, wsh, uh, gh, kbh);
+    auto other_half = [&]() -> bool {         // the other half of the time encoder's input first
+      ahead(wsi, ux, gx, kbh);
+      int64_t r2 = slot(ts);
+      if (a.x2_map) r2 = max(a.x2_map[r2], (int64_t)0);   // an empty slot reads row 0; its output is not used
+      turn();
+      if (!meet(put_block(parts, load_block(a.X2 + r2 * a.ldx2 + col0), kActScale))) return false;
+      gates(std::false_type(), in, in, wsi, ux, gx, kbh);
+      return true;
+    };
+    auto input_bias = [&]() {
+      if constexpr (!kLstm) acc[2] = scaled(load_block(gbias + 2 * H + col0));
+    };
     if constexpr (FOLD) {
-      if constexpr (!kLstm) acc[2] = load_block(gbias + 2 * H + col0);
-      if constexpr (CAT) {                    // the other half of the time encoder's input first
-        fetch_ahead<NG, DG>(wg, wsi, offx, gsx, kbh, lane16);
-        int64_t r2 = slot(ts);
-        if (a.x2_map) r2 = max(a.x2_map[r2], (int64_t)0);   // an empty slot reads row 0; its output is not used
-        turn();
-        put_block(load_block(a.X2 + r2 * a.ldx2 + col0));
-        __syncthreads();
-        product<NG, DG>(in, in, buf, wsi, offx, gsx, kbh, lane16, wg);
-      }
-      // The small part products apart, as in the transform that this stands for: a GRU's in sums of their own, an LSTM's (whose
-      // registers do not hold four more) for every k-block.
-      floatx16 sums[kLstm ? 1 : NG];
-      auto small = [&](int g) -> floatx16& { return sums[kLstm ? 0 : g]; };
-      if constexpr (!kLstm)
+      input_bias();
+      if constexpr (CAT)
+        if (!other_half()) return false;
+      // Three parts: the small part products apart, as in the transform that this stands for: a GRU's in sums of their own, an
+      // LSTM's (whose registers do not hold four more) for every k-block.
+      constexpr bool kApart = P == 3 && !kLstm;
+      floatx16 sums[kApart ? NG : 1];
+      auto small = [&](int g) -> floatx16& { return kApart ? sums[kApart ? g : 0] : acc[g]; };
+      if constexpr (kApart)
 #pragma unroll
         for (int g = 0; g < NG; ++g) sums[g] = (floatx16)(0.f);
-      const int offf = jb * nkb0 * kUnitBytes, gsf = njb * nkb0 * kUnitBytes;
       for (int k = 0; k < nchunk; ++k) {
         const int n = min(kbc, nkb0 - k * kbc);
         turn();
-        stage_x(s, k);
-        fetch_ahead<NG, DG>(wg, wsg, offf + k * kbc * kUnitBytes, gsf, n, lane16);
+        const bool out = stage_x(parts, s, k);
+        ahead(wsg, uf + k * kbc, gf, n);
         if (k + 1 < nchunk) request_x(s, k + 1);
-        __syncthreads();
-        product<NG, DG, kLstm>(in, small, buf, wsg, offf + k * kbc * kUnitBytes, gsf, n, lane16, wg);
+        if (!meet(out)) return false;
+        gates(std::bool_constant<P == 3 && kLstm>(), in, small, wsg, uf + k * kbc, gf, n);
       }
-      if constexpr (!kLstm)
+      if constexpr (kApart)
 #pragma unroll
         for (int g = 0; g < NG; ++g) acc[g] += sums[g];
     } else if constexpr (!STACK) {
-      floatx16 z, zs = (floatx16)(0.f);
+      floatx16 z = scaled(load_block(zbias + col0)), zs = (floatx16)(0.f);
       for (int k = 0; k < nchunk; ++k) {
         const int n = min(kbc, nkb0 - k * kbc);
         turn();
-        stage_x(s, k);
-        fetch_ahead<1, DZ>(wz, wsg, offz + k * kbc * kUnitBytes, 0, n, lane16);
+        uint4 wz[DZ][P];
+        const bool out = stage_x(parts, s, k);
+        fetch_ahead<1, DZ>(wz, wsg.stream(parts), (uz + k * kbc) * kUnit<P>, 0, n, lane16);
         if (k + 1 < nchunk) request_x(s, k + 1);
-        __syncthreads();
-        if (k == 0) z = load_block(zbias + col0);
-        product<1, DZ>([&](int) -> floatx16& { return z; }, [&](int) -> floatx16& { return zs; }, buf, wsg, offz + k * kbc * kUnitBytes, 0, n, lane16, wz);
+        if (!meet(out)) return false;
+        product<1, DZ, P>([&](int) -> floatx16& { return z; }, [&](int) -> floatx16& { return zs; }, buf, wsg.stream(parts),
+                          (uz + k * kbc) * kUnit<P>, 0, n, lane16, wz);
       }
       z += zs;
       if (a.act == DGC_ACT_RELU) relu(z);
-      if constexpr (CAT) {                    // the other half of the time encoder's input first
-        fetch_ahead<NG, DG>(wg, wsi, offx, gsx, kbh, lane16);
-        int64_t r2 = slot(ts);
-        if (a.x2_map) r2 = max(a.x2_map[r2], (int64_t)0);   // an empty slot reads row 0; its output is not used
-        turn();
-        put_block(load_block(a.X2 + r2 * a.ldx2 + col0));
-        __syncthreads();
-        product<NG, DG>(in, in, buf, wsi, offx, gsx, kbh, lane16, wg);
-      }
-      fetch_ahead<NG, DG>(wg, wsi, offx + (kbx - kbh) * kUnitBytes, gsx, kbh, lane16);
+      if constexpr (CAT)
+        if (!other_half()) return false;
+      ahead(wsi, ux + kbx - kbh, gx, kbh);
       turn();
-      put_block(z);
+      if (!meet(put_block(parts, z, kActScale * down))) return false;
+      input_bias();
+      gates(std::false_type(), in, in, wsi, ux + kbx - kbh, gx, kbh);
     } else {
-      fetch_ahead<NG, DG>(wg, wsi, offx, gsx, kbh, lane16);
+      ahead(wsi, ux, gx, kbh);
       turn();
-      stage_x(s, 0);
-    }
-    if constexpr (!FOLD) {
-      __syncthreads();
-      if constexpr (!kLstm) acc[2] = load_block(gbias + 2 * H + col0);
-      product<NG, DG, STACK>(in, in, buf, wsi, offx + (kbx - kbh) * kUnitBytes, gsx, kbh, lane16, wg);
+      if (!meet(stage_x(parts, s, 0))) return false;
+      input_bias();
+      gates(stack_links, in, in, wsi, ux, gx, kbh);
     }
     // requests of the next step go out before this step's stores: memory operations retire in order
     if (mapped) {
@@ -389,20 +477,20 @@ __device__ __forceinline__ void dense_split(const DenseArgs& a) {
       if (s + 1 < ch.w) yrow_next = (int)a.y_map[slot(ts + 1)];
     }
     if (s + 1 < ch.w) {
-      fetch_ahead<NG, DG>(wg, wsh, offh, gsh, kbh, lane16);
+      ahead(wsh, uh, gh, kbh);
       if constexpr (SEQ) request_state();
       request_x(s + 1, 0);
     }
 #pragma unroll
     for (int v = 0; v < 16; ++v) {
       if constexpr (kLstm) {                  // i, f, g, o
-        const float ig = sigmoid_fast(acc[0][v]), fg = sigmoid_fast(acc[1][v]);
-        const float gg = tanh_fast(acc[2][v]), og = sigmoid_fast(acc[3][v]);
+        const float ig = sigmoid_of(acc[0][v], down), fg = sigmoid_of(acc[1][v], down);
+        const float gg = tanh_of(acc[2][v], down), og = sigmoid_of(acc[3][v], down);
         c[v] = fg * c[v] + ig * gg;
-        h[v] = og * tanh_fast(c[v]);
+        h[v] = og * tanh_of(c[v], 1.f);
       } else {                                // r, z, input part of n, hidden part of n
-        const float r = sigmoid_fast(acc[0][v]), zg = sigmoid_fast(acc[1][v]);
-        const float n = tanh_fast(acc[2][v] + r * acc[3][v]);
+        const float r = sigmoid_of(acc[0][v], down), zg = sigmoid_of(acc[1][v], down);
+        const float n = tanh_of(acc[2][v] + r * acc[3][v], down);
         h[v] = (1.0f - zg) * n + zg * h[v];
       }
     }
@@ -415,7 +503,25 @@ __device__ __forceinline__ void dense_split(const DenseArgs& a) {
       }
     }
     if (s + 1 < ch.w) enter(ts + 1);
+    return true;
+  };
+  int s = 0;
+  if constexpr (HALVES) {
+    if (wsh.halves_good() && (STACK || wsg.halves_good()) && ((FOLD && !CAT) || wsi.halves_good()) &&
+        __builtin_amdgcn_readfirstlane(said[2]) == 0) {
+      const std::integral_constant<int, 2> parts;
+      uint4 wg[kHeldOf<NG, SEQ && kLstm, 2>][2];
+      fetch_ahead<NG, kHeldOf<NG, SEQ && kLstm, 2>>(wg, wsh.stream(parts), uh * kUnit<2>, gh * kUnit<2>, kbh, lane16);
+      request_x(0, 0);
+      while (s < ch.w && step(parts, wg, s)) ++s;
+      if (s == ch.w) return;
+    }
   }
+  const std::integral_constant<int, 3> parts;
+  uint4 wg[kHeldOf<NG, SEQ && kLstm, 3>][3];
+  fetch_ahead<NG, kHeldOf<NG, SEQ && kLstm, 3>>(wg, wsh.stream(parts), uh * kUnit<3>, gh * kUnit<3>, kbh, lane16);
+  request_x(s, 0);
+  for (; s < ch.w; ++s) step(parts, wg, s);
 }
 
 // Whether the weights can be folded is known on the device (k_fold), where a graph that was captured before other weights were
@@ -424,11 +530,11 @@ template <int KIND, bool SEQ, bool CAT, Input INPUT, int MAXW>
 __global__ __launch_bounds__(64 * MAXW, 2) void k_dense_split(DenseArgs a) {
   if constexpr (INPUT == kFolded) {
     if (table_entry(a.fold_bad, 0)) {
-      dense_split<KIND, SEQ, CAT, kTransform>(a);
+      dense_split<KIND, SEQ, CAT, kTransform, false>(a);
       return;
     }
   }
-  dense_split<KIND, SEQ, CAT, INPUT>(a);
+  dense_split<KIND, SEQ, CAT, INPUT, true>(a);
 }
 
 // Transforms alone, Y = act(M W^T + b): a workgroup takes a run of the row tiles (ordered by snapshot).  Its waves
@@ -518,8 +624,10 @@ __global__ __launch_bounds__(64 * MAXW, 2) void k_rows_split(DenseArgs a, int kb
 
 // W [n_out][n_in] (strides so, si) -> three bf16 parts per fragment: packed[((jb*nkb + kb)*3 + part)*64 + lane] holds of
 // row jb*32 + lane%32 the columns 16*kb + 8*p + 4*(lane/32) + e (p = 0, 1; e = 0..3), zero beyond n_in.
+// half (or nullptr): behind these, the same as two half-precision parts of 1024 w, and behind them a word that says whether
+// these stand for the weights (Weights::halves_good).
 __global__ void k_pack_split(const float* W, int64_t per_w, int64_t so, int64_t si, int32_t n_out, int32_t n_in, int64_t count,
-                             uint4* packed) {
+                             uint4* packed, uint4* half) {
   const int nkb = (n_in + 15) / 16;
   const int64_t per = (int64_t)(n_out / 32) * nkb * 64;
   const int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
@@ -538,6 +646,17 @@ __global__ void k_pack_split(const float* W, int64_t per_w, int64_t so, int64_t 
   uint4 part[3];
   split8(x, part);
   for (int p = 0; p < 3; ++p) packed[((m * per + (f << 6)) * 3 + p * 64) + lane] = part[p];
+  if (!half) return;
+  uint4 two[2];
+  halve8(x, kWeightScale, two);
+  for (int p = 0; p < 2; ++p) half[(f << 6) * 2 + p * 64 + lane] = two[p];
+  int32_t word = 0;
+  for (int k = 0; k < 8; ++k) {
+    if (!(fabsf(x[k]) <= kHalfWeight)) word |= kHalfLarge;
+    if (fabsf(x[k]) >= kHalfLeast) word |= kHalfFull;
+    if (x[k] != 0.f) word |= kHalfAny;
+  }
+  if (word) atomicOr(reinterpret_cast<int32_t*>(half + 2 * per), word);
 }
 
 // out[r][k] = sum over s of wih[r][s] wg[s][k], bias[r] = bih[r] + sum over s of wih[r][s] bg[s], both summed in double.
@@ -576,7 +695,7 @@ bool launch_time(DenseArgs a, int njb, hipStream_t st, std::string* why) {
   const int nkb0 = INPUT == kStack ? 2 * njb : (a.K0 + 15) / 16;
   // a staging buffer holds the state's k-blocks, and of a wider input row what 48 KB take
   a.kb_chunk = std::max(2 * njb, std::min(nkb0, 48 * 1024 / kUnitBytes));
-  const size_t lds = (size_t)2 * a.kb_chunk * kUnitBytes + sizeof(float) * 5 * 32 * njb;
+  const size_t lds = (size_t)2 * a.kb_chunk * kUnitBytes + sizeof(float) * 5 * 32 * njb + 4 * sizeof(int32_t);
   static std::atomic<uint64_t> ready{0};
   auto* kernel = &k_dense_split<KIND, SEQ, CAT, INPUT, MAXW>;
   if (!allow_lds(reinterpret_cast<const void*>(kernel), kMaxLds, ready, why)) return false;
@@ -680,11 +799,12 @@ void launch_fold(const float* wih, int64_t ld_wih, const float* wg, const float*
 }
 
 void launch_pack_split(const float* W, int64_t per_w, int64_t out_stride, int64_t in_stride, int32_t n_out, int32_t n_in,
-                       int64_t count, void* packed, hipStream_t st) {
+                       int64_t count, void* packed, bool halves, hipStream_t st) {
   const int64_t total = count * (n_out / 32) * ((n_in + 15) / 16) * 64;
+  uint4* const p = static_cast<uint4*>(packed);
   if (total > 0)
     hipLaunchKernelGGL(k_pack_split, (unsigned)((total + 255) / 256), 256, 0, st, W, per_w, out_stride, in_stride, n_out, n_in,
-                       count, static_cast<uint4*>(packed));
+                       count, p, halves ? p + 3 * total : nullptr);
 }
 
 }  // namespace dgc

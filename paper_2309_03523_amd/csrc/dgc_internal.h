@@ -237,13 +237,16 @@ bool launch_dense_split(const DenseArgs& a, hipStream_t st, std::string* why);
 inline int64_t split_weight_bytes(int32_t n_out, int32_t n_in) {
   return (int64_t)(n_out / 32) * ((n_in + 15) / 16) * 3 * 64 * 16;
 }
-// `count` matrices, per_w floats apart, element (out, in) at out * out_stride + in * in_stride
+// the same with the two half-precision parts that the time encoders read first, and the word behind them (k_pack_split)
+inline int64_t split_halves_bytes(int32_t n_out, int32_t n_in) { return split_weight_bytes(n_out, n_in) / 3 * 5 + 64; }
 bool dense_fold_wanted(int32_t S, int32_t K0, int32_t time_kind);   // whether folding saves products
 // out [gH][K0], bias [gH]; *bad is set where a value is not finite
 void launch_fold(const float* wih, int64_t ld_wih, const float* wg, const float* bg, const float* bih, int32_t gH, int32_t S, int32_t K0,
                  float* out, float* bias, int32_t* bad, hipStream_t st);
+// `count` matrices, per_w floats apart, element (out, in) at out * out_stride + in * in_stride; halves (one matrix): with the
+// half-precision parts, the word behind them zero before
 void launch_pack_split(const float* W, int64_t per_w, int64_t out_stride, int64_t in_stride, int32_t n_out, int32_t n_in,
-                       int64_t count, void* packed, hipStream_t st);
+                       int64_t count, void* packed, bool halves, hipStream_t st);
 size_t dense_lds_bytes(int32_t K0, int32_t S, int32_t H);
 int dense_ld(int32_t K0, int32_t S, int32_t H);
 

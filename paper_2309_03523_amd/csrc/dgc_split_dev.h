@@ -10,6 +10,8 @@ namespace split {
 typedef float floatx16 __attribute__((ext_vector_type(16)));
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+typedef _Float16 halfx8 __attribute__((ext_vector_type(8)));
+typedef _Float16 halfx2 __attribute__((ext_vector_type(2)));
 typedef int intx4 __attribute__((ext_vector_type(4)));
 
 constexpr int kFrag = 64;   // uint4 of one fragment part (32 rows x 16 k, one bf16 part)
@@ -100,6 +102,37 @@ __device__ __forceinline__ void put(uint4* frag, const float (&x)[8]) {
   split8(x, p);
 #pragma unroll
   for (int q = 0; q < 3; ++q) frag[q * kFrag] = p[q];
+}
+
+// x scale = h + l, two half-precision numbers, each the nearest to what is left: 22 to 24 bits of x, or what is above the
+// smallest half-precision number.  Returns the largest magnitude: above kHalfMost / scale, h is infinite.
+constexpr float kHalfMost = 65504.f;
+template <int N>    // N numbers, two a word of h and l
+__device__ __forceinline__ float halve(const float (&x)[N], float scale, uint32_t (&h)[N / 2], uint32_t (&l)[N / 2]) {
+  float top = 0.f;
+#pragma unroll
+  for (int i = 0; i < N / 2; ++i) {
+    const float x0 = x[2 * i], x1 = x[2 * i + 1];
+    const halfx2 a = {(_Float16)(x0 * scale), (_Float16)(x1 * scale)};
+    const halfx2 b = {(_Float16)fmaf(x0, scale, -(float)a.x), (_Float16)fmaf(x1, scale, -(float)a.y)};
+    h[i] = __builtin_bit_cast(uint32_t, a);
+    l[i] = __builtin_bit_cast(uint32_t, b);
+    top = fmaxf(top, fmaxf(fabsf(x0), fabsf(x1)));
+  }
+  return top;
+}
+__device__ __forceinline__ float halve8(const float (&x)[8], float scale, uint4 (&p)[2]) {
+  uint32_t h[4], l[4];
+  const float top = halve(x, scale, h, l);
+  p[0] = make_uint4(h[0], h[1], h[2], h[3]);
+  p[1] = make_uint4(l[0], l[1], l[2], l[3]);
+  return top;
+}
+__device__ __forceinline__ halfx8 as_halves(uint4 u) { return __builtin_bit_cast(halfx8, u); }
+__device__ __forceinline__ void three(floatx16& c, floatx16& small, const uint4 (&w)[2], const uint4 (&x)[2]) {
+  small = __builtin_amdgcn_mfma_f32_32x32x16_f16(as_halves(w[0]), as_halves(x[1]), small, 0, 0, 0);
+  small = __builtin_amdgcn_mfma_f32_32x32x16_f16(as_halves(w[1]), as_halves(x[0]), small, 0, 0, 0);
+  c = __builtin_amdgcn_mfma_f32_32x32x16_f16(as_halves(w[0]), as_halves(x[0]), c, 0, 0, 0);
 }
 
 // A table that no kernel writes while it is read: the address space lets wave-uniform entries come through the
