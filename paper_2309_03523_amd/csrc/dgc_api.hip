@@ -89,6 +89,12 @@ struct dgc_layer {
   Labelled lab{};                                // generated chunks (dgc_layer_set_labels)
   // input-gradient pass of EvolveGCN-O, allocated by the first backward that asks for dX
   float* d_dM = nullptr;                         // [T*N][F] gradient of the aggregated rows
+  AggItem* d_agg_items = nullptr;            // of the edge-table kernels
+  int64_t n_agg_items = 0;
+  // Table of the neighbours of a row's own chunk, which are all that hand a gradient to it: where each row's begin, how many there are
+  int64_t* d_inside_ptr = nullptr; int64_t n_inside = 0;
+  int2* d_inside = nullptr;
+  int2* inside_room = nullptr; int64_t n_inside_room = 0;      // memory for it behind d_dM
   int64_t* d_rowidx = nullptr;                   // [total rows] packed row -> t*N + v
   float4* d_Wt_plain = nullptr;                  // every W_t as (out = F, in = S) fragments
   bool m_saved = false;                          // d_M holds the aggregated rows of the last forward
@@ -309,6 +315,71 @@ dgc_status_t add_param(dgc_layer* L, const std::string& name, int32_t n_out, int
     if (narrow && (rc = packed(narrow_weight_bytes(n_out, n_in) / (int64_t)sizeof(float), &p.narrow)) != DGC_OK) return rc;
   }
   L->params[name] = p;
+  return DGC_OK;
+}
+
+SpmmArgs spmm_args(dgc_layer* L, const float* fresh, int64_t ld_fresh, const float* stale, int64_t ld_stale,
+                   int32_t F, float* M, int64_t ldm) {
+  SpmmArgs a{};
+  a.g = L->graph_dev();
+  a.segs = L->d_segs;
+  a.work_short = L->d_work_short; a.n_short = L->n_short;
+  a.work_long = L->d_work_long; a.n_long = L->n_long;
+  a.dinv = L->d_dinv;
+  a.fresh = fresh; a.ld_fresh = ld_fresh;
+  a.stale = stale; a.ld_stale = ld_stale;
+  a.halo = nullptr; a.ld_halo = 0; a.col_local = nullptr;
+  a.col_signed = L->lab.built ? L->lab.col_signed : nullptr;
+  a.F = F;
+  a.long_nnz = L->long_nnz; a.part_nnz = L->part_nnz; a.longest_row = L->longest_row;
+  a.partial = L->d_partial;
+  a.M = M; a.ldm = ldm;
+  a.row_map = nullptr;
+  a.ld_out = 0;
+  a.items = L->d_agg_items; a.n_items = L->n_agg_items;
+  a.skip_stale = false;
+  a.etab = L->d_etab;
+  return a;
+}
+
+// aggregation of one GCN layer, with or without the staged gather
+// Where the entries of each row's neighbours of its own chunk begin, and how many there are in all (waits for the stream).
+hipError_t count_inside(dgc_layer* L, int64_t* tmp, int64_t* total, hipStream_t st) {
+  hipError_t e = hipMemsetAsync(L->d_inside_ptr + L->total_rows, 0, sizeof(int64_t), st);
+  if (e != hipSuccess) return e;
+  launch_inside(spmm_args(L, nullptr, 0, nullptr, 0, L->desc.F, nullptr, 0), L->d_inside_ptr, nullptr, st);
+  launch_exclusive_scan(L->d_inside_ptr, L->total_rows + 1, tmp, total, st);
+  if ((e = hipMemcpyAsync(&L->n_inside, total, sizeof(int64_t), hipMemcpyDeviceToHost, st)) != hipSuccess) return e;
+  return hipStreamSynchronize(st);
+}
+
+// Row groups of the edge-table kernels, in the order of their snapshots.
+dgc_status_t build_agg_items(dgc_layer* L, hipStream_t st) {
+  Failer fail{L};
+  const std::vector<Segment>& segs = L->segs_host;
+  const int64_t ns = L->desc.F <= 32 ? 1 : (L->desc.F + 63) / 64;
+  int32_t rows = kAggRows;
+  if (L->desc.rows_per_group) rows = std::min(L->desc.rows_per_group, kAggRows);
+  else
+    // few rows: fewer a wave, so that more waves share them, down to one a lane group (14 x 1255 of 64 floats: 16, 8, 4 rows a wave take
+    // 39, 30, 22 us; 8 x 3000: 35, 28, 28; 16 x 3000: 34, 37, 38)
+    while (rows > 4 && L->total_rows * ns / rows < 2560) rows /= 2;
+  std::vector<int64_t> order(segs.size());
+  for (size_t s = 0; s < segs.size(); ++s) order[s] = (int64_t)s;
+  std::stable_sort(order.begin(), order.end(), [&](int64_t a, int64_t b) { return segs[a].t < segs[b].t; });
+  std::vector<AggItem> items;
+  for (int64_t s : order) {
+    const Segment& sg = segs[s];
+    const int64_t nv = sg.v_hi - sg.v_lo;
+    for (int64_t r = 0; r < nv; r += rows) {
+      const int32_t n = (int32_t)std::min<int64_t>(rows, nv - r);
+      items.push_back(AggItem{sg.row_off + r, sg.nnz_off - sg.e0, (int32_t)(sg.v_lo + r), sg.t, n, 0});
+    }
+  }
+  L->n_agg_items = (int64_t)items.size();
+  DGC_HIP_TRY(dev_alloc(L, &L->d_agg_items, L->n_agg_items));
+  DGC_HIP_TRY(hipMemcpyAsync(L->d_agg_items, items.data(), sizeof(AggItem) * items.size(), hipMemcpyHostToDevice, st));
+  DGC_HIP_TRY(hipStreamSynchronize(st));
   return DGC_OK;
 }
 
@@ -606,7 +677,7 @@ dgc_status_t build_layer(dgc_layer* L, const dgc_graph_t* graph, hipStream_t st)
   int64_t *d_rank = nullptr, *d_tmp = nullptr, *d_total = nullptr;
   DGC_HIP_TRY(dev_alloc(L, &d_bitmap, n_words));
   DGC_HIP_TRY(dev_alloc(L, &d_rank, n_words));
-  DGC_HIP_TRY(dev_alloc(L, &d_tmp, std::max(scan_tmp_elems(n_words), scan_tmp_elems(L->total_rows))));
+  DGC_HIP_TRY(dev_alloc(L, &d_tmp, std::max(scan_tmp_elems(n_words), scan_tmp_elems(L->total_rows + 1))));
   DGC_HIP_TRY(dev_alloc(L, &d_total, 1));
   DGC_HIP_TRY(hipMemsetAsync(d_bitmap, 0, sizeof(uint32_t) * std::max<int64_t>(n_words, 1), st));
   launch_mark_halo(g, L->d_segs, L->nseg, L->total_nnz, wps, d_bitmap, d_flags, st);
@@ -646,6 +717,10 @@ dgc_status_t build_layer(dgc_layer* L, const dgc_graph_t* graph, hipStream_t st)
     DGC_HIP_TRY(hipMemcpyAsync(L->d_work_short, ws.data(), sizeof(int32_t) * ws.size(), hipMemcpyHostToDevice, st));
     DGC_HIP_TRY(hipStreamSynchronize(st));  // ws goes out of scope
   }
+  if (d.struct_kind != DGC_STRUCT_GAT && d.gather_mode == DGC_GATHER_IN_PLACE && d.agg_kernel != DGC_AGG_WALK) {
+    const dgc_status_t e = build_agg_items(L, st);
+    if (e != DGC_OK) return e;
+  }
   int64_t* d_cnt = nullptr;
   DGC_HIP_TRY(dev_alloc(L, &d_cnt, L->total_rows));
   launch_long_count(g, L->d_segs, L->nseg, L->total_rows, L->long_nnz, L->part_nnz, d_cnt, st);
@@ -662,6 +737,11 @@ dgc_status_t build_layer(dgc_layer* L, const dgc_graph_t* graph, hipStream_t st)
       return fail(DGC_ERR_OOM, "no device memory for the aggregation's edge table (8 bytes per stored non-zero); "
                                "agg_kernel = DGC_AGG_WALK runs without it");
     launch_edge_table(g, L->d_segs, L->nseg, L->total_nnz, L->d_dinv, nullptr, L->d_etab, st);
+  }
+
+  if (L->d_etab && d.struct_kind == DGC_STRUCT_EVOLVE_GCN_O) {
+    DGC_HIP_TRY(dev_alloc(L, &L->d_inside_ptr, L->total_rows + 1));
+    DGC_HIP_TRY(count_inside(L, d_tmp, d_total, st));
   }
 
   // dense tiles: 64 consecutive vertices of a chunk
@@ -770,30 +850,6 @@ dgc_status_t check_tensor(const Failer& fail, const char* name, const void* p, i
   return DGC_OK;
 }
 
-SpmmArgs spmm_args(dgc_layer* L, const float* fresh, int64_t ld_fresh, const float* stale, int64_t ld_stale,
-                   int32_t F, float* M, int64_t ldm) {
-  SpmmArgs a{};
-  a.g = L->graph_dev();
-  a.segs = L->d_segs;
-  a.work_short = L->d_work_short; a.n_short = L->n_short;
-  a.work_long = L->d_work_long; a.n_long = L->n_long;
-  a.dinv = L->d_dinv;
-  a.fresh = fresh; a.ld_fresh = ld_fresh;
-  a.stale = stale; a.ld_stale = ld_stale;
-  a.halo = nullptr; a.ld_halo = 0; a.col_local = nullptr;
-  a.col_signed = L->lab.built ? L->lab.col_signed : nullptr;
-  a.F = F;
-  a.long_nnz = L->long_nnz; a.part_nnz = L->part_nnz; a.longest_row = L->longest_row;
-  a.partial = L->d_partial;
-  a.M = M; a.ldm = ldm;
-  a.row_map = nullptr;
-  a.ld_out = 0;
-  a.skip_stale = false;
-  a.etab = L->d_etab;
-  return a;
-}
-
-// aggregation of one GCN layer, with or without the staged gather
 void run_aggregate(dgc_layer* L, const float* fresh, int64_t ld_fresh, const float* stale, int64_t ld_stale,
                    int32_t F, float* M, int64_t ldm, hipStream_t st, const int64_t* row_map = nullptr) {
   SpmmArgs a = spmm_args(L, fresh, ld_fresh, stale, ld_stale, F, M, ldm);
@@ -975,7 +1031,7 @@ dgc_status_t dgc_layer_destroy(dgc_layer_t* L) {
 static hipError_t pack_split(const float* W, int32_t n_out, int32_t n_in, float4* packed) {
   char* const word = reinterpret_cast<char*>(packed) + split_halves_bytes(n_out, n_in) - 64;
   const hipError_t e = hipMemset(word, 0, sizeof(int32_t));
-  if (e == hipSuccess) launch_pack_split(W, 0, n_in, 1, n_out, n_in, 1, packed, true, nullptr);
+  if (e == hipSuccess) launch_pack_split(W, 0, n_in, 1, n_out, n_in, 1, packed, nullptr);
   return e;
 }
 
@@ -1307,9 +1363,19 @@ static dgc_status_t prepare_dx(dgc_layer* L, hipStream_t st) {
     return fail(DGC_ERR_UNSUPPORTED, "input gradient: more than 65535 chunks or snapshots per window");
   if (!L->d_dM) {
     const int64_t wt = (int64_t)L->T * evolve_packed_bytes(L->evo, L->evo.split) / (int64_t)sizeof(float4);
-    DGC_HIP_TRY(dev_alloc_all(L, Wanted<float>{&L->d_dM, (int64_t)L->T * L->N * d.F}, Wanted<int64_t>{&L->d_rowidx, L->total_rows},
+    // (the table of neighbours behind dM: an allocation takes longer than filling it)
+    const int64_t dm = ((int64_t)L->T * L->N * d.F + 1) / 2 * 2, table = L->d_etab ? L->n_inside + kEtabPad : 0;
+    DGC_HIP_TRY(dev_alloc_all(L, Wanted<float>{&L->d_dM, dm + 2 * table}, Wanted<int64_t>{&L->d_rowidx, L->total_rows},
                               Wanted<float4>{&L->d_Wt_plain, wt}));
+    L->inside_room = reinterpret_cast<int2*>(L->d_dM + dm);
+    L->n_inside_room = table;
     evolve_row_index(L->d_chunks, L->n_chunks, max_nv, max_w, L->N, L->d_rowidx, st);
+  }
+  if (L->d_etab && !L->d_inside) {
+    int2* inside = L->inside_room;
+    if (L->n_inside + kEtabPad > L->n_inside_room) DGC_HIP_TRY(dev_alloc(L, &inside, L->n_inside + kEtabPad));
+    launch_inside(spmm_args(L, L->d_dM, d.F, L->d_dM, d.F, d.F, L->d_dM, d.F), L->d_inside_ptr, inside, st);
+    L->d_inside = inside;
   }
   return DGC_OK;
 }
@@ -1401,6 +1467,9 @@ dgc_status_t dgc_layer_backward(dgc_layer_t* L, const void* Yv, int64_t ldy, con
     sa.ld_out = lddx;
     sa.row_map = L->d_rowidx;
     sa.skip_stale = true;
+    if (L->d_inside) {
+      sa.etab = L->d_inside; sa.eptr = L->d_inside_ptr;
+    }
     launch_spmm(sa, st);
   }
   DGC_HIP_TRY(hipGetLastError());
@@ -1555,6 +1624,18 @@ dgc_status_t dgc_layer_set_labels(dgc_layer_t* L, const int32_t* labels, void* s
   labels_build(L->graph_dev(), L->d_segs, labels, lab.col_signed, lab.seq_in, lab.seq_out, st);
   if (L->d_etab)      // the aggregation's table follows the labels: marked columns instead of the range test
     launch_edge_table(L->graph_dev(), L->d_segs, L->nseg, L->total_nnz, L->d_dinv, lab.col_signed, L->d_etab, st);
+  if (L->d_inside_ptr) {
+    if (L->d_inside) {          // of other labels
+      DGC_HIP_TRY(hipDeviceSynchronize());
+      if (L->d_inside != L->inside_room) dev_free(L, L->d_inside);
+      L->d_inside = nullptr;
+    }
+    int64_t* tmp = nullptr;
+    DGC_HIP_TRY(dev_alloc(L, &tmp, scan_tmp_elems(L->total_rows + 1) + 1));
+    const hipError_t e = count_inside(L, tmp, tmp + scan_tmp_elems(L->total_rows + 1), st);
+    dev_free(L, tmp);
+    DGC_HIP_TRY(e);
+  }
   DGC_HIP_TRY(hipStreamSynchronize(st));
   DGC_HIP_TRY(hipGetLastError());
   lab.built = true;

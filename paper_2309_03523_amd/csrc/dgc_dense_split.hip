@@ -799,12 +799,12 @@ void launch_fold(const float* wih, int64_t ld_wih, const float* wg, const float*
 }
 
 void launch_pack_split(const float* W, int64_t per_w, int64_t out_stride, int64_t in_stride, int32_t n_out, int32_t n_in,
-                       int64_t count, void* packed, bool halves, hipStream_t st) {
+                       int64_t count, void* packed, hipStream_t st) {
   const int64_t total = count * (n_out / 32) * ((n_in + 15) / 16) * 64;
   uint4* const p = static_cast<uint4*>(packed);
   if (total > 0)
     hipLaunchKernelGGL(k_pack_split, (unsigned)((total + 255) / 256), 256, 0, st, W, per_w, out_stride, in_stride, n_out, n_in,
-                       count, p, halves ? p + 3 * total : nullptr);
+                       count, p, per_w == 0 ? p + 3 * total : nullptr);
 }
 
 }  // namespace dgc

@@ -651,7 +651,7 @@ void evolve_forward_weights(const EvolveWs& ws, hipStream_t st) {
   const int64_t nn = (int64_t)ws.F * ws.S;
   launch_walk<false>(ws, st);
   if (ws.split) {
-    launch_pack_split(ws.Wt_f32, nn, 1, ws.S, ws.S, ws.F, ws.T, ws.Wt_packed, false, st);
+    launch_pack_split(ws.Wt_f32, nn, 1, ws.S, ws.S, ws.F, ws.T, ws.Wt_packed, st);
     return;
   }
   const int64_t per = (int64_t)(ws.S / 32) * ((ws.F + 7) / 8) * 64;
@@ -666,7 +666,7 @@ void evolve_row_index(const ChunkInfo* chunks, int32_t n_chunks, int64_t max_nv,
 
 void evolve_pack_weights_plain(const EvolveWs& ws, float4* packed, hipStream_t st) {
   if (ws.split) {
-    launch_pack_split(ws.Wt_f32, (int64_t)ws.F * ws.S, ws.S, 1, ws.F, ws.S, ws.T, packed, false, st);
+    launch_pack_split(ws.Wt_f32, (int64_t)ws.F * ws.S, ws.S, 1, ws.F, ws.S, ws.T, packed, st);
     return;
   }
   const int64_t per = (int64_t)(ws.F / 32) * ((ws.S + 7) / 8) * 64;

@@ -119,6 +119,14 @@ constexpr int64_t kMostTeams = 1 << 23, kTeamsAtOnce = 2048;
 // entries, up to 8 * (groups per wave) - 1 entries past the end of the row it works on.
 constexpr int64_t kEtabPad = 32;
 
+constexpr int kAggRows = 16;        // rows of an item of the edge-table kernels, at most
+struct AggItem {
+  int64_t row;       // first packed row
+  int64_t base;      // packed non-zeros before the segment's, less its first stored one in the snapshot
+  int32_t v0, t, n;  // first vertex, snapshot, rows
+  int32_t pad;
+};
+
 struct SpmmArgs {
   GraphDev g;
   const Segment* segs;
@@ -145,7 +153,13 @@ struct SpmmArgs {
   // is read from the cache; .y = the bits of the neighbour's degree scaling d_j^-1/2.  nullptr: the
   // kernels walk colidx and look the scaling up.
   const int2* etab;
+  const AggItem* items; int64_t n_items;      // row groups in the order of their snapshots
+  // etab holds the neighbours of the row's own chunk alone: the first entry of every packed row, and of the one past the last
+  const int64_t* eptr;
 };
+// The entries of the neighbours of a row's own chunk.  inside == nullptr: their number for every row, to eptr; else the entries,
+// from eptr on.
+void launch_inside(const SpmmArgs& a, int64_t* eptr, int2* inside, hipStream_t st);
 void launch_spmm(const SpmmArgs& a, hipStream_t st);
 // etab[p] for every packed non-zero p (col_signed: the marked columns of generated chunks, or nullptr:
 // mark by the segment's vertex range); the kEtabPad spare entries are (0, 0).
@@ -243,10 +257,10 @@ bool dense_fold_wanted(int32_t S, int32_t K0, int32_t time_kind);   // whether f
 // out [gH][K0], bias [gH]; *bad is set where a value is not finite
 void launch_fold(const float* wih, int64_t ld_wih, const float* wg, const float* bg, const float* bih, int32_t gH, int32_t S, int32_t K0,
                  float* out, float* bias, int32_t* bad, hipStream_t st);
-// `count` matrices, per_w floats apart, element (out, in) at out * out_stride + in * in_stride; halves (one matrix): with the
-// half-precision parts, the word behind them zero before
+// `count` matrices, per_w floats apart, element (out, in) at out * out_stride + in * in_stride.  per_w = 0: one matrix, with the
+// half-precision parts (split_halves_bytes; the word behind them is zero before).
 void launch_pack_split(const float* W, int64_t per_w, int64_t out_stride, int64_t in_stride, int32_t n_out, int32_t n_in,
-                       int64_t count, void* packed, bool halves, hipStream_t st);
+                       int64_t count, void* packed, hipStream_t st);
 size_t dense_lds_bytes(int32_t K0, int32_t S, int32_t H);
 int dense_ld(int32_t K0, int32_t S, int32_t H);
 

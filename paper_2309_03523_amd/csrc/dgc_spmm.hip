@@ -348,329 +348,351 @@ __global__ __launch_bounds__(256) void k_spmm_long_reduce(SpmmArgs a) {
 // fresh and the cache tensor).  The first generation above spends some
 // thirty vector instructions per gathered row on broadcasting column ids, range tests and 64-bit
 // address arithmetic, and is bound by instruction issue, not by memory.  Here the per-non-zero
-// work is prepared once, at packing time, in an edge table (SpmmArgs::etab): a lane reads the
-// marked column and the neighbour's scaling with one 8-byte load at a constant offset from a
-// running pointer, forms the row address with one 64-bit multiply-add, and no value has to be
-// made wave-uniform.  LPR lanes (16, 32 or 64, four floats each) cover a row, so a wave's load
-// instruction fetches G = 64 / LPR neighbour rows, U = 8 such loads in flight per lane group.
-//   One long row:   the G groups split its non-zeros (batches of U * G), partial sums added across
-//                   the groups at the end of the row.
-//   Short rows:     group g takes row r + g of its own (no cross-group sum, no idle half).
-// Slots past the end of a row (and, in the input-gradient pass, neighbours outside the chunk range)
-// load the row's own vertex instead, with weight zero: its stored self-loop makes that a row the
-// sum reads anyway, so nothing the sum does not depend on can leak a NaN into it.  The table has
-// kEtabPad spare entries so that whole batches can always be read.
-constexpr int kU = 8;            // table entries (neighbour rows) in flight per lane group
-constexpr int kSmallRow = 16;    // rows up to this many non-zeros share a wave with their neighbours
-static_assert(kEtabPad >= 4 * kU && kSmallRow <= 2 * kU, "batches of the last rows must stay inside the table's spare entries");
+// work is prepared once, at packing time, in an edge table (SpmmArgs::etab): the marked column and the neighbour's scaling.
+//
+// What bounds them on large graphs is what passes the L2s: random rows of a table that does not fit them come at 7.2 to 8 TB/s
+// whatever a kernel does (100 000 x 32 rows of 128 floats: 64 % of 211 M lines of 128 bytes miss; with the stores 6.5 TB/s pass); on small
+// ones the latency of the few gathers that are under way.  Both want many rows at once, of few columns each:
+//   A wave takes one slice of 4 LPR columns of up to kAggRows rows, LPR lanes of 16 bytes a row, so G = 64 / LPR rows at a time; where
+// one ends, its lanes take the next of the list.  Entries come eight to a load, one a lane and a batch ahead, and go to the LPR lanes by
+// swizzles.  Past a row's end a batch loads zeros, so nothing but the row's neighbours gets into its sum.  Rows of more than kAggLong non-zeros, and parts of
+// split rows, are shared by the G groups.  A row's sum runs in two chains.
+//   One row for the whole width of a wave and, where it is narrower, two or four of at most 16 non-zeros at a time took 2853 us where 64
+// columns a wave take 2660 (100 000 x 32 rows of 128 floats), 7151 and 6740 (62 500 x 64 of 256), 694 and 613 (30 001 x 24 of 128), 1200
+// and 1129 (40 000 x 32 of 172), 458 and 372 (20 000 x 8 of 300), 65 and 51 (12 345 x 10 of 50), 10.7 and 9.5 (1000 x 8 of 32).  32 columns
+// a wave are 2 to 4 % slower from 128 floats on (of a pitch of 704 bytes, where a line of 128 then lies across two, 11 %), 128 columns 2 to 12 %.
+//   A slice of all rows after the other, so that an XCD's L2 holds more of it: 104 M lines pass the L2s instead of 134 M, but the
+// launches take 2974 and 9238 us, since a slice of a power-of-two pitch lies in a quarter or an eighth of an L2's channels.  Two batches
+// under way: 3.5 % slower.  Items of 8, 16, 24, 32 rows: 2770, 2660, 2657, 2670 and 372, 374, 399, 404 us.
+constexpr int kAggLong = 64;
 
-template <int UU, bool TAIL, bool SKIP>
-__device__ __forceinline__ void agg_batch(const int2* p, int n_valid, int self_j, const char* fresh_l, const char* stale_l,
-                                          uint32_t ld_bytes, float (&acc)[4]) {
-  typedef int intx2 __attribute__((ext_vector_type(2)));
-  intx2 ent[UU];       // streamed once
-#pragma unroll
-  for (int u = 0; u < UU; ++u) ent[u] = __builtin_nontemporal_load(reinterpret_cast<const intx2*>(p) + u);
-  float4 v[UU];
-  float w[UU];
-#pragma unroll
-  for (int u = 0; u < UU; ++u) {
-    const bool ok = (!TAIL || u < n_valid) && (!SKIP || ent[u].x >= 0);
-    const int c = ok ? ent[u].x : self_j;
-    const bool in = c >= 0;
-    const uint32_t j = (uint32_t)(in ? c : ~c);
-    const char* base = in ? fresh_l : stale_l;
-    v[u] = *reinterpret_cast<const float4*>(base + (uint64_t)j * ld_bytes);
-    w[u] = ok ? __int_as_float(ent[u].y) : 0.f;
-  }
-#pragma unroll
-  for (int u = 0; u < UU; ++u) {
-    acc[0] = fmaf(w[u], v[u].x, acc[0]);
-    acc[1] = fmaf(w[u], v[u].y, acc[1]);
-    acc[2] = fmaf(w[u], v[u].z, acc[2]);
-    acc[3] = fmaf(w[u], v[u].w, acc[3]);
-  }
-}
-
-// Sum over the table entries [pos, end) of this lane's group, `stride` entries from batch to batch.
-template <int LPR, bool SKIP>
-__device__ __forceinline__ void agg_range(const int2* tab, int pos, int end, int stride, int self_j, const char* fresh_l,
-                                          const char* stale_l, uint32_t ld_bytes, float (&acc)[4]) {
-  constexpr int G = 64 / LPR;
-  for (;;) {
-    const int rem = end - pos;                       // uniform within a lane group
-    int rem_max = __builtin_amdgcn_readlane(rem, 0);
-#pragma unroll
-    for (int g = 1; g < G; ++g) {
-      const int r = __builtin_amdgcn_readlane(rem, g * LPR);
-      rem_max = r > rem_max ? r : rem_max;
-    }
-    if (rem_max <= 0) break;
-    int rem_min = __builtin_amdgcn_readlane(rem, 0);
-#pragma unroll
-    for (int g = 1; g < G; ++g) {
-      const int r = __builtin_amdgcn_readlane(rem, g * LPR);
-      rem_min = r < rem_min ? r : rem_min;
-    }
-    const int2* p = tab + pos;
-    if (rem_min >= kU) agg_batch<kU, false, SKIP>(p, kU, self_j, fresh_l, stale_l, ld_bytes, acc);
-    else if (rem_max > 4) agg_batch<8, true, SKIP>(p, rem, self_j, fresh_l, stale_l, ld_bytes, acc);
-    else if (rem_max > 2) agg_batch<4, true, SKIP>(p, rem, self_j, fresh_l, stale_l, ld_bytes, acc);
-    else if (rem_max > 1) agg_batch<2, true, SKIP>(p, rem, self_j, fresh_l, stale_l, ld_bytes, acc);
-    else agg_batch<1, true, SKIP>(p, rem, self_j, fresh_l, stale_l, ld_bytes, acc);
-    pos += stride;
-  }
-}
-
-// A launch's columns [c0, c1) of the output rows: all of them, or for rows of more than 256 floats one of two
-// stretches (c1 of the last stretch is the pitch).
-struct AggCols {
-  int32_t c0, c1;
+struct AggRow {
+  int64_t orow;      // row of M
+  int start, end;    // entries, from the item's first
+  float scale;
 };
 
-// Write this launch's columns of one output row: columns < F scaled, the others (up to the pitch) zero.  Lane l of
-// the writing group owns columns c0 + 4l .. +3 and, if there are more than the group spans, the same columns of
-// every further stretch of 4 * LPR.
+__device__ const float4 agg_zero = {0.f, 0.f, 0.f, 0.f};
+
+template <int LPR, int U>
+__device__ __forceinline__ int of_lane(int v) {      // lane U of each LPR
+  return __builtin_amdgcn_ds_swizzle(v, (U << 5) | (0x20 - LPR));
+}
+
 template <int LPR>
-__device__ __forceinline__ void agg_store(float* out, int l, AggCols cols, int F, const float (&acc)[4], float scale) {
-  const int fi = cols.c0 + 4 * l;
-  if (fi < cols.c1) {
+struct AggGather {
+  const char *fresh, *stale;      // this lane's 16 bytes of row 0
+  uint32_t ld_bytes;
+  template <int U>
+  __device__ __forceinline__ void one(int2 e, int n, float4& v, float& w) const {
+    const int col = of_lane<LPR, U>(e.x), b = of_lane<LPR, U>(e.y);
+    const char* const base = col >= 0 ? fresh : stale;
+    const char* const at = base + (uint64_t)(uint32_t)(col ^ (col >> 31)) * ld_bytes;
+    v = *reinterpret_cast<const float4*>(U < n ? at : reinterpret_cast<const char*>(&agg_zero));
+    w = __int_as_float(b);
+  }
+  // the n (of at most eight) non-zeros whose entries the lanes hold
+  __device__ __forceinline__ void batch(int2 e, int n, float4 (&v)[8], float (&w)[8]) const {
+    one<0>(e, n, v[0], w[0]); one<1>(e, n, v[1], w[1]); one<2>(e, n, v[2], w[2]); one<3>(e, n, v[3], w[3]);
+    one<4>(e, n, v[4], w[4]); one<5>(e, n, v[5], w[5]); one<6>(e, n, v[6], w[6]); one<7>(e, n, v[7], w[7]);
+  }
+};
+__device__ __forceinline__ void agg_add(const float4 (&v)[8], const float (&w)[8], float (&acc)[2][4]) {
+#pragma unroll
+  for (int u = 0; u < 8; ++u) {
+    acc[u & 1][0] = fmaf(w[u], v[u].x, acc[u & 1][0]);
+    acc[u & 1][1] = fmaf(w[u], v[u].y, acc[u & 1][1]);
+    acc[u & 1][2] = fmaf(w[u], v[u].z, acc[u & 1][2]);
+    acc[u & 1][3] = fmaf(w[u], v[u].w, acc[u & 1][3]);
+  }
+}
+// this lane's entry of the eight from pos on (past the row's end its last; kEtabPad spare ones end the table)
+__device__ __forceinline__ int2 agg_entry(const int2* tab, int start, int pos, int end) {
+  typedef int intx2 __attribute__((ext_vector_type(2)));
+  const int at = max(start, min(pos + (int)(threadIdx.x & 7), end - 1));
+  const intx2 e = __builtin_nontemporal_load(reinterpret_cast<const intx2*>(tab + at));    // streamed
+  return make_int2(e.x, e.y);
+}
+// this slice's columns of an output row, and zeros up to the pitch behind the last slice
+template <int LPR>
+__device__ __forceinline__ void agg_store(float* out, int fi, int c1, int F, const float (&acc)[4], float scale) {
+  if (fi < c1) {
     float o[4];
 #pragma unroll
-    for (int q = 0; q < 4; ++q) o[q] = (fi + q < F) ? acc[q] * scale : 0.f;
+    for (int q = 0; q < 4; ++q) o[q] = fi + q < F ? acc[q] * scale : 0.f;
     vstore<4>(out + fi, o);
   }
   const float z[4] = {0.f, 0.f, 0.f, 0.f};
-  for (int c = fi + 4 * LPR; c < cols.c1; c += 4 * LPR) vstore<4>(out + c, z);
+  for (int c = fi + 4 * LPR; c < c1; c += 4 * LPR) vstore<4>(out + c, z);
 }
 
+// The sum over [from, end), a share for every lane group; every group ends with all of it.
 template <int LPR>
-__device__ __forceinline__ void agg_reduce_groups(float (&acc)[4]) {
-  constexpr int G = 64 / LPR;
+__device__ __forceinline__ void agg_shared(const AggGather<LPR>& rows, const int2* tab, int from, int end, float (&sum)[4]) {
+  constexpr int kBatch = 8 * (64 / LPR);
+  const int g8 = from + 8 * ((threadIdx.x & 63) / LPR);
+  float acc[2][4] = {};
+  int2 e = agg_entry(tab, from, g8, end);
+  for (int i = 0; from + i < end; i += kBatch) {
+    float4 v[8];
+    float w[8];
+    const int n = end - (i + g8);
+    const int2 now = e;
+    e = agg_entry(tab, from, i + kBatch + g8, end);
+    rows.batch(now, n, v, w);
+    agg_add(v, w, acc);
+  }
+#pragma unroll
+  for (int q = 0; q < 4; ++q) sum[q] = acc[0][q] + acc[1][q];
 #pragma unroll
   for (int m = LPR; m < 64; m <<= 1)
 #pragma unroll
-    for (int q = 0; q < 4; ++q) acc[q] += __shfl_xor(acc[q], m);
-  (void)G;
+    for (int q = 0; q < 4; ++q) sum[q] += __shfl_xor(sum[q], m);
 }
 
-struct AggCtx {
-  const int2* tab;       // table entry of the work item's first non-zero
-  const char* fresh_l;   // snapshot's fresh rows + this lane's column offset
-  const char* stale_l;
-  uint32_t ld_bytes;
+// A wave's slice: columns fi .. +3 of this lane; stored up to column c1.
+template <int LPR>
+struct AggSlice {
+  int fi, c1, c0;
+  __device__ __forceinline__ AggSlice(const SpmmArgs& a, int slice) {
+    c0 = 4 * LPR * slice;
+    fi = c0 + 4 * ((threadIdx.x & 63) % LPR);
+    c1 = c0 + 4 * LPR < a.F ? c0 + 4 * LPR : (int)a.ldm;
+  }
+  __device__ __forceinline__ AggGather<LPR> of(const SpmmArgs& a, int t) const {
+    const int64_t col = (int64_t)t * a.g.N * a.ld_fresh + (fi < a.F ? fi : c0);     // lanes past the row's end re-read its first columns (never stored)
+    return AggGather<LPR>{reinterpret_cast<const char*>(a.fresh + col), reinterpret_cast<const char*>(a.stale + col), (uint32_t)(a.ld_fresh * sizeof(float))};
+  }
 };
 
-template <int LPR>
-__device__ __forceinline__ AggCtx agg_ctx(const SpmmArgs& a, const Segment& sg, int64_t first_e, int l, int c0) {
-  AggCtx c;
-  c.tab = a.etab + sg.nnz_off + (first_e - sg.e0);
-  const int fi = (c0 + 4 * l < a.F) ? c0 + 4 * l : c0;     // lanes past the row's end re-read its first columns (never stored)
-  const int64_t snap = (int64_t)sg.t * a.g.N * a.ld_fresh;
-  c.fresh_l = reinterpret_cast<const char*>(a.fresh + snap + fi);
-  c.stale_l = reinterpret_cast<const char*>(a.stale + snap + fi);
-  c.ld_bytes = (uint32_t)(a.ld_fresh * sizeof(float));
-  return c;
-}
-
-// TEAM: the four waves of a workgroup share the rows of more than kShared<LPR> non-zeros, a quarter each: they are left in
-// `queue` here and taken by k_agg_team.
+// A part of a split row, or a row that a workgroup's waves share.
 struct TeamRow {
-  int64_t e;        // table entry of the row's first non-zero
+  int64_t e;        // table entry of the first non-zero
   int64_t orow;     // row of M (a part: of the partial sums)
-  int nnz, self_j, t;
+  int nnz, t;
   float scale;
 };
 constexpr int kTeam = 4;
-template <int LPR> constexpr int kShared = 4 * kU * (64 / LPR);    // four batches of a wave
+template <int LPR> constexpr int kShared = 4 * 8 * (64 / LPR);    // four batches of a wave
 
-template <int LPR, bool SKIP, bool TEAM>
-__device__ __forceinline__ void agg_short(const SpmmArgs& a, AggCols cols, int64_t item, TeamRow* queue, int* n_queued) {
+// The part of a split row that `item` is; false if nobody wants the row (the merge skips it too).
+__device__ __forceinline__ bool agg_part(const SpmmArgs& a, int64_t item, TeamRow* to) {
+  const int32_t* w = a.work_long + 4 * item;
+  const Segment sg = a.segs[uniform(w[0])];
+  const int row = uniform(w[1]), p = uniform(w[2]), n_parts = uniform(w[3]);
+  if (a.row_map && a.row_map[sg.row_off + row] < 0) return false;
+  to->orow = item;
+  to->t = sg.t;
+  to->scale = 1.0f;
+  if (a.eptr) {          // equal shares of what the row has in this table
+    const int64_t ra = a.eptr[sg.row_off + row], n = a.eptr[sg.row_off + row + 1] - ra;
+    to->e = ra + n * p / n_parts;
+    to->nnz = (int)(ra + n * (p + 1) / n_parts - to->e);
+  } else {
+    const int64_t* rp = a.g.rowptr[sg.t] + sg.v_lo + row;
+    const int64_t ea = rp[0] + (int64_t)p * a.part_nnz, eb = rp[1];
+    to->e = sg.nnz_off + (ea - sg.e0);
+    to->nnz = (int)(min(ea + a.part_nnz, eb) - ea);
+  }
+  return true;
+}
+
+// The rows of an item.  TEAM: those of more than kShared<LPR> non-zeros are left in `queue`.
+template <int LPR, bool TEAM>
+__device__ __forceinline__ void agg_rows(const SpmmArgs& a, const AggSlice<LPR>& slice, int64_t item, AggRow* list, TeamRow* queue, int* queued) {
   constexpr int G = 64 / LPR;
-  const int lane = threadIdx.x & (kWave - 1);
-  if (item >= a.n_short) {
-    if (TEAM && lane == 0) *n_queued = 0;
+  const int lane = threadIdx.x & (kWave - 1), g = lane / LPR, l = lane % LPR;
+  if (item >= a.n_items) {
+    if (TEAM && lane == 0) *queued = 0;
     return;
   }
-  const int seg = uniform(a.work_short[3 * item + 0]);
-  const int r0 = uniform(a.work_short[3 * item + 1]);
-  const int n = uniform(a.work_short[3 * item + 2]);
-  const Segment sg = a.segs[seg];
-  const int g = lane / LPR, l = lane % LPR;
-  const int64_t* rp = a.g.rowptr[sg.t] + sg.v_lo + r0;
-  const int64_t rp0 = rp[0];
-  const int my_rel = lane <= n ? (int)(rp[lane] - rp0) : 0;     // lanes 0..n: row offsets relative to the group's start
-  const AggCtx c = agg_ctx<LPR>(a, sg, rp0, l, cols.c0);
-  const float* dinv_rows = a.dinv + (int64_t)sg.t * a.g.N + sg.v_lo + r0;
-  const int64_t prow0 = sg.row_off + r0;
+  const AggItem it = a.items[item];
+  const int n = uniform(it.n), t = uniform(it.t), v0 = uniform(it.v0);
+  const int64_t* rp = a.g.rowptr[t] + v0;
+  const int64_t stored = lane <= n ? rp[lane] : 0;
+  const int64_t ptr = lane <= n ? (a.eptr ? a.eptr[it.row + lane] : stored + it.base) : 0;
+  const int64_t first = readlane64(ptr, 0);
+  const int after = lane + 1 < kWave ? lane + 1 : lane;
+  const int start = (int)(ptr - first), end = __shfl(start, after);
+  const int64_t full = __shfl((long long)stored, after) - stored;
+  const int2* const tab = a.etab + first;
+  const AggGather<LPR> from = slice.of(a, t);
   const int64_t ldo = a.ld_out ? a.ld_out : a.ldm;
-  // rows whose output nobody wants (row_map < 0: absent under temporal fusion) are not computed
-  uint64_t todo = __ballot(lane < n && (!a.row_map || a.row_map[prow0 + lane] >= 0));
+  int64_t orow = -1;
+  float scale = 0.f;
+  if (lane < n) {
+    orow = a.row_map ? a.row_map[it.row + lane] : it.row + lane;
+    scale = a.dinv[(int64_t)t * a.g.N + v0 + lane];
+  }
+  // (rows whose output nobody wants, row_map < 0, and those that the parts make, are not taken)
+  const bool wanted = lane < n && orow >= 0 && full <= a.long_nnz;
+  const uint64_t below = (1ull << lane) - 1;
+  const uint64_t teams = TEAM ? __ballot(wanted && end - start > kShared<LPR>) : 0;
+  uint64_t shared = __ballot(wanted && end - start > kAggLong) & ~teams;
+  const uint64_t own = __ballot(wanted) & ~shared & ~teams;
+  if (own >> lane & 1) list[__popcll(own & below)] = AggRow{orow, start, end, scale};
   if constexpr (TEAM) {
-    const int nnz = __shfl(my_rel, lane + 1) - my_rel;           // of row `lane`, where todo has its bit
-    const bool wanted = todo >> lane & 1;
-    const uint64_t shared = __ballot(wanted && nnz > kShared<LPR> && nnz <= a.long_nnz);
-    if (shared >> lane & 1) {
-      const int64_t orow = a.row_map ? a.row_map[prow0 + lane] : prow0 + lane;
-      queue[__popcll(shared & ((1ull << lane) - 1))] =
-          TeamRow{sg.nnz_off + (rp0 - sg.e0) + my_rel, orow, nnz, (int)(sg.v_lo + r0 + lane), sg.t, dinv_rows[lane]};
-    }
-    if (lane == 0) *n_queued = __popcll(shared);
-    todo &= ~shared;
+    if (teams >> lane & 1) queue[__popcll(teams & below)] = TeamRow{ptr, orow, end - start, t, scale};
+    if (lane == 0) *queued = __popcll(teams);
   }
-  while (todo) {
-    const int r = __builtin_ctzll(todo);
-    const int e_r = __builtin_amdgcn_readlane(my_rel, r), e_r1 = __builtin_amdgcn_readlane(my_rel, r + 1);
-    const int nnz_r = e_r1 - e_r;
-    if (nnz_r > a.long_nnz) { todo &= todo - 1; continue; }
-    float acc[4] = {0.f, 0.f, 0.f, 0.f};
-    if (G == 1 || nnz_r > kSmallRow) {
-      // one row for the whole wave
-      agg_range<LPR, SKIP>(c.tab, e_r + g * kU, e_r1, kU * G, (int)(sg.v_lo + r0 + r), c.fresh_l, c.stale_l, c.ld_bytes, acc);
-      agg_reduce_groups<LPR>(acc);
-      const int64_t orow = a.row_map ? a.row_map[prow0 + r] : prow0 + r;
-      if (g == 0) agg_store<LPR>(a.M + orow * ldo, l, cols, a.F, acc, dinv_rows[r]);
-      todo &= todo - 1;
-    } else {
-      // up to G of the next wanted small rows, one per lane group
-      int take = 0, mine = r;
-      uint64_t m = todo;
-      while (take < G && m) {
-        const int r2 = __builtin_ctzll(m);
-        const int nn = __builtin_amdgcn_readlane(my_rel, r2 + 1) - __builtin_amdgcn_readlane(my_rel, r2);
-        if (nn > kSmallRow) break;
-        if (g == take) mine = r2;
-        ++take;
-        m &= m - 1;
+  const int listed = __popcll(own);
+  __builtin_amdgcn_wave_barrier();
+  while (shared) {
+    const int r = __builtin_ctzll(shared);
+    shared &= shared - 1;
+    float sum[4];
+    agg_shared<LPR>(from, tab, __builtin_amdgcn_readlane(start, r), __builtin_amdgcn_readlane(end, r), sum);
+    if (g == 0)
+      agg_store<LPR>(a.M + readlane64(orow, r) * ldo, slice.fi, slice.c1, a.F, sum, __int_as_float(__builtin_amdgcn_readlane(__float_as_int(scale), r)));
+  }
+  if (!listed) return;
+  int row = min(g, listed - 1), next = G;
+  bool busy = g < listed;
+  int pos = list[row].start, from_e = pos, to_e = list[row].end;
+  int2 e = agg_entry(tab, from_e, pos, to_e);
+  float acc[2][4] = {};
+  for (;;) {
+    float4 v[8];
+    float w[8];
+    const int left = busy ? to_e - pos : 0;
+    from.batch(e, left, v, w);
+    // where the next batch is: further in the row, or in the next row that no group has
+    const bool done = busy && left <= 8;
+    const uint64_t ends = __ballot(done && l == 0);
+    const int mine = row;
+    pos += 8;
+    if (done) {
+      const int r = next + __popcll(ends & ((1ull << (lane & ~(LPR - 1))) - 1));
+      busy = r < listed;
+      row = min(r, listed - 1);
+      pos = from_e = list[row].start;
+      to_e = list[row].end;
+    }
+    next += __popcll(ends);
+    e = agg_entry(tab, from_e, pos, to_e);
+    agg_add(v, w, acc);
+    if (done) {
+      const AggRow out = list[mine];
+      float sum[4];
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        sum[q] = acc[0][q] + acc[1][q];
+        acc[0][q] = acc[1][q] = 0.f;
       }
-      todo = m;
-      const int b = __shfl(my_rel, mine), e = __shfl(my_rel, mine + 1);
-      agg_range<LPR, SKIP>(c.tab, b, g < take ? e : b, kU, (int)(sg.v_lo + r0 + mine), c.fresh_l, c.stale_l, c.ld_bytes, acc);
-      const int64_t orow = a.row_map ? a.row_map[prow0 + mine] : prow0 + mine;
-      if (g < take) agg_store<LPR>(a.M + orow * ldo, l, cols, a.F, acc, dinv_rows[mine]);
+      agg_store<LPR>(a.M + out.orow * ldo, slice.fi, slice.c1, a.F, sum, out.scale);
     }
+    if (!__ballot(busy)) break;
   }
 }
 
-// One wave per part of a split row: unscaled partial sums.
-template <int LPR, bool SKIP>
-__device__ __forceinline__ void agg_long(const SpmmArgs& a, AggCols cols, int64_t item) {
-  constexpr int G = 64 / LPR;
-  const int lane = threadIdx.x & (kWave - 1);
-  if (item >= a.n_long) return;
-  const int seg = uniform(a.work_long[4 * item + 0]);
-  const int row = uniform(a.work_long[4 * item + 1]);
-  const int part = uniform(a.work_long[4 * item + 2]);
-  const Segment sg = a.segs[seg];
-  const int g = lane / LPR, l = lane % LPR;
-  if (a.row_map && a.row_map[sg.row_off + row] < 0) return;     // nobody wants this row (the merge skips it too)
-  const int64_t* rp = a.g.rowptr[sg.t] + sg.v_lo + row;
-  const int64_t ra = rp[0], rb = rp[1];
-  const int64_t ea = ra + (int64_t)part * a.part_nnz;
-  const int len = (int)((ea + a.part_nnz < rb ? ea + a.part_nnz : rb) - ea);
-  const AggCtx c = agg_ctx<LPR>(a, sg, ea, l, cols.c0);
-  float acc[4] = {0.f, 0.f, 0.f, 0.f};
-  agg_range<LPR, SKIP>(c.tab, g * kU, len, kU * G, (int)(sg.v_lo + row), c.fresh_l, c.stale_l, c.ld_bytes, acc);
-  agg_reduce_groups<LPR>(acc);
-  if (g == 0) agg_store<LPR>(a.partial + item * a.ldm, l, cols, a.F, acc, 1.0f);
-}
-
-// One launch for both lists, the split rows first: a part of one is the longest work there is, and on a small graph
-// a launch of its own waits for one.  As two launches and as one: 12 345 vertices x 10 snapshots, F = 50, 94 and
-// 72 us; 40 000 x 32, F = 172, 1.27 and 1.22 ms; 100 000 x 32, F = 128, 3.01 and 2.96 ms.
-template <int LPR, bool SKIP>
-__global__ __launch_bounds__(256) void k_agg(SpmmArgs a, AggCols cols, int64_t long_blocks) {
-  const int64_t block = blockIdx.x, wave = threadIdx.x / kWave;
-  if (block < long_blocks) agg_long<LPR, SKIP>(a, cols, block * kTeam + wave);
-  else agg_short<LPR, SKIP, false>(a, cols, (block - long_blocks) * kTeam + wave, nullptr, nullptr);
+// One launch for parts and rows, the parts first: one of them is the longest work there is, and on a small graph
+// a launch of its own waits for one.  A wave a part, a wave an item; ns slices of each.
+template <int LPR>
+__global__ __launch_bounds__(256) void k_agg(SpmmArgs a, int ns, int64_t part_blocks) {
+  __shared__ AggRow list[kTeam][kAggRows];
+  const int wave = uniform(threadIdx.x / kWave);
+  const bool part = blockIdx.x < part_blocks;
+  const int64_t place = (blockIdx.x - (part ? 0 : part_blocks)) * kTeam + wave, item = place / ns;
+  const AggSlice<LPR> slice(a, (int)(place - item * ns));
+  if (!part) {
+    agg_rows<LPR, false>(a, slice, item, list[wave], nullptr, nullptr);
+  } else if (item < a.n_long) {
+    TeamRow p;
+    if (!agg_part(a, item, &p)) return;
+    float sum[4];
+    agg_shared<LPR>(slice.of(a, p.t), a.etab + p.e, 0, p.nnz, sum);
+    if ((threadIdx.x & (kWave - 1)) < LPR) agg_store<LPR>(a.partial + item * a.ldm, slice.fi, slice.c1, a.F, sum, 1.0f);
+  }
 }
 
 // The same where there are rows long enough to be shared: on a graph that does not fill the chip for long the longest row is
 // what the launch waits for (1024 non-zeros are 32 batches of gathers, each waited for), so the four waves of a workgroup share a
-// part, and the longer rows of their four groups once they have done the short ones.  A row's quarters are added in wave order.
-template <int LPR, bool SKIP>
-__global__ __launch_bounds__(256) void k_agg_team(SpmmArgs a, AggCols cols, int64_t long_blocks) {
-  constexpr int G = 64 / LPR;
-  __shared__ TeamRow queue[kTeam][32];       // a group has at most 32 rows
+// part, and the longer rows of their four items once they have done the shorter ones.  A row's quarters are added in wave order.
+template <int LPR>
+__global__ __launch_bounds__(256) void k_agg_team(SpmmArgs a, int ns, int64_t part_blocks) {
+  __shared__ AggRow list[kTeam][kAggRows];
+  __shared__ TeamRow queue[kTeam][kAggRows];
   __shared__ int queued[kTeam];
   __shared__ float4 sums[2][kTeam][LPR];
   const int lane = threadIdx.x & (kWave - 1), wave = uniform(threadIdx.x / kWave);
   const int g = lane / LPR, l = lane % LPR;
-  const bool part = blockIdx.x < long_blocks;
+  const bool part = blockIdx.x < part_blocks;
+  const int64_t block = blockIdx.x - (part ? 0 : part_blocks), four = block / ns;
+  const AggSlice<LPR> slice(a, (int)(block - four * ns));
   if (part) {
-    if (lane == 0) queued[wave] = 0;
-    if (wave == 0) {
-      const int64_t item = blockIdx.x;
-      const int32_t* w = a.work_long + 4 * item;
-      const Segment sg = a.segs[uniform(w[0])];
-      const int row = uniform(w[1]);
-      const int64_t* rp = a.g.rowptr[sg.t] + sg.v_lo + row;
-      const int64_t ea = rp[0] + (int64_t)uniform(w[2]) * a.part_nnz, eb = rp[1];
-      const bool wanted = !a.row_map || a.row_map[sg.row_off + row] >= 0;
-      if (lane == 0 && wanted) {
-        queue[0][0] = TeamRow{sg.nnz_off + (ea - sg.e0), item, (int)(min(ea + a.part_nnz, eb) - ea), (int)(sg.v_lo + row), sg.t, 1.0f};
-        queued[0] = 1;
-      }
+    TeamRow p;
+    const bool there = wave == 0 && agg_part(a, four, &p);
+    if (lane == 0) {
+      queued[wave] = there;
+      if (there) queue[0][0] = p;
     }
   } else {
-    agg_short<LPR, SKIP, true>(a, cols, ((int64_t)blockIdx.x - long_blocks) * kTeam + wave, queue[wave], queued + wave);
+    agg_rows<LPR, true>(a, slice, four * kTeam + wave, list[wave], queue[wave], queued + wave);
   }
   __syncthreads();
   float* const out = part ? a.partial : a.M;
   const int64_t ldo = part || !a.ld_out ? a.ldm : a.ld_out;
-  const int fi = (cols.c0 + 4 * l < a.F) ? cols.c0 + 4 * l : cols.c0;
-  const uint32_t ld_bytes = (uint32_t)(a.ld_fresh * sizeof(float));
   int turn = 0;
   for (int from = 0; from < kTeam; ++from)
     for (int i = 0; i < queued[from]; ++i, ++turn) {
       const TeamRow row = queue[from][i];
-      const int t = uniform(row.t), nnz = uniform(row.nnz);
-      const int64_t snap = (int64_t)t * a.g.N * a.ld_fresh;
-      const int quarter = (nnz + kTeam - 1) / kTeam, e0 = wave * quarter;
-      float acc[4] = {0.f, 0.f, 0.f, 0.f};
-      agg_range<LPR, SKIP>(a.etab + row.e, e0 + g * kU, min(e0 + quarter, nnz), kU * G, row.self_j, reinterpret_cast<const char*>(a.fresh + snap + fi),
-                           reinterpret_cast<const char*>(a.stale + snap + fi), ld_bytes, acc);
-      agg_reduce_groups<LPR>(acc);
-      if (g == 0) sums[turn & 1][wave][l] = make_float4(acc[0], acc[1], acc[2], acc[3]);
+      const int nnz = uniform(row.nnz), quarter = (nnz + kTeam - 1) / kTeam, e0 = min(wave * quarter, nnz);
+      float part_sum[4];
+      agg_shared<LPR>(slice.of(a, uniform(row.t)), a.etab + row.e, e0, min(e0 + quarter, nnz), part_sum);
+      if (g == 0) sums[turn & 1][wave][l] = make_float4(part_sum[0], part_sum[1], part_sum[2], part_sum[3]);
       __syncthreads();       // (the next row's sums go to the other buffer)
       if (wave == (turn & (kTeam - 1)) && g == 0) {
         const float4 s0 = sums[turn & 1][0][l], s1 = sums[turn & 1][1][l], s2 = sums[turn & 1][2][l], s3 = sums[turn & 1][3][l];
         const float sum[4] = {((s0.x + s1.x) + s2.x) + s3.x, ((s0.y + s1.y) + s2.y) + s3.y, ((s0.z + s1.z) + s2.z) + s3.z,
                               ((s0.w + s1.w) + s2.w) + s3.w};
-        agg_store<LPR>(out + row.orow * ldo, l, cols, a.F, sum, row.scale);
+        agg_store<LPR>(out + row.orow * ldo, slice.fi, slice.c1, a.F, sum, row.scale);
       }
     }
 }
 
-// Without a row to share the team's queue and barriers would only cost (8 x 1000 rows of at most 30 non-zeros, width 32:
-// 9.0 us without, 10.0 with); with one the team is the faster at every size tried, 5000 x 8 rows up to 100 000 x 32.
-// Parts shorter than a shared row are a workgroup's only while the chip holds all of them at once: many of them are work for
-// every wave (4 x 400 000 rows, 1.7 M parts of 16: 2.25 -> 5.02 ms at width 8, 5.41 -> 7.13 at 256; 4 x 20 000: 147 -> 257 us at 8).
+// The team is for launches that the chip holds a few times over at most (it holds some 6000 waves): there the longest row is what they
+// wait for (12 345 x 10 rows of 50 floats 59 -> 51 us, 3000 x 16 of 64 40 -> 33); where there is more to do, waves of one item's slices side by side
+// are the faster ones (62 500 x 64 rows of 256 6.74 ms, 7.33 with the team; 20 000 x 8 of 300 374 us and 404).  And parts shorter than a
+// shared row are a workgroup's only while the chip holds all of them at once.
 template <int LPR>
-void launch_agg(const SpmmArgs& a, AggCols cols, hipStream_t st) {
-  const bool team = a.longest_row > kShared<LPR> && a.n_long <= (a.part_nnz > kShared<LPR> ? kMostTeams : kTeamsAtOnce);
-  const int64_t gs = (a.n_short + kTeam - 1) / kTeam, gl = team ? a.n_long : (a.n_long + kTeam - 1) / kTeam;
-  if (gs + gl == 0) return;
-  auto* kernel = team ? (a.skip_stale ? &k_agg_team<LPR, true> : &k_agg_team<LPR, false>)
-                      : (a.skip_stale ? &k_agg<LPR, true> : &k_agg<LPR, false>);
-  hipLaunchKernelGGL(kernel, (unsigned)(gs + gl), 256, 0, st, a, cols, gl);
+void launch_agg(const SpmmArgs& a, hipStream_t st) {
+  const int64_t ns = (a.F + 4 * LPR - 1) / (4 * LPR), few = 14 * 1024;
+  const bool team = a.longest_row > kShared<LPR> && a.n_items * ns <= few && a.n_long * ns <= (a.part_nnz > kShared<LPR> ? few : kTeamsAtOnce);
+  const int64_t parts = team ? a.n_long * ns : (a.n_long * ns + kTeam - 1) / kTeam;
+  const int64_t rows = team ? (a.n_items + kTeam - 1) / kTeam * ns : (a.n_items * ns + kTeam - 1) / kTeam;
+  if (parts + rows > 0) hipLaunchKernelGGL(team ? k_agg_team<LPR> : k_agg<LPR>, (unsigned)(parts + rows), 256, 0, st, a, (int)ns, parts);
 }
 
-// Rows wider than the 256 floats that a wave's lanes span go in stretches: 2.4 M gathers of 300 floats (uniform over
-// 20 000 vertices, 8 snapshots) as 256 + 44 take 514 us where the column-walking kernels took 853.
 void launch_agg_all(const SpmmArgs& a, hipStream_t st) {
-  for (int32_t c0 = 0; c0 < a.F; c0 += 256) {
-    const int32_t n = std::min(a.F - c0, 256);
-    const AggCols cols{c0, c0 + n < a.F ? c0 + n : (int32_t)a.ldm};
-    if (n <= 64) launch_agg<16>(a, cols, st);
-    else if (n <= 128) launch_agg<32>(a, cols, st);
-    else launch_agg<64>(a, cols, st);
-  }
+  if (a.F <= 32) launch_agg<8>(a, st);
+  else launch_agg<16>(a, st);
   const unsigned gl = (unsigned)((a.n_long + 3) / 4);
   if (!gl) return;
   if (a.ldm <= 64) hipLaunchKernelGGL((k_spmm_long_reduce<1>), gl, 256, 0, st, a);
   else if (a.ldm <= 128) hipLaunchKernelGGL((k_spmm_long_reduce<2>), gl, 256, 0, st, a);
   else hipLaunchKernelGGL((k_spmm_long_reduce<4>), gl, 256, 0, st, a);
+}
+
+// The first entry of every row in a table of the neighbours of its own chunk alone, counted (FILL: their entries, in order).
+template <bool FILL>
+__global__ __launch_bounds__(256) void k_inside(SpmmArgs a, int64_t* eptr, int2* inside) {
+  const int lane = threadIdx.x & (kWave - 1);
+  const int64_t item = (int64_t)blockIdx.x * kTeam + uniform(threadIdx.x / kWave);
+  if (item >= a.n_items) return;
+  const AggItem it = a.items[item];
+  const int64_t* rp = a.g.rowptr[it.t] + it.v0;
+  for (int r = 0; r < it.n; ++r) {
+    const int64_t ea = rp[r] + it.base, eb = rp[r + 1] + it.base;
+    int64_t at = FILL ? eptr[it.row + r] : 0;
+    for (int64_t e = ea; e < eb; e += kWave) {
+      const int2 entry = e + lane < eb ? a.etab[e + lane] : make_int2(-1, 0);
+      const uint64_t in = __ballot(entry.x >= 0);
+      if constexpr (FILL)
+        if (entry.x >= 0) inside[at + __popcll(in & ((1ull << lane) - 1))] = entry;
+      at += __popcll(in);
+    }
+    if (!FILL && lane == 0) eptr[it.row + r] = at;
+  }
 }
 
 // etab[p] = (marked column, scaling of the neighbour) for packed non-zero p
@@ -740,13 +762,20 @@ void launch_edge_table(const GraphDev& g, const Segment* segs, int64_t nseg, int
 
 void launch_spmm(const SpmmArgs& a, hipStream_t st) {
   // the edge-table kernels: rows read in place, one pitch for both sources
-  if (a.etab && !a.halo && a.ld_fresh == a.ld_stale && a.ld_fresh * 4 < (int64_t(1) << 31)) {
+  if (a.etab && !a.halo && a.ld_fresh == a.ld_stale && a.ld_fresh * 4 < (int64_t(1) << 31) && (!a.skip_stale || a.eptr)) {
     launch_agg_all(a, st);
     return;
   }
   if (a.F <= 64) launch_spmm_v<1>(a, st);
   else if (a.F <= 128) launch_spmm_v<4, true>(a, st);
   else launch_spmm_v<4>(a, st);
+}
+
+void launch_inside(const SpmmArgs& a, int64_t* eptr, int2* inside, hipStream_t st) {
+  const unsigned blocks = (unsigned)((a.n_items + kTeam - 1) / kTeam);
+  if (!blocks) return;
+  if (inside) hipLaunchKernelGGL(k_inside<true>, blocks, 256, 0, st, a, eptr, inside);
+  else hipLaunchKernelGGL(k_inside<false>, blocks, 256, 0, st, a, eptr, inside);
 }
 
 void launch_gather(const Segment* segs, int64_t nseg, const int32_t* halo_idx, const int64_t* halo_ptr,

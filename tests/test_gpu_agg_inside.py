@@ -1,0 +1,152 @@
+"""The edge-table kernels of the aggregation against the column-walking ones, over the forms that both take, and the input
+gradient's table of the neighbours of a row's own chunk: split rows in it, rows with no other neighbour, other labels afterwards.
+Bound of an fp32 sum of n products in any order: n + 3 roundings of 2^-24 of the sum of the products' sizes; two such sums
+of normalised rows of N(0,1) are within 1e-6 of each other, root mean square, with rows of up to 2000 neighbours."""
+import numpy as np
+import pytest
+
+import oracle
+from oracle import labelled
+from refs import rel_err
+from workloads import synth
+
+pytestmark = pytest.mark.gpu
+
+
+def _graph(rng, N, hubs, degree):
+    deg = rng.integers(0, degree, N)
+    src = np.repeat(np.arange(N), deg)
+    dst = rng.integers(0, N, src.size)
+    for h in hubs:
+        n = int(rng.integers(N // 40, N // 8))
+        src, dst = np.append(src, np.full(n, h)), np.append(dst, rng.integers(0, N, n))
+    key = np.unique(np.concatenate([src * N + dst, dst * N + src, np.arange(N) * N + np.arange(N)]))
+    rowptr = np.zeros(N + 1, np.int64)
+    rowptr[1:] = np.cumsum(np.bincount(key // N, minlength=N))
+    return rowptr, (key % N).astype(np.int32)
+
+
+@pytest.mark.parametrize("N,T,F,pitch,rows,long_nnz,part_nnz", [
+    (900, 3, 1, 4, 0, 0, 0), (900, 3, 31, 32, 0, 0, 0), (901, 2, 32, 40, 3, 100, 32), (2500, 2, 33, 36, 0, 64, 17),
+    (2500, 2, 64, 64, 16, 200, 64), (2500, 2, 130, 144, 5, 0, 0), (20000, 3, 300, 304, 0, 0, 0), (20000, 3, 260, 260, 0, 500, 100),
+    (30000, 4, 128, 128, 0, 300, 512)])
+def test_table_and_walk(N, T, F, pitch, rows, long_nnz, part_nnz):
+    import torch
+    from paper_2309_03523_amd import binding
+    rng = synth.stream(N + F, "inside")
+    snaps = [_graph(rng, N, rng.integers(0, N, 3), 12) for _ in range(T)]
+    rowptr, col = ([torch.from_numpy(s[k]).cuda() for s in snaps] for k in (0, 1))
+    cut = N // 3
+    chunks = [(0, cut, 0, T), (cut, N, 0, T - 1)]
+    X, C = (torch.zeros((T, N, pitch), device="cuda")[:, :, :F].copy_(torch.randn((T, N, F), device="cuda")) for _ in range(2))
+    out = []
+    for kernel in ("walk", "table"):
+        layer = binding.DgcLayer(rowptr, col, N, chunks, F=F, S=32, H=32, time_kind="none", rows_per_group=rows, long_nnz=long_nnz,
+                                 part_nnz=part_nnz, agg_kernel=kernel)
+        M = torch.full((cut * T + (N - cut) * (T - 1), (F + 7) // 8 * 8), float("nan"), device="cuda")
+        layer.aggregate(X, C, M)
+        torch.cuda.synchronize()
+        out.append(M.double())
+        layer.destroy()
+    assert torch.isfinite(out[1]).all() and bool((out[1][:, F:] == 0).all())
+    off = float((out[1] - out[0]).norm() / out[0].norm())
+    most = float((out[1] - out[0]).abs().max() / out[0].pow(2).mean().sqrt())
+    print(f"N={N} F={F}: {off:.2e}, most {most:.2e}", flush=True)
+    assert off < 1e-6 and most < 1e-4
+
+
+def test_missing_numbers_stay_where_they_are():
+    """NaN in the rows of other chunks' fresh features and in cache rows of the own chunk, which no sum depends on."""
+    import torch
+    from paper_2309_03523_amd import binding
+    N, F = 1000, 70
+    rowptr, col = _graph(synth.stream(3, "nan"), N, [5], 6)
+    X, C = (torch.randn((1, N, 72), device="cuda")[:, :, :F] for _ in range(2))
+    layer = binding.DgcLayer([torch.from_numpy(rowptr).cuda()], [torch.from_numpy(col).cuda()], N, [(200, 600, 0, 1)], F=F, S=32, H=32,
+                             time_kind="none")
+    M = torch.zeros((400, 72), device="cuda")
+    layer.aggregate(X, C, M)
+    want = M.clone()
+    X[0, :200] = float("nan")
+    X[0, 600:] = float("inf")
+    C[0, 200:600] = float("nan")
+    layer.aggregate(X, C, M)
+    torch.cuda.synchronize()
+    assert torch.equal(M, want)
+    layer.destroy()
+
+
+@pytest.mark.parametrize("F,rows,long_nnz,part_nnz", [(32, 0, 0, 0), (64, 4, 20, 7), (128, 16, 40, 16), (256, 0, 60, 200)])
+def test_input_gradient_of_split_rows(F, rows, long_nnz, part_nnz):
+    """Where an output lies within rounding of zero its ReLU may open on one side only, and its row's gradient is another one: such
+    elements of Y (at most a few in 1e5) and the rows that they hand a gradient to are left out."""
+    import torch
+    from paper_2309_03523_amd.runner import DeviceWorkload
+    T, N = 3, 410
+    chunks = [[0, 1, 0, 3], [1, 180, 0, 3], [180, 410, 1, 3]]          # (the first row: no neighbour of its chunk but itself)
+    wl = synth.random_small(300 + F, T, N, F, F, F, 6.0, chunks, "none", hub=True)
+    wl.params = synth.evolve_params(300 + F, F, F, random_bias=True)
+    target = synth.stream(F, "target").standard_normal((T, N, F)).astype(np.float32)
+    dw = DeviceWorkload(wl, struct_kind="evolve_gcn_o", act_out="relu", rows_per_group=rows, long_nnz=long_nnz, part_nnz=part_nnz)
+    Y = dw.forward()
+    dX = torch.full((T, N, F), np.nan, device="cuda")
+    dw.layer.backward(Y, target=torch.from_numpy(target).cuda(), dX=dX)
+    torch.cuda.synchronize()
+    got = Y.cpu().numpy()
+    want = oracle.evolve(wl.graph, wl.chunks, wl.params, wl.X, wl.C, target, want_grads=True, want_dx=True)
+    m = ~np.isnan(want["dX"]).any(axis=2) & ~np.isnan(want["Y"]).any(axis=2)
+    assert m.sum() == 3 + 3 * 179 + 2 * 230
+    flipped = ((got > 0) != (want["Y"] > 0)) & m[..., None]
+    assert flipped.sum() <= 3 and np.abs(got[flipped]).max(initial=0) < 1e-6 and np.abs(want["Y"][flipped]).max(initial=0) < 1e-6
+    for t, i in zip(*np.nonzero(flipped.any(axis=2))):
+        s = wl.graph.snaps[t]
+        m[t, s.col[s.rowptr[i]:s.rowptr[i + 1]]] = False
+    print(f"F={F}: {int(flipped.sum())} gates on one side only, {int(m.sum())} rows compared", flush=True)
+    assert m.sum() > 600
+    assert rel_err(got[m], want["Y"][m]) < 1e-4 and rel_err(dX.cpu().numpy()[m], want["dX"][m]) < 1e-4
+    dw.layer.destroy()
+
+
+def test_input_gradient_after_other_labels():
+    """Two input gradients of one layer, other labels in between: the table follows them."""
+    import torch
+    from paper_2309_03523_amd.runner import DeviceWorkload
+    T, N, F = 3, 200, 64
+    wl = synth.random_small(12, T, N, F, F, F, 6.0, [[0, N, 0, T]], "none", hub=True)
+    wl.params = synth.evolve_params(12, F, F, random_bias=True)
+    target = synth.stream(F, "target").standard_normal((T, N, F)).astype(np.float32)
+    dw = DeviceWorkload(wl, struct_kind="evolve_gcn_o", act_out="relu")
+    rng = np.random.default_rng(4)
+    for classes in (2, 9, 1):
+        lab = rng.integers(0, classes, (T, N))
+        dw.layer.set_labels(torch.from_numpy(lab.astype(np.int32).reshape(-1)).cuda())
+        Y = dw.forward()
+        dX = torch.full((T, N, F), np.nan, device="cuda")
+        dw.layer.backward(Y, target=torch.from_numpy(target).cuda(), dX=dX)
+        torch.cuda.synchronize()
+        want = labelled.evolve(wl.graph, lab, wl.params, wl.X, wl.C, target, want_dx=True)
+        assert rel_err(Y.cpu().numpy(), want["Y"]) < 1e-4 and rel_err(dX.cpu().numpy(), want["dX"]) < 1e-4, classes
+    dw.layer.destroy()
+
+
+@pytest.mark.parametrize("F", [20, 64, 200])
+def test_infinities_stay_infinities(F):
+    """Sums with one infinite term are infinite, not NaN, whatever the length of their row and of those beside it."""
+    import torch
+    from paper_2309_03523_amd import binding
+    N = 700
+    rowptr, col = _graph(synth.stream(9, "inf"), N, [5, 300], 9)
+    X = torch.randn((1, N, F), device="cuda")
+    X[0, ::13] = float("inf")
+    row = np.repeat(np.arange(N), np.diff(rowptr))
+    hit = np.zeros(N, bool)
+    hit[row[col % 13 == 0]] = True
+    assert 50 < hit.sum() < N - 50
+    layer = binding.DgcLayer([torch.from_numpy(rowptr).cuda()], [torch.from_numpy(col).cuda()], N, [(0, N, 0, 1)], F=F, S=32, H=32,
+                             time_kind="none")
+    M = torch.zeros((N, (F + 7) // 8 * 8), device="cuda")
+    layer.aggregate(X, X, M)
+    torch.cuda.synchronize()
+    got = M.cpu().numpy()[:, :F]
+    assert np.isposinf(got[hit]).all() and np.isfinite(got[~hit]).all()
+    layer.destroy()
