@@ -17,6 +17,15 @@ constexpr int kTileRows = 64;      // rows of one tile of the workgroup-tile den
 constexpr int kWaveTileRows = 32;  // rows of one tile of the split dense kernels and the weight-gradient kernel
 
 // One (chunk, snapshot) pair of the fused batch.
+#if defined(__HIP_DEVICE_COMPILE__) || defined(__HIPCC__)
+// Global memory by name: a pointer chosen between a tensor and a constant would else be read by flat loads, which wait for the
+// LDS, too.
+typedef const __attribute__((address_space(1))) char gbyte;
+typedef uint32_t uintx4 __attribute__((ext_vector_type(4)));
+__device__ __forceinline__ gbyte* in_global(const void* p) { return (gbyte*)(uintptr_t)p; }
+__device__ __forceinline__ uintx4 load16(gbyte* p) { return *(const __attribute__((address_space(1))) uintx4*)p; }
+#endif
+
 struct Segment {
   int64_t row_off;   // first packed row
   int64_t nnz_off;   // first packed non-zero
@@ -153,6 +162,7 @@ struct SpmmArgs {
   // is read from the cache; .y = the bits of the neighbour's degree scaling d_j^-1/2.  nullptr: the
   // kernels walk colidx and look the scaling up.
   const int2* etab;
+  bool keep_out;              // set by the launch: outputs are stored to stay in the caches
   const AggItem* items; int64_t n_items;      // row groups in the order of their snapshots
   // etab holds the neighbours of the row's own chunk alone: the first entry of every packed row, and of the one past the last
   const int64_t* eptr;

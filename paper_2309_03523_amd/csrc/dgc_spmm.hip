@@ -381,14 +381,14 @@ __device__ __forceinline__ int of_lane(int v) {      // lane U of each LPR
 
 template <int LPR>
 struct AggGather {
-  const char *fresh, *stale;      // this lane's 16 bytes of row 0
+  gbyte *fresh, *stale;      // this lane's 16 bytes of row 0
   uint32_t ld_bytes;
   template <int U>
   __device__ __forceinline__ void one(int2 e, int n, float4& v, float& w) const {
     const int col = of_lane<LPR, U>(e.x), b = of_lane<LPR, U>(e.y);
-    const char* const base = col >= 0 ? fresh : stale;
-    const char* const at = base + (uint64_t)(uint32_t)(col ^ (col >> 31)) * ld_bytes;
-    v = *reinterpret_cast<const float4*>(U < n ? at : reinterpret_cast<const char*>(&agg_zero));
+    gbyte* const base = col >= 0 ? fresh : stale;
+    gbyte* const at = base + (uint64_t)(uint32_t)(col ^ (col >> 31)) * ld_bytes;
+    v = __builtin_bit_cast(float4, load16(U < n ? at : in_global(&agg_zero)));
     w = __int_as_float(b);
   }
   // the n (of at most eight) non-zeros whose entries the lanes hold
@@ -408,19 +408,17 @@ __device__ __forceinline__ void agg_add(const float4 (&v)[8], const float (&w)[8
 }
 // this lane's entry of the eight from pos on (past the row's end its last; kEtabPad spare ones end the table)
 __device__ __forceinline__ int2 agg_entry(const int2* tab, int start, int pos, int end) {
-  typedef int intx2 __attribute__((ext_vector_type(2)));
-  const int at = max(start, min(pos + (int)(threadIdx.x & 7), end - 1));
-  const intx2 e = __builtin_nontemporal_load(reinterpret_cast<const intx2*>(tab + at));    // streamed
-  return make_int2(e.x, e.y);
+  return tab[max(start, min(pos + (int)(threadIdx.x & 7), end - 1))];    // (read again by the other slices: not as a stream, 95 -> 90 us of 10 x 12 345 rows)
 }
 // this slice's columns of an output row, and zeros up to the pitch behind the last slice
 template <int LPR>
-__device__ __forceinline__ void agg_store(float* out, int fi, int c1, int F, const float (&acc)[4], float scale) {
+__device__ __forceinline__ void agg_store(const SpmmArgs& a, float* out, int fi, int c1, const float (&acc)[4], float scale) {
   if (fi < c1) {
     float o[4];
 #pragma unroll
-    for (int q = 0; q < 4; ++q) o[q] = fi + q < F ? acc[q] * scale : 0.f;
-    vstore<4>(out + fi, o);
+    for (int q = 0; q < 4; ++q) o[q] = fi + q < a.F ? acc[q] * scale : 0.f;
+    if (a.keep_out) *reinterpret_cast<float4*>(out + fi) = make_float4(o[0], o[1], o[2], o[3]);
+    else vstore<4>(out + fi, o);
   }
   const float z[4] = {0.f, 0.f, 0.f, 0.f};
   for (int c = fi + 4 * LPR; c < c1; c += 4 * LPR) vstore<4>(out + c, z);
@@ -461,7 +459,7 @@ struct AggSlice {
   }
   __device__ __forceinline__ AggGather<LPR> of(const SpmmArgs& a, int t) const {
     const int64_t col = (int64_t)t * a.g.N * a.ld_fresh + (fi < a.F ? fi : c0);     // lanes past the row's end re-read its first columns (never stored)
-    return AggGather<LPR>{reinterpret_cast<const char*>(a.fresh + col), reinterpret_cast<const char*>(a.stale + col), (uint32_t)(a.ld_fresh * sizeof(float))};
+    return AggGather<LPR>{in_global(a.fresh + col), in_global(a.stale + col), (uint32_t)(a.ld_fresh * sizeof(float))};
   }
 };
 
@@ -543,7 +541,7 @@ __device__ __forceinline__ void agg_rows(const SpmmArgs& a, const AggSlice<LPR>&
     float sum[4];
     agg_shared<LPR>(from, tab, __builtin_amdgcn_readlane(start, r), __builtin_amdgcn_readlane(end, r), sum);
     if (g == 0)
-      agg_store<LPR>(a.M + readlane64(orow, r) * ldo, slice.fi, slice.c1, a.F, sum, __int_as_float(__builtin_amdgcn_readlane(__float_as_int(scale), r)));
+      agg_store<LPR>(a, a.M + readlane64(orow, r) * ldo, slice.fi, slice.c1, sum, __int_as_float(__builtin_amdgcn_readlane(__float_as_int(scale), r)));
   }
   if (!listed) return;
   int row = min(g, listed - 1), next = G;
@@ -579,7 +577,7 @@ __device__ __forceinline__ void agg_rows(const SpmmArgs& a, const AggSlice<LPR>&
         sum[q] = acc[0][q] + acc[1][q];
         acc[0][q] = acc[1][q] = 0.f;
       }
-      agg_store<LPR>(a.M + out.orow * ldo, slice.fi, slice.c1, a.F, sum, out.scale);
+      agg_store<LPR>(a, a.M + out.orow * ldo, slice.fi, slice.c1, sum, out.scale);
     }
     if (!__ballot(busy)) break;
   }
@@ -601,7 +599,7 @@ __global__ __launch_bounds__(256) void k_agg(SpmmArgs a, int ns, int64_t part_bl
     if (!agg_part(a, item, &p)) return;
     float sum[4];
     agg_shared<LPR>(slice.of(a, p.t), a.etab + p.e, 0, p.nnz, sum);
-    if ((threadIdx.x & (kWave - 1)) < LPR) agg_store<LPR>(a.partial + item * a.ldm, slice.fi, slice.c1, a.F, sum, 1.0f);
+    if ((threadIdx.x & (kWave - 1)) < LPR) agg_store<LPR>(a, a.partial + item * a.ldm, slice.fi, slice.c1, sum, 1.0f);
   }
 }
 
@@ -645,7 +643,7 @@ __global__ __launch_bounds__(256) void k_agg_team(SpmmArgs a, int ns, int64_t pa
         const float4 s0 = sums[turn & 1][0][l], s1 = sums[turn & 1][1][l], s2 = sums[turn & 1][2][l], s3 = sums[turn & 1][3][l];
         const float sum[4] = {((s0.x + s1.x) + s2.x) + s3.x, ((s0.y + s1.y) + s2.y) + s3.y, ((s0.z + s1.z) + s2.z) + s3.z,
                               ((s0.w + s1.w) + s2.w) + s3.w};
-        agg_store<LPR>(out + row.orow * ldo, slice.fi, slice.c1, a.F, sum, row.scale);
+        agg_store<LPR>(a, out + row.orow * ldo, slice.fi, slice.c1, sum, row.scale);
       }
     }
 }
@@ -655,7 +653,11 @@ __global__ __launch_bounds__(256) void k_agg_team(SpmmArgs a, int ns, int64_t pa
 // are the faster ones (62 500 x 64 rows of 256 6.74 ms, 7.33 with the team; 20 000 x 8 of 300 374 us and 404).  And parts shorter than a
 // shared row are a workgroup's only while the chip holds all of them at once.
 template <int LPR>
-void launch_agg(const SpmmArgs& a, hipStream_t st) {
+void launch_agg(SpmmArgs a, hipStream_t st) {
+  // Outputs of the size of the L2s are still there when the next kernel reads them; larger ones are streamed past the rows that are
+  // read again (8 x 1000 rows of 32 floats: a forward of 19.1 us takes 18.3, 10 x 12 345 of 50 95 and 92; 64 x 62 500 of 256, kept: 22.26 ms
+  // becomes 22.48).
+  a.keep_out = a.n_items * kAggRows * a.ldm * (int64_t)sizeof(float) <= 64 << 20;
   const int64_t ns = (a.F + 4 * LPR - 1) / (4 * LPR), few = 14 * 1024;
   const bool team = a.longest_row > kShared<LPR> && a.n_items * ns <= few && a.n_long * ns <= (a.part_nnz > kShared<LPR> ? few : kTeamsAtOnce);
   const int64_t parts = team ? a.n_long * ns : (a.n_long * ns + kTeam - 1) / kTeam;
