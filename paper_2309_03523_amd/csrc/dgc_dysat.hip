@@ -163,7 +163,7 @@ struct GatArgs {
 struct SoftAcc { float m, l, a0, a1; };
 constexpr float kLowest = -3.4028234663852886e38f;
 
-constexpr int kBatch = 4;    // neighbours per slot and batch (2: 95 us and 2.83 ms)
+constexpr int kBatch = 4;    // neighbours per slot and batch
 struct GatBatch { uint4 z[kBatch]; float e[kBatch]; };
 
 __device__ __forceinline__ float slots_max(float x) {    // over lanes l, l^16, l^32, l^48
@@ -262,47 +262,143 @@ __device__ __forceinline__ void gat_row_store(const GatArgs& a, int64_t row, con
 constexpr int kTeam = 4, kShared = 8 * 4 * kBatch;     // eight batches of a wave (four: the same on small graphs, 0.5 % more on large ones)
 struct TeamRow { int64_t e0; int32_t seg, i, n; };     // first non-zero, segment, vertex, non-zeros
 
+
+// Rows of at most kSlotRow non-zeros: one to each of a wave's four slots of 16 lanes, eight neighbours at a time; where one ends, its
+// slot takes the next of the item's.  What a row costs beside its neighbours is paid once for four, and nothing is summed across
+// slots: the kernel was bound by the vector units (323 instructions of a wave a row, where a wave took one row after the other).
+// 16 x 250 000 vertices 2826 -> 2212 us, 12 x 5001 51.6 -> 47.  (16, 24, 48, 64 non-zeros a slot: 98.8, 99.4, 101.9, 105 us of the whole
+// forward of the smaller, the same of the larger within 0.3 %; four waves a SIMD: 2313 us.)
+constexpr int kSlotRow = 24, kSlots = 4;
+struct SlotRow { int start, end, r; };        // non-zeros from the item's first; row of the item
+__device__ const uint4 kNoRow = {0, 0, 0, 0};      // what a slot loads past its row's end
+
+template <int U>
+__device__ __forceinline__ int of_slot(int v) {      // lane U of each 16
+  return __builtin_amdgcn_ds_swizzle(v, (U << 5) | 0x10);
+}
+
+struct SlotBatch { uint4 z[8]; float s[8]; };
+struct SlotRows {
+  gbyte *zx, *zc, *sx, *sc;       // vertex 0 of the snapshot: this lane's 16 bytes of a projection, its head's scalar
+  uint32_t lo, span;
+  template <int U>
+  __device__ __forceinline__ void one(int32_t ids, int n, SlotBatch& b) const {
+    const uint32_t j = (uint32_t)of_slot<U>(ids);
+    const bool in = j - lo < span;
+    gbyte* const z = (in ? zx : zc) + (uint64_t)j * (kS * 2);
+    b.z[U] = __builtin_bit_cast(uint4, load16(U < n ? z : in_global(&kNoRow)));
+    b.s[U] = *(const __attribute__((address_space(1))) float*)((in ? sx : sc) + (uint64_t)j * (in ? 64u : 32u));
+  }
+  __device__ __forceinline__ void batch(int32_t ids, int n, SlotBatch& b) const {
+    one<0>(ids, n, b); one<1>(ids, n, b); one<2>(ids, n, b); one<3>(ids, n, b);
+    one<4>(ids, n, b); one<5>(ids, n, b); one<6>(ids, n, b); one<7>(ids, n, b);
+  }
+};
+
+__device__ __forceinline__ void gat_slots(const GatArgs& a, const Segment& s, const int32_t* col, int64_t base, int64_t i0, const SlotRow* list,
+                                          int listed, int lane) {
+  const int slot = lane >> 4, sub = lane & 15, head = sub >> 1;
+  const SlotRows from{in_global(a.zX + base * kS + 8 * sub), in_global(a.zC + base * kS + 8 * sub), in_global(a.sX + base * 16 + head),
+                      in_global(a.sC + base * 8 + head), (uint32_t)s.v_lo, (uint32_t)(s.v_hi - s.v_lo)};
+  const float* const sd_of = a.sX + (base + i0) * 16 + 8 + head;
+  auto ids_at = [&](int pos, int end) { return end > pos ? col[min(pos + (sub & 7), end - 1)] : 0; };
+  int k = min(slot, listed - 1), next = kSlots;
+  bool busy = slot < listed;
+  SlotRow row = list[k];
+  int pos = row.start;
+  int32_t ids = ids_at(pos, row.end);
+  float sd = sd_of[row.r * 16], m = kLowest, l = 0.f, acc[8] = {};
+  for (;;) {
+    SlotBatch b;
+    const int left = busy ? row.end - pos : 0;
+    from.batch(ids, left, b);
+    const bool done = busy && left <= 8;
+    const uint64_t ends = __ballot(done && sub == 0);
+    const int r = row.r;
+    const bool stored = row.end > row.start;
+    const float sd_now = sd;
+    pos += 8;
+    if (done) {
+      k = next + __popcll(ends & ((1ull << (lane & ~15)) - 1));
+      busy = k < listed;
+      row = list[min(k, listed - 1)];
+      pos = row.start;
+      sd = sd_of[row.r * 16];
+    }
+    next += __popcll(ends);
+    ids = ids_at(pos, row.end);
+    float e[8], mn = m;
+#pragma unroll
+    for (int u = 0; u < 8; ++u) {
+      e[u] = u < left ? lrelu(sd_now + b.s[u]) : -INFINITY;
+      mn = fmaxf(mn, e[u]);
+    }
+    const float sc = __expf(m - mn);
+    m = mn;
+    l *= sc;
+#pragma unroll
+    for (int d = 0; d < 8; ++d) acc[d] *= sc;
+#pragma unroll
+    for (int u = 0; u < 8; ++u) {
+      const float p = __expf(e[u] - mn);
+      float z[8];
+      unpackh8(b.z[u], z);
+      l += p;
+#pragma unroll
+      for (int d = 0; d < 8; ++d) acc[d] += p * z[d];
+    }
+    if (done) {
+      const int64_t at = base + i0 + r;
+      const float sum = stored && l == 0.f ? NAN : l;      // (no logit above -inf: the softmax is NaN)
+      const float inv = sum > 0.f ? 1.f / sum : sum;
+      float4* const u = reinterpret_cast<float4*>(a.U + at * kS + 8 * sub);
+      u[0] = make_float4(acc[0] * inv, acc[1] * inv, acc[2] * inv, acc[3] * inv);
+      u[1] = make_float4(acc[4] * inv, acc[5] * inv, acc[6] * inv, acc[7] * inv);
+      if (!(sub & 1)) a.lse[at * 8 + head] = m + __logf(sum);
+      m = kLowest;
+      l = 0.f;
+#pragma unroll
+      for (int d = 0; d < 8; ++d) acc[d] = 0.f;
+    }
+    if (!__ballot(busy)) break;
+  }
+}
+
 template <bool TEAM>
-__device__ __forceinline__ void gat_short(const GatArgs& a, int64_t item, int lane, TeamRow* queue, int* n_queued) {
-  int queued = 0;
+__device__ __forceinline__ void gat_short(const GatArgs& a, int64_t item, int lane, SlotRow* list, TeamRow* queue, int* n_queued) {
   if constexpr (TEAM) {
     if (lane == 0) *n_queued = 0;
   }
   if (item >= a.n_work) return;
-  const int32_t si = a.work[3 * item], r0 = a.work[3 * item + 1], nr = a.work[3 * item + 2];
+  const int32_t si = a.work[3 * item], r0 = a.work[3 * item + 1], nr = a.work[3 * item + 2];      // (at most 32 rows)
   const Segment s = a.segs[si];
-  const int32_t* col = a.g.colidx[s.t];
   const int64_t base = (int64_t)s.t * a.g.N, i0 = s.v_lo + r0;
-  const int head = (lane & 15) >> 1;
-  const int64_t rp = a.g.rowptr[s.t][i0 + min(lane, nr)];      // of the whole group (at most 32 rows)
-  const int32_t rlo = (int32_t)(rp & 0xffffffff), rhi = (int32_t)(rp >> 32);
-  auto row_ptr = [&](int r) {
-    return ((int64_t)__builtin_amdgcn_readlane(rhi, r) << 32) | (uint32_t)__builtin_amdgcn_readlane(rlo, r);
-  };
-  int64_t e0 = row_ptr(0), e1 = row_ptr(1);
-  int32_t ids = e0 + lane < e1 ? col[e0 + lane] : 0;
-  float sd = a.sX[(base + i0) * 16 + 8 + head];
-  for (int rr = 0; rr < nr; ++rr) {
-    int64_t ne1 = e1;
-    int32_t nids = 0;
-    float nsd = 0.f;
-    if (rr + 1 < nr) {
-      ne1 = row_ptr(rr + 2);
-      nids = e1 + lane < ne1 ? col[e1 + lane] : 0;
-      nsd = a.sX[(base + i0 + rr + 1) * 16 + 8 + head];
-    }
-    if (TEAM && e1 - e0 > kShared && e1 - e0 <= a.long_nnz) {
-      if (lane == 0) queue[queued] = TeamRow{e0, si, (int32_t)(i0 + rr), (int32_t)(e1 - e0)};
-      ++queued;
-    } else if (e1 - e0 <= a.long_nnz) {    // split rows: gat_long
-      const SoftAcc r = gat_row_range(a, s, col + e0, base, sd, (int)(e1 - e0), ids, lane);
-      gat_row_store(a, base + i0 + rr, r, own_feature(lane), lane < 16 && !(lane & 1), head, e1 > e0);
-    }
-    e0 = e1; e1 = ne1; ids = nids; sd = nsd;
-  }
+  const int64_t rp = a.g.rowptr[s.t][i0 + min(lane, nr)];
+  const int64_t first = ((int64_t)__builtin_amdgcn_readfirstlane((int)(rp >> 32)) << 32) | (uint32_t)__builtin_amdgcn_readfirstlane((int)rp);
+  const int64_t len64 = __shfl_down((long long)rp, 1) - rp;
+  const int start = (int)(rp - first), len = (int)len64;
+  const int32_t* col = a.g.colidx[s.t] + first;
+  const bool here = lane < nr && len64 <= a.long_nnz;      // (split rows: gat_long)
+  const uint64_t below = (1ull << lane) - 1;
+  const uint64_t teams = TEAM ? __ballot(here && len > kShared) : 0;
+  uint64_t waves = __ballot(here && (len > kSlotRow || nr < kSlots)) & ~teams;
+  const uint64_t own = __ballot(here) & ~waves & ~teams;
+  if (own >> lane & 1) list[__popcll(own & below)] = SlotRow{start, start + len, lane};
   if constexpr (TEAM) {
-    if (lane == 0) *n_queued = queued;
+    if (teams >> lane & 1) queue[__popcll(teams & below)] = TeamRow{rp, si, (int32_t)(i0 + lane), len};
+    if (lane == 0) *n_queued = __popcll(teams);
   }
+  __builtin_amdgcn_wave_barrier();
+  const int head = (lane & 15) >> 1, listed = __popcll(own);
+  while (waves) {
+    const int r = __builtin_ctzll(waves);
+    waves &= waves - 1;
+    const int n = __builtin_amdgcn_readlane(len, r);
+    const int32_t* at = col + __builtin_amdgcn_readlane(start, r);
+    const SoftAcc sum = gat_row_range(a, s, at, base, a.sX[(base + i0 + r) * 16 + 8 + head], n, lane < n ? at[lane] : 0, lane);
+    gat_row_store(a, base + i0 + r, sum, own_feature(lane), lane < 16 && !(lane & 1), head);
+  }
+  if (listed) gat_slots(a, s, col, base, i0, list, listed, lane);
 }
 
 // record of one part of a split row: weighted sum [128], maximum [8], sum [8]
@@ -349,15 +445,17 @@ __device__ __forceinline__ void gat_long(const GatArgs& a, int64_t item, int lan
 
 __global__ __launch_bounds__(256, 5) void k_gat_aggregate(GatArgs a, int64_t long_blocks) {
   const int lane = threadIdx.x & 63;
+  __shared__ SlotRow list[kTeam][32];
   const int64_t block = blockIdx.x, wave = threadIdx.x >> 6;
   if (block < long_blocks) gat_long(a, block * kTeam + wave, lane);
-  else gat_short<false>(a, (block - long_blocks) * kTeam + wave, lane, nullptr, nullptr);
+  else gat_short<false>(a, (block - long_blocks) * kTeam + wave, lane, list[wave], nullptr, nullptr);
 }
 
 // The same where a row is longer than kShared: the launch on a small graph waits for its longest row (1024 non-zeros are 64
 // batches in turn), so the four waves of a workgroup share a part, and the longer rows of their groups
 // once the others are done.  The quarters' records meet in LDS and are merged in wave order.
 __global__ __launch_bounds__(256, 5) void k_gat_aggregate_team(GatArgs a, int64_t long_blocks) {
+  __shared__ SlotRow list[kTeam][32];
   __shared__ TeamRow queue[kTeam][32];          // a group has at most 32 rows
   __shared__ int queued[kTeam];
   __shared__ __align__(16) float recs[2][kTeam][kLongRec];
@@ -377,7 +475,7 @@ __global__ __launch_bounds__(256, 5) void k_gat_aggregate_team(GatArgs a, int64_
       }
     }
   } else {
-    gat_short<true>(a, (block - long_blocks) * kTeam + wave, lane, queue[wave], queued + wave);
+    gat_short<true>(a, (block - long_blocks) * kTeam + wave, lane, list[wave], queue[wave], queued + wave);
   }
   __syncthreads();
   int turn = 0;
