@@ -20,8 +20,9 @@ ROOT = os.path.dirname(os.path.abspath(__file__))
 if ROOT not in sys.path:
     sys.path.insert(0, ROOT)
 
-# the split dense kernels: an fp32 product is six bf16 ones (2.5 PFLOP/s dense)
+# the split dense kernels: an fp32 product is six bf16 ones (2.5 PFLOP/s dense), or three half-precision ones (at the same rate)
 PEAK_SPLIT_MFMA_TFLOPS = 2500.0 / 6
+PEAK_HALVES_MFMA_TFLOPS = 2500.0 / 3
 PEAK_HBM_GBS = 8000.0
 
 
@@ -127,9 +128,9 @@ def flops_per_row(wl) -> dict:
 
 def folds_transform(K0: int, S: int, kind: str) -> bool:
     """Whether the time encoder behind a transform without an activation takes the transform folded into its input-side weights
-    (the library's dense_fold_wanted): products in k-blocks of 16, an LSTM 96 or 128 wide from six saved on."""
+    (the library's dense_fold_wanted): wherever products in k-blocks of 16 are saved."""
     g, nkb = {"gru": 3, "lstm": 4}[kind], (K0 + 15) // 16
-    return nkb + g * (S // 16) - g * nkb >= (6 if kind == "lstm" and S in (96, 128) else 1)
+    return nkb + g * (S // 16) - g * nkb >= 1
 
 
 def runs_narrow(K0: int, S: int, kind: str, tiles: int, window: int) -> bool:
@@ -143,26 +144,28 @@ def runs_narrow(K0: int, S: int, kind: str, tiles: int, window: int) -> bool:
             return True
         if K0 > 48:
             return window > 1 or tiles >= 2048
-        return window > 1 and tiles <= (256 * w if folds else 1024)
+        return tiles <= (256 * (w - 1) if folds else min(512 * (w - 1), 1024))
     if window == 1:
-        return K0 > 128 and tiles <= 256
+        return tiles <= 128
     if folds:
-        return tiles <= (128 if K0 > 32 else 64) * w
-    return tiles <= (1024 if K0 > 96 else 640)
+        return tiles <= (384 if window >= (4 if K0 > 64 else 6) else 128)
+    return tiles <= (2048 if K0 > 144 else 384 if window == 2 else 512)
 
 
 def time_encoder_work(K0: int, S: int, kind: str, tiles: int, window: int, concat: bool = False) -> dict:
     """The kernel of the last GCN layer's transform and the time encoder (S = H, no activation between them), what it does, and
-    its flops per row: those of the layer as it is defined and those of the products that the kernel executes."""
+    its flops per row: those of the layer as it is defined and those of the products that the kernel executes; their peak rate."""
     gH = {"gru": 3, "lstm": 4}[kind] * S
     rest = 2 * S * gH * (2 if concat else 1)        # hidden side, and the other half of a concatenated input
     layer = 2 * K0 * S + 2 * S * gH + rest
     if not concat and runs_narrow(K0, S, kind, tiles, window):
-        return {"kernel": f"k_dense_narrow<{kind.upper()}>", "what": "GCN transform + time encoder", "layer": layer, "executed": layer}
+        return {"kernel": f"k_dense_narrow<{kind.upper()}>", "what": "GCN transform + time encoder", "layer": layer, "executed": layer,
+                "peak": PEAK_SPLIT_MFMA_TFLOPS}
     if folds_transform(K0, S, kind):
         return {"kernel": f"k_dense_split<{kind.upper()}>", "what": "time encoder with the GCN transform folded into its input-side weights",
-                "layer": layer, "executed": 2 * K0 * gH + rest}
-    return {"kernel": f"k_dense_split<{kind.upper()}>", "what": "GCN transform + time encoder", "layer": layer, "executed": layer}
+                "layer": layer, "executed": 2 * K0 * gH + rest, "peak": PEAK_HALVES_MFMA_TFLOPS}
+    return {"kernel": f"k_dense_split<{kind.upper()}>", "what": "GCN transform + time encoder", "layer": layer, "executed": layer,
+            "peak": PEAK_HALVES_MFMA_TFLOPS}
 
 
 def tiles_of(sizes) -> int:
@@ -814,8 +817,8 @@ def labelled_main(args):
                                    f"slots for {rows} present rows ({rows / max(1, n_lanes * T):.1%} of the slots filled); value counts present rows"),
                       "rows": rows, "nnz": nnz, "gather_mode": "in_place", "pass": "forward"},
            "roofline": {"kernel": f"{work['kernel']} ({work['what']}, over every vertex's label runs)",
-                        "bound": "mfma", "achieved": achieved, "peak": PEAK_SPLIT_MFMA_TFLOPS, "unit": "TFLOP/s",
-                        "frac": achieved / PEAK_SPLIT_MFMA_TFLOPS, "traffic": traffic.get("dense"),
+                        "bound": "mfma", "achieved": achieved, "peak": work["peak"], "unit": "TFLOP/s",
+                        "frac": achieved / work["peak"], "traffic": traffic.get("dense"),
                         "flops_per_launch": dense_flops, "layer_flops_per_launch": work["layer"] * dense_rows, "ms_per_launch": dense_ms},
            "roofline_aggregation": {"kernel": "k_agg_team / k_agg + k_spmm_long_reduce (edge-table kernels over pre-marked columns)",
                                     "bound": "hbm", "achieved": agg_bytes / (agg_ms * 1e-3) / 1e9, "peak": PEAK_HBM_GBS,
@@ -1099,8 +1102,8 @@ def gcn_run(args) -> dict:
     achieved = dense_flops / (dense_ms * 1e-3) / 1e12
     traffic = measured_traffic(args.workload, args.gather_mode)
     roofline = {"kernel": f"{work['kernel']} ({work['what']}, fused over the window)",
-                "bound": "mfma", "achieved": achieved, "peak": PEAK_SPLIT_MFMA_TFLOPS, "unit": "TFLOP/s",
-                "frac": achieved / PEAK_SPLIT_MFMA_TFLOPS, "traffic": traffic.get("dense"),
+                "bound": "mfma", "achieved": achieved, "peak": work["peak"], "unit": "TFLOP/s",
+                "frac": achieved / work["peak"], "traffic": traffic.get("dense"),
                 "flops_per_launch": dense_flops, "layer_flops_per_launch": work["layer"] * dense_rows, "ms_per_launch": dense_ms}
     # aggregation kernels: algorithmic (compulsory) bytes = X rows once + CSR + M written once
     nnz = int(layer.packing("seg_nnz_off")[-1])
@@ -1237,7 +1240,7 @@ def config3_run(args) -> dict:
     traffic = measured_traffic("config3_mpnn_lstm" if full else "config3", args.gather_mode)     # per window
     roofline = {"kernel": f"{work['kernel']} ({work['what']}, second GCN layer, fused over the window" +
                           (", and the second LSTM layer's launch)" if full else ")"), "bound": "mfma",
-                "achieved": ach, "peak": PEAK_SPLIT_MFMA_TFLOPS, "unit": "TFLOP/s", "frac": ach / PEAK_SPLIT_MFMA_TFLOPS,
+                "achieved": ach, "peak": work["peak"], "unit": "TFLOP/s", "frac": ach / work["peak"],
                 "traffic": traffic.get("dense"), "flops_per_launch": dense_flops / len(windows),
                 "layer_flops_per_launch": (work["layer"] + second) * rows / len(windows), "ms_per_launch": dense_ms / len(windows)}
     first_flops = 2 * F * S * rows

@@ -410,30 +410,32 @@ bool dense_narrow_supported(int32_t S, int32_t H, int32_t K0, int32_t time_kind)
   return S == H && (H == 32 || H == 64) && (time_kind == DGC_TIME_GRU || time_kind == DGC_TIME_LSTM) && narrow_lds(H, K0, time_kind) <= 160 * 1024;
 }
 
-// Against k_dense_split, which takes the folded transform where there is one.  What this kernel has the less of is the chain of a
-// step and the transform's time; what it pays is that a workgroup loads all weights first (with windows of one step for nothing)
-// and, where tiles are many, that fewer of them are on the chip at once.  So it is for few tiles, the more the longer the windows
-// are, for more where the other kernel's transform is not folded, and for any number where the input is wide.
-// A forward of 8 snapshots, GRU, other kernel -> this one, in us; w: the windows' snapshots (LSTM: 2 to 8 % better for this one).
-//   64 wide, folded, 64 columns:  128 tiles w 1 16.1 -> 16.3, w 2 19.9 -> 17.3, w 8 53.9 -> 33.4; 512 w 2 31.5 -> 33.6, w 8 98 -> 93;
-//                                 1024 w 8 151 -> 169
-//            folded, 16 columns:  128 tiles w 8 1.5 times as fast, 256 w 4 as fast, 400 w 8 0.92 times
-//            128 columns:         256 tiles w 1 19.4 -> 20.0, w 2 30.9 -> 28.2; 1024 w 2 80.3 -> 72.6, w 8 285 -> 241
-//            96 columns:          640 tiles w 2 as fast, w 8 1.14 times; 900 w 2 0.92, w 8 0.97 times
-//   32 wide, folded, 32 columns:  512 tiles w 1 15.8 -> 17.1, w 2 21.2 -> 21.2; 1024 w 2 33.4 -> 35.3, w 8 101 -> 98; 2048 w 8 161 -> 176
-//            48 columns:          1024 tiles w 8 118 -> 102; 2048 w 2 57.7 -> 60.2, w 8 185 -> 186
-//            64 columns:          1024 tiles w 1 24.7 -> 26.0, w 2 39.2 -> 38.9; 2048 w 1 41.2 -> 39.6, w 8 245 -> 205; 20 000 w 8 2082 -> 1945
-//            128 columns:         512 tiles w 1 24.3 -> 23.6; 20 000 w 8 4199 -> 3212
+// Against k_dense_split, which takes the folded transform where there is one, and half the matrix instructions.  What this kernel
+// has the less of is the chain of a step and the transform's time; what it pays is that a workgroup loads all weights first (with
+// windows of one step for nothing) and, where tiles are many, that fewer of them are on the chip at once.  So it is for few tiles,
+// the more the longer the windows are, for more where the other kernel's transform is not folded, and for many where the input is
+// so wide that few of the other kernel's workgroups fit a CU's LDS.
+// How many times as long the other kernel takes for a forward, GRU (LSTM: up to a tenth more); w: the windows' snapshots.
+//   64 wide, folded, 64 columns:  128 tiles w 1 1.04 to 1.12, w 2 1.08 to 1.2, w 4 1.36, w 8 1.43; 256 tiles w 2 and 4 0.98, w 8 1.06; 384 tiles
+//                                 w 4 0.99, w 8 1.03, w 16 1.05; 512 tiles w 8 0.89 (GRU over 64: 76 us and 86), 1024 0.72, 2048 0.82
+//            folded, 80 columns:  256 tiles w 4 1.07, 384 1.04, 512 0.91
+//            96 columns:          384 tiles w 2 1.05, 512 0.98, w 4 1.02, w 8 1.02, 768 0.89 to 0.95
+//            128 columns:         128 tiles w 1 1.0, 256 0.95; 384 w 2 1.01, w 4 1.10; 512 w 2 0.94, w 4 1.0, w 8 1.02; 768 w 8 0.91
+//            160, 176 columns:    512 tiles w 2 0.95, w 4 0.99, w 8 1.06; 768 w 2 1.07, w 8 1.2; 1024 w 2 1.0, w 8 1.07; 2048 w 2 and w 8 1.07, w 1 1.0
+//   32 wide, folded, 32 columns:  256 tiles w 1 1.01, w 2 1.1, 512 w 2 0.87, 768 w 4 1.01, w 8 1.07, 1024 w 4 0.94, w 16 0.99; 2048 w 8 0.77
+//            48 columns:          512 tiles w 1 0.98, w 2 1.04, 1024 w 2 0.94, w 4 1.07, w 8 1.1; 2048 w 8 0.91
+//            64 columns:          1024 tiles w 1 0.9, w 2 0.95, w 8 1.1; 2048 w 1 1.01, w 2 1.04, w 8 1.17
+//            80 columns, 128:     1024 tiles w 1 0.94, 1.17, w 8 1.14, 1.53; 2048 w 1 1.03, 1.18, w 8 1.14, 1.33
 bool dense_narrow_wanted(int32_t H, int32_t K0, bool folds, int64_t n_tiles32, int32_t window) {
   const int64_t w = std::min(window, 4);
   if (H == 32) {
     if (K0 > 64) return true;
     if (K0 > 48) return window > 1 || n_tiles32 >= 2048;
-    return window > 1 && n_tiles32 <= (folds ? 256 * w : 1024);
+    return n_tiles32 <= (folds ? 256 * (w - 1) : std::min<int64_t>(512 * (w - 1), 1024));
   }
-  if (window == 1) return K0 > 128 && n_tiles32 <= 256;
-  if (folds) return n_tiles32 <= (K0 > 32 ? 128 : 64) * w;
-  return n_tiles32 <= (K0 > 96 ? 1024 : 640);
+  if (window == 1) return n_tiles32 <= 128;
+  if (folds) return n_tiles32 <= (window >= (K0 > 64 ? 4 : 6) ? 384 : 128);
+  return n_tiles32 <= (K0 > 144 ? 2048 : window == 2 ? 384 : 512);
 }
 
 bool launch_dense_narrow(const DenseArgs& a, hipStream_t st, std::string* why) {

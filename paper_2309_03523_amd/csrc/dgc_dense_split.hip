@@ -783,14 +783,13 @@ bool launch_dense_split(const DenseArgs& a, hipStream_t st, std::string* why) {
 }
 
 // Products of a tile and 32 columns, in k-blocks: the gates over the input's width against the transform and the gates over its
-// output's.  Any that are saved pay (GRU 96 to 256 wide, 2 saved of 44 to 113: 5 to 10 %; LSTM 160 to 256 wide, 1 of 93 and more: 2 %),
-// but for the LSTM 96 and 128 wide: there the rounding additions of the small part products of every k-block are as much as
-// five (8 x 500 vertices, saved 2 of 74: 104.6 -> 110.5 us, 5 of 73: 97.6 -> 100.7, 8 of 72: 94.6 -> 93.9; 8 x 20 000, 5: 382 -> 374).
+// output's.  Any that are saved pay, and the pass of Z through LDS with them: on three parts GRU 96 to 256 wide, 2 saved of 44 to 113: 5 to 10 %;
+// LSTM 160 to 256 wide, 1 of 93 and more: 2 %; on halves LSTM 96 and 128 wide, 3 of 48 (8 x 500 vertices 65.1 -> 56.4 us, 8 x 20 000 204 -> 187),
+// 5 of 73 (75.7 -> 65.3, 282 -> 261), 2 of 74 (80.0 -> 71.5, 294 -> 279; 16 x 60 000 1515 -> 1464).
 bool dense_fold_wanted(int32_t S, int32_t K0, int32_t time_kind) {
-  const bool lstm = time_kind == DGC_TIME_LSTM;
-  const int ng = lstm ? 4 : 3, kbh = S / 16, nkb0 = (K0 + 15) / 16;
+  const int ng = time_kind == DGC_TIME_LSTM ? 4 : 3, kbh = S / 16, nkb0 = (K0 + 15) / 16;
   const int saved = nkb0 + ng * kbh - ng * nkb0;
-  return saved >= (lstm && (S == 96 || S == 128) ? 6 : 1);
+  return saved >= 1;
 }
 
 void launch_fold(const float* wih, int64_t ld_wih, const float* wg, const float* bg, const float* bih, int32_t gH, int32_t S, int32_t K0,
