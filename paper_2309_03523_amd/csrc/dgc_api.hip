@@ -93,6 +93,7 @@ struct dgc_layer {
   int64_t n_agg_items = 0;
   // Table of the neighbours of a row's own chunk, which are all that hand a gradient to it: where each row's begin, how many there are
   int64_t* d_inside_ptr = nullptr; int64_t n_inside = 0;
+  bool all_inside() const { return d_inside_ptr && n_inside == total_nnz; }     // the rows' table is that of their own chunks
   int2* d_inside = nullptr;
   int2* inside_room = nullptr; int64_t n_inside_room = 0;      // memory for it behind d_dM
   int64_t* d_rowidx = nullptr;                   // [total rows] packed row -> t*N + v
@@ -364,6 +365,7 @@ dgc_status_t build_agg_items(dgc_layer* L, hipStream_t st) {
     // few rows: fewer a wave, so that more waves share them, down to one a lane group (14 x 1255 of 64 floats: 16, 8, 4 rows a wave take
     // 39, 30, 22 us; 8 x 3000: 35, 28, 28; 16 x 3000: 34, 37, 38)
     while (rows > 4 && L->total_rows * ns / rows < 2560) rows /= 2;
+  while (rows < kAggRows && L->total_rows * ns / rows > 1 << 25) rows = std::min(2 * rows, kAggRows);      // (a launch has at most 2^32 threads)
   std::vector<int64_t> order(segs.size());
   for (size_t s = 0; s < segs.size(); ++s) order[s] = (int64_t)s;
   std::stable_sort(order.begin(), order.end(), [&](int64_t a, int64_t b) { return segs[a].t < segs[b].t; });
@@ -1366,14 +1368,14 @@ static dgc_status_t prepare_dx(dgc_layer* L, hipStream_t st) {
   if (!L->d_dM) {
     const int64_t wt = (int64_t)L->T * evolve_packed_bytes(L->evo, L->evo.split) / (int64_t)sizeof(float4);
     // (the table of neighbours behind dM: an allocation takes longer than filling it)
-    const int64_t dm = ((int64_t)L->T * L->N * d.F + 1) / 2 * 2, table = L->d_etab ? L->n_inside + kEtabPad : 0;
+    const int64_t dm = ((int64_t)L->T * L->N * d.F + 1) / 2 * 2, table = L->d_etab && !L->all_inside() ? L->n_inside + kEtabPad : 0;
     DGC_HIP_TRY(dev_alloc_all(L, Wanted<float>{&L->d_dM, dm + 2 * table}, Wanted<int64_t>{&L->d_rowidx, L->total_rows},
                               Wanted<float4>{&L->d_Wt_plain, wt}));
     L->inside_room = reinterpret_cast<int2*>(L->d_dM + dm);
     L->n_inside_room = table;
     evolve_row_index(L->d_chunks, L->n_chunks, max_nv, max_w, L->N, L->d_rowidx, st);
   }
-  if (L->d_etab && !L->d_inside) {
+  if (L->d_etab && !L->d_inside && !L->all_inside()) {
     int2* inside = L->inside_room;
     if (L->n_inside + kEtabPad > L->n_inside_room) DGC_HIP_TRY(dev_alloc(L, &inside, L->n_inside + kEtabPad));
     launch_inside(spmm_args(L, L->d_dM, d.F, L->d_dM, d.F, d.F, L->d_dM, d.F), L->d_inside_ptr, inside, st);
@@ -1468,7 +1470,7 @@ dgc_status_t dgc_layer_backward(dgc_layer_t* L, const void* Yv, int64_t ldy, con
     SpmmArgs sa = spmm_args(L, L->d_dM, d.F, L->d_dM, d.F, d.F, static_cast<float*>(dX), d.F);
     sa.ld_out = lddx;
     sa.row_map = L->d_rowidx;
-    sa.skip_stale = true;
+    sa.skip_stale = !L->d_etab || !L->all_inside();
     if (L->d_inside) {
       sa.etab = L->d_inside; sa.eptr = L->d_inside_ptr;
     }

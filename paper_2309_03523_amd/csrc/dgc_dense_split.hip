@@ -200,10 +200,10 @@ __device__ __forceinline__ void relu(floatx16& z) {
 
 // What a row of M is to the time encoder: Z's operand; its input by way of the folded weights (no transform: where no
 // activation stands between them, W_ih (W_g m + b_g) = (W_ih W_g) m + W_ih b_g); its input as it is (a second recurrent layer).
-// Folding takes 48 of 336 MFMAs a tile and step from a GRU 128 wide over 128 columns, and the matrix cores' power is what bounds
-// the kernel: 32 x 100 000 vertices 4.05 -> 3.5 ms, MPNN-LSTM's first LSTM layer with the concatenated input (624 -> 576) 2.92 -> 2.78.  The product of
-// the weights is summed in double and rounded once, where Z was rounded, so nothing gets further from 64 bits (0.87 of the
-// distance in the mean of 46 outputs of GRUs, 0.94 of 24 of LSTMs, 0.999 at most).
+// Folding takes 8 of 56 products of 16-wide links a tile, step and wave from a GRU 128 wide over 128 columns, the pass of Z through
+// LDS and a barrier: on three parts 32 x 100 000 vertices 4.05 -> 3.5 ms (2.45 on halves).  The product of
+// the weights is summed in double and rounded once, where Z was rounded, so nothing gets further from 64 bits (on three parts 0.87 of
+// the distance in the mean of 46 outputs of GRUs, 0.94 of 24 of LSTMs, 0.999 at most).
 enum Input { kTransform, kFolded, kStack };
 
 template <int NG, bool FEW, int P> constexpr int kHeldOf = FEW && P == 3 ? 2 : NG;     // weight fragments held of the gates

@@ -358,8 +358,8 @@ __global__ __launch_bounds__(256) void k_spmm_long_reduce(SpmmArgs a) {
 // swizzles.  Past a row's end a batch loads zeros, so nothing but the row's neighbours gets into its sum.  Rows of more than kAggLong non-zeros, and parts of
 // split rows, are shared by the G groups.  A row's sum runs in two chains.
 //   One row for the whole width of a wave and, where it is narrower, two or four of at most 16 non-zeros at a time took 2853 us where 64
-// columns a wave take 2660 (100 000 x 32 rows of 128 floats), 7151 and 6740 (62 500 x 64 of 256), 694 and 613 (30 001 x 24 of 128), 1200
-// and 1129 (40 000 x 32 of 172), 458 and 372 (20 000 x 8 of 300), 65 and 51 (12 345 x 10 of 50), 10.7 and 9.5 (1000 x 8 of 32).  32 columns
+// columns a wave take 2660 (100 000 x 32 rows of 128 floats), 7151 and 6630 (62 500 x 64 of 256), 694 and 613 (30 001 x 24 of 128), 1200
+// and 1129 (40 000 x 32 of 172), 458 and 366 (20 000 x 8 of 300), 65 and 50 (12 345 x 10 of 50), 10.7 and 9.5 (1000 x 8 of 32).  32 columns
 // a wave are 2 to 4 % slower from 128 floats on (of a pitch of 704 bytes, where a line of 128 then lies across two, 11 %), 128 columns 2 to 12 %.
 //   A slice of all rows after the other, so that an XCD's L2 holds more of it: 104 M lines pass the L2s instead of 134 M, but the
 // launches take 2974 and 9238 us, since a slice of a power-of-two pitch lies in a quarter or an eighth of an L2's channels.  Two batches
@@ -675,26 +675,25 @@ void launch_agg_all(const SpmmArgs& a, hipStream_t st) {
   else hipLaunchKernelGGL((k_spmm_long_reduce<4>), gl, 256, 0, st, a);
 }
 
-// The first entry of every row in a table of the neighbours of its own chunk alone, counted (FILL: their entries, in order).
+// The first entry of every row in a table of the neighbours of its own chunk alone, counted (FILL: their entries, in order).  A
+// wave a row: two dependent reads of a few microseconds each, and where a wave took an item's rows one after the other, sixteen
+// times that.
 template <bool FILL>
-__global__ __launch_bounds__(256) void k_inside(SpmmArgs a, int64_t* eptr, int2* inside) {
-  const int lane = threadIdx.x & (kWave - 1);
-  const int64_t item = (int64_t)blockIdx.x * kTeam + uniform(threadIdx.x / kWave);
-  if (item >= a.n_items) return;
-  const AggItem it = a.items[item];
-  const int64_t* rp = a.g.rowptr[it.t] + it.v0;
-  for (int r = 0; r < it.n; ++r) {
-    const int64_t ea = rp[r] + it.base, eb = rp[r + 1] + it.base;
-    int64_t at = FILL ? eptr[it.row + r] : 0;
-    for (int64_t e = ea; e < eb; e += kWave) {
-      const int2 entry = e + lane < eb ? a.etab[e + lane] : make_int2(-1, 0);
-      const uint64_t in = __ballot(entry.x >= 0);
-      if constexpr (FILL)
-        if (entry.x >= 0) inside[at + __popcll(in & ((1ull << lane) - 1))] = entry;
-      at += __popcll(in);
-    }
-    if (!FILL && lane == 0) eptr[it.row + r] = at;
+__global__ __launch_bounds__(kAggRows * kWave) void k_inside(SpmmArgs a, int64_t* eptr, int2* inside) {
+  const int lane = threadIdx.x, r = uniform(threadIdx.y);
+  const AggItem it = a.items[blockIdx.x];
+  if (r >= it.n) return;
+  const int64_t* rp = a.g.rowptr[it.t] + it.v0 + r;
+  const int64_t ea = rp[0] + it.base, eb = rp[1] + it.base;
+  int64_t at = FILL ? eptr[it.row + r] : 0;
+  for (int64_t e = ea; e < eb; e += kWave) {
+    const int2 entry = e + lane < eb ? a.etab[e + lane] : make_int2(-1, 0);
+    const uint64_t in = __ballot(entry.x >= 0);
+    if constexpr (FILL)
+      if (entry.x >= 0) inside[at + __popcll(in & ((1ull << lane) - 1))] = entry;
+    at += __popcll(in);
   }
+  if (!FILL && lane == 0) eptr[it.row + r] = at;
 }
 
 // etab[p] = (marked column, scaling of the neighbour) for packed non-zero p
@@ -774,10 +773,10 @@ void launch_spmm(const SpmmArgs& a, hipStream_t st) {
 }
 
 void launch_inside(const SpmmArgs& a, int64_t* eptr, int2* inside, hipStream_t st) {
-  const unsigned blocks = (unsigned)((a.n_items + kTeam - 1) / kTeam);
+  const unsigned blocks = (unsigned)a.n_items;
   if (!blocks) return;
-  if (inside) hipLaunchKernelGGL(k_inside<true>, blocks, 256, 0, st, a, eptr, inside);
-  else hipLaunchKernelGGL(k_inside<false>, blocks, 256, 0, st, a, eptr, inside);
+  if (inside) hipLaunchKernelGGL(k_inside<true>, blocks, dim3(kWave, kAggRows), 0, st, a, eptr, inside);
+  else hipLaunchKernelGGL(k_inside<false>, blocks, dim3(kWave, kAggRows), 0, st, a, eptr, inside);
 }
 
 void launch_gather(const Segment* segs, int64_t nseg, const int32_t* halo_idx, const int64_t* halo_ptr,
