@@ -76,7 +76,7 @@ enum { DGC_GATHER_IN_PLACE = 0, DGC_GATHER_STAGED = 1 };
  *  AUTO  the split kernels where they are built (S = H, or a transform alone), else the workgroup-tile kernel;
  *  TILE  64 vertices per workgroup, operands shared through LDS, fp32 matrix instructions (any S, H up to 256);
  *  WAVE  the split kernels: 32 vertices per workgroup (16 for narrow layers of few tiles), fp32 products
- *        as sums of bf16 products, for S = H in {32, 64, 128} (a transform alone: 256, too);
+ *        as sums of half-precision or bf16 products, for S = H in {32, 64, 128} (a transform alone: 256, too);
  *        DGC_ERR_UNSUPPORTED at forward otherwise. */
 enum { DGC_DENSE_AUTO = 0, DGC_DENSE_TILE = 1, DGC_DENSE_WAVE = 2 };
 /* Which kernels aggregate in IN_PLACE mode (STAGED always takes WALK):
