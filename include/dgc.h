@@ -240,8 +240,8 @@ dgc_status_t dgc_layer_set_presence(dgc_layer_t* layer, const uint8_t* present, 
  *     NULL): H0 is then the stale-state cache, [n_state * T*N, H], cell rows after all hidden rows;
  *   HN (optional, same shape): row t*N + i receives the state after step t wherever the next step
  *     belongs to another chunk (t = T-1 or labels[t+1,i] != labels[t,i]); other rows are not written.
- * reset_mask must be NULL.  May be called again with other labels; `labels` is only read during
- * the call, until dgc_layer_set_presence has been called on the layer (then DGC_ERR_STATE: labels
+ * reset_mask must be NULL.  May be called again with other labels (passes recorded into a HIP graph since the first
+ * call then run with these); `labels` is only read during the call, until dgc_layer_set_presence has been called on the layer (then DGC_ERR_STATE: labels
  * come first).  The packing arrays of the chunk-fusion packing and dgc_layer_shared_rows keep
  * describing the single rectangular chunk.  Synchronises `stream`. */
 dgc_status_t dgc_layer_set_labels(dgc_layer_t* layer, const int32_t* labels, void* stream);
@@ -264,7 +264,10 @@ dgc_status_t dgc_layer_set_labels(dgc_layer_t* layer, const int32_t* labels, voi
  *          own chunk that store it as a neighbour), other rows and the pitch padding are left
  *          alone.  DGC_STRUCT_EVOLVE_GCN_O: computing it uses up the aggregated rows the layer
  *          kept, so a further backward needs a forward first (DGC_ERR_STATE); the first such
- *          call allocates T*N*F floats of workspace.  DGC_STRUCT_GAT: bfloat16, lddx a multiple
+ *          call allocates T*N*F floats of workspace and, where memory is left for it, a table of 8
+ *          bytes per non-zero inside a chunk (a layer with labels: per non-zero and per row; the later
+ *          of this call and the first dgc_layer_set_labels allocates it).  A layer of several chunks
+ *          holds 8 bytes per row for the table since its creation.  DGC_STRUCT_GAT: bfloat16, lddx a multiple
  *          of 8; one more product per row on top of the parameter gradients.
  * The cache is a constant: no gradient flows into C.  Gradients are read with
  * dgc_layer_get_param(layer, "<name>.grad", ...).  Enqueues work only. */

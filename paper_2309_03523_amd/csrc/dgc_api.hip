@@ -91,11 +91,17 @@ struct dgc_layer {
   float* d_dM = nullptr;                         // [T*N][F] gradient of the aggregated rows
   AggItem* d_agg_items = nullptr;            // of the edge-table kernels
   int64_t n_agg_items = 0;
-  // Table of the neighbours of a row's own chunk, which are all that hand a gradient to it: where each row's begin, how many there are
-  int64_t* d_inside_ptr = nullptr; int64_t n_inside = 0;
-  bool all_inside() const { return d_inside_ptr && n_inside == total_nnz; }     // the rows' table is that of their own chunks
+  // Table of the neighbours of a row's own chunk, which are all that hand a gradient to it: where each row's begin, and their entries.
+  // Where there is none (all neighbours are inside, no labels yet, no memory for it) the gradient reads d_etab and leaves out what is
+  // marked there.  A pass that is recorded in either form stays right when other labels are set: both tables keep their places, and
+  // dgc_layer_set_labels fills both anew before it returns.
+  bool takes_labels() const {
+    return n_chunks == 1 && chunks[0].v_lo == 0 && chunks[0].v_hi == N && chunks[0].t_lo == 0 && chunks[0].t_hi == T;
+  }
+  int64_t n_inside = -1;                         // of chunks that stay what they are; -1: not counted
+  int64_t* d_inside_ptr = nullptr;
   int2* d_inside = nullptr;
-  int2* inside_room = nullptr; int64_t n_inside_room = 0;      // memory for it behind d_dM
+  int64_t* d_inside_tmp = nullptr;               // labels: of the scan
   int64_t* d_rowidx = nullptr;                   // [total rows] packed row -> t*N + v
   float4* d_Wt_plain = nullptr;                  // every W_t as (out = F, in = S) fragments
   bool m_saved = false;                          // d_M holds the aggregated rows of the last forward
@@ -343,15 +349,26 @@ SpmmArgs spmm_args(dgc_layer* L, const float* fresh, int64_t ld_fresh, const flo
   return a;
 }
 
-// aggregation of one GCN layer, with or without the staged gather
-// Where the entries of each row's neighbours of its own chunk begin, and how many there are in all (waits for the stream).
+// Where the entries of each row's neighbours of its own chunk begin; *total: how many there are in all.
 hipError_t count_inside(dgc_layer* L, int64_t* tmp, int64_t* total, hipStream_t st) {
-  hipError_t e = hipMemsetAsync(L->d_inside_ptr + L->total_rows, 0, sizeof(int64_t), st);
+  const hipError_t e = hipMemsetAsync(L->d_inside_ptr + L->total_rows, 0, sizeof(int64_t), st);
   if (e != hipSuccess) return e;
   launch_inside(spmm_args(L, nullptr, 0, nullptr, 0, L->desc.F, nullptr, 0), L->d_inside_ptr, nullptr, st);
   launch_exclusive_scan(L->d_inside_ptr, L->total_rows + 1, tmp, total, st);
-  if ((e = hipMemcpyAsync(&L->n_inside, total, sizeof(int64_t), hipMemcpyDeviceToHost, st)) != hipSuccess) return e;
-  return hipStreamSynchronize(st);
+  return hipSuccess;
+}
+void fill_inside(dgc_layer* L, hipStream_t st) {
+  launch_inside(spmm_args(L, nullptr, 0, nullptr, 0, L->desc.F, nullptr, 0), L->d_inside_ptr, L->d_inside, st);
+}
+// The table of a layer's labels, with room for any: allocated once, or not at all if there is no memory for it.
+hipError_t label_table(dgc_layer* L, hipStream_t st) {
+  const int64_t tmp = scan_tmp_elems(L->total_rows + 1);
+  if (!L->d_etab || (!L->d_inside && dev_alloc_all(L, Wanted<int64_t>{&L->d_inside_ptr, L->total_rows + 1}, Wanted<int64_t>{&L->d_inside_tmp, tmp + 1},
+                                                   Wanted<int2>{&L->d_inside, L->total_nnz + kEtabPad}) != hipSuccess))
+    return hipSuccess;
+  const hipError_t e = count_inside(L, L->d_inside_tmp, L->d_inside_tmp + tmp, st);
+  if (e == hipSuccess) fill_inside(L, st);
+  return e;
 }
 
 // Row groups of the edge-table kernels, in the order of their snapshots.
@@ -741,9 +758,11 @@ dgc_status_t build_layer(dgc_layer* L, const dgc_graph_t* graph, hipStream_t st)
     launch_edge_table(g, L->d_segs, L->nseg, L->total_nnz, L->d_dinv, nullptr, L->d_etab, st);
   }
 
-  if (L->d_etab && d.struct_kind == DGC_STRUCT_EVOLVE_GCN_O) {
+  if (L->d_etab && d.struct_kind == DGC_STRUCT_EVOLVE_GCN_O && !L->takes_labels()) {
     DGC_HIP_TRY(dev_alloc(L, &L->d_inside_ptr, L->total_rows + 1));
     DGC_HIP_TRY(count_inside(L, d_tmp, d_total, st));
+    DGC_HIP_TRY(hipMemcpyAsync(&L->n_inside, d_total, sizeof(int64_t), hipMemcpyDeviceToHost, st));
+    DGC_HIP_TRY(hipStreamSynchronize(st));
   }
 
   // dense tiles: 64 consecutive vertices of a chunk
@@ -852,6 +871,7 @@ dgc_status_t check_tensor(const Failer& fail, const char* name, const void* p, i
   return DGC_OK;
 }
 
+// aggregation of one GCN layer, with or without the staged gather
 void run_aggregate(dgc_layer* L, const float* fresh, int64_t ld_fresh, const float* stale, int64_t ld_stale,
                    int32_t F, float* M, int64_t ldm, hipStream_t st, const int64_t* row_map = nullptr) {
   SpmmArgs a = spmm_args(L, fresh, ld_fresh, stale, ld_stale, F, M, ldm);
@@ -1367,19 +1387,21 @@ static dgc_status_t prepare_dx(dgc_layer* L, hipStream_t st) {
     return fail(DGC_ERR_UNSUPPORTED, "input gradient: more than 65535 chunks or snapshots per window");
   if (!L->d_dM) {
     const int64_t wt = (int64_t)L->T * evolve_packed_bytes(L->evo, L->evo.split) / (int64_t)sizeof(float4);
-    // (the table of neighbours behind dM: an allocation takes longer than filling it)
-    const int64_t dm = ((int64_t)L->T * L->N * d.F + 1) / 2 * 2, table = L->d_etab && !L->all_inside() ? L->n_inside + kEtabPad : 0;
-    DGC_HIP_TRY(dev_alloc_all(L, Wanted<float>{&L->d_dM, dm + 2 * table}, Wanted<int64_t>{&L->d_rowidx, L->total_rows},
-                              Wanted<float4>{&L->d_Wt_plain, wt}));
-    L->inside_room = reinterpret_cast<int2*>(L->d_dM + dm);
-    L->n_inside_room = table;
+    // (the table of neighbours behind dM: an allocation takes longer than filling it.  Without the room for it the pass reads d_etab.)
+    const int64_t dm = ((int64_t)L->T * L->N * d.F + 1) / 2 * 2;
+    const bool some = L->n_inside >= 0 && L->n_inside < L->total_nnz;
+    auto room = [&](int64_t entries) {
+      return dev_alloc_all(L, Wanted<float>{&L->d_dM, dm + 2 * entries}, Wanted<int64_t>{&L->d_rowidx, L->total_rows},
+                           Wanted<float4>{&L->d_Wt_plain, wt});
+    };
+    const bool table = some && room(L->n_inside + kEtabPad) == hipSuccess;
+    if (!table) DGC_HIP_TRY(room(0));
     evolve_row_index(L->d_chunks, L->n_chunks, max_nv, max_w, L->N, L->d_rowidx, st);
-  }
-  if (L->d_etab && !L->d_inside && !L->all_inside()) {
-    int2* inside = L->inside_room;
-    if (L->n_inside + kEtabPad > L->n_inside_room) DGC_HIP_TRY(dev_alloc(L, &inside, L->n_inside + kEtabPad));
-    launch_inside(spmm_args(L, L->d_dM, d.F, L->d_dM, d.F, d.F, L->d_dM, d.F), L->d_inside_ptr, inside, st);
-    L->d_inside = inside;
+    if (table) {
+      L->d_inside = reinterpret_cast<int2*>(L->d_dM + dm);
+      fill_inside(L, st);
+    }
+    if (L->lab.built) DGC_HIP_TRY(label_table(L, st));
   }
   return DGC_OK;
 }
@@ -1470,7 +1492,7 @@ dgc_status_t dgc_layer_backward(dgc_layer_t* L, const void* Yv, int64_t ldy, con
     SpmmArgs sa = spmm_args(L, L->d_dM, d.F, L->d_dM, d.F, d.F, static_cast<float*>(dX), d.F);
     sa.ld_out = lddx;
     sa.row_map = L->d_rowidx;
-    sa.skip_stale = !L->d_etab || !L->all_inside();
+    sa.skip_stale = L->n_inside != L->total_nnz;
     if (L->d_inside) {
       sa.etab = L->d_inside; sa.eptr = L->d_inside_ptr;
     }
@@ -1613,8 +1635,7 @@ dgc_status_t dgc_layer_set_labels(dgc_layer_t* L, const int32_t* labels, void* s
   if (d.gather_mode != DGC_GATHER_IN_PLACE)
     return fail(DGC_ERR_UNSUPPORTED, "generated chunks need gather_mode DGC_GATHER_IN_PLACE");
   if (L->tf.built) return fail(DGC_ERR_STATE, "the labels of a layer are set before its presence mask, and not again after it");
-  const dgc_chunk_t& c = L->chunks[0];
-  if (L->n_chunks != 1 || c.v_lo != 0 || c.v_hi != L->N || c.t_lo != 0 || c.t_hi != L->T)
+  if (!L->takes_labels())
     return fail(DGC_ERR_STATE, "labels need a layer created with the single chunk [0,N) x [0,T)");
   if ((int64_t)L->T * L->N >= INT32_MAX) return fail(DGC_ERR_UNSUPPORTED, "generated chunks need T*N < 2^31");
   if (L->T > kMaxGridYZ) return fail(DGC_ERR_UNSUPPORTED, "generated chunks: more than 65535 snapshots");
@@ -1628,18 +1649,7 @@ dgc_status_t dgc_layer_set_labels(dgc_layer_t* L, const int32_t* labels, void* s
   labels_build(L->graph_dev(), L->d_segs, labels, lab.col_signed, lab.seq_in, lab.seq_out, st);
   if (L->d_etab)      // the aggregation's table follows the labels: marked columns instead of the range test
     launch_edge_table(L->graph_dev(), L->d_segs, L->nseg, L->total_nnz, L->d_dinv, lab.col_signed, L->d_etab, st);
-  if (L->d_inside_ptr) {
-    if (L->d_inside) {          // of other labels
-      DGC_HIP_TRY(hipDeviceSynchronize());
-      if (L->d_inside != L->inside_room) dev_free(L, L->d_inside);
-      L->d_inside = nullptr;
-    }
-    int64_t* tmp = nullptr;
-    DGC_HIP_TRY(dev_alloc(L, &tmp, scan_tmp_elems(L->total_rows + 1) + 1));
-    const hipError_t e = count_inside(L, tmp, tmp + scan_tmp_elems(L->total_rows + 1), st);
-    dev_free(L, tmp);
-    DGC_HIP_TRY(e);
-  }
+  if (L->d_dM) DGC_HIP_TRY(label_table(L, st));
   DGC_HIP_TRY(hipStreamSynchronize(st));
   DGC_HIP_TRY(hipGetLastError());
   lab.built = true;

@@ -379,16 +379,17 @@ __device__ __forceinline__ int of_lane(int v) {      // lane U of each LPR
   return __builtin_amdgcn_ds_swizzle(v, (U << 5) | (0x20 - LPR));
 }
 
-template <int LPR>
+// SKIP: neighbours that are marked stale add nothing.
+template <int LPR, bool SKIP>
 struct AggGather {
   gbyte *fresh, *stale;      // this lane's 16 bytes of row 0
   uint32_t ld_bytes;
   template <int U>
   __device__ __forceinline__ void one(int2 e, int n, float4& v, float& w) const {
     const int col = of_lane<LPR, U>(e.x), b = of_lane<LPR, U>(e.y);
-    gbyte* const base = col >= 0 ? fresh : stale;
+    gbyte* const base = SKIP || col >= 0 ? fresh : stale;
     gbyte* const at = base + (uint64_t)(uint32_t)(col ^ (col >> 31)) * ld_bytes;
-    v = __builtin_bit_cast(float4, load16(U < n ? at : in_global(&agg_zero)));
+    v = __builtin_bit_cast(float4, load16(U < n && (!SKIP || col >= 0) ? at : in_global(&agg_zero)));
     w = __int_as_float(b);
   }
   // the n (of at most eight) non-zeros whose entries the lanes hold
@@ -425,8 +426,8 @@ __device__ __forceinline__ void agg_store(const SpmmArgs& a, float* out, int fi,
 }
 
 // The sum over [from, end), a share for every lane group; every group ends with all of it.
-template <int LPR>
-__device__ __forceinline__ void agg_shared(const AggGather<LPR>& rows, const int2* tab, int from, int end, float (&sum)[4]) {
+template <int LPR, bool SKIP>
+__device__ __forceinline__ void agg_shared(const AggGather<LPR, SKIP>& rows, const int2* tab, int from, int end, float (&sum)[4]) {
   constexpr int kBatch = 8 * (64 / LPR);
   const int g8 = from + 8 * ((threadIdx.x & 63) / LPR);
   float acc[2][4] = {};
@@ -449,7 +450,7 @@ __device__ __forceinline__ void agg_shared(const AggGather<LPR>& rows, const int
 }
 
 // A wave's slice: columns fi .. +3 of this lane; stored up to column c1.
-template <int LPR>
+template <int LPR, bool SKIP>
 struct AggSlice {
   int fi, c1, c0;
   __device__ __forceinline__ AggSlice(const SpmmArgs& a, int slice) {
@@ -457,9 +458,9 @@ struct AggSlice {
     fi = c0 + 4 * ((threadIdx.x & 63) % LPR);
     c1 = c0 + 4 * LPR < a.F ? c0 + 4 * LPR : (int)a.ldm;
   }
-  __device__ __forceinline__ AggGather<LPR> of(const SpmmArgs& a, int t) const {
+  __device__ __forceinline__ AggGather<LPR, SKIP> of(const SpmmArgs& a, int t) const {
     const int64_t col = (int64_t)t * a.g.N * a.ld_fresh + (fi < a.F ? fi : c0);     // lanes past the row's end re-read its first columns (never stored)
-    return AggGather<LPR>{in_global(a.fresh + col), in_global(a.stale + col), (uint32_t)(a.ld_fresh * sizeof(float))};
+    return AggGather<LPR, SKIP>{in_global(a.fresh + col), in_global(a.stale + col), (uint32_t)(a.ld_fresh * sizeof(float))};
   }
 };
 
@@ -496,8 +497,8 @@ __device__ __forceinline__ bool agg_part(const SpmmArgs& a, int64_t item, TeamRo
 }
 
 // The rows of an item.  TEAM: those of more than kShared<LPR> non-zeros are left in `queue`.
-template <int LPR, bool TEAM>
-__device__ __forceinline__ void agg_rows(const SpmmArgs& a, const AggSlice<LPR>& slice, int64_t item, AggRow* list, TeamRow* queue, int* queued) {
+template <int LPR, bool SKIP, bool TEAM>
+__device__ __forceinline__ void agg_rows(const SpmmArgs& a, const AggSlice<LPR, SKIP>& slice, int64_t item, AggRow* list, TeamRow* queue, int* queued) {
   constexpr int G = 64 / LPR;
   const int lane = threadIdx.x & (kWave - 1), g = lane / LPR, l = lane % LPR;
   if (item >= a.n_items) {
@@ -514,7 +515,7 @@ __device__ __forceinline__ void agg_rows(const SpmmArgs& a, const AggSlice<LPR>&
   const int start = (int)(ptr - first), end = __shfl(start, after);
   const int64_t full = __shfl((long long)stored, after) - stored;
   const int2* const tab = a.etab + first;
-  const AggGather<LPR> from = slice.of(a, t);
+  const AggGather<LPR, SKIP> from = slice.of(a, t);
   const int64_t ldo = a.ld_out ? a.ld_out : a.ldm;
   int64_t orow = -1;
   float scale = 0.f;
@@ -539,7 +540,7 @@ __device__ __forceinline__ void agg_rows(const SpmmArgs& a, const AggSlice<LPR>&
     const int r = __builtin_ctzll(shared);
     shared &= shared - 1;
     float sum[4];
-    agg_shared<LPR>(from, tab, __builtin_amdgcn_readlane(start, r), __builtin_amdgcn_readlane(end, r), sum);
+    agg_shared<LPR, SKIP>(from, tab, __builtin_amdgcn_readlane(start, r), __builtin_amdgcn_readlane(end, r), sum);
     if (g == 0)
       agg_store<LPR>(a, a.M + readlane64(orow, r) * ldo, slice.fi, slice.c1, sum, __int_as_float(__builtin_amdgcn_readlane(__float_as_int(scale), r)));
   }
@@ -585,20 +586,20 @@ __device__ __forceinline__ void agg_rows(const SpmmArgs& a, const AggSlice<LPR>&
 
 // One launch for parts and rows, the parts first: one of them is the longest work there is, and on a small graph
 // a launch of its own waits for one.  A wave a part, a wave an item; ns slices of each.
-template <int LPR>
+template <int LPR, bool SKIP>
 __global__ __launch_bounds__(256) void k_agg(SpmmArgs a, int ns, int64_t part_blocks) {
   __shared__ AggRow list[kTeam][kAggRows];
   const int wave = uniform(threadIdx.x / kWave);
   const bool part = blockIdx.x < part_blocks;
   const int64_t place = (blockIdx.x - (part ? 0 : part_blocks)) * kTeam + wave, item = place / ns;
-  const AggSlice<LPR> slice(a, (int)(place - item * ns));
+  const AggSlice<LPR, SKIP> slice(a, (int)(place - item * ns));
   if (!part) {
-    agg_rows<LPR, false>(a, slice, item, list[wave], nullptr, nullptr);
+    agg_rows<LPR, SKIP, false>(a, slice, item, list[wave], nullptr, nullptr);
   } else if (item < a.n_long) {
     TeamRow p;
     if (!agg_part(a, item, &p)) return;
     float sum[4];
-    agg_shared<LPR>(slice.of(a, p.t), a.etab + p.e, 0, p.nnz, sum);
+    agg_shared<LPR, SKIP>(slice.of(a, p.t), a.etab + p.e, 0, p.nnz, sum);
     if ((threadIdx.x & (kWave - 1)) < LPR) agg_store<LPR>(a, a.partial + item * a.ldm, slice.fi, slice.c1, sum, 1.0f);
   }
 }
@@ -606,7 +607,7 @@ __global__ __launch_bounds__(256) void k_agg(SpmmArgs a, int ns, int64_t part_bl
 // The same where there are rows long enough to be shared: on a graph that does not fill the chip for long the longest row is
 // what the launch waits for (1024 non-zeros are 32 batches of gathers, each waited for), so the four waves of a workgroup share a
 // part, and the longer rows of their four items once they have done the shorter ones.  A row's quarters are added in wave order.
-template <int LPR>
+template <int LPR, bool SKIP>
 __global__ __launch_bounds__(256) void k_agg_team(SpmmArgs a, int ns, int64_t part_blocks) {
   __shared__ AggRow list[kTeam][kAggRows];
   __shared__ TeamRow queue[kTeam][kAggRows];
@@ -616,7 +617,7 @@ __global__ __launch_bounds__(256) void k_agg_team(SpmmArgs a, int ns, int64_t pa
   const int g = lane / LPR, l = lane % LPR;
   const bool part = blockIdx.x < part_blocks;
   const int64_t block = blockIdx.x - (part ? 0 : part_blocks), four = block / ns;
-  const AggSlice<LPR> slice(a, (int)(block - four * ns));
+  const AggSlice<LPR, SKIP> slice(a, (int)(block - four * ns));
   if (part) {
     TeamRow p;
     const bool there = wave == 0 && agg_part(a, four, &p);
@@ -625,7 +626,7 @@ __global__ __launch_bounds__(256) void k_agg_team(SpmmArgs a, int ns, int64_t pa
       if (there) queue[0][0] = p;
     }
   } else {
-    agg_rows<LPR, true>(a, slice, four * kTeam + wave, list[wave], queue[wave], queued + wave);
+    agg_rows<LPR, SKIP, true>(a, slice, four * kTeam + wave, list[wave], queue[wave], queued + wave);
   }
   __syncthreads();
   float* const out = part ? a.partial : a.M;
@@ -636,7 +637,7 @@ __global__ __launch_bounds__(256) void k_agg_team(SpmmArgs a, int ns, int64_t pa
       const TeamRow row = queue[from][i];
       const int nnz = uniform(row.nnz), quarter = (nnz + kTeam - 1) / kTeam, e0 = min(wave * quarter, nnz);
       float part_sum[4];
-      agg_shared<LPR>(slice.of(a, uniform(row.t)), a.etab + row.e, e0, min(e0 + quarter, nnz), part_sum);
+      agg_shared<LPR, SKIP>(slice.of(a, uniform(row.t)), a.etab + row.e, e0, min(e0 + quarter, nnz), part_sum);
       if (g == 0) sums[turn & 1][wave][l] = make_float4(part_sum[0], part_sum[1], part_sum[2], part_sum[3]);
       __syncthreads();       // (the next row's sums go to the other buffer)
       if (wave == (turn & (kTeam - 1)) && g == 0) {
@@ -652,7 +653,7 @@ __global__ __launch_bounds__(256) void k_agg_team(SpmmArgs a, int ns, int64_t pa
 // wait for (12 345 x 10 rows of 50 floats 59 -> 51 us, 3000 x 16 of 64 40 -> 33); where there is more to do, waves of one item's slices side by side
 // are the faster ones (62 500 x 64 rows of 256 6.74 ms, 7.33 with the team; 20 000 x 8 of 300 374 us and 404).  And parts shorter than a
 // shared row are a workgroup's only while the chip holds all of them at once.
-template <int LPR>
+template <int LPR, bool SKIP>
 void launch_agg(SpmmArgs a, hipStream_t st) {
   // Outputs of the size of the L2s are still there when the next kernel reads them; larger ones are streamed past the rows that are
   // read again (8 x 1000 rows of 32 floats: a forward of 19.1 us takes 18.3, 10 x 12 345 of 50 95 and 92; 64 x 62 500 of 256, kept: 22.26 ms
@@ -662,12 +663,13 @@ void launch_agg(SpmmArgs a, hipStream_t st) {
   const bool team = a.longest_row > kShared<LPR> && a.n_items * ns <= few && a.n_long * ns <= (a.part_nnz > kShared<LPR> ? few : kTeamsAtOnce);
   const int64_t parts = team ? a.n_long * ns : (a.n_long * ns + kTeam - 1) / kTeam;
   const int64_t rows = team ? (a.n_items + kTeam - 1) / kTeam * ns : (a.n_items * ns + kTeam - 1) / kTeam;
-  if (parts + rows > 0) hipLaunchKernelGGL(team ? k_agg_team<LPR> : k_agg<LPR>, (unsigned)(parts + rows), 256, 0, st, a, (int)ns, parts);
+  if (parts + rows > 0) hipLaunchKernelGGL((team ? k_agg_team<LPR, SKIP> : k_agg<LPR, SKIP>), (unsigned)(parts + rows), 256, 0, st, a, (int)ns, parts);
 }
 
 void launch_agg_all(const SpmmArgs& a, hipStream_t st) {
-  if (a.F <= 32) launch_agg<8>(a, st);
-  else launch_agg<16>(a, st);
+  const bool skip = a.skip_stale && !a.eptr;       // (a table of a row's own chunk has none to leave out)
+  if (a.F <= 32) skip ? launch_agg<8, true>(a, st) : launch_agg<8, false>(a, st);
+  else skip ? launch_agg<16, true>(a, st) : launch_agg<16, false>(a, st);
   const unsigned gl = (unsigned)((a.n_long + 3) / 4);
   if (!gl) return;
   if (a.ldm <= 64) hipLaunchKernelGGL((k_spmm_long_reduce<1>), gl, 256, 0, st, a);
@@ -763,7 +765,7 @@ void launch_edge_table(const GraphDev& g, const Segment* segs, int64_t nseg, int
 
 void launch_spmm(const SpmmArgs& a, hipStream_t st) {
   // the edge-table kernels: rows read in place, one pitch for both sources
-  if (a.etab && !a.halo && a.ld_fresh == a.ld_stale && a.ld_fresh * 4 < (int64_t(1) << 31) && (!a.skip_stale || a.eptr)) {
+  if (a.etab && !a.halo && a.ld_fresh == a.ld_stale && a.ld_fresh * 4 < (int64_t(1) << 31)) {
     launch_agg_all(a, st);
     return;
   }

@@ -129,6 +129,68 @@ def test_input_gradient_after_other_labels():
     dw.layer.destroy()
 
 
+@pytest.mark.parametrize("first,recorded", [(None, None), (None, 9), (4, 2), (4, None)])
+def test_recorded_training_step_after_other_labels(first, recorded):
+    """A step with input gradient that is recorded into a graph (classes of labels before the first eager step and before the recording), and replayed with labels that have more
+    and fewer neighbours in a chunk: every replay against an eager step of the same labels, and both against the oracle."""
+    import torch
+    from paper_2309_03523_amd.runner import DeviceWorkload
+    T, N, F = 3, 300, 64
+    wl = synth.random_small(13, T, N, F, F, F, 6.0, [[0, N, 0, T]], "none", hub=True)
+    wl.params = synth.evolve_params(13, F, F, random_bias=True)
+    target = synth.stream(F, "target").standard_normal((T, N, F)).astype(np.float32)
+    dw = DeviceWorkload(wl, struct_kind="evolve_gcn_o", act_out="relu", long_nnz=30, part_nnz=11)
+    on_device, dX = torch.from_numpy(target).cuda(), torch.zeros((T, N, F), device="cuda")
+    rng = np.random.default_rng(7)
+
+    def labels(classes):
+        lab = rng.integers(0, classes, (T, N))
+        dw.layer.set_labels(torch.from_numpy(lab.astype(np.int32).reshape(-1)).cuda())
+        return lab
+
+    def step():
+        dw.layer.forward(dw.X, dw.C, dw.Y)
+        dw.layer.backward(dw.Y, target=on_device, dX=dX)
+
+    def results():
+        torch.cuda.synchronize()
+        grads = {n: dw.layer.get_param(n + ".grad", wl.params[n].shape) for n in oracle.EVOLVE_PARAMS}
+        return dict(grads, Y=dw.Y.cpu().numpy(), dX=dX.cpu().numpy())
+
+    side = torch.cuda.Stream()
+    if first:
+        labels(first)
+    torch.cuda.synchronize()
+    with torch.cuda.stream(side):
+        step()
+    torch.cuda.synchronize()
+    if recorded:
+        labels(recorded)                       # no eager step between the labels and the recording
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=side):
+        step()
+    for classes, eager_first in ((5, False), (1, False), (30, True), (2, True)):
+        lab = labels(classes)
+        if eager_first:
+            step()
+            eager = results()
+        for t in (dw.Y, dX):
+            t.fill_(float("nan"))
+        graph.replay()
+        got = results()
+        if not eager_first:
+            step()
+            eager = results()
+        for k in eager:
+            if k == "dX" and not (first or recorded):      # recorded without labels: the same products, added in another order
+                assert np.linalg.norm(got[k] - eager[k]) < 1e-6 * np.linalg.norm(eager[k]), classes
+            else:
+                np.testing.assert_array_equal(got[k], eager[k], err_msg=f"{classes} classes: {k}")
+        want = labelled.evolve(wl.graph, lab, wl.params, wl.X, wl.C, target, want_dx=True)
+        assert rel_err(got["Y"], want["Y"]) < 1e-4 and rel_err(got["dX"], want["dX"]) < 1e-4, classes
+    dw.layer.destroy()
+
+
 @pytest.mark.parametrize("F", [20, 64, 200])
 def test_infinities_stay_infinities(F):
     """Sums with one infinite term are infinite, not NaN, whatever the length of their row and of those beside it."""
