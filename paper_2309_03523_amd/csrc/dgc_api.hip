@@ -382,7 +382,6 @@ dgc_status_t build_agg_items(dgc_layer* L, hipStream_t st) {
     // few rows: fewer a wave, so that more waves share them, down to one a lane group (14 x 1255 of 64 floats: 16, 8, 4 rows a wave take
     // 39, 30, 22 us; 8 x 3000: 35, 28, 28; 16 x 3000: 34, 37, 38)
     while (rows > 4 && L->total_rows * ns / rows < 2560) rows /= 2;
-  while (rows < kAggRows && L->total_rows * ns / rows > 1 << 25) rows = std::min(2 * rows, kAggRows);      // (a launch has at most 2^32 threads)
   std::vector<int64_t> order(segs.size());
   for (size_t s = 0; s < segs.size(); ++s) order[s] = (int64_t)s;
   std::stable_sort(order.begin(), order.end(), [&](int64_t a, int64_t b) { return segs[a].t < segs[b].t; });

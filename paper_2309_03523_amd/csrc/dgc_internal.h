@@ -120,6 +120,9 @@ int64_t shared_rows_mask_words(int32_t T, int64_t N, int32_t n_chunks);
 void launch_shared_rows(const Segment* segs, int64_t nseg, const int64_t* halo_ptr, const int32_t* halo_idx, int32_t T,
                         int64_t N, int32_t n_chunks, unsigned long long* mask, unsigned long long* out, hipStream_t st);
 
+// Blocks of 256 threads in one launch: grids end below 2^32 threads.  What may be more of them goes in several launches.
+constexpr int64_t kMostBlocks = 1 << 23;
+
 // Parts of split rows that a launch gives a workgroup each: grids end at 2^32 threads, and the chip holds 8 workgroups of four waves a CU.
 constexpr int64_t kMostTeams = 1 << 23, kTeamsAtOnce = 2048;
 

@@ -585,13 +585,14 @@ __device__ __forceinline__ void agg_rows(const SpmmArgs& a, const AggSlice<LPR, 
 }
 
 // One launch for parts and rows, the parts first: one of them is the longest work there is, and on a small graph
-// a launch of its own waits for one.  A wave a part, a wave an item; ns slices of each.
+// a launch of its own waits for one.  A wave a part, a wave an item; ns slices of each.  first: the launch's first block of all.
 template <int LPR, bool SKIP>
-__global__ __launch_bounds__(256) void k_agg(SpmmArgs a, int ns, int64_t part_blocks) {
+__global__ __launch_bounds__(256) void k_agg(SpmmArgs a, int ns, int64_t part_blocks, int64_t first) {
   __shared__ AggRow list[kTeam][kAggRows];
   const int wave = uniform(threadIdx.x / kWave);
-  const bool part = blockIdx.x < part_blocks;
-  const int64_t place = (blockIdx.x - (part ? 0 : part_blocks)) * kTeam + wave, item = place / ns;
+  const int64_t block = first + blockIdx.x;
+  const bool part = block < part_blocks;
+  const int64_t place = (block - (part ? 0 : part_blocks)) * kTeam + wave, item = place / ns;
   const AggSlice<LPR, SKIP> slice(a, (int)(place - item * ns));
   if (!part) {
     agg_rows<LPR, SKIP, false>(a, slice, item, list[wave], nullptr, nullptr);
@@ -663,7 +664,12 @@ void launch_agg(SpmmArgs a, hipStream_t st) {
   const bool team = a.longest_row > kShared<LPR> && a.n_items * ns <= few && a.n_long * ns <= (a.part_nnz > kShared<LPR> ? few : kTeamsAtOnce);
   const int64_t parts = team ? a.n_long * ns : (a.n_long * ns + kTeam - 1) / kTeam;
   const int64_t rows = team ? (a.n_items + kTeam - 1) / kTeam * ns : (a.n_items * ns + kTeam - 1) / kTeam;
-  if (parts + rows > 0) hipLaunchKernelGGL((team ? k_agg_team<LPR, SKIP> : k_agg<LPR, SKIP>), (unsigned)(parts + rows), 256, 0, st, a, (int)ns, parts);
+  if (team) {
+    if (parts + rows > 0) hipLaunchKernelGGL((k_agg_team<LPR, SKIP>), (unsigned)(parts + rows), 256, 0, st, a, (int)ns, parts);
+    return;
+  }
+  for (int64_t first = 0; first < parts + rows; first += kMostBlocks)
+    hipLaunchKernelGGL((k_agg<LPR, SKIP>), (unsigned)std::min(kMostBlocks, parts + rows - first), 256, 0, st, a, (int)ns, parts, first);
 }
 
 void launch_agg_all(const SpmmArgs& a, hipStream_t st) {
@@ -681,9 +687,9 @@ void launch_agg_all(const SpmmArgs& a, hipStream_t st) {
 // wave a row: two dependent reads of a few microseconds each, and where a wave took an item's rows one after the other, sixteen
 // times that.
 template <bool FILL>
-__global__ __launch_bounds__(kAggRows * kWave) void k_inside(SpmmArgs a, int64_t* eptr, int2* inside) {
+__global__ __launch_bounds__(kAggRows * kWave) void k_inside(SpmmArgs a, int64_t* eptr, int2* inside, int64_t first) {
   const int lane = threadIdx.x, r = uniform(threadIdx.y);
-  const AggItem it = a.items[blockIdx.x];
+  const AggItem it = a.items[first + blockIdx.x];
   if (r >= it.n) return;
   const int64_t* rp = a.g.rowptr[it.t] + it.v0 + r;
   const int64_t ea = rp[0] + it.base, eb = rp[1] + it.base;
@@ -775,10 +781,12 @@ void launch_spmm(const SpmmArgs& a, hipStream_t st) {
 }
 
 void launch_inside(const SpmmArgs& a, int64_t* eptr, int2* inside, hipStream_t st) {
-  const unsigned blocks = (unsigned)a.n_items;
-  if (!blocks) return;
-  if (inside) hipLaunchKernelGGL(k_inside<true>, blocks, dim3(kWave, kAggRows), 0, st, a, eptr, inside);
-  else hipLaunchKernelGGL(k_inside<false>, blocks, dim3(kWave, kAggRows), 0, st, a, eptr, inside);
+  const int64_t most = kMostBlocks * 256 / (kAggRows * kWave);
+  for (int64_t first = 0; first < a.n_items; first += most) {
+    const unsigned blocks = (unsigned)std::min(most, a.n_items - first);
+    if (inside) hipLaunchKernelGGL(k_inside<true>, blocks, dim3(kWave, kAggRows), 0, st, a, eptr, inside, first);
+    else hipLaunchKernelGGL(k_inside<false>, blocks, dim3(kWave, kAggRows), 0, st, a, eptr, inside, first);
+  }
 }
 
 void launch_gather(const Segment* segs, int64_t nseg, const int32_t* halo_idx, const int64_t* halo_ptr,

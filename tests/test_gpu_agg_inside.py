@@ -212,3 +212,76 @@ def test_infinities_stay_infinities(F):
     got = M.cpu().numpy()[:, :F]
     assert np.isposinf(got[hit]).all() and np.isfinite(got[~hit]).all()
     layer.destroy()
+
+
+def _pairs(N):
+    """Vertices 2k and 2k + 1 are neighbours; the last one of an odd number has none."""
+    import torch
+    i = torch.arange(N, device="cuda")
+    other = torch.where((i ^ 1) < N, i ^ 1, i)
+    n = 1 + (other != i).long()
+    rowptr = torch.zeros(N + 1, dtype=torch.int64, device="cuda")
+    rowptr[1:] = torch.cumsum(n, 0)
+    col = torch.stack([torch.minimum(i, other), torch.maximum(i, other)], 1).reshape(-1)
+    keep = torch.ones(2 * N, dtype=torch.bool, device="cuda")
+    keep[1::2] = n == 2
+    return rowptr, col[keep].to(torch.int32)
+
+
+def test_more_rows_than_a_launch_has_waves():
+    """Groups of one row: the second GCN layer's four slices of each are more waves than a launch can hold."""
+    import torch
+    from paper_2309_03523_amd import binding
+    N, F, S = (1 << 24) + 77, 16, 256
+    rowptr, col = _pairs(N)
+    gen = torch.Generator(device="cuda").manual_seed(3)
+    X = torch.randn((1, N, F), device="cuda", generator=gen)
+    C1 = torch.zeros((1, N, S), device="cuda")
+    layer = binding.DgcLayer([rowptr], [col], N, [(0, N, 0, 1)], F=F, S=S, H=S, time_kind="none", n_struct_layers=2, rows_per_group=1)
+    rng = synth.stream(3, "large")
+    p = {"gcn0.weight": rng.standard_normal((S, F)) / 4, "gcn0.bias": rng.standard_normal(S),
+         "gcn1.weight": rng.standard_normal((S, S)) / 16, "gcn1.bias": rng.standard_normal(S)}
+    p = {k: v.astype(np.float32) for k, v in p.items()}
+    layer.set_params(p)
+    Y = torch.full((1, N, S), float("nan"), device="cuda")
+    layer.forward(X, X, Y, C1=C1)
+    torch.cuda.synchronize()
+    layer.destroy()
+    assert all(bool(torch.isfinite(y).all()) for y in Y[0].split(1 << 20))
+    at = torch.cat([torch.arange(1000), N - 1 - torch.arange(1000), (1 << 23) - 500 + torch.arange(1000), torch.randint(0, N, (4000,))]).cuda()
+    w = {k: torch.from_numpy(v).double().cuda() for k, v in p.items()}
+
+    def first(i):
+        return torch.relu(mean(lambda j: X[0, j].double(), i) @ w["gcn0.weight"].T + w["gcn0.bias"])
+
+    def mean(f, i):
+        other = torch.where((i ^ 1) < N, i ^ 1, i)
+        return 0.5 * (f(i) + f(other))
+
+    want = mean(first, at) @ w["gcn1.weight"].T + w["gcn1.bias"]
+    assert float((Y[0, at].double() - want).norm() / want.norm()) < 1e-6
+
+
+def test_more_rows_than_a_launch_counts_neighbours_of():
+    """The input gradient's table over more groups than one launch counts and fills, against the kernels that walk the columns."""
+    import torch
+    from paper_2309_03523_amd import binding
+    N, F = (1 << 22) + 1001, 32
+    rowptr, col = _pairs(N)
+    gen = torch.Generator(device="cuda").manual_seed(4)
+    X, target = (torch.randn((1, N, F), device="cuda", generator=gen) for _ in range(2))
+    p = synth.evolve_params(4, F, F, random_bias=True)
+    cut = (1 << 21) + 1
+    out = []
+    for kernel in ("walk", "table"):
+        layer = binding.DgcLayer([rowptr], [col], N, [(0, cut, 0, 1), (cut, N, 0, 1)], F=F, S=F, H=F, time_kind="none",
+                                 struct_kind="evolve_gcn_o", act_out="relu", rows_per_group=1, agg_kernel=kernel)
+        layer.set_params(p)
+        Y, dX = torch.zeros((1, N, F), device="cuda"), torch.full((1, N, F), float("nan"), device="cuda")
+        layer.forward(X, X, Y)
+        layer.backward(Y, target=target, dX=dX)
+        torch.cuda.synchronize()
+        layer.destroy()
+        out.append(dX.double())
+    assert bool(torch.isfinite(out[1]).all())
+    assert float((out[0] - out[1]).norm() / out[0].norm()) < 1e-6
