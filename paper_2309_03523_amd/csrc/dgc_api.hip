@@ -379,9 +379,17 @@ dgc_status_t build_agg_items(dgc_layer* L, hipStream_t st) {
   int32_t rows = kAggRows;
   if (L->desc.rows_per_group) rows = std::min(L->desc.rows_per_group, kAggRows);
   else
-    // few rows: fewer a wave, so that more waves share them, down to one a lane group (14 x 1255 of 64 floats: 16, 8, 4 rows a wave take
-    // 39, 30, 22 us; 8 x 3000: 35, 28, 28; 16 x 3000: 34, 37, 38)
-    while (rows > 4 && L->total_rows * ns / rows < 2560) rows /= 2;
+    // few rows: fewer a wave, so that more waves share them (14 x 1255 of 64 floats: 16, 8, 4 rows a wave take 39, 30, 22 us; 8 x 3000: 35, 28, 28;
+    // 16 x 3000: 34, 37, 38; 2 x 3000: 25, 21, 17, and two 16; without long rows, or of 32 floats, two are slower: 8 x 1000 4.7 and 5.6)
+    while (rows > (L->longest_row > 128 && L->desc.F > 32 ? 2 : 4) && L->total_rows * ns / rows < 2560) rows /= 2;
+  // No long rows: there is little to balance between a wave's lane groups, and more waves hide more of the gathers' latency; of a dozen neighbours
+  // and more a row for each lane group (one row a wave -> 16 -> 8 -> 4, us: 8 x 2000 of 256 floats, 33 neighbours 56 -> 73 -> 55 -> 40, 13 neighbours 27
+  // -> 35 -> 30 -> 27; 8 x 4000 of 128, 33: 56 -> 68 -> 56 -> 42; 8 x 10 000 of 256, 33: 364 -> 327 -> 288 -> 258; 16 x 3000 of 256, 5: 43 -> 43 -> 40 ->
+  // 43; 4 x 400 000 of 132, 9: 1368 -> 1406 -> 1429 -> 1536; from a million rows on the three are within 3 %).
+  if (!L->desc.rows_per_group && L->longest_row <= 128 && L->total_rows < 1 << 20) {
+    if (L->total_nnz >= 12 * L->total_rows) rows = std::min(rows, L->desc.F <= 32 ? 8 : 4);
+    else if (L->desc.F > 64 && L->total_rows < 1 << 18) rows = std::min(rows, 8);
+  }
   std::vector<int64_t> order(segs.size());
   for (size_t s = 0; s < segs.size(); ++s) order[s] = (int64_t)s;
   std::stable_sort(order.begin(), order.end(), [&](int64_t a, int64_t b) { return segs[a].t < segs[b].t; });

@@ -55,6 +55,37 @@ def test_table_and_walk(N, T, F, pitch, rows, long_nnz, part_nnz):
     assert off < 1e-6 and most < 1e-4
 
 
+def _ring(N, reach):
+    """Every vertex with the `reach` before and behind it."""
+    import torch
+    i = torch.arange(N, device="cuda")
+    col = torch.sort((i[:, None] + torch.arange(-reach, reach + 1, device="cuda")) % N, 1)[0]
+    return torch.arange(N + 1, device="cuda") * (2 * reach + 1), col.reshape(-1).to(torch.int32)
+
+
+@pytest.mark.parametrize("N,T,F,pitch,reach,long_nnz,part_nnz", [
+    (90001, 3, 193, 200, 2, 0, 0), (90001, 3, 224, 224, 3, 4, 3), (90001, 3, 225, 232, 3, 0, 0),       # two slices of 128 columns; four of 64
+    ((1 << 20) + 3, 1, 132, 132, 8, 0, 0), ((1 << 20) + 3, 1, 176, 176, 8, 0, 0),
+    (3000, 4, 72, 72, 6, 0, 0), (3000, 4, 20, 24, 8, 0, 0)])                                           # a row for each lane group
+def test_wide_slices_and_short_groups(N, T, F, pitch, reach, long_nnz, part_nnz):
+    import torch
+    from paper_2309_03523_amd import binding
+    rowptr, col = _ring(N, reach)
+    gen = torch.Generator(device="cuda").manual_seed(F)
+    X, C = (torch.zeros((T, N, pitch), device="cuda")[:, :, :F].copy_(torch.randn((T, N, F), device="cuda", generator=gen)) for _ in range(2))
+    out = []
+    for kernel in ("walk", "table"):
+        layer = binding.DgcLayer([rowptr] * T, [col] * T, N, [(0, N // 3, 0, T), (N // 3, N, 0, T)], F=F, S=32, H=32, time_kind="none",
+                                 long_nnz=long_nnz, part_nnz=part_nnz, agg_kernel=kernel)
+        M = torch.full((N * T, (F + 7) // 8 * 8), float("nan"), device="cuda")
+        layer.aggregate(X, C, M)
+        torch.cuda.synchronize()
+        out.append(M)
+        layer.destroy()
+    assert bool(torch.isfinite(out[1]).all()) and bool((out[1][:, F:] == 0).all())
+    assert float((out[1] - out[0]).double().norm() / out[0].double().norm()) < 1e-6
+
+
 def test_missing_numbers_stay_where_they_are():
     """NaN in the rows of other chunks' fresh features and in cache rows of the own chunk, which no sum depends on."""
     import torch
