@@ -339,6 +339,7 @@ SpmmArgs spmm_args(dgc_layer* L, const float* fresh, int64_t ld_fresh, const flo
   a.col_signed = L->lab.built ? L->lab.col_signed : nullptr;
   a.F = F;
   a.long_nnz = L->long_nnz; a.part_nnz = L->part_nnz; a.longest_row = L->longest_row;
+  a.n_rows = L->total_rows; a.nnz = L->total_nnz;
   a.partial = L->d_partial;
   a.M = M; a.ldm = ldm;
   a.row_map = nullptr;

@@ -155,6 +155,7 @@ struct SpmmArgs {
   int32_t F;
   int32_t long_nnz, part_nnz;
   int32_t longest_row;        // non-zeros of the longest stored row
+  int64_t n_rows, nnz;        // of all segments
   float* partial;             // [n_long][ldm] scratch for split rows
   float* M; int64_t ldm;      // [rows, ldm]; columns F..ldm-1 are written as zero
   const int64_t* row_map;     // nullptr, or [rows]: row of M that packed row r goes to (< 0: skip the row)

@@ -661,10 +661,10 @@ void launch_agg(SpmmArgs a, hipStream_t st) {
   // becomes 22.48).
   a.keep_out = a.n_items * kAggRows * a.ldm * (int64_t)sizeof(float) <= 64 << 20;
   const int64_t ns = (a.F + 4 * LPR - 1) / (4 * LPR), few = 14 * 1024;
-  const bool team = a.longest_row > kShared<LPR> && a.n_items * ns <= few && a.n_long * ns <= (a.part_nnz > kShared<LPR> ? few : kTeamsAtOnce);
+  const bool team = LPR < 32 && a.longest_row > kShared<LPR> && a.n_items * ns <= few && a.n_long * ns <= (a.part_nnz > kShared<LPR> ? few : kTeamsAtOnce);
   const int64_t parts = team ? a.n_long * ns : (a.n_long * ns + kTeam - 1) / kTeam;
   const int64_t rows = team ? (a.n_items + kTeam - 1) / kTeam * ns : (a.n_items * ns + kTeam - 1) / kTeam;
-  if (team) {
+  if constexpr (LPR < 32) if (team) {
     if (parts + rows > 0) hipLaunchKernelGGL((k_agg_team<LPR, SKIP>), (unsigned)(parts + rows), 256, 0, st, a, (int)ns, parts);
     return;
   }
@@ -672,9 +672,24 @@ void launch_agg(SpmmArgs a, hipStream_t st) {
     hipLaunchKernelGGL((k_agg<LPR, SKIP>), (unsigned)std::min(kMostBlocks, parts + rows - first), 256, 0, st, a, (int)ns, parts, first);
 }
 
+// Two slices of 128 columns instead of three or four of 64, the last of which may hold few: on large graphs (from where no team is
+// wanted), where a row's own cost counts (few neighbours, a narrow fourth slice) or the table's lines do (many neighbours, a narrow third).
+// One wave for all columns -> slices of 64 -> of 128, us.  4 x 400 000 rows of 200 floats, Chung-Lu degrees: 4.5 neighbours a row 1191 -> 1323 ->
+// 1178, 14 2393 -> 2524 -> 2361; of 256: 1253 -> 1360 -> 1226; 16 x 30 000 of 200, 5 neighbours: 367 -> 395 -> 361, of 256, 9: 634 -> 545 -> 591;
+// 16 x 8000 of 200: 98 -> 89 -> 98.  4 x 400 000 of 132, equal degrees: 33 neighbours 4618 -> 4925 -> 4608, 17 2444 -> 2558 -> 2361; of 176: 33
+// 5519 -> 5814 -> 5603; 32 x 40 000 of 160, 17 neighbours: 1462 -> 1316 -> 1351.
+bool wide_slices(const SpmmArgs& a) {
+  if (a.F <= 128 || a.F > 256 || a.n_rows < 1 << 18 || a.skip_stale) return false;
+  const bool hubs = a.longest_row > 1024;
+  if (a.F > 224) return hubs && a.nnz < 8 * a.n_rows;
+  if (a.F > 192) return a.nnz < (hubs ? 16 : 9) * a.n_rows;
+  return a.n_rows >= 1 << 20 && a.nnz >= (a.F <= 160 ? 16 : 24) * a.n_rows;
+}
+
 void launch_agg_all(const SpmmArgs& a, hipStream_t st) {
   const bool skip = a.skip_stale && !a.eptr;       // (a table of a row's own chunk has none to leave out)
   if (a.F <= 32) skip ? launch_agg<8, true>(a, st) : launch_agg<8, false>(a, st);
+  else if (wide_slices(a)) launch_agg<32, false>(a, st);
   else skip ? launch_agg<16, true>(a, st) : launch_agg<16, false>(a, st);
   const unsigned gl = (unsigned)((a.n_long + 3) / 4);
   if (!gl) return;
