@@ -91,3 +91,15 @@ def rel_err(got: np.ndarray, want: np.ndarray, floor: float = 1e-1) -> float:
     tau = floor * float(np.sqrt(np.mean(want * want))) if want.size else 0.0
     den = np.maximum(np.abs(want), max(tau, 1e-300))
     return float(np.max(np.abs(got - want) / den)) if want.size else 0.0
+
+
+def narrow_takes(kind: str, H: int, K0: int, tiles: int, window: int, act: str = "none") -> bool:
+    """Whether the library gives `tiles` tiles of 32 vertices to the narrow time encoder (its own rule, asked where a test wants
+    sizes on either side of it)."""
+    import ctypes as ct
+    import os
+    lib = ct.CDLL(os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))), "paper_2309_03523_amd", "libdgc.so"))
+    fold, narrow = lib._ZN3dgc17dense_fold_wantedEiii, lib._ZN3dgc19dense_narrow_wantedEiibli
+    fold.restype = narrow.restype = ct.c_bool
+    fold.argtypes, narrow.argtypes = [ct.c_int32] * 3, [ct.c_int32, ct.c_int32, ct.c_bool, ct.c_int64, ct.c_int32]
+    return bool(narrow(H, K0, act == "none" and fold(H, K0, {"gru": 1, "lstm": 2}[kind]), tiles, window))

@@ -1,30 +1,34 @@
 """Layers 32 and 64 wide on either side of the sizes where the narrow kernel gives way to the one on halves, and LSTMs 96 and 128
 wide whose transform's folding saves few products; windows of equal length, resets, chunks that leave the last tile part empty.
 The oracle and the bars are those of the narrow kernel's tests and of the folded transform's (4e-7, LSTMs of several steps)."""
-import ctypes as ct
-import os
-
 import numpy as np
 import pytest
 
+from refs import narrow_takes
 from test_gpu_dense_fold import _close, _oracle
 from test_gpu_dense_narrow import _check
 from workloads import synth
 
 pytestmark = pytest.mark.gpu
-LIB = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))), "paper_2309_03523_amd", "libdgc.so")
+
+
+def _most(kind, H, F, window):
+    """The most tiles of 32 vertices, up to 2048, that the narrow kernel takes."""
+    few, many = 2, 2049
+    while many - few > 1:
+        n = (few + many) // 2
+        few, many = (n, many) if narrow_takes(kind, H, F, n, window) else (few, n)
+    return few
 
 
 @pytest.mark.parametrize("over", [0, 1])
-@pytest.mark.parametrize("kind,H,F,window,most", [  # the most tiles of 32 vertices that the narrow kernel takes
-    ("gru", 32, 30, 2, 256), ("lstm", 32, 17, 4, 768), ("gru", 32, 40, 2, 512), ("lstm", 32, 48, 3, 1024),
-    ("gru", 64, 200, 1, 128), ("lstm", 64, 33, 3, 128), ("gru", 64, 64, 6, 384), ("lstm", 64, 70, 4, 384),
-    ("gru", 64, 100, 2, 384), ("lstm", 64, 130, 3, 512), ("gru", 64, 150, 2, 2048)])
-def test_either_side(kind, H, F, window, most, over):
-    wanted = ct.CDLL(LIB)._ZN3dgc19dense_narrow_wantedEiibli
-    wanted.restype, wanted.argtypes = ct.c_bool, [ct.c_int32, ct.c_int32, ct.c_bool, ct.c_int64, ct.c_int32]
-    folds = F <= (32 if H == 32 else 80)
-    assert wanted(H, F, folds, most + over, window) == (over == 0)
+@pytest.mark.parametrize("kind,H,F,window", [
+    ("gru", 32, 30, 2), ("lstm", 32, 17, 4), ("gru", 32, 40, 2), ("lstm", 32, 48, 3),
+    ("gru", 64, 200, 1), ("lstm", 64, 33, 3), ("gru", 64, 64, 6), ("lstm", 64, 70, 4),
+    ("gru", 64, 100, 2), ("lstm", 64, 130, 3), ("gru", 64, 150, 2)])
+def test_either_side(kind, H, F, window, over):
+    most = _most(kind, H, F, window)
+    print(f"{kind} {H} wide, {F} columns, windows of {window}: {most} tiles", flush=True)
     T = 2 * window                             # two windows with half of the tiles each
     first, N = (most + over) // 2, most + over - (most + over) // 2
     N = 32 * N - 9

@@ -8,7 +8,7 @@ import numpy as np
 import pytest
 
 import oracle
-from refs import rel_err
+from refs import narrow_takes, rel_err
 from workloads import synth
 
 pytestmark = pytest.mark.gpu
@@ -53,28 +53,34 @@ def test_input_widths(F, H, kind):
     _check(wl, kind, H, chunks, F + H)
 
 
-# Workgroups that the chip holds at once, and the most tiles of 32 vertices with which the kernel runs for inputs of 20 columns
-# and windows of at most 3 and of 6, where the transform can be folded; where an activation forbids it.
+# Workgroups that the chip holds at once.
 GROUPS = {32: 768, 64: 256}
-LIMIT = {(32, 3): 768, (64, 3): 192, (32, 6): 1024, (64, 6): 256}
-LIMIT_UNFOLDED = {32: 1024, 64: 640}
 
 
-@pytest.mark.parametrize("H,act,N,ranges", [(32, "none", 7000, 48), (32, "none", 24000, 48), (32, "relu", 9000, 48), (32, "relu", 24000, 48),
-                                            (64, "none", 2000, 16), (64, "none", 6000, 48), (64, "relu", 6000, 48), (64, "relu", 24000, 48)])
-@pytest.mark.parametrize("kind", ["gru", "lstm"])
-def test_many_tiles_and_masks(H, act, N, ranges, kind):
-    """More half tiles than workgroups; windows of 1, 2 and 3.  The smaller sizes are this kernel's, the larger ones the other's."""
-    T = 6
+def _uneven_chunks(H, N, ranges):
+    """Ranges cut at random, with windows of 1, 2 and 3; some vertices are not covered in some snapshots."""
     rng = synth.stream(H, "bounds")
     cut = np.concatenate([[0], np.sort(rng.choice(N - 1, ranges - 1, replace=False)) + 1, [N]])
     chunks = []
     for i in range(ranges):
         chunks += [[int(cut[i]), int(cut[i + 1]), t, t + w] for t, w in ([(0, 1), (1, 2), (3, 3)] if i % 2 else [(0, 3), (3, 2), (5, 1)])]
-    chunks = [c for c in chunks if (c[2] + c[0]) % 7]         # some vertices are not covered there
+    chunks = [c for c in chunks if (c[2] + c[0]) % 7]
     size = np.array([c[1] - c[0] for c in chunks])
-    tiles, limit = (-(-size // 32)).sum(), LIMIT[H, 3] if act == "none" else LIMIT_UNFOLDED[H]
-    assert (-(-size // 16)).sum() > GROUPS[H] and (tiles <= limit) == (N < 24000 and (H, act, N) != (64, "none", 6000))
+    return chunks, int((-(-size // 32)).sum()), int((-(-size // 16)).sum()), rng
+
+
+@pytest.mark.parametrize("side", ["narrow", "other"])
+@pytest.mark.parametrize("H,act,ranges", [(32, "none", 48), (32, "relu", 48), (64, "none", 16), (64, "relu", 48)])
+@pytest.mark.parametrize("kind", ["gru", "lstm"])
+def test_many_tiles_and_masks(H, act, ranges, side, kind):
+    """As many vertices as the narrow kernel takes with these windows, more half tiles than workgroups where it takes so many (all
+    but 64 wide without activation); and as few as are the other kernel's."""
+    T = 6
+    takes = {N: narrow_takes(kind, H, 20, _uneven_chunks(H, N, ranges)[1], 3, act) for N in range(500, 24500, 500)}
+    N = max(n for n in takes if takes[n]) if side == "narrow" else min(n for n in takes if not takes[n])
+    chunks, tiles, halves, rng = _uneven_chunks(H, N, ranges)
+    assert halves > GROUPS[H] or (H, act) == (64, "none")
+    print(f"{N} vertices, {tiles} tiles", flush=True)
     wl = synth.random_small(H, T, N, 20, H, H, 2.0, chunks, kind)
     mask = (rng.random((T, N)) < 0.3).astype(np.uint8)
     _check(wl, kind, H, chunks, H, mask, act)
@@ -112,7 +118,7 @@ def test_many_sequences(H, kind, what):
     if what != "labels":
         dw.layer.set_presence(torch.from_numpy(present.astype(np.uint8)).cuda())
     lanes = np.diff(dw.layer.packing("lane_ptr")) if what != "labels" else np.array([N])
-    assert (-(-lanes // 16)).sum() > GROUPS[H] and (-(-lanes // 32)).sum() <= LIMIT[H, 6]
+    assert (-(-lanes // 16)).sum() > GROUPS[H] and narrow_takes(kind, H, F, int((-(-lanes // 32)).sum()), 6)
     HN = torch.full((n_state * off, H), float("nan"), device="cuda")
     dw.Y.fill_(float("nan"))
     dw.layer.forward(dw.X, dw.C, dw.Y, H0=torch.from_numpy(H0).cuda(), HN=HN)
