@@ -149,7 +149,7 @@ def runs_narrow(K0: int, S: int, kind: str, tiles: int, window: int) -> bool:
         return tiles <= 128
     if folds:
         return tiles <= (384 if window >= (4 if K0 > 64 else 6) else 128)
-    return tiles <= (2048 if K0 > 144 else 384 if window == 2 else 512)
+    return tiles <= (2048 if K0 > 128 else 384 if window == 2 else 512)
 
 
 def time_encoder_work(K0: int, S: int, kind: str, tiles: int, window: int, concat: bool = False) -> dict:

@@ -421,7 +421,8 @@ bool dense_narrow_supported(int32_t S, int32_t H, int32_t K0, int32_t time_kind)
 //            folded, 80 columns:  256 tiles w 4 1.07, 384 1.04, 512 0.91
 //            96 columns:          384 tiles w 2 1.05, 512 0.98, w 4 1.02, w 8 1.02, 768 0.89 to 0.95
 //            128 columns:         128 tiles w 1 1.0, 256 0.95; 384 w 2 1.01, w 4 1.10; 512 w 2 0.94, w 4 1.0, w 8 1.02; 768 w 8 0.91
-//            160, 176 columns:    512 tiles w 2 0.95, w 4 0.99, w 8 1.06; 768 w 2 1.07, w 8 1.2; 1024 w 2 1.0, w 8 1.07; 2048 w 2 and w 8 1.07, w 1 1.0
+//            132 to 176 columns:  512 tiles w 2 0.95, w 4 1.0, w 8 1.05; 640 w 2 1.12, w 8 1.33; 768 w 2 1.08, w 8 1.2; 1024 w 2 1.0, w 8 1.06; 2048 w 2
+//                                 and w 8 1.07, w 1 1.0
 //   32 wide, folded, 32 columns:  256 tiles w 1 1.01, w 2 1.1, 512 w 2 0.87, 768 w 4 1.01, w 8 1.07, 1024 w 4 0.94, w 16 0.99; 2048 w 8 0.77
 //            48 columns:          512 tiles w 1 0.98, w 2 1.04, 1024 w 2 0.94, w 4 1.07, w 8 1.1; 2048 w 8 0.91
 //            64 columns:          1024 tiles w 1 0.9, w 2 0.95, w 8 1.1; 2048 w 1 1.01, w 2 1.04, w 8 1.17
@@ -435,7 +436,7 @@ bool dense_narrow_wanted(int32_t H, int32_t K0, bool folds, int64_t n_tiles32, i
   }
   if (window == 1) return n_tiles32 <= 128;
   if (folds) return n_tiles32 <= (window >= (K0 > 64 ? 4 : 6) ? 384 : 128);
-  return n_tiles32 <= (K0 > 144 ? 2048 : window == 2 ? 384 : 512);
+  return n_tiles32 <= (K0 > 128 ? 2048 : window == 2 ? 384 : 512);
 }
 
 bool launch_dense_narrow(const DenseArgs& a, hipStream_t st, std::string* why) {
