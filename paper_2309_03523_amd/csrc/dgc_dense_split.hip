@@ -12,11 +12,18 @@
 //
 // Time encoders: their sums go into sigmoid and tanh, which are at most 1 and off by a rounding of 1, so an error that is small
 // beside 1 does.  There a number is two half-precision numbers (halve8), and a product three MFMAs: hi*lo, lo*hi, hi*hi.  Two
-// halves hold 22 to 24 bits of a number, and nothing below 2^-31 of an input or a state (taken 64 times) and 2^-35 of a weight
-// (1024 times); what is left out, lo*lo, is within 2^-22 of the product and of either sign.  With tanh_of, whose series keeps what
-// 1 - 2 / (1 + e^2x) loses below 1/2, outputs and states are nearer to 64 bits than on six bf16 products and the plain
-// formula: over 46 outputs of drawn cases 0.69 of the distance in the mean, 0.95 at most.  Where an operand is above 1023 (or a weight
-// above 16, all of a matrix below 2^-8, a bias above 1e30) the tile goes on from that step on three bf16 parts.
+// halves hold 22 to 24 bits of a number, and nothing below 2^-31 of an input or a state (taken 64 times) and 2^-37 of a weight
+// (4096 times); what is left out, lo*lo, is within 2^-22 of the product and of either sign.  tanh_of, whose series keeps what
+// 1 - 2 / (1 + e^2x) loses below 1/2, takes back more than that, as long as the sums are of the size of 1.
+// What is not: an input above 1023, a bias above 1e30, and weights whose rows are so long that the 2^-31 counts (kLongestRow): there
+// the tile goes on from that step, which it does again, to its window's end (for weights from the first) on three bf16 parts: a whole forward
+// where all rows are 10 x 12 345, width 64, 85 -> 100 us, 32 x 100 000 of 128 5.0 -> 6.0 ms, MPNN-LSTM 5.3 -> 6.2, LSTM over labels 1.39 -> 1.73,
+// GRU 256 over 300 0.88 -> 1.13, all of them no slower than on six products with the plain formula; where one row in a thousand of the last
+// step is, nothing.
+// Distance from 64 bits in that of six bf16 products with the plain formula, GRU and LSTM 128 and 256 wide over inputs of N(0, 1) times x,
+// weights Xavier times w: x up to 1e-3 0.00 to 0.01 (without biases; with them 0.2 to 0.4), x = 1 0.3 to 1.0, 2 0.3 to 1.26, 5 0.5 to 1.43, 30 0.8
+// to 1.65, 300 1.05 to 1.7 (of 1.5 to 14e-7: 22 bits of 24, lo*lo, one sum for all); w = 4, x = 1 1.13 to 1.39 (of 2.5 to 4.6e-7).  The
+// small products apart or added by link take 0.1 to 0.2 off that and cost 1 to 10 %, lo*lo as well 0.1 and 5 %.
 // GRU 128 wide, 3.2 M rows: 3.5 -> 2.35 ms; the two LSTM layers of MPNN-LSTM over 1.28 M rows 2.78 + 1.99 -> 1.9 + 1.2.
 //
 // With the weights as A operand (lane l: A[l%32][8*(l/32) .. +7]) and 32 activation rows as B operand
@@ -52,10 +59,7 @@ using namespace split;
 constexpr int kUnitBytes = 3 * kFrag * 16; // a weight fragment's three parts
 template <int P> constexpr int kUnit = P * kFrag * 16;    // P parts
 
-// What a matrix's word says of it: a weight is above 16 or not finite; one is at least 2^-8; one is not zero.
-constexpr int32_t kHalfLarge = 1, kHalfFull = 2, kHalfAny = 4;
-constexpr float kHalfLeast = 0x1p-8f, kHalfWeight = 16.f;
-constexpr float kActScale = 64.f, kWeightScale = 1024.f, kSumScale = kActScale * kWeightScale;
+constexpr float kActScale = 64.f, kWeightScale = 4096.f, kSumScale = kActScale * kWeightScale;
 constexpr float kMostBias = 1e30f;
 
 // Of x scale: the gates' arguments come in the scale of their sums.
@@ -91,7 +95,8 @@ __device__ __forceinline__ WeightStream make_stream(const void* p, int64_t bytes
   return w;
 }
 
-// A matrix of `units` fragments as k_pack_split leaves it: three bf16 parts a fragment, two halves a fragment, and a word.
+// A matrix of `units` fragments as k_pack_split leaves it: three bf16 parts a fragment, two halves a fragment, and a word that is not
+// zero where the halves do not stand for the matrix (k_halves_word).
 struct Weights {
   const uint4* parts;
   int units;
@@ -101,8 +106,7 @@ struct Weights {
     return make_stream(parts + (int64_t)units * 3 * kFrag, (int64_t)units * kUnit<2>);
   }
   __device__ __forceinline__ bool halves_good() const {
-    const int32_t w = table_entry(reinterpret_cast<const int32_t*>(parts + (int64_t)units * 5 * kFrag), 0);
-    return !(w & kHalfLarge) && (w & (kHalfFull | kHalfAny)) != kHalfAny;
+    return table_entry(reinterpret_cast<const int32_t*>(parts + (int64_t)units * 5 * kFrag), 0) == 0;
   }
 };
 
@@ -624,8 +628,7 @@ __global__ __launch_bounds__(64 * MAXW, 2) void k_rows_split(DenseArgs a, int kb
 
 // W [n_out][n_in] (strides so, si) -> three bf16 parts per fragment: packed[((jb*nkb + kb)*3 + part)*64 + lane] holds of
 // row jb*32 + lane%32 the columns 16*kb + 8*p + 4*(lane/32) + e (p = 0, 1; e = 0..3), zero beyond n_in.
-// half (or nullptr): behind these, the same as two half-precision parts of 1024 w, and behind them a word that says whether
-// these stand for the weights (Weights::halves_good).
+// half (or nullptr): behind these, the same as two half-precision parts of 4096 w.
 __global__ void k_pack_split(const float* W, int64_t per_w, int64_t so, int64_t si, int32_t n_out, int32_t n_in, int64_t count,
                              uint4* packed, uint4* half) {
   const int nkb = (n_in + 15) / 16;
@@ -650,13 +653,16 @@ __global__ void k_pack_split(const float* W, int64_t per_w, int64_t so, int64_t 
   uint4 two[2];
   halve8(x, kWeightScale, two);
   for (int p = 0; p < 2; ++p) half[(f << 6) * 2 + p * 64 + lane] = two[p];
-  int32_t word = 0;
-  for (int k = 0; k < 8; ++k) {
-    if (!(fabsf(x[k]) <= kHalfWeight)) word |= kHalfLarge;
-    if (fabsf(x[k]) >= kHalfLeast) word |= kHalfFull;
-    if (x[k] != 0.f) word |= kHalfAny;
-  }
-  if (word) atomicOr(reinterpret_cast<int32_t*>(half + 2 * per), word);
+}
+
+// A wave a row: *word is set where a row of W is longer than `most`, or not finite.
+__global__ __launch_bounds__(256) void k_halves_word(const float* W, int32_t n_out, int32_t n_in, float most, int32_t* word) {
+  const int row = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
+  if (row >= n_out) return;
+  float sum = 0.f;
+  for (int k = lane; k < n_in; k += 64) sum = fmaf(W[(int64_t)row * n_in + k], W[(int64_t)row * n_in + k], sum);
+  for (int m = 1; m < 64; m <<= 1) sum += __shfl_xor(sum, m);
+  if (lane == 0 && !(sum <= most * most)) atomicOr(word, 1);
 }
 
 // out[r][k] = sum over s of wih[r][s] wg[s][k], bias[r] = bih[r] + sum over s of wih[r][s] bg[s], both summed in double.
@@ -804,6 +810,11 @@ void launch_pack_split(const float* W, int64_t per_w, int64_t out_stride, int64_
   if (total > 0)
     hipLaunchKernelGGL(k_pack_split, (unsigned)((total + 255) / 256), 256, 0, st, W, per_w, out_stride, in_stride, n_out, n_in,
                        count, p, per_w == 0 ? p + 3 * total : nullptr);
+}
+
+void launch_halves_word(const float* W, int32_t n_out, int32_t n_in, float most, void* packed, hipStream_t st) {
+  int32_t* const word = reinterpret_cast<int32_t*>(static_cast<char*>(packed) + split_halves_bytes(n_out, n_in) - 64);
+  hipLaunchKernelGGL(k_halves_word, (unsigned)((n_out + 3) / 4), 256, 0, st, W, n_out, n_in, most, word);
 }
 
 }  // namespace dgc

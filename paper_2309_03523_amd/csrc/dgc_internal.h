@@ -272,9 +272,14 @@ bool dense_fold_wanted(int32_t S, int32_t K0, int32_t time_kind);   // whether f
 void launch_fold(const float* wih, int64_t ld_wih, const float* wg, const float* bg, const float* bih, int32_t gH, int32_t S, int32_t K0,
                  float* out, float* bias, int32_t* bad, hipStream_t st);
 // `count` matrices, per_w floats apart, element (out, in) at out * out_stride + in * in_stride.  per_w = 0: one matrix, with the
-// half-precision parts (split_halves_bytes; the word behind them is zero before).
+// half-precision parts (split_halves_bytes).
 void launch_pack_split(const float* W, int64_t per_w, int64_t out_stride, int64_t in_stride, int32_t n_out, int32_t n_in,
                        int64_t count, void* packed, hipStream_t st);
+// The word behind the halves (zero before): set where they do not stand for the matrix, since a row of it is longer than `most` (at most
+// 15.9: halves end there).  The error that inputs cut at 2^-31 make of a gate's argument is 2^-32 times the length of the row that they
+// are multiplied with, for a transform's times that of the gate's as well; 1 - 2 / (1 + e^2x) is off by 3e-8.
+constexpr float kLongestRow = 8.f, kLongestFolded = 15.f;
+void launch_halves_word(const float* W, int32_t n_out, int32_t n_in, float most, void* packed, hipStream_t st);
 size_t dense_lds_bytes(int32_t K0, int32_t S, int32_t H);
 int dense_ld(int32_t K0, int32_t S, int32_t H);
 

@@ -95,7 +95,7 @@ def test_many_sequences(H, kind, what):
     import torch
     from oracle import tfusion
     from paper_2309_03523_amd.runner import DeviceWorkload
-    T, F, N = 6, 20, {32: 20000, 64: 6000}[H]
+    T, F, N = 6, 20, {32: 17000, 64: 6000}[H]
     rng = synth.stream(H, "sequences")
     chunks = [[0, N // 3, 0, 6], [N // 3, N, 0, 2], [N // 3, N, 2, 6]] if what == "presence" else [[0, N, 0, T]]
     wl = synth.random_small(H, T, N, F, H, H, 0.0, chunks, kind)
