@@ -1026,9 +1026,7 @@ dgc_status_t dgc_layer_create(const dgc_layer_desc_t* desc, const dgc_graph_t* g
     // least 8192 work items, so that its rows spread over the chip instead of queueing in few waves
     int64_t rows = 0;
     for (int32_t k = 0; k < n_chunks; ++k) rows += (chunks[k].v_hi - chunks[k].v_lo) * (int64_t)(chunks[k].t_hi - chunks[k].t_lo);
-    // (the graph attention takes four rows of a group at a time: 6 x 800 vertices 39.5 us with four and 36.7 with one, 12 x 1500 49.5 and 51)
-    const int32_t least = desc->struct_kind == DGC_STRUCT_GAT && rows >= 8192 ? 4 : 1;
-    while (L->rows_per_group > least && rows / L->rows_per_group < 8192) L->rows_per_group >>= 1;
+    while (L->rows_per_group > 1 && rows / L->rows_per_group < 8192) L->rows_per_group >>= 1;
   }
   if (desc->long_nnz) L->long_nnz = desc->long_nnz;
   if (desc->part_nnz) L->part_nnz = desc->part_nnz;

@@ -14,3 +14,20 @@ pytestmark = pytest.mark.gpu
 ])
 def test_slots(T, N, cut, kw):
     _row_lengths(T, N, cut, kw)
+
+
+@pytest.mark.parametrize("N", [700, 2500, 6000])
+def test_default_groups(N):
+    """The work list is what the header says: groups of 16 rows, halved while there are fewer than 8192 of them."""
+    import oracle
+    from paper_2309_03523_amd.runner import DysatDevice
+    from workloads import synth
+    T = 6
+    wl = synth.dysat_small(5, T, N, 128, 8, 3.0, [[0, N // 3, 0, T], [N // 3, N, 0, T]])
+    rows = 16
+    while rows > 1 and T * N // rows < 8192:
+        rows //= 2
+    dd = DysatDevice(wl)
+    want = oracle.worklist(wl.graph, wl.chunks, rows, 1024, 512)["work_short"]
+    assert dd.layer.packing("work_short").tolist() == [list(x) for x in want]
+    dd.layer.destroy()
