@@ -676,7 +676,7 @@ void dysat_forward(const DysatWs& ws, const void* X, int64_t ldx, const void* C,
   hipLaunchKernelGGL(k_gat_project, (unsigned)std::min<int64_t>(512, (ptiles + 7) / 8), 512, 0, st, pa);
   if (ev) (void)hipEventRecord(ev[1], st);
   GatArgs ga{};
-  ga.g = ws.g; ga.segs = ws.segs; ga.work = ws.work_short; ga.n_work = ws.n_short;
+  ga.g = ws.g; ga.segs = ws.segs; ga.work = ws.work_fwd; ga.n_work = ws.n_fwd;
   ga.work_long = ws.work_long; ga.n_long = ws.n_long; ga.long_nnz = ws.long_nnz; ga.part_nnz = ws.part_nnz;
   ga.long_partial = ws.long_partial;
   ga.zX = ws.zX; ga.zC = ws.zC; ga.sX = ws.sX; ga.sC = ws.sC; ga.U = ws.U; ga.lse = ws.lse;
@@ -684,7 +684,7 @@ void dysat_forward(const DysatWs& ws, const void* X, int64_t ldx, const void* C,
   // neighbours, 0.5 M parts of 32: an inference 0.99 -> 2.03 ms)
   const bool team = ws.longest_row > kShared && ws.n_long <= (ws.part_nnz > kShared ? kMostTeams : kTeamsAtOnce);
   const int64_t long_blocks = team ? ws.n_long : (ws.n_long + kTeam - 1) / kTeam;
-  hipLaunchKernelGGL(team ? k_gat_aggregate_team : k_gat_aggregate, (unsigned)(long_blocks + (ws.n_short + kTeam - 1) / kTeam), 256, 0, st,
+  hipLaunchKernelGGL(team ? k_gat_aggregate_team : k_gat_aggregate, (unsigned)(long_blocks + (ws.n_fwd + kTeam - 1) / kTeam), 256, 0, st,
                      ga, long_blocks);
   if (ws.n_long > 0) hipLaunchKernelGGL(k_gat_aggregate_merge, blocks_for(ws.n_long, 4), 256, 0, st, ga);
   if (ev) (void)hipEventRecord(ev[2], st);
