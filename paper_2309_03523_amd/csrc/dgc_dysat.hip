@@ -396,7 +396,7 @@ __device__ __forceinline__ void gat_short(const GatArgs& a, int64_t item, int la
     const int n = __builtin_amdgcn_readlane(len, r);
     const int32_t* at = col + __builtin_amdgcn_readlane(start, r);
     const SoftAcc sum = gat_row_range(a, s, at, base, a.sX[(base + i0 + r) * 16 + 8 + head], n, lane < n ? at[lane] : 0, lane);
-    gat_row_store(a, base + i0 + r, sum, own_feature(lane), lane < 16 && !(lane & 1), head);
+    gat_row_store(a, base + i0 + r, sum, own_feature(lane), lane < 16 && !(lane & 1), head, n > 0);
   }
   if (listed) gat_slots(a, s, col, base, i0, list, listed, lane);
 }

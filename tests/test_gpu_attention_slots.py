@@ -31,3 +31,28 @@ def test_default_groups(N):
     want = oracle.worklist(wl.graph, wl.chunks, rows, 1024, 512)["work_short"]
     assert dd.layer.packing("work_short").tolist() == [list(x) for x in want]
     dd.layer.destroy()
+
+
+@pytest.mark.parametrize("rows", [1, 3, 4, 8])
+def test_rows_that_store_nothing(rows):
+    """A vertex without so much as a self-loop, which only validate_level = 1 refuses: its row is zero whatever group it is in."""
+    import numpy as np
+    from paper_2309_03523_amd.runner import DysatDevice
+    from workloads import synth
+    T, N = 2, 160
+    wl = synth.dysat_small(8, T, N, 128, 8, 3.0, [[0, 60, 0, T], [60, N, 0, T]])
+    out = []
+    for empty in (False, True):
+        if empty:
+            for s in wl.graph.snaps:          # of a vertex that is its own only neighbour
+                alone = int(np.nonzero(np.diff(s.rowptr) == 1)[0][0])
+                s.col = np.delete(s.col, s.rowptr[alone])
+                s.rowptr[alone + 1:] -= 1
+        dd = DysatDevice(wl, rows_per_group=rows)
+        out.append(dd.forward().float().cpu().numpy())
+        dd.layer.destroy()
+        if not empty:
+            lone = [int(np.nonzero(np.diff(s.rowptr) == 1)[0][0]) for s in wl.graph.snaps]
+    assert np.isfinite(out[1]).all()
+    others = [i for i in range(N) if i not in lone]
+    np.testing.assert_array_equal(out[0][:, others], out[1][:, others])
