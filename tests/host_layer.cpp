@@ -88,6 +88,14 @@ void launch_fold(const float* wih, int64_t, const float* wg, const float* bg, co
 void launch_pack_split(const float* w, int64_t, int64_t, int64_t, int32_t, int32_t, int64_t, void* packed, hipStream_t) {
   launched("pack weight", {w, packed});
 }
+void launch_inside(const SpmmArgs& a, int64_t* eptr, int2* inside, hipStream_t) {
+  launched(inside ? "fill neighbours" : "count neighbours", {a.etab, eptr});
+}
+void launch_exclusive_scan(int64_t* data, int64_t, int64_t* tmp, int64_t* total, hipStream_t) { launched("scan", {data, tmp, total}); }
+int64_t scan_tmp_elems(int64_t) { return 4; }
+void launch_edge_table(const GraphDev&, const Segment*, int64_t, int64_t, const float*, const int32_t*, int2* etab, hipStream_t) {
+  launched("edge table", {etab});
+}
 bool dense_narrow_wanted(int32_t, int32_t, bool, int64_t, int32_t) { return false; }
 void evolve_forward_weights(const EvolveWs&, hipStream_t) { launched("recurrence", {}); }
 bool evolve_backward_dw(const EvolveWs&, const EvolveBwdIn&, bool, hipStream_t, std::string*) { launched("weight gradient", {}); return true; }
@@ -166,6 +174,50 @@ static void label_memory() {
     fails_at = 0;
     expect(dgc_layer_set_labels(L, labels.data(), nullptr) == DGC_OK && count("labels") == 1 && !null_pointer, "with memory it works");
   }
+}
+
+// The input gradient's table of neighbours: without memory for it the gradient is computed without it; a labelled layer's keeps its place
+// and is filled by every set_labels from the first dX on, and only there.
+static void neighbour_table() {
+  static int2 etab[128];
+  static int64_t begins[96];
+  for (int n = 0; n <= 1; ++n) {             // two chunks with neighbours in each other
+    dgc_layer* L = evolve_layer();
+    L->chunks = {dgc_chunk_t{0, 20, 0, 2}, dgc_chunk_t{20, 40, 0, 2}};
+    L->n_chunks = 2;
+    L->d_etab = etab; L->d_inside_ptr = begins; L->n_inside = 60;
+    calls.clear();
+    allocations = 0; fails_at = n;
+    expect(dgc_layer_backward(L, tensor, 32, nullptr, 0, tensor, 32, nullptr, tensor, 32, nullptr) == DGC_OK, "the input gradient is computed");
+    expect(count("fill neighbours") == 1 - n && (L->d_inside != nullptr) == (n == 0) && count("spmm") == 1 && !null_pointer, "with the table if there is memory for it");
+    expect(hipGetLastError() == hipSuccess, "no error is left for a later call");
+    L->m_saved = true;
+    allocations = 0;
+    expect(dgc_layer_backward(L, tensor, 32, nullptr, 0, tensor, 32, nullptr, tensor, 32, nullptr) == DGC_OK && allocations == 0 &&
+           count("fill neighbours") == 1 - n, "the next one as well");
+  }
+  fails_at = 0;
+  dgc_layer* L = evolve_layer();
+  L->d_etab = etab;
+  std::vector<int32_t> labels(80, 0);
+  auto backward = [&] { L->forward_done = L->m_saved = true; return dgc_layer_backward(L, tensor, 32, nullptr, 0, tensor, 32, nullptr, tensor, 32, nullptr); };
+  calls.clear();
+  expect(dgc_layer_set_labels(L, labels.data(), nullptr) == DGC_OK && count("fill neighbours") == 0, "no table before the first dX");
+  expect(backward() == DGC_OK && count("fill neighbours") == 1, "the first dX makes it");
+  const int2* const place = L->d_inside;
+  allocations = 0;
+  expect(dgc_layer_set_labels(L, labels.data(), nullptr) == DGC_OK && count("fill neighbours") == 2 && allocations == 0 && L->d_inside == place,
+         "other labels fill it where it is");
+  expect(backward() == DGC_OK && count("fill neighbours") == 2 && allocations == 0, "a backward does not");
+  L = evolve_layer();
+  L->d_etab = etab;
+  calls.clear();
+  expect(backward() == DGC_OK && !L->d_inside && count("fill neighbours") == 0, "no table without labels");
+  allocations = 0; fails_at = 5;             // (the labels take four)
+  expect(dgc_layer_set_labels(L, labels.data(), nullptr) == DGC_OK && !L->d_inside && L->lab.built, "labels need no table");
+  expect(backward() == DGC_OK && count("spmm") == 2, "nor does the gradient");
+  fails_at = 0;
+  expect(dgc_layer_set_labels(L, labels.data(), nullptr) == DGC_OK && L->d_inside && count("fill neighbours") == 1 && !null_pointer, "later ones make it");
 }
 
 // What an EvolveGCN-O layer keeps per snapshot beside the partial sums of the weight gradients: the weights and gates in double,
@@ -319,6 +371,7 @@ int main(int argc, char** argv) {
   const std::string check = argc > 1 ? argv[1] : "";
   if (check == "input gradient memory") input_gradient_memory();
   else if (check == "label memory") label_memory();
+  else if (check == "neighbour table") neighbour_table();
   else if (check == "stage events") stage_events();
   else if (check == "lds per device") lds_per_device();
   else if (check == "one stream") one_stream();

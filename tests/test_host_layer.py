@@ -19,7 +19,7 @@ def program(tmp_path_factory):
     return out
 
 
-@pytest.mark.parametrize("check", ["input gradient memory", "label memory", "stage events", "one stream", "lds per device", "evolve memory", "gradient read", "folded weights"])
+@pytest.mark.parametrize("check", ["input gradient memory", "label memory", "neighbour table", "stage events", "one stream", "lds per device", "evolve memory", "gradient read", "folded weights"])
 def test_host_layer(program, check):
     r = subprocess.run([program, check], capture_output=True, text=True, timeout=60)
     assert r.returncode == 0, r.stdout + r.stderr
