@@ -1073,13 +1073,10 @@ dgc_status_t dgc_layer_destroy(dgc_layer_t* L) {
 }
 
 // A weight in both forms that the split kernel reads.
-static hipError_t pack_split(const float* W, int32_t n_out, int32_t n_in, float longest_row, float4* packed) {
+static hipError_t pack_split(const float* W, int32_t n_out, int32_t n_in, float4* packed) {
   char* const word = reinterpret_cast<char*>(packed) + split_halves_bytes(n_out, n_in) - 64;
   const hipError_t e = hipMemset(word, 0, sizeof(int32_t));
-  if (e == hipSuccess) {
-    launch_pack_split(W, 0, n_in, 1, n_out, n_in, 1, packed, nullptr);
-    launch_halves_word(W, n_out, n_in, longest_row, packed, nullptr);
-  }
+  if (e == hipSuccess) launch_pack_split(W, 0, n_in, 1, n_out, n_in, 1, packed, nullptr);
   return e;
 }
 
@@ -1103,7 +1100,7 @@ static dgc_status_t refold(dgc_layer* L, const std::string& name) {
   DGC_HIP_TRY(hipMemset(f.bad, 0, sizeof(int32_t)));
   launch_fold(wih.raw + other, wih.n_in, wg.raw, L->params[names[1]].raw, L->params[names[3]].raw, wih.n_out, d.S, wg.n_in, f.W, f.bias,
               f.bad, nullptr);
-  DGC_HIP_TRY(pack_split(f.W, wih.n_out, wg.n_in, kLongestFolded, f.packed));
+  DGC_HIP_TRY(pack_split(f.W, wih.n_out, wg.n_in, f.packed));
   DGC_HIP_TRY(hipGetLastError());
   DGC_HIP_TRY(hipDeviceSynchronize());
   f.made = true;
@@ -1127,7 +1124,7 @@ dgc_status_t dgc_layer_set_param(dgc_layer_t* L, const char* name, const float* 
     DGC_HIP_TRY(hipDeviceSynchronize());
   } else if (p.packed) {
     if (p.narrow) launch_pack_narrow(p.raw, p.n_out, p.n_in, p.narrow, nullptr);
-    if (p.split) DGC_HIP_TRY(pack_split(p.raw, p.n_out, p.n_in, kLongestRow, p.packed));
+    if (p.split) DGC_HIP_TRY(pack_split(p.raw, p.n_out, p.n_in, p.packed));
     else launch_pack_weight(p.raw, p.n_out, p.n_in, p.packed, nullptr);
     DGC_HIP_TRY(hipDeviceSynchronize());
   }

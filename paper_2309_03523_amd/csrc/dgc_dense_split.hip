@@ -655,14 +655,20 @@ __global__ void k_pack_split(const float* W, int64_t per_w, int64_t so, int64_t 
   for (int p = 0; p < 2; ++p) half[(f << 6) * 2 + p * 64 + lane] = two[p];
 }
 
-// A wave a row: *word is set where a row of W is longer than `most`, or not finite.
-__global__ __launch_bounds__(256) void k_halves_word(const float* W, int32_t n_out, int32_t n_in, float most, int32_t* word) {
+// A wave a row: *word is set where a row of W is longer than kLongestRow, or not finite.  The error that inputs cut at 2^-31 make of a gate's
+// argument is 2^-32 times the length of the row that they are multiplied with, for a transform's times that of the gate's as well;
+// 1 - 2 / (1 + e^2x) is off by 3e-8.
+constexpr float kLongestRow = 8.f;
+__global__ __launch_bounds__(256) void k_halves_word(const float* W, int64_t so, int64_t si, int32_t n_out, int32_t n_in, int32_t* word) {
   const int row = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
   if (row >= n_out) return;
   float sum = 0.f;
-  for (int k = lane; k < n_in; k += 64) sum = fmaf(W[(int64_t)row * n_in + k], W[(int64_t)row * n_in + k], sum);
+  for (int k = lane; k < n_in; k += 64) {
+    const float w = W[row * so + k * si];
+    sum = fmaf(w, w, sum);
+  }
   for (int m = 1; m < 64; m <<= 1) sum += __shfl_xor(sum, m);
-  if (lane == 0 && !(sum <= most * most)) atomicOr(word, 1);
+  if (lane == 0 && !(sum <= kLongestRow * kLongestRow)) atomicOr(word, 1);
 }
 
 // out[r][k] = sum over s of wih[r][s] wg[s][k], bias[r] = bih[r] + sum over s of wih[r][s] bg[s], both summed in double.
@@ -810,11 +816,9 @@ void launch_pack_split(const float* W, int64_t per_w, int64_t out_stride, int64_
   if (total > 0)
     hipLaunchKernelGGL(k_pack_split, (unsigned)((total + 255) / 256), 256, 0, st, W, per_w, out_stride, in_stride, n_out, n_in,
                        count, p, per_w == 0 ? p + 3 * total : nullptr);
-}
-
-void launch_halves_word(const float* W, int32_t n_out, int32_t n_in, float most, void* packed, hipStream_t st) {
-  int32_t* const word = reinterpret_cast<int32_t*>(static_cast<char*>(packed) + split_halves_bytes(n_out, n_in) - 64);
-  hipLaunchKernelGGL(k_halves_word, (unsigned)((n_out + 3) / 4), 256, 0, st, W, n_out, n_in, most, word);
+  if (total > 0 && per_w == 0)
+    hipLaunchKernelGGL(k_halves_word, (unsigned)((n_out + 3) / 4), 256, 0, st, W, out_stride, in_stride, n_out, n_in,
+                       reinterpret_cast<int32_t*>(p + 5 * total));
 }
 
 }  // namespace dgc

@@ -16,7 +16,6 @@ constexpr int kWave = 64;
 constexpr int kTileRows = 64;      // rows of one tile of the workgroup-tile dense kernel
 constexpr int kWaveTileRows = 32;  // rows of one tile of the split dense kernels and the weight-gradient kernel
 
-// One (chunk, snapshot) pair of the fused batch.
 #if defined(__HIP_DEVICE_COMPILE__) || defined(__HIPCC__)
 // Global memory by name: a pointer chosen between a tensor and a constant would else be read by flat loads, which wait for the
 // LDS, too.
@@ -26,6 +25,7 @@ __device__ __forceinline__ gbyte* in_global(const void* p) { return (gbyte*)(uin
 __device__ __forceinline__ uintx4 load16(gbyte* p) { return *(const __attribute__((address_space(1))) uintx4*)p; }
 #endif
 
+// One (chunk, snapshot) pair of the fused batch.
 struct Segment {
   int64_t row_off;   // first packed row
   int64_t nnz_off;   // first packed non-zero
@@ -127,8 +127,8 @@ constexpr int64_t kMostBlocks = 1 << 23;
 constexpr int64_t kMostTeams = 1 << 23, kTeamsAtOnce = 2048;
 
 // ---- aggregation / gather (dgc_spmm.hip)
-// Spare entries after the last non-zero of the edge table: a lane group reads whole batches of 8
-// entries, up to 8 * (groups per wave) - 1 entries past the end of the row it works on.
+// Spare entries after the last non-zero of the edge table: a lane reads one entry even where its row, or its share of one, has none,
+// and that is at most the next one behind it.
 constexpr int64_t kEtabPad = 32;
 
 constexpr int kAggRows = 16;        // rows of an item of the edge-table kernels, at most
@@ -272,14 +272,9 @@ bool dense_fold_wanted(int32_t S, int32_t K0, int32_t time_kind);   // whether f
 void launch_fold(const float* wih, int64_t ld_wih, const float* wg, const float* bg, const float* bih, int32_t gH, int32_t S, int32_t K0,
                  float* out, float* bias, int32_t* bad, hipStream_t st);
 // `count` matrices, per_w floats apart, element (out, in) at out * out_stride + in * in_stride.  per_w = 0: one matrix, with the
-// half-precision parts (split_halves_bytes).
+// half-precision parts (split_halves_bytes; the word behind them is zero before).
 void launch_pack_split(const float* W, int64_t per_w, int64_t out_stride, int64_t in_stride, int32_t n_out, int32_t n_in,
                        int64_t count, void* packed, hipStream_t st);
-// The word behind the halves (zero before): set where they do not stand for the matrix, since a row of it is longer than `most` (at most
-// 15.9: halves end there).  The error that inputs cut at 2^-31 make of a gate's argument is 2^-32 times the length of the row that they
-// are multiplied with, for a transform's times that of the gate's as well; 1 - 2 / (1 + e^2x) is off by 3e-8.
-constexpr float kLongestRow = 8.f, kLongestFolded = 15.f;
-void launch_halves_word(const float* W, int32_t n_out, int32_t n_in, float most, void* packed, hipStream_t st);
 size_t dense_lds_bytes(int32_t K0, int32_t S, int32_t H);
 int dense_ld(int32_t K0, int32_t S, int32_t H);
 
