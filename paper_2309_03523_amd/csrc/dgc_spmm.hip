@@ -360,7 +360,8 @@ __global__ __launch_bounds__(256) void k_spmm_long_reduce(SpmmArgs a) {
 //   One row for the whole width of a wave and, where it is narrower, two or four of at most 16 non-zeros at a time took 2853 us where 64
 // columns a wave take 2660 (100 000 x 32 rows of 128 floats), 7151 and 6630 (62 500 x 64 of 256), 694 and 613 (30 001 x 24 of 128), 1200
 // and 1129 (40 000 x 32 of 172), 458 and 366 (20 000 x 8 of 300), 65 and 50 (12 345 x 10 of 50), 10.7 and 9.5 (1000 x 8 of 32).  32 columns
-// a wave are 2 to 4 % slower from 128 floats on (of a pitch of 704 bytes, where a line of 128 then lies across two, 11 %), 128 columns 2 to 12 %.
+// a wave are 2 to 4 % slower from 128 floats on (of a pitch of 704 bytes, where a line of 128 then lies across two, 11 %), 128 columns 2 to 12 %
+// (but see wide_slices).
 //   A slice of all rows after the other, so that an XCD's L2 holds more of it: 104 M lines pass the L2s instead of 134 M, but the
 // launches take 2974 and 9238 us, since a slice of a power-of-two pitch lies in a quarter or an eighth of an L2's channels.  Two batches
 // under way: 3.5 % slower.  Items of 8, 16, 24, 32 rows: 2770, 2660, 2657, 2670 and 372, 374, 399, 404 us.
