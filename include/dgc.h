@@ -78,11 +78,11 @@ enum { DGC_GATHER_IN_PLACE = 0, DGC_GATHER_STAGED = 1 };
  *  WAVE  the split kernels: 32 vertices per workgroup (16 for narrow layers of few tiles), fp32 products
  *        as sums of half-precision or bf16 products, for S = H in {32, 64, 128} (a transform alone: 256, too);
  *        DGC_ERR_UNSUPPORTED at forward otherwise.
- * The split time encoder takes a number as two half-precision parts: 22 to 24 bits of it, and nothing below 2^-31 of an input
+ * The split time encoder takes a number as two half-precision parts: 22 to 24 bits of it, and nothing below 2^-36 of an input
  * row or a state.  Outputs and states are nearer to double precision than with fp32 products and 1 - 2 / (1 + e^2x) while the
- * gates' arguments are up to 1.5 in the root mean square (at tiny inputs too, where that formula loses more), and up to 1.7 times as
- * far, some 3e-7 of their size, where they are larger.  Tiles with an input above 1023, and layers with a weight matrix that has a
- * row longer (2-norm) than 8, run on three bf16 parts, which hold every bit, in 1.2 to 1.3 times the time. */
+ * gates' arguments are up to 1.5 in the root mean square (at tiny inputs too, where that formula loses more), and up to 1.4 times as
+ * far, some 3e-7 of their size, where they are larger.  Tiles with an input of 32 and more, and layers with a weight matrix that has
+ * a row longer (2-norm) than 8, run on three bf16 parts, which hold every bit, in 1.2 to 1.3 times the time. */
 enum { DGC_DENSE_AUTO = 0, DGC_DENSE_TILE = 1, DGC_DENSE_WAVE = 2 };
 /* Which kernels aggregate in IN_PLACE mode (STAGED always takes WALK):
  *  TABLE  kernels that read a per-non-zero table built at create (8 bytes per stored non-zero: the column,

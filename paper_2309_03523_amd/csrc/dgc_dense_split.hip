@@ -12,18 +12,20 @@
 //
 // Time encoders: their sums go into sigmoid and tanh, which are at most 1 and off by a rounding of 1, so an error that is small
 // beside 1 does.  There a number is two half-precision numbers (halve8), and a product three MFMAs: hi*lo, lo*hi, hi*hi.  Two
-// halves hold 22 to 24 bits of a number, and nothing below 2^-31 of an input or a state (taken 64 times) and 2^-37 of a weight
+// halves hold 22 to 24 bits of a number, and nothing below 2^-36 of an input or a state (taken 2048 times) and 2^-37 of a weight
 // (4096 times); what is left out, lo*lo, is within 2^-22 of the product and of either sign.  tanh_of, whose series keeps what
 // 1 - 2 / (1 + e^2x) loses below 1/2, takes back more than that, as long as the sums are of the size of 1.
-// What is not: an input above 1023, a bias above 1e30, and weights whose rows are so long that the 2^-31 counts (kLongestRow): there
+// What is not: an input from 32 on, a bias above 1e30, and weights whose rows are longer than kLongestRow: there
 // the tile goes on from that step, which it does again, to its window's end (for weights from the first) on three bf16 parts: a whole forward
 // where all rows are 10 x 12 345, width 64, 85 -> 100 us, 32 x 100 000 of 128 5.0 -> 6.0 ms, MPNN-LSTM 5.3 -> 6.2, LSTM over labels 1.39 -> 1.73,
 // GRU 256 over 300 0.88 -> 1.13, all of them no slower than on six products with the plain formula; where one row in a thousand of the last
 // step is, nothing.
-// Distance from 64 bits in that of six bf16 products with the plain formula, GRU and LSTM 128 and 256 wide over inputs of N(0, 1) times x,
-// weights Xavier times w: x up to 1e-3 0.00 to 0.01 (without biases; with them 0.2 to 0.4), x = 1 0.3 to 1.0, 2 0.3 to 1.26, 5 0.5 to 1.43, 30 0.8
-// to 1.65, 300 1.05 to 1.7 (of 1.5 to 14e-7: 22 bits of 24, lo*lo, one sum for all); w = 4, x = 1 1.13 to 1.39 (of 2.5 to 4.6e-7).  The
-// small products apart or added by link take 0.1 to 0.2 off that and cost 1 to 10 %, lo*lo as well 0.1 and 5 %.
+// Distance from 64 bits in that of six bf16 products with the plain formula: 0.58 in the mean and 1.003 at most of 206 outputs of drawn
+// cases.  Over inputs of N(0, 1) times x and Xavier weights times w (GRU and LSTM 128 and 256 wide, one and two layers): x up to 1e-3 0.00 to 0.01
+// without biases (1e-10: 0.3 to 0.9) and 0.17 to 0.5 with them, x = 1 0.3 to 0.8, 2 0.3 to 1.03, 5 0.5 to 1.23, 12 0.6 to 1.3, from 30 on 0.7 to 1.0 (three
+// parts); w = 2, x = 1 0.7 to 1.14, 12 1.0 to 1.4, w = 4 0.9 to 1.03 (three parts).  Where it is above 1, by 22 bits instead of 24, lo*lo and the
+// small products that are not summed apart, it is 1.5 to 4e-7 of the outputs.  All small products apart or added by link would take 0.05 to 0.1 off that
+// and cost 1 to 10 %, lo*lo as well 0.1 and 5 %.  Inputs taken 64 times, up to 1023: 1.7 at x = 300, and 32 times as far at 1e-5 and below.
 // GRU 128 wide, 3.2 M rows: 3.5 -> 2.35 ms; the two LSTM layers of MPNN-LSTM over 1.28 M rows 2.78 + 1.99 -> 1.9 + 1.2.
 //
 // With the weights as A operand (lane l: A[l%32][8*(l/32) .. +7]) and 32 activation rows as B operand
@@ -59,7 +61,7 @@ using namespace split;
 constexpr int kUnitBytes = 3 * kFrag * 16; // a weight fragment's three parts
 template <int P> constexpr int kUnit = P * kFrag * 16;    // P parts
 
-constexpr float kActScale = 64.f, kWeightScale = 4096.f, kSumScale = kActScale * kWeightScale;
+constexpr float kActScale = 2048.f, kWeightScale = 4096.f, kSumScale = kActScale * kWeightScale;
 constexpr float kMostBias = 1e30f;
 
 // Of x scale: the gates' arguments come in the scale of their sums.
@@ -665,9 +667,9 @@ __global__ void k_pack_split(const float* W, int64_t per_w, int64_t so, int64_t 
   for (int p = 0; p < 2; ++p) half[(f << 6) * 2 + p * 64 + lane] = two[p];
 }
 
-// A wave a row: *word is set where a row of W is longer than kLongestRow, or not finite.  The error that inputs cut at 2^-31 make of a gate's
-// argument is 2^-32 times the length of the row that they are multiplied with, for a transform's times that of the gate's as well;
-// 1 - 2 / (1 + e^2x) is off by 3e-8.
+// A wave a row: *word is set where a row of W is longer than kLongestRow, or not finite.  The error that inputs cut at 2^-36 make of a gate's
+// argument is 2^-37 times the length of the row that they are multiplied with, for a transform's times that of the gate's as well; and
+// where rows are so long the gates' arguments are, too (above).
 constexpr float kLongestRow = 8.f;
 __global__ __launch_bounds__(256) void k_halves_word(const float* W, int64_t so, int64_t si, int32_t n_out, int32_t n_in, int32_t* word) {
   const int row = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
