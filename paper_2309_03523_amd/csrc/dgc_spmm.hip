@@ -705,6 +705,8 @@ void launch_agg_all(const SpmmArgs& a, hipStream_t st) {
 template <bool FILL>
 __global__ __launch_bounds__(kAggRows * kWave) void k_inside(SpmmArgs a, int64_t* eptr, int2* inside, int64_t first) {
   const int lane = threadIdx.x, r = uniform(threadIdx.y);
+  // (what a last row without neighbours reads: its weight is multiplied with zero)
+  if (FILL && first + blockIdx.x == 0 && r == 0 && lane == 0) inside[eptr[a.n_rows]] = make_int2(0, 0);
   const AggItem it = a.items[first + blockIdx.x];
   if (r >= it.n) return;
   const int64_t* rp = a.g.rowptr[it.t] + it.v0 + r;

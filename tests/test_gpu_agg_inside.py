@@ -316,3 +316,34 @@ def test_more_rows_than_a_launch_counts_neighbours_of():
         out.append(dX.double())
     assert bool(torch.isfinite(out[1]).all())
     assert float((out[0] - out[1]).norm() / out[0].norm()) < 1e-6
+
+
+@pytest.mark.parametrize("labelled_layer", [False, True])
+def test_last_row_without_a_neighbour_of_its_chunk(labelled_layer):
+    """Only a graph without the row's self-loop, which validate_level = 1 refuses, has one; nothing hands a gradient to it.  Its lanes read the
+    entry behind the table's last."""
+    import torch
+    from paper_2309_03523_amd import binding
+    N, F = 64, 32
+    i = torch.arange(N - 1, device="cuda")
+    rowptr = torch.arange(N + 1, device="cuda")
+    rowptr[1:] += 1                                               # vertex 0: itself and the last one
+    col = torch.cat([i[:1], i.new_tensor([N - 1]), i[1:], i[:1]]).to(torch.int32)
+    chunks = [(0, N, 0, 1)] if labelled_layer else [(0, N // 2, 0, 1), (N // 2, N, 0, 1)]
+    gen = torch.Generator(device="cuda").manual_seed(5)
+    X, target = (torch.randn((1, N, F), device="cuda", generator=gen) for _ in range(2))
+    layer = binding.DgcLayer([rowptr], [col], N, chunks, F=F, S=F, H=F, time_kind="none", struct_kind="evolve_gcn_o", act_out="relu",
+                             validate_level=0)
+    layer.set_params(synth.evolve_params(5, F, F, random_bias=True))
+    if labelled_layer:
+        layer.set_labels((torch.arange(N, device="cuda") >= N // 2).to(torch.int32))
+    Y, dX = torch.zeros((1, N, F), device="cuda"), torch.full((1, N, F), float("nan"), device="cuda")
+    left = [torch.full((k,), float("nan"), device="cuda") for k in (1 << 12, 1 << 16, 1 << 19)]      # for the layer's workspace to find
+    torch.cuda.synchronize()
+    del left
+    torch.cuda.empty_cache()
+    layer.forward(X, X, Y)
+    layer.backward(Y, target=target, dX=dX)
+    torch.cuda.synchronize()
+    assert bool(torch.isfinite(dX).all()) and bool((dX[0, N - 1] == 0).all()) and bool((dX[0, N - 2] != 0).any())
+    layer.destroy()
